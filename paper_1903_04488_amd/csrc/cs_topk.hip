@@ -4,19 +4,30 @@
 // Exact radix select on the 31-bit magnitude key  bits(est) & 0x7fffffff  (monotone in |est|
 // for IEEE binary32): three histograms (11 + 10 + 10 bits) find the key theta of the
 // k-th largest magnitude and how many entries equal to theta are still needed; an ordered
-// compaction (per-block counts, scan over blocks, write) then emits, in ascending index
-// order, every index with key > theta plus the lowest-index entries with key == theta.
-// Everything is integer work, so the result is a deterministic function of est.
+// compaction then emits, in ascending index order, every index with key > theta plus the
+// lowest-index entries with key == theta.  Everything is integer work, so the result is a
+// deterministic function of est.
 //
-// Passes over est.  Done plainly that is five reads of est (three histograms, count, write).
-// After the first histogram the bin of the k-th largest key is known, and only entries in that
-// bin or above can be selected: with k << d they are a small multiple of k.  One pass copies
-// them, block by block in index order, into a candidate list (k_topk_compact), and the two
-// remaining histograms, the count and the write run over that list only: two reads of est
-// (one when the caller brings the first histogram, which the estimate kernel can fill as it
-// writes est).  The list has a fixed capacity; if the input does not fit it (many equal
-// magnitudes, k close to d) a flag is raised on the device and the five-pass form, whose
-// kernels are enqueued behind and return at once otherwise, does the work instead.
+// Launches.  A launch costs about 4.7 us on this machine however little it does, and a selection
+// written as one kernel per pass (clear, histogram, find, compact, ..., count, scan, write) spent
+// 50 of its 70 us on them.  There are three now:
+//   k_topk_hist0     the first histogram, when the caller does not bring it (the estimate kernel
+//                    can fill it as it writes est);
+//   k_topk_compact   every workgroup finds the bin of the k-th largest key in that histogram; only
+//                    entries in that bin or above can be selected, and with k << d they are a
+//                    small multiple of k: they are copied, block by block in index order, into a
+//                    candidate list.  The one full read of est;
+//   k_topk_finish    the two remaining histograms, the count and the ordered write over the list.
+// A selection from at most kSmall entries is one launch of one workgroup that holds every key in
+// LDS (k_topk_small).
+//
+// k_topk_finish does the same with the candidates when there are at most kSmall of them: its
+// first workgroup does everything, the others return.  Longer lists, and inputs that do not fit
+// the list (many equal magnitudes, k close to d: decided on the device), are shared out among
+// the workgroups: the work is cut into 4 phases of T tasks, T workgroups draw tasks in order
+// from a counter, and before it starts a task it waits until every task of the phase before is
+// done.  Those were drawn earlier, by workgroups that are running and themselves wait for earlier
+// tasks only, so every wait ends whatever part of the grid is resident.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,29 +39,37 @@
 
 namespace cs {
 
-constexpr int kBins = 2048;           // bins of the widest pass
-constexpr int kItems = 4;             // consecutive elements per thread in a tile
-constexpr int kTile = kBlock * kItems;
-constexpr int kMaxSelBlocks = 4096;   // blocks of the count / write passes
+constexpr int kBins = 2048;           // bins of the first histogram
+constexpr int kItems = 4;             // consecutive elements per thread and load
+constexpr int kSelBlock = 1024;       // threads of the workgroups that select
+constexpr int kSelWaves = kSelBlock / 64;
+constexpr int kKeep = 32;             // keys per thread that a single-workgroup selection keeps in LDS (128 KB)
+constexpr int64_t kSmall = static_cast<int64_t>(kSelBlock) * kKeep;
+// Workgroups that read est in one pass.  512 of 512 threads keep 32 KB of reads in flight on every
+// CU; more of them only add to the atomic adds on one address at their end (12 ns each, one
+// after the other: with 3200 workgroups those were 38 of the compaction's 39 us at d = 6.5 M).
+constexpr int kScanBlock = 512;
+constexpr int kScanWaves = kScanBlock / 64;
+constexpr int kMaxSegs = 512;
+constexpr int kStage = 8192;          // candidates one block can hold in LDS for its chunk
+constexpr int kFinishBlocks = 256;
 
-struct TopkSel {
-    uint32_t prefix;      // key bits fixed so far (after pass n: the top 11, 21, 31 bits)
-    uint32_t pad;
-    uint64_t k_rem;       // how many of the entries sharing `prefix` are still wanted
-};
-
-constexpr int kStage = 4096;          // candidates one block can hold in LDS for its chunk
-
-// workspace layout (all 8-byte aligned); the candidate list follows the struct
+// workspace layout (all 8-byte aligned); the candidate list follows the struct.  `hist[1..2]` and
+// everything from `ticket` to `heavy` are zero when a selection starts and are left zero when it ends.
 struct TopkWs {
     uint64_t hist[3][kBins];
-    TopkSel sel;
+    uint32_t prefix;                // bin of the k-th largest key in the first histogram
     uint32_t failed;                // != 0: the candidate list could not be built, est is read instead
+    uint64_t k_rem;                 // how many entries of that bin are wanted
+    uint32_t ticket;                // next task to draw
+    uint32_t exits;                 // workgroups that are through
+    uint32_t done[4];               // finished tasks per phase
     uint32_t ncand;                 // candidates appended so far
-    uint64_t gt[kMaxSelBlocks];     // per block: entries with key > theta  -> exclusive scan
-    uint64_t eq[kMaxSelBlocks];     // per block: entries with key == theta -> exclusive scan
-    uint32_t seg_base[kMaxSelBlocks];    // block b's candidates are cand[seg_base[b] .. + seg_count[b])
-    uint32_t seg_count[kMaxSelBlocks];
+    uint32_t heavy;                 // selected entries that passed the threshold (KeyHeavymix)
+    uint64_t gt[kMaxSegs];          // per segment (or task): entries with key > theta
+    uint64_t eq[kMaxSegs];          // per segment (or task): entries with key == theta
+    uint32_t seg_base[kMaxSegs];    // block b's candidates are cand[seg_base[b] .. + seg_count[b])
+    uint32_t seg_count[kMaxSegs];
 };
 constexpr size_t kCandBytes = sizeof(int64_t) + sizeof(float);   // index and value of a candidate
 
@@ -58,7 +77,7 @@ constexpr size_t kCandBytes = sizeof(int64_t) + sizeof(float);   // index and va
 // few per cent of d (the P k candidates of Alg. 3 with P in the tens) the list is sized more
 // tightly: the entries of the k-th largest key's bin and above are k plus that bin's own
 // population, at most a few tenths of k for magnitudes that fall off smoothly (a bin is an
-// eighth of a binade wide); should they not fit, the five-pass form takes over on the device.
+// eighth of a binade wide); should they not fit, est itself is read again on the device.
 __host__ inline int64_t candidate_capacity_for(int64_t d, int64_t k) {
     const int64_t roomy = 8 * k + 65536;
     if (roomy <= d / 4) return roomy;
@@ -100,174 +119,69 @@ struct KeyHeavymix {
     }
 };
 
-__global__ void __launch_bounds__(kBlock) k_topk_clear(TopkWs* ws, uint64_t k) {
+__global__ void __launch_bounds__(kBlock) k_topk_clear(TopkWs* ws) {
     for (int t = threadIdx.x; t < 3 * kBins; t += kBlock) (&ws->hist[0][0])[t] = 0;
     if (threadIdx.x == 0) {
-        ws->sel.prefix = 0;
-        ws->sel.pad = 0;
-        ws->sel.k_rem = k;
+        ws->ticket = 0;
+        ws->exits = 0;
+        for (int q = 0; q < 4; ++q) ws->done[q] = 0;
         ws->failed = 0;
         ws->ncand = 0;
+        ws->heavy = 0;
     }
 }
 
-// The histogram, count and write kernels below exist once and work either on the candidate
-// list or on est itself: `listed` says that a list was asked for, and ws->failed, which the
-// compaction sets on the device, that it could not be built -- then the same launches fall
-// back to reading est (the five-pass form), without the host having to know.
-__device__ __forceinline__ bool use_list(const TopkWs* ws, bool listed) {
-    return listed && ws->failed == 0;
-}
-
-// PASS 0: bin = key >> 20 (2048 bins); PASS 1: entries with key >> 20 == prefix, bin = bits
-// 19..10; PASS 2: entries with key >> 10 == prefix, bin = bits 9..0.
-template <int PASS, bool VEC, typename KEY>
-__global__ void __launch_bounds__(kBlock)
-k_topk_hist(const float* __restrict__ est, int64_t d, TopkWs* ws, uint64_t* __restrict__ hist_out,
-            bool listed, const int64_t* __restrict__ cand_idx, const float* __restrict__ cand_val,
-            KEY kf) {
-    kf.init();
-    // Magnitudes crowd into a few of the pass-0 bins (same exponent), and lanes that hit the same
-    // LDS word are served one after the other: pass 0 keeps kCopies histograms and lane l adds
-    // into copy l mod kCopies.
-    constexpr int kCopies = (PASS == 0) ? 4 : 1;
-    constexpr int nb = (PASS == 0) ? 2048 : 1024;
-    __shared__ uint32_t lh_all[kCopies][nb];
-    const bool from_list = PASS > 0 && use_list(ws, listed);
-    constexpr unsigned kListBlocks = 128;           // the list is short: a few blocks are plenty
-    if (from_list && blockIdx.x >= kListBlocks) return;
-    for (int t = threadIdx.x; t < kCopies * nb; t += kBlock) (&lh_all[0][0])[t] = 0;
-    __syncthreads();
-    uint32_t* lh = lh_all[threadIdx.x % kCopies];
-    const uint32_t prefix = PASS > 0 ? ws->sel.prefix : 0u;
-    auto tally = [&](uint32_t key) {
-        if (PASS == 0) {
-            atomicAdd(&lh[key >> 20], 1u);
-        } else if (PASS == 1) {
-            if ((key >> 20) == prefix) atomicAdd(&lh[(key >> 10) & 1023u], 1u);
-        } else {
-            if ((key >> 10) == prefix) atomicAdd(&lh[key & 1023u], 1u);
-        }
-    };
-    if (from_list) {
-        const uint32_t n = ws->ncand;
-        const unsigned blocks = gridDim.x < kListBlocks ? gridDim.x : kListBlocks;
-        for (uint32_t t = blockIdx.x * kBlock + threadIdx.x; t < n; t += blocks * kBlock)
-            tally(kf(cand_val[t], cand_idx[t]));
-    } else {
-        const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-        const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-        int64_t done = 0;
-        if (VEC) {                                   // est is 16-byte aligned: four elements per load
-            const int64_t n4 = d / 4;
-            const float4* est4 = reinterpret_cast<const float4*>(est);
-            int64_t t = t0;
-            for (; t + stride < n4; t += 2 * stride) {   // two loads in flight
-                const float4 u = est4[t], w = est4[t + stride];
-                tally(kf(u.x, 4 * t)); tally(kf(u.y, 4 * t + 1)); tally(kf(u.z, 4 * t + 2)); tally(kf(u.w, 4 * t + 3));
-                const int64_t t2 = t + stride;
-                tally(kf(w.x, 4 * t2)); tally(kf(w.y, 4 * t2 + 1)); tally(kf(w.z, 4 * t2 + 2)); tally(kf(w.w, 4 * t2 + 3));
-            }
-            if (t < n4) {
-                const float4 u = est4[t];
-                tally(kf(u.x, 4 * t)); tally(kf(u.y, 4 * t + 1)); tally(kf(u.z, 4 * t + 2)); tally(kf(u.w, 4 * t + 3));
-            }
-            done = n4 * 4;
-        }
-        for (int64_t t = done + t0; t < d; t += stride) tally(kf(est[t], t));
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < nb; t += kBlock) {
-        uint32_t v = 0;
-#pragma unroll
-        for (int q = 0; q < kCopies; ++q) v += lh_all[q][t];
-        if (v) atomicAdd(reinterpret_cast<unsigned long long*>(&hist_out[t]),
-                         static_cast<unsigned long long>(v));
-    }
-}
-
-// One workgroup: walk the histogram of this pass from the top bin down to the bin that holds
-// the k_rem-th largest entry; append that bin to the prefix, and drop from k_rem the entries
-// in higher bins (they are all selected).
-// Sum of v over the threads before this one in the workgroup (shuffles within a wavefront, one
-// LDS word per wavefront); *total receives the sum over all threads.
-__device__ __forceinline__ uint64_t block_exclusive_sum64(uint64_t v, uint64_t* lds, uint64_t* total) {
+// Sum of v over the threads before this one in a workgroup of WAVES wavefronts; *total receives
+// the sum over all threads.  `lds` holds one word per wavefront; the workgroup is in step on return.
+template <int WAVES, typename T>
+__device__ __forceinline__ T block_exclusive_sum(T v, T* lds, T* total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint64_t inc = v;
+    T inc = v;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-        const uint64_t up = __shfl_up(inc, off, 64);
+        const T up = __shfl_up(inc, off, 64);
         if (lane >= off) inc += up;
     }
     if (lane == 63) lds[wave] = inc;
     __syncthreads();
-    uint64_t before = 0, all = 0;
+    T before = 0, all = 0;
 #pragma unroll
-    for (int wv = 0; wv < kBlock / 64; ++wv) {
-        const uint64_t s = lds[wv];
+    for (int wv = 0; wv < WAVES; ++wv) {
+        const T s = lds[wv];
         if (wv < wave) before += s;
         all += s;
     }
+    __syncthreads();
     *total = all;
     return before + inc - v;
 }
 
-// h: the histogram of this pass (for PASS 0 possibly one the caller brought)
-template <int PASS>
-__global__ void __launch_bounds__(kBlock) k_topk_find(TopkWs* ws, const uint64_t* __restrict__ h) {
-    constexpr int nb = (PASS == 0) ? 2048 : 1024;
-    constexpr int per = nb / kBlock;              // bins per thread: 8 or 4
-    __shared__ uint64_t wave_sum[kBlock / 64];
-    const uint64_t k_rem = ws->sel.k_rem;
-    const uint32_t prefix = ws->sel.prefix;
+// The bin of a histogram (PER consecutive bins per thread, cnt[] of mine) that holds the k_rem-th
+// entry counted from the top; *rem = how many of that bin's entries are wanted.  All threads of the
+// workgroup get the answer through `found`.
+template <int WAVES, int PER>
+__device__ __forceinline__ void find_bin(const uint64_t (&cnt)[PER], uint64_t k_rem, uint64_t* lds,
+                                         uint64_t* found, uint32_t* bin, uint64_t* rem) {
     uint64_t mine = 0;
-    for (int q = 0; q < per; ++q) mine += h[threadIdx.x * per + q];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) mine += cnt[q];
     uint64_t all;
-    const uint64_t below = block_exclusive_sum64(mine, wave_sum, &all);
-    const uint64_t above = all - below - mine;     // entries in bins above my segment
-    if (above < k_rem && k_rem <= above + mine) {  // true for exactly one thread
-        uint64_t acc = above;
-        for (int q = per - 1; q >= 0; --q) {
-            const int bin = threadIdx.x * per + q;
-            const uint64_t cnt = h[bin];
-            if (k_rem <= acc + cnt) {
-                constexpr int bits = (PASS == 0) ? 11 : 10;
-                ws->sel.prefix = (PASS == 0) ? static_cast<uint32_t>(bin)
-                                             : ((prefix << bits) | static_cast<uint32_t>(bin));
-                ws->sel.k_rem = k_rem - acc;
-                break;
+    const uint64_t below = block_exclusive_sum<WAVES>(mine, lds, &all);
+    uint64_t acc = all - below - mine;             // entries in bins above my segment
+    if (acc < k_rem && k_rem <= acc + mine) {      // true for exactly one thread
+#pragma unroll
+        for (int q = PER - 1; q >= 0; --q) {
+            if (acc < k_rem && k_rem <= acc + cnt[q]) {
+                found[0] = static_cast<uint64_t>(threadIdx.x) * PER + q;
+                found[1] = k_rem - acc;
             }
-            acc += cnt;
+            acc += cnt[q];
         }
     }
-}
-
-// flags of one element against theta, packed: low 16 bits count "greater", high 16 "equal"
-__device__ __forceinline__ uint32_t classify(uint32_t key, uint32_t theta) {
-    return (key > theta ? 1u : 0u) | (key == theta ? 0x10000u : 0u);
-}
-
-// inclusive scan of a packed counter over the workgroup; returns the inclusive value and
-// writes the workgroup total to *total.  `lds` holds one word per wavefront.
-__device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t v, uint32_t* lds, uint32_t* total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t up = __shfl_up(v, off, 64);
-        if (lane >= off) v += up;
-    }
-    if (lane == 63) lds[wave] = v;
     __syncthreads();
-    uint32_t before = 0, all = 0;
-#pragma unroll
-    for (int wv = 0; wv < kBlock / 64; ++wv) {
-        const uint32_t s = lds[wv];
-        if (wv < wave) before += s;
-        all += s;
-    }
+    *bin = static_cast<uint32_t>(found[0]);
+    *rem = found[1];
     __syncthreads();
-    *total = all;
-    return v + before;
 }
 
 template <bool VEC>
@@ -287,32 +201,78 @@ __device__ __forceinline__ void load_items(const float* __restrict__ est, int64_
     }
 }
 
-// The candidate list.  Block b scans its chunk of est (the chunks of the count / write passes)
-// and keeps, in index order, every entry whose key lies in the bin of the k-th largest key or
-// above (sel.prefix after the first histogram).  Each wavefront takes a consecutive quarter of
-// the chunk, 256 entries at a time, and stages its candidates in its own part of LDS (their
-// places come from wavefront ballots, no barrier inside the loop); the block then appends
-// them to the list as one segment, whose place comes from a single atomic add.  Segments lie
-// in the list in the order the blocks finished; (seg_base[b], seg_count[b]) lets the later
-// kernels visit them in block order, i.e. in index order.  A wavefront with more than
-// kStage / 4 candidates, or a list that would exceed `cap`, raises ws->failed.
+// First histogram: hist_out[key >> 20] += 1 over est (2048 bins).  Magnitudes crowd into a few bins
+// (same exponent), and lanes that hit the same LDS word are served one after the other: a
+// workgroup keeps kCopies histograms and lane l adds into copy l mod kCopies.
 template <bool VEC, typename KEY>
-__global__ void __launch_bounds__(kBlock)
-k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* ws, uint32_t cap,
+__global__ void __launch_bounds__(kScanBlock)
+k_topk_hist0(const float* __restrict__ est, int64_t d, uint64_t* __restrict__ hist_out, KEY kf) {
+    kf.init();
+    constexpr int kCopies = 4;
+    __shared__ uint32_t lh_all[kCopies][kBins];
+    for (int t = threadIdx.x; t < kCopies * kBins; t += kScanBlock) (&lh_all[0][0])[t] = 0;
+    __syncthreads();
+    uint32_t* lh = lh_all[threadIdx.x % kCopies];
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kScanBlock;
+    for (int64_t t = static_cast<int64_t>(blockIdx.x) * kScanBlock + threadIdx.x; t * kItems < d; t += 2 * stride) {
+        float v[2][kItems];
+        int n[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) load_items<VEC>(est, (t + u * stride) * kItems, d, v[u], n[u]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int q = 0; q < kItems; ++q)
+                if (q < n[u]) atomicAdd(&lh[kf(v[u][q], (t + u * stride) * kItems + q) >> 20], 1u);
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < kBins; t += kScanBlock) {
+        uint32_t v = 0;
+#pragma unroll
+        for (int q = 0; q < kCopies; ++q) v += lh_all[q][t];
+        if (v) atomicAdd(reinterpret_cast<unsigned long long*>(&hist_out[t]),
+                         static_cast<unsigned long long>(v));
+    }
+}
+
+// The candidate list.  Block b scans its chunk of est and keeps, in index order, every entry whose
+// key lies in the bin of the k-th largest key or above.  Each wavefront takes a consecutive part of
+// the chunk, 1024 entries at a time (four loads in flight), and stages its candidates in its own
+// part of LDS (their places come from wavefront ballots, no barrier inside the loop); the block
+// then appends them to the list as one segment, whose place comes from a single atomic add.
+// Segments lie in the list in the order the blocks finished; (seg_base[b], seg_count[b]) lets
+// k_topk_finish put them in block order, i.e. in index order.  A wavefront with more than
+// kStage / 8 candidates, or a list that would exceed `cap`, raises ws->failed.
+template <bool VEC, typename KEY>
+__global__ void __launch_bounds__(kScanBlock)
+k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* ws,
+               const uint64_t* __restrict__ hist0, uint64_t k, uint32_t cap,
                int64_t* __restrict__ cand_idx, float* __restrict__ cand_val, KEY kf) {
     kf.init();
-    constexpr int kWaves = kBlock / 64;
-    constexpr int kWaveStage = kStage / kWaves;
+    constexpr int kWaveStage = kStage / kScanWaves;
     constexpr int kWaveTile = 64 * kItems;
+    constexpr int kTiles = 4;
     __shared__ uint32_t st_off[kStage];
     __shared__ float st_val[kStage];
-    __shared__ uint32_t wave_n[kWaves];
+    __shared__ uint64_t scan[kScanWaves], found[2];
+    __shared__ uint32_t wave_n[kScanWaves];
     __shared__ uint32_t seg[2];                     // base, ok
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t bin0 = ws->sel.prefix;
+    uint32_t bin0;
+    {
+        constexpr int per = kBins / kScanBlock;
+        uint64_t cnt[per], rem;
+#pragma unroll
+        for (int q = 0; q < per; ++q) cnt[q] = hist0[threadIdx.x * per + q];
+        find_bin<kScanWaves, per>(cnt, k, scan, found, &bin0, &rem);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            ws->prefix = bin0;
+            ws->k_rem = rem;
+        }
+    }
     const int64_t lo = static_cast<int64_t>(blockIdx.x) * chunk;
     const int64_t hi = (lo + chunk < d) ? lo + chunk : d;
-    const int64_t part = (chunk / kWaves + kWaveTile - 1) / kWaveTile * kWaveTile;
+    const int64_t part = (chunk / kScanWaves + kWaveTile - 1) / kWaveTile * kWaveTile;
     const int64_t wlo = lo + wave * part;
     const int64_t whi = (wlo + part < hi) ? wlo + part : hi;
     uint32_t* my_off = st_off + wave * kWaveStage;
@@ -322,15 +282,20 @@ k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* 
     bool overflow = false;
     auto take = [&](const float (&v)[kItems], int nvalid, int64_t base) {
         bool f[kItems];
-        uint32_t before = 0, total = 0;
+        bool any = false;
 #pragma unroll
         for (int q = 0; q < kItems; ++q) {
             f[q] = q < nvalid && (kf(v[q], base + q) >> 20) >= bin0;
+            any |= f[q];
+        }
+        if (__builtin_amdgcn_ballot_w64(any) == 0) return;
+        uint32_t before = 0, total = 0;
+#pragma unroll
+        for (int q = 0; q < kItems; ++q) {
             const uint64_t m = __builtin_amdgcn_ballot_w64(f[q]);
             before += __builtin_popcountll(m & below);
             total += __builtin_popcountll(m);
         }
-        if (total == 0) return;
         if (staged + total > static_cast<uint32_t>(kWaveStage)) { overflow = true; return; }
         uint32_t pos = staged + before;
 #pragma unroll
@@ -342,21 +307,22 @@ k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* 
             }
         staged += total;
     };
-    for (int64_t tile = wlo; tile < whi && !overflow; tile += 2 * kWaveTile) {   // two loads in flight
-        float v0[kItems], v1[kItems];
-        int n0, n1 = 0;
-        const int64_t b0 = tile + static_cast<int64_t>(lane) * kItems, b1 = b0 + kWaveTile;
-        load_items<VEC>(est, b0, whi, v0, n0);
-        if (tile + kWaveTile < whi) load_items<VEC>(est, b1, whi, v1, n1);
-        take(v0, n0, b0);
-        if (tile + kWaveTile < whi && !overflow) take(v1, n1, b1);
+    for (int64_t tile = wlo; tile < whi && !overflow; tile += kTiles * kWaveTile) {
+        float v[kTiles][kItems];
+        int n[kTiles];
+        const int64_t b0 = tile + static_cast<int64_t>(lane) * kItems;
+#pragma unroll
+        for (int u = 0; u < kTiles; ++u) load_items<VEC>(est, b0 + u * kWaveTile, whi, v[u], n[u]);
+#pragma unroll
+        for (int u = 0; u < kTiles; ++u)
+            if (!overflow) take(v[u], n[u], b0 + u * kWaveTile);
     }
     if (lane == 0) wave_n[wave] = overflow ? 0xffffffffu : staged;
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t total = 0;
         bool ok = true;
-        for (int w = 0; w < kWaves; ++w) {
+        for (int w = 0; w < kScanWaves; ++w) {
             if (wave_n[w] == 0xffffffffu) ok = false;
             else total += wave_n[w];
         }
@@ -381,176 +347,418 @@ k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* 
     }
 }
 
-// per block: how many entries of its chunk (or of its segment of the list) are above / equal
-// to theta
-template <bool VEC, typename KEY>
-__global__ void __launch_bounds__(kBlock)
-k_topk_count(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* ws, int nblocks,
-             bool listed, const int64_t* __restrict__ cand_idx, const float* __restrict__ cand_val,
-             KEY kf) {
-    kf.init();
-    const uint32_t theta = ws->sel.prefix;
-    if (use_list(ws, listed)) {                     // one wavefront per segment
-        const int b = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-        if (b >= nblocks) return;
-        const int lane = threadIdx.x & 63;
-        const uint32_t base = ws->seg_base[b], n = ws->seg_count[b];
-        uint32_t n_gt = 0, n_eq = 0;
-        for (uint32_t t = lane; t < n; t += 64) {
-            const uint32_t key = kf(cand_val[base + t], cand_idx[base + t]);
-            n_gt += key > theta ? 1u : 0u;
-            n_eq += key == theta ? 1u : 0u;
+// where a selection goes
+struct SelOut {
+    int64_t* idx;                   // k indices, ascending
+    float* val;                     // their values, or null
+    const int64_t* remap;           // null, or: idx[slot] = remap[i] instead of i
+    unsigned long long* n_heavy;    // null, or: how many of the selected keys have bit 30 set
+    int64_t k;
+    __device__ __forceinline__ void put(uint64_t slot, int64_t i, float v) const {
+        if (slot >= static_cast<uint64_t>(k)) return;
+        idx[slot] = remap ? remap[i] : i;
+        if (val) val[slot] = v;
+    }
+};
+
+// LDS of a selection by one workgroup (of the 160 KB that a CU has)
+struct SmallLds {
+    uint32_t key[kSmall];
+    uint32_t hist[kBins];
+    uint64_t mask_gt[kKeep * kSelWaves], mask_eq[kKeep * kSelWaves];   // flags of 64 items each, in memory order
+    uint64_t before[kKeep * kSelWaves];       // flags set before those 64 (low word: gt, high word: eq)
+    uint64_t seg[kMaxSegs];                   // (selected before segment b) - (flags before its first item)
+    uint64_t scan[kSelWaves], found[2];
+    uint32_t heavy;
+};
+
+// Selection among n <= kSmall items by one workgroup of kSelBlock threads that keeps their keys in
+// LDS: the remaining histograms in LDS, then one ballot per 64 items and kind (greater than
+// theta, equal to it) from which the number of flags before any item can be read, so that an
+// item's slot needs no second pass.  Items come in `nseg` segments, contiguous in memory but in any
+// order; segment b precedes segment b + 1 in index order and holds the indices of
+// [b seg_len, (b + 1) seg_len).  DIRECT: the items are est itself (index = position, one segment)
+// and the first histogram is taken here as well.
+template <bool DIRECT, typename KEY>
+__device__ __forceinline__ void select_in_workgroup(SmallLds& s, const float* __restrict__ val,
+                                                    const int64_t* __restrict__ idx, uint32_t n,
+                                                    uint32_t bin0, uint64_t k_rem,
+                                                    const uint32_t* __restrict__ seg_base,
+                                                    const uint32_t* __restrict__ seg_count, int nseg,
+                                                    uint32_t seg_tiles, const SelOut& out, const KEY& kf) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll 8
+    for (uint32_t p = tid; p < n; p += kSelBlock) s.key[p] = kf(val[p], DIRECT ? static_cast<int64_t>(p) : idx[p]);
+    // (a thread reads back only keys that it wrote itself)
+    if constexpr (DIRECT) {
+        for (int t = tid; t < kBins; t += kSelBlock) s.hist[t] = 0;
+        __syncthreads();
+#pragma unroll 4
+        for (uint32_t p = tid; p < n; p += kSelBlock) atomicAdd(&s.hist[s.key[p] >> 20], 1u);
+        __syncthreads();
+        const uint64_t cnt[2] = {s.hist[2 * tid], s.hist[2 * tid + 1]};
+        find_bin<kSelWaves, 2>(cnt, k_rem, s.scan, s.found, &bin0, &k_rem);
+    }
+    uint32_t theta = bin0;
+#pragma unroll
+    for (int pass = 1; pass <= 2; ++pass) {         // bits 19..10, then 9..0
+        const int shift = pass == 1 ? 10 : 0;
+        s.hist[tid] = 0;
+        __syncthreads();
+#pragma unroll 4
+        for (uint32_t p = tid; p < n; p += kSelBlock) {
+            const uint32_t key = s.key[p];
+            if ((key >> (shift + 10)) == theta) atomicAdd(&s.hist[(key >> shift) & 1023u], 1u);
+        }
+        __syncthreads();
+        const uint64_t cnt[1] = {s.hist[tid]};
+        uint32_t bin;
+        find_bin<kSelWaves, 1>(cnt, k_rem, s.scan, s.found, &bin, &k_rem);
+        theta = (theta << 10) | bin;
+    }
+    const uint64_t need_eq = k_rem;
+    const int groups = static_cast<int>((n + 63) / 64);       // of 64 items
+    for (int t = wave; t < groups; t += kSelWaves) {
+        const uint32_t p = t * 64 + lane;
+        const bool in = p < n;
+        const uint32_t key = in ? s.key[p] : 0u;
+        const uint64_t g = __builtin_amdgcn_ballot_w64(in && key > theta);
+        const uint64_t e = __builtin_amdgcn_ballot_w64(in && key == theta);
+        if (lane == 0) {
+            s.mask_gt[t] = g;
+            s.mask_eq[t] = e;
+        }
+    }
+    if (tid == 0) s.heavy = 0;
+    __syncthreads();
+    auto counts = [&](int t) -> uint64_t {          // low word: gt, high word: eq
+        return static_cast<uint64_t>(__builtin_popcountll(s.mask_gt[t])) |
+               (static_cast<uint64_t>(__builtin_popcountll(s.mask_eq[t])) << 32);
+    };
+    uint64_t all;
+    {
+        static_assert(kKeep * kSelWaves <= kSelBlock && kMaxSegs <= kKeep * kSelWaves, "one group of 64 items per thread");
+        const uint64_t mine = tid < groups ? counts(tid) : 0;
+        const uint64_t b = block_exclusive_sum<kSelWaves>(mine, s.scan, &all);
+        if (tid < groups) s.before[tid] = b;
+    }
+    __syncthreads();
+    auto flags_before = [&](uint32_t p) -> uint64_t {   // of items [0, p)
+        const uint32_t t = p >> 6, r = p & 63u;
+        if (static_cast<int>(t) >= groups) return all;
+        const uint64_t low = r ? (~0ull >> (64 - r)) : 0ull;
+        return s.before[t] + (static_cast<uint64_t>(__builtin_popcountll(s.mask_gt[t] & low)) |
+                              (static_cast<uint64_t>(__builtin_popcountll(s.mask_eq[t] & low)) << 32));
+    };
+    if constexpr (!DIRECT) {                        // two 32-bit counters side by side, modulo 2^32 each
+        uint32_t base = 0, cnt = 0;
+        if (tid < nseg) { base = seg_base[tid]; cnt = seg_count[tid]; }
+        const uint64_t f0 = cnt ? flags_before(base) : 0, f1 = cnt ? flags_before(base + cnt) : 0;
+        const uint64_t b = block_exclusive_sum<kSelWaves>(f1 - f0, s.scan, &all);
+        if (tid < nseg)
+            s.seg[tid] = static_cast<uint32_t>(static_cast<uint32_t>(b) - static_cast<uint32_t>(f0)) |
+                         (static_cast<uint64_t>(static_cast<uint32_t>(b >> 32) - static_cast<uint32_t>(f0 >> 32)) << 32);
+        __syncthreads();
+    }
+    uint32_t heavy = 0;
+    constexpr int kAhead = 4;                       // items of a thread whose index and value are on their way
+    for (uint32_t p0 = tid; p0 < n; p0 += kAhead * kSelBlock) {
+        int64_t at[kAhead];
+        float x[kAhead];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const uint32_t p = p0 + q * kSelBlock < n ? p0 + q * kSelBlock : p0;
+            at[q] = DIRECT ? static_cast<int64_t>(p) : idx[p];
+            x[q] = val[p];
         }
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            n_gt += __shfl_down(n_gt, off, 64);
-            n_eq += __shfl_down(n_eq, off, 64);
+        for (int q = 0; q < kAhead; ++q) {
+            const uint32_t p = p0 + q * kSelBlock;
+            if (p >= n) break;
+            const uint32_t key = s.key[p];
+            const bool is_gt = key > theta, is_eq = key == theta;
+            if (!(is_gt || is_eq)) continue;
+            const uint64_t f = flags_before(p);
+            uint32_t g = static_cast<uint32_t>(f), e = static_cast<uint32_t>(f >> 32);
+            if constexpr (!DIRECT) {
+                const uint64_t sg = s.seg[static_cast<uint32_t>(at[q] >> 10) / seg_tiles];
+                g += static_cast<uint32_t>(sg);
+                e += static_cast<uint32_t>(sg >> 32);
+            }
+            if (is_gt || e < need_eq) {
+                out.put(static_cast<uint64_t>(g) + (e < need_eq ? e : need_eq), at[q], x[q]);
+                heavy += key >> 30;
+            }
         }
-        if (lane == 0) {
-            ws->gt[b] = n_gt;
-            ws->eq[b] = n_eq;
-        }
+    }
+    if (out.n_heavy) {
+        if (heavy) atomicAdd(&s.heavy, heavy);
+        __syncthreads();
+        if (tid == 0) *out.n_heavy = s.heavy;
+    }
+}
+
+template <typename KEY>
+__global__ void __launch_bounds__(kSelBlock)
+k_topk_small(const float* __restrict__ est, uint32_t d, SelOut out, KEY kf) {
+    kf.init();
+    __shared__ SmallLds s;
+    select_in_workgroup<true>(s, est, nullptr, d, 0u, static_cast<uint64_t>(out.k), nullptr, nullptr, 1, 1u, out, kf);
+}
+
+// values that other workgroups of the launch wrote or added to: read past this XCD's caches
+template <typename T>
+__device__ __forceinline__ T load_shared(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void store_shared(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The rest of a selection, see the head of this file.  `listed`: a candidate list was asked for (it
+// is used unless ws->failed says that it could not be built).  Phases of the shared form: 0 and 1
+// the histograms of bits 19..10 and 9..0, 2 the counts of greater and equal entries per segment
+// (per task when est is read), 3 the ordered write, whose starting slots are a scan of those counts.
+template <bool VEC, typename KEY>
+__global__ void __launch_bounds__(kSelBlock)
+k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64_t* __restrict__ hist0,
+              bool listed, int nseg, uint32_t seg_tiles, const int64_t* __restrict__ cand_idx,
+              const float* __restrict__ cand_val, SelOut out, KEY kf) {
+    kf.init();
+    __shared__ SmallLds s;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool from_list = listed && ws->failed == 0;
+    const uint32_t n = from_list ? ws->ncand : 0u;
+    if (from_list && n <= kSmall) {
+        if (blockIdx.x != 0) return;
+        select_in_workgroup<false>(s, cand_val, cand_idx, n, ws->prefix, ws->k_rem, ws->seg_base, ws->seg_count,
+                                   nseg, seg_tiles, out, kf);
+        if (tid == 0) ws->ncand = 0;
         return;
     }
-    __shared__ uint32_t lds[kBlock / 64];
-    const int64_t lo = static_cast<int64_t>(blockIdx.x) * chunk;
-    const int64_t hi = (lo + chunk < d) ? lo + chunk : d;
-    uint64_t n_gt = 0, n_eq = 0;
-    for (int64_t tile = lo; tile < hi; tile += kTile) {
-        float v[kItems];
-        int nvalid;
-        const int64_t base = tile + static_cast<int64_t>(threadIdx.x) * kItems;
-        load_items<VEC>(est, base, hi, v, nvalid);
-        uint32_t c = 0;
-#pragma unroll
-        for (int q = 0; q < kItems; ++q)
-            if (q < nvalid) c += classify(kf(v[q], base + q), theta);
-        uint32_t total;
-        block_inclusive_scan(c, lds, &total);
-        n_gt += total & 0xffffu;
-        n_eq += total >> 16;
-    }
-    if (threadIdx.x == 0) {
-        ws->gt[blockIdx.x] = n_gt;
-        ws->eq[blockIdx.x] = n_eq;
-    }
-}
-
-// one workgroup: exclusive scan of the per-block counts, in place
-__global__ void __launch_bounds__(kBlock) k_topk_scan(TopkWs* ws, int nblocks) {
-    __shared__ uint64_t wave_gt[kBlock / 64], wave_eq[kBlock / 64];
-    constexpr int per = kMaxSelBlocks / kBlock;     // 16 consecutive blocks per thread
-    uint64_t g[per], e[per], sg = 0, se = 0;
-    for (int q = 0; q < per; ++q) {
-        const int b = threadIdx.x * per + q;
-        g[q] = (b < nblocks) ? ws->gt[b] : 0;
-        e[q] = (b < nblocks) ? ws->eq[b] : 0;
-        sg += g[q];
-        se += e[q];
-    }
-    uint64_t all;
-    uint64_t bg = block_exclusive_sum64(sg, wave_gt, &all);
-    uint64_t be = block_exclusive_sum64(se, wave_eq, &all);
-    for (int q = 0; q < per; ++q) {
-        const int b = threadIdx.x * per + q;
-        if (b < nblocks) { ws->gt[b] = bg; ws->eq[b] = be; }
-        bg += g[q];
-        be += e[q];
-    }
-}
-
-// ordered compaction: index t is selected when key > theta, or key == theta and fewer than
-// need_eq equal entries precede it; its output slot is (#greater before t) + min(#equal
-// before t, need_eq), which is its rank among the selected in ascending index order.
-template <bool VEC, typename KEY>
-__global__ void __launch_bounds__(kBlock)
-k_topk_write(const float* __restrict__ est, int64_t d, int64_t chunk, const TopkWs* ws, int nblocks,
-             int64_t k, int64_t* __restrict__ idx_out, float* __restrict__ val_out, bool listed,
-             const int64_t* __restrict__ cand_idx, const float* __restrict__ cand_val, KEY kf) {
-    kf.init();
-    const uint32_t theta = ws->sel.prefix;
-    const uint64_t need_eq = ws->sel.k_rem;
-    if (use_list(ws, listed)) {                     // one wavefront per segment, 64 candidates at a time
-        const int b = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-        if (b >= nblocks) return;
-        const int lane = threadIdx.x & 63;
-        uint64_t g = ws->gt[b], e = ws->eq[b];      // greater / equal entries before this batch
-        const uint32_t base = ws->seg_base[b], n = ws->seg_count[b];
-        const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));   // lanes before mine
-        for (uint32_t t0 = 0; t0 < n; t0 += 64) {
-            const uint32_t t = t0 + lane;
-            bool is_gt = false, is_eq = false;
-            int64_t i = 0;
-            float v = 0.0f;
-            if (t < n) {
-                i = cand_idx[base + t];
-                v = cand_val[base + t];
-                const uint32_t key = kf(v, i);
-                is_gt = key > theta;
-                is_eq = key == theta;
+    // 4096 entries per task: a phase is then one load per thread.  What the phases hand on (the
+    // histograms, the counts) is written and read with device-scope atomic accesses only, so no
+    // cache has to be written back or invalidated in between: a task's accesses are complete
+    // when its wavefronts have waited for them, and then it is counted as done.
+    const int64_t items = from_list ? static_cast<int64_t>(n) : d;
+    int64_t want = (items + 4095) / 4096;
+    if (want > static_cast<int64_t>(gridDim.x)) want = gridDim.x;
+    if (from_list && want > nseg) want = nseg;
+    const uint32_t tasks = static_cast<uint32_t>(want);
+    if (blockIdx.x >= tasks) return;
+    __shared__ uint32_t drawn;
+    auto wait_for = [&](int phase) {                // every task of that phase is done
+        if (tid == 0)
+            while (load_shared(&ws->done[phase]) < tasks) __builtin_amdgcn_s_sleep(8);
+        __syncthreads();
+    };
+    auto finish_task = [&](int phase) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) __hip_atomic_fetch_add(&ws->done[phase], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    // the bins found so far: prefix of `bits` key bits and entries still wanted (every workgroup
+    // finds them again from the finished histograms)
+    uint32_t prefix = 0;
+    uint64_t k_rem = static_cast<uint64_t>(out.k);
+    int known = 0;                                  // histograms already looked at
+    auto know = [&](int upto) {
+        for (; known < upto; ++known) {
+            uint32_t bin;
+            if (known == 0) {
+                const uint64_t cnt[2] = {hist0[2 * tid], hist0[2 * tid + 1]};
+                find_bin<kSelWaves, 2>(cnt, k_rem, s.scan, s.found, &bin, &k_rem);
+                prefix = bin;
+            } else {
+                const uint64_t cnt[1] = {load_shared(&ws->hist[known][tid])};
+                find_bin<kSelWaves, 1>(cnt, k_rem, s.scan, s.found, &bin, &k_rem);
+                prefix = (prefix << 10) | bin;
             }
-            const uint64_t m_gt = __builtin_amdgcn_ballot_w64(is_gt);
-            const uint64_t m_eq = __builtin_amdgcn_ballot_w64(is_eq);
-            const uint64_t my_g = g + __builtin_popcountll(m_gt & below);
-            const uint64_t my_e = e + __builtin_popcountll(m_eq & below);
-            if (is_gt || (is_eq && my_e < need_eq)) {
-                const uint64_t slot = my_g + (my_e < need_eq ? my_e : need_eq);
-                if (slot < static_cast<uint64_t>(k)) {
-                    idx_out[slot] = i;
-                    if (val_out) val_out[slot] = v;
+        }
+    };
+    const int64_t est_chunk = ((d + tasks - 1) / tasks + 4095) / 4096 * 4096;
+    for (;;) {
+        if (tid == 0) drawn = atomicAdd(&ws->ticket, 1u);
+        __syncthreads();
+        const uint32_t ticket = drawn;
+        __syncthreads();
+        if (ticket >= 4 * tasks) break;
+        const int phase = static_cast<int>(ticket / tasks);
+        const uint32_t t = ticket - phase * tasks;
+        if (phase > 0) wait_for(phase - 1);
+        know(phase < 2 ? phase + 1 : 3);
+        const int64_t lo = static_cast<int64_t>(t) * est_chunk;
+        const int64_t hi = lo + est_chunk < d ? lo + est_chunk : d;
+        const int seg0 = static_cast<int>(static_cast<int64_t>(nseg) * t / tasks);
+        const int seg1 = static_cast<int>(static_cast<int64_t>(nseg) * (t + 1) / tasks);
+        if (phase < 2) {
+            const int shift = phase == 0 ? 10 : 0;
+            s.hist[tid] = 0;
+            __syncthreads();
+            auto tally = [&](uint32_t key) {
+                if ((key >> (shift + 10)) == prefix) atomicAdd(&s.hist[(key >> shift) & 1023u], 1u);
+            };
+            if (from_list) {
+                for (uint32_t p = t * kSelBlock + tid; p < n; p += tasks * kSelBlock) tally(kf(cand_val[p], cand_idx[p]));
+            } else {
+                for (int64_t tile = lo; tile < hi; tile += kSelBlock * kItems) {
+                    float v[kItems];
+                    int nvalid;
+                    const int64_t base = tile + static_cast<int64_t>(tid) * kItems;
+                    load_items<VEC>(est, base, hi, v, nvalid);
+#pragma unroll
+                    for (int q = 0; q < kItems; ++q)
+                        if (q < nvalid) tally(kf(v[q], base + q));
                 }
             }
-            g += __builtin_popcountll(m_gt);
-            e += __builtin_popcountll(m_eq);
-        }
-        return;
-    }
-    __shared__ uint32_t lds[kBlock / 64];
-    uint64_t gt_before = ws->gt[blockIdx.x];
-    uint64_t eq_before = ws->eq[blockIdx.x];
-    const int64_t lo = static_cast<int64_t>(blockIdx.x) * chunk;
-    const int64_t hi = (lo + chunk < d) ? lo + chunk : d;
-    for (int64_t tile = lo; tile < hi; tile += kTile) {
-        float v[kItems];
-        int nvalid;
-        const int64_t base = tile + static_cast<int64_t>(threadIdx.x) * kItems;
-        load_items<VEC>(est, base, hi, v, nvalid);
-        uint32_t c = 0;
+            __syncthreads();
+            const uint32_t v = s.hist[tid];
+            if (v) atomicAdd(reinterpret_cast<unsigned long long*>(&ws->hist[phase + 1][tid]),
+                             static_cast<unsigned long long>(v));
+        } else if (phase == 2) {
+            if (from_list) {                        // one wavefront per segment
+                for (int b = seg0 + wave; b < seg1; b += kSelWaves) {
+                    const uint32_t base = ws->seg_base[b], cnt = ws->seg_count[b];
+                    uint32_t n_gt = 0, n_eq = 0;
+                    for (uint32_t p = lane; p < cnt; p += 64) {
+                        const uint32_t key = kf(cand_val[base + p], cand_idx[base + p]);
+                        n_gt += key > prefix ? 1u : 0u;
+                        n_eq += key == prefix ? 1u : 0u;
+                    }
 #pragma unroll
-        for (int q = 0; q < kItems; ++q)
-            if (q < nvalid) c += classify(kf(v[q], base + q), theta);
-        uint32_t total;
-        const uint32_t incl = block_inclusive_scan(c, lds, &total);
-        if (c) {
-            uint64_t g = gt_before + ((incl - c) & 0xffffu);
-            uint64_t e = eq_before + ((incl - c) >> 16);
-#pragma unroll
-            for (int q = 0; q < kItems; ++q) {
-                if (q >= nvalid) break;
-                const uint32_t key = kf(v[q], base + q);
-                const bool is_gt = key > theta, is_eq = key == theta;
-                if (is_gt || (is_eq && e < need_eq)) {
-                    const uint64_t slot = g + (e < need_eq ? e : need_eq);
-                    if (slot < static_cast<uint64_t>(k)) {
-                        idx_out[slot] = base + q;
-                        if (val_out) val_out[slot] = v[q];
+                    for (int off = 32; off > 0; off >>= 1) {
+                        n_gt += __shfl_down(n_gt, off, 64);
+                        n_eq += __shfl_down(n_eq, off, 64);
+                    }
+                    if (lane == 0) {
+                        store_shared(&ws->gt[b], static_cast<uint64_t>(n_gt));
+                        store_shared(&ws->eq[b], static_cast<uint64_t>(n_eq));
                     }
                 }
-                g += is_gt;
-                e += is_eq;
+            } else {
+                uint64_t n_gt = 0, n_eq = 0, sum_gt, sum_eq;
+                for (int64_t tile = lo; tile < hi; tile += kSelBlock * kItems) {
+                    float v[kItems];
+                    int nvalid;
+                    const int64_t base = tile + static_cast<int64_t>(tid) * kItems;
+                    load_items<VEC>(est, base, hi, v, nvalid);
+#pragma unroll
+                    for (int q = 0; q < kItems; ++q) {
+                        if (q >= nvalid) break;
+                        const uint32_t key = kf(v[q], base + q);
+                        n_gt += key > prefix ? 1u : 0u;
+                        n_eq += key == prefix ? 1u : 0u;
+                    }
+                }
+                block_exclusive_sum<kSelWaves>(n_gt, s.scan, &sum_gt);
+                block_exclusive_sum<kSelWaves>(n_eq, s.scan, &sum_eq);
+                if (tid == 0) {
+                    store_shared(&ws->gt[t], sum_gt);
+                    store_shared(&ws->eq[t], sum_eq);
+                }
             }
+        } else {
+            const uint64_t need_eq = k_rem;
+            uint32_t heavy = 0;
+            if (from_list) {
+                // slots before each segment: a scan over all of them
+                uint64_t all;
+                const bool in = tid < nseg;
+                const uint64_t g0 = block_exclusive_sum<kSelWaves>(in ? load_shared(&ws->gt[tid]) : 0, s.scan, &all);
+                const uint64_t e0 = block_exclusive_sum<kSelWaves>(in ? load_shared(&ws->eq[tid]) : 0, s.scan, &all);
+                if (in) { s.mask_gt[tid] = g0; s.mask_eq[tid] = e0; }
+                __syncthreads();
+                const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));   // lanes before mine
+                for (int b = seg0 + wave; b < seg1; b += kSelWaves) {
+                    uint64_t g = s.mask_gt[b], e = s.mask_eq[b];
+                    const uint32_t base = ws->seg_base[b], cnt = ws->seg_count[b];
+                    for (uint32_t p0 = 0; p0 < cnt; p0 += 64) {
+                        const uint32_t p = p0 + lane;
+                        bool is_gt = false, is_eq = false;
+                        int64_t i = 0;
+                        float v = 0.0f;
+                        uint32_t key = 0;
+                        if (p < cnt) {
+                            i = cand_idx[base + p];
+                            v = cand_val[base + p];
+                            key = kf(v, i);
+                            is_gt = key > prefix;
+                            is_eq = key == prefix;
+                        }
+                        const uint64_t m_gt = __builtin_amdgcn_ballot_w64(is_gt);
+                        const uint64_t m_eq = __builtin_amdgcn_ballot_w64(is_eq);
+                        const uint64_t my_g = g + __builtin_popcountll(m_gt & below);
+                        const uint64_t my_e = e + __builtin_popcountll(m_eq & below);
+                        if (is_gt || (is_eq && my_e < need_eq)) {
+                            out.put(my_g + (my_e < need_eq ? my_e : need_eq), i, v);
+                            heavy += key >> 30;
+                        }
+                        g += __builtin_popcountll(m_gt);
+                        e += __builtin_popcountll(m_eq);
+                    }
+                }
+            } else {
+                uint64_t g, e;                      // greater / equal entries before the tile
+                {
+                    uint64_t all_g, all_e;
+                    const bool in = tid < static_cast<int>(t);
+                    block_exclusive_sum<kSelWaves>(in ? load_shared(&ws->gt[tid]) : 0, s.scan, &all_g);
+                    block_exclusive_sum<kSelWaves>(in ? load_shared(&ws->eq[tid]) : 0, s.scan, &all_e);
+                    g = all_g;
+                    e = all_e;
+                }
+                for (int64_t tile = lo; tile < hi; tile += kSelBlock * kItems) {
+                    float v[kItems];
+                    int nvalid;
+                    const int64_t base = tile + static_cast<int64_t>(tid) * kItems;
+                    load_items<VEC>(est, base, hi, v, nvalid);
+                    uint64_t c = 0;                 // low word: greater, high word: equal
+#pragma unroll
+                    for (int q = 0; q < kItems; ++q) {
+                        if (q >= nvalid) break;
+                        const uint32_t key = kf(v[q], base + q);
+                        c += (key > prefix ? 1ull : 0ull) | (key == prefix ? 1ull << 32 : 0ull);
+                    }
+                    uint64_t total;
+                    const uint64_t before = block_exclusive_sum<kSelWaves>(c, s.scan, &total);
+                    if (c) {
+                        uint64_t my_g = g + static_cast<uint32_t>(before), my_e = e + (before >> 32);
+#pragma unroll
+                        for (int q = 0; q < kItems; ++q) {
+                            if (q >= nvalid) break;
+                            const uint32_t key = kf(v[q], base + q);
+                            const bool is_gt = key > prefix, is_eq = key == prefix;
+                            if (is_gt || (is_eq && my_e < need_eq)) {
+                                out.put(my_g + (my_e < need_eq ? my_e : need_eq), base + q, v[q]);
+                                heavy += key >> 30;
+                            }
+                            my_g += is_gt;
+                            my_e += is_eq;
+                        }
+                    }
+                    g += static_cast<uint32_t>(total);
+                    e += total >> 32;
+                }
+            }
+            if (out.n_heavy && heavy) atomicAdd(&ws->heavy, heavy);
         }
-        gt_before += total & 0xffffu;
-        eq_before += total >> 16;
+        finish_task(phase);
     }
-}
-
-// idx[t] = cand[idx[t]]: positions within the candidate list -> coordinates
-__global__ void __launch_bounds__(kBlock)
-k_remap_positions(int64_t* __restrict__ idx, const int64_t* __restrict__ cand, int64_t k) {
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-    for (int64_t t = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; t < k; t += stride)
-        idx[t] = cand[idx[t]];
+    // the last workgroup to leave puts the workspace back as it was
+    if (tid == 0) drawn = atomicAdd(&ws->exits, 1u);
+    __syncthreads();
+    if (drawn + 1 != tasks) return;
+    for (int t = tid; t < 2 * kBins; t += kSelBlock) (&ws->hist[1][0])[t] = 0;
+    if (tid == 0) {
+        if (out.n_heavy) *out.n_heavy = load_shared(&ws->heavy);
+        ws->ticket = 0;
+        ws->exits = 0;
+        for (int q = 0; q < 4; ++q) ws->done[q] = 0;
+        ws->failed = 0;
+        ws->ncand = 0;
+        ws->heavy = 0;
+    }
 }
 
 // Alg. 1 step 1: out[1 + j] = sum_b S[j][b]^2, one workgroup of 1024 threads per row, binary64
@@ -600,21 +808,6 @@ __global__ void k_median_of_rows(double* out, int r) {
     out[0] = v[r / 2];
 }
 
-// how many of the selected coordinates passed the threshold
-__global__ void __launch_bounds__(kBlock)
-k_count_heavy(const float* __restrict__ est, const int64_t* __restrict__ idx, int64_t k,
-              KeyHeavymix kf, unsigned long long* __restrict__ n_heavy) {
-    kf.init();
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-    unsigned long long mine = 0;
-    for (int64_t t = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; t < k; t += stride)
-        mine += kf.heavy(est[idx[t]]) ? 1u : 0u;
-    for (int off = 32; off > 0; off >>= 1) mine += __shfl_down(mine, off, 64);
-    if ((threadIdx.x & 63) == 0 && mine) atomicAdd(n_heavy, mine);
-}
-
-__global__ void k_clear_u64(unsigned long long* x) { *x = 0; }
-
 __global__ void __launch_bounds__(kBlock) k_hist_zero(uint64_t* hist) {
     for (int t = threadIdx.x; t < kBins; t += kBlock) hist[t] = 0;
 }
@@ -624,31 +817,23 @@ int launch_magnitude_hist_zero(uint64_t* hist, hipStream_t stream) {
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
+// workgroups of the first histogram (more of them only add to the atomic adds at their end)
+static unsigned hist0_grid(int64_t d) {
+    const int64_t b = (d + kScanBlock * kItems * 2 - 1) / (kScanBlock * kItems * 2);
+    return static_cast<unsigned>(b < kMaxSegs ? (b < 1 ? 1 : b) : kMaxSegs);
+}
+
 int launch_magnitude_hist(const float* est, int64_t d, uint64_t* hist, hipStream_t stream) {
-    const unsigned hgrid = static_cast<unsigned>(
-        (d + kBlock * 16 - 1) / (kBlock * 16) < 2048 ? (d + kBlock * 16 - 1) / (kBlock * 16) : 2048);
     if (reinterpret_cast<uintptr_t>(est) % 16 == 0)
-        k_topk_hist<0, true, KeyMagnitude><<<hgrid, kBlock, 0, stream>>>(est, d, nullptr, hist, false, nullptr,
-                                                                        nullptr, KeyMagnitude{});
+        k_topk_hist0<true, KeyMagnitude><<<hist0_grid(d), kScanBlock, 0, stream>>>(est, d, hist, KeyMagnitude{});
     else
-        k_topk_hist<0, false, KeyMagnitude><<<hgrid, kBlock, 0, stream>>>(est, d, nullptr, hist, false, nullptr,
-                                                                         nullptr, KeyMagnitude{});
+        k_topk_hist0<false, KeyMagnitude><<<hist0_grid(d), kScanBlock, 0, stream>>>(est, d, hist, KeyMagnitude{});
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
 }  // namespace cs
 
 using namespace cs;
-
-static void topk_geometry(int64_t d, int* nblocks, int64_t* chunk) {
-    int64_t tiles = (d + kTile - 1) / kTile;
-    int64_t nb = tiles < kMaxSelBlocks ? tiles : kMaxSelBlocks;
-    if (nb < 1) nb = 1;
-    int64_t tiles_per_block = (tiles + nb - 1) / nb;
-    *chunk = tiles_per_block * kTile;
-    *nblocks = static_cast<int>((d + *chunk - 1) / *chunk);
-    if (*nblocks < 1) *nblocks = 1;
-}
 
 extern "C" int cs_topk_workspace_bytes(int64_t d, int64_t k, size_t* bytes) {
     if (!bytes || d < 1 || k < 1 || k > d) return CS_EINVAL;
@@ -659,53 +844,52 @@ extern "C" int cs_topk_workspace_bytes(int64_t d, int64_t k, size_t* bytes) {
 // the k entries with the largest keys, ascending by index (see the header of this file).
 // hist0: device uint64[2048], the histogram of key >> 20 over est, when the caller has it.
 template <typename KEY, bool VEC>
-static void enqueue_selection(const float* est, int64_t d, int64_t k, const uint64_t* hist0,
-                              int64_t* idx_out, float* val_out, TopkWs* ws, int64_t cap, bool listed,
-                              hipStream_t s, KEY kf) {
+static void enqueue_selection(const float* est, int64_t d, const uint64_t* hist0, const SelOut& out,
+                              TopkWs* ws, int64_t cap, bool listed, hipStream_t s, KEY kf) {
     int64_t* cand_idx = reinterpret_cast<int64_t*>(ws + 1);
     float* cand_val = reinterpret_cast<float*>(cand_idx + cap);
-    const unsigned hgrid = static_cast<unsigned>(
-        (d + kBlock * 16 - 1) / (kBlock * 16) < 2048 ? (d + kBlock * 16 - 1) / (kBlock * 16) : 2048);
-    int nblocks;
-    int64_t chunk;
-    topk_geometry(d, &nblocks, &chunk);
-    k_topk_clear<<<1, kBlock, 0, s>>>(ws, static_cast<uint64_t>(k));
-    if (!hist0)
-        k_topk_hist<0, VEC, KEY><<<hgrid, kBlock, 0, s>>>(est, d, ws, ws->hist[0], false, cand_idx, cand_val, kf);
-    k_topk_find<0><<<1, kBlock, 0, s>>>(ws, hist0 ? hist0 : ws->hist[0]);
+    k_topk_clear<<<1, kBlock, 0, s>>>(ws);
+    if (!hist0) {
+        k_topk_hist0<VEC, KEY><<<hist0_grid(d), kScanBlock, 0, s>>>(est, d, ws->hist[0], kf);
+        hist0 = ws->hist[0];
+    }
+    // chunks of whole KiB-tiles, at most kMaxSegs of them
+    const int64_t tiles = (d + 1023) / 1024;
+    const int64_t want = (tiles + 3) / 4 < kMaxSegs ? (tiles + 3) / 4 : kMaxSegs;   // >= 4096 entries each
+    const int64_t seg_tiles = (tiles + want - 1) / want, chunk = seg_tiles * 1024;
+    const int nseg = static_cast<int>((d + chunk - 1) / chunk);
     if (listed)
-        k_topk_compact<VEC, KEY><<<nblocks, kBlock, 0, s>>>(est, d, chunk, ws, static_cast<uint32_t>(cap),
-                                                            cand_idx, cand_val, kf);
-    k_topk_hist<1, VEC, KEY><<<hgrid, kBlock, 0, s>>>(est, d, ws, ws->hist[1], listed, cand_idx, cand_val, kf);
-    k_topk_find<1><<<1, kBlock, 0, s>>>(ws, ws->hist[1]);
-    k_topk_hist<2, VEC, KEY><<<hgrid, kBlock, 0, s>>>(est, d, ws, ws->hist[2], listed, cand_idx, cand_val, kf);
-    k_topk_find<2><<<1, kBlock, 0, s>>>(ws, ws->hist[2]);
-    k_topk_count<VEC, KEY><<<nblocks, kBlock, 0, s>>>(est, d, chunk, ws, nblocks, listed, cand_idx, cand_val, kf);
-    k_topk_scan<<<1, kBlock, 0, s>>>(ws, nblocks);
-    k_topk_write<VEC, KEY><<<nblocks, kBlock, 0, s>>>(est, d, chunk, ws, nblocks, k, idx_out, val_out, listed,
-                                                      cand_idx, cand_val, kf);
+        k_topk_compact<VEC, KEY><<<nseg, kScanBlock, 0, s>>>(est, d, chunk, ws, hist0, static_cast<uint64_t>(out.k),
+                                                             static_cast<uint32_t>(cap), cand_idx, cand_val, kf);
+    k_topk_finish<VEC, KEY><<<kFinishBlocks, kSelBlock, 0, s>>>(est, d, ws, hist0, listed, nseg,
+                                                                static_cast<uint32_t>(seg_tiles), cand_idx, cand_val,
+                                                                out, kf);
 }
 
 template <typename KEY>
-static int select_largest(const float* est, int64_t d, int64_t k, const uint64_t* hist0,
-                          int64_t* idx_out, float* val_out, void* workspace, size_t ws_bytes,
-                          hipStream_t s, KEY kf) {
-    if (d < 1 || k < 1 || k > d || !est || !idx_out || !workspace) return CS_EINVAL;
+static int select_largest(const float* est, int64_t d, const uint64_t* hist0, const SelOut& out,
+                          void* workspace, size_t ws_bytes, hipStream_t s, KEY kf) {
+    const int64_t k = out.k;
+    if (d < 1 || k < 1 || k > d || !est || !out.idx || !workspace) return CS_EINVAL;
     if (reinterpret_cast<uintptr_t>(workspace) % 8 != 0) return CS_EINVAL;
     if (hist0 && reinterpret_cast<uintptr_t>(hist0) % 8 != 0) return CS_EINVAL;
     if (ws_bytes < sizeof(TopkWs)) return CS_EWORKSPACE;
+    if (d <= kSmall) {
+        k_topk_small<KEY><<<1, kSelBlock, 0, s>>>(est, static_cast<uint32_t>(d), out, kf);
+        return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+    }
     TopkWs* ws = static_cast<TopkWs*>(workspace);
     // The candidate list takes what the workspace holds beyond the struct, up to what is worth
-    // having; it is used when that is at least 2 k + kStage entries (the k-th largest key's own
+    // having; it is used when that is at least 2 k + 4096 entries (the k-th largest key's own
     // bin has to fit beside the k entries above it) and clearly less than d.
     int64_t cap = static_cast<int64_t>((ws_bytes - sizeof(TopkWs)) / kCandBytes);
     if (cap > candidate_capacity_for(d, k)) cap = candidate_capacity_for(d, k);
     if (cap > 0xffffffffll) cap = 0xffffffffll;
-    const bool listed = cap >= 2 * k + kStage;
+    const bool listed = cap >= 2 * k + 4096;
     if (reinterpret_cast<uintptr_t>(est) % 16 == 0)
-        enqueue_selection<KEY, true>(est, d, k, hist0, idx_out, val_out, ws, cap, listed, s, kf);
+        enqueue_selection<KEY, true>(est, d, hist0, out, ws, cap, listed, s, kf);
     else
-        enqueue_selection<KEY, false>(est, d, k, hist0, idx_out, val_out, ws, cap, listed, s, kf);
+        enqueue_selection<KEY, false>(est, d, hist0, out, ws, cap, listed, s, kf);
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
@@ -713,7 +897,7 @@ extern "C" int cs_heavy_hitters_topk(const float* est, int64_t d, int64_t k,
                                      const uint64_t* hist_or_null, int64_t* idx_out,
                                      float* val_out, void* workspace, size_t ws_bytes,
                                      void* stream) {
-    return select_largest(est, d, k, hist_or_null, idx_out, val_out, workspace, ws_bytes,
+    return select_largest(est, d, hist_or_null, SelOut{idx_out, val_out, nullptr, nullptr, k}, workspace, ws_bytes,
                           reinterpret_cast<hipStream_t>(stream), KeyMagnitude{});
 }
 
@@ -750,7 +934,7 @@ extern "C" int cs_heavy_hitters_topk_static(const float* est, int64_t d, int64_t
     void* ws = nullptr;
     const int rc = static_scratch(&ws);
     if (rc != CS_OK) return rc;
-    return select_largest(est, d, k, nullptr, idx_out, val_out, ws, sizeof(scratch),
+    return select_largest(est, d, nullptr, SelOut{idx_out, val_out, nullptr, nullptr, k}, ws, sizeof(scratch),
                           reinterpret_cast<hipStream_t>(stream), KeyMagnitude{});
 }
 
@@ -770,29 +954,18 @@ extern "C" int cs_heavymix_select(const float* est, int64_t d, int64_t k, const 
                                   void* stream) {
     if (!l2sq || reinterpret_cast<uintptr_t>(l2sq) % 8 != 0) return CS_EINVAL;
     if (n_heavy && reinterpret_cast<uintptr_t>(n_heavy) % 8 != 0) return CS_EINVAL;
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    KeyHeavymix kf{l2sq, static_cast<double>(k), rng_seed, 0.0};
-    const int rc = select_largest(est, d, k, nullptr, idx_out, val_out, workspace, ws_bytes, s, kf);
-    if (rc != CS_OK || !n_heavy) return rc;
-    unsigned long long* cnt = reinterpret_cast<unsigned long long*>(n_heavy);
-    k_clear_u64<<<1, 1, 0, s>>>(cnt);
-    int64_t b = (k + kBlock - 1) / kBlock;
-    if (b > 1024) b = 1024;
-    k_count_heavy<<<static_cast<unsigned>(b), kBlock, 0, s>>>(est, idx_out, k, kf, cnt);
-    return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+    return select_largest(est, d, nullptr,
+                          SelOut{idx_out, val_out, nullptr, reinterpret_cast<unsigned long long*>(n_heavy), k},
+                          workspace, ws_bytes, reinterpret_cast<hipStream_t>(stream),
+                          KeyHeavymix{l2sq, static_cast<double>(k), rng_seed, 0.0});
 }
 
 extern "C" int cs_select_exact_topk(const int64_t* cand, const float* x, int64_t n, int64_t k,
                                     int64_t* idx_out, float* val_out, void* workspace,
                                     size_t ws_bytes, void* stream) {
     if (!cand) return CS_EINVAL;
-    // positions of the k largest |x| (ascending), then positions -> coordinates; cand is
-    // ascending, so the result is ascending too
-    const int rc = cs_heavy_hitters_topk(x, n, k, nullptr, idx_out, val_out, workspace, ws_bytes, stream);
-    if (rc != CS_OK) return rc;
-    int64_t b = (k + kBlock - 1) / kBlock;
-    if (b > 4096) b = 4096;
-    k_remap_positions<<<static_cast<unsigned>(b), kBlock, 0, reinterpret_cast<hipStream_t>(stream)>>>(
-        idx_out, cand, k);
-    return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+    // positions of the k largest |x| (ascending), written as the coordinates they stand for; cand
+    // is ascending, so the result is ascending too
+    return select_largest(x, n, nullptr, SelOut{idx_out, val_out, cand, nullptr, k}, workspace, ws_bytes,
+                          reinterpret_cast<hipStream_t>(stream), KeyMagnitude{});
 }
