@@ -35,10 +35,9 @@ bool lattice_applies(const cs_params* p, int64_t d);
 
 int launch_accumulate_lattice(const cs_params* p, const LatticePtrs& ptrs, int nw, int64_t d,
                               int64_t i0, float scale, hipStream_t stream);
-// *hist_done = true when the kernels that wrote est also filled hist (see launch_estimate_walk)
+// hist (or null) is cleared and receives the counts of est by magnitude bin
 int launch_estimate_lattice(const cs_params* p, const float* S, int64_t d, int64_t i0,
-                            float* est, float* rows, uint64_t* hist, bool* hist_done,
-                            hipStream_t stream);
+                            float* est, float* rows, uint64_t* hist, hipStream_t stream);
 // hist[b] = number of t < d with (bits(est[t]) & 0x7fffffff) >> 20 == b, b < 2048 (cs_topk.hip);
 // the _zero form only clears the 2048 counters
 int launch_magnitude_hist_zero(uint64_t* hist, hipStream_t stream);

@@ -229,33 +229,75 @@ k_row_values_lattice(KParams p, const float* __restrict__ S, int64_t d, int64_t 
 }
 
 // est[t] = median over rows of rows[j][t]; VEC: four coordinates per thread with 16-byte
-// accesses (d a multiple of 4, both arrays 16-byte aligned, so every row is aligned too)
-template <int R, bool VEC>
-__global__ void __launch_bounds__(kBlock)
-k_median_rows(const float* __restrict__ rows, int64_t d, float* __restrict__ est) {
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-    const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (VEC) {
+// accesses (d a multiple of 4, both arrays 16-byte aligned, so every row is aligned too), else
+// with 16-byte accesses at any dword address (rows of odd length start anywhere).
+// HIST: the estimates are counted by the top 11 bits of their magnitude into hist[2048] on the way,
+// which saves the selection a launch and a read of est (8 to 18 us at d = 10^6 .. 10^7).  Few
+// large workgroups then: every one adds its counts to the same addresses at the end, 12 ns each.
+constexpr int kMedianHistBlock = 1024;
+constexpr int kMedianHistCopies = 4;                // lane l counts in copy l mod 4: crowded bins
+template <int R, bool VEC, bool HIST>
+__global__ void __launch_bounds__(HIST ? kMedianHistBlock : kBlock)
+k_median_rows(const float* __restrict__ rows, int64_t d, float* __restrict__ est,
+              unsigned long long* __restrict__ hist) {
+    constexpr int kThreads = HIST ? kMedianHistBlock : kBlock;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+    const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+    __shared__ uint32_t lh_all[HIST ? kMedianHistCopies : 1][HIST ? 2048 : 1];
+    uint32_t* lh = lh_all[HIST ? threadIdx.x % kMedianHistCopies : 0];
+    if constexpr (HIST) {
+        for (int t = threadIdx.x; t < kMedianHistCopies * 2048; t += kThreads) (&lh_all[0][0])[t] = 0;
+        __syncthreads();
+    }
+    auto put = [&](int64_t t, float v) {
+        est[t] = v;
+        if constexpr (HIST) atomicAdd(&lh[(__float_as_uint(v) & 0x7fffffffu) >> 20], 1u);
+    };
+    {
         const int64_t n4 = d / 4;
         for (int64_t t = t0; t < n4; t += stride) {
             typedef float f4 __attribute__((ext_vector_type(4)));
             float vx[R], vy[R], vz[R], vw[R];
 #pragma unroll
             for (int j = 0; j < R; ++j) {
-                const f4 q = __builtin_nontemporal_load(
-                    reinterpret_cast<const f4*>(rows + static_cast<size_t>(j) * d) + t);
+                f4 q;
+                if constexpr (VEC) {
+                    q = __builtin_nontemporal_load(reinterpret_cast<const f4*>(rows + static_cast<size_t>(j) * d) + t);
+                } else {
+                    const float4u u = reinterpret_cast<const float4u*>(rows + static_cast<size_t>(j) * d)[t];
+                    q.x = u.x; q.y = u.y; q.z = u.z; q.w = u.w;
+                }
                 vx[j] = q.x; vy[j] = q.y; vz[j] = q.z; vw[j] = q.w;
             }
-            reinterpret_cast<float4*>(est)[t] =
-                make_float4(median_odd<R>(vx), median_odd<R>(vy), median_odd<R>(vz), median_odd<R>(vw));
+            const float4 m = make_float4(median_odd<R>(vx), median_odd<R>(vy), median_odd<R>(vz), median_odd<R>(vw));
+            if constexpr (VEC) {
+                reinterpret_cast<float4*>(est)[t] = m;
+            } else {
+                float4u u;
+                u.x = m.x; u.y = m.y; u.z = m.z; u.w = m.w;
+                reinterpret_cast<float4u*>(est)[t] = u;
+            }
+            if constexpr (HIST) {
+                const float x[4] = {m.x, m.y, m.z, m.w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) atomicAdd(&lh[(__float_as_uint(x[q]) & 0x7fffffffu) >> 20], 1u);
+            }
         }
-        return;
     }
-    for (int64_t t = t0; t < d; t += stride) {
+    for (int64_t t = d / 4 * 4 + t0; t < d; t += stride) {
         float v[R];
 #pragma unroll
         for (int j = 0; j < R; ++j) v[j] = rows[static_cast<size_t>(j) * d + t];
-        est[t] = median_odd<R>(v);
+        put(t, median_odd<R>(v));
+    }
+    if constexpr (HIST) {
+        __syncthreads();
+        for (int t = threadIdx.x; t < 2048; t += kThreads) {
+            uint32_t n = 0;
+#pragma unroll
+            for (int q = 0; q < kMedianHistCopies; ++q) n += lh_all[q][t];
+            if (n) atomicAdd(&hist[t], static_cast<unsigned long long>(n));
+        }
     }
 }
 
@@ -312,26 +354,32 @@ int launch_accumulate_lattice(const cs_params* p, const LatticePtrs& ptrs, int n
 }
 
 int launch_estimate_lattice(const cs_params* p, const float* S, int64_t d, int64_t i0,
-                            float* est, float* rows, uint64_t* hist, bool* hist_done,
-                            hipStream_t stream) {
-    *hist_done = false;
+                            float* est, float* rows, uint64_t* hist, hipStream_t stream) {
     if (walk_applies(p, d)) {
         const bool fuse_last = d >= (static_cast<int64_t>(1) << 24);
-        const int rc = launch_estimate_walk(p, S, d, i0, est, rows, fuse_last, fuse_last ? hist : nullptr, stream);
-        *hist_done = fuse_last && hist != nullptr;
+        const int rc = launch_estimate_walk(p, S, d, i0, est, rows, fuse_last, hist, stream);
         if (rc != CS_OK || fuse_last) return rc;
     } else {
+        if (hist) {
+            const int rc = launch_magnitude_hist_zero(hist, stream);
+            if (rc != CS_OK) return rc;
+        }
         const dim3 grid(lattice_grid_x(p, d), p->r);
         k_row_values_lattice<<<grid, 64, 0, stream>>>(kparams(p), S, d, i0, rows);
     }
-    int64_t b = (d + kBlock - 1) / kBlock;
-    if (b > 256 * 16) b = 256 * 16;
-    const unsigned mg = static_cast<unsigned>(b);
+    const int64_t threads = (d + 3) / 4, block = hist ? kMedianHistBlock : kBlock;
+    int64_t b = (threads + block - 1) / block;
+    const int64_t most = hist ? 512 : 256 * 16;
+    if (b > most) b = most;
+    const unsigned mg = static_cast<unsigned>(b), mb = static_cast<unsigned>(block);
+    unsigned long long* h = reinterpret_cast<unsigned long long*>(hist);
     const bool vec = d % 4 == 0 && (reinterpret_cast<uintptr_t>(rows) | reinterpret_cast<uintptr_t>(est)) % 16 == 0;
-#define CS_MEDIAN(R_)                                                                   \
-    case R_:                                                                            \
-        if (vec) k_median_rows<R_, true><<<mg, kBlock, 0, stream>>>(rows, d, est);       \
-        else k_median_rows<R_, false><<<mg, kBlock, 0, stream>>>(rows, d, est);          \
+#define CS_MEDIAN(R_)                                                                            \
+    case R_:                                                                                     \
+        if (vec && h) k_median_rows<R_, true, true><<<mg, mb, 0, stream>>>(rows, d, est, h);      \
+        else if (vec) k_median_rows<R_, true, false><<<mg, mb, 0, stream>>>(rows, d, est, h);     \
+        else if (h) k_median_rows<R_, false, true><<<mg, mb, 0, stream>>>(rows, d, est, h);       \
+        else k_median_rows<R_, false, false><<<mg, mb, 0, stream>>>(rows, d, est, h);             \
         break;
     switch (p->r) {
         CS_MEDIAN(1) CS_MEDIAN(3) CS_MEDIAN(5) CS_MEDIAN(7) CS_MEDIAN(9) CS_MEDIAN(11) CS_MEDIAN(13) CS_MEDIAN(15)

@@ -985,6 +985,9 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
     const int j = RF ? RF - 1 : blockIdx.y;
     const int nseg = segs.n[j];
     if (static_cast<int>(blockIdx.z) >= nseg) return;
+    // the counters that a later kernel of the query adds to are cleared here: a launch less
+    if (RF == 0 && hist && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+        for (int t = threadIdx.x; t < 2048; t += 64) hist[t] = 0;
     __shared__ uint32_t lh[HIST ? 2048 : 1];
     if (HIST) {
         for (int t = threadIdx.x; t < 2048; t += 64 * NW) lh[t] = 0;
@@ -1337,7 +1340,7 @@ int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t 
 // fuse_last = false: all rows into the scratch (the caller takes the median).  fuse_last = true:
 // the last row's walk takes the median itself; worth it for long vectors, where the scratch
 // traffic it saves (write and read of one row) outweighs a second, narrower launch.
-// hist (with fuse_last): zeroed by the caller; receives the counts of est by magnitude bin.
+// hist: cleared; with fuse_last it also receives the counts of est by magnitude bin.
 int launch_estimate_walk(const cs_params* p, const float* S, int64_t d, int64_t i0,
                          float* est, float* rows, bool fuse_last, uint64_t* hist, hipStream_t stream) {
     int64_t most = 1;
@@ -1363,18 +1366,21 @@ int launch_estimate_walk(const cs_params* p, const float* S, int64_t d, int64_t 
         segs.n[j] = static_cast<int>(n);
         if (segs.n[j] > most_segs) most_segs = segs.n[j];
     }
+    unsigned long long* h = reinterpret_cast<unsigned long long*>(hist);
     if (!fuse_last) {
         const dim3 grid(static_cast<unsigned>(gx), p->r, static_cast<unsigned>(most_segs));
-        k_row_values_walk<0, false><<<grid, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, nullptr);
+        k_row_values_walk<0, false><<<grid, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);
         return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
     }
     // rows 0 .. r-2 into the scratch, then the last row together with the median
     if (p->r > 1) {
         const dim3 grid(static_cast<unsigned>(gx), p->r - 1, static_cast<unsigned>(most_segs));
-        k_row_values_walk<0, false><<<grid, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, nullptr);
+        k_row_values_walk<0, false><<<grid, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);
+    } else if (h) {
+        const int rc = launch_magnitude_hist_zero(hist, stream);
+        if (rc != CS_OK) return rc;
     }
     const dim3 grid(static_cast<unsigned>(gx), 1, static_cast<unsigned>(segs.n[p->r - 1]));
-    unsigned long long* h = reinterpret_cast<unsigned long long*>(hist);
     const dim3 hgrid(static_cast<unsigned>(((gx + kHistWaves - 1) / kHistWaves + 7) / 8 * 8), 1, grid.z);
 #define CS_LAST(R_)                                                                                    \
     case R_:                                                                                           \
