@@ -189,7 +189,7 @@ def _check(status: int, what: str):
         raise CsError(f"{what}: {cs_status_string(status)} ({status})")
 
 
-def _dev(t: torch.Tensor, dtype, name: str, numel: int | None = None):
+def _address(t: torch.Tensor, dtype, name: str, numel: int | None = None) -> int:
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise CsError(f"{name} must be a tensor on the GPU")
     if t.dtype != dtype:
@@ -198,18 +198,52 @@ def _dev(t: torch.Tensor, dtype, name: str, numel: int | None = None):
         raise CsError(f"{name} must be contiguous")
     if numel is not None and t.numel() != numel:
         raise CsError(f"{name} must have {numel} elements, got {t.numel()}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _dev(t: torch.Tensor, dtype, name: str, numel: int | None = None):
+    return ctypes.c_void_p(_address(t, dtype, name, numel))
 
 
 def _stream(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    # the raw handle: building a torch.cuda.Stream object for it costs ten times as much
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(t.device.index))
+
+
+class DeviceVectors:
+    """W vectors of the same length on the GPU, checked once and handed to several calls in place of
+    the list (which it keeps alive): with hundreds of workers the checks are most of a small
+    step's host time."""
+
+    def __init__(self, tensors, dtype=torch.float32, name: str = "vectors"):
+        self.tensors = list(tensors)
+        if not self.tensors:
+            raise CsError(f"{name} must be a non-empty list")
+        self.d = self.tensors[0].numel()
+        self.dtype = dtype
+        self.ptrs = _ptr_array(self.tensors, dtype, name, self.d)
+
+    def __len__(self):
+        return len(self.tensors)
+
+    def __getitem__(self, w):
+        return self.tensors[w]
 
 
 def _ptr_array(tensors, dtype, name, numel=None):
-    arr = (ctypes.c_void_p * len(tensors))()
-    for w, t in enumerate(tensors):
-        arr[w] = _dev(t, dtype, f"{name}[{w}]", numel).value
-    return arr
+    if isinstance(tensors, DeviceVectors):
+        if tensors.dtype != dtype or (numel is not None and tensors.d != numel):
+            raise CsError(f"{name} must hold vectors of {numel} elements of {dtype}")
+        return tensors.ptrs
+    try:
+        fine = all(t.is_cuda and t.dtype == dtype and t.is_contiguous() and (numel is None or t.numel() == numel)
+                   for t in tensors)
+    except AttributeError:
+        fine = False
+    if not fine:                                     # names the one that is not
+        for w, t in enumerate(tensors):
+            _address(t, dtype, f"{name}[{w}]", numel)
+    return (ctypes.c_void_p * len(tensors))(*[t.data_ptr() for t in tensors])
 
 
 def _cells(p: CsParams) -> int:
