@@ -224,8 +224,16 @@ int cs_sketch_accumulate_bundle(const cs_params* p, float* T, int32_t W,
  * device pointers to float[d].  W >= 1, d >= 0, i0 as for cs_sketch_accumulate. */
 int cs_sketch_accumulate_sum(const cs_params* p, float* S, int32_t W, const float* const* g_w,
                              int64_t d, int64_t i0, float scale, void* stream);
+/* out[t] = alpha * sum_{w<W} x_w[w][t], the sum accumulated in binary64 and rounded to binary32
+ * (once per 256 vectors).  By the same linearity this and one cs_sketch_accumulate of `out` sketch
+ * the W workers of a device with W d floats read once, for callers that have d floats to spare.
+ * x_w: HOST array of W device pointers to float[d]; out: device float[d], none of the x_w. */
+int cs_vectors_sum(const float* const* x_w, int32_t W, int64_t d, float alpha, float* out, void* stream);
 int cs_bundle_merge(const cs_params* p, float* dst, float beta, const float* T, int32_t W,
                     float alpha, void* stream);
+/* cs_bundle_merge into S_t (beta = 0) and cs_sketch_momentum with it, in one pass */
+int cs_bundle_merge_momentum(const cs_params* p, float* S_t, float* S_u, float* S_v, const float* T,
+                             int32_t W, float alpha, float rho, void* stream);
 
 /* Alg. 4 update for a list of (index, value) pairs:
  *     S[j][h_j(idx[t])] += scale * s_j(idx[t]) * val[t]
@@ -331,6 +339,14 @@ int cs_topk_workspace_bytes(int64_t d, int64_t k, size_t* bytes);
 int cs_heavy_hitters_topk(const float* est, int64_t d, int64_t k, const uint64_t* hist_or_null,
                           int64_t* idx_out, float* val_out,
                           void* workspace, size_t ws_bytes, void* stream);
+/* The same for a workspace that the caller keeps: cleared once by cs_topk_workspace_clear, then used
+ * by selections of this library only, one after the other, each of which leaves it clear. */
+int cs_topk_workspace_clear(void* workspace, size_t ws_bytes, void* stream);
+int cs_heavy_hitters_topk_kept(const float* est, int64_t d, int64_t k, const uint64_t* hist_or_null,
+                               int64_t* idx_out, float* val_out, void* workspace, size_t ws_bytes,
+                               void* stream);
+/* Selections from up to this many entries are one launch that needs no histogram. */
+#define CS_TOPK_SMALL_D 32768
 
 /* cs_heavy_hitters_topk for callers that cannot allocate device memory or hand over a
  * workspace: code under HIP graph capture, tight serving loops, harnesses that forbid
@@ -429,6 +445,10 @@ int cs_dense_mask(float* const* u_w, float* const* v_w, int32_t W, const int64_t
  * S: device float[r][c]; idx: device int64[k], distinct; val: device float[k] (output). */
 int cs_sketch_feedback(const cs_params* p, float* S, const int64_t* idx, int64_t k,
                        float* val, void* stream);
+/* cs_sketch_feedback of two different tables with the same hashes and coordinates (error and
+ * momentum sketch), in half the launches */
+int cs_sketch_feedback_pair(const cs_params* p, float* S_v, float* S_u, const int64_t* idx, int64_t k,
+                            float* val_v, float* val_u, void* stream);
 
 const char* cs_status_string(int status);
 

@@ -128,6 +128,10 @@ _SIGNATURES = {
     "cs_heavy_hitters_topk": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p,
                               ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t,
                               ctypes.c_void_p],
+    "cs_topk_workspace_clear": [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p],
+    "cs_heavy_hitters_topk_kept": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p,
+                                   ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t,
+                                   ctypes.c_void_p],
     "cs_heavy_hitters_topk_static": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64,
                                      ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p],
     "cs_select_exact_topk": [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64,
@@ -135,6 +139,11 @@ _SIGNATURES = {
                              ctypes.c_void_p],
     "cs_bundle_update_launches": [ctypes.POINTER(CsParams), ctypes.c_int32, ctypes.c_int64,
                                   ctypes.POINTER(ctypes.c_int32)],
+    "cs_bundle_merge_momentum": [ctypes.POINTER(CsParams), ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
+                                 ctypes.c_void_p, ctypes.c_int32, ctypes.c_float, ctypes.c_float,
+                                 ctypes.c_void_p],
+    "cs_sketch_feedback_pair": [ctypes.POINTER(CsParams), ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
+                                ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p],
     "cs_quantize16": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p],
     "cs_dequantize16": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p],
     "cs_bundle_merge16": [ctypes.POINTER(CsParams), ctypes.c_void_p, ctypes.c_float, ctypes.c_void_p,
@@ -416,6 +425,7 @@ def cs_estimate_workspace_bytes(p, d: int) -> int:
 
 
 CS_TOPK_HIST_BINS = 2048
+CS_TOPK_SMALL_D = 32768
 
 
 def _hist(hist):
@@ -457,6 +467,36 @@ def cs_heavy_hitters_topk(est, k: int, idx_out, val_out, workspace, hist=None):
         _dev(val_out, torch.float32, "val_out", k) if val_out is not None else ctypes.c_void_p(0),
         _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(est)),
         "cs_heavy_hitters_topk")
+
+
+def cs_topk_workspace_clear(workspace):
+    _check(load_library().cs_topk_workspace_clear(
+        _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(workspace)), "cs_topk_workspace_clear")
+
+
+def cs_heavy_hitters_topk_kept(est, k: int, idx_out, val_out, workspace, hist=None):
+    d = est.numel()
+    _check(load_library().cs_heavy_hitters_topk_kept(
+        _dev(est, torch.float32, "est"), d, k, _hist(hist), _dev(idx_out, torch.int64, "idx_out", k),
+        _dev(val_out, torch.float32, "val_out", k) if val_out is not None else ctypes.c_void_p(0),
+        _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(est)),
+        "cs_heavy_hitters_topk_kept")
+
+
+def cs_bundle_merge_momentum(p, S_t, S_u, S_v, T, W: int, alpha: float, rho: float):
+    n = _cells(p)
+    _check(load_library().cs_bundle_merge_momentum(
+        ctypes.byref(p), _dev(S_t, torch.float32, "S_t", n), _dev(S_u, torch.float32, "S_u", n),
+        _dev(S_v, torch.float32, "S_v", n), _dev(T, torch.float32, "T", cs_bundle_floats(p, W)), W, alpha, rho,
+        _stream(S_t)), "cs_bundle_merge_momentum")
+
+
+def cs_sketch_feedback_pair(p, S_v, S_u, idx, val_v, val_u):
+    k, n = idx.numel(), _cells(p)
+    _check(load_library().cs_sketch_feedback_pair(
+        ctypes.byref(p), _dev(S_v, torch.float32, "S_v", n), _dev(S_u, torch.float32, "S_u", n),
+        _dev(idx, torch.int64, "idx"), k, _dev(val_v, torch.float32, "val_v", k),
+        _dev(val_u, torch.float32, "val_u", k), _stream(S_v)), "cs_sketch_feedback_pair")
 
 
 def cs_heavy_hitters_topk_static(est, k: int, idx_out, val_out):

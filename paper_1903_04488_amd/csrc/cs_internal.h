@@ -66,6 +66,8 @@ int launch_estimate_walk(const cs_params* p, const float* S, int64_t d, int64_t 
 int launch_bundle_zero(float* T, int64_t n, hipStream_t stream);
 int launch_bundle_merge(float* dst, float beta, const float* T, int groups, float alpha,
                         int64_t cells, hipStream_t stream);
+int launch_bundle_merge_momentum(float* St, float* Su, float* Sv, const float* T, int groups, float alpha,
+                                 float rho, int64_t cells, hipStream_t stream);
 int launch_bundle_merge16(float* dst, float beta, const uint16_t* T16, int groups, float alpha,
                           int64_t cells, int fmt, hipStream_t stream);
 

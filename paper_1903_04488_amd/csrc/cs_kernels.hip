@@ -462,6 +462,50 @@ k_estimate_sparse(KParams p, const float* __restrict__ S, const int64_t* __restr
     }
 }
 
+// Error feedback, S -= sketch of the estimates at idx, for one or two tables (blockIdx.y) with the
+// same hashes.  All estimates are taken from the table as it is on entry.  Up to kFeedbackSmall
+// coordinates one workgroup per table does both halves, a barrier between them, in one launch
+// (two tables: four launches of 4 to 5 us before); more are a launch per half.
+struct FeedbackTables {
+    float* S[2];
+    float* val[2];
+};
+constexpr int kFeedbackBlock = 512;
+constexpr int64_t kFeedbackSmall = 4 * kFeedbackBlock;
+
+template <int R, bool POW2>
+__device__ __forceinline__ float estimate_at(const KParams& p, const Columns& col, const float* S, uint64_t i) {
+    float v[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+        v[j] = apply_sign(S[static_cast<size_t>(j) * p.c + bucket_of<POW2>(hash_state(p.a[j], p.b[j], i), col)],
+                          sign_flip_of(hash_state(p.as[j], p.bs[j], i)));
+    return median_odd<R>(v);
+}
+
+// PHASES: 1 the estimates, 2 the subtraction, 3 both (one workgroup per table)
+template <int R, bool POW2, int PHASES>
+__global__ void __launch_bounds__(kFeedbackBlock)
+k_feedback(KParams p, FeedbackTables tab, const int64_t* __restrict__ idx, int64_t n) {
+    float* S = tab.S[blockIdx.y];
+    float* val = tab.val[blockIdx.y];
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kFeedbackBlock;
+    const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kFeedbackBlock + threadIdx.x;
+    const Columns col = columns_of<POW2>(p.c);
+    if (PHASES & 1)
+        for (int64_t t = t0; t < n; t += stride) val[t] = estimate_at<R, POW2>(p, col, S, static_cast<uint64_t>(idx[t]));
+    if (PHASES == 3) __syncthreads();
+    if (PHASES & 2)
+        for (int64_t t = t0; t < n; t += stride) {
+            const uint64_t i = static_cast<uint64_t>(idx[t]);
+            const float v = -val[t];
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                atomic_add_noret(S + static_cast<size_t>(j) * p.c + bucket_of<POW2>(hash_state(p.a[j], p.b[j], i), col),
+                                 apply_sign(v, sign_flip_of(hash_state(p.as[j], p.bs[j], i))));
+        }
+}
+
 // ---------------------------------------------------------------------------------------
 // gather_exact: second round
 // ---------------------------------------------------------------------------------------
@@ -765,6 +809,14 @@ extern "C" int cs_bundle_merge(const cs_params* p, float* dst, float beta, const
                                static_cast<int64_t>(p->r) * p->c, as_stream(stream));
 }
 
+extern "C" int cs_bundle_merge_momentum(const cs_params* p, float* S_t, float* S_u, float* S_v, const float* T,
+                                        int32_t W, float alpha, float rho, void* stream) {
+    if (!bundle_ok(p, W) || !S_t || !S_u || !S_v || !T) return CS_EINVAL;
+    if (reinterpret_cast<uintptr_t>(T) % 16 != 0) return CS_EINVAL;
+    return launch_bundle_merge_momentum(S_t, S_u, S_v, T, static_cast<int>(bundle_groups(W)), alpha, rho,
+                                        static_cast<int64_t>(p->r) * p->c, as_stream(stream));
+}
+
 extern "C" int cs_quantize16(const float* x, int64_t n, uint16_t* out, int32_t fmt, void* stream) {
     if (n < 0 || (fmt != CS_FMT_BF16 && fmt != CS_FMT_F16)) return CS_EINVAL;
     if (n == 0) return CS_OK;
@@ -1060,14 +1112,38 @@ extern "C" int cs_dense_mask(float* const* u_w, float* const* v_w, int32_t W, co
     return CS_OK;
 }
 
+static int feedback_tables(const cs_params* p, const FeedbackTables& tab, unsigned ntab, const int64_t* idx,
+                           int64_t k, void* stream) {
+    if (k <= kFeedbackSmall) {
+        const dim3 grid(1, ntab);
+#define CALL(R_, P2_) k_feedback<R_, P2_, 3><<<grid, kFeedbackBlock, 0, as_stream(stream)>>>(kparams(p), tab, idx, k)
+        CS_DISPATCH_R(p, CALL);
+#undef CALL
+        return launch_status();
+    }
+    const dim3 grid(grid_for(k, kFeedbackBlock), ntab);
+#define CALL(R_, P2_)                                                                                            \
+    do {                                                                                                         \
+        k_feedback<R_, P2_, 1><<<grid, kFeedbackBlock, 0, as_stream(stream)>>>(kparams(p), tab, idx, k);          \
+        k_feedback<R_, P2_, 2><<<grid, kFeedbackBlock, 0, as_stream(stream)>>>(kparams(p), tab, idx, k);          \
+    } while (0)
+    CS_DISPATCH_R(p, CALL);
+#undef CALL
+    return launch_status();
+}
+
 extern "C" int cs_sketch_feedback(const cs_params* p, float* S, const int64_t* idx, int64_t k,
                                   float* val, void* stream) {
     if (!params_ok(p) || k < 0) return CS_EINVAL;
     if (k == 0) return CS_OK;
     if (!S || !idx || !val) return CS_EINVAL;
-    // all k estimates are taken from the table as it is on entry (first kernel), and only
-    // then is the sketch of (idx, val) subtracted (second kernel, same stream).
-    int rc = cs_sketch_estimate_sparse(p, S, idx, k, val, stream);
-    if (rc != CS_OK) return rc;
-    return cs_sketch_accumulate_sparse(p, S, idx, val, k, -1.0f, stream);
+    return feedback_tables(p, FeedbackTables{{S, S}, {val, val}}, 1, idx, k, stream);
+}
+
+extern "C" int cs_sketch_feedback_pair(const cs_params* p, float* S_v, float* S_u, const int64_t* idx, int64_t k,
+                                       float* val_v, float* val_u, void* stream) {
+    if (!params_ok(p) || k < 0) return CS_EINVAL;
+    if (k == 0) return CS_OK;
+    if (!S_v || !S_u || !idx || !val_v || !val_u || S_v == S_u || val_v == val_u) return CS_EINVAL;
+    return feedback_tables(p, FeedbackTables{{S_v, S_u}, {val_v, val_u}}, 2, idx, k, stream);
 }

@@ -845,10 +845,10 @@ extern "C" int cs_topk_workspace_bytes(int64_t d, int64_t k, size_t* bytes) {
 // hist0: device uint64[2048], the histogram of key >> 20 over est, when the caller has it.
 template <typename KEY, bool VEC>
 static void enqueue_selection(const float* est, int64_t d, const uint64_t* hist0, const SelOut& out,
-                              TopkWs* ws, int64_t cap, bool listed, hipStream_t s, KEY kf) {
+                              TopkWs* ws, int64_t cap, bool listed, bool clean, hipStream_t s, KEY kf) {
     int64_t* cand_idx = reinterpret_cast<int64_t*>(ws + 1);
     float* cand_val = reinterpret_cast<float*>(cand_idx + cap);
-    k_topk_clear<<<1, kBlock, 0, s>>>(ws);
+    if (!clean || !hist0) k_topk_clear<<<1, kBlock, 0, s>>>(ws);   // (hist[0] is not left clear)
     if (!hist0) {
         k_topk_hist0<VEC, KEY><<<hist0_grid(d), kScanBlock, 0, s>>>(est, d, ws->hist[0], kf);
         hist0 = ws->hist[0];
@@ -868,7 +868,7 @@ static void enqueue_selection(const float* est, int64_t d, const uint64_t* hist0
 
 template <typename KEY>
 static int select_largest(const float* est, int64_t d, const uint64_t* hist0, const SelOut& out,
-                          void* workspace, size_t ws_bytes, hipStream_t s, KEY kf) {
+                          void* workspace, size_t ws_bytes, hipStream_t s, KEY kf, bool clean = false) {
     const int64_t k = out.k;
     if (d < 1 || k < 1 || k > d || !est || !out.idx || !workspace) return CS_EINVAL;
     if (reinterpret_cast<uintptr_t>(workspace) % 8 != 0) return CS_EINVAL;
@@ -887,9 +887,9 @@ static int select_largest(const float* est, int64_t d, const uint64_t* hist0, co
     if (cap > 0xffffffffll) cap = 0xffffffffll;
     const bool listed = cap >= 2 * k + 4096;
     if (reinterpret_cast<uintptr_t>(est) % 16 == 0)
-        enqueue_selection<KEY, true>(est, d, hist0, out, ws, cap, listed, s, kf);
+        enqueue_selection<KEY, true>(est, d, hist0, out, ws, cap, listed, clean, s, kf);
     else
-        enqueue_selection<KEY, false>(est, d, hist0, out, ws, cap, listed, s, kf);
+        enqueue_selection<KEY, false>(est, d, hist0, out, ws, cap, listed, clean, s, kf);
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
@@ -899,6 +899,23 @@ extern "C" int cs_heavy_hitters_topk(const float* est, int64_t d, int64_t k,
                                      void* stream) {
     return select_largest(est, d, hist_or_null, SelOut{idx_out, val_out, nullptr, nullptr, k}, workspace, ws_bytes,
                           reinterpret_cast<hipStream_t>(stream), KeyMagnitude{});
+}
+
+// A workspace that its owner keeps for one stream of selections is cleared once, here; every
+// selection leaves it clear, so that cs_heavy_hitters_topk_kept needs no launch for that.
+extern "C" int cs_topk_workspace_clear(void* workspace, size_t ws_bytes, void* stream) {
+    if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 8 != 0) return CS_EINVAL;
+    if (ws_bytes < sizeof(TopkWs)) return CS_EWORKSPACE;
+    k_topk_clear<<<1, kBlock, 0, reinterpret_cast<hipStream_t>(stream)>>>(static_cast<TopkWs*>(workspace));
+    return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+}
+
+extern "C" int cs_heavy_hitters_topk_kept(const float* est, int64_t d, int64_t k,
+                                          const uint64_t* hist_or_null, int64_t* idx_out,
+                                          float* val_out, void* workspace, size_t ws_bytes,
+                                          void* stream) {
+    return select_largest(est, d, hist_or_null, SelOut{idx_out, val_out, nullptr, nullptr, k}, workspace, ws_bytes,
+                          reinterpret_cast<hipStream_t>(stream), KeyMagnitude{}, true);
 }
 
 // ---------------------------------------------------------------------------------------

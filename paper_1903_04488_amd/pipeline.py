@@ -50,6 +50,7 @@ class HotPath:
         self.uhat = torch.empty(k, **f32)
         self.topk_ws = torch.empty(B.cs_topk_workspace_bytes(d, self.kq), dtype=torch.uint8,
                                    device=self.device)
+        B.cs_topk_workspace_clear(self.topk_ws)      # once: every selection leaves it clear
         # counts of the estimates by magnitude bin: filled by the estimate, read by the selection
         self.hist = torch.zeros(B.CS_TOPK_HIST_BINS, dtype=torch.int64, device=self.device)
         n_est = B.cs_estimate_workspace_bytes(self.params, d)
@@ -82,11 +83,15 @@ class HotPath:
     def query_table(self):
         return self.S_v if self.rho is not None else self.S_t
 
+    def _hist(self):
+        """the counts, where the selection reads them"""
+        return self.hist if self.d > B.CS_TOPK_SMALL_D else None
+
     def estimate(self):
-        B.cs_sketch_estimate(self.params, self.query_table(), self.est, 0, self.est_ws, self.hist)
+        B.cs_sketch_estimate(self.params, self.query_table(), self.est, 0, self.est_ws, self._hist())
 
     def topk(self):
-        B.cs_heavy_hitters_topk(self.est, self.kq, self.cand, self.est_at_cand, self.topk_ws, self.hist)
+        B.cs_heavy_hitters_topk_kept(self.est, self.kq, self.cand, self.est_at_cand, self.topk_ws, self._hist())
 
     def gather(self, g_w):
         B.cs_gather_exact(g_w, self.cand, self.x_cand, alpha=1.0 / self.W)
@@ -95,15 +100,22 @@ class HotPath:
 
     def feedback(self):
         if self.rho is not None:
-            B.cs_sketch_feedback(self.params, self.S_v, self.idx, self.delta)
-            B.cs_sketch_feedback(self.params, self.S_u, self.idx, self.uhat)
+            B.cs_sketch_feedback_pair(self.params, self.S_v, self.S_u, self.idx, self.delta, self.uhat)
+
+    def aggregate(self):
+        """merge and momentum, in one pass where the workers have tables of their own"""
+        if self.rho is None or self.fold_workers:
+            self.merge()
+            self.momentum()
+            return
+        B.cs_bundle_merge_momentum(self.params, self.S_t, self.S_u, self.S_v, self.T, self.W, 1.0 / self.W, self.rho)
 
     def step(self, g_w):
         """g_w: list of W fp32[d] device tensors.  Returns (idx, x): chosen coordinates
         (ascending) and their exact mean over workers."""
+        g_w = B.DeviceVectors(g_w, name="g_w")
         self.accumulate(g_w)
-        self.merge()
-        self.momentum()
+        self.aggregate()
         self.estimate()
         self.topk()
         self.gather(g_w)
@@ -141,6 +153,10 @@ class ReproduciblePath(HotPath):
 
     def merge(self):
         B.cs_fixed_to_float(self.params, self.acc, self.frac_bits, self.S_t, alpha=1.0 / self.W)
+
+    def aggregate(self):
+        self.merge()
+        self.momentum()
 
     def _feedback(self, S, val):
         B.cs_sketch_estimate_sparse(self.params, S, self.idx, val)
