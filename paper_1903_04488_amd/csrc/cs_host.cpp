@@ -118,20 +118,26 @@ void plan_walk(cs_row_plan* rp, uint64_t a, uint64_t as, uint32_t c, bool pow2, 
     rp->ADws = mulmod(as, rp->Dw);
 }
 
-// Estimated time, in nanoseconds, of one launch of the bundle update for a group of 8 workers:
-// `visits` turns of the busiest wavefront in a row (each costs about kVisitNs of latency that
-// nothing hides when few wavefronts are resident), stretched when there are more wavefronts
-// than the chip holds at once; never less than reading the 8 vectors at the rate this access
-// pattern reaches; plus the atomic requests at the rate of the memory-side atomic unit.  The
-// constants are measurements on MI355X (bundle update at d = 10^6 .. 10^8).
-double update_time_ns(double visits, double residues, double requests, double d) {
+// Estimated time, in nanoseconds, of one row's part in a launch of the bundle update for a group of
+// 8 workers: `visits` turns of the busiest wavefront (each costs about kVisitNs of latency
+// that nothing hides when few wavefronts are resident), stretched when there are more wavefronts
+// than the chip holds at once; with `shared` the turns may be shared out among several
+// wavefronts, each of which sends requests of its own; never less than reading the 8 vectors at
+// the rate this access pattern reaches; plus the atomic requests at the rate of the memory-side
+// atomic unit.  The constants are measurements on MI355X (bundle update at d = 10^6 .. 10^8).
+double update_time_ns(double visits, double residues, double requests, double d, bool shared) {
     const double kVisitNs = 900.0, kResidentWaves = 4096.0;
     const double kBytesPerNs = 4600.0, kRequestsPerNs = 24.0;
     const double waves = residues / 128.0;
-    double serial = visits * kVisitNs;
-    if (waves > kResidentWaves) serial *= waves / kResidentWaves;
     const double stream = d * 32.0 / kBytesPerNs;
-    return (serial > stream ? serial : stream) + requests / kRequestsPerNs;
+    double best = 1e300;
+    for (double n = 1.0; n <= (shared ? 32.0 : 1.0) && (n == 1.0 || visits / n >= 3.0); n += 1.0) {
+        double serial = visits / n * kVisitNs;
+        if (waves * n > kResidentWaves) serial *= waves * n / kResidentWaves;
+        const double t = (serial > stream ? serial : stream) + n * requests / kRequestsPerNs;
+        if (t < best) best = t;
+    }
+    return best;
 }
 
 // Visit list of the bundle update for one row (cs_visit_plan).
@@ -161,7 +167,9 @@ void plan_visits(cs_visit_plan* vp, const cs_row_plan* rp, uint64_t a, uint64_t 
         const uint64_t mag = Uw < kP61 - Uw ? Uw : kP61 - Uw;
         const double requests = (double)d_hint * ((double)mag / (double)cell) + (double)rp->Dw;
         vp->cost_walk = (uint64_t)update_time_ns((double)d_hint / (double)rp->Dw, (double)rp->Dw,
-                                                 requests, (double)d_hint);
+                                                 requests, (double)d_hint, false);
+        // the rows without a list take a launch of their own, after the one along the lists
+        vp->cost_walk += 10000;
     }
     const double per_cell = (double)d_hint / (double)c;    // list entries per cell of bound
     double omega_max = (CS_MAX_VISITS - 16) / per_cell;
@@ -197,7 +205,7 @@ void plan_visits(cs_visit_plan* vp, const cs_row_plan* rp, uint64_t a, uint64_t 
         if (K < 4 || K > CS_MAX_VISITS) continue;
         const uint64_t ncell = ((bound + cell - 1) >> sh) + 1;
         const uint64_t cost = (uint64_t)update_time_ns((double)K, (double)gmax,
-                                                       (double)(ncell * gmax), (double)d_hint);
+                                                       (double)(ncell * gmax), (double)d_hint, true);
         if (cost < best_cost) { best_cost = cost; best_bound = bound; }
     }
     if (best_bound == 0) return;
@@ -268,7 +276,7 @@ void plan_anyc(cs_anyc_plan* vp, uint64_t a, uint32_t c, bool pow2, uint64_t d_h
             }
         }
     }
-    vp->cost_direct = (uint64_t)update_time_ns(1.0, 128.0, (double)d_hint, (double)d_hint);
+    vp->cost_direct = (uint64_t)update_time_ns(1.0, 128.0, (double)d_hint, (double)d_hint, false);
     uint64_t best_cost = ~0ull;
     std::vector<uint32_t> best_gaps;
     uint32_t best_omega = 0;
@@ -302,7 +310,7 @@ void plan_anyc(cs_anyc_plan* vp, uint64_t a, uint32_t c, bool pow2, uint64_t d_h
             if (d_hint - prev > gmax) gmax = d_hint - prev;
             if (gaps.size() < 4) continue;
             const uint64_t cost = (uint64_t)update_time_ns((double)gaps.size(), (double)gmax,
-                                                           2.0 * omega * (double)gmax, (double)d_hint);
+                                                           2.0 * omega * (double)gmax, (double)d_hint, true);
             if (cost < best_cost) { best_cost = cost; best_gaps = gaps; best_omega = omega; }
         }
     }

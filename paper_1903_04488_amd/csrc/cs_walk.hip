@@ -33,6 +33,7 @@
 // per walker by its lanes and shared through LDS.  Nothing is shared between the wavefronts of
 // a workgroup, so LDS needs no barrier.
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include <type_traits>
@@ -274,6 +275,7 @@ int launch_walk(const cs_params* p, const WalkArgs& a, int nrows, hipStream_t st
 struct VisitArgs {
     uint32_t K;                  // visits
     int32_t j;                   // sketch row
+    uint32_t pieces;             // the visits are shared out among this many wavefronts (blockIdx.z)
     uint64_t gmax;
     uint64_t a, b, as, bs;       // hash constants of row j
     uint64_t gap[4], A[4], As[4];
@@ -299,6 +301,7 @@ struct VisitRows {
 struct VisitGaps {
     uint32_t K;
     int32_t j;
+    uint32_t pieces;
     uint64_t gmax;
     uint64_t a, b, as, bs;
     uint32_t omega;              // running sums: omega cells from the first one, omega more after a wrap
@@ -347,6 +350,19 @@ __device__ __forceinline__ void load_floats(gfloat_ptr src, float (&out)[N]) {
     }
 }
 
+// Offset of visit k: the sum of the gaps before it, taken by the lanes of a wavefront together.
+template <typename GAP>
+__device__ __forceinline__ int64_t offset_of_visit(uint32_t k, GAP gap_of) {
+    if (k == 0) return 0;
+    int64_t mine = 0;
+    for (uint32_t t = threadIdx.x & 63; t < k; t += 64) mine += gap_of(t);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(mine));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(static_cast<uint64_t>(mine) >> 32));
+    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+
 // LIST = VisitRows (power-of-two column counts: three gaps and 2-bit codes, the NC cells are
 // neighbours) or VisitGapsRows (any column count: gaps one by one, NC = 2 omega cells of which
 // the second half lies p mod c cells back).
@@ -355,9 +371,9 @@ __global__ void __launch_bounds__(64 * NWAVE)
 k_accumulate_visits(LIST rows, VisitWorkers a) {
     constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
     const auto& v = rows.at(blockIdx.y);
+    if (blockIdx.z >= v.pieces) return;
     constexpr int WPW = 64 / WL;                       // walkers per wavefront
     constexpr int PPL = RUN / WL;                      // hash values each lane computes
-    constexpr int FPL = RUN / WL;                      // floats each lane requests per worker
     constexpr int SPAN = WPW * RUN;                    // residues a wavefront owns
     constexpr int kStride = RUN + 1;
     constexpr int kSetBlock = kVisitSetBlock;          // neighbouring walker sets per XCD turn
@@ -424,19 +440,20 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
     const uint32_t* my_rec = rec_lds + h * kRecWalker;
     uint32_t* rec_dst = rec_lds + h * kRecWalker + m0 * kRec;
     const uint64_t Aj = v.a, Asj = v.as;
-    // loader role: floats lspan .. lspan + FPL - 1 of the wavefront's span, of every worker;
-    // they belong to walker lspan / RUN and go to that walker's row of each worker
-    // With 8 workers and 8-byte pieces, two workers share a request instead: the lower 32 lanes
-    // take 16 bytes each of one worker's 512-byte span, the upper 32 lanes of the next worker's.
-    // Same bytes and the same time, but half the load instructions and half the address
-    // registers (16 VGPRs fewer).
-    constexpr bool PAIR = WL == 8 && FPL == 2;
-    constexpr int kLoads = PAIR ? WL / 2 : WL;         // load instructions per visit
-    constexpr int kPer = PAIR ? 2 * FPL : FPL;         // floats per lane and instruction
-    const int half = PAIR ? lane >> 5 : 0;
-    const int lspan = PAIR ? (lane & 31) * kPer : lane * FPL;
-    float* tile_dst = tile_lds + ((lspan / RUN) * WL + half) * kStride + lspan % RUN;
-    constexpr int kRowStep = PAIR ? 2 * kStride : kStride;   // tile rows between my loads
+    // loader role: floats lspan .. lspan + kPer - 1 of the wavefront's span of one worker at a time;
+    // they belong to walker lspan / RUN and go to that walker's row of the worker.  Requests are 16
+    // bytes or more per lane: where a worker's span is shorter than 64 of them, kShare workers
+    // share a request (8 workers and RUN = 16: two, 512 bytes of each; against 8-byte
+    // pieces the same time with half the load instructions and 16 VGPRs fewer).
+    constexpr int kShare = SPAN >= 256 ? 1 : 256 / SPAN;
+    constexpr int kLoads = WL / kShare;                // load instructions per visit
+    constexpr int kPer = SPAN >= 256 ? SPAN / 64 : 4;  // floats per lane and instruction
+    constexpr int kLanesPerWorker = 64 / kShare;
+    static_assert(kLoads * kShare == WL && kPer <= RUN, "whole requests, each within one run");
+    const int part = lane / kLanesPerWorker;
+    const int lspan = (lane % kLanesPerWorker) * kPer;
+    float* tile_dst = tile_lds + ((lspan / RUN) * WL + part) * kStride + lspan % RUN;
+    constexpr int kRowStep = kShare * kStride;         // tile rows between my loads
     // gap and hash advances of visit k.  Power-of-two lists: three gaps and the cut last one
     // live in scalar registers and a 2-bit code per visit picks among them; other lists are
     // read visit by visit from the kernel arguments.
@@ -473,6 +490,9 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
     // the visits with the largest gap, so the sets of walkers are dealt to the XCDs in short
     // blocks rather than as eight long ranges: every XCD gets the same mix.
     const int64_t ngroups = (nwaves + NWAVE - 1) / NWAVE;
+    // my piece of the chain of visits: k0 .. k1 - 1, the first of them at offset s0
+    const uint32_t k0 = v.K * blockIdx.z / v.pieces, k1 = v.K * (blockIdx.z + 1) / v.pieces;
+    const int64_t s0 = offset_of_visit(k0, [&](uint32_t k) { return gap_of(code_of(k)); });
     for (int64_t vi = blockIdx.x; ; vi += gridDim.x) {
         const int64_t slot = vi >> 3;
         const int64_t set = ((slot / kSetBlock) * 8 + (vi & 7)) * kSetBlock + slot % kSetBlock;
@@ -494,6 +514,10 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
                 if (q + 1 < PPL) tb = hash_advance(tb, Aj);
             }
         }
+        if (k0 > 0) {
+            yb = hash_state(v.a, v.b, static_cast<uint64_t>(a.i0 + first_res + h * RUN + m0 + s0));
+            ys = hash_state(v.as, v.bs, static_cast<uint64_t>(a.i0 + first_res + h * RUN + m0 + s0));
+        }
 
         float acc[NC][RUN];
 #pragma unroll
@@ -508,13 +532,13 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
         float pre[kLoads][kPer];
         // the vector that load instruction `w` of this lane reads
         auto vector_of = [&](int w) -> gfloat_ptr {
-            if constexpr (PAIR) {
-                const float* lo = a.g[2 * w < nw ? 2 * w : 0];
-                const float* hi = a.g[2 * w + 1 < nw ? 2 * w + 1 : 0];
-                return (gfloat_ptr)(half ? hi : lo);
-            } else {
-                return (gfloat_ptr)a.g[w < nw ? w : 0];
+            const float* x = a.g[w * kShare < nw ? w * kShare : 0];
+#pragma unroll
+            for (int u = 1; u < kShare; ++u) {
+                const float* y = a.g[w * kShare + u < nw ? w * kShare + u : 0];
+                x = part == u ? y : x;
             }
+            return (gfloat_ptr)x;
         };
         auto load_visit = [&](int64_t s, int64_t room) {
             if (room >= SPAN) {
@@ -544,11 +568,11 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
             return in_gap < in_vec ? in_gap : in_vec;
         };
 
-        int64_t s = 0;                                 // offset of visit k
-        uint32_t code = code_of(0);
-        bool active = room_of(0, gap_of(code)) > 0;
-        if (active) load_visit(0, room_of(0, gap_of(code)));
-        for (uint32_t k = 0; k < v.K; ++k) {
+        int64_t s = s0;                                // offset of visit k
+        uint32_t code = code_of(k0);
+        bool active = room_of(s, gap_of(code)) > 0;
+        if (active) load_visit(s, room_of(s, gap_of(code)));
+        for (uint32_t k = k0; k < k1; ++k) {
             // visit k: its values are on their way (requested one turn earlier)
             const bool was_active = active;
             if (was_active) {
@@ -562,7 +586,7 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
             const uint32_t code_k = code;
             s += gap_of(code_k);
             active = false;
-            if (k + 1 < v.K) {
+            if (k + 1 < k1) {
                 code = code_of(k + 1);
                 const int64_t room = room_of(s, gap_of(code));
                 active = room > 0;
@@ -652,6 +676,41 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
         }
         // every running sum goes to memory once
         const uint32_t* first = first_lds + h * RUN;
+        if (POW2 && RUN == 8 && !fold) {
+            // Two neighbouring cells of a bundle are one aligned 64-byte block when the lower one is
+            // even.  The sums of a residue take the slots of those blocks in LDS (an even first
+            // cell: slots 0 .. NC-1, an odd one: 1 .. NC), and a block then leaves as one request:
+            // on average NC / 2 + 1/2 requests per residue instead of NC.  Only short vectors (RUN =
+            // 8) gain, whose time is mostly these requests; long ones stream meanwhile and
+            // only lose the registers (2.5 % at d = 10^8).
+            constexpr int kSlots = (NC + 2) / 2 * 2;
+            uint32_t* cell0_lds = raw_lds;             // a walker's first block, as an even cell
+#pragma unroll
+            for (int m = 0; m < RUN; ++m) {
+                const uint32_t c0 = first[m], odd = c0 & 1u;
+                float* dst = tile_lds + h * (kSlots * WL) + wl;
+#pragma unroll
+                for (int q = 0; q < kSlots; ++q) {
+                    // slot q holds sum q (even first cell) or q - 1 (odd)
+                    const float even_v = q < NC ? acc[q < NC ? q : 0][m] : 0.0f;
+                    const float odd_v = q > 0 && q - 1 < NC ? acc[q > 0 && q - 1 < NC ? q - 1 : 0][m] : 0.0f;
+                    dst[q * WL] = live ? (odd ? odd_v : even_v) : 0.0f;
+                }
+                if (wl == 0) cell0_lds[h] = c0 - odd;
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int t = 0; t < kSlots; ++t) {     // WPW * kSlots * WL items, 64 at a time
+                    const uint32_t item = t * 64 + lane;
+                    const uint32_t of = item / (kSlots * WL), q = item / WL % kSlots, w = item % WL;
+                    const float sum = tile_lds[item];
+                    if (sum != 0.0f)
+                        atomic_add_noret(a.T + (static_cast<size_t>(v.j) * a.c + ((cell0_lds[of] + q) & mask)) * kGroup + w,
+                                         a.scale * sum);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            continue;
+        }
 #pragma unroll
         for (int m = 0; m < RUN; ++m) {
             const uint32_t c0 = first[m];
@@ -675,24 +734,54 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
     }
 }
 
+// Pieces that the chains of visits of a launch are cut into, each walked by wavefronts of its own.
+// A wavefront makes its visits one after the other, visit_ns each when the chip is not full, and
+// every piece sends its own requests (requests[q] per piece of row q) at 24 G/s: the common
+// length of the pieces with the smallest sum of the two is taken.  stream_ns: what the launch
+// takes to read its vectors in any case, so that long vectors, which fill the chip, stay whole.
+// Returns the largest number of pieces.
+constexpr uint32_t kMaxPieces = 32;
+unsigned choose_pieces(int nrows, const uint32_t* K, const double* requests, double visit_ns, double stream_ns,
+                       uint32_t* pieces) {
+    uint32_t longest = 1;
+    for (int q = 0; q < nrows; ++q) longest = K[q] > longest ? K[q] : longest;
+    double best = 1e300, best_len = longest;
+    for (double len = longest; len >= 3.0; len *= 0.8) {
+        double cost = len * visit_ns > stream_ns ? len * visit_ns : stream_ns;
+        for (int q = 0; q < nrows; ++q) cost += ceil(K[q] / len) * requests[q] / 24.0;
+        if (cost < best) { best = cost; best_len = len; }
+    }
+    unsigned most = 1;
+    for (int q = 0; q < nrows; ++q) {
+        double n = ceil(K[q] / best_len);
+        if (n > kMaxPieces) n = kMaxPieces;
+        pieces[q] = n < 1.0 ? 1u : static_cast<uint32_t>(n);
+        if (pieces[q] > most) most = pieces[q];
+    }
+    return most;
+}
+
+// a turn of the walkers of 8 (4, 2) workers with RUN = 8, and of a single vector
+constexpr double kVisitNs8 = 700.0, kVisitNsOne = 500.0;
+constexpr double kStreamBytesPerNs = 5000.0;
+
+void fill_visit_args(const cs_params* p, uint32_t j, VisitArgs& v) {
+    const cs_visit_plan& vp = p->visit[j];
+    v.K = vp.K;
+    v.j = static_cast<int32_t>(j);
+    v.gmax = vp.gmax;
+    v.a = p->a[j]; v.b = p->b[j]; v.as = p->as[j]; v.bs = p->bs[j];
+    for (int t = 0; t < 4; ++t) { v.gap[t] = vp.gap[t]; v.A[t] = vp.A[t]; v.As[t] = vp.As[t]; }
+    for (int t = 0; t < CS_MAX_VISITS / 16; ++t) v.code[t] = vp.code[t];
+}
+
 // one launch: the rows `js` (all with ncell running sums) of one group of workers
-template <int WL, int RUN, int NWAVE>
-int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js, int nrows,
-                  uint32_t ncell, hipStream_t stream) {
+template <int WL, int RUN, int NWAVE, typename LIST>
+dim3 visits_grid(const LIST& rows, int nrows, unsigned pieces) {
     constexpr int WPW = 64 / WL;
-    VisitRows rows{};
     int64_t most = 1;
     for (int q = 0; q < nrows; ++q) {
-        const uint32_t j = js[q];
-        const cs_visit_plan& vp = p->visit[j];
-        VisitArgs& v = rows.row[q];
-        v.K = vp.K;
-        v.j = static_cast<int32_t>(j);
-        v.gmax = vp.gmax;
-        v.a = p->a[j]; v.b = p->b[j]; v.as = p->as[j]; v.bs = p->bs[j];
-        for (int t = 0; t < 4; ++t) { v.gap[t] = vp.gap[t]; v.A[t] = vp.A[t]; v.As[t] = vp.As[t]; }
-        for (int t = 0; t < CS_MAX_VISITS / 16; ++t) v.code[t] = vp.code[t];
-        const int64_t chunks = (static_cast<int64_t>(vp.gmax) + RUN - 1) / RUN;
+        const int64_t chunks = (static_cast<int64_t>(rows.row[q].gmax) + RUN - 1) / RUN;
         const int64_t nwaves = (chunks + WPW - 1) / WPW;
         const int64_t ngroups = (nwaves + NWAVE - 1) / NWAVE;
         if (ngroups > most) most = ngroups;
@@ -702,7 +791,13 @@ int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js,
     // the kernel deals sets to the 8 XCDs in blocks of kVisitSetBlock: whole blocks, so that
     // no workgroup takes a second set
     gx = (gx + 8 * kVisitSetBlock - 1) / (8 * kVisitSetBlock) * (8 * kVisitSetBlock);
-    const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(nrows)), block(64 * NWAVE);
+    return dim3(static_cast<unsigned>(gx), static_cast<unsigned>(nrows), pieces);
+}
+
+template <int WL, int RUN, int NWAVE>
+int launch_visits_run(const VisitRows& rows, const VisitWorkers& a, int nrows, unsigned pieces, uint32_t ncell,
+                      hipStream_t stream) {
+    const dim3 grid = visits_grid<WL, RUN, NWAVE>(rows, nrows, pieces), block(64 * NWAVE);
     switch (ncell) {
         case 2: k_accumulate_visits<WL, RUN, NWAVE, 2, VisitRows><<<grid, block, 0, stream>>>(rows, a); break;
         case 3: k_accumulate_visits<WL, RUN, NWAVE, 3, VisitRows><<<grid, block, 0, stream>>>(rows, a); break;
@@ -710,6 +805,35 @@ int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js,
         default: return CS_EINVAL;
     }
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+}
+
+// Wavefronts of a launch with RUN = 16, and whether they leave most of the chip idle (1024 SIMDs):
+// then RUN = 8 gives twice as many, each with half the work per visit, which is what a short
+// vector's time consists of.
+template <int WL, typename LIST>
+bool few_waves(const LIST& rows, int nrows) {
+    int64_t waves = 0;
+    for (int q = 0; q < nrows; ++q) waves += static_cast<int64_t>(rows.row[q].gmax) * WL / 1024 * rows.row[q].pieces;
+    return waves < 2048;
+}
+
+template <int WL, int NWAVE>
+int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js, int nrows,
+                  uint32_t ncell, hipStream_t stream) {
+    VisitRows rows{};
+    uint32_t K[kRowsPerLaunch], n[kRowsPerLaunch];
+    double requests[kRowsPerLaunch];
+    for (int q = 0; q < nrows; ++q) {
+        const cs_visit_plan& vp = p->visit[js[q]];
+        fill_visit_args(p, js[q], rows.row[q]);
+        K[q] = vp.K;
+        requests[q] = (0.5 * vp.ncell + 0.5) * static_cast<double>(vp.gmax);   // as RUN = 8 sends them
+    }
+    const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * nrows / kStreamBytesPerNs;
+    const unsigned most = choose_pieces(nrows, K, requests, kVisitNs8, stream_ns, n);
+    for (int q = 0; q < nrows; ++q) rows.row[q].pieces = n[q];
+    if (few_waves<WL>(rows, nrows)) return launch_visits_run<WL, 8, 1>(rows, a, nrows, most, ncell, stream);
+    return launch_visits_run<WL, 16, NWAVE>(rows, a, nrows, most, ncell, stream);
 }
 
 // the visit list of row j serves vectors of length d, and (unless any_cost) is expected to take
@@ -758,26 +882,29 @@ int for_each_anyc_launch(const cs_params* p, uint32_t nrows_of_sketch, FN fn) {
 
 // one launch: rows js[0 .. n) (all with the same omega) of one group of workers, each along
 // its list for any column count
-template <int WL, int RUN, int NWAVE>
+template <int WL, int NWAVE>
 int launch_visits_anyc(const cs_params* p, const VisitWorkers& a, const uint32_t* js, int n,
                        uint32_t omega, hipStream_t stream) {
-    constexpr int WPW = 64 / WL;
     VisitGapsRows rows{};
-    int64_t most = 1;
+    uint32_t K[kAnycRowsPerLaunch], pieces[kAnycRowsPerLaunch];
+    double requests[kAnycRowsPerLaunch];
     for (int q = 0; q < n; ++q) {
         fill_visit_gaps(p, js[q], rows.row[q]);
-        const int64_t chunks = (static_cast<int64_t>(p->anyc[js[q]].gmax) + RUN - 1) / RUN;
-        const int64_t nwaves = (chunks + WPW - 1) / WPW;
-        const int64_t ngroups = (nwaves + NWAVE - 1) / NWAVE;
-        if (ngroups > most) most = ngroups;
+        K[q] = rows.row[q].K;
+        requests[q] = 2.0 * rows.row[q].omega * static_cast<double>(rows.row[q].gmax);
     }
-    const int64_t cap = 256 * 64 / NWAVE;
-    int64_t gx = most < cap ? most : cap;
-    gx = (gx + 8 * kVisitSetBlock - 1) / (8 * kVisitSetBlock) * (8 * kVisitSetBlock);
-    const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(n)), block(64 * NWAVE);
-    if (omega == 1) k_accumulate_visits<WL, RUN, NWAVE, 2, VisitGapsRows><<<grid, block, 0, stream>>>(rows, a);
-    else if (omega == 2) k_accumulate_visits<WL, RUN, NWAVE, 4, VisitGapsRows><<<grid, block, 0, stream>>>(rows, a);
-    else return CS_EINVAL;
+    const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * n / kStreamBytesPerNs;
+    const unsigned most = choose_pieces(n, K, requests, kVisitNs8, stream_ns, pieces);
+    for (int q = 0; q < n; ++q) rows.row[q].pieces = pieces[q];
+    if (few_waves<WL>(rows, n)) {
+        const dim3 grid = visits_grid<WL, 8, 1>(rows, n, most);
+        if (omega == 1) k_accumulate_visits<WL, 8, 1, 2, VisitGapsRows><<<grid, 64, 0, stream>>>(rows, a);
+        else k_accumulate_visits<WL, 8, 1, 4, VisitGapsRows><<<grid, 64, 0, stream>>>(rows, a);
+    } else {
+        const dim3 grid = visits_grid<WL, 16, NWAVE>(rows, n, most), block(64 * NWAVE);
+        if (omega == 1) k_accumulate_visits<WL, 16, NWAVE, 2, VisitGapsRows><<<grid, block, 0, stream>>>(rows, a);
+        else k_accumulate_visits<WL, 16, NWAVE, 4, VisitGapsRows><<<grid, block, 0, stream>>>(rows, a);
+    }
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
@@ -827,10 +954,10 @@ int launch_accumulate_anyc(const cs_params* p, float* T, int W, const float* con
         vw.scale = scale;
         vw.fold = fold ? 1 : 0;
         const int rc = for_each_anyc_launch(p, p->r, [&](const uint32_t* js, int n, uint32_t omega) {
-            if (nw > 4) return launch_visits_anyc<8, 16, kWavesPerGroupOf8>(p, vw, js, n, omega, stream);
-            if (nw > 2) return launch_visits_anyc<4, 16, 1>(p, vw, js, n, omega, stream);
-            if (nw > 1) return launch_visits_anyc<2, 16, 1>(p, vw, js, n, omega, stream);
-            return launch_visits_anyc<1, 16, 1>(p, vw, js, n, omega, stream);
+            if (nw > 4) return launch_visits_anyc<8, kWavesPerGroupOf8>(p, vw, js, n, omega, stream);
+            if (nw > 2) return launch_visits_anyc<4, 1>(p, vw, js, n, omega, stream);
+            if (nw > 1) return launch_visits_anyc<2, 1>(p, vw, js, n, omega, stream);
+            return launch_visits_anyc<1, 1>(p, vw, js, n, omega, stream);
         });
         if (rc != CS_OK) return rc;
     }
@@ -904,10 +1031,10 @@ int launch_accumulate_walk(const cs_params* p, float* T, int W, const float* con
             const int nrows = nlisted - q0 < kRowsPerLaunch ? nlisted - q0 : kRowsPerLaunch;
             const uint32_t* js = listed + q0;
             int rc;
-            if (nw > 4) rc = launch_visits<8, 16, kWavesPerGroupOf8>(p, vw, js, nrows, ncell, stream);
-            else if (nw > 2) rc = launch_visits<4, 16, 1>(p, vw, js, nrows, ncell, stream);
-            else if (nw > 1) rc = launch_visits<2, 16, 1>(p, vw, js, nrows, ncell, stream);
-            else rc = launch_visits<1, 16, 1>(p, vw, js, nrows, ncell, stream);
+            if (nw > 4) rc = launch_visits<8, kWavesPerGroupOf8>(p, vw, js, nrows, ncell, stream);
+            else if (nw > 2) rc = launch_visits<4, 1>(p, vw, js, nrows, ncell, stream);
+            else if (nw > 1) rc = launch_visits<2, 1>(p, vw, js, nrows, ncell, stream);
+            else rc = launch_visits<1, 1>(p, vw, js, nrows, ncell, stream);
             if (rc != CS_OK) return rc;
         }
         // the other rows: stride walk, all in one launch, the longest chains of visits
