@@ -53,6 +53,10 @@ bool all_rows_listed(const cs_params* p, int64_t d);
 int launch_accumulate_walk(const cs_params* p, float* T, int W, const float* const* g_w,
                            int64_t d, int64_t i0, float scale, bool fold, hipStream_t stream);
 int count_accumulate_walk_launches(const cs_params* p, int W, int64_t d);
+// one vector along visit lists, any column count (one_applies(p, d) must hold); S = float[r][c][cell_floats]
+bool one_applies(const cs_params* p, int64_t d);
+int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const float* g, int64_t d,
+                          int64_t i0, float scale, hipStream_t stream);
 // the same along visit lists for column counts that are not a power of two
 bool anyc_visits_apply(const cs_params* p, int64_t d);
 bool anyc_visits_serve_query(const cs_params* p, int64_t d);

@@ -701,6 +701,7 @@ extern "C" int cs_sketch_accumulate(const cs_params* p, float* S, const float* g
     if (!params_ok(p) || d < 0 || i0 < 0 || i0 > (int64_t)kP61 - d) return CS_EINVAL;
     if (d == 0) return CS_OK;
     if (!S || !g) return CS_EINVAL;
+    if (one_applies(p, d)) return launch_accumulate_one(p, S, 1, g, d, i0, scale, as_stream(stream));
     BatchPtrs ptrs{};
     ptrs.S[0] = S;
     ptrs.g[0] = g;

@@ -908,6 +908,229 @@ int launch_visits_anyc(const cs_params* p, const VisitWorkers& a, const uint32_t
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
+// ---------------------------------------------------------------------------------------
+// The update of one vector (one worker, or the workers' vectors summed beforehand) along visit
+// lists.
+//
+// With one vector nothing is shared between lanes, so a lane owns 4 neighbouring residues: a visit
+// is one 16-byte load, 4 hash steps and 4 NC masked additions in registers, without LDS, and a
+// wavefront reads 1 KB of contiguous addresses.  Loads of the next kOneAhead visits are in flight.
+// At the end the NC sums of a residue, which lie in neighbouring cells, are brought to
+// neighbouring lanes, so that they leave as one request (an aligned 64-byte block touched by an
+// instruction is one) instead of NC.  Bound: r reads of the vector at 6 TB/s and about 25 vector
+// operations per coordinate and row, side by side, then 1.2 gmax r requests at 21 G/s.
+// ---------------------------------------------------------------------------------------
+constexpr int kOneRun = 4;
+constexpr int kOneAhead = 3;
+
+template <int NC, typename LIST>
+__global__ void __launch_bounds__(64)
+k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, uint32_t c,
+                 int cell_floats, int64_t d, int64_t i0, float scale) {
+    constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
+    constexpr int SPAN = 64 * kOneRun;
+    const auto& v = rows.at(blockIdx.y);
+    if (blockIdx.z >= v.pieces) return;
+    const int lane = threadIdx.x;
+    __shared__ float sum_lds[SPAN * NC];
+    __shared__ uint32_t first_lds[SPAN];
+    // hash advances of an any-c list, see k_row_values_visits
+    __shared__ uint64_t adv_b[POW2 ? 1 : CS_ANYC_MAX_VISITS], adv_s[POW2 ? 1 : CS_ANYC_MAX_VISITS];
+    __shared__ uint32_t adv_c[POW2 ? 1 : CS_ANYC_MAX_VISITS];
+    const Columns col = columns_of<POW2>(c);
+    if constexpr (!POW2) {
+        for (uint32_t k = lane; k < v.K; k += 64) {
+            const uint64_t A = mulmod_p(v.a, v.gap[k]);
+            adv_b[k] = A;
+            adv_s[k] = mulmod_p(v.as, v.gap[k]);
+            adv_c[k] = bucket_of<false>(A + 1, col);
+        }
+        __syncthreads();
+    }
+    const uint32_t mask = c - 1u;
+    const uint64_t Aj = v.a, Asj = v.as;
+    const uint32_t Ajc = POW2 ? 0u : bucket_of<false>(Aj + 1, col);
+    auto pick = [](uint32_t code, uint64_t x0, uint64_t x1, uint64_t x2, uint64_t x3) {
+        return code == 0u ? x0 : code == 1u ? x1 : code == 2u ? x2 : x3;
+    };
+    auto code_of = [&](uint32_t k) -> uint32_t {
+        if constexpr (POW2) return (v.code[k >> 4] >> ((k & 15u) * 2u)) & 3u;
+        else return k;
+    };
+    auto gap_of = [&](uint32_t k) -> int64_t {
+        if constexpr (POW2) return static_cast<int64_t>(pick(code_of(k), v.gap[0], v.gap[1], v.gap[2], v.gap[3]));
+        else return static_cast<int64_t>(v.gap[k]);
+    };
+    // a hash value moves on by A; for other column counts its remainder modulo c moves along with
+    // it (A mod c further, p mod c back on a wrap past p), which saves a 64-bit remainder
+    auto advance = [&](uint64_t& y, [[maybe_unused]] uint32_t& rem, uint64_t A, [[maybe_unused]] uint32_t Ac) {
+        const uint64_t t = y + A;
+        y = (t & kP61) + (t >> 61);
+        if constexpr (!POW2) {
+            uint32_t u = rem + Ac;
+            u = u >= c ? u - c : u;
+            const uint32_t u2 = u + (c - v.pc);
+            rem = (t >> 61) == 0 ? u : (u2 >= c ? u2 - c : u2);
+        }
+    };
+    auto cell_of = [&](uint64_t y, [[maybe_unused]] uint32_t rem) -> uint32_t {
+        if constexpr (POW2) return (static_cast<uint32_t>(y) - 1u) & mask;
+        else return rem;
+    };
+    // the running sum of a coordinate in `cell` that started in `first`; >= NC: none (never with a
+    // list of cs_params_init)
+    auto sum_of = [&](uint32_t cell, uint32_t first) -> uint32_t {
+        if constexpr (POW2) {
+            return (cell - first) & mask;
+        } else {
+            const uint32_t t = cell >= first ? cell - first : cell + c - first;
+            if (t < v.omega) return t;
+            const uint32_t t2 = t + v.pc >= c ? t + v.pc - c : t + v.pc;
+            return t2 < v.omega ? v.omega + t2 : static_cast<uint32_t>(NC);
+        }
+    };
+    auto cell_of_sum = [&](uint32_t first, uint32_t q) -> uint32_t {
+        if constexpr (POW2) {
+            return (first + q) & mask;
+        } else {
+            const uint32_t x = q < v.omega ? first + q : first + (q - v.omega) + (c - v.pc);
+            return x >= c ? x - c : x;
+        }
+    };
+    float* __restrict__ Sj = S + static_cast<size_t>(v.j) * c * cell_floats;
+    const int64_t nwaves = (static_cast<int64_t>(v.gmax) + SPAN - 1) / SPAN;
+    const uint32_t k0 = v.K * blockIdx.z / v.pieces, k1 = v.K * (blockIdx.z + 1) / v.pieces;
+    const int64_t s0 = offset_of_visit(k0, gap_of);
+
+    // sets of neighbouring wavefronts go to one XCD, as in k_accumulate_visits
+    constexpr int kBlk = kVisitSetBlock;
+    for (int64_t vi = blockIdx.x; ; vi += gridDim.x) {
+        const int64_t slot = vi >> 3;
+        const int64_t wv = ((slot / kBlk) * 8 + (vi & 7)) * kBlk + slot % kBlk;
+        if ((slot / kBlk) * 8 * kBlk >= nwaves) break;
+        if (wv >= nwaves) continue;
+        const int64_t wave_res = wv * SPAN;
+        const int64_t my_res = wave_res + lane * kOneRun;
+        uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
+        uint32_t rb = POW2 ? 0u : bucket_of<false>(yb, col);
+        uint32_t first[kOneRun];
+        {
+            uint64_t tb = yb;
+            uint32_t tr = rb;
+#pragma unroll
+            for (int m = 0; m < kOneRun; ++m) {
+                first[m] = cell_of(tb, tr);
+                advance(tb, tr, Aj, Ajc);
+            }
+        }
+        if (k0 > 0) {
+            yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res + s0));
+            if constexpr (!POW2) rb = bucket_of<false>(yb, col);
+        }
+        uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res + s0));
+
+        float acc[NC][kOneRun];
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+#pragma unroll
+            for (int m = 0; m < kOneRun; ++m) acc[q][m] = 0.0f;
+
+        // residues from wave_res on that take part in the visit at offset s and exist in the vector
+        auto room_of = [&](int64_t s, int64_t gap) -> int64_t {
+            const int64_t in_gap = gap - wave_res, in_vec = d - s - wave_res;
+            return in_gap < in_vec ? in_gap : in_vec;
+        };
+        uint32_t kl = k0;                               // next visit to request, at offset sl
+        int64_t sl = s0;
+        auto request = [&](float (&buf)[kOneRun]) {
+            if (kl < k1) {
+                const int64_t gap = gap_of(kl), room = room_of(sl, gap);
+                const gfloat_ptr src = (gfloat_ptr)g + sl + my_res;
+                if (room >= SPAN) {
+                    load_floats<kOneRun>(src, buf);
+                } else if (room > 0) {
+                    const int64_t len = room - lane * kOneRun;
+#pragma unroll
+                    for (int m = 0; m < kOneRun; ++m) {
+                        buf[m] = 0.0f;
+                        if (m < len) buf[m] = src[m];
+                    }
+                }
+                sl += gap;
+                ++kl;
+            }
+        };
+        float buf[kOneAhead][kOneRun];
+#pragma unroll
+        for (int u = 0; u < kOneAhead; ++u) request(buf[u]);
+        int64_t s = s0;
+        auto add_up = [&](uint32_t k, const float (&x)[kOneRun]) {
+            const int64_t gap = gap_of(k);
+            if (room_of(s, gap) > 0) {
+                uint64_t tb = yb, ts = ys;
+                uint32_t tr = rb;
+#pragma unroll
+                for (int m = 0; m < kOneRun; ++m) {
+                    const uint32_t cell = cell_of(tb, tr), rel = sum_of(cell, first[m]);
+                    const float val = apply_sign(x[m], sign_flip_of(ts));
+                    uint32_t rest = __float_as_uint(val);
+#pragma unroll
+                    for (int q = 0; q + 1 < NC; ++q) {
+                        const uint32_t t = rel == static_cast<uint32_t>(q) ? __float_as_uint(val) : 0u;
+                        acc[q][m] += __uint_as_float(t);
+                        rest ^= t;
+                    }
+                    const bool stray = rel >= static_cast<uint32_t>(NC);
+                    acc[NC - 1][m] += stray ? 0.0f : __uint_as_float(rest);
+                    if (stray && val != 0.0f)
+                        atomic_add_noret(Sj + static_cast<size_t>(cell) * cell_floats, scale * val);
+                    if (m + 1 < kOneRun) {
+                        advance(tb, tr, Aj, Ajc);
+                        ts = hash_advance(ts, Asj);
+                    }
+                }
+            }
+            s += gap;
+            if constexpr (POW2) {
+                const uint32_t code = code_of(k);
+                advance(yb, rb, pick(code, v.A[0], v.A[1], v.A[2], v.A[3]), 0u);
+                ys = hash_advance(ys, pick(code, v.As[0], v.As[1], v.As[2], v.As[3]));
+            } else {
+                advance(yb, rb, adv_b[k], adv_c[k]);
+                ys = hash_advance(ys, adv_s[k]);
+            }
+        };
+        // (a buffer is refilled where it was read: moving a value that is still on its way would
+        // wait for it)
+        for (uint32_t k = k0; k < k1; k += kOneAhead) {
+#pragma unroll
+            for (int u = 0; u < kOneAhead; ++u) {
+                if (k + u < k1) {
+                    add_up(k + u, buf[u]);
+                    request(buf[u]);
+                }
+            }
+        }
+        // every sum goes to memory once, the NC sums of a residue by neighbouring lanes
+#pragma unroll
+        for (int m = 0; m < kOneRun; ++m) {
+            first_lds[lane * kOneRun + m] = first[m];
+#pragma unroll
+            for (int q = 0; q < NC; ++q) sum_lds[(lane * kOneRun + m) * NC + q] = acc[q][m];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < kOneRun * NC; ++t) {
+            const uint32_t item = t * 64 + lane;
+            const float sum = sum_lds[item];
+            if (sum != 0.0f)
+                atomic_add_noret(Sj + static_cast<size_t>(cell_of_sum(first_lds[item / NC], item % NC)) * cell_floats,
+                                 scale * sum);
+        }
+        __syncthreads();
+    }
+}
+
 }  // namespace
 
 // Every row has a list for this column count and vector length, and by its own estimate the
@@ -944,9 +1167,15 @@ int launch_accumulate_anyc(const cs_params* p, float* T, int W, const float* con
     const size_t row_floats = static_cast<size_t>(p->c) * kGroup;
     for (int w0 = 0; w0 < W; w0 += kGroup) {
         const int nw = (W - w0 < kGroup) ? (W - w0) : kGroup;
+        float* Tg = fold ? T : T + static_cast<size_t>(w0 / kGroup) * p->r * row_floats;
+        if (nw == 1 && one_applies(p, d)) {
+            const int rc = launch_accumulate_one(p, Tg, fold ? 1 : kGroup, g_w[w0], d, i0, scale, stream);
+            if (rc != CS_OK) return rc;
+            continue;
+        }
         VisitWorkers vw{};
         for (int w = 0; w < nw; ++w) vw.g[w] = g_w[w0 + w];
-        vw.T = fold ? T : T + static_cast<size_t>(w0 / kGroup) * p->r * row_floats;
+        vw.T = Tg;
         vw.d = d;
         vw.i0 = i0;
         vw.c = p->c;
@@ -992,15 +1221,84 @@ bool all_rows_listed(const cs_params* p, int64_t d) {
     return true;
 }
 
+// The lists serve the update of one vector: every row has one that covers d, and all of them
+// together send fewer requests than the lattice form (about one per 8 to 15 coordinates).
+bool one_applies(const cs_params* p, int64_t d) {
+    double residues = 0.0;
+    if (p->c_pow2) {
+        if (!all_rows_listed(p, d)) return false;
+        for (uint32_t j = 0; j < p->r; ++j) residues += static_cast<double>(p->visit[j].gmax);
+    } else {
+        if (!anyc_visits_apply(p, d)) return false;
+        for (uint32_t j = 0; j < p->r; ++j) residues += static_cast<double>(p->anyc[j].gmax);
+    }
+    return 1.2 * residues <= static_cast<double>(p->r) * static_cast<double>(d) / 8.0;
+}
+
+// S = float[r][c][cell_floats]: the table itself (1) or one worker's slot of a bundle (kGroup)
+int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const float* g, int64_t d,
+                          int64_t i0, float scale, hipStream_t stream) {
+    // grid of a launch of n rows, whose pieces are chosen here
+    auto shape = [&](auto& rows, int n) {
+        uint32_t K[kRowsPerLaunch], pieces[kRowsPerLaunch];
+        double requests[kRowsPerLaunch];
+        for (int q = 0; q < n; ++q) {
+            K[q] = rows.row[q].K;
+            requests[q] = 1.2 * static_cast<double>(rows.row[q].gmax);
+        }
+        const double stream_ns = 4.0 * static_cast<double>(d) * n / kStreamBytesPerNs;
+        const unsigned most = choose_pieces(n, K, requests, kVisitNsOne, stream_ns, pieces);
+        for (int q = 0; q < n; ++q) rows.row[q].pieces = pieces[q];
+        return visits_grid<1, kOneRun, 1>(rows, n, most);
+    };
+    if (!p->c_pow2)
+        return for_each_anyc_launch(p, p->r, [&](const uint32_t* js, int n, uint32_t omega) {
+            VisitGapsRows rows{};
+            for (int q = 0; q < n; ++q) fill_visit_gaps(p, js[q], rows.row[q]);
+            const dim3 grid = shape(rows, n);
+            if (omega == 1) k_accumulate_one<2, VisitGapsRows><<<grid, 64, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale);
+            else k_accumulate_one<4, VisitGapsRows><<<grid, 64, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale);
+            return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+        });
+    uint32_t order[CS_MAX_R], ncell = 2;
+    for (uint32_t j = 0; j < p->r; ++j) {              // the longest lists first
+        if (p->visit[j].ncell > ncell) ncell = p->visit[j].ncell;
+        int at = static_cast<int>(j);
+        for (; at > 0 && p->visit[order[at - 1]].K < p->visit[j].K; --at) order[at] = order[at - 1];
+        order[at] = j;
+    }
+    for (uint32_t q0 = 0; q0 < p->r; q0 += kRowsPerLaunch) {
+        const int n = p->r - q0 < kRowsPerLaunch ? static_cast<int>(p->r - q0) : kRowsPerLaunch;
+        VisitRows rows{};
+        for (int q = 0; q < n; ++q) fill_visit_args(p, order[q0 + q], rows.row[q]);
+        const dim3 grid = shape(rows, n);
+        switch (ncell) {
+            case 2: k_accumulate_one<2, VisitRows><<<grid, 64, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
+            case 3: k_accumulate_one<3, VisitRows><<<grid, 64, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
+            case 4: k_accumulate_one<4, VisitRows><<<grid, 64, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
+            default: return CS_EINVAL;
+        }
+        if (hipGetLastError() != hipSuccess) return CS_EHIP;
+    }
+    return CS_OK;
+}
+
 // fold: T is one table float[r][c] that receives the sum over all W workers (all_rows_listed
 // must hold); otherwise T is the bundle and every worker has its own slot.
 int launch_accumulate_walk(const cs_params* p, float* T, int W, const float* const* g_w,
                            int64_t d, int64_t i0, float scale, bool fold, hipStream_t stream) {
     if (fold && !all_rows_listed(p, d)) return CS_EINVAL;
     const size_t row_floats = static_cast<size_t>(p->c) * kGroup;
+    bool one = W % kGroup == 1 && one_applies(p, d);   // a group of one worker: a single vector
+    for (uint32_t j = 0; j < p->r; ++j) one = one && visits_apply(p, j, d, fold);
     for (int w0 = 0; w0 < W; w0 += kGroup) {
         const int nw = (W - w0 < kGroup) ? (W - w0) : kGroup;
         float* Tg = fold ? T : T + static_cast<size_t>(w0 / kGroup) * p->r * row_floats;
+        if (nw == 1 && one) {
+            const int rc = launch_accumulate_one(p, Tg, fold ? 1 : kGroup, g_w[w0], d, i0, scale, stream);
+            if (rc != CS_OK) return rc;
+            continue;
+        }
         VisitWorkers vw{};
         for (int w = 0; w < nw; ++w) vw.g[w] = g_w[w0 + w];
         vw.T = Tg;
