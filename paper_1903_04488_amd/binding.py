@@ -154,6 +154,8 @@ _SIGNATURES = {
                            ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p],
     "cs_gather_exact": [ctypes.POINTER(ctypes.c_void_p), ctypes.c_int32, ctypes.c_void_p,
                         ctypes.c_int64, ctypes.c_float, ctypes.c_void_p, ctypes.c_void_p],
+    "cs_vectors_sum": [ctypes.POINTER(ctypes.c_void_p), ctypes.c_int32, ctypes.c_int64,
+                       ctypes.c_float, ctypes.c_void_p, ctypes.c_void_p],
     "cs_dense_momentum": [ctypes.POINTER(ctypes.c_void_p), ctypes.POINTER(ctypes.c_void_p),
                           ctypes.POINTER(ctypes.c_void_p), ctypes.c_int32, ctypes.c_int64,
                           ctypes.c_float, ctypes.c_void_p],
@@ -566,6 +568,16 @@ def cs_gather_exact(vec, idx, out, alpha: float = 1.0):
     _check(load_library().cs_gather_exact(
         _ptr_array(vec, torch.float32, "vec", d), len(vec), _dev(idx, torch.int64, "idx"), k,
         alpha, _dev(out, torch.float32, "out", k), _stream(out)), "cs_gather_exact")
+
+
+def cs_vectors_sum(x_w, out, alpha: float = 1.0):
+    W = len(x_w)
+    if W == 0:
+        raise CsError("x_w must be a non-empty list")
+    d = x_w[0].numel()
+    _check(load_library().cs_vectors_sum(
+        _ptr_array(x_w, torch.float32, "x_w", d), W, d, alpha, _dev(out, torch.float32, "out", d),
+        _stream(out)), "cs_vectors_sum")
 
 
 def cs_dense_momentum(u_w, v_w, g_w, rho: float):

@@ -525,6 +525,57 @@ k_gather(GatherPtrs ptrs, int nw, const int64_t* __restrict__ idx, int64_t k, fl
     }
 }
 
+// out = alpha * (sum of W vectors), added up in binary64 and rounded once.  Folded workers are
+// summed before they are sketched: the sketch is linear, W d floats are then read once
+// instead of r times.  Bound by that read; 4 vectors' 16-byte pieces are in flight per thread.
+// More vectors than one launch takes: later launches add to out, which then holds the unscaled sum.
+constexpr int kMaxSum = 256;
+struct SumPtrs {
+    const float* x[kMaxSum];
+};
+
+template <bool VEC>
+__global__ void __launch_bounds__(kBlock)
+k_vectors_sum(SumPtrs ptrs, int nw, int64_t d, float alpha, float* __restrict__ out, int first_launch) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
+    const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    int64_t done = 0;
+    if (VEC) {
+        const int64_t n4 = d / 4;
+        for (int64_t t = t0; t < n4; t += stride) {
+            double s[4] = {0.0, 0.0, 0.0, 0.0};
+            auto add = [&](const f4& u) {
+                s[0] += static_cast<double>(u.x); s[1] += static_cast<double>(u.y);
+                s[2] += static_cast<double>(u.z); s[3] += static_cast<double>(u.w);
+            };
+            if (!first_launch) add(reinterpret_cast<const f4*>(out)[t]);
+            int w = 0;
+            for (; w + 4 <= nw; w += 4) {
+                f4 u[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    u[q] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(ptrs.x[w + q]) + t);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) add(u[q]);
+            }
+            for (; w < nw; ++w) add(__builtin_nontemporal_load(reinterpret_cast<const f4*>(ptrs.x[w]) + t));
+            const double a = static_cast<double>(alpha);
+            f4 o;
+            o.x = static_cast<float>(a * s[0]); o.y = static_cast<float>(a * s[1]);
+            o.z = static_cast<float>(a * s[2]); o.w = static_cast<float>(a * s[3]);
+            reinterpret_cast<f4*>(out)[t] = o;
+        }
+        done = n4 * 4;
+    }
+    for (int64_t t = done + t0; t < d; t += stride) {
+        double s = first_launch ? 0.0 : static_cast<double>(out[t]);
+#pragma unroll 4
+        for (int w = 0; w < nw; ++w) s += static_cast<double>(ptrs.x[w][t]);
+        out[t] = static_cast<float>(static_cast<double>(alpha) * s);
+    }
+}
+
 template <int FMT>
 __global__ void __launch_bounds__(kBlock)
 k_quantize16(const float* __restrict__ x, int64_t n, uint16_t* __restrict__ out) {
@@ -1038,6 +1089,28 @@ extern "C" int cs_gather_exact(const float* const* vec, int32_t W, const int64_t
         for (int w = 0; w < nw; ++w) ptrs.vec[w] = vec[w0 + w];
         k_gather<<<grid_for(k), kBlock, 0, as_stream(stream)>>>(ptrs, nw, idx, k, alpha, out,
                                                                 w0 == 0, w0 + nw == W);
+        if (launch_status() != CS_OK) return CS_EHIP;
+    }
+    return CS_OK;
+}
+
+extern "C" int cs_vectors_sum(const float* const* x_w, int32_t W, int64_t d, float alpha, float* out,
+                              void* stream) {
+    if (!x_w || W < 1 || d < 0 || !out) return CS_EINVAL;
+    bool vec = reinterpret_cast<uintptr_t>(out) % 16 == 0;
+    for (int w = 0; w < W; ++w) {
+        if (!x_w[w] || x_w[w] == out) return CS_EINVAL;
+        vec = vec && reinterpret_cast<uintptr_t>(x_w[w]) % 16 == 0;
+    }
+    if (d == 0) return CS_OK;
+    for (int w0 = 0; w0 < W; w0 += kMaxSum) {
+        const int nw = (W - w0 < kMaxSum) ? (W - w0) : kMaxSum;
+        SumPtrs ptrs{};
+        for (int w = 0; w < nw; ++w) ptrs.x[w] = x_w[w0 + w];
+        const unsigned grid = grid_for(vec ? (d + 3) / 4 : d, kBlock, 256 * 32);
+        const float a = w0 + nw == W ? alpha : 1.0f;
+        if (vec) k_vectors_sum<true><<<grid, kBlock, 0, as_stream(stream)>>>(ptrs, nw, d, a, out, w0 == 0);
+        else k_vectors_sum<false><<<grid, kBlock, 0, as_stream(stream)>>>(ptrs, nw, d, a, out, w0 == 0);
         if (launch_status() != CS_OK) return CS_EHIP;
     }
     return CS_OK;

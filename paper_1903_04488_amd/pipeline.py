@@ -2,13 +2,13 @@
 
 Per step (Alg. 3 of the paper, with the W workers simulated on the one device):
     worker sketches   S^w = S(g^w)                cs_sketch_accumulate_bundle  (T[w/8][j][b][w%8])
-    aggregate         S_t = (1/W) sum_w S^w       cs_bundle_merge
-                      (fold_workers: both at once, S_t += (1/W) S(g^w), cs_sketch_accumulate_sum)
+    aggregate         S_t = (1/W) sum_w S^w       cs_bundle_merge[_momentum]
+                      (fold_workers: S_t = S((1/W) sum_w g^w), cs_vectors_sum, cs_sketch_accumulate)
     momentum, error   S_u = rho S_u + S_t ; S_v += S_u      cs_sketch_momentum   (stateful only)
     query all         est = estimate(S_v or S_t)  cs_sketch_estimate
-    choose largest    idx = top-k |est|           cs_heavy_hitters_topk
+    choose largest    idx = top-k |est|           cs_heavy_hitters_topk_kept
     second round      x = (1/W) sum_w g^w[idx]    cs_gather_exact
-    feedback          S_v -= S(est[idx]) ; S_u -= S(estimate(S_u, idx))   cs_sketch_feedback (stateful)
+    feedback          S_v -= S(est[idx]) ; S_u -= S(estimate(S_u, idx))   cs_sketch_feedback_pair (stateful)
 Every arithmetic step runs inside libcsketch.so; this class only owns tensors.
 """
 from __future__ import annotations
@@ -23,8 +23,9 @@ class HotPath:
                  rho: float | None = None, device="cuda:0", P: int = 1, fold_workers: bool = False):
         """P > 1: the sketch is queried for the top P*k coordinates, the workers for their exact
         values, and the k largest exact sums are kept (Alg. 3 as the paper trains with it).
-        fold_workers: the workers, which share this GPU, are summed as they are sketched
-        (cs_sketch_accumulate_sum straight into S_t): no worker tables, no merge."""
+        fold_workers: the workers, which share this GPU, are summed before they are sketched
+        (every vector is read once; the sum goes into d floats of scratch, then straight into
+        S_t): no worker tables, no merge."""
         self.d, self.W, self.r, self.c, self.k = d, W, r, c, k
         self.P = P
         self.fold_workers = fold_workers
@@ -56,6 +57,11 @@ class HotPath:
         n_est = B.cs_estimate_workspace_bytes(self.params, d)
         self.est_ws = (torch.empty(n_est, dtype=torch.uint8, device=self.device)
                        if n_est else None)
+        # the workers' mean, when they are folded: the scratch of the query is free until then
+        self.g_mean = None
+        if fold_workers and W > 1:
+            self.g_mean = (self.est_ws[:4 * d].view(torch.float32) if n_est >= 4 * d
+                           else torch.empty(d, **f32))
 
     # individual stages (bench.py times them separately) ---------------------------------
     def worker_table(self, w: int):
@@ -66,7 +72,11 @@ class HotPath:
     def accumulate(self, g_w):
         if self.fold_workers:
             B.cs_sketch_zero(self.params, self.S_t)
-            B.cs_sketch_accumulate_sum(self.params, self.S_t, g_w, scale=1.0 / self.W)
+            if self.W == 1:
+                B.cs_sketch_accumulate(self.params, self.S_t, g_w[0])
+                return
+            B.cs_vectors_sum(g_w, self.g_mean, alpha=1.0 / self.W)
+            B.cs_sketch_accumulate(self.params, self.S_t, self.g_mean)
             return
         B.cs_bundle_zero(self.params, self.T, self.W)
         B.cs_sketch_accumulate_bundle(self.params, self.T, g_w)
