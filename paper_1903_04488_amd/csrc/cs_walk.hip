@@ -275,14 +275,18 @@ int launch_walk(const cs_params* p, const WalkArgs& a, int nrows, hipStream_t st
 struct VisitArgs {
     uint32_t K;                  // visits
     int32_t j;                   // sketch row
-    uint32_t pieces;             // the visits are shared out among this many wavefronts (blockIdx.z)
+    uint32_t pieces;             // the visits are shared out among this many wavefronts
+    uint32_t blocks;             // workgroups of one piece
     uint64_t gmax;
     uint64_t a, b, as, bs;       // hash constants of row j
     uint64_t gap[4], A[4], As[4];
     uint32_t code[CS_MAX_VISITS / 16];
 };
-// The rows of a sketch are updated by one launch (blockIdx.y = row of the set): their serial
-// chains of visits overlap, and there are fewer launch tails.
+// The rows of a sketch are updated by one launch: their serial chains of visits overlap, and there
+// are fewer launch tails.  Row q has the workgroups first[q] .. first[q] + blocks * pieces - 1: the
+// rows of one sketch differ in gmax and in pieces by a factor of 30, so that a grid of
+// (most blocks, rows, most pieces) is nearly all empty workgroups for a short vector (32 000 for 2 500
+// at d = 30 403, c = 256, which took most of 19 us).
 constexpr int kRowsPerLaunch = 8;
 // Neighbouring sets of walkers that go to the same XCD (the kernel deals sets to XCDs in blocks
 // of this many, so that an XCD reads a few KB of contiguous addresses per visit).  Five, not a
@@ -291,6 +295,7 @@ constexpr int kRowsPerLaunch = 8;
 // (1, 2, 4, 16: slower; 3, 5, 6, 8: within 0.5 % of each other).
 constexpr int kVisitSetBlock = 5;
 struct VisitRows {
+    uint32_t first[kRowsPerLaunch];              // ~0: no such row
     VisitArgs row[kRowsPerLaunch];
     __device__ __forceinline__ const VisitArgs& at(unsigned y) const { return row[y]; }
 };
@@ -301,7 +306,7 @@ struct VisitRows {
 struct VisitGaps {
     uint32_t K;
     int32_t j;
-    uint32_t pieces;
+    uint32_t pieces, blocks;
     uint64_t gmax;
     uint64_t a, b, as, bs;
     uint32_t omega;              // running sums: omega cells from the first one, omega more after a wrap
@@ -310,6 +315,7 @@ struct VisitGaps {
 };
 constexpr int kAnycRowsPerLaunch = 6;
 struct VisitGapsRows {
+    uint32_t first[kAnycRowsPerLaunch];          // ~0: no such row
     VisitGaps row[kAnycRowsPerLaunch];
     __device__ __forceinline__ const VisitGaps& at(unsigned y) const { return row[y]; }
 };
@@ -363,6 +369,16 @@ __device__ __forceinline__ int64_t offset_of_visit(uint32_t k, GAP gap_of) {
     return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
 }
 
+// the row that this workgroup works for
+template <typename LIST>
+__device__ __forceinline__ unsigned row_of_block(const LIST& rows) {
+    constexpr int N = sizeof(rows.first) / sizeof(rows.first[0]);
+    unsigned q = 0;
+#pragma unroll
+    for (int t = 1; t < N; ++t) q += blockIdx.x >= rows.first[t] ? 1u : 0u;
+    return q;
+}
+
 // LIST = VisitRows (power-of-two column counts: three gaps and 2-bit codes, the NC cells are
 // neighbours) or VisitGapsRows (any column count: gaps one by one, NC = 2 omega cells of which
 // the second half lies p mod c cells back).
@@ -370,8 +386,10 @@ template <int WL, int RUN, int NWAVE, int NC, typename LIST>
 __global__ void __launch_bounds__(64 * NWAVE)
 k_accumulate_visits(LIST rows, VisitWorkers a) {
     constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
-    const auto& v = rows.at(blockIdx.y);
-    if (blockIdx.z >= v.pieces) return;
+    const unsigned row = row_of_block(rows);
+    const auto& v = rows.at(row);
+    const uint32_t piece = (blockIdx.x - rows.first[row]) / v.blocks;
+    const uint32_t block = (blockIdx.x - rows.first[row]) % v.blocks;
     constexpr int WPW = 64 / WL;                       // walkers per wavefront
     constexpr int PPL = RUN / WL;                      // hash values each lane computes
     constexpr int SPAN = WPW * RUN;                    // residues a wavefront owns
@@ -491,9 +509,9 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
     // blocks rather than as eight long ranges: every XCD gets the same mix.
     const int64_t ngroups = (nwaves + NWAVE - 1) / NWAVE;
     // my piece of the chain of visits: k0 .. k1 - 1, the first of them at offset s0
-    const uint32_t k0 = v.K * blockIdx.z / v.pieces, k1 = v.K * (blockIdx.z + 1) / v.pieces;
+    const uint32_t k0 = v.K * piece / v.pieces, k1 = v.K * (piece + 1) / v.pieces;
     const int64_t s0 = offset_of_visit(k0, [&](uint32_t k) { return gap_of(code_of(k)); });
-    for (int64_t vi = blockIdx.x; ; vi += gridDim.x) {
+    for (int64_t vi = block; ; vi += v.blocks) {
         const int64_t slot = vi >> 3;
         const int64_t set = ((slot / kSetBlock) * 8 + (vi & 7)) * kSetBlock + slot % kSetBlock;
         if ((slot / kSetBlock) * 8 * kSetBlock >= ngroups) break;
@@ -739,31 +757,40 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
 // every piece sends its own requests (requests[q] per piece of row q) at 24 G/s: the common
 // length of the pieces with the smallest sum of the two is taken.  stream_ns: what the launch
 // takes to read its vectors in any case, so that long vectors, which fill the chip, stay whole.
-// Returns the largest number of pieces.
 constexpr uint32_t kMaxPieces = 32;
-unsigned choose_pieces(int nrows, const uint32_t* K, const double* requests, double visit_ns, double stream_ns,
-                       uint32_t* pieces) {
+template <typename LIST>
+void choose_pieces(LIST& rows, int nrows, const double* requests, double visit_ns, double stream_ns) {
     uint32_t longest = 1;
-    for (int q = 0; q < nrows; ++q) longest = K[q] > longest ? K[q] : longest;
+    for (int q = 0; q < nrows; ++q) longest = rows.row[q].K > longest ? rows.row[q].K : longest;
     double best = 1e300, best_len = longest;
     for (double len = longest; len >= 3.0; len *= 0.8) {
         double cost = len * visit_ns > stream_ns ? len * visit_ns : stream_ns;
-        for (int q = 0; q < nrows; ++q) cost += ceil(K[q] / len) * requests[q] / 24.0;
+        for (int q = 0; q < nrows; ++q) cost += ceil(rows.row[q].K / len) * requests[q] / 24.0;
         if (cost < best) { best = cost; best_len = len; }
     }
-    unsigned most = 1;
     for (int q = 0; q < nrows; ++q) {
-        double n = ceil(K[q] / best_len);
-        if (n > kMaxPieces) n = kMaxPieces;
-        pieces[q] = n < 1.0 ? 1u : static_cast<uint32_t>(n);
-        if (pieces[q] > most) most = pieces[q];
+        const double n = ceil(rows.row[q].K / best_len);
+        rows.row[q].pieces = n < 1.0 ? 1u : n > kMaxPieces ? kMaxPieces : static_cast<uint32_t>(n);
     }
-    return most;
 }
 
-// a turn of the walkers of 8 (4, 2) workers with RUN = 8, and of a single vector
-constexpr double kVisitNs8 = 700.0, kVisitNsOne = 500.0;
+// a turn of the walkers of 8 (4, 2) workers with RUN = 8 and with RUN = 16, and of a single vector
+// (priced as RUN = 8, chains of 316 visits of 4 workers stayed whole: d = 22.4 M, c = 65 536, 738 us a step for 596)
+constexpr double kVisitNs8 = 700.0, kVisitNs16 = 1300.0, kVisitNsOne = 500.0;
 constexpr double kStreamBytesPerNs = 5000.0;
+
+// The same for a group of workers; true = RUN = 8.
+// RUN = 16 with few wavefronts leaves most of the chip idle (1024 SIMDs): RUN = 8 then gives twice as
+// many, each with half the work per visit, which is what a short vector's time consists of.
+template <int WL, typename LIST>
+bool choose_run8(LIST& rows, int nrows, const double* requests, double stream_ns) {
+    choose_pieces(rows, nrows, requests, kVisitNs8, stream_ns);
+    int64_t waves = 0;                                   // with RUN = 16
+    for (int q = 0; q < nrows; ++q) waves += static_cast<int64_t>(rows.row[q].gmax) * WL / 1024 * rows.row[q].pieces;
+    if (waves < 2048) return true;
+    choose_pieces(rows, nrows, requests, kVisitNs16, stream_ns);
+    return false;
+}
 
 void fill_visit_args(const cs_params* p, uint32_t j, VisitArgs& v) {
     const cs_visit_plan& vp = p->visit[j];
@@ -775,29 +802,34 @@ void fill_visit_args(const cs_params* p, uint32_t j, VisitArgs& v) {
     for (int t = 0; t < CS_MAX_VISITS / 16; ++t) v.code[t] = vp.code[t];
 }
 
-// one launch: the rows `js` (all with ncell running sums) of one group of workers
+// Workgroups of a launch of nrows rows whose gmax and pieces are set; fills in `blocks` and `first`.
 template <int WL, int RUN, int NWAVE, typename LIST>
-dim3 visits_grid(const LIST& rows, int nrows, unsigned pieces) {
+unsigned visits_grid(LIST& rows, int nrows) {
     constexpr int WPW = 64 / WL;
-    int64_t most = 1;
+    constexpr int N = sizeof(rows.first) / sizeof(rows.first[0]);
+    unsigned total = 0;
     for (int q = 0; q < nrows; ++q) {
         const int64_t chunks = (static_cast<int64_t>(rows.row[q].gmax) + RUN - 1) / RUN;
         const int64_t nwaves = (chunks + WPW - 1) / WPW;
         const int64_t ngroups = (nwaves + NWAVE - 1) / NWAVE;
-        if (ngroups > most) most = ngroups;
+        const int64_t cap = 256 * 64 / NWAVE;              // enough to fill the chip several times over
+        int64_t n = ngroups < cap ? ngroups : cap;
+        // the kernel deals sets to the 8 XCDs in blocks of kVisitSetBlock: whole blocks, so that
+        // no workgroup takes a second set
+        n = (n + 8 * kVisitSetBlock - 1) / (8 * kVisitSetBlock) * (8 * kVisitSetBlock);
+        rows.row[q].blocks = static_cast<uint32_t>(n);
+        rows.first[q] = total;
+        total += rows.row[q].blocks * rows.row[q].pieces;
     }
-    const int64_t cap = 256 * 64 / NWAVE;
-    int64_t gx = most < cap ? most : cap;
-    // the kernel deals sets to the 8 XCDs in blocks of kVisitSetBlock: whole blocks, so that
-    // no workgroup takes a second set
-    gx = (gx + 8 * kVisitSetBlock - 1) / (8 * kVisitSetBlock) * (8 * kVisitSetBlock);
-    return dim3(static_cast<unsigned>(gx), static_cast<unsigned>(nrows), pieces);
+    for (int q = nrows; q < N; ++q) rows.first[q] = ~0u;
+    return total;
 }
 
+// one launch: rows that all have ncell running sums, of one group of workers
 template <int WL, int RUN, int NWAVE>
-int launch_visits_run(const VisitRows& rows, const VisitWorkers& a, int nrows, unsigned pieces, uint32_t ncell,
+int launch_visits_run(VisitRows& rows, const VisitWorkers& a, int nrows, uint32_t ncell,
                       hipStream_t stream) {
-    const dim3 grid = visits_grid<WL, RUN, NWAVE>(rows, nrows, pieces), block(64 * NWAVE);
+    const dim3 grid(visits_grid<WL, RUN, NWAVE>(rows, nrows)), block(64 * NWAVE);
     switch (ncell) {
         case 2: k_accumulate_visits<WL, RUN, NWAVE, 2, VisitRows><<<grid, block, 0, stream>>>(rows, a); break;
         case 3: k_accumulate_visits<WL, RUN, NWAVE, 3, VisitRows><<<grid, block, 0, stream>>>(rows, a); break;
@@ -807,33 +839,19 @@ int launch_visits_run(const VisitRows& rows, const VisitWorkers& a, int nrows, u
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
-// Wavefronts of a launch with RUN = 16, and whether they leave most of the chip idle (1024 SIMDs):
-// then RUN = 8 gives twice as many, each with half the work per visit, which is what a short
-// vector's time consists of.
-template <int WL, typename LIST>
-bool few_waves(const LIST& rows, int nrows) {
-    int64_t waves = 0;
-    for (int q = 0; q < nrows; ++q) waves += static_cast<int64_t>(rows.row[q].gmax) * WL / 1024 * rows.row[q].pieces;
-    return waves < 2048;
-}
-
 template <int WL, int NWAVE>
 int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js, int nrows,
                   uint32_t ncell, hipStream_t stream) {
     VisitRows rows{};
-    uint32_t K[kRowsPerLaunch], n[kRowsPerLaunch];
     double requests[kRowsPerLaunch];
     for (int q = 0; q < nrows; ++q) {
         const cs_visit_plan& vp = p->visit[js[q]];
         fill_visit_args(p, js[q], rows.row[q]);
-        K[q] = vp.K;
         requests[q] = (0.5 * vp.ncell + 0.5) * static_cast<double>(vp.gmax);   // as RUN = 8 sends them
     }
     const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * nrows / kStreamBytesPerNs;
-    const unsigned most = choose_pieces(nrows, K, requests, kVisitNs8, stream_ns, n);
-    for (int q = 0; q < nrows; ++q) rows.row[q].pieces = n[q];
-    if (few_waves<WL>(rows, nrows)) return launch_visits_run<WL, 8, 1>(rows, a, nrows, most, ncell, stream);
-    return launch_visits_run<WL, 16, NWAVE>(rows, a, nrows, most, ncell, stream);
+    if (choose_run8<WL>(rows, nrows, requests, stream_ns)) return launch_visits_run<WL, 8, 1>(rows, a, nrows, ncell, stream);
+    return launch_visits_run<WL, 16, NWAVE>(rows, a, nrows, ncell, stream);
 }
 
 // the visit list of row j serves vectors of length d, and (unless any_cost) is expected to take
@@ -886,22 +904,18 @@ template <int WL, int NWAVE>
 int launch_visits_anyc(const cs_params* p, const VisitWorkers& a, const uint32_t* js, int n,
                        uint32_t omega, hipStream_t stream) {
     VisitGapsRows rows{};
-    uint32_t K[kAnycRowsPerLaunch], pieces[kAnycRowsPerLaunch];
     double requests[kAnycRowsPerLaunch];
     for (int q = 0; q < n; ++q) {
         fill_visit_gaps(p, js[q], rows.row[q]);
-        K[q] = rows.row[q].K;
         requests[q] = 2.0 * rows.row[q].omega * static_cast<double>(rows.row[q].gmax);
     }
     const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * n / kStreamBytesPerNs;
-    const unsigned most = choose_pieces(n, K, requests, kVisitNs8, stream_ns, pieces);
-    for (int q = 0; q < n; ++q) rows.row[q].pieces = pieces[q];
-    if (few_waves<WL>(rows, n)) {
-        const dim3 grid = visits_grid<WL, 8, 1>(rows, n, most);
+    if (choose_run8<WL>(rows, n, requests, stream_ns)) {
+        const dim3 grid(visits_grid<WL, 8, 1>(rows, n));
         if (omega == 1) k_accumulate_visits<WL, 8, 1, 2, VisitGapsRows><<<grid, 64, 0, stream>>>(rows, a);
         else k_accumulate_visits<WL, 8, 1, 4, VisitGapsRows><<<grid, 64, 0, stream>>>(rows, a);
     } else {
-        const dim3 grid = visits_grid<WL, 16, NWAVE>(rows, n, most), block(64 * NWAVE);
+        const dim3 grid(visits_grid<WL, 16, NWAVE>(rows, n)), block(64 * NWAVE);
         if (omega == 1) k_accumulate_visits<WL, 16, NWAVE, 2, VisitGapsRows><<<grid, block, 0, stream>>>(rows, a);
         else k_accumulate_visits<WL, 16, NWAVE, 4, VisitGapsRows><<<grid, block, 0, stream>>>(rows, a);
     }
@@ -929,8 +943,10 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
                  int cell_floats, int64_t d, int64_t i0, float scale) {
     constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
     constexpr int SPAN = 64 * kOneRun;
-    const auto& v = rows.at(blockIdx.y);
-    if (blockIdx.z >= v.pieces) return;
+    const unsigned row = row_of_block(rows);
+    const auto& v = rows.at(row);
+    const uint32_t piece = (blockIdx.x - rows.first[row]) / v.blocks;
+    const uint32_t block = (blockIdx.x - rows.first[row]) % v.blocks;
     const int lane = threadIdx.x;
     __shared__ float sum_lds[SPAN * NC];
     __shared__ uint32_t first_lds[SPAN];
@@ -999,12 +1015,12 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
     };
     float* __restrict__ Sj = S + static_cast<size_t>(v.j) * c * cell_floats;
     const int64_t nwaves = (static_cast<int64_t>(v.gmax) + SPAN - 1) / SPAN;
-    const uint32_t k0 = v.K * blockIdx.z / v.pieces, k1 = v.K * (blockIdx.z + 1) / v.pieces;
+    const uint32_t k0 = v.K * piece / v.pieces, k1 = v.K * (piece + 1) / v.pieces;
     const int64_t s0 = offset_of_visit(k0, gap_of);
 
     // sets of neighbouring wavefronts go to one XCD, as in k_accumulate_visits
     constexpr int kBlk = kVisitSetBlock;
-    for (int64_t vi = blockIdx.x; ; vi += gridDim.x) {
+    for (int64_t vi = block; ; vi += v.blocks) {
         const int64_t slot = vi >> 3;
         const int64_t wv = ((slot / kBlk) * 8 + (vi & 7)) * kBlk + slot % kBlk;
         if ((slot / kBlk) * 8 * kBlk >= nwaves) break;
@@ -1240,16 +1256,11 @@ int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const f
                           int64_t i0, float scale, hipStream_t stream) {
     // grid of a launch of n rows, whose pieces are chosen here
     auto shape = [&](auto& rows, int n) {
-        uint32_t K[kRowsPerLaunch], pieces[kRowsPerLaunch];
         double requests[kRowsPerLaunch];
-        for (int q = 0; q < n; ++q) {
-            K[q] = rows.row[q].K;
-            requests[q] = 1.2 * static_cast<double>(rows.row[q].gmax);
-        }
+        for (int q = 0; q < n; ++q) requests[q] = 1.2 * static_cast<double>(rows.row[q].gmax);
         const double stream_ns = 4.0 * static_cast<double>(d) * n / kStreamBytesPerNs;
-        const unsigned most = choose_pieces(n, K, requests, kVisitNsOne, stream_ns, pieces);
-        for (int q = 0; q < n; ++q) rows.row[q].pieces = pieces[q];
-        return visits_grid<1, kOneRun, 1>(rows, n, most);
+        choose_pieces(rows, n, requests, kVisitNsOne, stream_ns);
+        return dim3(visits_grid<1, kOneRun, 1>(rows, n));
     };
     if (!p->c_pow2)
         return for_each_anyc_launch(p, p->r, [&](const uint32_t* js, int n, uint32_t omega) {
