@@ -329,7 +329,7 @@ int cs_sketch_estimate_sparse(const cs_params* p, const float* S, const int64_t*
  * (device uint64[CS_TOPK_HIST_BINS], read only); a histogram of other data gives a wrong
  * selection.
  * workspace: device, 8-byte aligned, contents irrelevant on entry.  cs_topk_workspace_bytes(d, k)
- * is what makes the call fastest: about 114 KiB of histograms and counters plus, when k is
+ * is what makes the call fastest: about 60 KiB of histograms and counters plus, when k is
  * small against d, room for a list of 8 k + 65 536 candidates (12 bytes each; 3 k + 65 536
  * when k is a few per cent of d), with which est is read twice (once with hist_or_null)
  * instead of five times.  Any size from cs_topk_workspace_bytes(1, 1) (the fixed
@@ -340,7 +340,12 @@ int cs_heavy_hitters_topk(const float* est, int64_t d, int64_t k, const uint64_t
                           int64_t* idx_out, float* val_out,
                           void* workspace, size_t ws_bytes, void* stream);
 /* The same for a workspace that the caller keeps: cleared once by cs_topk_workspace_clear, then used
- * by selections of this library only, one after the other, each of which leaves it clear. */
+ * by selections of this library only, one after the other, each of which leaves it clear.
+ * A selection shares its work out through counters in the workspace.  One that finds them
+ * other than clear (never cleared, written by others, a selection on another stream at the same
+ * time) gives no selection: slots of idx_out and val_out may be left as they were, and where
+ * its workgroups wait for work that was never counted, they give up after a second or two
+ * and idx_out becomes 0 .. k-1, val_out NaN.  Clear the workspace again after that. */
 int cs_topk_workspace_clear(void* workspace, size_t ws_bytes, void* stream);
 int cs_heavy_hitters_topk_kept(const float* est, int64_t d, int64_t k, const uint64_t* hist_or_null,
                                int64_t* idx_out, float* val_out, void* workspace, size_t ws_bytes,
@@ -351,12 +356,15 @@ int cs_heavy_hitters_topk_kept(const float* est, int64_t d, int64_t k, const uin
 /* cs_heavy_hitters_topk for callers that cannot allocate device memory or hand over a
  * workspace: code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same result as cs_heavy_hitters_topk (same kernels); the workspace is a fixed
- * array of 1.7 MB inside the library's device image (histograms, counters and room for
- * 131 072 candidates), which every GPU the library runs on holds until the process ends.  The call allocates and frees nothing, clears what it
- * needs with a kernel (no memset node under capture), and looks up the array's address once
- * per device, on the first call with that device current (`stream` must belong to the current
- * device).  All calls on one GPU share the array: calls that overlap on one GPU (different
- * streams, different threads) race and give wrong selections -- serialise them.
+ * array of 1.6 MB inside the library's device image (histograms, counters and room for
+ * 131 072 candidates), which every GPU the library runs on holds until the process ends.  The
+ * call allocates and frees nothing, clears what it needs with a kernel (no memset node under
+ * capture), and looks up the array's address once per device, on the first call with that device
+ * current (`stream` must belong to the current device).  All calls on one GPU share the array:
+ * calls that overlap on one GPU (different streams, different threads) race.  Their selections
+ * are then wrong, slots of idx_out may be left unwritten, and a call whose counters another one
+ * clears spends up to some seconds waiting before it gives up (idx_out 0 .. k-1, val_out NaN)
+ * -- serialise them.
  * CS_ELIMIT when d > CS_TOPK_STATIC_MAX_D (2^32: the supported range of this entry point;
  * the array's size does not grow with d); other arguments and errors as cs_heavy_hitters_topk. */
 #define CS_TOPK_STATIC_MAX_D (((int64_t)1) << 32)

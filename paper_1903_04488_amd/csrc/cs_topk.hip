@@ -27,7 +27,10 @@
 // the workgroups: the work is cut into 4 phases of T tasks, T workgroups draw tasks in order
 // from a counter, and before it starts a task it waits until every task of the phase before is
 // done.  Those were drawn earlier, by workgroups that are running and themselves wait for earlier
-// tasks only, so every wait ends whatever part of the grid is resident.
+// tasks only, so every wait ends whatever part of the grid is resident -- as long as the counters are
+// this call's alone.  Overlapping calls on one workspace, or a kept workspace that was never
+// cleared, break that; a wait whose phase makes no progress any more is therefore given up, and
+// the call then ends with indices and values that show it (k_topk_finish, `abandon`).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -53,6 +56,10 @@ constexpr int kScanWaves = kScanBlock / 64;
 constexpr int kMaxSegs = 512;
 constexpr int kStage = 8192;          // candidates one block can hold in LDS for its chunk
 constexpr int kFinishBlocks = 256;
+// Polls of a phase's counter, without a task of that phase ending in between, after which a wait is
+// given up: 1.4 s (a poll sleeps 512 cycles and reads memory, 0.33 us measured), plus one poll per
+// 16 entries of a task, forty times what a task with the chip to itself takes.
+constexpr uint32_t kIdlePolls = 1u << 22;
 
 // workspace layout (all 8-byte aligned); the candidate list follows the struct.  `hist[1..2]` and
 // everything from `ticket` to `heavy` are zero when a selection starts and are left zero when it ends.
@@ -548,10 +555,28 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
     const uint32_t tasks = static_cast<uint32_t>(want);
     if (blockIdx.x >= tasks) return;
     __shared__ uint32_t drawn;
-    auto wait_for = [&](int phase) {                // every task of that phase is done
-        if (tid == 0)
-            while (load_shared(&ws->done[phase]) < tasks) __builtin_amdgcn_s_sleep(8);
+    const int64_t est_chunk = ((d + tasks - 1) / tasks + 4095) / 4096 * 4096;
+    const int64_t idle_polls = kIdlePolls + est_chunk / 16;
+    __shared__ uint32_t finished;
+    auto wait_for = [&](int phase) -> bool {        // every task of that phase is done; false: given up
+        if (tid == 0) {
+            uint32_t seen = load_shared(&ws->done[phase]);
+            for (int64_t idle = 0; seen < tasks && idle < idle_polls; ++idle) {
+                __builtin_amdgcn_s_sleep(8);
+                const uint32_t now = load_shared(&ws->done[phase]);
+                if (now != seen) idle = 0;
+                seen = now;
+            }
+            finished = seen;
+        }
         __syncthreads();
+        return finished >= tasks;
+    };
+    // No selection came about (see the head of this file): indices that are in range, so that what
+    // reads through them stays inside its vectors, and values that nobody takes for estimates.
+    auto abandon = [&]() {
+        for (int64_t t = tid; t < out.k; t += kSelBlock) out.put(static_cast<uint64_t>(t), t, __uint_as_float(0x7fc00000u));
+        if (tid == 0 && out.n_heavy) *out.n_heavy = 0;
     };
     auto finish_task = [&](int phase) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -577,7 +602,7 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
             }
         }
     };
-    const int64_t est_chunk = ((d + tasks - 1) / tasks + 4095) / 4096 * 4096;
+    bool gave_up = false;
     for (;;) {
         if (tid == 0) drawn = atomicAdd(&ws->ticket, 1u);
         __syncthreads();
@@ -586,7 +611,10 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
         if (ticket >= 4 * tasks) break;
         const int phase = static_cast<int>(ticket / tasks);
         const uint32_t t = ticket - phase * tasks;
-        if (phase > 0) wait_for(phase - 1);
+        if (phase > 0 && !wait_for(phase - 1)) {
+            gave_up = true;
+            break;
+        }
         know(phase < 2 ? phase + 1 : 3);
         const int64_t lo = static_cast<int64_t>(t) * est_chunk;
         const int64_t hi = lo + est_chunk < d ? lo + est_chunk : d;
@@ -745,13 +773,21 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
         }
         finish_task(phase);
     }
-    // the last workgroup to leave puts the workspace back as it was
+    if (gave_up) abandon();
+    // the last workgroup to leave puts the workspace back as it was; every count of a finished task
+    // has arrived by then
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
     if (tid == 0) drawn = atomicAdd(&ws->exits, 1u);
     __syncthreads();
     if (drawn + 1 != tasks) return;
+    if (tid == 0) finished = load_shared(&ws->done[3]);
+    __syncthreads();
+    const bool whole = finished == tasks;
+    if (!whole && !gave_up) abandon();
     for (int t = tid; t < 2 * kBins; t += kSelBlock) (&ws->hist[1][0])[t] = 0;
     if (tid == 0) {
-        if (out.n_heavy) *out.n_heavy = load_shared(&ws->heavy);
+        if (out.n_heavy && whole) *out.n_heavy = load_shared(&ws->heavy);
         ws->ticket = 0;
         ws->exits = 0;
         for (int q = 0; q < 4; ++q) ws->done[q] = 0;
