@@ -112,9 +112,13 @@ class HotPath:
         if self.rho is not None:
             B.cs_sketch_feedback_pair(self.params, self.S_v, self.S_u, self.idx, self.delta, self.uhat)
 
+    def _overridden(self, stage):
+        return stage in self.__dict__ or getattr(type(self), stage) is not getattr(HotPath, stage)
+
     def aggregate(self):
-        """merge and momentum, in one pass where the workers have tables of their own"""
-        if self.rho is None or self.fold_workers:
+        """merge and momentum, in one pass where the workers have tables of their own and neither
+        stage is overridden"""
+        if self.rho is None or self.fold_workers or self._overridden("merge") or self._overridden("momentum"):
             self.merge()
             self.momentum()
             return
@@ -163,10 +167,6 @@ class ReproduciblePath(HotPath):
 
     def merge(self):
         B.cs_fixed_to_float(self.params, self.acc, self.frac_bits, self.S_t, alpha=1.0 / self.W)
-
-    def aggregate(self):
-        self.merge()
-        self.momentum()
 
     def _feedback(self, S, val):
         B.cs_sketch_estimate_sparse(self.params, S, self.idx, val)

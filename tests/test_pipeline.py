@@ -1,0 +1,67 @@
+"""What HotPath does around the library's calls, without a GPU: the calls are recorded."""
+import types
+
+import pytest
+import torch
+
+from paper_1903_04488_amd import binding, pipeline
+
+
+@pytest.fixture
+def calls(monkeypatch):
+    """names of the library calls that the pipeline makes, in order, with their arguments"""
+    made = []
+    fake = types.SimpleNamespace(**{n: getattr(binding, n) for n in dir(binding) if n.startswith("CS_")})
+    fake.DeviceVectors = lambda vectors, name=None: list(vectors)
+    for name in dir(binding):
+        if name.startswith("cs_"):
+            setattr(fake, name, lambda *a, _name=name, **kw: made.append((_name, a, kw)))
+    monkeypatch.setattr(pipeline, "B", fake)
+    return made
+
+
+def bare(cls=pipeline.HotPath, **attributes):
+    """a path whose tensors are what the test gives it"""
+    path = cls.__new__(cls)
+    for name in ("params", "T", "S_t", "S_u", "S_v", "est", "est_ws", "cand", "est_at_cand", "x_cand", "idx", "x",
+                 "delta", "uhat", "topk_ws", "hist"):
+        if name not in attributes and not isinstance(getattr(cls, name, None), property):
+            setattr(path, name, None)
+    path.d, path.W, path.r, path.c, path.k, path.kq, path.P = 100_000, 4, 5, 64, 2, 2, 1
+    path.rho, path.fold_workers, path.device = 0.9, False, torch.device("cpu")
+    for name, value in attributes.items():
+        setattr(path, name, value)
+    return path
+
+
+def names(made):
+    return [name for name, _, _ in made]
+
+
+def test_a_step_runs_the_stages_that_a_subclass_overrides(calls):
+    class Reduced(pipeline.HotPath):
+        def merge(self):
+            calls.append(("all-reduce", (), {}))
+
+    class Plain(pipeline.HotPath):
+        def momentum(self):
+            calls.append(("no momentum", (), {}))
+
+    bare().step([None])
+    assert "cs_bundle_merge_momentum" in names(calls)
+    calls.clear()
+    bare(Reduced).step([None])
+    assert names(calls).count("all-reduce") == 1 and "cs_sketch_momentum" in names(calls)
+    assert "cs_bundle_merge_momentum" not in names(calls)
+    calls.clear()
+    bare(Plain).step([None])
+    assert "cs_bundle_merge" in names(calls) and names(calls).count("no momentum") == 1
+    assert "cs_bundle_merge_momentum" not in names(calls) and "cs_sketch_momentum" not in names(calls)
+    calls.clear()
+    path = bare()
+    path.merge = lambda: calls.append(("wrapped", (), {}))           # on the object itself
+    path.step([None])
+    assert "wrapped" in names(calls) and "cs_bundle_merge_momentum" not in names(calls)
+    calls.clear()
+    bare(pipeline.ReproduciblePath, acc=torch.zeros(1), frac_bits=40, dropped=None, S_fb=None).step([None])
+    assert "cs_fixed_to_float" in names(calls) and "cs_bundle_merge_momentum" not in names(calls)
