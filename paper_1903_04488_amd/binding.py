@@ -221,24 +221,18 @@ def _stream(t: torch.Tensor):
     return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(t.device.index))
 
 
-class DeviceVectors:
+class DeviceVectors(tuple):
     """W vectors of the same length on the GPU, checked once and handed to several calls in place of
-    the list (which it keeps alive): with hundreds of workers the checks are most of a small
-    step's host time."""
+    the list: with hundreds of workers the checks are most of a small step's host time."""
 
-    def __init__(self, tensors, dtype=torch.float32, name: str = "vectors"):
-        self.tensors = list(tensors)
-        if not self.tensors:
+    def __new__(cls, tensors, dtype=torch.float32, name: str = "vectors"):
+        self = super().__new__(cls, tensors)
+        if not self:
             raise CsError(f"{name} must be a non-empty list")
-        self.d = self.tensors[0].numel()
+        self.d = self[0].numel()
         self.dtype = dtype
-        self.ptrs = _ptr_array(self.tensors, dtype, name, self.d)
-
-    def __len__(self):
-        return len(self.tensors)
-
-    def __getitem__(self, w):
-        return self.tensors[w]
+        self.ptrs = _ptr_array(tuple(self), dtype, name, self.d)
+        return self
 
 
 def _ptr_array(tensors, dtype, name, numel=None):

@@ -65,3 +65,17 @@ def test_a_step_runs_the_stages_that_a_subclass_overrides(calls):
     calls.clear()
     bare(pipeline.ReproduciblePath, acc=torch.zeros(1), frac_bits=40, dropped=None, S_fb=None).step([None])
     assert "cs_fixed_to_float" in names(calls) and "cs_bundle_merge_momentum" not in names(calls)
+
+
+def test_the_vectors_of_a_step_reach_overridden_stages_as_a_sequence_of_tensors(calls, monkeypatch):
+    monkeypatch.setattr(pipeline.B, "DeviceVectors", binding.DeviceVectors)
+    monkeypatch.setattr(binding, "_ptr_array", lambda tensors, dtype, name, numel=None: None)   # (host tensors here)
+    seen = []
+
+    class Stacked(pipeline.HotPath):
+        def accumulate(self, g_w):
+            seen.append(torch.stack(g_w).sum(0))
+            seen.append([g + 1 for g in g_w[1:]])
+
+    bare(Stacked).step([torch.ones(3), torch.full((3,), 2.0)])
+    assert seen[0].tolist() == [3.0, 3.0, 3.0] and len(seen[1]) == 1 and seen[1][0].tolist() == [3.0, 3.0, 3.0]
