@@ -25,7 +25,9 @@ class HotPath:
         values, and the k largest exact sums are kept (Alg. 3 as the paper trains with it).
         fold_workers: the workers, which share this GPU, are summed before they are sketched
         (every vector is read once; the sum goes into d floats of scratch, then straight into
-        S_t): no worker tables, no merge."""
+        S_t): no worker tables, no merge.  The scratch is the query's, so the stages of one
+        path run one after the other; where the query has none (short vectors and column counts
+        without a traversal plan) the path holds d floats more."""
         self.d, self.W, self.r, self.c, self.k = d, W, r, c, k
         self.P = P
         self.fold_workers = fold_workers
@@ -57,11 +59,9 @@ class HotPath:
         n_est = B.cs_estimate_workspace_bytes(self.params, d)
         self.est_ws = (torch.empty(n_est, dtype=torch.uint8, device=self.device)
                        if n_est else None)
-        # the workers' mean, when they are folded: the scratch of the query is free until then
         self.g_mean = None
         if fold_workers and W > 1:
-            self.g_mean = (self.est_ws[:4 * d].view(torch.float32) if n_est >= 4 * d
-                           else torch.empty(d, **f32))
+            self._mean_buffer(d)
 
     # individual stages (bench.py times them separately) ---------------------------------
     def worker_table(self, w: int):
@@ -69,14 +69,25 @@ class HotPath:
         g = B.CS_BUNDLE_GROUP
         return self.T.view(-1, self.r, self.c, g)[w // g, :, :, w % g]
 
+    def _mean_buffer(self, n: int):
+        """n floats for the mean of folded workers: the query's scratch, which is free until the
+        estimate, or memory that is kept where the query needs too little of it"""
+        if self.g_mean is None or self.g_mean.numel() < n:
+            size = max(n, self.d)
+            fits = self.est_ws is not None and self.est_ws.numel() >= 4 * size
+            self.g_mean = (self.est_ws[:4 * size].view(torch.float32) if fits
+                           else torch.empty(size, dtype=torch.float32, device=self.device))
+        return self.g_mean[:n]
+
     def accumulate(self, g_w):
         if self.fold_workers:
             B.cs_sketch_zero(self.params, self.S_t)
-            if self.W == 1:
-                B.cs_sketch_accumulate(self.params, self.S_t, g_w[0])
+            if len(g_w) == 1:
+                B.cs_sketch_accumulate(self.params, self.S_t, g_w[0], scale=1.0 / self.W)
                 return
-            B.cs_vectors_sum(g_w, self.g_mean, alpha=1.0 / self.W)
-            B.cs_sketch_accumulate(self.params, self.S_t, self.g_mean)
+            mean = self._mean_buffer(g_w[0].numel())
+            B.cs_vectors_sum(g_w, mean, alpha=1.0 / self.W)
+            B.cs_sketch_accumulate(self.params, self.S_t, mean)
             return
         B.cs_bundle_zero(self.params, self.T, self.W)
         B.cs_sketch_accumulate_bundle(self.params, self.T, g_w)

@@ -79,3 +79,25 @@ def test_the_vectors_of_a_step_reach_overridden_stages_as_a_sequence_of_tensors(
 
     bare(Stacked).step([torch.ones(3), torch.full((3,), 2.0)])
     assert seen[0].tolist() == [3.0, 3.0, 3.0] and len(seen[1]) == 1 and seen[1][0].tolist() == [3.0, 3.0, 3.0]
+
+
+@pytest.mark.parametrize("scratch", [0, 4 * 100_000, 20 * 100_000])
+@pytest.mark.parametrize("W,given,length", [(4, 4, 100_000), (1, 3, 100_000), (1, 1, 100_000), (4, 3, 70_000),
+                                            (4, 4, 130_000)])
+def test_folded_workers_are_all_summed_whenever_folding_was_chosen(calls, W, given, length, scratch):
+    """fold_workers set on a finished object, more vectors than W said, vectors of another length than d"""
+    path = bare(W=W, est_ws=torch.empty(scratch, dtype=torch.uint8) if scratch else None, g_mean=None)
+    path.fold_workers = True
+    vectors = [torch.full((length,), float(w)) for w in range(given)]
+    path.accumulate(vectors)
+    made = [(name, a, kw) for name, a, kw in calls if name != "cs_sketch_zero"]
+    if given == 1:
+        assert names(made) == ["cs_sketch_accumulate"] and made[0][1][2] is vectors[0]
+        assert made[0][2].get("scale", 1.0) == 1.0 / W
+        return
+    assert names(made) == ["cs_vectors_sum", "cs_sketch_accumulate"]
+    (x_w, out), kw = made[0][1], made[0][2]
+    assert len(x_w) == given and kw["alpha"] == 1.0 / W
+    assert out.numel() == length and out.dtype == torch.float32 and made[1][1][2] is out
+    if scratch >= 4 * length and length <= path.d:                   # no memory of its own where the query has scratch
+        assert out.data_ptr() == path.est_ws.data_ptr()
