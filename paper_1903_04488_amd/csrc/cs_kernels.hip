@@ -528,7 +528,8 @@ k_gather(GatherPtrs ptrs, int nw, const int64_t* __restrict__ idx, int64_t k, fl
 // out = alpha * (sum of W vectors), added up in binary64 and rounded once.  Folded workers are
 // summed before they are sketched: the sketch is linear, W d floats are then read once
 // instead of r times.  Bound by that read; 4 vectors' 16-byte pieces are in flight per thread.
-// More vectors than one launch takes: later launches add to out, which then holds the unscaled sum.
+// More vectors than one launch takes: later launches add their share, scaled like the first's (so that
+// nothing overflows that alpha times the whole sum does not).
 constexpr int kMaxSum = 256;
 struct SumPtrs {
     const float* x[kMaxSum];
@@ -549,7 +550,8 @@ k_vectors_sum(SumPtrs ptrs, int nw, int64_t d, float alpha, float* __restrict__ 
                 s[0] += static_cast<double>(u.x); s[1] += static_cast<double>(u.y);
                 s[2] += static_cast<double>(u.z); s[3] += static_cast<double>(u.w);
             };
-            if (!first_launch) add(reinterpret_cast<const f4*>(out)[t]);
+            f4 base = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (!first_launch) base = reinterpret_cast<const f4*>(out)[t];
             int w = 0;
             for (; w + 4 <= nw; w += 4) {
                 f4 u[4];
@@ -562,17 +564,18 @@ k_vectors_sum(SumPtrs ptrs, int nw, int64_t d, float alpha, float* __restrict__ 
             for (; w < nw; ++w) add(__builtin_nontemporal_load(reinterpret_cast<const f4*>(ptrs.x[w]) + t));
             const double a = static_cast<double>(alpha);
             f4 o;
-            o.x = static_cast<float>(a * s[0]); o.y = static_cast<float>(a * s[1]);
-            o.z = static_cast<float>(a * s[2]); o.w = static_cast<float>(a * s[3]);
+            o.x = static_cast<float>(base.x + a * s[0]); o.y = static_cast<float>(base.y + a * s[1]);
+            o.z = static_cast<float>(base.z + a * s[2]); o.w = static_cast<float>(base.w + a * s[3]);
             reinterpret_cast<f4*>(out)[t] = o;
         }
         done = n4 * 4;
     }
     for (int64_t t = done + t0; t < d; t += stride) {
-        double s = first_launch ? 0.0 : static_cast<double>(out[t]);
+        const double base = first_launch ? 0.0 : static_cast<double>(out[t]);
+        double s = 0.0;
 #pragma unroll 4
         for (int w = 0; w < nw; ++w) s += static_cast<double>(ptrs.x[w][t]);
-        out[t] = static_cast<float>(static_cast<double>(alpha) * s);
+        out[t] = static_cast<float>(base + static_cast<double>(alpha) * s);
     }
 }
 
@@ -1108,9 +1111,8 @@ extern "C" int cs_vectors_sum(const float* const* x_w, int32_t W, int64_t d, flo
         SumPtrs ptrs{};
         for (int w = 0; w < nw; ++w) ptrs.x[w] = x_w[w0 + w];
         const unsigned grid = grid_for(vec ? (d + 3) / 4 : d, kBlock, 256 * 32);
-        const float a = w0 + nw == W ? alpha : 1.0f;
-        if (vec) k_vectors_sum<true><<<grid, kBlock, 0, as_stream(stream)>>>(ptrs, nw, d, a, out, w0 == 0);
-        else k_vectors_sum<false><<<grid, kBlock, 0, as_stream(stream)>>>(ptrs, nw, d, a, out, w0 == 0);
+        if (vec) k_vectors_sum<true><<<grid, kBlock, 0, as_stream(stream)>>>(ptrs, nw, d, alpha, out, w0 == 0);
+        else k_vectors_sum<false><<<grid, kBlock, 0, as_stream(stream)>>>(ptrs, nw, d, alpha, out, w0 == 0);
         if (launch_status() != CS_OK) return CS_EHIP;
     }
     return CS_OK;

@@ -38,3 +38,17 @@ def test_vectors_sum(W, d):
     out = torch.empty(d, dtype=torch.float32, device=DEV)
     cs.cs_vectors_sum([x[w] for w in range(W)], out, alpha=1.0 / W)
     torch.testing.assert_close(out.cpu(), x.cpu().double().mean(0).float(), rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+def test_vectors_sum_of_large_values_above_one_launch(offset):
+    """The mean of 300 vectors of 2e36 is finite though their sum is not: the part that the first launch
+    (256 vectors) leaves in `out` is scaled already."""
+    W, d = 300, 1029
+    g = torch.Generator().manual_seed(7)
+    x = (torch.rand(W, d + offset, generator=g) + 0.5) * 2e36
+    dev = [x[w].to(DEV)[offset:] for w in range(W)]
+    out = torch.empty(d, dtype=torch.float32, device=DEV)
+    cs.cs_vectors_sum(dev, out, alpha=1.0 / W)
+    # two partial means, each rounded once, and their sum
+    torch.testing.assert_close(out.cpu(), x[:, offset:].double().mean(0).float(), rtol=3 * 2.0 ** -24, atol=0.0)
