@@ -224,10 +224,11 @@ int cs_sketch_accumulate_bundle(const cs_params* p, float* T, int32_t W,
  * device pointers to float[d].  W >= 1, d >= 0, i0 as for cs_sketch_accumulate. */
 int cs_sketch_accumulate_sum(const cs_params* p, float* S, int32_t W, const float* const* g_w,
                              int64_t d, int64_t i0, float scale, void* stream);
-/* out[t] = alpha * sum_{w<W} x_w[w][t], the sum accumulated in binary64 and rounded to binary32
- * (once per 256 vectors).  By the same linearity this and one cs_sketch_accumulate of `out` sketch
+/* out[t] = alpha * sum_{w<W} x_w[w][t], the sum accumulated in binary64, scaled and rounded to
+ * binary32 (once per 256 vectors).  By the same linearity this and one cs_sketch_accumulate of `out` sketch
  * the W workers of a device with W d floats read once, for callers that have d floats to spare.
- * x_w: HOST array of W device pointers to float[d]; out: device float[d], none of the x_w. */
+ * x_w: HOST array of W device pointers to float[d]; out: device float[d] that overlaps
+ * none of the x_w (CS_EINVAL if it does). */
 int cs_vectors_sum(const float* const* x_w, int32_t W, int64_t d, float alpha, float* out, void* stream);
 int cs_bundle_merge(const cs_params* p, float* dst, float beta, const float* T, int32_t W,
                     float alpha, void* stream);

@@ -1100,9 +1100,11 @@ extern "C" int cs_gather_exact(const float* const* vec, int32_t W, const int64_t
 extern "C" int cs_vectors_sum(const float* const* x_w, int32_t W, int64_t d, float alpha, float* out,
                               void* stream) {
     if (!x_w || W < 1 || d < 0 || !out) return CS_EINVAL;
-    bool vec = reinterpret_cast<uintptr_t>(out) % 16 == 0;
+    const uintptr_t o = reinterpret_cast<uintptr_t>(out), bytes = sizeof(float) * static_cast<uintptr_t>(d);
+    bool vec = o % 16 == 0;
     for (int w = 0; w < W; ++w) {
-        if (!x_w[w] || x_w[w] == out) return CS_EINVAL;
+        const uintptr_t x = reinterpret_cast<uintptr_t>(x_w[w]);
+        if (!x_w[w] || x_w[w] == out || (x < o ? o - x : x - o) < bytes) return CS_EINVAL;
         vec = vec && reinterpret_cast<uintptr_t>(x_w[w]) % 16 == 0;
     }
     if (d == 0) return CS_OK;

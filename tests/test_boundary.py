@@ -210,6 +210,16 @@ def test_invalid_arguments_are_rejected_without_a_gpu(lib):
     assert lib.cs_heavymix_select(fake, 10, 5, fake, 1, fake, null, null, fake, 8, null) == -2
 
 
+def test_vectors_sum_refuses_an_output_that_overlaps_an_input(lib):
+    """threads write `out` while others still read the vectors: 4 bytes in common are too many"""
+    null, d = ctypes.c_void_p(0), 10
+    one = (ctypes.c_void_p * 2)(1 << 20, 1 << 24)
+    for base in (1 << 20, 1 << 24):
+        for shift in (-4 * (d - 1), -4, 0, 4, 4 * (d - 1)):
+            assert lib.cs_vectors_sum(one, 2, d, 1.0, ctypes.c_void_p(base + shift), null) == -1, shift
+    assert lib.cs_vectors_sum(one, 2, 0, 1.0, ctypes.c_void_p((1 << 20) + 4), null) == 0     # nothing to overlap
+
+
 def test_update_launch_count_follows_the_grouping(lib):
     """cs_bundle_update_launches: per group of 8 workers one launch for the rows with a visit list
     (8 rows at most per launch) and one for the rows walked by stride; for other column counts
