@@ -9,7 +9,8 @@ Per step (Alg. 3 of the paper, with the W workers simulated on the one device):
     choose largest    idx = top-k |est|           cs_heavy_hitters_topk_kept
     second round      x = (1/W) sum_w g^w[idx]    cs_gather_exact
     feedback          S_v -= S(est[idx]) ; S_u -= S(estimate(S_u, idx))   cs_sketch_feedback_pair (stateful)
-Every arithmetic step runs inside libcsketch.so; this class only owns tensors.
+Every arithmetic step runs inside libcsketch.so; this class only owns tensors (and counts `hist` of
+short vectors for whoever asks).
 """
 from __future__ import annotations
 
@@ -54,8 +55,7 @@ class HotPath:
         self.topk_ws = torch.empty(B.cs_topk_workspace_bytes(d, self.kq), dtype=torch.uint8,
                                    device=self.device)
         B.cs_topk_workspace_clear(self.topk_ws)      # once: every selection leaves it clear
-        # counts of the estimates by magnitude bin: filled by the estimate, read by the selection
-        self.hist = torch.zeros(B.CS_TOPK_HIST_BINS, dtype=torch.int64, device=self.device)
+        self._counts = torch.zeros(B.CS_TOPK_HIST_BINS, dtype=torch.int64, device=self.device)
         n_est = B.cs_estimate_workspace_bytes(self.params, d)
         self.est_ws = (torch.empty(n_est, dtype=torch.uint8, device=self.device)
                        if n_est else None)
@@ -104,9 +104,23 @@ class HotPath:
     def query_table(self):
         return self.S_v if self.rho is not None else self.S_t
 
+    @property
+    def hist(self):
+        """Counts of est by magnitude bin.  The estimate fills them where the selection reads them;
+        up to CS_TOPK_SMALL_D coordinates, whose selection counts by itself, they are taken here,
+        so that a step does not launch for them."""
+        if self.d <= B.CS_TOPK_SMALL_D:
+            bins = ((self.est.view(torch.int32) & 0x7FFFFFFF) >> 20).long()
+            self._counts.zero_().scatter_add_(0, bins, torch.ones_like(bins))
+        return self._counts
+
+    @hist.setter
+    def hist(self, counts):
+        self._counts = counts
+
     def _hist(self):
         """the counts, where the selection reads them"""
-        return self.hist if self.d > B.CS_TOPK_SMALL_D else None
+        return self._counts if self.d > B.CS_TOPK_SMALL_D else None
 
     def estimate(self):
         B.cs_sketch_estimate(self.params, self.query_table(), self.est, 0, self.est_ws, self._hist())

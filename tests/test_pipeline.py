@@ -24,9 +24,8 @@ def bare(cls=pipeline.HotPath, **attributes):
     """a path whose tensors are what the test gives it"""
     path = cls.__new__(cls)
     for name in ("params", "T", "S_t", "S_u", "S_v", "est", "est_ws", "cand", "est_at_cand", "x_cand", "idx", "x",
-                 "delta", "uhat", "topk_ws", "hist"):
-        if name not in attributes and not isinstance(getattr(cls, name, None), property):
-            setattr(path, name, None)
+                 "delta", "uhat", "topk_ws", "_counts"):
+        setattr(path, name, None)
     path.d, path.W, path.r, path.c, path.k, path.kq, path.P = 100_000, 4, 5, 64, 2, 2, 1
     path.rho, path.fold_workers, path.device = 0.9, False, torch.device("cpu")
     for name, value in attributes.items():
@@ -101,3 +100,23 @@ def test_folded_workers_are_all_summed_whenever_folding_was_chosen(calls, W, giv
     assert out.numel() == length and out.dtype == torch.float32 and made[1][1][2] is out
     if scratch >= 4 * length and length <= path.d:                   # no memory of its own where the query has scratch
         assert out.data_ptr() == path.est_ws.data_ptr()
+
+
+@pytest.mark.parametrize("d", [784, 32_768, 32_769])
+def test_counts_by_magnitude_are_there_for_vectors_of_any_length(calls, d):
+    """up to CS_TOPK_SMALL_D neither the estimate nor the selection is given the counts; whoever reads
+    them gets those of the estimates all the same"""
+    est = torch.randn(d, generator=torch.Generator().manual_seed(d))
+    counts = torch.full((binding.CS_TOPK_HIST_BINS,), 7, dtype=torch.int64)
+    path = bare(hist=counts)
+    path.d, path.est = d, est
+    path.estimate()
+    path.topk()
+    given = calls[0][1][-1]
+    assert (given is None) == (d <= binding.CS_TOPK_SMALL_D) and calls[1][1][-1] is given
+    if given is not None:
+        assert given is counts and path.hist is counts
+        return
+    bins = (est.numpy().view("uint32") & 0x7FFFFFFF) >> 20
+    assert path.hist is counts
+    assert counts.tolist() == torch.bincount(torch.from_numpy(bins.astype("int64")), minlength=2048).tolist()
