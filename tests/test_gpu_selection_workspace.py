@@ -39,3 +39,53 @@ def test_selection_with_a_stale_counter_ends_and_shows_it(with_val):
         np.testing.assert_array_equal(idx.cpu().numpy(), want)
         if with_val:
             np.testing.assert_array_equal(val.cpu().numpy(), est[want])
+
+
+def test_one_kept_workspace_serves_every_kind_of_selection_in_turn():
+    """Each leaves the workspace clear for the next: ordinary lists, a list that is too long for one
+    workgroup, lists that cannot be built (one stretch of heavy entries, all magnitudes in one bin),
+    HEAVYMIX with its list and without, P k candidates, and vectors of one workgroup."""
+    d = 3_000_017
+    rng = np.random.default_rng(5)
+    noise = (rng.standard_normal(d) * 0.01).astype(np.float32)
+    stretch = noise.copy()
+    stretch[700_000:709_000] = rng.uniform(0.5, 1.0, size=9000).astype(np.float32)
+    one_bin = (rng.uniform(1.0, 1.05, size=d) * rng.choice([-1.0, 1.0], size=d)).astype(np.float32)
+    ws = torch.full((cs.cs_topk_workspace_bytes(d, 60_000),), 0xA7, dtype=torch.uint8, device=DEV)
+    cs.cs_topk_workspace_clear(ws)
+
+    def kept(est, k):
+        dev_est = torch.from_numpy(est).to(DEV)
+        bins = (est.view(np.uint32) & np.uint32(0x7FFFFFFF)) >> np.uint32(20)
+        hist = torch.from_numpy(np.bincount(bins, minlength=2048).astype(np.int64)).to(DEV)
+        idx = torch.full((k,), -1, dtype=torch.int64, device=DEV)
+        val = torch.empty(k, dtype=torch.float32, device=DEV)
+        cs.cs_heavy_hitters_topk_kept(dev_est, k, idx, val, ws, hist)
+        want = orc.topk_threshold(est, k)
+        np.testing.assert_array_equal(idx.cpu().numpy(), want)
+        np.testing.assert_array_equal(val.cpu().numpy().view(np.uint32), est[want].view(np.uint32))
+
+    def heavymix(est, k, l2sq):
+        idx = torch.full((k,), -1, dtype=torch.int64, device=DEV)
+        val = torch.empty(k, dtype=torch.float32, device=DEV)
+        n_heavy = torch.full((1,), -1, dtype=torch.int64, device=DEV)
+        cs.cs_heavymix_select(torch.from_numpy(est).to(DEV), k, torch.tensor([l2sq], dtype=torch.float64, device=DEV), 9,
+                              idx, val, n_heavy, ws)
+        want, heavy = orc.heavymix_select(est, k, l2sq, 9)
+        np.testing.assert_array_equal(idx.cpu().numpy(), want)
+        assert int(n_heavy.item()) == heavy
+
+    def exact(n, k):
+        cand = np.sort(rng.choice(10**8, n, replace=False)).astype(np.int64)
+        x = (np.round(rng.standard_normal(n) * 50) / 50).astype(np.float32)      # ties
+        idx = torch.full((k,), -1, dtype=torch.int64, device=DEV)
+        val = torch.empty(k, dtype=torch.float32, device=DEV)
+        cs.cs_select_exact_topk(torch.from_numpy(cand).to(DEV), torch.from_numpy(x).to(DEV), k, idx, val, ws)
+        np.testing.assert_array_equal(idx.cpu().numpy(), cand[orc.topk_threshold(x, k)])
+
+    for step in (lambda: kept(stretch, 2000), lambda: kept(one_bin, 2000), lambda: heavymix(noise, 3000, 1e-12),
+                 lambda: heavymix(noise, 3000, 1e12), lambda: exact(200_000, 3000), lambda: kept(noise, 60_000),
+                 lambda: kept(noise[:20_000].copy(), 5), lambda: exact(500, 20)):
+        kept(noise, 2000)
+        step()
+        kept(noise, 2000)

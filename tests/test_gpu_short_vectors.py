@@ -52,3 +52,106 @@ def test_vectors_sum_of_large_values_above_one_launch(offset):
     cs.cs_vectors_sum(dev, out, alpha=1.0 / W)
     # two partial means, each rounded once, and their sum
     torch.testing.assert_close(out.cpu(), x[:, offset:].double().mean(0).float(), rtol=3 * 2.0 ** -24, atol=0.0)
+
+
+@pytest.mark.parametrize("W", [1, 3, 5])
+@pytest.mark.parametrize("d", [1, 3, 4, 1029])
+@pytest.mark.parametrize("odd", ["inputs", "one input", "output"])
+def test_vectors_sum_at_any_dword_address(W, d, odd):
+    """views that begin 4, 8 or 12 bytes past a 16-byte boundary; nothing around `out` is written"""
+    x = torch.randn(W, d, generator=torch.Generator().manual_seed(W * d))
+    views = []
+    for w in range(W):
+        shift = (1 + w % 3) if odd == "inputs" or (odd == "one input" and w == W - 1) else 0
+        buf = torch.zeros(d + 8, dtype=torch.float32, device=DEV)
+        views.append(buf[shift:shift + d])
+        views[-1].copy_(x[w])
+    shift = 2 if odd == "output" else 0
+    buf = torch.full((d + 8,), 7.0, dtype=torch.float32, device=DEV)
+    cs.cs_vectors_sum(views, buf[shift:shift + d], alpha=0.5)
+    # exact sums in binary64, scaled by a power of two, rounded once
+    np.testing.assert_array_equal(buf[shift:shift + d].cpu().numpy(), (0.5 * x.double().sum(0)).float().numpy())
+    assert (buf[:shift] == 7.0).all() and (buf[shift + d:] == 7.0).all()
+
+
+@pytest.mark.parametrize("W", [1, 8, 9, 40])
+@pytest.mark.parametrize("r,c", [(3, 1), (5, 1 << 10), (7, 771)])
+def test_bundle_merge_with_momentum(W, r, c):
+    p = cs.cs_params_init(r, c, 3)
+    rng = np.random.default_rng(W + c)
+    G = cs.CS_BUNDLE_GROUP
+    T = rng.standard_normal((-(-W // G), r, c, G)).astype(np.float32)
+    if W % G:
+        T[-1, :, :, W % G:] = 0.0                                    # padding slots
+    su, sv = (rng.standard_normal((r, c)).astype(np.float32) for _ in range(2))
+    S_t = torch.full((r, c), float("nan"), dtype=torch.float32, device=DEV)
+    S_u, S_v = torch.from_numpy(su).to(DEV), torch.from_numpy(sv).to(DEV)
+    alpha = float(np.float32(1.0 / W))
+    cs.cs_bundle_merge_momentum(p, S_t, S_u, S_v, torch.from_numpy(T.reshape(-1)).to(DEV), W, alpha, 0.9)
+    merged = orc.merge([T[w // G, :, :, w % G] for w in range(W)], alpha=alpha)
+    st = orc.SketchSpaceState(orc.SketchOracle(r, c, 3), 0.9)
+    st.S_u, st.S_v = su.astype(np.float64), sv.astype(np.float64)
+    st.momentum(merged)
+    # the merge is rounded once, the momentum twice more and the accumulation once more, each to 2^-24 of
+    # an operand: four roundings of values below |S_t| + |S_u| + |S_v|
+    bound = 4 * 2.0 ** -24 * (np.abs(merged) + np.abs(su) + np.abs(sv))
+    for got, want, name in ((S_t, merged, "S_t"), (S_u, st.S_u, "S_u"), (S_v, st.S_v, "S_v")):
+        assert (np.abs(got.cpu().numpy() - want) <= bound).all(), name
+
+
+def _listed(p, d, forged):
+    """the lists of p, or lists of evenly spaced visits that keep no coordinate within its cells; either
+    way short enough in residues that the update of one vector follows them"""
+    import ctypes
+    P = (1 << 61) - 1
+    plans = p.visit if p.c_pow2 else p.anyc
+    for j in range(p.r if forged else 0):
+        v, K = plans[j], 40
+        ctypes.memset(ctypes.byref(v), 0, ctypes.sizeof(v))
+        gap = d // K - j
+        last = d - (K - 1) * gap
+        v.K, v.cover, v.gmax, v.cost = K, d, max(gap, last), 1
+        if p.c_pow2:
+            v.ncell, v.cost_walk = 2 + j % 3, 2
+            v.gap[0], v.gap[3] = gap, last
+            v.A[0], v.As[0] = (p.a[j] * gap) % P, (p.as_[j] * gap) % P
+            v.code[(K - 1) // 16] |= 3 << (2 * ((K - 1) % 16))       # the last visit: code 3
+        else:
+            v.omega, v.cost_direct = 1 + j % 2, 2
+            for k in range(K):
+                v.gap[k] = gap if k + 1 < K else last
+    assert all(v.K > 0 and v.cover >= d and v.cost < (v.cost_walk if p.c_pow2 else v.cost_direct) for v in plans[:p.r])
+    assert 1.2 * sum(plans[j].gmax for j in range(p.r)) <= p.r * d / 8
+    return p
+
+
+@pytest.mark.parametrize("r,c,d", [(5, 1 << 12, 200_003), (3, 5001, 1_000_003)])
+@pytest.mark.parametrize("forged", [False, True])
+def test_update_of_one_vector_with_nan_infinities_and_forged_lists(r, c, d, forged):
+    """Into a table of its own, into a slot of a bundle (the ninth worker), and summed: a NaN or an
+    infinity reaches the r cells of its coordinate and no others, and a wrong list costs time only."""
+    p = _listed(cs.cs_params_init(r, c, 11, d), d, forged)
+    sk = orc.SketchOracle(r, c, 11)
+    rng = np.random.default_rng(c)
+    g = (rng.standard_normal(d) * 0.01).astype(np.float32)
+    g[[7, 30_001]] = [np.nan, np.inf]
+    g[[50_000, 50_001, d - 1]] = [-np.inf, np.inf, np.nan]
+    plain = (rng.standard_normal(d) * 0.01).astype(np.float32)
+    G = cs.CS_BUNDLE_GROUP
+    for vec in (plain, g):
+        with np.errstate(invalid="ignore"):
+            ref = sk.sketch(vec, i0=3, scale=0.5)
+        dev = torch.from_numpy(vec).to(DEV)
+        S = torch.zeros(r, c, dtype=torch.float32, device=DEV)
+        cs.cs_sketch_accumulate(p, S, dev, i0=3, scale=0.5)
+        S_sum = torch.zeros(r, c, dtype=torch.float32, device=DEV)
+        cs.cs_sketch_accumulate_sum(p, S_sum, [dev], i0=3, scale=0.5)
+        T = torch.zeros(cs.cs_bundle_floats(p, 9), dtype=torch.float32, device=DEV)
+        cs.cs_sketch_accumulate_bundle(p, T, [torch.ones_like(dev)] * 8 + [dev], i0=3, scale=0.5)
+        for table in (S, S_sum, T.view(-1, r, c, G)[1, :, :, 0]):
+            got = table.cpu().numpy()
+            np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+            np.testing.assert_array_equal(np.where(np.isinf(got), got, 0), np.where(np.isinf(ref), ref, 0))
+            fin = np.isfinite(ref)
+            assert fin.sum() >= ref.size - 5 * r
+            assert_cells_close(np.where(fin, got, 0), np.where(fin, ref, 0), terms_per_cell=d / c)
