@@ -201,8 +201,8 @@ def main():
                          "per worker.  heavymix: Alg. 1 selection (norm estimate, threshold, random "
                          "fill) on the merged sketch, no state.  top-pk: P = 16 candidates per "
                          "selected coordinate, exact second round, k largest exact sums.  "
-                         "fused-merge: sketch-state with the workers summed as they are sketched "
-                         "(cs_sketch_accumulate_sum: no worker tables, no merge pass) -- what a "
+                         "fused-merge: sketch-state with the workers summed before they are sketched "
+                         "(HotPath(fold_workers=True): no worker tables, no merge pass) -- what a "
                          "device that hosts several workers can do; not the headline path")
     ap.add_argument("--graph", action="store_true",
                     help="also time the same step replayed from a HIP graph (one submission per "
@@ -283,9 +283,8 @@ def main():
 
         def update(vecs):
             if hp.fold_workers:
-                B.cs_sketch_zero(hp.params, hp.S_t)
                 mark(8)
-                B.cs_sketch_accumulate_sum(hp.params, hp.S_t, vecs, scale=1.0 / hp.W)
+                hp.accumulate(vecs)
                 mark(9)
                 return
             B.cs_bundle_zero(hp.params, hp.T, hp.W)
@@ -353,7 +352,8 @@ def main():
     # the update runs as a few launches per group of 8 workers (rows that share a traversal
     # share a launch); the algorithmic bytes of the whole update (every gradient read once,
     # every worker table written once) are spread evenly over those launches
-    n_launch = B.cs_bundle_update_launches(hp.params, cfg.W, cfg.d)
+    # (folded workers: one call of several different kernels, taken as a whole)
+    n_launch = 1 if hp.fold_workers else B.cs_bundle_update_launches(hp.params, cfg.W, cfg.d)
     acc_kernel_ms = sum(ev[8].elapsed_time(ev[9]) for ev in events) / args.steps / n_launch
     per_set = [[] for _ in range(n_sets)]         # the update's time on each resident input set
     for t, ev in enumerate(events):
@@ -364,8 +364,8 @@ def main():
     tables_written = 1 if variant == "fused-merge" else cfg.W
     alg_bytes = (4.0 * cfg.W * cfg.d + 4.0 * cfg.r * cfg.c * tables_written) / n_launch
     achieved = alg_bytes / (acc_kernel_ms * 1e-3) / 1e9
-    step_alg_bytes = (4.0 * cfg.W * cfg.d + 4.0 * cfg.r * cfg.c * cfg.W          # update
-                      + 4.0 * cfg.r * cfg.c * (cfg.W + 1)                        # merge
+    step_alg_bytes = (4.0 * cfg.W * cfg.d + 4.0 * cfg.r * cfg.c * tables_written  # update
+                      + (0.0 if hp.fold_workers else 4.0 * cfg.r * cfg.c * (cfg.W + 1))   # merge
                       + (4.0 * cfg.r * cfg.c * 5 if cfg.stateful else 0.0)       # momentum
                       + 4.0 * cfg.r * cfg.c + 4.0 * cfg.d                        # estimate
                       + 4.0 * cfg.d                                              # top-k
@@ -426,7 +426,7 @@ def main():
                             for name in ("accumulate", "dense_momentum", "estimate", "topk", "heavymix_select")
                             if stage_ms.get(name)},
         "roofline": {
-            "kernel": ("k_accumulate_visits (all launches of cs_sketch_accumulate_sum)" if variant == "fused-merge"
+            "kernel": ("HotPath.accumulate (k_vectors_sum, then k_accumulate_one)" if variant == "fused-merge"
                        else "k_accumulate_visits (all launches of cs_sketch_accumulate_bundle)"),
             "bound": "hbm",
             "achieved": achieved,

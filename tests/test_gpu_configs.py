@@ -172,7 +172,7 @@ def test_small_variant_all_steps(cfg):
 
 @pytest.mark.parametrize("cfg", [1, 4, 5])
 def test_small_variant_with_the_workers_summed_as_they_are_sketched(cfg):
-    """the same steps through cs_sketch_accumulate_sum (no worker tables, no merge pass)"""
+    """the same steps with fold_workers: the workers summed, then one sketch (no worker tables, no merge pass)"""
     base = wl.CONFIGS[cfg]
     small = wl.scaled(cfg, d=(1 << 21) + 12_345, W=min(base.W, 12), c=1 << 14,
                       k=2000, steps=min(base.steps, 4),
