@@ -248,8 +248,11 @@ k_topk_hist0(const float* __restrict__ est, int64_t d, uint64_t* __restrict__ hi
 // part of LDS (their places come from wavefront ballots, no barrier inside the loop); the block
 // then appends them to the list as one segment, whose place comes from a single atomic add.
 // Segments lie in the list in the order the blocks finished; (seg_base[b], seg_count[b]) lets
-// k_topk_finish put them in block order, i.e. in index order.  A wavefront with more than
-// kStage / 8 candidates, or a list that would exceed `cap`, raises ws->failed.
+// k_topk_finish put them in block order, i.e. in index order.  A wavefront whose part holds more
+// candidates than it can stage counts them all and reads its part once more to write them (k of
+// 4 % of d and more: at d = 90 M, k = 3.6 M this kernel takes 105 us for 75 and k_topk_finish, which had to read
+// est three times when such a list was given up, 180 for 570).
+// A list that would exceed `cap` raises ws->failed.
 template <bool VEC, typename KEY>
 __global__ void __launch_bounds__(kScanBlock)
 k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* ws,
@@ -285,9 +288,10 @@ k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* 
     uint32_t* my_off = st_off + wave * kWaveStage;
     float* my_val = st_val + wave * kWaveStage;
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));   // lanes before mine
-    uint32_t staged = 0;                            // the same in every lane of the wavefront
-    bool overflow = false;
-    auto take = [&](const float (&v)[kItems], int nvalid, int64_t base) {
+    // candidates of my part so far, the same in every lane of the wavefront.  The first kWaveStage are
+    // staged; with `direct` (second reading) all go to the list from `at` on.
+    uint32_t got = 0;
+    auto take = [&](const float (&v)[kItems], int nvalid, int64_t base, bool direct, uint32_t at) {
         bool f[kItems];
         bool any = false;
 #pragma unroll
@@ -303,38 +307,42 @@ k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* 
             before += __builtin_popcountll(m & below);
             total += __builtin_popcountll(m);
         }
-        if (staged + total > static_cast<uint32_t>(kWaveStage)) { overflow = true; return; }
-        uint32_t pos = staged + before;
+        uint32_t pos = got + before;
+        got += total;
+        if (!direct && got > static_cast<uint32_t>(kWaveStage)) return;
 #pragma unroll
         for (int q = 0; q < kItems; ++q)
             if (f[q]) {
-                my_off[pos] = static_cast<uint32_t>(base + q - lo);
-                my_val[pos] = v[q];
+                if (direct) {
+                    cand_idx[at + pos] = base + q;
+                    cand_val[at + pos] = v[q];
+                } else {
+                    my_off[pos] = static_cast<uint32_t>(base + q - lo);
+                    my_val[pos] = v[q];
+                }
                 ++pos;
             }
-        staged += total;
     };
-    for (int64_t tile = wlo; tile < whi && !overflow; tile += kTiles * kWaveTile) {
-        float v[kTiles][kItems];
-        int n[kTiles];
-        const int64_t b0 = tile + static_cast<int64_t>(lane) * kItems;
+    auto read_part = [&](bool direct, uint32_t at) {
+        for (int64_t tile = wlo; tile < whi; tile += kTiles * kWaveTile) {
+            float v[kTiles][kItems];
+            int n[kTiles];
+            const int64_t b0 = tile + static_cast<int64_t>(lane) * kItems;
 #pragma unroll
-        for (int u = 0; u < kTiles; ++u) load_items<VEC>(est, b0 + u * kWaveTile, whi, v[u], n[u]);
+            for (int u = 0; u < kTiles; ++u) load_items<VEC>(est, b0 + u * kWaveTile, whi, v[u], n[u]);
 #pragma unroll
-        for (int u = 0; u < kTiles; ++u)
-            if (!overflow) take(v[u], n[u], b0 + u * kWaveTile);
-    }
-    if (lane == 0) wave_n[wave] = overflow ? 0xffffffffu : staged;
+            for (int u = 0; u < kTiles; ++u) take(v[u], n[u], b0 + u * kWaveTile, direct, at);
+        }
+    };
+    read_part(false, 0u);
+    if (lane == 0) wave_n[wave] = got;
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t total = 0;
-        bool ok = true;
-        for (int w = 0; w < kScanWaves; ++w) {
-            if (wave_n[w] == 0xffffffffu) ok = false;
-            else total += wave_n[w];
-        }
+        for (int w = 0; w < kScanWaves; ++w) total += wave_n[w];
         uint32_t base = 0;
-        if (ok && total) {
+        bool ok = true;
+        if (total) {
             base = atomicAdd(&ws->ncand, total);
             ok = static_cast<uint64_t>(base) + total <= cap;
         }
@@ -348,7 +356,12 @@ k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* 
     if (seg[1] == 0u) return;
     uint32_t at = seg[0];
     for (int w = 0; w < wave; ++w) at += wave_n[w];
-    for (uint32_t t = lane; t < staged; t += 64) {
+    if (got > static_cast<uint32_t>(kWaveStage)) {
+        got = 0;
+        read_part(true, at);
+        return;
+    }
+    for (uint32_t t = lane; t < got; t += 64) {
         cand_idx[at + t] = lo + my_off[t];
         cand_val[at + t] = my_val[t];
     }

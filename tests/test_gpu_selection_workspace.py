@@ -89,3 +89,37 @@ def test_one_kept_workspace_serves_every_kind_of_selection_in_turn():
         kept(noise, 2000)
         step()
         kept(noise, 2000)
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("k", [3_000, 300_000, 400_001])
+def test_selection_from_crowded_parts_and_long_segments(offset, k):
+    """Parts of the vector with more candidates than a wavefront stages (2048 of 2048, and half of them),
+    a list with more than 512 candidates per segment, and equal magnitudes at the k-th place, with and
+    without room for the list, and as HEAVYMIX."""
+    d = 8_400_005
+    rng = np.random.default_rng(k + offset)
+    est = (rng.standard_normal(d) * 0.01).astype(np.float32)
+    some = rng.choice(d, 500_000, replace=False)
+    est[some] = (rng.integers(16, 31, size=some.size) / 16 * rng.choice([-1.0, 1.0], size=some.size)).astype(np.float32)
+    est[1_000_001:1_009_000] = 1.5
+    est[5_000_000:5_040_000:2] = -1.25
+    base = torch.zeros(d + 1, dtype=torch.float32, device=DEV)
+    view = base[offset:offset + d]
+    view.copy_(torch.from_numpy(est))
+    want = orc.topk_threshold(est, k)
+    full, bare = cs.cs_topk_workspace_bytes(d, k), cs.cs_topk_workspace_bytes(1, 1)
+    assert full > bare + 12 * (2 * k + 4096)
+    for nbytes in (full, bare):
+        ws = torch.full((nbytes,), 0x3D, dtype=torch.uint8, device=DEV)
+        idx = torch.full((k,), -1, dtype=torch.int64, device=DEV)
+        val = torch.empty(k, dtype=torch.float32, device=DEV)
+        cs.cs_heavy_hitters_topk(view, k, idx, val, ws)
+        np.testing.assert_array_equal(idx.cpu().numpy(), want)
+        np.testing.assert_array_equal(val.cpu().numpy(), est[want])
+        n_heavy = torch.full((1,), -1, dtype=torch.int64, device=DEV)
+        l2sq = float(k) * 1.2 ** 2                                  # heavy: magnitudes of 1.25 and more
+        cs.cs_heavymix_select(view, k, torch.tensor([l2sq], dtype=torch.float64, device=DEV), 5, idx, val, n_heavy, ws)
+        mix, heavy = orc.heavymix_select(est, k, l2sq, 5)
+        np.testing.assert_array_equal(idx.cpu().numpy(), mix)
+        assert int(n_heavy.item()) == heavy
