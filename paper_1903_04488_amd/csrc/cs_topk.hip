@@ -566,6 +566,12 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
     if (want > static_cast<int64_t>(gridDim.x)) want = gridDim.x;
     if (from_list && want > nseg) want = nseg;
     const uint32_t tasks = static_cast<uint32_t>(want);
+    // Segments of the list that are long on the average are worked through by a whole workgroup, short
+    // ones by a wavefront each (a workgroup has two or three of them, so that most of its wavefronts
+    // would stand by while long ones are read 64 candidates at a time).  Lists of 3.6 M, 2.6 M and 1.6 M
+    // candidates: this kernel takes 105, 100 and 85 us for 180, 170 and 125; a few hundred per segment
+    // take two or three turns either way.
+    const bool long_segments = n > 512u * static_cast<uint32_t>(nseg);
     if (blockIdx.x >= tasks) return;
     __shared__ uint32_t drawn;
     const int64_t est_chunk = ((d + tasks - 1) / tasks + 4095) / 4096 * 4096;
@@ -658,7 +664,22 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
             if (v) atomicAdd(reinterpret_cast<unsigned long long*>(&ws->hist[phase + 1][tid]),
                              static_cast<unsigned long long>(v));
         } else if (phase == 2) {
-            if (from_list) {                        // one wavefront per segment
+            if (from_list && long_segments) {       // the workgroup together, one segment after the other
+                for (int b = seg0; b < seg1; ++b) {
+                    const uint32_t base = ws->seg_base[b], cnt = ws->seg_count[b];
+                    uint64_t c = 0, total;          // low word: greater, high word: equal
+#pragma unroll 4
+                    for (uint32_t p = tid; p < cnt; p += kSelBlock) {
+                        const uint32_t key = kf(cand_val[base + p], cand_idx[base + p]);
+                        c += (key > prefix ? 1ull : 0ull) | (key == prefix ? 1ull << 32 : 0ull);
+                    }
+                    block_exclusive_sum<kSelWaves>(c, s.scan, &total);
+                    if (tid == 0) {
+                        store_shared(&ws->gt[b], static_cast<uint64_t>(static_cast<uint32_t>(total)));
+                        store_shared(&ws->eq[b], total >> 32);
+                    }
+                }
+            } else if (from_list) {                 // one wavefront per segment
                 for (int b = seg0 + wave; b < seg1; b += kSelWaves) {
                     const uint32_t base = ws->seg_base[b], cnt = ws->seg_count[b];
                     uint32_t n_gt = 0, n_eq = 0;
@@ -702,6 +723,36 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
         } else {
             const uint64_t need_eq = k_rem;
             uint32_t heavy = 0;
+            // one tile of the workgroup: kItems consecutive items per thread, g greater and e equal
+            // ones before the tile (moved on past it); at(q) is the index of the thread's q-th item
+            auto write_tile = [&](const float (&v)[kItems], int nvalid, uint64_t& g, uint64_t& e, auto at) {
+                uint64_t c = 0;                     // low word: greater, high word: equal
+#pragma unroll
+                for (int q = 0; q < kItems; ++q) {
+                    if (q >= nvalid) break;
+                    const uint32_t key = kf(v[q], at(q));
+                    c += (key > prefix ? 1ull : 0ull) | (key == prefix ? 1ull << 32 : 0ull);
+                }
+                uint64_t total;
+                const uint64_t before = block_exclusive_sum<kSelWaves>(c, s.scan, &total);
+                if (c) {
+                    uint64_t my_g = g + static_cast<uint32_t>(before), my_e = e + (before >> 32);
+#pragma unroll
+                    for (int q = 0; q < kItems; ++q) {
+                        if (q >= nvalid) break;
+                        const uint32_t key = kf(v[q], at(q));
+                        const bool is_gt = key > prefix, is_eq = key == prefix;
+                        if (is_gt || (is_eq && my_e < need_eq)) {
+                            out.put(my_g + (my_e < need_eq ? my_e : need_eq), at(q), v[q]);
+                            heavy += key >> 30;
+                        }
+                        my_g += is_gt;
+                        my_e += is_eq;
+                    }
+                }
+                g += static_cast<uint32_t>(total);
+                e += total >> 32;
+            };
             if (from_list) {
                 // slots before each segment: a scan over all of them
                 uint64_t all;
@@ -711,7 +762,29 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
                 if (in) { s.mask_gt[tid] = g0; s.mask_eq[tid] = e0; }
                 __syncthreads();
                 const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));   // lanes before mine
-                for (int b = seg0 + wave; b < seg1; b += kSelWaves) {
+                for (int b = seg0; long_segments && b < seg1; ++b) {
+                    uint64_t g = s.mask_gt[b], e = s.mask_eq[b];
+                    const uint32_t base = ws->seg_base[b], cnt = ws->seg_count[b];
+                    for (uint32_t p0 = 0; p0 < cnt; p0 += kSelBlock * kItems) {
+                        float v[kItems];
+                        int64_t i[kItems];
+                        int nvalid = 0;
+                        const uint32_t p = p0 + tid * kItems;
+#pragma unroll
+                        for (int q = 0; q < kItems; ++q) {
+                            if (p + q < cnt) {
+                                v[q] = cand_val[base + p + q];
+                                i[q] = cand_idx[base + p + q];
+                                nvalid = q + 1;
+                            } else {
+                                v[q] = 0.0f;
+                                i[q] = 0;
+                            }
+                        }
+                        write_tile(v, nvalid, g, e, [&](int q) { return i[q]; });
+                    }
+                }
+                for (int b = seg0 + wave; !long_segments && b < seg1; b += kSelWaves) {
                     uint64_t g = s.mask_gt[b], e = s.mask_eq[b];
                     const uint32_t base = ws->seg_base[b], cnt = ws->seg_count[b];
                     for (uint32_t p0 = 0; p0 < cnt; p0 += 64) {
@@ -754,32 +827,7 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
                     int nvalid;
                     const int64_t base = tile + static_cast<int64_t>(tid) * kItems;
                     load_items<VEC>(est, base, hi, v, nvalid);
-                    uint64_t c = 0;                 // low word: greater, high word: equal
-#pragma unroll
-                    for (int q = 0; q < kItems; ++q) {
-                        if (q >= nvalid) break;
-                        const uint32_t key = kf(v[q], base + q);
-                        c += (key > prefix ? 1ull : 0ull) | (key == prefix ? 1ull << 32 : 0ull);
-                    }
-                    uint64_t total;
-                    const uint64_t before = block_exclusive_sum<kSelWaves>(c, s.scan, &total);
-                    if (c) {
-                        uint64_t my_g = g + static_cast<uint32_t>(before), my_e = e + (before >> 32);
-#pragma unroll
-                        for (int q = 0; q < kItems; ++q) {
-                            if (q >= nvalid) break;
-                            const uint32_t key = kf(v[q], base + q);
-                            const bool is_gt = key > prefix, is_eq = key == prefix;
-                            if (is_gt || (is_eq && my_e < need_eq)) {
-                                out.put(my_g + (my_e < need_eq ? my_e : need_eq), base + q, v[q]);
-                                heavy += key >> 30;
-                            }
-                            my_g += is_gt;
-                            my_e += is_eq;
-                        }
-                    }
-                    g += static_cast<uint32_t>(total);
-                    e += total >> 32;
+                    write_tile(v, nvalid, g, e, [&](int q) { return base + q; });
                 }
             }
             if (out.n_heavy && heavy) atomicAdd(&ws->heavy, heavy);
