@@ -125,6 +125,9 @@ void plan_walk(cs_row_plan* rp, uint64_t a, uint64_t as, uint32_t c, bool pow2, 
 // wavefronts, each of which sends requests of its own; never less than reading the 8 vectors at
 // the rate this access pattern reaches; plus the atomic requests at the rate of the memory-side
 // atomic unit.  The constants are measurements on MI355X (bundle update at d = 10^6 .. 10^8).
+// A list is chosen before it is known how many workers will follow it: the group of 8 stands for
+// all, single vectors included, and kVisitNs for the run lengths of the launch, which cuts the
+// chains by its own prices (cs_walk.hip: 700 ns with RUN = 8, 1300 with 16, 500 for one vector).
 double update_time_ns(double visits, double residues, double requests, double d, bool shared) {
     const double kVisitNs = 900.0, kResidentWaves = 4096.0;
     const double kBytesPerNs = 4600.0, kRequestsPerNs = 24.0;

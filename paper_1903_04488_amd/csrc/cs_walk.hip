@@ -777,21 +777,24 @@ void choose_pieces(LIST& rows, int nrows, const double* requests, double visit_n
     }
 }
 
-// a turn of the walkers of 8 (4, 2) workers with RUN = 8 and with RUN = 16, and of a single vector
+// A turn of the walkers of 8 (4, 2) workers with RUN = 8 and with RUN = 16, and of a single vector.  (The
+// planner, which knows neither the workers nor the run length that a launch will have, prices a
+// turn at 900 ns.)
 // (priced as RUN = 8, chains of 316 visits of 4 workers stayed whole: d = 22.4 M, c = 65 536, 738 us a step for 596)
 constexpr double kVisitNs8 = 700.0, kVisitNs16 = 1300.0, kVisitNsOne = 500.0;
 constexpr double kStreamBytesPerNs = 5000.0;
 
-// The same for a group of workers; true = RUN = 8.
+// The same for a group of workers; true = RUN = 8.  requests8, requests16: what a residue of each row
+// sends with either run length.
 // RUN = 16 with few wavefronts leaves most of the chip idle (1024 SIMDs): RUN = 8 then gives twice as
 // many, each with half the work per visit, which is what a short vector's time consists of.
 template <int WL, typename LIST>
-bool choose_run8(LIST& rows, int nrows, const double* requests, double stream_ns) {
-    choose_pieces(rows, nrows, requests, kVisitNs8, stream_ns);
+bool choose_run8(LIST& rows, int nrows, const double* requests8, const double* requests16, double stream_ns) {
+    choose_pieces(rows, nrows, requests8, kVisitNs8, stream_ns);
     int64_t waves = 0;                                   // with RUN = 16
     for (int q = 0; q < nrows; ++q) waves += static_cast<int64_t>(rows.row[q].gmax) * WL / 1024 * rows.row[q].pieces;
     if (waves < 2048) return true;
-    choose_pieces(rows, nrows, requests, kVisitNs16, stream_ns);
+    choose_pieces(rows, nrows, requests16, kVisitNs16, stream_ns);
     return false;
 }
 
@@ -846,14 +849,17 @@ template <int WL, int NWAVE>
 int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js, int nrows,
                   uint32_t ncell, hipStream_t stream) {
     VisitRows rows{};
-    double requests[kRowsPerLaunch];
+    // every sum is a request, but RUN = 8 sends the two cells of an aligned block of a bundle in one
+    double requests8[kRowsPerLaunch], requests16[kRowsPerLaunch];
     for (int q = 0; q < nrows; ++q) {
         const cs_visit_plan& vp = p->visit[js[q]];
         fill_visit_args(p, js[q], rows.row[q]);
-        requests[q] = (0.5 * vp.ncell + 0.5) * static_cast<double>(vp.gmax);   // as RUN = 8 sends them
+        requests16[q] = static_cast<double>(vp.ncell) * static_cast<double>(vp.gmax);
+        requests8[q] = a.fold ? requests16[q] : (0.5 * vp.ncell + 0.5) * static_cast<double>(vp.gmax);
     }
     const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * nrows / kStreamBytesPerNs;
-    if (choose_run8<WL>(rows, nrows, requests, stream_ns)) return launch_visits_run<WL, 8, 1>(rows, a, nrows, ncell, stream);
+    if (choose_run8<WL>(rows, nrows, requests8, requests16, stream_ns))
+        return launch_visits_run<WL, 8, 1>(rows, a, nrows, ncell, stream);
     return launch_visits_run<WL, 16, NWAVE>(rows, a, nrows, ncell, stream);
 }
 
@@ -913,7 +919,7 @@ int launch_visits_anyc(const cs_params* p, const VisitWorkers& a, const uint32_t
         requests[q] = 2.0 * rows.row[q].omega * static_cast<double>(rows.row[q].gmax);
     }
     const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * n / kStreamBytesPerNs;
-    if (choose_run8<WL>(rows, n, requests, stream_ns)) {
+    if (choose_run8<WL>(rows, n, requests, requests, stream_ns)) {
         const dim3 grid(visits_grid<WL, 8, 1>(rows, n));
         if (omega == 1) k_accumulate_visits<WL, 8, 1, 2, VisitGapsRows><<<grid, 64, 0, stream>>>(rows, a);
         else k_accumulate_visits<WL, 8, 1, 4, VisitGapsRows><<<grid, 64, 0, stream>>>(rows, a);
