@@ -137,13 +137,13 @@ class HotPath:
         if self.rho is not None:
             B.cs_sketch_feedback_pair(self.params, self.S_v, self.S_u, self.idx, self.delta, self.uhat)
 
-    def _overridden(self, stage):
-        return stage in self.__dict__ or getattr(type(self), stage) is not getattr(HotPath, stage)
-
     def aggregate(self):
         """merge and momentum, in one pass where the workers have tables of their own and neither
         stage is overridden"""
-        if self.rho is None or self.fold_workers or self._overridden("merge") or self._overridden("momentum"):
+        cls, own = type(self), self.__dict__
+        if (self.rho is None or self.fold_workers
+                or cls.merge is not HotPath.merge or cls.momentum is not HotPath.momentum
+                or "merge" in own or "momentum" in own):
             self.merge()
             self.momentum()
             return
