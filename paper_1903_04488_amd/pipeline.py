@@ -85,7 +85,10 @@ class HotPath:
             if len(g_w) == 1:
                 B.cs_sketch_accumulate(self.params, self.S_t, g_w[0], scale=1.0 / self.W)
                 return
-            mean = self._mean_buffer(g_w[0].numel())
+            n = g_w[0].numel()
+            mean = self.g_mean
+            if mean is None or mean.numel() != n:
+                mean = self._mean_buffer(n)
             B.cs_vectors_sum(g_w, mean, alpha=1.0 / self.W)
             B.cs_sketch_accumulate(self.params, self.S_t, mean)
             return
