@@ -293,7 +293,19 @@ constexpr int kRowsPerLaunch = 8;
 // power of two: with 4 sets of 2 wavefronts an XCD's block is exactly 4 KB of every vector, each
 // XCD then keeps meeting the same addresses modulo 32 KB, and the update measured 1 % slower
 // (1, 2, 4, 16: slower; 3, 5, 6, 8: within 0.5 % of each other).
+// A row with fewer sets than one round of that (8 XCDs x 5) has a workgroup per set, dealt singly: its
+// sets would all go to the first XCDs, and most of the workgroups would be empty (15 rows,
+// c = 128, d = 11 475: 7160 of them for 560 sets, 13.9 us a launch of 8 workers for 10.2).
 constexpr int kVisitSetBlock = 5;
+constexpr uint32_t kVisitRound = 8 * kVisitSetBlock;
+// the set that turn vi of a row with `blocks` workgroups stands for, and the first set of its round
+__device__ __forceinline__ int64_t visit_set(int64_t vi, uint32_t blocks) {
+    const int64_t slot = vi >> 3;
+    return blocks < kVisitRound ? vi : ((slot / kVisitSetBlock) * 8 + (vi & 7)) * kVisitSetBlock + slot % kVisitSetBlock;
+}
+__device__ __forceinline__ int64_t visit_round(int64_t vi, uint32_t blocks) {
+    return blocks < kVisitRound ? vi : (vi >> 3) / kVisitSetBlock * kVisitRound;
+}
 struct VisitRows {
     uint32_t first[kRowsPerLaunch];              // ~0: no such row
     VisitArgs row[kRowsPerLaunch];
@@ -394,7 +406,6 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
     constexpr int PPL = RUN / WL;                      // hash values each lane computes
     constexpr int SPAN = WPW * RUN;                    // residues a wavefront owns
     constexpr int kStride = RUN + 1;
-    constexpr int kSetBlock = kVisitSetBlock;          // neighbouring walker sets per XCD turn
     constexpr int kRec = NC == 2 ? 2 : 4;              // words of a coordinate's record
     // records of one walker, padded by one record: the 8 lanes of a walker read the same record
     // (a broadcast), the walkers of a wavefront different ones, which without the pad would
@@ -512,9 +523,8 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
     const uint32_t k0 = v.K * piece / v.pieces, k1 = v.K * (piece + 1) / v.pieces;
     const int64_t s0 = offset_of_visit(k0, [&](uint32_t k) { return gap_of(code_of(k)); });
     for (int64_t vi = block; ; vi += v.blocks) {
-        const int64_t slot = vi >> 3;
-        const int64_t set = ((slot / kSetBlock) * 8 + (vi & 7)) * kSetBlock + slot % kSetBlock;
-        if ((slot / kSetBlock) * 8 * kSetBlock >= ngroups) break;
+        if (visit_round(vi, v.blocks) >= ngroups) break;
+        const int64_t set = visit_set(vi, v.blocks);
         const int64_t wv = set * NWAVE + wq;
         if (set >= ngroups || wv >= nwaves) continue;
         const int64_t first_res = wv * SPAN;           // first residue of this wavefront's walkers
@@ -820,9 +830,9 @@ unsigned visits_grid(LIST& rows, int nrows) {
         const int64_t ngroups = (nwaves + NWAVE - 1) / NWAVE;
         const int64_t cap = 256 * 64 / NWAVE;              // enough to fill the chip several times over
         int64_t n = ngroups < cap ? ngroups : cap;
-        // the kernel deals sets to the 8 XCDs in blocks of kVisitSetBlock: whole blocks, so that
+        // the kernel deals sets to the 8 XCDs in blocks of kVisitSetBlock: whole rounds, so that
         // no workgroup takes a second set
-        n = (n + 8 * kVisitSetBlock - 1) / (8 * kVisitSetBlock) * (8 * kVisitSetBlock);
+        if (n >= kVisitRound) n = (n + kVisitRound - 1) / kVisitRound * kVisitRound;
         rows.row[q].blocks = static_cast<uint32_t>(n);
         rows.first[q] = total;
         total += rows.row[q].blocks * rows.row[q].pieces;
@@ -1028,11 +1038,9 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
     const int64_t s0 = offset_of_visit(k0, gap_of);
 
     // sets of neighbouring wavefronts go to one XCD, as in k_accumulate_visits
-    constexpr int kBlk = kVisitSetBlock;
     for (int64_t vi = block; ; vi += v.blocks) {
-        const int64_t slot = vi >> 3;
-        const int64_t wv = ((slot / kBlk) * 8 + (vi & 7)) * kBlk + slot % kBlk;
-        if ((slot / kBlk) * 8 * kBlk >= nwaves) break;
+        if (visit_round(vi, v.blocks) >= nwaves) break;
+        const int64_t wv = visit_set(vi, v.blocks);
         if (wv >= nwaves) continue;
         const int64_t wave_res = wv * SPAN;
         const int64_t my_res = wave_res + lane * kOneRun;
