@@ -125,7 +125,7 @@ def _listed(p, d, forged):
     return p
 
 
-@pytest.mark.parametrize("r,c,d", [(5, 1 << 12, 200_003), (3, 5001, 1_000_003)])
+@pytest.mark.parametrize("r,c,d", [(5, 1 << 12, 200_003), (3, 5001, 1_000_003), (5, 1 << 15, 2_500_003)])
 @pytest.mark.parametrize("forged", [False, True])
 def test_update_of_one_vector_with_nan_infinities_and_forged_lists(r, c, d, forged):
     """Into a table of its own, into a slot of a bundle (the ninth worker), and summed: a NaN or an
@@ -155,3 +155,23 @@ def test_update_of_one_vector_with_nan_infinities_and_forged_lists(r, c, d, forg
             fin = np.isfinite(ref)
             assert fin.sum() >= ref.size - 5 * r
             assert_cells_close(np.where(fin, got, 0), np.where(fin, ref, 0), terms_per_cell=d / c)
+
+
+@pytest.mark.parametrize("r,c", [(3, 1 << 14), (5, 1 << 16)])
+@pytest.mark.parametrize("below", [0, 1])
+def test_update_of_one_vector_where_its_two_forms_meet(r, c, below):
+    """r d = 12 million: from there on along visit lists, below as a lattice"""
+    d = 12_000_000 // r - below
+    p = cs.cs_params_init(r, c, 21, d)
+    g = torch.randn(d, generator=torch.Generator().manual_seed(d)) * 0.01
+    S = torch.full((r, c), 0.25, dtype=torch.float32, device=DEV)
+    cs.cs_sketch_accumulate(p, S, g.to(DEV), i0=11, scale=-0.5)
+    ref = sketch_in_slices_from(orc.SketchOracle(r, c, 21), g.numpy(), 11)
+    assert_cells_close(S.cpu().numpy(), 0.25 - 0.5 * ref, terms_per_cell=d / c)
+
+
+def sketch_in_slices_from(sk, g, i0):
+    from concurrent.futures import ThreadPoolExecutor
+    n = 1 << 19
+    with ThreadPoolExecutor(max_workers=8) as pool:
+        return sum(pool.map(lambda lo: sk.sketch(g[lo:lo + n], i0=i0 + lo), range(0, g.size, n)), sk.zeros())
