@@ -756,11 +756,12 @@ extern "C" int cs_sketch_accumulate(const cs_params* p, float* S, const float* g
     if (d == 0) return CS_OK;
     if (!S || !g) return CS_EINVAL;
     // The lattice form is the better one for short vectors: its time is about 5 us plus that of r d
-    // coordinates at 300 to 400 G/s, while a list's chains of visits and their requests take 30 us and more
-    // from d = 10^6 on and 10 to 30 below.  Lists against lattice, us: 31 / 19 (5 x 8192, d = 1.1 M), 45 / 40
-    // (3 x 32 768, 3.9 M), 51 / 57 (3 x 65 536, 4.5 M), 47 / 52 (7 x 4096, 1.6 M), 61 / 72 (5 x 65 536, 4.0 M),
-    // 466 / 1162 (5 x 2^20, 73 M): the two meet where r d is about 12 million.
-    constexpr int64_t kOneFrom = 12000000;
+    // coordinates at 250 to 400 G/s, while a list's chains of visits and their requests take 35 to 45 us from
+    // r d = 5 million on and 10 to 30 below.  Lists / lattice, us: 31 / 19 (5 x 8192, d = 1.1 M), 45 / 40
+    // (3 x 32 768, 3.9 M), 61 / 72 (5 x 65 536, 4.0 M), 48 / 65 (5 x 16 384, 3.5 M), 466 / 1162 (5 x 2^20, 73 M).
+    // Of 67 shapes with r d of 7 to 18 million the lattice is ahead in 36 of the 38 below 12 million (by up to
+    // 1.5 times, behind by 4 % at most), the two take turns up to 15, and lists are ahead from there.
+    constexpr int64_t kOneFrom = 15000000;
     const bool short_vector = lattice_applies(p, d) && static_cast<int64_t>(p->r) * d < kOneFrom;
     if (!short_vector && one_applies(p, d)) return launch_accumulate_one(p, S, 1, g, d, i0, scale, as_stream(stream));
     BatchPtrs ptrs{};

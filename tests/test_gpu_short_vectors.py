@@ -125,7 +125,7 @@ def _listed(p, d, forged):
     return p
 
 
-@pytest.mark.parametrize("r,c,d", [(5, 1 << 12, 200_003), (3, 5001, 1_000_003), (5, 1 << 15, 2_500_003)])
+@pytest.mark.parametrize("r,c,d", [(5, 1 << 12, 200_003), (3, 5001, 1_000_003), (5, 1 << 15, 3_000_003)])
 @pytest.mark.parametrize("forged", [False, True])
 def test_update_of_one_vector_with_nan_infinities_and_forged_lists(r, c, d, forged):
     """Into a table of its own, into a slot of a bundle (the ninth worker), and summed: a NaN or an
@@ -160,8 +160,8 @@ def test_update_of_one_vector_with_nan_infinities_and_forged_lists(r, c, d, forg
 @pytest.mark.parametrize("r,c", [(3, 1 << 14), (5, 1 << 16)])
 @pytest.mark.parametrize("below", [0, 1])
 def test_update_of_one_vector_where_its_two_forms_meet(r, c, below):
-    """r d = 12 million: from there on along visit lists, below as a lattice"""
-    d = 12_000_000 // r - below
+    """r d = 15 million: from there on along visit lists, below as a lattice"""
+    d = 15_000_000 // r - below
     p = cs.cs_params_init(r, c, 21, d)
     g = torch.randn(d, generator=torch.Generator().manual_seed(d)) * 0.01
     S = torch.full((r, c), 0.25, dtype=torch.float32, device=DEV)
