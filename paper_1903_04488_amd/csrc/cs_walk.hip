@@ -293,11 +293,14 @@ constexpr int kRowsPerLaunch = 8;
 // power of two: with 4 sets of 2 wavefronts an XCD's block is exactly 4 KB of every vector, each
 // XCD then keeps meeting the same addresses modulo 32 KB, and the update measured 1 % slower
 // (1, 2, 4, 16: slower; 3, 5, 6, 8: within 0.5 % of each other).
-// A row with fewer sets than one round of that (8 XCDs x 5) has a workgroup per set, dealt singly: its
-// sets would all go to the first XCDs, and most of the workgroups would be empty (15 rows,
-// c = 128, d = 11 475: 7160 of them for 560 sets, 13.9 us a launch of 8 workers for 10.2).
+// Whole rounds of 8 XCDs x 5 sets leave workgroups empty, most of them where rows of a few sets are
+// cut into many pieces; a launch that would have more than kRoundsUpTo workgroups for that deals rows of less
+// than a round singly, a workgroup per set (15 rows, c = 128, d = 11 475: 7160 workgroups for 560 sets,
+// 13.9 us a launch of 8 workers for 10.2).  Smaller launches keep the rounds: neighbouring sets share
+// cache lines (7 rows, c = 512, d = 12 494, 1480 workgroups for 608 sets: 0.6 us less than dealt singly).
 constexpr int kVisitSetBlock = 5;
 constexpr uint32_t kVisitRound = 8 * kVisitSetBlock;
+constexpr unsigned kRoundsUpTo = 2048;
 // the set that turn vi of a row with `blocks` workgroups stands for, and the first set of its round
 __device__ __forceinline__ int64_t visit_set(int64_t vi, uint32_t blocks) {
     const int64_t slot = vi >> 3;
@@ -823,20 +826,25 @@ template <int WL, int RUN, int NWAVE, typename LIST>
 unsigned visits_grid(LIST& rows, int nrows) {
     constexpr int WPW = 64 / WL;
     constexpr int N = sizeof(rows.first) / sizeof(rows.first[0]);
-    unsigned total = 0;
-    for (int q = 0; q < nrows; ++q) {
-        const int64_t chunks = (static_cast<int64_t>(rows.row[q].gmax) + RUN - 1) / RUN;
-        const int64_t nwaves = (chunks + WPW - 1) / WPW;
-        const int64_t ngroups = (nwaves + NWAVE - 1) / NWAVE;
-        const int64_t cap = 256 * 64 / NWAVE;              // enough to fill the chip several times over
-        int64_t n = ngroups < cap ? ngroups : cap;
-        // the kernel deals sets to the 8 XCDs in blocks of kVisitSetBlock: whole rounds, so that
-        // no workgroup takes a second set
-        if (n >= kVisitRound) n = (n + kVisitRound - 1) / kVisitRound * kVisitRound;
-        rows.row[q].blocks = static_cast<uint32_t>(n);
-        rows.first[q] = total;
-        total += rows.row[q].blocks * rows.row[q].pieces;
-    }
+    auto lay_out = [&](bool singly) -> unsigned {
+        unsigned total = 0;
+        for (int q = 0; q < nrows; ++q) {
+            const int64_t chunks = (static_cast<int64_t>(rows.row[q].gmax) + RUN - 1) / RUN;
+            const int64_t nwaves = (chunks + WPW - 1) / WPW;
+            const int64_t ngroups = (nwaves + NWAVE - 1) / NWAVE;
+            const int64_t cap = 256 * 64 / NWAVE;              // enough to fill the chip several times over
+            int64_t n = ngroups < cap ? ngroups : cap;
+            // the kernel deals sets to the 8 XCDs in blocks of kVisitSetBlock: whole rounds, so that
+            // no workgroup takes a second set
+            if (!singly || n >= kVisitRound) n = (n + kVisitRound - 1) / kVisitRound * kVisitRound;
+            rows.row[q].blocks = static_cast<uint32_t>(n);
+            rows.first[q] = total;
+            total += rows.row[q].blocks * rows.row[q].pieces;
+        }
+        return total;
+    };
+    unsigned total = lay_out(false);
+    if (total > kRoundsUpTo) total = lay_out(true);
     for (int q = nrows; q < N; ++q) rows.first[q] = ~0u;
     return total;
 }
