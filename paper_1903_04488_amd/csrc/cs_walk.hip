@@ -950,87 +950,168 @@ int launch_visits_anyc(const cs_params* p, const VisitWorkers& a, const uint32_t
 }
 
 // ---------------------------------------------------------------------------------------
+// What a visit does to the hashes of a coordinate, told by two comparisons.
+//
+// Visit k is at offset s_k, and with A = (a s_k) mod p the bucket hash of i + s_k is x + A, less p if
+// x >= p - A, where x is that of i.  A is the same for every coordinate, so the bucket moves on by A mod c,
+// and by p mod c back in the second case (one cell further if c is a power of two, for p = -1 mod c):
+// one of two cells, and which one is the comparison of x with p - 1 - A.  The sign hash likewise: its
+// parity is that of x' plus that of A', inverted after a wrap.  So a lane keeps the top 32 bits of x and x' of
+// its coordinates and compares them with the top 32 bits of the visit's two thresholds (bits 29..60);
+// where they are equal the lower bits would decide, and the visit is hashed by the definition
+// instead (once in 2^31 coordinates and visits).  Against carrying two 61-bit states per coordinate from visit
+// to visit this takes 10 vector operations per coordinate and visit for about 25.
+//
+// The visits are walked in the order of A mod c, so that at any time only the two sums of one value of it are
+// in registers; the others wait in LDS.
+// ---------------------------------------------------------------------------------------
+constexpr int kTopShift = 29;                          // 61-bit hash value -> its top 32 bits
+__device__ __forceinline__ uint32_t top_of(uint64_t y) { return static_cast<uint32_t>((y - 1) >> kTopShift); }
+// x wraps on an advance by A when it is above p - 1 - A
+__device__ __forceinline__ uint32_t threshold_of(uint64_t A) { return static_cast<uint32_t>((kP61 - 1 - A) >> kTopShift); }
+
+// A visit.  x: threshold of the bucket hash, y: of the sign hash, z: offset, w: bits 0..28 its gap (residues
+// that take part), bit 29 the parity of A', bits 30-31 A mod c (the running sum of a coordinate that does not
+// wrap), or 3 where that is none of the sums that are kept.
+constexpr uint32_t kGapMask = (1u << 29) - 1u;
+constexpr int64_t kStepsMaxD = 1ll << 29;              // offsets and gaps of longer vectors do not fit
+
+// The visits k0 .. k1 - 1 (at most MAX) in the order of A mod c, by all wavefronts of the workgroup; returns how
+// many of them are not `3`, which come first.  gap_of(k): residues of visit k; within: A mod c must be below it.
+template <bool POW2, int NWAVE, int MAX, typename GAP>
+__device__ __forceinline__ uint32_t fill_visit_steps(uint4* steps, uint32_t k0, uint32_t k1, uint64_t a, uint64_t as,
+                                                     const Columns& col, uint32_t within, GAP gap_of) {
+    constexpr int kChunks = (MAX + 63) / 64;
+    constexpr int kMine = (kChunks + NWAVE - 1) / NWAVE;
+    __shared__ uint32_t count[kChunks][4];
+    const int lane = threadIdx.x & 63, wq = threadIdx.x >> 6;
+    uint4 mine[kMine];
+    uint32_t rank[kMine];
+#pragma unroll
+    for (int u = 0; u < kMine; ++u) {
+        const int chunk = u * NWAVE + wq;
+        const uint32_t base = k0 + chunk * 64, k = base + lane;
+        if (chunk >= kChunks) continue;
+        uint32_t q = 4u;                               // no such visit
+        if (base < k1) {
+            const int64_t before = offset_of_visit(base, gap_of);
+            const uint64_t gap = k < k1 ? static_cast<uint64_t>(gap_of(k)) : 0;
+            uint64_t upto = gap;                       // of the gaps up to mine
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint64_t other = __shfl_up(upto, off);
+                upto += lane >= off ? other : 0;
+            }
+            const uint64_t s = static_cast<uint64_t>(before) + upto - gap;
+            const uint64_t A = mulmod_p(a, s), As = mulmod_p(as, s);
+            const uint32_t cell = bucket_of<POW2>(A + 1, col);
+            if (k < k1) q = cell < within ? cell : 3u;
+            mine[u] = make_uint4(threshold_of(A), threshold_of(As),
+                                 static_cast<uint32_t>(s < kStepsMaxD ? s : kStepsMaxD),
+                                 static_cast<uint32_t>(gap < kGapMask ? gap : kGapMask) |
+                                     static_cast<uint32_t>(As & 1u) << 29 | q << 30);
+        }
+        rank[u] = ~0u;
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) {
+            const uint64_t same = __builtin_amdgcn_ballot_w64(q == t);
+            if (lane == 0) count[chunk][t] = __builtin_popcountll(same);
+            if (q == t) rank[u] = t << 16 | __builtin_popcountll(same & ((1ull << lane) - 1));
+        }
+    }
+    __syncthreads();
+    uint32_t listed = 0;
+#pragma unroll
+    for (int u = 0; u < kMine; ++u) {
+        const int chunk = u * NWAVE + wq;
+        if (chunk >= kChunks || rank[u] == ~0u) continue;
+        uint32_t at = rank[u] & 0xffffu;
+        const uint32_t q = rank[u] >> 16;
+        for (uint32_t t = 0; t <= q; ++t)
+            for (int ch = 0; ch < (t < q ? kChunks : chunk); ++ch) at += count[ch][t];
+        steps[at] = mine[u];
+    }
+    for (int ch = 0; ch < kChunks; ++ch) listed += count[ch][0] + count[ch][1] + count[ch][2];
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(listed);
+}
+
+// The visits of steps[0 .. n) that residues from first_res on take part in, one after the other: a list with one
+// short and one long gap leaves most walkers with few of its visits (K = 277, gaps 243 885 and 1 495 226:
+// 66 for five residues in six), and looking at 64 visits at once finds the next without stepping through the others.
+struct VisitCursor {
+    const uint4* steps;
+    uint64_t todo;                                      // visits base .. base + 63 that are left
+    uint32_t base, n;
+    uint32_t first_res, d;
+    __device__ __forceinline__ void look() {
+        const uint32_t k = base + (threadIdx.x & 63);
+        const uint4 e = steps[k < n ? k : 0];
+        todo = __builtin_amdgcn_ballot_w64(k < n && (e.w & kGapMask) > first_res && e.z + first_res < d);
+    }
+    __device__ __forceinline__ VisitCursor(const uint4* steps_, uint32_t n_, uint32_t first_res_, uint32_t d_)
+        : steps(steps_), base(0), n(n_), first_res(first_res_), d(d_) { look(); }
+    // the next visit, or ~0u
+    __device__ __forceinline__ uint32_t next() {
+        while (todo == 0) {
+            if (base + 64 >= n) return ~0u;
+            base += 64;
+            look();
+        }
+        const uint32_t k = base + static_cast<uint32_t>(__builtin_ctzll(todo));
+        todo &= todo - 1;
+        return k;
+    }
+};
+
+// ---------------------------------------------------------------------------------------
 // The update of one vector (one worker, or the workers' vectors summed beforehand) along visit
 // lists.
 //
 // With one vector nothing is shared between lanes, so a lane owns 4 neighbouring residues: a visit
-// is one 16-byte load, 4 hash steps and 4 NC masked additions in registers, without LDS, and a
-// wavefront reads 1 KB of contiguous addresses.  Loads of the next kOneAhead visits are in flight.
+// is one 16-byte load, 8 comparisons and 8 masked additions in registers, and a
+// wavefront reads 1 KB of contiguous addresses.  Loads of the next kOneAhead visits are in flight; every
+// request is one whole load, at the vector's last four values where its own would lie beyond, so that
+// the wait for a visit's values counts the loads behind them.
 // At the end the NC sums of a residue, which lie in neighbouring cells, are brought to
 // neighbouring lanes, so that they leave as one request (an aligned 64-byte block touched by an
-// instruction is one) instead of NC.  Bound: r reads of the vector at 6 TB/s and about 25 vector
-// operations per coordinate and row, side by side, then 1.2 gmax r requests at 21 G/s.
+// instruction is one) instead of NC.  A workgroup of kOneWaves wavefronts shares one table of visits.
+// Measured (update alone, in us; with two 61-bit states per coordinate and a load for every visit of the list, taken
+// part in or not -> now): d = 73 M, 5 x 2^20 468 -> 326; d = 25 M, 5 x 2^19 176 -> 137; d = 11 M, 5 x 2^18 102 -> 74;
+// d = 73 M, 5 x 180 000 492 -> 445.  Bound: the requests at the end (without them 216, 92, 43 and 227 us, which
+// is the five reads at 6.8 TB/s); 2 and 4 loads ahead and 2 and 8 wavefronts per workgroup: within 4 % either way.
 // ---------------------------------------------------------------------------------------
 constexpr int kOneRun = 4;
 constexpr int kOneAhead = 3;
+constexpr int kOneWaves = 4;
 
 template <int NC, typename LIST>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(64 * kOneWaves)
 k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, uint32_t c,
                  int cell_floats, int64_t d, int64_t i0, float scale) {
     constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
     constexpr int SPAN = 64 * kOneRun;
+    constexpr int kMaxSteps = POW2 ? CS_MAX_VISITS : CS_ANYC_MAX_VISITS;
     const unsigned row = row_of_block(rows);
     const auto& v = rows.at(row);
     const uint32_t piece = (blockIdx.x - rows.first[row]) / v.blocks;
     const uint32_t block = (blockIdx.x - rows.first[row]) % v.blocks;
-    const int lane = threadIdx.x;
-    __shared__ float sum_lds[SPAN * NC];
-    __shared__ uint32_t first_lds[SPAN];
-    // hash advances of an any-c list, see k_row_values_visits
-    __shared__ uint64_t adv_b[POW2 ? 1 : CS_ANYC_MAX_VISITS], adv_s[POW2 ? 1 : CS_ANYC_MAX_VISITS];
-    __shared__ uint32_t adv_c[POW2 ? 1 : CS_ANYC_MAX_VISITS];
+    const int lane = threadIdx.x & 63;
+    const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wavefront-uniform
+    __shared__ uint4 steps[kMaxSteps];
+    __shared__ __attribute__((aligned(16))) float sum_lds_all[kOneWaves][NC][SPAN];
+    __shared__ uint32_t left_all[kOneWaves][kMaxSteps / 32 + 1];       // visits left for the definition
+    __shared__ uint32_t first_lds_all[kOneWaves][SPAN];                // cell | sign of a residue
+    float (*sums)[SPAN] = sum_lds_all[wq];
+    uint32_t* first = first_lds_all[wq];
+    uint32_t* left = left_all[wq];
     const Columns col = columns_of<POW2>(c);
-    if constexpr (!POW2) {
-        for (uint32_t k = lane; k < v.K; k += 64) {
-            const uint64_t A = mulmod_p(v.a, v.gap[k]);
-            adv_b[k] = A;
-            adv_s[k] = mulmod_p(v.as, v.gap[k]);
-            adv_c[k] = bucket_of<false>(A + 1, col);
-        }
-        __syncthreads();
-    }
     const uint32_t mask = c - 1u;
-    const uint64_t Aj = v.a, Asj = v.as;
-    const uint32_t Ajc = POW2 ? 0u : bucket_of<false>(Aj + 1, col);
-    auto pick = [](uint32_t code, uint64_t x0, uint64_t x1, uint64_t x2, uint64_t x3) {
-        return code == 0u ? x0 : code == 1u ? x1 : code == 2u ? x2 : x3;
-    };
-    auto code_of = [&](uint32_t k) -> uint32_t {
-        if constexpr (POW2) return (v.code[k >> 4] >> ((k & 15u) * 2u)) & 3u;
-        else return k;
-    };
+    uint32_t omega = NC - 1;                           // values of A mod c that the sums cover
+    if constexpr (!POW2) omega = v.omega;
     auto gap_of = [&](uint32_t k) -> int64_t {
-        if constexpr (POW2) return static_cast<int64_t>(pick(code_of(k), v.gap[0], v.gap[1], v.gap[2], v.gap[3]));
+        if constexpr (POW2) return static_cast<int64_t>(v.gap[(v.code[k >> 4] >> ((k & 15u) * 2u)) & 3u]);
         else return static_cast<int64_t>(v.gap[k]);
-    };
-    // a hash value moves on by A; for other column counts its remainder modulo c moves along with
-    // it (A mod c further, p mod c back on a wrap past p), which saves a 64-bit remainder
-    auto advance = [&](uint64_t& y, [[maybe_unused]] uint32_t& rem, uint64_t A, [[maybe_unused]] uint32_t Ac) {
-        const uint64_t t = y + A;
-        y = (t & kP61) + (t >> 61);
-        if constexpr (!POW2) {
-            uint32_t u = rem + Ac;
-            u = u >= c ? u - c : u;
-            const uint32_t u2 = u + (c - v.pc);
-            rem = (t >> 61) == 0 ? u : (u2 >= c ? u2 - c : u2);
-        }
-    };
-    auto cell_of = [&](uint64_t y, [[maybe_unused]] uint32_t rem) -> uint32_t {
-        if constexpr (POW2) return (static_cast<uint32_t>(y) - 1u) & mask;
-        else return rem;
-    };
-    // the running sum of a coordinate in `cell` that started in `first`; >= NC: none (never with a
-    // list of cs_params_init)
-    auto sum_of = [&](uint32_t cell, uint32_t first) -> uint32_t {
-        if constexpr (POW2) {
-            return (cell - first) & mask;
-        } else {
-            const uint32_t t = cell >= first ? cell - first : cell + c - first;
-            if (t < v.omega) return t;
-            const uint32_t t2 = t + v.pc >= c ? t + v.pc - c : t + v.pc;
-            return t2 < v.omega ? v.omega + t2 : static_cast<uint32_t>(NC);
-        }
     };
     auto cell_of_sum = [&](uint32_t first, uint32_t q) -> uint32_t {
         if constexpr (POW2) {
@@ -1042,133 +1123,176 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
     };
     float* __restrict__ Sj = S + static_cast<size_t>(v.j) * c * cell_floats;
     const int64_t nwaves = (static_cast<int64_t>(v.gmax) + SPAN - 1) / SPAN;
+    const int64_t nsets = (nwaves + kOneWaves - 1) / kOneWaves;
     const uint32_t k0 = v.K * piece / v.pieces, k1 = v.K * (piece + 1) / v.pieces;
-    const int64_t s0 = offset_of_visit(k0, gap_of);
+    const uint32_t listed = fill_visit_steps<POW2, kOneWaves, kMaxSteps>(steps, k0, k1, v.a, v.as, col, omega, gap_of);
+    const uint32_t last4 = static_cast<uint32_t>(d) - kOneRun;
 
     // sets of neighbouring wavefronts go to one XCD, as in k_accumulate_visits
     for (int64_t vi = block; ; vi += v.blocks) {
-        if (visit_round(vi, v.blocks) >= nwaves) break;
-        const int64_t wv = visit_set(vi, v.blocks);
+        if (visit_round(vi, v.blocks) >= nsets) break;
+        const int64_t wv = visit_set(vi, v.blocks) * kOneWaves + wq;
         if (wv >= nwaves) continue;
-        const int64_t wave_res = wv * SPAN;
-        const int64_t my_res = wave_res + lane * kOneRun;
-        uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
-        uint32_t rb = POW2 ? 0u : bucket_of<false>(yb, col);
-        uint32_t first[kOneRun];
+        const uint32_t wave_res = static_cast<uint32_t>(wv * SPAN);
+        const uint32_t my_res = wave_res + lane * kOneRun;
+        uint32_t xb[kOneRun], xs[kOneRun];              // top bits of the hashes at my residues
         {
-            uint64_t tb = yb;
-            uint32_t tr = rb;
+            uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
+            uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res));
 #pragma unroll
             for (int m = 0; m < kOneRun; ++m) {
-                first[m] = cell_of(tb, tr);
-                advance(tb, tr, Aj, Ajc);
+                xb[m] = top_of(yb);
+                xs[m] = top_of(ys);
+                yb = hash_advance(yb, v.a);
+                ys = hash_advance(ys, v.as);
             }
         }
-        if (k0 > 0) {
-            yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res + s0));
-            if constexpr (!POW2) rb = bucket_of<false>(yb, col);
-        }
-        uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res + s0));
-
-        float acc[NC][kOneRun];
-#pragma unroll
-        for (int q = 0; q < NC; ++q)
-#pragma unroll
-            for (int m = 0; m < kOneRun; ++m) acc[q][m] = 0.0f;
-
-        // residues from wave_res on that take part in the visit at offset s and exist in the vector
-        auto room_of = [&](int64_t s, int64_t gap) -> int64_t {
-            const int64_t in_gap = gap - wave_res, in_vec = d - s - wave_res;
+        struct Step {                                   // a visit that was requested
+            vec4f x;
+            uint32_t tb, ts, s, w;                      // the step, as in steps[k]
+            uint32_t k;                                 // ~0u for none
+        };
+        VisitCursor cursor(steps, listed, wave_res, static_cast<uint32_t>(d));
+        auto request = [&](Step& st) {
+            st.k = cursor.next();
+            const uint4 e = steps[st.k == ~0u ? 0u : st.k];
+            st.tb = e.x;
+            st.ts = e.y;
+            st.s = __builtin_amdgcn_readfirstlane(e.z);
+            st.w = __builtin_amdgcn_readfirstlane(e.w);
+            uint32_t at = st.s + my_res;
+            at = at < last4 ? at : last4;
+            st.x = *(gvec4_ptr)((gfloat_ptr)g + at);
+        };
+        // of the residues from wave_res on, how many take part in the visit and exist in the vector (> 0)
+        auto room_of = [&](uint32_t s, uint32_t w) -> uint32_t {
+            const uint32_t in_gap = (w & kGapMask) - wave_res, in_vec = static_cast<uint32_t>(d) - s - wave_res;
             return in_gap < in_vec ? in_gap : in_vec;
         };
-        uint32_t kl = k0;                               // next visit to request, at offset sl
-        int64_t sl = s0;
-        auto request = [&](float (&buf)[kOneRun]) {
-            if (kl < k1) {
-                const int64_t gap = gap_of(kl), room = room_of(sl, gap);
-                const gfloat_ptr src = (gfloat_ptr)g + sl + my_res;
-                if (room >= SPAN) {
-                    load_floats<kOneRun>(src, buf);
-                } else if (room > 0) {
-                    const int64_t len = room - lane * kOneRun;
+        // x: four values read at min(s + my_res, last4)  ->  those of my residues, 0 for the missing ones
+        auto cut = [&](vec4f x, uint32_t s, uint32_t room) -> vec4f {
+            const int len = static_cast<int>(room) - lane * kOneRun;
+            const int over = static_cast<int>(s + my_res) - static_cast<int>(last4);
+            const float in[kOneRun] = {x.x, x.y, x.z, x.w};
+            float out[kOneRun];
 #pragma unroll
-                    for (int m = 0; m < kOneRun; ++m) {
-                        buf[m] = 0.0f;
-                        if (m < len) buf[m] = src[m];
-                    }
-                }
-                sl += gap;
-                ++kl;
+            for (int m = 0; m < kOneRun; ++m) {
+                float val = over <= 0 ? in[m] : 0.0f;
+#pragma unroll
+                for (int t = m + 1; t < kOneRun; ++t) val = over == t - m ? in[t] : val;
+                out[m] = m < len ? val : 0.0f;
+            }
+            return vec4f{out[0], out[1], out[2], out[3]};
+        };
+        // sums of the coordinates whose bucket hash did not wrap and of those whose did, for visits with
+        // A mod c = cur; their signs less that of the residue itself
+        float plain[kOneRun], wrapped[kOneRun];
+        uint32_t cur = 0;
+#pragma unroll
+        for (int m = 0; m < kOneRun; ++m) plain[m] = wrapped[m] = 0.0f;
+#pragma unroll
+        for (int q = 0; q < NC; ++q) *reinterpret_cast<vec4f*>(&sums[q][lane * kOneRun]) = vec4f{0.0f, 0.0f, 0.0f, 0.0f};
+        auto park = [&](uint32_t q, const float (&x)[kOneRun]) {
+            *reinterpret_cast<vec4f*>(&sums[q][lane * kOneRun]) = vec4f{x[0], x[1], x[2], x[3]};
+        };
+        auto next_sums = [&]() {                        // neighbouring cells share a sum (power-of-two c)
+            park(cur, plain);
+            if constexpr (!POW2) park(cur + NC / 2, wrapped);
+#pragma unroll
+            for (int m = 0; m < kOneRun; ++m) {
+                plain[m] = POW2 ? wrapped[m] : 0.0f;
+                wrapped[m] = 0.0f;
+            }
+            ++cur;
+        };
+        bool any_left = listed < k1 - k0;
+        if (lane <= kMaxSteps / 32) left[lane] = 0;
+        auto add_up = [&](Step& st) {
+            const uint32_t room = room_of(st.s, st.w);
+            vec4f x = st.x;
+            if (room < SPAN) x = cut(x, st.s, room);
+            while (cur < st.w >> 30) next_sums();
+            bool unsure = false;
+#pragma unroll
+            for (int m = 0; m < kOneRun; ++m) unsure |= xb[m] == st.tb || xs[m] == st.ts;
+            if (__builtin_amdgcn_ballot_w64(unsure) != 0) {
+                if (lane == 0) left[st.k >> 5] |= 1u << (st.k & 31u);
+                any_left = true;
+                x = vec4f{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+            const bool odd = (st.w >> 29 & 1u) != 0;
+            const float in[kOneRun] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int m = 0; m < kOneRun; ++m) {
+                const float val = (xs[m] > st.ts) != odd ? -in[m] : in[m];
+                const bool wraps = xb[m] > st.tb;
+                plain[m] += wraps ? 0.0f : val;
+                wrapped[m] += wraps ? val : 0.0f;
             }
         };
-        float buf[kOneAhead][kOneRun];
+        Step st[kOneAhead];
 #pragma unroll
-        for (int u = 0; u < kOneAhead; ++u) request(buf[u]);
-        int64_t s = s0;
-        auto add_up = [&](uint32_t k, const float (&x)[kOneRun]) {
-            const int64_t gap = gap_of(k);
-            if (room_of(s, gap) > 0) {
-                uint64_t tb = yb, ts = ys;
-                uint32_t tr = rb;
-#pragma unroll
-                for (int m = 0; m < kOneRun; ++m) {
-                    const uint32_t cell = cell_of(tb, tr), rel = sum_of(cell, first[m]);
-                    const float val = apply_sign(x[m], sign_flip_of(ts));
-                    uint32_t rest = __float_as_uint(val);
-#pragma unroll
-                    for (int q = 0; q + 1 < NC; ++q) {
-                        const uint32_t t = rel == static_cast<uint32_t>(q) ? __float_as_uint(val) : 0u;
-                        acc[q][m] += __uint_as_float(t);
-                        rest ^= t;
-                    }
-                    const bool stray = rel >= static_cast<uint32_t>(NC);
-                    acc[NC - 1][m] += stray ? 0.0f : __uint_as_float(rest);
-                    if (stray && val != 0.0f)
-                        atomic_add_noret(Sj + static_cast<size_t>(cell) * cell_floats, scale * val);
-                    if (m + 1 < kOneRun) {
-                        advance(tb, tr, Aj, Ajc);
-                        ts = hash_advance(ts, Asj);
-                    }
-                }
-            }
-            s += gap;
-            if constexpr (POW2) {
-                const uint32_t code = code_of(k);
-                advance(yb, rb, pick(code, v.A[0], v.A[1], v.A[2], v.A[3]), 0u);
-                ys = hash_advance(ys, pick(code, v.As[0], v.As[1], v.As[2], v.As[3]));
-            } else {
-                advance(yb, rb, adv_b[k], adv_c[k]);
-                ys = hash_advance(ys, adv_s[k]);
-            }
-        };
+        for (int u = 0; u < kOneAhead; ++u) request(st[u]);
         // (a buffer is refilled where it was read: moving a value that is still on its way would
         // wait for it)
-        for (uint32_t k = k0; k < k1; k += kOneAhead) {
+        for (bool more = true; more;) {
 #pragma unroll
             for (int u = 0; u < kOneAhead; ++u) {
-                if (k + u < k1) {
-                    add_up(k + u, buf[u]);
-                    request(buf[u]);
+                if (st[u].k == ~0u) {
+                    more = false;
+                    break;
+                }
+                add_up(st[u]);
+                request(st[u]);
+            }
+        }
+        park(cur, plain);
+        park(cur + (POW2 ? 1 : NC / 2), wrapped);
+        __builtin_amdgcn_wave_barrier();
+        // visits that the comparisons could not tell, or whose cells are not kept: hashed by the definition,
+        // straight into memory
+        if (any_left) {
+            for (uint32_t k = 0; k < k1 - k0; ++k) {
+                if (k < listed && (left[k >> 5] >> (k & 31u) & 1u) == 0) continue;
+                const uint32_t s = __builtin_amdgcn_readfirstlane(steps[k].z), w = __builtin_amdgcn_readfirstlane(steps[k].w);
+                if ((w & kGapMask) <= wave_res || s + wave_res >= static_cast<uint32_t>(d)) continue;
+                const uint32_t at = s + my_res;
+                const vec4f x = cut(*(gvec4_ptr)((gfloat_ptr)g + (at < last4 ? at : last4)), s, room_of(s, w));
+                const float in[kOneRun] = {x.x, x.y, x.z, x.w};
+                uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + at));
+                uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + at));
+#pragma unroll
+                for (int m = 0; m < kOneRun; ++m) {
+                    const float val = apply_sign(scale * in[m], sign_flip_of(ys));
+                    if (val != 0.0f)
+                        atomic_add_noret(Sj + static_cast<size_t>(bucket_of<POW2>(yb, col)) * cell_floats, val);
+                    yb = hash_advance(yb, v.a);
+                    ys = hash_advance(ys, v.as);
                 }
             }
         }
         // every sum goes to memory once, the NC sums of a residue by neighbouring lanes
+        {
+            uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
+            uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res));
 #pragma unroll
-        for (int m = 0; m < kOneRun; ++m) {
-            first_lds[lane * kOneRun + m] = first[m];
-#pragma unroll
-            for (int q = 0; q < NC; ++q) sum_lds[(lane * kOneRun + m) * NC + q] = acc[q][m];
+            for (int m = 0; m < kOneRun; ++m) {
+                first[lane * kOneRun + m] = bucket_of<POW2>(yb, col) | sign_flip_of(ys);
+                yb = hash_advance(yb, v.a);
+                ys = hash_advance(ys, v.as);
+            }
         }
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < kOneRun * NC; ++t) {
-            const uint32_t item = t * 64 + lane;
-            const float sum = sum_lds[item];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (uint32_t item = lane; item < SPAN * NC; item += 64) {
+            const uint32_t res = item / NC, q = item % NC;
+            const float sum = sums[q][res];
+            const uint32_t f = first[res];
             if (sum != 0.0f)
-                atomic_add_noret(Sj + static_cast<size_t>(cell_of_sum(first_lds[item / NC], item % NC)) * cell_floats,
-                                 scale * sum);
+                atomic_add_noret(Sj + static_cast<size_t>(cell_of_sum(f & 0x7fffffffu, q)) * cell_floats,
+                                 apply_sign(scale * sum, f & 0x80000000u));
         }
-        __syncthreads();
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -1265,6 +1389,7 @@ bool all_rows_listed(const cs_params* p, int64_t d) {
 // The lists serve the update of one vector: every row has one that covers d, and all of them
 // together send fewer requests than the lattice form (about one per 8 to 15 coordinates).
 bool one_applies(const cs_params* p, int64_t d) {
+    if (d > kStepsMaxD) return false;                  // (lists end at 2^28)
     double residues = 0.0;
     if (p->c_pow2) {
         if (!all_rows_listed(p, d)) return false;
@@ -1285,15 +1410,15 @@ int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const f
         for (int q = 0; q < n; ++q) requests[q] = 1.2 * static_cast<double>(rows.row[q].gmax);
         const double stream_ns = 4.0 * static_cast<double>(d) * n / kStreamBytesPerNs;
         choose_pieces(rows, n, requests, kVisitNsOne, stream_ns);
-        return dim3(visits_grid<1, kOneRun, 1>(rows, n));
+        return dim3(visits_grid<1, kOneRun, kOneWaves>(rows, n));
     };
     if (!p->c_pow2)
         return for_each_anyc_launch(p, p->r, [&](const uint32_t* js, int n, uint32_t omega) {
             VisitGapsRows rows{};
             for (int q = 0; q < n; ++q) fill_visit_gaps(p, js[q], rows.row[q]);
             const dim3 grid = shape(rows, n);
-            if (omega == 1) k_accumulate_one<2, VisitGapsRows><<<grid, 64, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale);
-            else k_accumulate_one<4, VisitGapsRows><<<grid, 64, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale);
+            if (omega == 1) k_accumulate_one<2, VisitGapsRows><<<grid, 64 * kOneWaves, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale);
+            else k_accumulate_one<4, VisitGapsRows><<<grid, 64 * kOneWaves, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale);
             return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
         });
     uint32_t order[CS_MAX_R], ncell = 2;
@@ -1309,9 +1434,9 @@ int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const f
         for (int q = 0; q < n; ++q) fill_visit_args(p, order[q0 + q], rows.row[q]);
         const dim3 grid = shape(rows, n);
         switch (ncell) {
-            case 2: k_accumulate_one<2, VisitRows><<<grid, 64, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
-            case 3: k_accumulate_one<3, VisitRows><<<grid, 64, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
-            case 4: k_accumulate_one<4, VisitRows><<<grid, 64, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
+            case 2: k_accumulate_one<2, VisitRows><<<grid, 64 * kOneWaves, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
+            case 3: k_accumulate_one<3, VisitRows><<<grid, 64 * kOneWaves, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
+            case 4: k_accumulate_one<4, VisitRows><<<grid, 64 * kOneWaves, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
             default: return CS_EINVAL;
         }
         if (hipGetLastError() != hipSuccess) return CS_EHIP;
