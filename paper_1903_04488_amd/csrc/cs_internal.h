@@ -57,6 +57,22 @@ int count_accumulate_walk_launches(const cs_params* p, int W, int64_t d);
 bool one_applies(const cs_params* p, int64_t d);
 int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const float* g, int64_t d,
                           int64_t i0, float scale, hipStream_t stream);
+// The update along visit lists into a workspace of running sums, one group of workers at a time, and what lies where
+// in it: row j's sums [pieces][piece_floats], piece_floats = residues (rounded up to whole wavefronts) x running sums x
+// lanes of a walker.
+struct SumsRow {
+    uint64_t at, residues, piece_floats;
+    uint32_t pieces, ncell, log_run;
+};
+struct SumsPlan {
+    uint64_t floats;             // of one group
+    SumsRow row[CS_MAX_R];
+};
+bool sums_apply(const cs_params* p, int64_t d);
+int sums_lanes(int W);           // lanes of a walker (1, 2, 4, 8) with W workers, the same in all groups of 8
+// nw <= lanes: workers of the group; g_w null: the plan only
+int launch_accumulate_sums(const cs_params* p, float* sums, int lanes, int nw, const float* const* g_w, int64_t d,
+                           float scale, SumsPlan& plan, hipStream_t stream);
 // the same along visit lists for column counts that are not a power of two
 bool anyc_visits_apply(const cs_params* p, int64_t d);
 bool anyc_visits_serve_query(const cs_params* p, int64_t d);

@@ -47,7 +47,10 @@ namespace cs {
 namespace {
 
 constexpr int kGroup = CS_BUNDLE_GROUP;  // workers per bundle group
-constexpr int kWavesPerGroupOf8 = 2;      // wavefronts per workgroup of the 8-worker kernels
+constexpr int kWalkWaves = 2;             // wavefronts per workgroup of the 8-worker stride walk
+// ... and of the 8-worker list kernel: they share a table of visits.  (2: d = 6.5 M, 5 x 2^17 196 us for 184, d = 11 M
+// 313 for 304, d = 25 M, 7 x 2^19 1098 for 1075, d = 10^8 the same.)
+constexpr int kWavesPerGroupOf8 = 4;
 
 // Vectors are addressed as global memory explicitly: the pointers pass through an LDS table,
 // and a generic ("flat") load would count against the LDS counter as well and force the
@@ -279,7 +282,9 @@ struct VisitArgs {
     uint32_t blocks;             // workgroups of one piece
     uint64_t gmax;
     uint64_t a, b, as, bs;       // hash constants of row j
-    uint64_t gap[4], A[4], As[4];
+    uint64_t at;                 // floats of the workspace before those of this row's sums
+    uint64_t gap[4];
+    uint32_t ncell;              // running sums of a coordinate
     uint32_t code[CS_MAX_VISITS / 16];
 };
 // The rows of a sketch are updated by one launch: their serial chains of visits overlap, and there
@@ -342,6 +347,7 @@ struct VisitWorkers {
     uint32_t c;
     int32_t nw;                  // workers in this group (<= kGroup)
     float scale;
+    float* sums;                 // PARTIAL: where the running sums go
     int32_t fold;                // != 0: the workers' sums of a cell are added up across the lanes
                                  // of a walker and leave as one 4-byte request into a single table
 };
@@ -371,19 +377,6 @@ __device__ __forceinline__ void load_floats(gfloat_ptr src, float (&out)[N]) {
     }
 }
 
-// Offset of visit k: the sum of the gaps before it, taken by the lanes of a wavefront together.
-template <typename GAP>
-__device__ __forceinline__ int64_t offset_of_visit(uint32_t k, GAP gap_of) {
-    if (k == 0) return 0;
-    int64_t mine = 0;
-    for (uint32_t t = threadIdx.x & 63; t < k; t += 64) mine += gap_of(t);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(mine));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(static_cast<uint64_t>(mine) >> 32));
-    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
 // the row that this workgroup works for
 template <typename LIST>
 __device__ __forceinline__ unsigned row_of_block(const LIST& rows) {
@@ -394,10 +387,159 @@ __device__ __forceinline__ unsigned row_of_block(const LIST& rows) {
     return q;
 }
 
-// LIST = VisitRows (power-of-two column counts: three gaps and 2-bit codes, the NC cells are
-// neighbours) or VisitGapsRows (any column count: gaps one by one, NC = 2 omega cells of which
+// ---------------------------------------------------------------------------------------
+// What a visit does to the hashes of a coordinate, told by two comparisons.
+//
+// Visit k is at offset s_k, and with A = (a s_k) mod p the bucket hash of i + s_k is x + A, less p if
+// x >= p - A, where x is that of i.  A is the same for every coordinate, so the bucket moves on by A mod c,
+// and by p mod c back in the second case (one cell further if c is a power of two, for p = -1 mod c):
+// one of two cells, and which one is the comparison of x with p - 1 - A.  The sign hash likewise: its
+// parity is that of x' plus that of A', inverted after a wrap.  So a lane keeps the top 32 bits of x and x' of
+// its coordinates and compares them with the top 32 bits of the visit's two thresholds (bits 29..60);
+// where they are equal the lower bits would decide, and the visit is hashed by the definition
+// instead (once in 2^31 coordinates and visits).  Against carrying two 61-bit states per coordinate from visit
+// to visit this takes 10 vector operations per coordinate and visit for about 25.
+//
+// Only the two sums of one value of A mod c are in registers at a time; the others wait in LDS.
+// ---------------------------------------------------------------------------------------
+constexpr int kTopShift = 29;                          // 61-bit hash value -> its top 32 bits
+__device__ __forceinline__ uint32_t top_of(uint64_t y) { return static_cast<uint32_t>((y - 1) >> kTopShift); }
+// x wraps on an advance by A when it is above p - 1 - A
+__device__ __forceinline__ uint32_t threshold_of(uint64_t A) { return static_cast<uint32_t>((kP61 - 1 - A) >> kTopShift); }
+
+// A visit.  x: threshold of the bucket hash, y: of the sign hash, z: offset, w: bits 0..28 its gap (residues
+// that take part), bit 29 the parity of A', bits 30-31 A mod c (the running sum of a coordinate that does not
+// wrap), or 3 where that is none of the sums that are kept.
+constexpr uint32_t kGapMask = (1u << 29) - 1u;
+constexpr int64_t kStepsMaxD = 1ll << 29;              // offsets and gaps of longer vectors do not fit
+
+// Offsets and gaps of the visits of a list, by the lanes of a wavefront together.  A power-of-two list has four gaps
+// and a 2-bit code per visit: the offset of a visit is how often each code comes before it, counted word by word
+// and summed up over the words once.  Other lists have their gaps one by one.
+struct VisitPlaces {
+    uint32_t codes, before;      // my word of the list; numbers of the codes 1, 2, 3 in the words before it, 10 bits each
+    __device__ __forceinline__ static uint32_t numbers(uint32_t w) {
+        const uint32_t lo = w & 0x55555555u, hi = w >> 1 & 0x55555555u;
+        return static_cast<uint32_t>(__builtin_popcount(lo & ~hi)) | static_cast<uint32_t>(__builtin_popcount(hi & ~lo)) << 10 |
+               static_cast<uint32_t>(__builtin_popcount(lo & hi)) << 20;
+    }
+    __device__ __forceinline__ void init(const VisitArgs& v) {
+        static_assert(CS_MAX_VISITS == 512, "32 words, numbers below 2^10");
+        const uint32_t lane = threadIdx.x & 63;
+        codes = lane < CS_MAX_VISITS / 16 ? v.code[lane] : 0u;
+        uint32_t upto = numbers(codes);
+#pragma unroll
+        for (uint32_t off = 1; off < CS_MAX_VISITS / 16; off <<= 1) {
+            const uint32_t other = __shfl_up(upto, off);
+            upto += lane >= off ? other : 0u;
+        }
+        before = upto - numbers(codes);
+    }
+    // offset (at most kStepsMaxD) and gap (at most kGapMask) of visit k, which may differ between the lanes
+    __device__ __forceinline__ void at(const VisitArgs& v, uint32_t k, uint32_t& s, uint32_t& gap) const {
+        const uint32_t w = __shfl(codes, k >> 4), bits = 2u * (k & 15u);
+        const uint32_t n = __shfl(before, k >> 4) + numbers(w & ((1u << bits) - 1u));
+        const uint32_t n1 = n & 1023u, n2 = n >> 10 & 1023u, n3 = n >> 20;
+        uint64_t x = v.gap[0] * (k - n1 - n2 - n3) + v.gap[1] * n1 + v.gap[2] * n2 + v.gap[3] * n3;
+        s = static_cast<uint32_t>(x < kStepsMaxD ? x : kStepsMaxD);
+        const uint32_t code = w >> bits & 3u;
+        x = code == 0u ? v.gap[0] : code == 1u ? v.gap[1] : code == 2u ? v.gap[2] : v.gap[3];
+        gap = static_cast<uint32_t>(x < kGapMask ? x : kGapMask);
+    }
+    __device__ __forceinline__ void init(const VisitGaps&) {}
+    // (the lanes ask for neighbouring visits, the first lane for the first)
+    __device__ __forceinline__ void at(const VisitGaps& v, uint32_t k, uint32_t& s, uint32_t& gap) const {
+        const uint32_t lane = threadIdx.x & 63, base = __builtin_amdgcn_readfirstlane(k);
+        auto gap_of = [&](uint32_t t) { return v.gap[t] < kGapMask ? v.gap[t] : kGapMask; };
+        gap = k < v.K ? gap_of(k) : 0u;
+        uint64_t sum = 0;                              // of the gaps before the first lane's visit
+        for (uint32_t t = lane; t < base; t += 64) sum += gap_of(t);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+        uint64_t upto = gap;                           // of the gaps from there up to mine
+#pragma unroll
+        for (uint32_t off = 1; off < 64; off <<= 1) {
+            const uint64_t other = __shfl_up(upto, off);
+            upto += lane >= off ? other : 0u;
+        }
+        sum += upto - gap;
+        s = static_cast<uint32_t>(sum < kStepsMaxD ? sum : kStepsMaxD);
+    }
+};
+
+// The visits k0 .. k1 - 1, by all wavefronts of the workgroup; returns how many of them are not `3`.  within: A mod c
+// must be below it.
+template <bool POW2, int NWAVE, typename ARGS>
+__device__ __forceinline__ uint32_t fill_visit_steps(uint4* steps, const VisitPlaces& places, const ARGS& v, uint32_t k0,
+                                                     uint32_t k1, const Columns& col, uint32_t within) {
+    __shared__ uint32_t count[CS_MAX_VISITS / 64];
+    const uint32_t lane = threadIdx.x & 63, wq = threadIdx.x >> 6;
+    const uint32_t chunks = (k1 - k0 + 63) / 64;
+    for (uint32_t chunk = wq; chunk < chunks; chunk += NWAVE) {
+        const uint32_t k = k0 + chunk * 64 + lane;
+        uint32_t s, gap;
+        places.at(v, k, s, gap);
+        const uint64_t A = mulmod_p(v.a, s), As = mulmod_p(v.as, s);
+        const uint32_t cell = bucket_of<POW2>(A + 1, col);
+        const uint32_t q = cell < within ? cell : 3u;
+        const uint32_t listed = __builtin_popcountll(__builtin_amdgcn_ballot_w64(k < k1 && q < 3u));
+        if (lane == 0) count[chunk] = listed;
+        if (k < k1)
+            steps[k - k0] = make_uint4(threshold_of(A), threshold_of(As), s, gap | static_cast<uint32_t>(As & 1u) << 29 | q << 30);
+    }
+    __syncthreads();
+    uint32_t listed = 0;
+    for (uint32_t ch = 0; ch < chunks; ++ch) listed += count[ch];
+    return __builtin_amdgcn_readfirstlane(listed);
+}
+
+// The visits of steps[0 .. n) that are not `3` and that residues from first_res on take part in, one after the other: a list with one
+// short and one long gap leaves most walkers with few of its visits (K = 277, gaps 243 885 and 1 495 226:
+// 66 for five residues in six), and looking at 64 visits at once finds the next without stepping through the others.
+struct VisitCursor {
+    const uint4* steps;
+    uint64_t todo;                                      // visits base .. base + 63 that are left
+    uint32_t base, n;
+    uint32_t first_res, d;
+    __device__ __forceinline__ void look() {
+        const uint32_t k = base + (threadIdx.x & 63);
+        const uint4 e = steps[k < n ? k : 0];
+        todo = __builtin_amdgcn_ballot_w64(k < n && e.w >> 30 < 3u && (e.w & kGapMask) > first_res && e.z + first_res < d);
+    }
+    __device__ __forceinline__ VisitCursor(const uint4* steps_, uint32_t n_, uint32_t first_res_, uint32_t d_)
+        : steps(steps_), base(0), n(n_), first_res(first_res_), d(d_) { look(); }
+    // the next visit, or ~0u
+    __device__ __forceinline__ uint32_t next() {
+        while (todo == 0) {
+            if (base + 64 >= n) return ~0u;
+            base += 64;
+            look();
+        }
+        const uint32_t k = base + static_cast<uint32_t>(__builtin_ctzll(todo));
+        todo &= todo - 1;
+        return k;
+    }
+};
+
+// LIST = VisitRows (power-of-two column counts: three gaps and 2-bit codes, the ncell cells of a
+// coordinate are neighbours) or VisitGapsRows (any column count: gaps one by one, ncell = 2 omega cells of which
 // the second half lies p mod c cells back).
-template <int WL, int RUN, int NWAVE, int NC, typename LIST>
+//
+// One lane of a walker tells cell and sign of RUN / WL of the walker's coordinates, and the comparisons of a
+// wavefront are two masks per coordinate of a lane, from which every lane takes the bits of its walker.
+// The NC >= ncell sums of a coordinate stay in registers; the two that a visit adds to are `plain` and `wrapped`, the
+// others are moved there when the visits come to another value of A mod c, so that the additions are written once.
+// All of a coordinate leave together at the end: sent one by one as they are complete, its cells, which are
+// neighbours, were fetched and written back by the memory-side cache once each (d = 10^8, 8 workers, 5 x 2^20: 3455 us).
+// Measured against records of sign and masks in LDS, two 61-bit states per pair of coordinates, and a turn for every
+// visit of the list (us, update alone): d = 6.5 M, 8 workers, 5 x 2^17 206 -> 184; 6.5 M, 5 x 180 000 268 -> 246; 11 M,
+// 5 x 2^18 317 -> 304; 3 M, 2 workers, 3 x 2^15 48 -> 42; 90 M, 4 workers, 15 x 180 000 4177 -> 4074; 10^8, 8 workers,
+// 5 x 2^20 3260 -> 3156; 25 M, 7 x 2^19 1068 -> 1075; 40 M, 5 x 2^19 1116 -> 1143 (lists whose walkers nearly all take part
+// in nearly all visits have nothing to skip).  Bound: reads at 5.7 to 6.2 TB/s; without its requests the launch at
+// 10^8 takes 2690 us, which is 18.3 GB at 6.8 TB/s (16.0 GB and the cache lines that two wavefronts share).  Sums waiting in
+// LDS instead of registers: 10^8 3130, 25 M 1131; four wavefronts in step by a barrier per visit: 11 M 293, 10^8 3269.
+// PARTIAL (power-of-two columns): the sums go to a workspace instead of being added to the table (cs_index.hip).
+template <int WL, int RUN, int NWAVE, int NC, bool PARTIAL, typename LIST>
 __global__ void __launch_bounds__(64 * NWAVE)
 k_accumulate_visits(LIST rows, VisitWorkers a) {
     constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
@@ -406,31 +548,25 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
     const uint32_t piece = (blockIdx.x - rows.first[row]) / v.blocks;
     const uint32_t block = (blockIdx.x - rows.first[row]) % v.blocks;
     constexpr int WPW = 64 / WL;                       // walkers per wavefront
-    constexpr int PPL = RUN / WL;                      // hash values each lane computes
+    constexpr int PPL = RUN / WL;                      // coordinates whose hashes a lane looks at
     constexpr int SPAN = WPW * RUN;                    // residues a wavefront owns
     constexpr int kStride = RUN + 1;
-    constexpr int kRec = NC == 2 ? 2 : 4;              // words of a coordinate's record
-    // records of one walker, padded by one record: the 8 lanes of a walker read the same record
-    // (a broadcast), the walkers of a wavefront different ones, which without the pad would
-    // all start in the same LDS bank
-    constexpr int kRecWalker = (RUN + 1) * kRec;
     static_assert(WL <= 8 && WL * PPL == RUN, "every coordinate of a walker gets a hash lane");
-    static_assert(NC >= 2 && NC <= 4, "two to four running sums");
-    // Per wavefront: the value tile (one padded row per lane), one record per coordinate of
-    // every walker (sign word, then one all-ones / all-zeros word per cell but the last,
-    // telling which running sum the coordinate belongs to in this visit), the walkers' first
-    // cells, and the (bucket | sign) words of the stride walk, for the fallback.
+    // Two neighbouring cells of a bundle are one aligned 64-byte block when the lower one is
+    // even, and leave as one request then: on average ncell / 2 + 1/2 requests per residue instead of ncell.  For
+    // that the sums go through LDS.  Only short vectors (RUN = 8) gain, whose time is mostly these
+    // requests; long ones stream meanwhile.
+    constexpr bool kPairs = !PARTIAL && POW2 && RUN == 8;
+    // Per wavefront: the value tile (one padded row per lane), the walkers' first cells and signs
     __shared__ float tile_lds_all[NWAVE][64 * kStride];
-    __shared__ __attribute__((aligned(16))) uint32_t rec_lds_all[NWAVE][WPW * kRecWalker];
     __shared__ uint32_t first_lds_all[NWAVE][SPAN];
-    __shared__ uint32_t raw_lds_all[NWAVE][SPAN];
+    // the visits of my piece, behind them the sums that wait, [][RUN][64] per wavefront
+    extern __shared__ uint4 steps[];
 
     const int lane = threadIdx.x & 63;
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wavefront-uniform
     float* tile_lds = tile_lds_all[wq];
-    uint32_t* rec_lds = rec_lds_all[wq];
     uint32_t* first_lds = first_lds_all[wq];
-    uint32_t* raw_lds = raw_lds_all[wq];
     const int h = lane / WL, wl = lane % WL;
     const int nw = a.nw;
     const bool live = wl < nw;                          // my worker exists
@@ -439,39 +575,31 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
     const int64_t nwaves = (chunks + WPW - 1) / WPW;
     const uint32_t mask = a.c - 1u;
     const Columns col = columns_of<POW2>(a.c);
-    const int64_t d = a.d;
+    const uint32_t d = static_cast<uint32_t>(a.d);
     const bool fold = a.fold != 0;
     const size_t cell_floats = fold ? 1 : kGroup;      // floats from one cell to the next
     float* __restrict__ Tcol = fold ? a.T + static_cast<size_t>(v.j) * a.c
                                     : a.T + static_cast<size_t>(v.j) * a.c * kGroup + wl;
-    // which running sum a coordinate now in `cell` belongs to, given the cell it started in;
-    // >= NC: none of them (never with a list of cs_params_init)
-    auto sum_of = [&](uint32_t cell, uint32_t first) -> uint32_t {
-        if constexpr (POW2) {
-            return (cell - first) & mask;
-        } else {
-            const uint32_t c = a.c, omega = v.omega;
-            const uint32_t t = cell >= first ? cell - first : cell + c - first;    // (cell - first) mod c
-            if (t < omega) return t;
-            const uint32_t t2 = t + v.pc >= c ? t + v.pc - c : t + v.pc;            // after a wrap past p
-            return t2 < omega ? omega + t2 : static_cast<uint32_t>(NC);
-        }
-    };
+    uint32_t ncell, omega;                             // running sums, and the values of A mod c that they cover
+    if constexpr (POW2) {
+        ncell = v.ncell;
+        omega = ncell - 1;
+    } else {
+        omega = v.omega;
+        ncell = 2 * omega;
+    }
     // the cell of running sum q of a coordinate that started in cell `first`
-    auto cell_of_sum = [&](uint32_t first, int q) -> uint32_t {
+    auto cell_of_sum = [&](uint32_t first, uint32_t q) -> uint32_t {
         if constexpr (POW2) {
-            return (first + static_cast<uint32_t>(q)) & mask;
+            return (first + q) & mask;
         } else {
-            const uint32_t c = a.c, omega = v.omega;
-            uint32_t x = static_cast<uint32_t>(q) < omega ? first + q : first + (q - omega) + (c - v.pc);
+            const uint32_t c = a.c;
+            const uint32_t x = q < omega ? first + q : first + (q - omega) + (c - v.pc);
             return x >= c ? x - c : x;
         }
     };
     const int m0 = wl * PPL;                           // hash role: coordinates m0 .. m0 + PPL - 1
     float* my_row = tile_lds + lane * kStride;         // consumer role: my walker's run of my worker
-    const uint32_t* my_rec = rec_lds + h * kRecWalker;
-    uint32_t* rec_dst = rec_lds + h * kRecWalker + m0 * kRec;
-    const uint64_t Aj = v.a, Asj = v.as;
     // loader role: floats lspan .. lspan + kPer - 1 of the wavefront's span of one worker at a time;
     // they belong to walker lspan / RUN and go to that walker's row of the worker.  Requests are 16
     // bytes or more per lane: where a worker's span is shorter than 64 of them, kShare workers
@@ -486,281 +614,265 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
     const int lspan = (lane % kLanesPerWorker) * kPer;
     float* tile_dst = tile_lds + ((lspan / RUN) * WL + part) * kStride + lspan % RUN;
     constexpr int kRowStep = kShare * kStride;         // tile rows between my loads
-    // gap and hash advances of visit k.  Power-of-two lists: three gaps and the cut last one
-    // live in scalar registers and a 2-bit code per visit picks among them; other lists are
-    // read visit by visit from the kernel arguments.
-    auto pick = [](uint32_t code, uint64_t x0, uint64_t x1, uint64_t x2, uint64_t x3) {
-        return code == 0u ? x0 : code == 1u ? x1 : code == 2u ? x2 : x3;
-    };
-    auto code_of = [&](uint32_t k) -> uint32_t {
-        if constexpr (POW2) return (v.code[k >> 4] >> ((k & 15u) * 2u)) & 3u;
-        else return k;
-    };
-    auto gap_of = [&](uint32_t code) -> int64_t {
-        if constexpr (POW2) return static_cast<int64_t>(pick(code, v.gap[0], v.gap[1], v.gap[2], v.gap[3]));
-        else return static_cast<int64_t>(v.gap[code]);
-    };
-    // hash advances of the visits of an any-c list: once per workgroup into LDS
-    __shared__ uint64_t adv_b[POW2 ? 1 : CS_ANYC_MAX_VISITS], adv_s[POW2 ? 1 : CS_ANYC_MAX_VISITS];
-    if constexpr (!POW2) {
-        for (uint32_t k = threadIdx.x; k < v.K; k += 64 * NWAVE) {
-            adv_b[k] = mulmod_p(v.a, v.gap[k]);
-            adv_s[k] = mulmod_p(v.as, v.gap[k]);
-        }
-        __syncthreads();
+    gfloat_ptr src_of[kLoads];                         // where load instruction w of this lane reads, at residue 0
+#pragma unroll
+    for (int w = 0; w < kLoads; ++w) {
+        const int from = w * kShare + part;
+        src_of[w] = (gfloat_ptr)a.g[from < nw ? from : 0] + lspan;
     }
-    auto A_of = [&](uint32_t code) -> uint64_t {
-        if constexpr (POW2) return pick(code, v.A[0], v.A[1], v.A[2], v.A[3]);
-        else return adv_b[code];
-    };
-    auto As_of = [&](uint32_t code) -> uint64_t {
-        if constexpr (POW2) return pick(code, v.As[0], v.As[1], v.As[2], v.As[3]);
-        else return adv_s[code];
-    };
-
     // Walkers with small residues take part in every visit, those with large ones only in
     // the visits with the largest gap, so the sets of walkers are dealt to the XCDs in short
     // blocks rather than as eight long ranges: every XCD gets the same mix.
     const int64_t ngroups = (nwaves + NWAVE - 1) / NWAVE;
-    // my piece of the chain of visits: k0 .. k1 - 1, the first of them at offset s0
+    // my piece of the chain of visits: k0 .. k1 - 1
     const uint32_t k0 = v.K * piece / v.pieces, k1 = v.K * (piece + 1) / v.pieces;
-    const int64_t s0 = offset_of_visit(k0, [&](uint32_t k) { return gap_of(code_of(k)); });
+    VisitPlaces places;
+    places.init(v);
+    const uint32_t listed = fill_visit_steps<POW2, NWAVE>(steps, places, v, k0, k1, col, omega);
     for (int64_t vi = block; ; vi += v.blocks) {
         if (visit_round(vi, v.blocks) >= ngroups) break;
         const int64_t set = visit_set(vi, v.blocks);
         const int64_t wv = set * NWAVE + wq;
         if (set >= ngroups || wv >= nwaves) continue;
-        const int64_t first_res = wv * SPAN;           // first residue of this wavefront's walkers
-        uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(a.i0 + first_res + h * RUN + m0));
-        uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(a.i0 + first_res + h * RUN + m0));
+        const uint32_t first_res = static_cast<uint32_t>(wv * SPAN);   // first residue of this wavefront's walkers
+        const uint32_t* first = first_lds + h * RUN;
 
-        // the cells my coordinates start in (visit 0, whether or not I take part in it)
-        uint32_t first_cell[PPL];
-        {
-            uint64_t tb = yb;
-#pragma unroll
-            for (int q = 0; q < PPL; ++q) {
-                first_cell[q] = bucket_of<POW2>(tb, col);
-                first_lds[h * RUN + m0 + q] = first_cell[q];
-                if (q + 1 < PPL) tb = hash_advance(tb, Aj);
-            }
-        }
-        if (k0 > 0) {
-            yb = hash_state(v.a, v.b, static_cast<uint64_t>(a.i0 + first_res + h * RUN + m0 + s0));
-            ys = hash_state(v.as, v.bs, static_cast<uint64_t>(a.i0 + first_res + h * RUN + m0 + s0));
-        }
-
-        float acc[NC][RUN];
-#pragma unroll
-        for (int q = 0; q < NC; ++q)
-#pragma unroll
-            for (int m = 0; m < RUN; ++m) acc[q][m] = 0.0f;
-
-        // Offsets are counted from the piece's first visit, so that s begins at 0: beginning at s0 the
-        // compiler keeps 8 registers more, which with 3 running sums and RUN = 16 is a wavefront per
-        // SIMD less (3 for 4; d = 11 M, W = 8: 13 us more of 336).
-        // Requests of the visit at offset s0 + s.  `room` = residues from first_res on that belong
+        // Requests of a visit.  `room` = residues from first_res on that belong
         // to the visit and exist; when the whole span does, every piece is whole and needs no
         // check (one wavefront-uniform base per worker plus a fixed lane offset).  Otherwise
         // pieces are cut where the visit or the vector ends, and missing values count as 0.
         float pre[kLoads][kPer];
-        // the vector that load instruction `w` of this lane reads
-        auto vector_of = [&](int w) -> gfloat_ptr {
-            const float* x = a.g[w * kShare < nw ? w * kShare : 0];
-#pragma unroll
-            for (int u = 1; u < kShare; ++u) {
-                const float* y = a.g[w * kShare + u < nw ? w * kShare + u : 0];
-                x = part == u ? y : x;
-            }
-            return (gfloat_ptr)x;
-        };
-        auto load_visit = [&](int64_t s, int64_t room) {
+        auto load_visit = [&](uint32_t s, uint32_t w) {
+            const uint32_t in_gap = (w & kGapMask) - first_res, in_vec = d - s - first_res;
+            const uint32_t room = in_gap < in_vec ? in_gap : in_vec;
             if (room >= SPAN) {
 #pragma unroll
-                for (int w = 0; w < kLoads; ++w)
-                    load_floats<kPer>(vector_of(w) + (first_res + s0 + s) + lspan, pre[w]);
+                for (int l = 0; l < kLoads; ++l) load_floats<kPer>(src_of[l] + (first_res + s), pre[l]);
             } else {
                 const int len = static_cast<int>(room) - lspan;    // of my piece: >= kPer whole, <= 0 none
 #pragma unroll
-                for (int w = 0; w < kLoads; ++w) {
-                    const gfloat_ptr src = vector_of(w) + (first_res + s0 + s) + lspan;
+                for (int l = 0; l < kLoads; ++l) {
+                    const gfloat_ptr src = src_of[l] + (first_res + s);
 #pragma unroll
-                    for (int t = 0; t < kPer; ++t) pre[w][t] = 0.0f;
+                    for (int t = 0; t < kPer; ++t) pre[l][t] = 0.0f;
                     if (len >= kPer) {
-                        load_floats<kPer>(src, pre[w]);
+                        load_floats<kPer>(src, pre[l]);
                     } else {
 #pragma unroll
                         for (int t = 0; t < kPer; ++t)
-                            if (t < len) pre[w][t] = src[t];
+                            if (t < len) pre[l][t] = src[t];
                     }
                 }
             }
         };
-        // room of the visit with gap `gap` at offset s0 + s; > 0 means this wavefront takes part
-        auto room_of = [&](int64_t s, int64_t gap) {
-            const int64_t in_gap = gap - first_res, in_vec = d - s0 - s - first_res;
-            return in_gap < in_vec ? in_gap : in_vec;
+        uint32_t xb[PPL], xs[PPL];                     // top bits of the hashes at my walker's residues
+        {
+            uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(a.i0 + first_res + h * RUN + m0));
+            uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(a.i0 + first_res + h * RUN + m0));
+#pragma unroll
+            for (int q = 0; q < PPL; ++q) {
+                xb[q] = top_of(yb);
+                xs[q] = top_of(ys);
+                first_lds[h * RUN + m0 + q] = bucket_of<POW2>(yb, col) | sign_flip_of(ys);
+                if (q + 1 < PPL) {
+                    yb = hash_advance(yb, v.a);
+                    ys = hash_advance(ys, v.as);
+                }
+            }
+        }
+        // sums of the coordinates whose bucket hash did not wrap and of those whose did, for visits with
+        // A mod c = cur; their signs less that of the residue itself
+        float plain[RUN], wrapped[RUN];
+        uint32_t cur = 0;
+#pragma unroll
+        for (int m = 0; m < RUN; ++m) plain[m] = wrapped[m] = 0.0f;
+        // The other sums.  Power-of-two c, where neighbouring cells share a sum: sum q is in other[q mod 2] (two on is
+        // the one that comes for it; other[0] if there are three), else those of the other value of A mod c.
+        float other[NC > 2 ? NC - 2 : 1][RUN];
+#pragma unroll
+        for (int t = 0; t < NC - 2; ++t)
+#pragma unroll
+            for (int m = 0; m < RUN; ++m) other[t][m] = 0.0f;
+        auto move_to = [&](uint32_t q) {
+            if (cur == q) return;
+            if constexpr (!POW2) {
+                if constexpr (NC > 2) {
+#pragma unroll
+                    for (int m = 0; m < RUN; ++m) {
+                        const float p = plain[m], w = wrapped[m];
+                        plain[m] = other[0][m];
+                        wrapped[m] = other[1][m];
+                        other[0][m] = p;
+                        other[1][m] = w;
+                    }
+                }
+                cur = q;
+            } else if constexpr (NC > 2) {
+                while (cur != q) {
+                    const bool up = cur < q, second = NC > 3 && (up ? cur == 1u : cur == 2u);    // of other[]
+#pragma unroll
+                    for (int m = 0; m < RUN; ++m) {
+                        const float o0 = other[0][m], o1 = other[NC - 3][m], lower = plain[m], upper = wrapped[m];
+                        const float in = second ? o1 : o0, out = up ? lower : upper;
+                        other[NC - 3][m] = second ? out : o1;
+                        other[0][m] = second ? o0 : out;
+                        plain[m] = up ? upper : in;
+                        wrapped[m] = up ? in : lower;
+                    }
+                    cur = up ? cur + 1 : cur - 1;
+                }
+            }
         };
-
-        int64_t s = 0;                                 // visit k is at offset s0 + s
-        uint32_t code = code_of(k0);
-        bool active = room_of(s, gap_of(code)) > 0;
-        if (active) load_visit(s, room_of(s, gap_of(code)));
-        for (uint32_t k = k0; k < k1; ++k) {
-            // visit k: its values are on their way (requested one turn earlier)
-            const bool was_active = active;
-            if (was_active) {
+        VisitCursor cursor(steps, k1 - k0, first_res, d);
+        uint32_t k = cursor.next();                    // the visit whose values are on their way
+        uint4 e = steps[k == ~0u ? 0u : k];
+        if (k != ~0u) load_visit(__builtin_amdgcn_readfirstlane(e.z), __builtin_amdgcn_readfirstlane(e.w));
+        uint32_t k_next = cursor.next();
+        uint4 e_next = steps[k_next == ~0u ? 0u : k_next];
+        while (k != ~0u) {
+            const uint32_t w = __builtin_amdgcn_readfirstlane(e.w);
+            move_to(w >> 30);
 #pragma unroll
-                for (int w = 0; w < kLoads; ++w)
+            for (int l = 0; l < kLoads; ++l)
 #pragma unroll
-                    for (int t = 0; t < kPer; ++t) tile_dst[w * kRowStep + t] = pre[w][t];
+                for (int t = 0; t < kPer; ++t) tile_dst[l * kRowStep + t] = pre[l][t];
+            // request the next visit as soon as the registers of this one are free, to fly while
+            // this one is looked at and added up
+            if (k_next != ~0u) load_visit(__builtin_amdgcn_readfirstlane(e_next.z), __builtin_amdgcn_readfirstlane(e_next.w));
+            uint64_t flips[PPL], wraps[PPL];           // lane h WL + l: coordinate l PPL + q of walker h
+            bool unsure = false;
+#pragma unroll
+            for (int q = 0; q < PPL; ++q) {
+                flips[q] = __builtin_amdgcn_ballot_w64(xs[q] > e.y);
+                wraps[q] = __builtin_amdgcn_ballot_w64(xb[q] > e.x);
+                unsure |= xs[q] == e.y || xb[q] == e.x;
             }
-            // request visit k + 1 as soon as the registers of visit k are free, to fly while
-            // visit k is hashed and added up
-            const uint32_t code_k = code;
-            s += gap_of(code_k);
-            active = false;
-            if (k + 1 < k1) {
-                code = code_of(k + 1);
-                const int64_t room = room_of(s, gap_of(code));
-                active = room > 0;
-                if (active) load_visit(s, room);
-            }
-            bool bad = false;
-            if (was_active) {
-                uint64_t tb = yb, ts = ys;
+            if (__builtin_amdgcn_ballot_w64(unsure) != 0) {
+                // the lower bits decide: whole hash values against whole thresholds
+                const uint64_t A = mulmod_p(v.a, e.z), As = mulmod_p(v.as, e.z);
+                uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(a.i0 + first_res + h * RUN + m0));
+                uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(a.i0 + first_res + h * RUN + m0));
 #pragma unroll
                 for (int q = 0; q < PPL; ++q) {
-                    const uint32_t cell = bucket_of<POW2>(tb, col);
-                    const uint32_t rel = sum_of(cell, first_cell[q]);
-                    const uint32_t flip = sign_flip_of(ts);
-                    bad |= rel >= static_cast<uint32_t>(NC);
-                    if (NC == 2) {
-                        *reinterpret_cast<uint2*>(rec_dst + q * kRec) =
-                            make_uint2(flip, rel == 0u ? ~0u : 0u);
-                    } else {
-                        *reinterpret_cast<uint4*>(rec_dst + q * kRec) = make_uint4(
-                            flip, rel == 0u ? ~0u : 0u, rel == 1u ? ~0u : 0u, rel == 2u ? ~0u : 0u);
-                    }
-                    if (q + 1 < PPL) {
-                        tb = hash_advance(tb, Aj);
-                        ts = hash_advance(ts, Asj);
-                    }
+                    flips[q] = __builtin_amdgcn_ballot_w64(ys > kP61 - As);
+                    wraps[q] = __builtin_amdgcn_ballot_w64(yb > kP61 - A);
+                    yb = hash_advance(yb, v.a);
+                    ys = hash_advance(ys, v.as);
                 }
             }
-            // A coordinate outside the NC cells cannot happen with a list built by
-            // cs_params_init; the check is kept so that a wrong list costs time, never
-            // correctness: such a visit's values go to memory one by one, and the tile is
-            // cleared so that the sums below take nothing from it.
-            const bool stray = was_active && __builtin_amdgcn_ballot_w64(bad) != 0;
-            if (stray) {
-                uint64_t tb = yb, ts = ys;
+            {
+                // the bits of my walker: bit l of word q is coordinate l PPL + q
+                uint32_t flip[PPL], wrap[PPL];
+                const uint64_t odd = (w >> 29 & 1u) != 0 ? ~0ull : 0ull;
 #pragma unroll
                 for (int q = 0; q < PPL; ++q) {
-                    raw_lds[h * RUN + m0 + q] = bucket_of<POW2>(tb, col) | sign_flip_of(ts);
-                    if (q + 1 < PPL) {
-                        tb = hash_advance(tb, Aj);
-                        ts = hash_advance(ts, Asj);
-                    }
+                    const uint64_t f = flips[q] ^ odd;
+                    const uint32_t shift = static_cast<uint32_t>(h * WL) & 31u;
+                    flip[q] = (lane < 32 ? static_cast<uint32_t>(f) : static_cast<uint32_t>(f >> 32)) >> shift;
+                    wrap[q] = (lane < 32 ? static_cast<uint32_t>(wraps[q]) : static_cast<uint32_t>(wraps[q] >> 32)) >> shift;
                 }
-            }
-            yb = hash_advance(yb, A_of(code_k));
-            ys = hash_advance(ys, As_of(code_k));
-            __builtin_amdgcn_wave_barrier();
-            if (stray) {
-                const uint32_t* raw = raw_lds + h * RUN;
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
                 for (int m = 0; m < RUN; ++m) {
-                    const uint32_t pk = raw[m];
-                    const float val = apply_sign(a.scale * my_row[m], pk & 0x80000000u);
-                    if (live && val != 0.0f)
-                        atomic_add_noret(Tcol + static_cast<size_t>(pk & 0x7fffffffu) * cell_floats, val);
-                    my_row[m] = 0.0f;
-                }
-            }
-            if (was_active) {
-#pragma unroll
-                for (int m = 0; m < RUN; ++m) {
-                    if (NC == 2) {
-                        const uint2 rec = *reinterpret_cast<const uint2*>(my_rec + m * kRec);
-                        const uint32_t bits = __float_as_uint(my_row[m]) ^ rec.x;
-                        const uint32_t t0 = bits & rec.y;
-                        acc[0][m] += __uint_as_float(t0);
-                        acc[1][m] += __uint_as_float(bits ^ t0);
-                    } else {
-                        const uint4 rec = *reinterpret_cast<const uint4*>(my_rec + m * kRec);
-                        const uint32_t bits = __float_as_uint(my_row[m]) ^ rec.x;
-                        const uint32_t t0 = bits & rec.y, t1 = bits & rec.z;
-                        acc[0][m] += __uint_as_float(t0);
-                        acc[1][m] += __uint_as_float(t1);
-                        if (NC == 3) {
-                            acc[2][m] += __uint_as_float(bits ^ t0 ^ t1);
-                        } else {
-                            const uint32_t t2 = bits & rec.w;
-                            acc[2][m] += __uint_as_float(t2);
-                            acc[NC - 1][m] += __uint_as_float(bits ^ t0 ^ t1 ^ t2);
-                        }
-                    }
+                    const int l = m / PPL, q = m % PPL;
+                    const uint32_t bits = __float_as_uint(my_row[m]) ^ ((flip[q] << (31 - l)) & 0x80000000u);
+                    const uint32_t to = static_cast<uint32_t>(static_cast<int32_t>(wrap[q] << (31 - l)) >> 31);
+                    plain[m] += __uint_as_float(bits & ~to);
+                    wrapped[m] += __uint_as_float(bits & to);
                     // keeps the LDS reads of later coordinates from being hoisted over the sums
                     // of earlier ones, which would cost a register per read in flight
                     if (m % 4 == 3) __builtin_amdgcn_sched_barrier(0);
                 }
             }
             __builtin_amdgcn_wave_barrier();
+            k = k_next;
+            e = e_next;
+            k_next = cursor.next();
+            e_next = steps[k_next == ~0u ? 0u : k_next];
         }
-        // every running sum goes to memory once
-        const uint32_t* first = first_lds + h * RUN;
-        if (POW2 && RUN == 8 && !fold) {
-            // Two neighbouring cells of a bundle are one aligned 64-byte block when the lower one is
-            // even.  The sums of a residue take the slots of those blocks in LDS (an even first
-            // cell: slots 0 .. NC-1, an odd one: 1 .. NC), and a block then leaves as one request:
-            // on average NC / 2 + 1/2 requests per residue instead of NC.  Only short vectors (RUN =
-            // 8) gain, whose time is mostly these requests; long ones stream meanwhile and
-            // only lose the registers (2.5 % at d = 10^8).
-            constexpr int kSlots = (NC + 2) / 2 * 2;
-            uint32_t* cell0_lds = raw_lds;             // a walker's first block, as an even cell
+        // every sum in its place: plain, wrapped = sums 0 and 1 (0 and omega)
+        move_to(0);
+        auto sum_of = [&](int q, int m) -> float {
+            if constexpr (POW2) return q == 0 ? plain[m] : q == 1 ? wrapped[m] : other[q > 1 && q - 2 < NC - 2 ? q - 2 : 0][m];
+            else return q == 0 ? plain[m] : q == NC / 2 ? wrapped[m] : other[q > 1 && NC > 2 ? 1 : 0][m];
+        };
+        if constexpr (PARTIAL) {
+            // [piece][wavefront][m][walker][running sum][worker]: the sums of a residue are neighbours, as the cells are
+            // that they belong to
+            float* dst = a.sums + v.at + (static_cast<uint64_t>(piece) * nwaves + wv) * (SPAN * WL) * ncell + h * ncell * WL + wl;
 #pragma unroll
             for (int m = 0; m < RUN; ++m) {
-                const uint32_t c0 = first[m], odd = c0 & 1u;
+                const uint32_t flip = first[m] & 0x80000000u;
+#pragma unroll
+                for (int q = 0; q < NC; ++q)
+                    if (q < static_cast<int>(ncell))
+                        dst[(m * WPW * ncell + q) * WL] = live ? apply_sign(a.scale * sum_of(q, m), flip) : 0.0f;
+            }
+        } else if (kPairs && !fold) {
+            // The sums of a residue take the slots of those blocks in LDS (an even first cell: slots 0 .. ncell-1, an
+            // odd one: 1 .. ncell), and a block then leaves as one request.
+            constexpr int kSlots = (NC + 2) / 2 * 2;
+#pragma unroll
+            for (int m = 0; m < RUN; ++m) {
+                const uint32_t f = first[m], odd = f & 1u;
                 float* dst = tile_lds + h * (kSlots * WL) + wl;
 #pragma unroll
                 for (int q = 0; q < kSlots; ++q) {
                     // slot q holds sum q (even first cell) or q - 1 (odd)
-                    const float even_v = q < NC ? acc[q < NC ? q : 0][m] : 0.0f;
-                    const float odd_v = q > 0 && q - 1 < NC ? acc[q > 0 && q - 1 < NC ? q - 1 : 0][m] : 0.0f;
-                    dst[q * WL] = live ? (odd ? odd_v : even_v) : 0.0f;
+                    const float even_v = q < NC ? sum_of(q < NC ? q : 0, m) : 0.0f;
+                    const float odd_v = q > 0 && q - 1 < NC ? sum_of(q > 0 && q - 1 < NC ? q - 1 : 0, m) : 0.0f;
+                    dst[q * WL] = live ? apply_sign(odd ? odd_v : even_v, f & 0x80000000u) : 0.0f;
                 }
-                if (wl == 0) cell0_lds[h] = c0 - odd;
                 __builtin_amdgcn_wave_barrier();
 #pragma unroll
                 for (int t = 0; t < kSlots; ++t) {     // WPW * kSlots * WL items, 64 at a time
                     const uint32_t item = t * 64 + lane;
-                    const uint32_t of = item / (kSlots * WL), q = item / WL % kSlots, w = item % WL;
+                    const uint32_t of = item / (kSlots * WL), slot = item / WL % kSlots, from = item % WL;
                     const float sum = tile_lds[item];
+                    const uint32_t cell0 = first_lds[of * RUN + m] & 0x7ffffffeu;
                     if (sum != 0.0f)
-                        atomic_add_noret(a.T + (static_cast<size_t>(v.j) * a.c + ((cell0_lds[of] + q) & mask)) * kGroup + w,
+                        atomic_add_noret(a.T + (static_cast<size_t>(v.j) * a.c + ((cell0 + slot) & mask)) * kGroup + from,
                                          a.scale * sum);
                 }
                 __builtin_amdgcn_wave_barrier();
             }
-            continue;
+        } else {
+#pragma unroll
+            for (int m = 0; m < RUN; ++m) {
+                const uint32_t f = first[m], flip = f & 0x80000000u;
+#pragma unroll
+                for (int q = 0; q < NC; ++q) {
+                    float x = live ? sum_of(q, m) : 0.0f;
+                    if (fold) {                        // the WL lanes of my walker hold the workers' sums of a cell
+#pragma unroll
+                        for (int off = 1; off < WL; off <<= 1) x += __shfl_xor(x, off);
+                        if (wl != 0) x = 0.0f;
+                    }
+                    if (x != 0.0f)
+                        atomic_add_noret(Tcol + static_cast<size_t>(cell_of_sum(f & 0x7fffffffu, q)) * cell_floats,
+                                         apply_sign(a.scale * x, flip));
+                }
+            }
         }
-#pragma unroll
-        for (int m = 0; m < RUN; ++m) {
-            const uint32_t c0 = first[m];
-#pragma unroll
-            for (int q = 0; q < NC; ++q) {
-                if (!fold) {
-                    if (live && acc[q][m] != 0.0f)
-                        atomic_add_noret(Tcol + static_cast<size_t>(cell_of_sum(c0, q)) * kGroup,
-                                         a.scale * acc[q][m]);
-                } else {
-                    // the WL lanes of my walker hold the same cell's sums of the WL workers
-                    float sum = live ? acc[q][m] : 0.0f;
-#pragma unroll
-                    for (int off = 1; off < WL; off <<= 1) sum += __shfl_xor(sum, off);
-                    if (wl == 0 && sum != 0.0f)
-                        atomic_add_noret(Tcol + cell_of_sum(c0, q), a.scale * sum);
+        // Visits whose cells are not kept (which cannot be with a list built by cs_params_init: a wrong list costs
+        // time, never correctness): hashed by the definition, straight into memory.
+        if (!PARTIAL && listed < k1 - k0) {
+            const gfloat_ptr of_mine = (gfloat_ptr)a.g[live ? wl : 0];
+            for (uint32_t t = 0; t < k1 - k0; ++t) {
+                if (__builtin_amdgcn_readfirstlane(steps[t].w) >> 30 < 3u) continue;
+                const uint32_t s = __builtin_amdgcn_readfirstlane(steps[t].z), gap = __builtin_amdgcn_readfirstlane(steps[t].w) & kGapMask;
+                if (gap <= first_res || s + first_res >= d) continue;
+                const uint32_t in_gap = gap - first_res, in_vec = d - s - first_res;
+                const int len = static_cast<int>(in_gap < in_vec ? in_gap : in_vec) - h * RUN;     // of my walker's run
+                const uint32_t at = s + first_res + h * RUN;
+                uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(a.i0 + at));
+                uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(a.i0 + at));
+                for (int m = 0; m < RUN && m < len; ++m) {
+                    const float val = live ? apply_sign(a.scale * of_mine[at + m], sign_flip_of(ys)) : 0.0f;
+                    if (val != 0.0f)
+                        atomic_add_noret(Tcol + static_cast<size_t>(bucket_of<POW2>(yb, col)) * cell_floats, val);
+                    yb = hash_advance(yb, v.a);
+                    ys = hash_advance(ys, v.as);
                 }
             }
         }
@@ -817,7 +929,8 @@ void fill_visit_args(const cs_params* p, uint32_t j, VisitArgs& v) {
     v.j = static_cast<int32_t>(j);
     v.gmax = vp.gmax;
     v.a = p->a[j]; v.b = p->b[j]; v.as = p->as[j]; v.bs = p->bs[j];
-    for (int t = 0; t < 4; ++t) { v.gap[t] = vp.gap[t]; v.A[t] = vp.A[t]; v.As[t] = vp.As[t]; }
+    v.ncell = vp.ncell;
+    for (int t = 0; t < 4; ++t) v.gap[t] = vp.gap[t];
     for (int t = 0; t < CS_MAX_VISITS / 16; ++t) v.code[t] = vp.code[t];
 }
 
@@ -849,23 +962,45 @@ unsigned visits_grid(LIST& rows, int nrows) {
     return total;
 }
 
-// one launch: rows that all have ncell running sums, of one group of workers
-template <int WL, int RUN, int NWAVE>
-int launch_visits_run(VisitRows& rows, const VisitWorkers& a, int nrows, uint32_t ncell,
-                      hipStream_t stream) {
-    const dim3 grid(visits_grid<WL, RUN, NWAVE>(rows, nrows)), block(64 * NWAVE);
-    switch (ncell) {
-        case 2: k_accumulate_visits<WL, RUN, NWAVE, 2, VisitRows><<<grid, block, 0, stream>>>(rows, a); break;
-        case 3: k_accumulate_visits<WL, RUN, NWAVE, 3, VisitRows><<<grid, block, 0, stream>>>(rows, a); break;
-        case 4: k_accumulate_visits<WL, RUN, NWAVE, 4, VisitRows><<<grid, block, 0, stream>>>(rows, a); break;
-        default: return CS_EINVAL;
+// Visits of the longest piece of a launch's lists
+template <typename LIST>
+uint32_t most_steps(const LIST& rows, int nrows) {
+    uint32_t most = 1;
+    for (int q = 0; q < nrows; ++q) {
+        const uint32_t n = (rows.row[q].K + rows.row[q].pieces - 1) / rows.row[q].pieces;
+        most = n > most ? n : most;
     }
+    return most;
+}
+
+// one launch: rows that all have at most ncell running sums, of one group of workers
+template <int WL, int RUN, int NWAVE, typename LIST>
+int launch_visits_run(LIST& rows, const VisitWorkers& a, int nrows, uint32_t ncell, hipStream_t stream) {
+    const dim3 grid(visits_grid<WL, RUN, NWAVE>(rows, nrows)), block(64 * NWAVE);
+    const size_t lds = most_steps(rows, nrows) * sizeof(uint4);
+    constexpr bool pow2 = std::is_same<LIST, VisitRows>::value;
+    if (!(a.sums ? pow2 : a.T != nullptr)) return CS_EINVAL;            // running sums: power-of-two columns only
+    auto launch = [&](auto nc) {
+        constexpr int NC = decltype(nc)::value;
+        if constexpr (pow2) {
+            if (a.sums) {
+                k_accumulate_visits<WL, RUN, NWAVE, NC, true, LIST><<<grid, block, lds, stream>>>(rows, a);
+                return;
+            }
+        }
+        k_accumulate_visits<WL, RUN, NWAVE, NC, false, LIST><<<grid, block, lds, stream>>>(rows, a);
+    };
+    if (ncell == 2) launch(std::integral_constant<int, 2>());
+    else if (ncell == 4) launch(std::integral_constant<int, 4>());
+    else if constexpr (pow2) launch(std::integral_constant<int, 3>());
+    else return CS_EINVAL;
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
 template <int WL, int NWAVE>
 int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js, int nrows,
                   uint32_t ncell, hipStream_t stream) {
+    if (ncell < 2 || ncell > 4) return CS_EINVAL;
     VisitRows rows{};
     // every sum is a request, but RUN = 8 sends the two cells of an aligned block of a bundle in one
     double requests8[kRowsPerLaunch], requests16[kRowsPerLaunch];
@@ -886,7 +1021,7 @@ int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js,
 bool visits_apply(const cs_params* p, uint32_t j, int64_t d, bool any_cost = false) {
     const cs_visit_plan& vp = p->visit[j];
     if ((p->flags & CS_FLAG_NO_VISIT_LIST) != 0 || vp.K == 0) return false;
-    if (vp.ncell < 2 || vp.ncell > 4 || vp.K > CS_MAX_VISITS) return false;
+    if (vp.ncell < 2 || vp.ncell > 4 || vp.K > CS_MAX_VISITS || d > kStepsMaxD) return false;   // (lists end at 2^28)
     if (static_cast<uint64_t>(d) > vp.cover) return false;
     return any_cost || vp.cost < vp.cost_walk;
 }
@@ -937,132 +1072,10 @@ int launch_visits_anyc(const cs_params* p, const VisitWorkers& a, const uint32_t
         requests[q] = 2.0 * rows.row[q].omega * static_cast<double>(rows.row[q].gmax);
     }
     const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * n / kStreamBytesPerNs;
-    if (choose_run8<WL>(rows, n, requests, requests, stream_ns)) {
-        const dim3 grid(visits_grid<WL, 8, 1>(rows, n));
-        if (omega == 1) k_accumulate_visits<WL, 8, 1, 2, VisitGapsRows><<<grid, 64, 0, stream>>>(rows, a);
-        else k_accumulate_visits<WL, 8, 1, 4, VisitGapsRows><<<grid, 64, 0, stream>>>(rows, a);
-    } else {
-        const dim3 grid(visits_grid<WL, 16, NWAVE>(rows, n)), block(64 * NWAVE);
-        if (omega == 1) k_accumulate_visits<WL, 16, NWAVE, 2, VisitGapsRows><<<grid, block, 0, stream>>>(rows, a);
-        else k_accumulate_visits<WL, 16, NWAVE, 4, VisitGapsRows><<<grid, block, 0, stream>>>(rows, a);
-    }
-    return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+    if (choose_run8<WL>(rows, n, requests, requests, stream_ns))
+        return launch_visits_run<WL, 8, 1>(rows, a, n, 2 * omega, stream);
+    return launch_visits_run<WL, 16, NWAVE>(rows, a, n, 2 * omega, stream);
 }
-
-// ---------------------------------------------------------------------------------------
-// What a visit does to the hashes of a coordinate, told by two comparisons.
-//
-// Visit k is at offset s_k, and with A = (a s_k) mod p the bucket hash of i + s_k is x + A, less p if
-// x >= p - A, where x is that of i.  A is the same for every coordinate, so the bucket moves on by A mod c,
-// and by p mod c back in the second case (one cell further if c is a power of two, for p = -1 mod c):
-// one of two cells, and which one is the comparison of x with p - 1 - A.  The sign hash likewise: its
-// parity is that of x' plus that of A', inverted after a wrap.  So a lane keeps the top 32 bits of x and x' of
-// its coordinates and compares them with the top 32 bits of the visit's two thresholds (bits 29..60);
-// where they are equal the lower bits would decide, and the visit is hashed by the definition
-// instead (once in 2^31 coordinates and visits).  Against carrying two 61-bit states per coordinate from visit
-// to visit this takes 10 vector operations per coordinate and visit for about 25.
-//
-// The visits are walked in the order of A mod c, so that at any time only the two sums of one value of it are
-// in registers; the others wait in LDS.
-// ---------------------------------------------------------------------------------------
-constexpr int kTopShift = 29;                          // 61-bit hash value -> its top 32 bits
-__device__ __forceinline__ uint32_t top_of(uint64_t y) { return static_cast<uint32_t>((y - 1) >> kTopShift); }
-// x wraps on an advance by A when it is above p - 1 - A
-__device__ __forceinline__ uint32_t threshold_of(uint64_t A) { return static_cast<uint32_t>((kP61 - 1 - A) >> kTopShift); }
-
-// A visit.  x: threshold of the bucket hash, y: of the sign hash, z: offset, w: bits 0..28 its gap (residues
-// that take part), bit 29 the parity of A', bits 30-31 A mod c (the running sum of a coordinate that does not
-// wrap), or 3 where that is none of the sums that are kept.
-constexpr uint32_t kGapMask = (1u << 29) - 1u;
-constexpr int64_t kStepsMaxD = 1ll << 29;              // offsets and gaps of longer vectors do not fit
-
-// The visits k0 .. k1 - 1 (at most MAX) in the order of A mod c, by all wavefronts of the workgroup; returns how
-// many of them are not `3`, which come first.  gap_of(k): residues of visit k; within: A mod c must be below it.
-template <bool POW2, int NWAVE, int MAX, typename GAP>
-__device__ __forceinline__ uint32_t fill_visit_steps(uint4* steps, uint32_t k0, uint32_t k1, uint64_t a, uint64_t as,
-                                                     const Columns& col, uint32_t within, GAP gap_of) {
-    constexpr int kChunks = (MAX + 63) / 64;
-    constexpr int kMine = (kChunks + NWAVE - 1) / NWAVE;
-    __shared__ uint32_t count[kChunks][4];
-    const int lane = threadIdx.x & 63, wq = threadIdx.x >> 6;
-    uint4 mine[kMine];
-    uint32_t rank[kMine];
-#pragma unroll
-    for (int u = 0; u < kMine; ++u) {
-        const int chunk = u * NWAVE + wq;
-        const uint32_t base = k0 + chunk * 64, k = base + lane;
-        if (chunk >= kChunks) continue;
-        uint32_t q = 4u;                               // no such visit
-        if (base < k1) {
-            const int64_t before = offset_of_visit(base, gap_of);
-            const uint64_t gap = k < k1 ? static_cast<uint64_t>(gap_of(k)) : 0;
-            uint64_t upto = gap;                       // of the gaps up to mine
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint64_t other = __shfl_up(upto, off);
-                upto += lane >= off ? other : 0;
-            }
-            const uint64_t s = static_cast<uint64_t>(before) + upto - gap;
-            const uint64_t A = mulmod_p(a, s), As = mulmod_p(as, s);
-            const uint32_t cell = bucket_of<POW2>(A + 1, col);
-            if (k < k1) q = cell < within ? cell : 3u;
-            mine[u] = make_uint4(threshold_of(A), threshold_of(As),
-                                 static_cast<uint32_t>(s < kStepsMaxD ? s : kStepsMaxD),
-                                 static_cast<uint32_t>(gap < kGapMask ? gap : kGapMask) |
-                                     static_cast<uint32_t>(As & 1u) << 29 | q << 30);
-        }
-        rank[u] = ~0u;
-#pragma unroll
-        for (uint32_t t = 0; t < 4; ++t) {
-            const uint64_t same = __builtin_amdgcn_ballot_w64(q == t);
-            if (lane == 0) count[chunk][t] = __builtin_popcountll(same);
-            if (q == t) rank[u] = t << 16 | __builtin_popcountll(same & ((1ull << lane) - 1));
-        }
-    }
-    __syncthreads();
-    uint32_t listed = 0;
-#pragma unroll
-    for (int u = 0; u < kMine; ++u) {
-        const int chunk = u * NWAVE + wq;
-        if (chunk >= kChunks || rank[u] == ~0u) continue;
-        uint32_t at = rank[u] & 0xffffu;
-        const uint32_t q = rank[u] >> 16;
-        for (uint32_t t = 0; t <= q; ++t)
-            for (int ch = 0; ch < (t < q ? kChunks : chunk); ++ch) at += count[ch][t];
-        steps[at] = mine[u];
-    }
-    for (int ch = 0; ch < kChunks; ++ch) listed += count[ch][0] + count[ch][1] + count[ch][2];
-    __syncthreads();
-    return __builtin_amdgcn_readfirstlane(listed);
-}
-
-// The visits of steps[0 .. n) that residues from first_res on take part in, one after the other: a list with one
-// short and one long gap leaves most walkers with few of its visits (K = 277, gaps 243 885 and 1 495 226:
-// 66 for five residues in six), and looking at 64 visits at once finds the next without stepping through the others.
-struct VisitCursor {
-    const uint4* steps;
-    uint64_t todo;                                      // visits base .. base + 63 that are left
-    uint32_t base, n;
-    uint32_t first_res, d;
-    __device__ __forceinline__ void look() {
-        const uint32_t k = base + (threadIdx.x & 63);
-        const uint4 e = steps[k < n ? k : 0];
-        todo = __builtin_amdgcn_ballot_w64(k < n && (e.w & kGapMask) > first_res && e.z + first_res < d);
-    }
-    __device__ __forceinline__ VisitCursor(const uint4* steps_, uint32_t n_, uint32_t first_res_, uint32_t d_)
-        : steps(steps_), base(0), n(n_), first_res(first_res_), d(d_) { look(); }
-    // the next visit, or ~0u
-    __device__ __forceinline__ uint32_t next() {
-        while (todo == 0) {
-            if (base + 64 >= n) return ~0u;
-            base += 64;
-            look();
-        }
-        const uint32_t k = base + static_cast<uint32_t>(__builtin_ctzll(todo));
-        todo &= todo - 1;
-        return k;
-    }
-};
 
 // ---------------------------------------------------------------------------------------
 // The update of one vector (one worker, or the workers' vectors summed beforehand) along visit
@@ -1085,47 +1098,52 @@ constexpr int kOneRun = 4;
 constexpr int kOneAhead = 3;
 constexpr int kOneWaves = 4;
 
-template <int NC, typename LIST>
+// PARTIAL: the sums go to a workspace, [piece][residue][running sum], instead of being added to the table
+// (cs_index.hip).
+template <int NC, bool PARTIAL, typename LIST>
 __global__ void __launch_bounds__(64 * kOneWaves)
 k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, uint32_t c,
                  int cell_floats, int64_t d, int64_t i0, float scale) {
     constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
     constexpr int SPAN = 64 * kOneRun;
-    constexpr int kMaxSteps = POW2 ? CS_MAX_VISITS : CS_ANYC_MAX_VISITS;
     const unsigned row = row_of_block(rows);
     const auto& v = rows.at(row);
     const uint32_t piece = (blockIdx.x - rows.first[row]) / v.blocks;
     const uint32_t block = (blockIdx.x - rows.first[row]) % v.blocks;
     const int lane = threadIdx.x & 63;
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wavefront-uniform
-    __shared__ uint4 steps[kMaxSteps];
+    extern __shared__ uint4 steps[];                   // the visits of my piece
     __shared__ __attribute__((aligned(16))) float sum_lds_all[kOneWaves][NC][SPAN];
-    __shared__ uint32_t left_all[kOneWaves][kMaxSteps / 32 + 1];       // visits left for the definition
-    __shared__ uint32_t first_lds_all[kOneWaves][SPAN];                // cell | sign of a residue
-    float (*sums)[SPAN] = sum_lds_all[wq];
-    uint32_t* first = first_lds_all[wq];
-    uint32_t* left = left_all[wq];
+    __shared__ uint32_t first_lds_all[PARTIAL ? 1 : kOneWaves][SPAN];  // first cell of a residue
+    float (*parked)[SPAN] = sum_lds_all[wq];
+    uint32_t* first = first_lds_all[PARTIAL ? 0 : wq];
     const Columns col = columns_of<POW2>(c);
     const uint32_t mask = c - 1u;
-    uint32_t omega = NC - 1;                           // values of A mod c that the sums cover
-    if constexpr (!POW2) omega = v.omega;
-    auto gap_of = [&](uint32_t k) -> int64_t {
-        if constexpr (POW2) return static_cast<int64_t>(v.gap[(v.code[k >> 4] >> ((k & 15u) * 2u)) & 3u]);
-        else return static_cast<int64_t>(v.gap[k]);
-    };
+    uint32_t ncell, omega;                             // running sums, and the values of A mod c that they cover
+    if constexpr (POW2) {
+        ncell = v.ncell;
+        omega = ncell - 1;
+    } else {
+        omega = v.omega;
+        ncell = 2 * omega;
+    }
     auto cell_of_sum = [&](uint32_t first, uint32_t q) -> uint32_t {
         if constexpr (POW2) {
             return (first + q) & mask;
         } else {
-            const uint32_t x = q < v.omega ? first + q : first + (q - v.omega) + (c - v.pc);
+            const uint32_t x = q < omega ? first + q : first + (q - omega) + (c - v.pc);
             return x >= c ? x - c : x;
         }
     };
-    float* __restrict__ Sj = S + static_cast<size_t>(v.j) * c * cell_floats;
+    uint64_t at = static_cast<uint64_t>(v.j) * c * cell_floats;
+    if constexpr (PARTIAL) at = v.at;
+    float* __restrict__ Sj = S + at;
     const int64_t nwaves = (static_cast<int64_t>(v.gmax) + SPAN - 1) / SPAN;
     const int64_t nsets = (nwaves + kOneWaves - 1) / kOneWaves;
     const uint32_t k0 = v.K * piece / v.pieces, k1 = v.K * (piece + 1) / v.pieces;
-    const uint32_t listed = fill_visit_steps<POW2, kOneWaves, kMaxSteps>(steps, k0, k1, v.a, v.as, col, omega, gap_of);
+    VisitPlaces places;
+    places.init(v);
+    const uint32_t listed = fill_visit_steps<POW2, kOneWaves>(steps, places, v, k0, k1, col, omega);
     const uint32_t last4 = static_cast<uint32_t>(d) - kOneRun;
 
     // sets of neighbouring wavefronts go to one XCD, as in k_accumulate_visits
@@ -1136,6 +1154,7 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
         const uint32_t wave_res = static_cast<uint32_t>(wv * SPAN);
         const uint32_t my_res = wave_res + lane * kOneRun;
         uint32_t xb[kOneRun], xs[kOneRun];              // top bits of the hashes at my residues
+        uint32_t signs = 0;                             // bit m: the sign of residue m is -1
         {
             uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
             uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res));
@@ -1143,6 +1162,7 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
             for (int m = 0; m < kOneRun; ++m) {
                 xb[m] = top_of(yb);
                 xs[m] = top_of(ys);
+                signs |= (sign_flip_of(ys) >> 31) << m;
                 yb = hash_advance(yb, v.a);
                 ys = hash_advance(ys, v.as);
             }
@@ -1152,7 +1172,7 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
             uint32_t tb, ts, s, w;                      // the step, as in steps[k]
             uint32_t k;                                 // ~0u for none
         };
-        VisitCursor cursor(steps, listed, wave_res, static_cast<uint32_t>(d));
+        VisitCursor cursor(steps, k1 - k0, wave_res, static_cast<uint32_t>(d));
         auto request = [&](Step& st) {
             st.k = cursor.next();
             const uint4 e = steps[st.k == ~0u ? 0u : st.k];
@@ -1190,44 +1210,59 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
         uint32_t cur = 0;
 #pragma unroll
         for (int m = 0; m < kOneRun; ++m) plain[m] = wrapped[m] = 0.0f;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) *reinterpret_cast<vec4f*>(&sums[q][lane * kOneRun]) = vec4f{0.0f, 0.0f, 0.0f, 0.0f};
         auto park = [&](uint32_t q, const float (&x)[kOneRun]) {
-            *reinterpret_cast<vec4f*>(&sums[q][lane * kOneRun]) = vec4f{x[0], x[1], x[2], x[3]};
-        };
-        auto next_sums = [&]() {                        // neighbouring cells share a sum (power-of-two c)
-            park(cur, plain);
-            if constexpr (!POW2) park(cur + NC / 2, wrapped);
+            vec4f u;
 #pragma unroll
-            for (int m = 0; m < kOneRun; ++m) {
-                plain[m] = POW2 ? wrapped[m] : 0.0f;
-                wrapped[m] = 0.0f;
-            }
-            ++cur;
+            for (int m = 0; m < kOneRun; ++m) u[m] = x[m];
+            *reinterpret_cast<vec4f*>(&parked[q][lane * kOneRun]) = u;
         };
-        bool any_left = listed < k1 - k0;
-        if (lane <= kMaxSteps / 32) left[lane] = 0;
+        auto fetch = [&](uint32_t q, float (&x)[kOneRun]) {
+            const vec4f u = *reinterpret_cast<const vec4f*>(&parked[q][lane * kOneRun]);
+#pragma unroll
+            for (int m = 0; m < kOneRun; ++m) x[m] = u[m];
+        };
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+            *reinterpret_cast<vec4f*>(&parked[q][lane * kOneRun]) = vec4f{0.0f, 0.0f, 0.0f, 0.0f};
+        auto move_to = [&](uint32_t q) {                // (neighbouring cells share a sum: power-of-two c)
+            const uint32_t step = POW2 ? 1 : omega;
+            park(cur, plain);
+            park(cur + step, wrapped);
+            fetch(q, plain);
+            fetch(q + step, wrapped);
+            cur = q;
+        };
         auto add_up = [&](Step& st) {
             const uint32_t room = room_of(st.s, st.w);
             vec4f x = st.x;
             if (room < SPAN) x = cut(x, st.s, room);
-            while (cur < st.w >> 30) next_sums();
-            bool unsure = false;
-#pragma unroll
-            for (int m = 0; m < kOneRun; ++m) unsure |= xb[m] == st.tb || xs[m] == st.ts;
-            if (__builtin_amdgcn_ballot_w64(unsure) != 0) {
-                if (lane == 0) left[st.k >> 5] |= 1u << (st.k & 31u);
-                any_left = true;
-                x = vec4f{0.0f, 0.0f, 0.0f, 0.0f};
-            }
-            const bool odd = (st.w >> 29 & 1u) != 0;
-            const float in[kOneRun] = {x.x, x.y, x.z, x.w};
+            if (cur != st.w >> 30) move_to(st.w >> 30);
+            bool flip[kOneRun], wrap[kOneRun], unsure = false;
 #pragma unroll
             for (int m = 0; m < kOneRun; ++m) {
-                const float val = (xs[m] > st.ts) != odd ? -in[m] : in[m];
-                const bool wraps = xb[m] > st.tb;
-                plain[m] += wraps ? 0.0f : val;
-                wrapped[m] += wraps ? val : 0.0f;
+                flip[m] = xs[m] > st.ts;
+                wrap[m] = xb[m] > st.tb;
+                unsure |= xb[m] == st.tb || xs[m] == st.ts;
+            }
+            if (__builtin_amdgcn_ballot_w64(unsure) != 0) {
+                // the lower bits decide: whole hash values against whole thresholds
+                const uint64_t A = mulmod_p(v.a, st.s), As = mulmod_p(v.as, st.s);
+                uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
+                uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res));
+#pragma unroll
+                for (int m = 0; m < kOneRun; ++m) {
+                    flip[m] = ys > kP61 - As;
+                    wrap[m] = yb > kP61 - A;
+                    yb = hash_advance(yb, v.a);
+                    ys = hash_advance(ys, v.as);
+                }
+            }
+            const bool odd = (st.w >> 29 & 1u) != 0;
+#pragma unroll
+            for (int m = 0; m < kOneRun; ++m) {
+                const float val = flip[m] != odd ? -x[m] : x[m];
+                plain[m] += wrap[m] ? 0.0f : val;
+                wrapped[m] += wrap[m] ? val : 0.0f;
             }
         };
         Step st[kOneAhead];
@@ -1247,52 +1282,59 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
             }
         }
         park(cur, plain);
-        park(cur + (POW2 ? 1 : NC / 2), wrapped);
+        park(cur + (POW2 ? 1 : omega), wrapped);
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {                  // the signs of the residues
+            float x[kOneRun];
+            fetch(q, x);
+#pragma unroll
+            for (int m = 0; m < kOneRun; ++m) x[m] = apply_sign(x[m], (signs >> m) << 31);
+            park(q, x);
+        }
         __builtin_amdgcn_wave_barrier();
-        // visits that the comparisons could not tell, or whose cells are not kept: hashed by the definition,
-        // straight into memory
-        if (any_left) {
-            for (uint32_t k = 0; k < k1 - k0; ++k) {
-                if (k < listed && (left[k >> 5] >> (k & 31u) & 1u) == 0) continue;
+        if constexpr (PARTIAL) {
+            float* dst = Sj + (static_cast<uint64_t>(piece) * nwaves + wv) * SPAN * ncell;
+            for (uint32_t item = lane; item < SPAN * ncell; item += 64)
+                dst[item] = scale * parked[item % ncell][item / ncell];
+            __builtin_amdgcn_wave_barrier();
+        } else {
+            // visits whose cells are not kept (never with a list of cs_params_init): hashed by the definition,
+            // straight into memory
+            for (uint32_t k = 0; listed < k1 - k0 && k < k1 - k0; ++k) {
                 const uint32_t s = __builtin_amdgcn_readfirstlane(steps[k].z), w = __builtin_amdgcn_readfirstlane(steps[k].w);
+                if (w >> 30 < 3u) continue;
                 if ((w & kGapMask) <= wave_res || s + wave_res >= static_cast<uint32_t>(d)) continue;
                 const uint32_t at = s + my_res;
                 const vec4f x = cut(*(gvec4_ptr)((gfloat_ptr)g + (at < last4 ? at : last4)), s, room_of(s, w));
-                const float in[kOneRun] = {x.x, x.y, x.z, x.w};
                 uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + at));
                 uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + at));
 #pragma unroll
                 for (int m = 0; m < kOneRun; ++m) {
-                    const float val = apply_sign(scale * in[m], sign_flip_of(ys));
+                    const float val = apply_sign(scale * x[m], sign_flip_of(ys));
                     if (val != 0.0f)
                         atomic_add_noret(Sj + static_cast<size_t>(bucket_of<POW2>(yb, col)) * cell_floats, val);
                     yb = hash_advance(yb, v.a);
                     ys = hash_advance(ys, v.as);
                 }
             }
-        }
-        // every sum goes to memory once, the NC sums of a residue by neighbouring lanes
-        {
+            // every sum goes to memory once, the NC sums of a residue by neighbouring lanes
             uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
-            uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res));
 #pragma unroll
             for (int m = 0; m < kOneRun; ++m) {
-                first[lane * kOneRun + m] = bucket_of<POW2>(yb, col) | sign_flip_of(ys);
+                first[lane * kOneRun + m] = bucket_of<POW2>(yb, col);
                 yb = hash_advance(yb, v.a);
-                ys = hash_advance(ys, v.as);
             }
-        }
-        __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll 1
-        for (uint32_t item = lane; item < SPAN * NC; item += 64) {
-            const uint32_t res = item / NC, q = item % NC;
-            const float sum = sums[q][res];
-            const uint32_t f = first[res];
-            if (sum != 0.0f)
-                atomic_add_noret(Sj + static_cast<size_t>(cell_of_sum(f & 0x7fffffffu, q)) * cell_floats,
-                                 apply_sign(scale * sum, f & 0x80000000u));
+            for (uint32_t item = lane; item < SPAN * NC; item += 64) {
+                const uint32_t res = item / NC, q = item % NC;
+                const float sum = parked[q][res];
+                const uint32_t f = first[res];
+                if (sum != 0.0f)
+                    atomic_add_noret(Sj + static_cast<size_t>(cell_of_sum(f, q)) * cell_floats, scale * sum);
+            }
+            __builtin_amdgcn_wave_barrier();
         }
-        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -1301,7 +1343,7 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
 // Every row has a list for this column count and vector length, and by its own estimate the
 // list beats one request per coordinate.
 bool anyc_visits_apply(const cs_params* p, int64_t d) {
-    if (p->c_pow2 || (p->flags & CS_FLAG_NO_VISIT_LIST) != 0) return false;
+    if (p->c_pow2 || d > kStepsMaxD || (p->flags & CS_FLAG_NO_VISIT_LIST) != 0) return false;
     for (uint32_t j = 0; j < p->r; ++j) {
         const cs_anyc_plan& vp = p->anyc[j];
         if (vp.K == 0 || vp.K > CS_ANYC_MAX_VISITS || (vp.omega != 1 && vp.omega != 2)) return false;
@@ -1389,7 +1431,6 @@ bool all_rows_listed(const cs_params* p, int64_t d) {
 // The lists serve the update of one vector: every row has one that covers d, and all of them
 // together send fewer requests than the lattice form (about one per 8 to 15 coordinates).
 bool one_applies(const cs_params* p, int64_t d) {
-    if (d > kStepsMaxD) return false;                  // (lists end at 2^28)
     double residues = 0.0;
     if (p->c_pow2) {
         if (!all_rows_listed(p, d)) return false;
@@ -1417,8 +1458,8 @@ int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const f
             VisitGapsRows rows{};
             for (int q = 0; q < n; ++q) fill_visit_gaps(p, js[q], rows.row[q]);
             const dim3 grid = shape(rows, n);
-            if (omega == 1) k_accumulate_one<2, VisitGapsRows><<<grid, 64 * kOneWaves, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale);
-            else k_accumulate_one<4, VisitGapsRows><<<grid, 64 * kOneWaves, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale);
+            if (omega == 1) k_accumulate_one<2, false, VisitGapsRows><<<grid, 64 * kOneWaves, most_steps(rows, n) * sizeof(uint4), stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale);
+            else k_accumulate_one<4, false, VisitGapsRows><<<grid, 64 * kOneWaves, most_steps(rows, n) * sizeof(uint4), stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale);
             return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
         });
     uint32_t order[CS_MAX_R], ncell = 2;
@@ -1434,14 +1475,138 @@ int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const f
         for (int q = 0; q < n; ++q) fill_visit_args(p, order[q0 + q], rows.row[q]);
         const dim3 grid = shape(rows, n);
         switch (ncell) {
-            case 2: k_accumulate_one<2, VisitRows><<<grid, 64 * kOneWaves, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
-            case 3: k_accumulate_one<3, VisitRows><<<grid, 64 * kOneWaves, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
-            case 4: k_accumulate_one<4, VisitRows><<<grid, 64 * kOneWaves, 0, stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
+            case 2: k_accumulate_one<2, false, VisitRows><<<grid, 64 * kOneWaves, most_steps(rows, n) * sizeof(uint4), stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
+            case 3: k_accumulate_one<3, false, VisitRows><<<grid, 64 * kOneWaves, most_steps(rows, n) * sizeof(uint4), stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
+            case 4: k_accumulate_one<4, false, VisitRows><<<grid, 64 * kOneWaves, most_steps(rows, n) * sizeof(uint4), stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
             default: return CS_EINVAL;
         }
         if (hipGetLastError() != hipSuccess) return CS_EHIP;
     }
     return CS_OK;
+}
+
+// ---------------------------------------------------------------------------------------
+// The update into a workspace of running sums instead of a table (cs_index.hip gathers them): what
+// the rows of one group of workers write and where.
+// ---------------------------------------------------------------------------------------
+namespace {
+
+// Every visit of the rows' lists moves a coordinate by fewer cells than it has running sums, which is what the
+// kernels rely on when the sums are all they write.  (Lists of cs_params_init do.)
+bool lists_hold(const cs_params* p) {
+    auto mulmod = [](uint64_t a, uint64_t b) {
+        const unsigned __int128 t = static_cast<unsigned __int128>(a) * b;
+        return reduce_p((static_cast<uint64_t>(t) & kP61) + static_cast<uint64_t>(t >> 61));
+    };
+    for (uint32_t j = 0; j < p->r; ++j) {
+        const cs_visit_plan& vp = p->visit[j];
+        uint64_t advance[4], s = 0, A = 0;
+        for (int t = 0; t < 4; ++t) {
+            if (vp.gap[t] >= static_cast<uint64_t>(kStepsMaxD)) return false;
+            advance[t] = mulmod(p->a[j], vp.gap[t]);
+        }
+        for (uint32_t k = 0; k < vp.K; ++k) {
+            if ((A & (p->c - 1)) + 1 >= vp.ncell) return false;
+            const uint32_t code = (vp.code[k / 16] >> (2 * (k % 16))) & 3u;
+            if ((s += vp.gap[code]) > static_cast<uint64_t>(kStepsMaxD)) return false;
+            A += advance[code];
+            A = A >= kP61 ? A - kP61 : A;
+        }
+    }
+    return true;
+}
+
+// The rows of one launch: pieces and run length are chosen, their places in the workspace taken, and, with
+// `run`, the launch is made.
+template <int WL>
+int partial_rows(VisitRows& rows, const VisitWorkers& a, int n, bool run, SumsPlan& plan, hipStream_t stream) {
+    double writes[kRowsPerLaunch];
+    uint32_t most = 2;
+    for (int q = 0; q < n; ++q) {
+        const VisitArgs& v = rows.row[q];
+        most = v.ncell > most ? v.ncell : most;
+        // a running sum costs as many requests of 1/24 ns as four times its bytes written and read would take to stream
+        // (one to eight times: within 3 % of each other, but for d = 60 789, W = 11, 5 x 1024: 32.8, 29.8, 28.4, 27.9 us)
+        writes[q] = 24.0 * 32.0 * WL * v.ncell * static_cast<double>(v.gmax) / kStreamBytesPerNs;
+    }
+    const double stream_ns = 4.0 * static_cast<double>(a.d) * WL * n / kStreamBytesPerNs;
+    int log_run = 0;                                   // (of one vector the sums lie in the order of the residues)
+    if (WL == 1) choose_pieces(rows, n, writes, kVisitNsOne, stream_ns);
+    else log_run = choose_run8<WL>(rows, n, writes, writes, stream_ns) ? 3 : 4;
+    const uint64_t span = WL == 1 ? 64 * kOneRun : 64u / WL << log_run;
+    for (int q = 0; q < n; ++q) {
+        VisitArgs& v = rows.row[q];
+        SumsRow& out = plan.row[v.j];
+        v.at = out.at = plan.floats;
+        out.residues = v.gmax;
+        out.piece_floats = (v.gmax + span - 1) / span * span * WL * v.ncell;
+        out.pieces = v.pieces;
+        out.ncell = v.ncell;
+        out.log_run = log_run;
+        plan.floats += out.piece_floats * v.pieces;
+    }
+    if (!run) return CS_OK;
+    if constexpr (WL == 1) {
+        const dim3 grid(visits_grid<1, kOneRun, kOneWaves>(rows, n));
+        k_accumulate_one<4, true, VisitRows><<<grid, 64 * kOneWaves, most_steps(rows, n) * sizeof(uint4), stream>>>(
+            rows, a.g[0], a.sums, a.c, 1, a.d, a.i0, a.scale);
+        return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+    } else {
+        if (log_run == 3) return launch_visits_run<WL, 8, 1>(rows, a, n, most, stream);
+        return launch_visits_run<WL, 16, WL == 8 ? kWavesPerGroupOf8 : 1>(rows, a, n, most, stream);
+    }
+}
+
+template <int WL>
+int partial_group(const cs_params* p, const VisitWorkers& a, bool run, SumsPlan& plan, hipStream_t stream) {
+    uint32_t order[CS_MAX_R];
+    for (uint32_t j = 0; j < p->r; ++j) {              // the longest lists first
+        int at = static_cast<int>(j);
+        for (; at > 0 && p->visit[order[at - 1]].K < p->visit[j].K; --at) order[at] = order[at - 1];
+        order[at] = j;
+    }
+    for (uint32_t q0 = 0; q0 < p->r; q0 += kRowsPerLaunch) {
+        const int n = p->r - q0 < kRowsPerLaunch ? static_cast<int>(p->r - q0) : kRowsPerLaunch;
+        VisitRows rows{};
+        for (int q = 0; q < n; ++q) fill_visit_args(p, order[q0 + q], rows.row[q]);
+        const int rc = partial_rows<WL>(rows, a, n, run, plan, stream);
+        if (rc != CS_OK) return rc;
+    }
+    return CS_OK;
+}
+
+}  // namespace
+
+// Power-of-two columns only: the two sums of a residue of another sketch belong to cells far apart, so that reading
+// them by cell fetches a block for each (5 x 180 000, d = 6.5 M, 8 workers: update 181 us and gathering 78, for
+// 255 with requests to the table).
+bool sums_apply(const cs_params* p, int64_t d) {
+    if (!p->c_pow2 || !all_rows_listed(p, d)) return false;
+    // (a list that is priced a little above the stride walk still belongs into the one launch of all rows)
+    for (uint32_t j = 0; j < p->r; ++j)
+        if (p->visit[j].cost > p->visit[j].cost_walk + p->visit[j].cost_walk / 4) return false;
+    return lists_hold(p);
+}
+
+int sums_lanes(int W) { return W > 4 ? 8 : W > 2 ? 4 : W; }
+
+// g_w null: the plan only
+int launch_accumulate_sums(const cs_params* p, float* sums, int lanes, int nw, const float* const* g_w, int64_t d,
+                           float scale, SumsPlan& plan, hipStream_t stream) {
+    plan = SumsPlan{};
+    VisitWorkers a{};
+    for (int w = 0; g_w && w < nw; ++w) a.g[w] = g_w[w];
+    a.sums = sums;
+    a.d = d;
+    a.c = p->c;
+    a.nw = nw;
+    a.scale = scale;
+    switch (lanes) {
+        case 1: return partial_group<1>(p, a, g_w != nullptr, plan, stream);
+        case 2: return partial_group<2>(p, a, g_w != nullptr, plan, stream);
+        case 4: return partial_group<4>(p, a, g_w != nullptr, plan, stream);
+        default: return partial_group<8>(p, a, g_w != nullptr, plan, stream);
+    }
 }
 
 // fold: T is one table float[r][c] that receives the sum over all W workers (all_rows_listed
@@ -1514,7 +1679,7 @@ int launch_accumulate_walk(const cs_params* p, float* T, int W, const float* con
         }
         if (nwalked > 0) {
             int rc;
-            if (nw > 4) rc = launch_walk<8, 16, kWavesPerGroupOf8>(p, a, nwalked, stream);
+            if (nw > 4) rc = launch_walk<8, 16, kWalkWaves>(p, a, nwalked, stream);
             else if (nw > 2) rc = launch_walk<4, 16, 1>(p, a, nwalked, stream);
             else if (nw > 1) rc = launch_walk<2, 16, 1>(p, a, nwalked, stream);
             else rc = launch_walk<1, 16, 1>(p, a, nwalked, stream);

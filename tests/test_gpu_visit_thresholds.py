@@ -36,13 +36,13 @@ def _sketch(sk, g, i0):
         return sum(pool.map(lambda lo: sk.sketch(g[lo:lo + n], i0=i0 + lo), range(0, g.size, n)), sk.zeros())
 
 
-# a power of two with two to four running sums, and one and two cells per wrap for another column count
-@pytest.mark.parametrize("r,c,d", [(5, 1 << 14, 3_000_003), (3, 5001, 1_000_003)])
+# a power of two with two to four running sums, and one and two cells per wrap for other column counts
+@pytest.mark.parametrize("r,c,d,seed", [(5, 1 << 15, 3_200_003, 31), (3, 5001, 1_000_003, 31), (3, 9001, 400_003, 47)])
 @pytest.mark.parametrize("sign", [False, True])
 @pytest.mark.parametrize("below", [1, 0, -(1 << 28), 1 << 28])
-def test_update_at_the_thresholds(r, c, d, sign, below):
-    p = cs.cs_params_init(r, c, 31, d)
-    sk = orc.SketchOracle(r, c, 31)
+def test_update_at_the_thresholds(r, c, d, seed, sign, below):
+    p = cs.cs_params_init(r, c, seed, d)
+    sk = orc.SketchOracle(r, c, seed)
     j = r - 1
     lists = p.visit if p.c_pow2 else p.anyc
     assert all(lists[q].K > 0 for q in range(r))
@@ -57,3 +57,12 @@ def test_update_at_the_thresholds(r, c, d, sign, below):
     S = torch.zeros(r, c, dtype=torch.float32, device=DEV)
     cs.cs_sketch_accumulate(p, S, dev, i0=i0)
     assert_cells_close(S.cpu().numpy(), ref, terms_per_cell=d / c)
+    for W in (2, 3, 8):                              # walkers of 2, 4 and 8 workers, the vector last among them
+        gs = [torch.zeros_like(dev)] * (W - 1) + [dev]
+        T = torch.zeros(cs.cs_bundle_floats(p, W), dtype=torch.float32, device=DEV)
+        cs.cs_sketch_accumulate_bundle(p, T, gs, i0=i0)
+        assert_cells_close(T.view(r, c, cs.CS_BUNDLE_GROUP)[:, :, W - 1].cpu().numpy(), ref, terms_per_cell=d / c,
+                           what=f"{W} workers")
+        S.zero_()
+        cs.cs_sketch_accumulate_sum(p, S, gs, i0=i0)
+        assert_cells_close(S.cpu().numpy(), ref, terms_per_cell=d / c, what=f"sum of {W} workers")
