@@ -236,6 +236,26 @@ int cs_bundle_merge(const cs_params* p, float* dst, float beta, const float* T, 
 int cs_bundle_merge_momentum(const cs_params* p, float* S_t, float* S_u, float* S_v, const float* T,
                              int32_t W, float alpha, float rho, void* stream);
 
+/* The sketches of W workers written (not added) into the bundle T in two passes, with the merge over workers and
+ * sketch-space momentum along: running sums along the visit lists go to a workspace, then every cell is gathered
+ * from the sums that belong to it.  No atomics and no clearing of T; the same bits in every run.  What
+ * lies where is laid out once per sketch in an index (device memory of the caller).
+ *     T[w/8][j][b][w%8] = sum_t scale * s_j(t) * g_w[w][t] over the t < d with h_j(t) = b     (global index of g_w[w][0]: 0)
+ *     S_t = alpha * sum_w S^w (S_t null: left out);  S_u = rho S_u + S_t, S_v += S_u (S_u, S_v null: left out)
+ * cs_update_index_bytes: 0 where the sketch has no lists for vectors of length d, its column count is no power of
+ * two, or cs_bundle_zero, cs_sketch_accumulate_bundle and cs_bundle_merge take less time (W = 0: for one vector and T null,
+ * cs_sketch_zero and cs_sketch_accumulate).  index: what cs_update_index_build
+ * wrote for the same p and d (of another sketch: wrong sums, never an access out of range).  ws:
+ * cs_update_workspace_bytes, or a ceil(W/8)-th of it at least (then in several passes), 16-byte aligned like T;
+ * contents are scratch.
+ * T may be null for W <= 8 if S_t is wanted only. */
+int cs_update_index_bytes(const cs_params* p, int32_t W, int64_t d, size_t* bytes);
+int cs_update_index_build(const cs_params* p, int64_t d, void* index, size_t bytes, void* stream);
+int cs_update_workspace_bytes(const cs_params* p, int32_t W, int64_t d, size_t* bytes);
+int cs_bundle_sketch(const cs_params* p, float* T, int32_t W, const float* const* g_w, int64_t d, float scale,
+                     const void* index, size_t index_bytes, void* ws, size_t ws_bytes, float* S_t, float alpha,
+                     float* S_u, float* S_v, float rho, void* stream);
+
 /* Alg. 4 update for a list of (index, value) pairs:
  *     S[j][h_j(idx[t])] += scale * s_j(idx[t]) * val[t]
  * idx: device int64[n] (0 <= idx[t] < 2^61, repeats allowed and summed), val: device float[n]. */

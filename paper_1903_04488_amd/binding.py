@@ -97,6 +97,17 @@ _SIGNATURES = {
                                  ctypes.c_int64, ctypes.c_float, ctypes.c_void_p],
     "cs_bundle_merge": [ctypes.POINTER(CsParams), ctypes.c_void_p, ctypes.c_float,
                         ctypes.c_void_p, ctypes.c_int32, ctypes.c_float, ctypes.c_void_p],
+    "cs_update_index_bytes": [ctypes.POINTER(CsParams), ctypes.c_int32, ctypes.c_int64,
+                              ctypes.POINTER(ctypes.c_size_t)],
+    "cs_update_index_build": [ctypes.POINTER(CsParams), ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t,
+                              ctypes.c_void_p],
+    "cs_update_workspace_bytes": [ctypes.POINTER(CsParams), ctypes.c_int32, ctypes.c_int64,
+                                  ctypes.POINTER(ctypes.c_size_t)],
+    "cs_bundle_sketch": [ctypes.POINTER(CsParams), ctypes.c_void_p, ctypes.c_int32,
+                         ctypes.POINTER(ctypes.c_void_p), ctypes.c_int64, ctypes.c_float,
+                         ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_size_t,
+                         ctypes.c_void_p, ctypes.c_float, ctypes.c_void_p, ctypes.c_void_p,
+                         ctypes.c_float, ctypes.c_void_p],
     "cs_sketch_accumulate_sparse": [ctypes.POINTER(CsParams), ctypes.c_void_p, ctypes.c_void_p,
                                     ctypes.c_void_p, ctypes.c_int64, ctypes.c_float,
                                     ctypes.c_void_p],
@@ -485,6 +496,42 @@ def cs_bundle_merge_momentum(p, S_t, S_u, S_v, T, W: int, alpha: float, rho: flo
         ctypes.byref(p), _dev(S_t, torch.float32, "S_t", n), _dev(S_u, torch.float32, "S_u", n),
         _dev(S_v, torch.float32, "S_v", n), _dev(T, torch.float32, "T", cs_bundle_floats(p, W)), W, alpha, rho,
         _stream(S_t)), "cs_bundle_merge_momentum")
+
+
+def cs_update_index_bytes(p, W: int, d: int) -> int:
+    n = ctypes.c_size_t()
+    _check(load_library().cs_update_index_bytes(ctypes.byref(p), W, d, ctypes.byref(n)), "cs_update_index_bytes")
+    return n.value
+
+
+def cs_update_index_build(p, d: int, index):
+    _check(load_library().cs_update_index_build(ctypes.byref(p), d, _dev(index, torch.uint8, "index"), index.numel(),
+                                                _stream(index)), "cs_update_index_build")
+
+
+def cs_update_workspace_bytes(p, W: int, d: int) -> int:
+    n = ctypes.c_size_t()
+    _check(load_library().cs_update_workspace_bytes(ctypes.byref(p), W, d, ctypes.byref(n)),
+           "cs_update_workspace_bytes")
+    return n.value
+
+
+def cs_bundle_sketch(p, T, g_w, index, workspace, scale: float = 1.0, S_t=None, alpha: float = 1.0, S_u=None, S_v=None,
+                     rho: float = 0.0):
+    """T (or None, for up to 8 workers with S_t): the bundle, written whole; S_t, S_u, S_v: merge and momentum with it"""
+    W, n = len(g_w), _cells(p)
+    if W == 0:
+        raise CsError("g_w must be a non-empty list")
+    d = g_w[0].numel()
+
+    def table(S, name):
+        return None if S is None else _dev(S, torch.float32, name, n)
+
+    _check(load_library().cs_bundle_sketch(
+        ctypes.byref(p), None if T is None else _dev(T, torch.float32, "T", cs_bundle_floats(p, W)), W,
+        _ptr_array(g_w, torch.float32, "g_w", d), d, scale, _dev(index, torch.uint8, "index"), index.numel(),
+        _dev(workspace, torch.uint8, "workspace"), workspace.numel(), table(S_t, "S_t"), alpha, table(S_u, "S_u"),
+        table(S_v, "S_v"), rho, _stream(index)), "cs_bundle_sketch")
 
 
 def cs_sketch_feedback_pair(p, S_v, S_u, idx, val_v, val_u):

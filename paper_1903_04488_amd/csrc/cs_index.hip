@@ -1,0 +1,381 @@
+// Alg. 4 update in two passes: running sums along visit lists into a workspace (cs_walk.hip), then every table cell
+// gathered from the sums that belong to it.
+//
+// A walker of the list update ends with two to four sums per residue, and adding them into the
+// table is one atomic request per sum to a random cell: the memory-side atomic unit takes 21 to 24 G requests/s,
+// and the worker tables of a large sketch (168 MB per 8 workers at 5 x 2^20) are pushed out of the memory-side
+// cache by the streams, so that a request also reads and writes its block.  Written to the workspace in the order
+// in which they are computed the same sums are whole contiguous lines.  Which residues start in which cell
+// depends on the hash constants alone, so it is laid out once (the index: for every row the residues in the order
+// of their cells), and a thread per cell reads the two to five sums that are its own, adds them in a fixed
+// order, and writes the cell: the tables need no clearing, no atomics, the result does not depend on
+// the order of execution, and the merge over workers and the momentum, which read every cell, come along.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "cs_device.h"
+#include "cs_internal.h"
+#include "csketch.h"
+
+namespace cs {
+
+namespace {
+
+// the index: row j has start[c + 1] (the first of a cell's residues), then those residues
+struct IndexRows {
+    uint64_t at[CS_MAX_R];       // words before row j's start
+    uint64_t words;
+    uint64_t residues[CS_MAX_R];
+};
+
+IndexRows index_rows(const cs_params* p) {
+    IndexRows x{};
+    for (uint32_t j = 0; j < p->r; ++j) {
+        x.residues[j] = p->visit[j].gmax;
+        x.at[j] = x.words;
+        x.words += p->c + 1 + x.residues[j];
+    }
+    return x;
+}
+
+__global__ void __launch_bounds__(kBlock) k_index_count(KParams p, IndexRows rows, uint32_t* __restrict__ index) {
+    const uint32_t j = blockIdx.y;
+    uint32_t* start = index + rows.at[j];
+    const Columns col = columns_of<true>(p.c);
+    const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kBlock;
+    for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x; i < rows.residues[j]; i += stride)
+        atomicAdd(&start[bucket_of<true>(hash_state(p.a[j], p.b[j], i), col)], 1u);
+}
+
+// counts -> the end of every cell's residues; a workgroup per row
+__global__ void __launch_bounds__(1024) k_index_scan(KParams p, IndexRows rows, uint32_t* __restrict__ index) {
+    uint32_t* start = index + rows.at[blockIdx.x];
+    __shared__ uint32_t part[1024];
+    const uint32_t per = (p.c + 1023) / 1024, lo = threadIdx.x * per;
+    const uint32_t hi = lo + per < p.c ? lo + per : p.c;
+    uint32_t sum = 0;
+    for (uint32_t b = lo; b < hi; ++b) sum += start[b];
+    part[threadIdx.x] = sum;
+    __syncthreads();
+    for (uint32_t off = 1; off < 1024; off <<= 1) {
+        const uint32_t other = threadIdx.x >= off ? part[threadIdx.x - off] : 0u;
+        __syncthreads();
+        part[threadIdx.x] += other;
+        __syncthreads();
+    }
+    uint32_t end = part[threadIdx.x] - sum;
+    for (uint32_t b = lo; b < hi; ++b) {
+        end += start[b];
+        start[b] = end;
+    }
+    if (threadIdx.x == 0) start[p.c] = static_cast<uint32_t>(rows.residues[blockIdx.x]);
+}
+
+__global__ void __launch_bounds__(kBlock) k_index_fill(KParams p, IndexRows rows, uint32_t* __restrict__ index) {
+    const uint32_t j = blockIdx.y;
+    uint32_t* start = index + rows.at[j];
+    uint32_t* residue = start + p.c + 1;
+    const Columns col = columns_of<true>(p.c);
+    const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kBlock;
+    for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x; i < rows.residues[j]; i += stride)
+        residue[atomicSub(&start[bucket_of<true>(hash_state(p.a[j], p.b[j], i), col)], 1u) - 1u] = static_cast<uint32_t>(i);
+}
+
+// a cell's residues in ascending order, so that sums have one order
+__global__ void __launch_bounds__(kBlock) k_index_sort(uint32_t c, IndexRows rows, uint32_t* __restrict__ index) {
+    uint32_t* start = index + rows.at[blockIdx.y];
+    uint32_t* residue = start + c + 1;
+    const uint32_t b = blockIdx.x * kBlock + threadIdx.x;
+    if (b >= c) return;
+    const uint32_t lo = start[b], hi = start[b + 1];
+    for (uint32_t e = lo + 1; e < hi; ++e) {
+        const uint32_t x = residue[e];
+        uint32_t at = e;
+        for (; at > lo && residue[at - 1] > x; --at) residue[at] = residue[at - 1];
+        residue[at] = x;
+    }
+}
+
+struct GatherRow {
+    uint64_t index_at, at, piece_floats;
+    uint32_t residues, pieces, ncell, log_run;
+};
+struct GatherArgs {
+    const uint32_t* index;
+    const float* sums;           // of the first group
+    uint64_t group_floats;       // from one group's sums to the next
+    float* T;                    // the first group's table, or null
+    float* S_t;                  // or null: the merge of all groups (they must be all there are)
+    float* S_u;                  // or null: momentum and error accumulation behind it
+    float* S_v;
+    float alpha, rho;
+    int32_t groups;
+    uint32_t r, c;
+    GatherRow row[CS_MAX_R];
+};
+
+typedef float vec4f __attribute__((ext_vector_type(4)));
+
+// kCellLanes lanes per cell: one where there are cells enough to fill the chip, more where there are few, each
+// with many sums (a short vector's chains of visits are cut into pieces, every one with sums of its own).  WL = lanes
+// of a walker: the workers whose sums lie together.  Each lane has the reads of kAhead sums in flight.
+// The merge is accumulated in binary64 and rounded once, as in k_bundle_merge.
+template <int WL, int kCellLanes>
+__global__ void __launch_bounds__(kBlock) k_gather_sums(GatherArgs a) {
+    constexpr int kAhead = WL == 8 ? 4 : 8;
+    constexpr int kCells = kBlock / kCellLanes;        // of a workgroup
+    const uint32_t j = blockIdx.y, part = threadIdx.x % kCellLanes;
+    const uint32_t b = blockIdx.x * kCells + threadIdx.x / kCellLanes;
+    if (b >= a.c) return;                              // (all lanes of a cell together)
+    const GatherRow& row = a.row[j];
+    const uint32_t* start = a.index + row.index_at;
+    const uint32_t* residue = start + a.c + 1;
+    constexpr int kWalkers = 64 / WL;                  // of a wavefront
+    // the residues whose running sum q belongs to this cell: entry t of them all, upto[q - 1] <= t < upto[q], is
+    // residue[from[q] + t]
+    uint32_t from[4], upto[4], n = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+        from[q] = 0;
+        if (q < row.ncell) {
+            const uint32_t first = (b - q) & (a.c - 1u);
+            const uint32_t lo = start[first];
+            uint32_t hi = start[first + 1];
+            hi = hi < row.residues ? hi : row.residues;
+            from[q] = lo - n;
+            n += hi > lo ? hi - lo : 0u;
+        }
+        upto[q] = n;
+    }
+    const uint32_t items = n * row.pieces;
+    double total = 0.0;
+    const float* sums = a.sums + row.at;
+    for (int g = 0; g < a.groups; ++g, sums += a.group_floats) {
+        float cell[WL];
+#pragma unroll
+        for (int w = 0; w < WL; ++w) cell[w] = 0.0f;
+        for (uint32_t t0 = part; t0 < items; t0 += kAhead * kCellLanes) {
+            float x[kAhead][WL];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const uint32_t t = t0 + u * kCellLanes;
+                const uint32_t piece = row.pieces == 1 ? 0u : t / n, e = t - piece * n;
+                const uint32_t q = (e >= upto[0] ? 1u : 0u) + (e >= upto[1] ? 1u : 0u) + (e >= upto[2] ? 1u : 0u);
+                const uint32_t base = e < upto[0] ? from[0] : e < upto[1] ? from[1] : e < upto[2] ? from[2] : from[3];
+                uint32_t i = t < items ? residue[base + e] : ~0u;
+                const bool there = i < row.residues;   // (not: no more items, or an index of another sketch)
+                i = there ? i : 0u;
+                // [wavefront][m][walker]: residue i is m = i mod 2^log_run of walker i / 2^log_run
+                const uint32_t m = i & ((1u << row.log_run) - 1u), walker = i >> row.log_run;
+                const uint32_t slot = (((walker / kWalkers) << row.log_run) + m) * kWalkers + walker % kWalkers;
+                const float* src = sums + (there ? piece : 0u) * row.piece_floats +
+                                   (static_cast<uint64_t>(slot) * row.ncell + (there ? q : 0u)) * WL;
+#pragma unroll
+                for (int w = 0; w < WL; ++w) x[u][w] = 0.0f;
+                if (there) {
+                    if constexpr (WL >= 4) {
+#pragma unroll
+                        for (int w = 0; w < WL; w += 4) {
+                            const vec4f v = *reinterpret_cast<const vec4f*>(src + w);
+#pragma unroll
+                            for (int l = 0; l < 4; ++l) x[u][w + l] = v[l];
+                        }
+                    } else {
+#pragma unroll
+                        for (int w = 0; w < WL; ++w) x[u][w] = src[w];
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                for (int w = 0; w < WL; ++w) cell[w] += x[u][w];
+        }
+        if constexpr (kCellLanes > 1) {
+#pragma unroll
+            for (int off = 1; off < kCellLanes; off <<= 1)
+#pragma unroll
+                for (int w = 0; w < WL; ++w) cell[w] += __shfl_xor(cell[w], off);
+        }
+        if (a.T && part == 0) {
+            static_assert(CS_BUNDLE_GROUP == 8, "a cell of a bundle is two pieces of 16 bytes");
+            vec4f* dst = reinterpret_cast<vec4f*>(a.T + ((static_cast<uint64_t>(g) * a.r + j) * a.c + b) * CS_BUNDLE_GROUP);
+            vec4f u[2];
+#pragma unroll
+            for (int w = 0; w < CS_BUNDLE_GROUP; ++w) u[w / 4][w % 4] = w < WL ? cell[w < WL ? w : 0] : 0.0f;
+            dst[0] = u[0];
+            dst[1] = u[1];
+        }
+        if (a.S_t) {
+#pragma unroll
+            for (int w = 0; w < WL; ++w) total += static_cast<double>(cell[w]);
+        }
+    }
+    if (a.S_t && part == 0) {
+        const uint64_t t = static_cast<uint64_t>(j) * a.c + b;
+        const float st = static_cast<float>(static_cast<double>(a.alpha) * total);
+        a.S_t[t] = st;
+        if (a.S_u) {
+            const float u = a.rho * a.S_u[t] + st;
+            a.S_u[t] = u;
+            a.S_v[t] = a.S_v[t] + u;
+        }
+    }
+}
+
+// lanes per cell: about 2^18 lanes in all
+template <int WL>
+int launch_gather(const cs_params* p, const GatherArgs& a, hipStream_t stream) {
+    const uint64_t cells = static_cast<uint64_t>(p->r) * p->c;
+    auto grid = [&](unsigned per) { return dim3((p->c + per - 1) / per, p->r); };
+    if (cells >= (1u << 17)) k_gather_sums<WL, 1><<<grid(kBlock), kBlock, 0, stream>>>(a);
+    else if (cells >= (1u << 15)) k_gather_sums<WL, 4><<<grid(kBlock / 4), kBlock, 0, stream>>>(a);
+    else if (cells >= (1u << 13)) k_gather_sums<WL, 16><<<grid(kBlock / 16), kBlock, 0, stream>>>(a);
+    else k_gather_sums<WL, 64><<<grid(kBlock / 64), kBlock, 0, stream>>>(a);
+    return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+}
+
+int launch_index_build(const cs_params* p, uint32_t* index, hipStream_t stream) {
+    const IndexRows rows = index_rows(p);
+    const int rc = launch_bundle_zero(reinterpret_cast<float*>(index), static_cast<int64_t>(rows.words), stream);
+    if (rc != CS_OK) return rc;
+    const dim3 grid(2048, p->r), cells((p->c + kBlock - 1) / kBlock, p->r);
+    k_index_count<<<grid, kBlock, 0, stream>>>(kparams(p), rows, index);
+    k_index_scan<<<p->r, 1024, 0, stream>>>(kparams(p), rows, index);
+    k_index_fill<<<grid, kBlock, 0, stream>>>(kparams(p), rows, index);
+    k_index_sort<<<cells, kBlock, 0, stream>>>(p->c, rows, index);
+    return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+}
+
+// Groups of workers are taken as many at a time as the workspace holds; with one batch the merge and the momentum
+// come from it, else they read the tables afterwards.
+int launch_bundle_sketch(const cs_params* p, float* T, int W, const float* const* g_w, int64_t d, float scale,
+                         const uint32_t* index, float* ws, uint64_t ws_floats, float* S_t, float alpha,
+                         float* S_u, float* S_v, float rho, hipStream_t stream) {
+    const IndexRows rows = index_rows(p);
+    const int groups = (W + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP, lanes = sums_lanes(W);
+    const uint64_t table = static_cast<uint64_t>(p->r) * p->c * CS_BUNDLE_GROUP;
+    SumsPlan plan;
+    int rc = launch_accumulate_sums(p, nullptr, lanes, 0, nullptr, d, scale, plan, stream);
+    if (rc != CS_OK) return rc;
+    const uint64_t at_once = ws_floats / plan.floats;
+    if (at_once == 0) return CS_EWORKSPACE;
+    GatherArgs a{};
+    a.index = index;
+    a.sums = ws;
+    a.group_floats = plan.floats;
+    a.alpha = alpha;
+    a.rho = rho;
+    a.r = p->r;
+    a.c = p->c;
+    for (uint32_t j = 0; j < p->r; ++j) {
+        const SumsRow& s = plan.row[j];
+        a.row[j] = GatherRow{rows.at[j], s.at, s.piece_floats, static_cast<uint32_t>(s.residues), s.pieces, s.ncell, s.log_run};
+    }
+    for (int g0 = 0; g0 < groups; g0 += a.groups) {
+        a.groups = static_cast<uint64_t>(groups - g0) < at_once ? groups - g0 : static_cast<int>(at_once);
+        for (int g = g0; g < g0 + a.groups; ++g) {
+            const int w0 = g * CS_BUNDLE_GROUP, nw = W - w0 < CS_BUNDLE_GROUP ? W - w0 : CS_BUNDLE_GROUP;
+            rc = launch_accumulate_sums(p, ws + (g - g0) * plan.floats, lanes, nw, g_w + w0, d, scale, plan, stream);
+            if (rc != CS_OK) return rc;
+        }
+        a.T = T ? T + g0 * table : nullptr;
+        if (a.groups == groups) {
+            a.S_t = S_t;
+            a.S_u = S_u;
+            a.S_v = S_v;
+        }
+        switch (lanes) {
+            case 1: rc = launch_gather<1>(p, a, stream); break;
+            case 2: rc = launch_gather<2>(p, a, stream); break;
+            case 4: rc = launch_gather<4>(p, a, stream); break;
+            default: rc = launch_gather<8>(p, a, stream);
+        }
+        if (rc != CS_OK) return rc;
+        if (a.groups == groups) return CS_OK;
+    }
+    if (!S_t) return CS_OK;
+    const int64_t cells = static_cast<int64_t>(p->r) * p->c;
+    if (S_u) return launch_bundle_merge_momentum(S_t, S_u, S_v, T, groups, alpha, rho, cells, stream);
+    return launch_bundle_merge(S_t, 0.0f, T, groups, alpha, cells, stream);
+}
+
+bool params_ok(const cs_params* p) {
+    return p && p->r >= 1 && p->r <= CS_MAX_R && (p->r & 1u) && p->c >= 1 && p->c <= (1u << 31);
+}
+
+}  // namespace
+
+}  // namespace cs
+
+using namespace cs;
+
+// Where the two passes take less time than clearing, requests and merge (us, update with merge: requests / two passes):
+//  * up to 4 workers, where a request carries 4 to 16 bytes and costs what one of 32 does: 1 worker, d = 2 M, 5 x 65 536:
+//    65 / 32; 2 workers, 25 M, 5 x 2^19: 332 / 254; 2 workers, 100 M, 5 x 2^20: 936 / 791; 4 workers, 2^20, 5 x 2^15: 45 / 32;
+//    30 M, 5 x 2^18: 436 / 426; unless the vectors take long to read and the requests little beside that: 4 workers,
+//    16 M, 5 x 32 768 (requests 0.29 of the reads at 24 G/s and 5 TB/s): 251 / 273; 30 M, 5 x 65 536: 429 / 449;
+//  * up to 16 workers and short vectors, whose time is requests, and three launches where one does: 8 workers, d = 30 000,
+//    5 x 512: 21 / 14; 16 workers, 300 000, 5 x 4096: 47 / 38; 16 workers, 2^20, 5 x 2^15: 111 / 98; (8 workers, 700 000,
+//    7 x 2^14: 50 / 54); from 3 million on even (8 workers, 3 M: 106 / 109; 6.5 M: 200 / 201; 16 workers, 11 M: 641 / 651),
+//    and with many groups of workers behind (39 workers, 106 000, 5 x 4096: 138 / 152);
+//    (of 55 shapes with r d below 10 million and 1 to 16 workers two passes are ahead in 41, by up to 1.8 times, and at most
+//    14 % behind: 5 workers, 9170, 7 x 64: 15 / 17);
+//  * long vectors with tables that the memory-side cache does not hold beside them: 8 workers, 100 M, 5 x 2^20: 3284 / 3208;
+//    16 workers, 50 M, 5 x 2^19: 2963 / 2895; even at 25 M (1121 / 1118).
+// W = 0, a single vector into a table: against cs_sketch_zero and cs_sketch_accumulate, whose lattice form sends a request per
+// 8 to 15 coordinates.  Ahead from r d = 10 million on where the lists keep few sums: 5 x 65 536, d = 2.6 M, 0.14 sums per
+// coordinate and row: 51 / 33; 15 x 32 768, 1.3 M, 0.17: 112 / 75; 15 x 65 536, 1.8 M, 0.26: 101 / 144; 5 x 4096,
+// 460 000: 15 / 17.
+static bool sums_pay(const cs_params* p, int32_t W, int64_t d) {
+    double sums = 0.0;
+    for (uint32_t j = 0; j < p->r; ++j) sums += static_cast<double>(p->visit[j].ncell) * static_cast<double>(p->visit[j].gmax);
+    const double rd = static_cast<double>(p->r) * static_cast<double>(d);
+    if (W == 0) return rd >= 1e7 && sums <= 0.2 * rd;
+    if (W <= 4) {
+        const double read_ns = 4.0 * rd * W / 5000.0;
+        return read_ns < 1e5 || sums / 24.0 >= 0.33 * read_ns;
+    }
+    if (W <= 16 && rd <= 1e7) return true;
+    return W <= 64 && d >= 32'000'000 && static_cast<uint64_t>(p->r) * p->c * CS_BUNDLE_GROUP * sizeof(float) >= (64u << 20);
+}
+
+extern "C" int cs_update_index_bytes(const cs_params* p, int32_t W, int64_t d, size_t* bytes) {
+    if (!params_ok(p) || W < 0 || d < 0 || !bytes) return CS_EINVAL;
+    *bytes = sums_pay(p, W, d) && sums_apply(p, d) ? index_rows(p).words * sizeof(uint32_t) : 0;
+    return CS_OK;
+}
+
+extern "C" int cs_update_index_build(const cs_params* p, int64_t d, void* index, size_t bytes, void* stream) {
+    if (!params_ok(p) || d < 0 || !index || reinterpret_cast<uintptr_t>(index) % 4 != 0) return CS_EINVAL;
+    if (!sums_apply(p, d)) return CS_EINVAL;
+    if (bytes < index_rows(p).words * sizeof(uint32_t)) return CS_EWORKSPACE;
+    return launch_index_build(p, static_cast<uint32_t*>(index), static_cast<hipStream_t>(stream));
+}
+
+extern "C" int cs_update_workspace_bytes(const cs_params* p, int32_t W, int64_t d, size_t* bytes) {
+    if (!params_ok(p) || W < 1 || d < 0 || !bytes) return CS_EINVAL;
+    *bytes = 0;
+    if (!sums_apply(p, d)) return CS_OK;
+    SumsPlan plan;
+    const int rc = launch_accumulate_sums(p, nullptr, sums_lanes(W), 0, nullptr, d, 1.0f, plan, nullptr);
+    *bytes = plan.floats * sizeof(float) * ((W + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP);
+    return rc;
+}
+
+extern "C" int cs_bundle_sketch(const cs_params* p, float* T, int32_t W, const float* const* g_w, int64_t d,
+                                float scale, const void* index, size_t index_bytes, void* ws, size_t ws_bytes,
+                                float* S_t, float alpha, float* S_u, float* S_v, float rho, void* stream) {
+    int64_t floats;
+    int rc = cs_bundle_floats(p, W, &floats);
+    if (rc != CS_OK || d < 0 || !g_w || !index || !ws) return CS_EINVAL;
+    if ((!T && (W > CS_BUNDLE_GROUP || !S_t)) || (!S_u != !S_v) || (S_u && !S_t)) return CS_EINVAL;
+    for (int w = 0; w < W; ++w)
+        if (!g_w[w]) return CS_EINVAL;
+    if (reinterpret_cast<uintptr_t>(T) % 16 != 0 || reinterpret_cast<uintptr_t>(ws) % 16 != 0 ||
+        reinterpret_cast<uintptr_t>(index) % 4 != 0) return CS_EINVAL;
+    if (!sums_apply(p, d)) return CS_EINVAL;
+    if (index_bytes < index_rows(p).words * sizeof(uint32_t)) return CS_EWORKSPACE;
+    return launch_bundle_sketch(p, T, W, g_w, d, scale, static_cast<const uint32_t*>(index), static_cast<float*>(ws),
+                                ws_bytes / sizeof(float), S_t, alpha, S_u, S_v, rho, static_cast<hipStream_t>(stream));
+}

@@ -1,7 +1,8 @@
 """One pass of the hot path on one GPU: buffers and the order of library calls, nothing else.
 
 Per step (Alg. 3 of the paper, with the W workers simulated on the one device):
-    worker sketches   S^w = S(g^w)                cs_sketch_accumulate_bundle  (T[w/8][j][b][w%8])
+    worker sketches   S^w = S(g^w)                cs_bundle_sketch  (T[w/8][j][b][w%8]), with the next two steps; where
+                                                  the sketch has no lists cs_sketch_accumulate_bundle
     aggregate         S_t = (1/W) sum_w S^w       cs_bundle_merge[_momentum]
                       (fold_workers: S_t = S((1/W) sum_w g^w), cs_vectors_sum, cs_sketch_accumulate)
     momentum, error   S_u = rho S_u + S_t ; S_v += S_u      cs_sketch_momentum   (stateful only)
@@ -20,6 +21,11 @@ from . import binding as B
 
 
 class HotPath:
+    # the update by way of running sums (cs_bundle_sketch), where the sketch has lists for it: its index, its
+    # workspace, and whether that leaves room for the mean of folded workers
+    _index = _sums_ws = _sums_fold = None
+    SUMS_OWN_BYTES = 256 << 20           # a workspace of its own for them up to here
+
     def __init__(self, d: int, W: int, r: int, c: int, k: int, seed: int,
                  rho: float | None = None, device="cuda:0", P: int = 1, fold_workers: bool = False):
         """P > 1: the sketch is queried for the top P*k coordinates, the workers for their exact
@@ -62,6 +68,7 @@ class HotPath:
         self.g_mean = None
         if fold_workers and W > 1:
             self._mean_buffer(d)
+        self._build_index()
 
     # individual stages (bench.py times them separately) ---------------------------------
     def worker_table(self, w: int):
@@ -79,18 +86,58 @@ class HotPath:
                            else torch.empty(size, dtype=torch.float32, device=self.device))
         return self.g_mean[:n]
 
+    def _build_index(self):
+        n = B.cs_update_index_bytes(self.params, 0 if self.fold_workers else self.W, self.d)
+        if not n:
+            return
+        W = 1 if self.fold_workers else self.W
+        # the workspace is the query's scratch, free until the estimate, where that is large enough: all of it, or
+        # what the mean of folded workers leaves
+        need = B.cs_update_workspace_bytes(self.params, W, self.d)
+        skip = (4 * self.d + 255) // 256 * 256 if self.fold_workers else 0
+        fits = self.est_ws is not None and self.est_ws.numel() >= skip + need
+        if not fits and need > self.SUMS_OWN_BYTES:
+            return
+        self._sums_ws = self.est_ws[skip:] if fits else torch.empty(need, dtype=torch.uint8, device=self.device)
+        self._index = torch.empty(n, dtype=torch.uint8, device=self.device)
+        B.cs_update_index_build(self.params, self.d, self._index)
+        self._sums_fold = self.fold_workers
+
+    def _indexed(self, g_w):
+        """the vectors are those that the index and its workspace were made for"""
+        return (self._index is not None and self.fold_workers == self._sums_fold and g_w[0].numel() == self.d
+                and (self.fold_workers or len(g_w) == self.W))
+
+    def _mean(self, g_w):
+        """the mean of folded workers, in scratch"""
+        n = g_w[0].numel()
+        mean = self.g_mean
+        if mean is None or mean.numel() != n:
+            mean = self._mean_buffer(n)
+        B.cs_vectors_sum(g_w, mean, alpha=1.0 / self.W)
+        return mean
+
+    def _sketch_indexed(self, g_w, **tables):
+        """accumulate, and with the tables S_t (S_u, S_v) what follows it, in the pass that gathers the sums"""
+        if not self.fold_workers:
+            B.cs_bundle_sketch(self.params, self.T, g_w, self._index, self._sums_ws, alpha=1.0 / self.W, **tables)
+        elif len(g_w) == 1:
+            B.cs_bundle_sketch(self.params, None, g_w, self._index, self._sums_ws, 1.0 / self.W,
+                               **{"S_t": self.S_t, **tables})
+        else:
+            B.cs_bundle_sketch(self.params, None, [self._mean(g_w)], self._index, self._sums_ws,
+                               **{"S_t": self.S_t, **tables})
+
     def accumulate(self, g_w):
+        if self._index is not None and self._indexed(g_w):
+            self._sketch_indexed(g_w)
+            return
         if self.fold_workers:
             B.cs_sketch_zero(self.params, self.S_t)
             if len(g_w) == 1:
                 B.cs_sketch_accumulate(self.params, self.S_t, g_w[0], scale=1.0 / self.W)
-                return
-            n = g_w[0].numel()
-            mean = self.g_mean
-            if mean is None or mean.numel() != n:
-                mean = self._mean_buffer(n)
-            B.cs_vectors_sum(g_w, mean, alpha=1.0 / self.W)
-            B.cs_sketch_accumulate(self.params, self.S_t, mean)
+            else:
+                B.cs_sketch_accumulate(self.params, self.S_t, self._mean(g_w))
             return
         B.cs_bundle_zero(self.params, self.T, self.W)
         B.cs_sketch_accumulate_bundle(self.params, self.T, g_w)
@@ -152,12 +199,25 @@ class HotPath:
             return
         B.cs_bundle_merge_momentum(self.params, self.S_t, self.S_u, self.S_v, self.T, self.W, 1.0 / self.W, self.rho)
 
+    def _not_overridden(self, *stages):
+        cls, own = type(self), self.__dict__
+        return all(getattr(cls, x) is getattr(HotPath, x) and x not in own for x in stages)
+
+    def sketch_and_aggregate(self, g_w):
+        """accumulate, merge and momentum: the last two come out of the pass that writes the tables, where there
+        is one and no stage is overridden"""
+        if (self._index is not None and self._not_overridden("accumulate", "merge", "momentum", "aggregate")
+                and self._indexed(g_w)):
+            self._sketch_indexed(g_w, S_t=self.S_t, S_u=self.S_u, S_v=self.S_v, rho=self.rho or 0.0)
+            return
+        self.accumulate(g_w)
+        self.aggregate()
+
     def step(self, g_w):
         """g_w: list of W fp32[d] device tensors.  Returns (idx, x): chosen coordinates
         (ascending) and their exact mean over workers."""
         g_w = B.DeviceVectors(g_w, name="g_w")
-        self.accumulate(g_w)
-        self.aggregate()
+        self.sketch_and_aggregate(g_w)
         self.estimate()
         self.topk()
         self.gather(g_w)
@@ -179,6 +239,9 @@ class ReproduciblePath(HotPath):
                           cs_sketch_estimate_sparse, cs_fixed_accumulate_sparse, cs_sketch_axpby
     `dropped` counts the coordinates that were left out (not finite, or too large for the
     chosen frac_bits) since the object was made."""
+
+    def _build_index(self):
+        pass                                          # (its update is another)
 
     def __init__(self, d, W, r, c, k, seed, rho=None, device="cuda:0", frac_bits: int = 40):
         super().__init__(d, 1, r, c, k, seed, rho=rho, device=device)     # no bundle of W tables
@@ -238,8 +301,11 @@ class DenseStatePath(HotPath):
 
     def step(self, g_w):
         self.dense_momentum(g_w)
-        self.accumulate(self.v_w)
-        self.merge()
+        if self._indexed(self.v_w) and self._not_overridden("accumulate", "merge"):
+            self._sketch_indexed(self.v_w, S_t=self.S_t)
+        else:
+            self.accumulate(self.v_w)
+            self.merge()
         self.estimate()
         self.topk()
         self.gather(self.v_w)

@@ -1,0 +1,125 @@
+"""cs_bundle_sketch: the update by way of running sums that are gathered by cell, at the edges of its tiles."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_1903_04488_amd as cs
+from oracle import cs_oracle as orc
+from parity_util import assert_cells_close, sketch_in_slices
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+G = cs.CS_BUNDLE_GROUP
+P = (1 << 61) - 1
+
+
+def _index(p, d):
+    index = torch.empty(cs.cs_update_index_bytes(p, 1, d), dtype=torch.uint8, device=DEV)
+    cs.cs_update_index_build(p, d, index)
+    return index
+
+
+def _workspace(p, W, d, groups=None):
+    """for so many groups of 8 workers at a time"""
+    n = cs.cs_update_workspace_bytes(p, W, d)
+    return torch.empty(n if groups is None else n // -(-W // G) * groups, dtype=torch.uint8, device=DEV)
+
+
+@pytest.mark.parametrize("W,at_once", [(1, 1), (2, 1), (3, 1), (5, 1), (8, 1), (9, 1), (16, 2), (20, 2), (20, 3)])
+@pytest.mark.parametrize("r,c,d", [(5, 64, 4097), (5, 1 << 12, 255_999), (15, 1 << 12, 300_001),
+                                   (5, 1 << 15, 1_048_579), (5, 1 << 15, 3_200_003)])
+def test_tables_merge_and_momentum(W, at_once, r, c, d):
+    if r * d * W > 90_000_000:
+        pytest.skip("the long vectors are for three and four sums and the long runs of a walker")
+    p = cs.cs_params_init(r, c, 31, d)
+    sk = orc.SketchOracle(r, c, 31)
+    rng = np.random.default_rng(d + W)
+    gs = [(rng.standard_normal(d) * 0.01).astype(np.float32) for _ in range(W)]
+    dev = [torch.from_numpy(g).to(DEV) for g in gs]
+    index, ws = _index(p, d), _workspace(p, W, d, at_once)
+    f32 = dict(dtype=torch.float32, device=DEV)
+    T = torch.full((cs.cs_bundle_floats(p, W),), float("nan"), **f32)    # written whole, never read
+    ws.view(torch.float32).fill_(float("nan"))
+    S_t, S_u, S_v = torch.empty(r, c, **f32), torch.randn(r, c, **f32), torch.randn(r, c, **f32)
+    u0, v0 = S_u.double().cpu().numpy(), S_v.double().cpu().numpy()
+    cs.cs_bundle_sketch(p, T, dev, index, ws, scale=0.5, S_t=S_t, alpha=0.25, S_u=S_u, S_v=S_v, rho=0.75)
+    got = T.cpu().numpy().reshape(-1, r, c, G)
+    refs = [sketch_in_slices(sk, g, 0.5) for g in gs]
+    for w in range(W):
+        assert_cells_close(got[w // G, :, :, w % G], refs[w], terms_per_cell=d / c, what=f"worker {w}")
+    for w in range(W, got.shape[0] * G):
+        assert not got[w // G, :, :, w % G].any()
+    # what follows is computed from the tables: merged in binary64 and rounded once, then three roundings more
+    merged = 0.25 * np.sum([got[w // G, :, :, w % G].astype(np.float64) for w in range(W)], axis=0)
+    u = 0.75 * u0 + merged
+    bound = 4 * 2.0 ** -24 * (np.abs(merged) + np.abs(u0) + np.abs(v0))
+    for table, want in ((S_t, merged), (S_u, u), (S_v, v0 + u)):
+        assert (np.abs(table.cpu().numpy() - want) <= bound).all()
+    again = torch.empty_like(T)
+    cs.cs_bundle_sketch(p, again, dev, index, ws, scale=0.5)
+    torch.testing.assert_close(again, T, rtol=0, atol=0)                 # one order of additions
+    if W <= G:
+        only = torch.empty_like(S_t)
+        cs.cs_bundle_sketch(p, None, dev, index, ws, scale=0.5, S_t=only, alpha=0.25)
+        torch.testing.assert_close(only, S_t, rtol=0, atol=0)
+
+
+@pytest.mark.parametrize("W", [1, 2, 3, 8])
+@pytest.mark.parametrize("r,c,d", [(5, 1 << 12, 200_003), (3, 1 << 13, 400_003)])
+@pytest.mark.parametrize("below", [1, 0, -(1 << 28), 1 << 28])
+def test_hashes_at_the_thresholds(W, r, c, d, below):
+    """The bucket hash of a coordinate, and the sign hash of another, moved on by a visit to `below` short of p; a NaN
+    and infinities reach the r cells of their coordinates and no others."""
+    p = cs.cs_params_init(r, c, 43, d)
+    sk = orc.SketchOracle(r, c, 43)
+    g = (np.random.default_rng(W).standard_normal(d) * 0.01).astype(np.float32)
+    for j in range(r):
+        plan = p.visit[j]
+        k = plan.K // 2
+        s = sum(plan.gaps()[:k])
+        for i, own, consts in ((5, p.a[j], (p.b, sk.b)), (9, p.as_[j], (p.bs, sk.bs))):
+            for table in consts:                     # the free term puts that hash there
+                table[j] = (P - own * s - below - own * i) % P
+            g[i + s] = 1.0 + i
+    g[[17, d - 1]], g[100] = np.inf, np.nan
+    with np.errstate(invalid="ignore"):
+        ref = sk.sketch(g)
+    gs = [torch.zeros(d, dtype=torch.float32, device=DEV)] * (W - 1) + [torch.from_numpy(g).to(DEV)]
+    T = torch.empty(cs.cs_bundle_floats(p, W), dtype=torch.float32, device=DEV)
+    cs.cs_bundle_sketch(p, T, gs, _index(p, d), _workspace(p, W, d))
+    got = T.view(r, c, G)[:, :, W - 1].cpu().numpy()
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+    np.testing.assert_array_equal(np.where(np.isinf(got), got, 0), np.where(np.isinf(ref), ref, 0))
+    fin = np.isfinite(ref)
+    assert fin.sum() >= ref.size - 3 * r
+    assert_cells_close(np.where(fin, got, 0), np.where(fin, ref, 0), terms_per_cell=d / c)
+
+
+def test_what_is_refused():
+    r, c, d, W = 5, 1 << 12, 200_003, 3
+    p = cs.cs_params_init(r, c, 11, d)
+    g = [torch.zeros(d, dtype=torch.float32, device=DEV)] * W
+    T = torch.empty(cs.cs_bundle_floats(p, W), dtype=torch.float32, device=DEV)
+    index, ws = _index(p, d), _workspace(p, W, d)
+    short = dict(dtype=torch.uint8, device=DEV)
+    for bad in (dict(index=index[:-4]), dict(workspace=ws[:1024]), dict(workspace=torch.empty(ws.numel() + 4, **short)[4:]),
+                dict(T=None), dict(S_u=torch.zeros(r, c, device=DEV))):
+        with pytest.raises(cs.CsError):
+            cs.cs_bundle_sketch(p, **{"T": T, "g_w": g, "index": index, "workspace": ws, **bad})
+    # lists that do not keep a coordinate within its sums have no index: the visits' values have no place
+    forged = cs.CsParams.from_buffer_copy(p)
+    ctypes.memset(ctypes.byref(forged.visit[1]), 0, ctypes.sizeof(forged.visit[1]))
+    v = forged.visit[1]
+    v.K, v.ncell, v.cover, v.gmax, v.cost, v.cost_walk = 3, 2, d, d - 60_022, 1, 2
+    v.gap[0], v.gap[3], v.code[0] = 30_011, d - 60_022, 0b110000
+    assert cs.cs_update_index_bytes(forged, W, d) == 0 and cs.cs_update_workspace_bytes(forged, W, d) == 0
+    with pytest.raises(cs.CsError):
+        cs.cs_bundle_sketch(forged, T, g, index, ws)
+    for other in ((7, 40, 784), (3, 5001, 400_003), (5, 1 << 12, 1000)):
+        p = cs.cs_params_init(other[0], other[1], 1, other[2])
+        assert cs.cs_update_index_bytes(p, 1, other[2]) == 0
+        with pytest.raises(cs.CsError):
+            cs.cs_bundle_sketch(p, torch.empty(cs.cs_bundle_floats(p, 1), dtype=torch.float32, device=DEV),
+                                [torch.zeros(other[2], device=DEV)], index, ws)
