@@ -333,6 +333,9 @@ int cs_sketch_momentum(const cs_params* p, float* S_u, float* S_v, const float* 
  * size is 0).  */
 #define CS_TOPK_HIST_BINS 2048
 int cs_estimate_workspace_bytes(const cs_params* p, int64_t d, size_t* bytes);
+/* Scratch with which the query is fastest: what cs_estimate_workspace_bytes says it needs, or, where it needs none
+ * but would use some (other column counts than powers of two, vectors of middling length), that. */
+int cs_estimate_scratch_bytes(const cs_params* p, int64_t d, size_t* bytes);
 int cs_sketch_estimate(const cs_params* p, const float* S, int64_t d, int64_t i0,
                        float* est, uint64_t* hist_or_null, void* rows_ws, size_t ws_bytes,
                        void* stream);

@@ -130,6 +130,8 @@ _SIGNATURES = {
                            ctypes.c_void_p, ctypes.c_float, ctypes.c_void_p],
     "cs_estimate_workspace_bytes": [ctypes.POINTER(CsParams), ctypes.c_int64,
                                     ctypes.POINTER(ctypes.c_size_t)],
+    "cs_estimate_scratch_bytes": [ctypes.POINTER(CsParams), ctypes.c_int64,
+                                  ctypes.POINTER(ctypes.c_size_t)],
     "cs_sketch_estimate": [ctypes.POINTER(CsParams), ctypes.c_void_p, ctypes.c_int64,
                            ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
                            ctypes.c_size_t, ctypes.c_void_p],
@@ -439,6 +441,12 @@ def _hist(hist):
     if hist is None:
         return ctypes.c_void_p(0)
     return _dev(hist, torch.int64, "hist", CS_TOPK_HIST_BINS)
+
+
+def cs_estimate_scratch_bytes(p, d: int) -> int:
+    n = ctypes.c_size_t()
+    _check(load_library().cs_estimate_scratch_bytes(ctypes.byref(p), d, ctypes.byref(n)), "cs_estimate_scratch_bytes")
+    return n.value
 
 
 def cs_sketch_estimate(p, S, est, i0: int = 0, workspace=None, hist=None):

@@ -76,11 +76,12 @@ int launch_accumulate_sums(const cs_params* p, float* sums, int lanes, int nw, c
 // the same along visit lists for column counts that are not a power of two
 bool anyc_visits_apply(const cs_params* p, int64_t d);
 bool anyc_visits_serve_query(const cs_params* p, int64_t d);
+bool anyc_query_needs_scratch(const cs_params* p, int64_t d);    // ... and is the only form for this length
 int launch_accumulate_anyc(const cs_params* p, float* T, int W, const float* const* g_w,
                            int64_t d, int64_t i0, float scale, bool fold, hipStream_t stream);
 int count_accumulate_anyc_launches(const cs_params* p, int W);
 int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t i0, float* est,
-                         float* rows, hipStream_t stream);
+                         float* rows, uint64_t* hist, hipStream_t stream);
 int launch_estimate_walk(const cs_params* p, const float* S, int64_t d, int64_t i0,
                          float* est, float* rows, bool fuse_last, uint64_t* hist, hipStream_t stream);
 int launch_bundle_zero(float* T, int64_t n, hipStream_t stream);

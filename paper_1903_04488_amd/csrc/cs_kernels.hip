@@ -1033,9 +1033,16 @@ extern "C" int cs_sketch_momentum(const cs_params* p, float* S_u, float* S_v, co
 extern "C" int cs_estimate_workspace_bytes(const cs_params* p, int64_t d, size_t* bytes) {
     if (!params_ok(p) || d < 0 || !bytes) return CS_EINVAL;
     // the stride-aligned path stores the r signed cells of every coordinate before the median
-    *bytes = (lattice_applies(p, d) || anyc_visits_serve_query(p, d))
+    *bytes = (lattice_applies(p, d) || anyc_query_needs_scratch(p, d))
                  ? sizeof(float) * static_cast<size_t>(p->r) * static_cast<size_t>(d) : 0;
     return CS_OK;
+}
+
+extern "C" int cs_estimate_scratch_bytes(const cs_params* p, int64_t d, size_t* bytes) {
+    const int rc = cs_estimate_workspace_bytes(p, d, bytes);
+    if (rc == CS_OK && *bytes == 0 && anyc_visits_serve_query(p, d))
+        *bytes = sizeof(float) * static_cast<size_t>(p->r) * static_cast<size_t>(d);
+    return rc;
 }
 
 static int estimate_all(const cs_params* p, const float* S, int64_t d, int64_t i0, float* est,
@@ -1054,9 +1061,11 @@ static int estimate_all(const cs_params* p, const float* S, int64_t d, int64_t i
     };
     if (anyc_visits_serve_query(p, d)) {
         const size_t need = sizeof(float) * static_cast<size_t>(p->r) * static_cast<size_t>(d);
-        if (!rows_ws || reinterpret_cast<uintptr_t>(rows_ws) % 4 != 0) return CS_EINVAL;
-        if (ws_bytes < need) return CS_EWORKSPACE;
-        return counted(launch_estimate_anyc(p, S, d, i0, est, static_cast<float*>(rows_ws), as_stream(stream)));
+        const bool room = rows_ws && reinterpret_cast<uintptr_t>(rows_ws) % 4 == 0 && ws_bytes >= need;
+        if (room) return launch_estimate_anyc(p, S, d, i0, est, static_cast<float*>(rows_ws), hist, as_stream(stream));
+        // (shorter vectors go without scratch as well)
+        if (anyc_query_needs_scratch(p, d))
+            return !rows_ws || reinterpret_cast<uintptr_t>(rows_ws) % 4 != 0 ? CS_EINVAL : CS_EWORKSPACE;
     }
     const unsigned grid = grid_for(d, kBlock * 8, 256 * 8);
 #define CALL(R_, P2_) \

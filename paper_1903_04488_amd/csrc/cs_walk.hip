@@ -1352,11 +1352,17 @@ bool anyc_visits_apply(const cs_params* p, int64_t d) {
     return true;
 }
 
-// The query follows the lists when there is enough of it: one launch per row with short chains
-// of visits loses to r gathers per coordinate on small inputs (measured: 5 rows over 6.5 M
-// coordinates 0.19 against 0.15 ms, 15 rows over 6.5 M 0.59 against 0.90 ms).
+// The query follows the lists where its r launches are worth it. Below d = 1.5 million they are not (us of
+// the query of one vector, r gathers per coordinate against the lists: 0.7M x 15 rows 60 / 99, 2M x 5 rows
+// 62 / 52, 2M x 15 rows 145 / 116, 4M x 5 rows 101 / 58, 6.5M x 5 rows 149 / 85, 2.2M x 3 rows 50 / 31; the
+// shortest with narrow tables about even: 2.1M x 3 rows of 9001 columns, lists of up to 135 visits, 43 / 46).
 bool anyc_visits_serve_query(const cs_params* p, int64_t d) {
-    return anyc_visits_apply(p, d) && d * static_cast<int64_t>(p->r - 1) >= (static_cast<int64_t>(1) << 26);
+    return anyc_visits_apply(p, d) && d >= 3 * (static_cast<int64_t>(1) << 19) &&
+           d * static_cast<int64_t>(p->r - 1) >= (static_cast<int64_t>(1) << 22);
+}
+// Up to here r gathers per coordinate do as well where the caller has no scratch.
+bool anyc_query_needs_scratch(const cs_params* p, int64_t d) {
+    return anyc_visits_serve_query(p, d) && d * static_cast<int64_t>(p->r - 1) >= (static_cast<int64_t>(1) << 26);
 }
 
 int count_accumulate_anyc_launches(const cs_params* p, int W) {
@@ -1859,173 +1865,172 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
 //
 // The list that serves the update serves the query: whatever a lane meets at i + s_k lies in
 // one of the NC = 2 omega cells that the cell of i fixes, so the lane fetches those NC cell
-// values once, keeps them in registers, and for the rest of the vector picks one of them per
-// visit -- no gather inside the loop.  (Without a list the query is r random gathers per
-// coordinate from a table that L2 does not hold: ~80 G gathers/s.  For power-of-two column
-// counts the stride walk above does the same job faster than this kernel's form with three
-// gaps: both are then bound by their hashing and the walk balances its load better.)
+// values once, with the sign of i, keeps them in registers, and for the rest of the vector picks one of them per
+// visit by the two comparisons of the update -- no gather and no hash inside the loop.  (Without a list the query is r
+// random gathers per coordinate from a table that L2 does not hold: ~80 G gathers/s.  For power-of-two column
+// counts the stride walk above does the same job and balances its load better.)
 // A lane owns 4 neighbouring residues below the largest gap, a wavefront 256, and every visit
 // writes 1 KB of contiguous rows[j][i] (RF = 0) or, for the last row (RF = R), reads the other
-// rows' values there, takes the median and writes est.  A coordinate outside the NC cells
-// cannot occur with a list from cs_params_init; it is checked all the same and such a value
-// is gathered from the table directly.
+// rows' values there, takes the median and writes est, with HIST counted by magnitude as in the stride walk.  A
+// coordinate outside the NC cells cannot occur with a list from cs_params_init; such visits (and those that the
+// comparisons cannot tell) are hashed by the definition, value by value, and gathered from the table.
+// What bounds it is the scratch: r - 1 rows written and read, est written.  With two 61-bit hash states per
+// residue moved on at each visit, and the counts of magnitudes in a pass of their own, the query took 2960 us for
+// 15 rows of 90 M (10.4 GB of traffic: 1.7 ms at 6.2 TB/s) and 744 us for 5 rows of 73 M; now 2691 and 651.
 // ---------------------------------------------------------------------------------------
-template <int RF, int NC>
-__global__ void __launch_bounds__(64)
+constexpr int kQueryWaves = 4;                         // wavefronts per workgroup: one table of visits, one set of counters
+template <int RF, int NC, bool HIST>
+__global__ void __launch_bounds__(64 * kQueryWaves)
 k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, int64_t d, int64_t i0,
-                    float* __restrict__ rows, float* __restrict__ est, int nseg) {
+                    float* __restrict__ rows, float* __restrict__ est, unsigned long long* __restrict__ hist, int nseg) {
     static_assert(kQRun == 4, "one 16-byte piece per lane");
     static_assert(NC == 2 || NC == 4, "omega = 1 or 2");
-    const int lane = threadIdx.x;
+    static_assert(!HIST || RF > 0, "only the kernel that writes est can count it");
+    const int lane = threadIdx.x & 63;
+    const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const VisitGaps& v = vr.row[blockIdx.y];           // the rows of a launch run side by side
     const int j = v.j;
-    // hash advances of the visits, (a_j gap_k) mod p and (a'_j gap_k) mod p: computed here once
-    // per wavefront instead of travelling with the list
-    __shared__ uint64_t A_of[CS_ANYC_MAX_VISITS], As_of[CS_ANYC_MAX_VISITS];
-    __shared__ uint32_t Ac_of[CS_ANYC_MAX_VISITS];     // A_of[k] mod c
-    const Columns colc = columns_of<false>(c);
-    for (uint32_t k = lane; k < v.K; k += 64) {
-        const uint64_t A = mulmod_p(v.a, v.gap[k]);
-        A_of[k] = A;
-        As_of[k] = mulmod_p(v.as, v.gap[k]);
-        Ac_of[k] = bucket_of<false>(A + 1, colc);     // bucket_of takes the y form, x + 1
-    }
-    __syncthreads();
+    // the counters that a later kernel of the query adds to are cleared here: a launch less
+    if (RF == 0 && hist && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+        for (int t = threadIdx.x; t < 2048; t += 64 * kQueryWaves) hist[t] = 0;
+    __shared__ uint32_t lh[HIST ? 2048 : 1];
+    if (HIST)
+        for (int t = threadIdx.x; t < 2048; t += 64 * kQueryWaves) lh[t] = 0;
+    auto tally = [&](float x) {
+        if (HIST) atomicAdd(&lh[(__float_as_uint(x) & 0x7fffffffu) >> 20], 1u);
+    };
+    __shared__ uint4 steps[CS_ANYC_MAX_VISITS];
     const Columns col = columns_of<false>(c);
     const float* __restrict__ Sj = S + static_cast<size_t>(j) * c;
     float* __restrict__ out = rows + static_cast<size_t>(j) * d;
-    const uint64_t Aj = v.a, Asj = v.as;
     const uint32_t omega = v.omega, pc = v.pc;
-    auto sum_of = [&](uint32_t cell, uint32_t first) -> uint32_t {
-        const uint32_t t = cell >= first ? cell - first : cell + c - first;
-        if (t < omega) return t;
-        const uint32_t t2 = t + pc >= c ? t + pc - c : t + pc;
-        return t2 < omega ? omega + t2 : static_cast<uint32_t>(NC);
-    };
-    auto cell_of_sum = [&](uint32_t first, int q) -> uint32_t {
-        const uint32_t x = static_cast<uint32_t>(q) < omega ? first + q : first + (q - omega) + (c - pc);
+    auto cell_of_sum = [&](uint32_t first, uint32_t q) -> uint32_t {
+        const uint32_t x = q < omega ? first + q : first + (q - omega) + (c - pc);
         return x >= c ? x - c : x;
     };
-    // The bucket x mod c is carried along with the hash value instead of being taken again by a
-    // 64-bit remainder at every coordinate: when x moves on by A (mod p), x mod c moves on by
-    // A mod c, less p mod c if x wrapped past p.  All terms are below c <= 2^31, so the sums
-    // stay below 2^32.  Exact, like the hash state itself.
-    const uint32_t Ajc = bucket_of<false>(Aj + 1, colc);          // a_j mod c
-    auto advance = [&](uint64_t& y, uint32_t& rem, uint64_t A, uint32_t Ac) {
-        const uint64_t t = y + A;
-        const bool wrapped = (t >> 61) != 0;
-        y = (t & kP61) + (t >> 61);
-        uint32_t u = rem + Ac;
-        u = u >= c ? u - c : u;
-        const uint32_t u2 = u + (c - pc);
-        rem = !wrapped ? u : (u2 >= c ? u2 - c : u2);
-    };
+    // A launch with few rows leaves the chip half empty and waits on its longest chain of
+    // visits, so the chains are cut into nseg pieces walked by separate workgroups (blockIdx.z).
+    const uint32_t k0 = v.K * blockIdx.z / nseg, k1 = v.K * (blockIdx.z + 1) / nseg;
+    VisitPlaces places;
+    places.init(v);
+    fill_visit_steps<false, kQueryWaves>(steps, places, v, k0, k1, col, omega);          // (a barrier in it: lh is clear)
+    const uint32_t d32 = static_cast<uint32_t>(d);
     const int64_t nwaves = (static_cast<int64_t>(v.gmax) + 64 * kQRun - 1) / (64 * kQRun);
-    const int64_t per_xcd = (nwaves + 7) / 8;
+    const int64_t nsets = (nwaves + kQueryWaves - 1) / kQueryWaves;
+    const int64_t per_xcd = (nsets + 7) / 8;
     const int64_t xcd_first = static_cast<int64_t>(blockIdx.x & 7) * per_xcd;
     for (int64_t kk = blockIdx.x >> 3; kk < per_xcd; kk += gridDim.x >> 3) {
-        const int64_t wv = xcd_first + kk;
-        if (wv >= nwaves) break;
-        const int64_t wave_res = wv * 64 * kQRun;                   // first residue of the wavefront
-        const int64_t my_res = wave_res + static_cast<int64_t>(lane) * kQRun;
-        uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
-        uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res));
-        uint32_t rb = bucket_of<false>(yb, col);                    // bucket of my first coordinate
-        uint32_t first_cell[kQRun];
+        const int64_t wv = (xcd_first + kk) * kQueryWaves + wq;
+        if (xcd_first + kk >= nsets || wv >= nwaves) break;
+        const uint32_t wave_res = static_cast<uint32_t>(wv * 64 * kQRun);    // first residue of the wavefront
+        const uint32_t my_res = wave_res + lane * kQRun;
+        uint32_t xb[kQRun], xs[kQRun];                 // top bits of the hashes at my residues
         float cellv[kQRun][NC];
         {
-            uint64_t tb = yb;
-            uint32_t tr = rb;
+            uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
+            uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res));
 #pragma unroll
             for (int m = 0; m < kQRun; ++m) {
-                first_cell[m] = tr;
+                xb[m] = top_of(yb);
+                xs[m] = top_of(ys);
+                const uint32_t first = bucket_of<false>(yb, col);
 #pragma unroll
-                for (int n = 0; n < NC; ++n) cellv[m][n] = Sj[cell_of_sum(first_cell[m], n)];
-                advance(tb, tr, Aj, Ajc);
+                for (int n = 0; n < NC; ++n) cellv[m][n] = apply_sign(Sj[cell_of_sum(first, n)], sign_flip_of(ys));
+                yb = hash_advance(yb, v.a);
+                ys = hash_advance(ys, v.as);
             }
         }
-        // A launch with few rows leaves the chip half empty and waits on its longest chain of
-        // visits, so the chains are cut into nseg pieces walked by separate wavefronts
-        // (blockIdx.z); a piece that does not start at visit 0 takes its hash state from the
-        // definition at its first coordinate (the cells it can meet are still those of visit 0).
-        const uint32_t k0 = v.K * blockIdx.z / nseg, k1 = v.K * (blockIdx.z + 1) / nseg;
-        int64_t s = 0;
-        if (k0 > 0) {
-            for (uint32_t k = 0; k < k0; ++k) s += static_cast<int64_t>(v.gap[k]);
-            yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res + s));
-            ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res + s));
-            rb = bucket_of<false>(yb, col);
-        }
-        for (uint32_t k = k0; k < k1; ++k) {
-            const int64_t gap = static_cast<int64_t>(v.gap[k]);
+        for (uint32_t k = 0; k < k1 - k0; ++k) {
+            const uint4 e = steps[k];
+            const uint32_t s = __builtin_amdgcn_readfirstlane(e.z), w = __builtin_amdgcn_readfirstlane(e.w);
+            if ((w & kGapMask) <= wave_res || s + wave_res >= d32) continue;
             // residues from wave_res on that take part in this visit and exist in the vector
-            const int64_t in_gap = gap - wave_res, in_vec = d - s - wave_res;
-            const int64_t room = in_gap < in_vec ? in_gap : in_vec;
-            if (room > 0) {
-                const int64_t my_len = room - static_cast<int64_t>(lane) * kQRun;   // of my 4: >= 4 all, <= 0 none
-                [[maybe_unused]] vec4f other[RF > 1 ? RF - 1 : 1];
-                if constexpr (RF > 1) {
-                    if (my_len >= kQRun) {
+            const uint32_t in_gap = (w & kGapMask) - wave_res, in_vec = d32 - s - wave_res;
+            const int my_len = static_cast<int>(in_gap < in_vec ? in_gap : in_vec) - lane * kQRun;    // of my 4: >= 4 all, <= 0 none
+            const size_t at = static_cast<size_t>(s) + my_res;
+            [[maybe_unused]] vec4f other[RF > 1 ? RF - 1 : 1];
+            if constexpr (RF > 1) {
+                if (my_len >= kQRun) {
 #pragma unroll
-                        for (int q = 0; q < RF - 1; ++q)
-                            other[q] = __builtin_nontemporal_load(reinterpret_cast<const vec4f_u*>(
-                                rows + static_cast<size_t>(q) * d + s + my_res));
-                    }
+                    for (int q = 0; q < RF - 1; ++q)
+                        other[q] = __builtin_nontemporal_load(reinterpret_cast<const vec4f_u*>(
+                            rows + static_cast<size_t>(q) * d + at));
                 }
-                uint64_t tb = yb, ts = ys;
-                uint32_t tr = rb;
-                float o[kQRun];
+            }
+            bool flip[kQRun], wrap[kQRun], unsure = false;
+#pragma unroll
+            for (int m = 0; m < kQRun; ++m) {
+                flip[m] = xs[m] > e.y;
+                wrap[m] = xb[m] > e.x;
+                unsure |= xb[m] == e.x || xs[m] == e.y;
+            }
+            const bool odd = (w >> 29 & 1u) != 0, second = NC > 2 && w >> 30 == 1u;
+            float o[kQRun];
+#pragma unroll
+            for (int m = 0; m < kQRun; ++m) {
+                float plain = cellv[m][0], wrapped = cellv[m][NC / 2];
+                if (NC > 2) {
+                    plain = second ? cellv[m][NC / 2 - 1] : plain;
+                    wrapped = second ? cellv[m][NC - 1] : wrapped;
+                }
+                const float x = wrap[m] ? wrapped : plain;
+                o[m] = flip[m] != odd ? -x : x;
+            }
+            if (w >> 30 == 3u || __builtin_amdgcn_ballot_w64(unsure) != 0) {
+                uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0) + at);
+                uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0) + at);
 #pragma unroll
                 for (int m = 0; m < kQRun; ++m) {
-                    const uint32_t cell = tr;
-                    const uint32_t rel = sum_of(cell, first_cell[m]);
-                    float x = cellv[m][NC - 1];
-#pragma unroll
-                    for (int n = NC - 2; n >= 0; --n) x = rel == static_cast<uint32_t>(n) ? cellv[m][n] : x;
-                    if (rel >= static_cast<uint32_t>(NC) && m < my_len) x = Sj[cell];
-                    o[m] = apply_sign(x, sign_flip_of(ts));
-                    advance(tb, tr, Aj, Ajc);
-                    ts = hash_advance(ts, Asj);
-                }
-                if constexpr (RF > 0) {
-                    float* dst = est + s + my_res;
-                    if (my_len >= kQRun) {
-                        float vx[RF], vy[RF], vz[RF], vw[RF];
-#pragma unroll
-                        for (int q = 0; q < RF - 1; ++q) {
-                            vx[q] = other[q].x; vy[q] = other[q].y; vz[q] = other[q].z; vw[q] = other[q].w;
-                        }
-                        vx[RF - 1] = o[0]; vy[RF - 1] = o[1]; vz[RF - 1] = o[2]; vw[RF - 1] = o[3];
-                        vec4f u;
-                        u.x = median_odd<RF>(vx); u.y = median_odd<RF>(vy);
-                        u.z = median_odd<RF>(vz); u.w = median_odd<RF>(vw);
-                        __builtin_nontemporal_store(u, reinterpret_cast<vec4f_u*>(dst));
-                    } else {
-                        for (int m = 0; m < kQRun; ++m) {
-                            if (m >= my_len) break;
-                            float t[RF];
-#pragma unroll
-                            for (int q = 0; q < RF - 1; ++q) t[q] = rows[static_cast<size_t>(q) * d + s + my_res + m];
-                            t[RF - 1] = o[m];
-                            dst[m] = median_odd<RF>(t);
-                        }
-                    }
-                } else {
-                    float* dst = out + s + my_res;
-                    if (my_len >= kQRun) {
-                        vec4f u;
-                        u.x = o[0]; u.y = o[1]; u.z = o[2]; u.w = o[3];
-                        __builtin_nontemporal_store(u, reinterpret_cast<vec4f_u*>(dst));
-                    } else if (my_len > 0) {
-                        dst[0] = o[0];
-                        if (my_len > 1) dst[1] = o[1];
-                        if (my_len > 2) dst[2] = o[2];
-                    }
+                    if (m < my_len) o[m] = apply_sign(Sj[bucket_of<false>(yb, col)], sign_flip_of(ys));
+                    yb = hash_advance(yb, v.a);
+                    ys = hash_advance(ys, v.as);
                 }
             }
-            s += gap;
-            advance(yb, rb, A_of[k], Ac_of[k]);
-            ys = hash_advance(ys, As_of[k]);
+            if constexpr (RF > 0) {
+                float* dst = est + at;
+                if (my_len >= kQRun) {
+                    float vx[RF], vy[RF], vz[RF], vw[RF];
+#pragma unroll
+                    for (int q = 0; q < RF - 1; ++q) {
+                        vx[q] = other[q].x; vy[q] = other[q].y; vz[q] = other[q].z; vw[q] = other[q].w;
+                    }
+                    vx[RF - 1] = o[0]; vy[RF - 1] = o[1]; vz[RF - 1] = o[2]; vw[RF - 1] = o[3];
+                    vec4f u;
+                    u.x = median_odd<RF>(vx); u.y = median_odd<RF>(vy);
+                    u.z = median_odd<RF>(vz); u.w = median_odd<RF>(vw);
+                    __builtin_nontemporal_store(u, reinterpret_cast<vec4f_u*>(dst));
+                    tally(u.x); tally(u.y); tally(u.z); tally(u.w);
+                } else {
+                    for (int m = 0; m < kQRun; ++m) {
+                        if (m >= my_len) break;
+                        float t[RF];
+#pragma unroll
+                        for (int q = 0; q < RF - 1; ++q) t[q] = rows[static_cast<size_t>(q) * d + at + m];
+                        t[RF - 1] = o[m];
+                        const float med = median_odd<RF>(t);
+                        dst[m] = med;
+                        tally(med);
+                    }
+                }
+            } else {
+                float* dst = out + at;
+                if (my_len >= kQRun) {
+                    vec4f u;
+                    u.x = o[0]; u.y = o[1]; u.z = o[2]; u.w = o[3];
+                    __builtin_nontemporal_store(u, reinterpret_cast<vec4f_u*>(dst));
+                } else if (my_len > 0) {
+                    dst[0] = o[0];
+                    if (my_len > 1) dst[1] = o[1];
+                    if (my_len > 2) dst[2] = o[2];
+                }
+            }
+        }
+    }
+    if (HIST) {
+        __syncthreads();
+        for (int t = threadIdx.x; t < 2048; t += 64 * kQueryWaves) {
+            const uint32_t n = lh[t];
+            if (n) atomicAdd(&hist[t], static_cast<unsigned long long>(n));
         }
     }
 }
@@ -2036,14 +2041,22 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
 // up to kAnycRowsPerLaunch rows per launch (one row's wavefronts alone fill a third to two
 // thirds of the chip, and every launch has the tail of its longest chain of visits), then the
 // last row together with the median.  The rows of a launch use the same number of cells.
+// hist (or null): cleared, and receives the counts of est by magnitude bin
 int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t i0, float* est,
-                         float* rows, hipStream_t stream) {
+                         float* rows, uint64_t* hist, hipStream_t stream) {
+    unsigned long long* h = reinterpret_cast<unsigned long long*>(hist);
+    if (h && p->r == 1) {                              // (no kernel of rows 0 .. r-2 clears them)
+        const int rc = launch_magnitude_hist_zero(hist, stream);
+        if (rc != CS_OK) return rc;
+    }
     auto grid_x = [](uint64_t gmax) {
-        const int64_t nwaves = (static_cast<int64_t>(gmax) + 64 * kQRun - 1) / (64 * kQRun);
-        const int64_t cap = 256 * 64;
-        const int64_t gx = nwaves < cap ? nwaves : cap;
+        const int64_t span = 64 * kQRun * kQueryWaves;
+        const int64_t nsets = (static_cast<int64_t>(gmax) + span - 1) / span;
+        const int64_t cap = 256 * 64 / kQueryWaves;
+        const int64_t gx = nsets < cap ? nsets : cap;
         return static_cast<unsigned>((gx + 7) / 8 * 8);
     };
+    unsigned long long* clear = h;                     // by the first launch
     // pieces per chain of a launch: enough wavefronts for about two per SIMD slot of the chip,
     // at least 8 visits per piece
     auto pieces = [](uint64_t waves, uint32_t shortest_list) {
@@ -2066,8 +2079,9 @@ int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t 
         }
         const unsigned nseg = pieces(waves, shortest);
         const dim3 grid(grid_x(most), static_cast<unsigned>(n), nseg);
-        if (omega == 1) k_row_values_visits<0, 2><<<grid, 64, 0, stream>>>(vr, S, p->c, d, i0, rows, est, static_cast<int>(nseg));
-        else k_row_values_visits<0, 4><<<grid, 64, 0, stream>>>(vr, S, p->c, d, i0, rows, est, static_cast<int>(nseg));
+        if (omega == 1) k_row_values_visits<0, 2, false><<<grid, 64 * kQueryWaves, 0, stream>>>(vr, S, p->c, d, i0, rows, est, clear, static_cast<int>(nseg));
+        else k_row_values_visits<0, 4, false><<<grid, 64 * kQueryWaves, 0, stream>>>(vr, S, p->c, d, i0, rows, est, clear, static_cast<int>(nseg));
+        clear = nullptr;
         return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
     });
     if (rc != CS_OK) return rc;
@@ -2075,16 +2089,21 @@ int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t 
     const uint32_t omega_last = p->anyc[last].omega;
     const unsigned nseg_last = pieces((p->anyc[last].gmax + 64 * kQRun - 1) / (64 * kQRun), p->anyc[last].K);
     const dim3 gx(grid_x(p->anyc[last].gmax), 1, nseg_last);
+#define CS_LASTQ(R_, NC_, H_) \
+    k_row_values_visits<R_, NC_, H_><<<gx, 64 * kQueryWaves, 0, stream>>>(vr, S, p->c, d, i0, rows, est, h, static_cast<int>(nseg_last))
 #define CS_LASTR(R_)                                                                                 \
     case R_:                                                                                         \
-        if (omega_last == 1) k_row_values_visits<R_, 2><<<gx, 64, 0, stream>>>(vr, S, p->c, d, i0, rows, est, static_cast<int>(nseg_last)); \
-        else k_row_values_visits<R_, 4><<<gx, 64, 0, stream>>>(vr, S, p->c, d, i0, rows, est, static_cast<int>(nseg_last));             \
+        if (omega_last == 1 && h) CS_LASTQ(R_, 2, true);                                             \
+        else if (omega_last == 1) CS_LASTQ(R_, 2, false);                                            \
+        else if (h) CS_LASTQ(R_, 4, true);                                                           \
+        else CS_LASTQ(R_, 4, false);                                                                 \
         break;
     switch (p->r) {
         CS_LASTR(1) CS_LASTR(3) CS_LASTR(5) CS_LASTR(7) CS_LASTR(9) CS_LASTR(11) CS_LASTR(13) CS_LASTR(15)
         default: return CS_EINVAL;
     }
 #undef CS_LASTR
+#undef CS_LASTQ
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 

@@ -62,7 +62,7 @@ class HotPath:
                                    device=self.device)
         B.cs_topk_workspace_clear(self.topk_ws)      # once: every selection leaves it clear
         self._counts = torch.zeros(B.CS_TOPK_HIST_BINS, dtype=torch.int64, device=self.device)
-        n_est = B.cs_estimate_workspace_bytes(self.params, d)
+        n_est = B.cs_estimate_scratch_bytes(self.params, d)
         self.est_ws = (torch.empty(n_est, dtype=torch.uint8, device=self.device)
                        if n_est else None)
         self.g_mean = None
