@@ -1713,10 +1713,14 @@ namespace {
 constexpr int kQRun = 4;
 
 // A short vector leaves a row with few chunks (Dw / 256 wavefronts) and a long serial chain
-// of visits each; the chain is then cut into segments that separate wavefronts walk
-// (blockIdx.z), at the price of one more gather per lane and segment.
+// of visits each; the chain is then cut into n segments that separate wavefronts walk, at the price of one more gather
+// per lane and segment.  Row j has the workgroups first[j] .. first[j] + n[j] across[j] - 1 of a launch of rows 0 ..
+// (the strides of one sketch differ by a factor of 300, so that a grid of (most chunks, rows, most segments) is nearly all
+// empty workgroups, which start at 4 to 5 a nanosecond: 68 800 of 5 x 2^15 at d = 2^20, where 10 000 have work).
 struct RowSegments {
     int n[CS_MAX_R];
+    uint32_t across[CS_MAX_R];   // a multiple of 8: blockIdx.x & 7 stays the XCD
+    uint32_t first[CS_MAX_R];    // ~0: no such row
 };
 
 // RF = 0: rows[j][i] for the rows j = blockIdx.y.  RF = R (the row count): the walk of the last
@@ -1739,11 +1743,15 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
     constexpr int NW = HIST ? kHistWaves : 1;          // wavefronts per workgroup
     const int lane = threadIdx.x & 63;
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j = RF ? RF - 1 : blockIdx.y;
+    int j = RF ? RF - 1 : 0;
+    if (RF == 0)
+#pragma unroll
+        for (int q = 1; q < CS_MAX_R; ++q) j += blockIdx.x >= segs.first[q] ? 1 : 0;
     const int nseg = segs.n[j];
-    if (static_cast<int>(blockIdx.z) >= nseg) return;
+    const uint32_t block = blockIdx.x - (RF ? 0u : segs.first[j]), across = RF ? gridDim.x / nseg : segs.across[j];
+    const uint32_t seg = block / across, bx = block % across;
     // the counters that a later kernel of the query adds to are cleared here: a launch less
-    if (RF == 0 && hist && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+    if (RF == 0 && hist && blockIdx.x == 0)
         for (int t = threadIdx.x; t < 2048; t += 64) hist[t] = 0;
     __shared__ uint32_t lh[HIST ? 2048 : 1];
     if (HIST) {
@@ -1755,8 +1763,8 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
     };
     const int64_t D = static_cast<int64_t>(p.plan[j].Dw);
     const int64_t visits = (d + D - 1) / D;
-    const int64_t nD0 = visits * blockIdx.z / nseg * D;          // my segment of the chain
-    const int64_t nD1 = visits * (blockIdx.z + 1) / nseg * D;
+    const int64_t nD0 = visits * seg / nseg * D;                 // my segment of the chain
+    const int64_t nD1 = visits * (seg + 1) / nseg * D;
     const uint64_t ADb = p.plan[j].ADw, ADs = p.plan[j].ADws;
     const uint64_t Ab = p.a[j], As = p.as[j];
     const int64_t chunks = (D + kQRun - 1) / kQRun;
@@ -1766,9 +1774,8 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
     float* __restrict__ out = rows + static_cast<size_t>(j) * d;
 
     const int64_t per_xcd = (nwaves + 7) / 8;
-    const int64_t xcd_first = static_cast<int64_t>(blockIdx.x & 7) * per_xcd;
-    for (int64_t k = static_cast<int64_t>(blockIdx.x >> 3) * NW + wq; k < per_xcd;
-         k += static_cast<int64_t>(gridDim.x >> 3) * NW) {
+    const int64_t xcd_first = static_cast<int64_t>(bx & 7) * per_xcd;
+    for (int64_t k = static_cast<int64_t>(bx >> 3) * NW + wq; k < per_xcd; k += static_cast<int64_t>(across >> 3) * NW) {
         const int64_t wv = xcd_first + k;
         if (wv >= nwaves) break;
         const int64_t chunk0 = wv * 64;
@@ -2113,18 +2120,10 @@ int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t 
 // hist: cleared; with fuse_last it also receives the counts of est by magnitude bin.
 int launch_estimate_walk(const cs_params* p, const float* S, int64_t d, int64_t i0,
                          float* est, float* rows, bool fuse_last, uint64_t* hist, hipStream_t stream) {
-    int64_t most = 1;
-    for (uint32_t j = 0; j < p->r; ++j) {
-        const int64_t chunks = (static_cast<int64_t>(p->plan[j].Dw) + kQRun - 1) / kQRun;
-        const int64_t nwaves = (chunks + 63) / 64;
-        if (nwaves > most) most = nwaves;
-    }
-    const int64_t cap = 256 * 64;
-    int64_t gx = most < cap ? most : cap;
-    gx = (gx + 7) / 8 * 8;
     // about 2048 wavefronts per row, at least 4 visits per segment
     RowSegments segs{};
-    int most_segs = 1;
+    uint32_t total = 0, before_last = 0;
+    for (uint32_t j = 0; j < CS_MAX_R; ++j) segs.first[j] = ~0u;
     for (uint32_t j = 0; j < p->r; ++j) {
         const int64_t Dw = static_cast<int64_t>(p->plan[j].Dw);
         const int64_t nwaves = ((Dw + kQRun - 1) / kQRun + 63) / 64;
@@ -2134,24 +2133,24 @@ int launch_estimate_walk(const cs_params* p, const float* S, int64_t d, int64_t 
         if (n < 1) n = 1;
         if (n > 1024) n = 1024;
         segs.n[j] = static_cast<int>(n);
-        if (segs.n[j] > most_segs) most_segs = segs.n[j];
+        segs.across[j] = static_cast<uint32_t>(((nwaves < 256 * 64 ? nwaves : 256 * 64) + 7) / 8 * 8);
+        segs.first[j] = before_last = total;
+        total += segs.across[j] * static_cast<uint32_t>(n);
     }
     unsigned long long* h = reinterpret_cast<unsigned long long*>(hist);
     if (!fuse_last) {
-        const dim3 grid(static_cast<unsigned>(gx), p->r, static_cast<unsigned>(most_segs));
-        k_row_values_walk<0, false><<<grid, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);
+        k_row_values_walk<0, false><<<total, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);
         return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
     }
     // rows 0 .. r-2 into the scratch, then the last row together with the median
     if (p->r > 1) {
-        const dim3 grid(static_cast<unsigned>(gx), p->r - 1, static_cast<unsigned>(most_segs));
-        k_row_values_walk<0, false><<<grid, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);
+        k_row_values_walk<0, false><<<before_last, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);
     } else if (h) {
         const int rc = launch_magnitude_hist_zero(hist, stream);
         if (rc != CS_OK) return rc;
     }
-    const dim3 grid(static_cast<unsigned>(gx), 1, static_cast<unsigned>(segs.n[p->r - 1]));
-    const dim3 hgrid(static_cast<unsigned>(((gx + kHistWaves - 1) / kHistWaves + 7) / 8 * 8), 1, grid.z);
+    const uint32_t last = p->r - 1, nlast = static_cast<uint32_t>(segs.n[last]), grid = segs.across[last] * nlast;
+    const uint32_t hgrid = ((segs.across[last] + kHistWaves - 1) / kHistWaves + 7) / 8 * 8 * nlast;
 #define CS_LAST(R_)                                                                                    \
     case R_:                                                                                           \
         if (h) k_row_values_walk<R_, true><<<hgrid, 64 * kHistWaves, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h); \

@@ -49,3 +49,20 @@ def test_query_with_lists_is_the_query_by_hashes(r, c, d, seed, below, sign):
         got = torch.full((d,), 77.0, device=DEV)
         cs.cs_sketch_estimate(p, S, got, i0, ws)
         np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
+
+
+# strides that differ by a factor of 250 between the rows (one row of 8 wavefronts in 256 segments beside rows of
+# 1100 in one), the shortest vector that is walked, and the lengths on both sides of the fused last row
+@pytest.mark.parametrize("r,c,d", [(15, 1 << 16, 2_000_000), (5, 1 << 15, 1 << 20), (3, 64, 4096), (1, 1 << 10, 70_001),
+                                   (5, 1 << 16, (1 << 24) - 1), (5, 1 << 16, 1 << 24)])
+def test_query_by_walks_is_the_query_of_single_coordinates(r, c, d):
+    p = cs.cs_params_init(r, c, 190304488, d)
+    S = torch.randn(r, c, generator=torch.Generator().manual_seed(d)).to(DEV)
+    want = torch.empty(d, device=DEV)
+    cs.cs_sketch_estimate_sparse(p, S, torch.arange(3, d + 3, device=DEV), want)
+    for hist in (None, torch.full((2048,), 9, dtype=torch.int64, device=DEV)):
+        got = torch.full((d,), 77.0, device=DEV)
+        cs.cs_sketch_estimate(p, S, got, 3, _scratch(cs.cs_estimate_workspace_bytes(p, d)), hist)
+        assert torch.equal(got, want)
+    bins = (want.abs().view(torch.int32).long() >> 20)
+    assert torch.equal(hist, torch.bincount(bins, minlength=2048))
