@@ -1883,16 +1883,36 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
 // comparisons cannot tell) are hashed by the definition, value by value, and gathered from the table.
 // What bounds it is the scratch: r - 1 rows written and read, est written.  With two 61-bit hash states per
 // residue moved on at each visit, and the counts of magnitudes in a pass of their own, the query took 2960 us for
-// 15 rows of 90 M (10.4 GB of traffic: 1.7 ms at 6.2 TB/s) and 744 us for 5 rows of 73 M; now 2691 and 651.
+// 15 rows of 90 M (10.4 GB of traffic: 1.7 ms at 6.2 TB/s) and 744 us for 5 rows of 73 M; now 2236 and 569.
 // ---------------------------------------------------------------------------------------
 constexpr int kQueryWaves = 4;                         // wavefronts per workgroup: one table of visits, one set of counters
-template <int RF, int NC, bool HIST>
+constexpr int kQWave = 64 * kQRun;                     // residues of a wavefront
+constexpr int kQLine = 32;                             // floats of a line of memory
+// Where the scratch is larger than the memory-side cache (256 MB), a line that two wavefronts write in part each
+// costs about four times a whole one: 1 KB pieces that begin anywhere are written at 3.1 to 5.0 TB/s, pieces on lines at 4.1
+// to 6.9, and the row kernels spent 1520 of the 2700 us of 15 rows of 90 M at 3.3 TB/s.  With LINES a wavefront also works out
+// the 32 residues behind its own and writes the 256 that begin on a line (one short part at each visit's ends).  That is a
+// quarter more arithmetic, so only from r d = 200 million on (us, pieces anywhere / on lines: 6.5M x 5 rows 85 / 94,
+// 20M x 5 215 / 241, 30M x 5 280 / 298, 20M x 15 648 / 651, 50M x 5 452 / 412, 73M x 5 651 / 569, 90M x 15 2697 / 2236).
+constexpr int64_t kLinesFrom = 200000000;
+template <bool LINES>
+__device__ __forceinline__ vec4f load_values(const float* p) {
+    if (LINES) return *reinterpret_cast<const vec4f_u*>(p);
+    return __builtin_nontemporal_load(reinterpret_cast<const vec4f_u*>(p));
+}
+template <bool LINES>
+__device__ __forceinline__ void store_values(float* p, vec4f u) {
+    if (LINES) *reinterpret_cast<vec4f*>(p) = u;
+    else __builtin_nontemporal_store(u, reinterpret_cast<vec4f_u*>(p));
+}
+template <int RF, int NC, bool HIST, bool LINES>
 __global__ void __launch_bounds__(64 * kQueryWaves)
 k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, int64_t d, int64_t i0,
                     float* __restrict__ rows, float* __restrict__ est, unsigned long long* __restrict__ hist, int nseg) {
     static_assert(kQRun == 4, "one 16-byte piece per lane");
     static_assert(NC == 2 || NC == 4, "omega = 1 or 2");
     static_assert(!HIST || RF > 0, "only the kernel that writes est can count it");
+    constexpr int kOwn = kQRun + (LINES ? 1 : 0);
     const int lane = threadIdx.x & 63;
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const VisitGaps& v = vr.row[blockIdx.y];           // the rows of a launch run side by side
@@ -1907,9 +1927,13 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
         if (HIST) atomicAdd(&lh[(__float_as_uint(x) & 0x7fffffffu) >> 20], 1u);
     };
     __shared__ uint4 steps[CS_ANYC_MAX_VISITS];
+    __shared__ __align__(16) float turn_all[LINES ? kQueryWaves : 1][LINES ? kQWave + kQLine : 4];
+    float* turn = turn_all[LINES ? wq : 0];
     const Columns col = columns_of<false>(c);
     const float* __restrict__ Sj = S + static_cast<size_t>(j) * c;
     float* __restrict__ out = rows + static_cast<size_t>(j) * d;
+    // floats from the last line boundary to the coordinate 0 that I write
+    const uint32_t line0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(RF ? est : out) / sizeof(float)) % kQLine;
     const uint32_t omega = v.omega, pc = v.pc;
     auto cell_of_sum = [&](uint32_t first, uint32_t q) -> uint32_t {
         const uint32_t x = q < omega ? first + q : first + (q - omega) + (c - pc);
@@ -1931,13 +1955,18 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
         if (xcd_first + kk >= nsets || wv >= nwaves) break;
         const uint32_t wave_res = static_cast<uint32_t>(wv * 64 * kQRun);    // first residue of the wavefront
         const uint32_t my_res = wave_res + lane * kQRun;
-        uint32_t xb[kQRun], xs[kQRun];                 // top bits of the hashes at my residues
-        float cellv[kQRun][NC];
+        // my residues: four neighbours, and with LINES one of the kQLine that follow the wavefront's
+        uint32_t xb[kOwn], xs[kOwn];                   // top bits of their hashes
+        float cellv[kOwn][NC];
         {
             uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
             uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res));
 #pragma unroll
-            for (int m = 0; m < kQRun; ++m) {
+            for (int m = 0; m < kOwn; ++m) {
+                if (LINES && m == kQRun) {
+                    yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + wave_res + kQWave + lane % kQLine));
+                    ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + wave_res + kQWave + lane % kQLine));
+                }
                 xb[m] = top_of(yb);
                 xs[m] = top_of(ys);
                 const uint32_t first = bucket_of<false>(yb, col);
@@ -1953,28 +1982,30 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
             if ((w & kGapMask) <= wave_res || s + wave_res >= d32) continue;
             // residues from wave_res on that take part in this visit and exist in the vector
             const uint32_t in_gap = (w & kGapMask) - wave_res, in_vec = d32 - s - wave_res;
-            const int my_len = static_cast<int>(in_gap < in_vec ? in_gap : in_vec) - lane * kQRun;    // of my 4: >= 4 all, <= 0 none
-            const size_t at = static_cast<size_t>(s) + my_res;
+            const int len = static_cast<int>(in_gap < in_vec ? in_gap : in_vec);
+            // with LINES the wavefront writes from its first whole line on, and on into the line of its last residue
+            const uint32_t t = LINES ? (0u - (line0 + s + wave_res)) % kQLine : 0u;
+            const int my_len = len - static_cast<int>(t) - lane * kQRun;      // of the 4 that I write: >= 4 all, <= 0 none
+            const size_t at = static_cast<size_t>(s) + wave_res + t + lane * kQRun;
             [[maybe_unused]] vec4f other[RF > 1 ? RF - 1 : 1];
             if constexpr (RF > 1) {
                 if (my_len >= kQRun) {
 #pragma unroll
                     for (int q = 0; q < RF - 1; ++q)
-                        other[q] = __builtin_nontemporal_load(reinterpret_cast<const vec4f_u*>(
-                            rows + static_cast<size_t>(q) * d + at));
+                        other[q] = load_values<LINES>(rows + static_cast<size_t>(q) * d + at);
                 }
             }
-            bool flip[kQRun], wrap[kQRun], unsure = false;
+            bool flip[kOwn], wrap[kOwn], unsure = false;
 #pragma unroll
-            for (int m = 0; m < kQRun; ++m) {
+            for (int m = 0; m < kOwn; ++m) {
                 flip[m] = xs[m] > e.y;
                 wrap[m] = xb[m] > e.x;
                 unsure |= xb[m] == e.x || xs[m] == e.y;
             }
             const bool odd = (w >> 29 & 1u) != 0, second = NC > 2 && w >> 30 == 1u;
-            float o[kQRun];
+            float o[kOwn];
 #pragma unroll
-            for (int m = 0; m < kQRun; ++m) {
+            for (int m = 0; m < kOwn; ++m) {
                 float plain = cellv[m][0], wrapped = cellv[m][NC / 2];
                 if (NC > 2) {
                     plain = second ? cellv[m][NC / 2 - 1] : plain;
@@ -1984,52 +2015,76 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
                 o[m] = flip[m] != odd ? -x : x;
             }
             if (w >> 30 == 3u || __builtin_amdgcn_ballot_w64(unsure) != 0) {
-                uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0) + at);
-                uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0) + at);
+                uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0) + (LINES ? static_cast<size_t>(s) + my_res : at));
+                uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0) + (LINES ? static_cast<size_t>(s) + my_res : at));
 #pragma unroll
-                for (int m = 0; m < kQRun; ++m) {
-                    if (m < my_len) o[m] = apply_sign(Sj[bucket_of<false>(yb, col)], sign_flip_of(ys));
+                for (int m = 0; m < kOwn; ++m) {
+                    if (LINES && m == kQRun) {
+                        yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0) + s + wave_res + kQWave + lane % kQLine);
+                        ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0) + s + wave_res + kQWave + lane % kQLine);
+                    }
+                    if (LINES || m < my_len) o[m] = apply_sign(Sj[bucket_of<false>(yb, col)], sign_flip_of(ys));
                     yb = hash_advance(yb, v.a);
                     ys = hash_advance(ys, v.as);
                 }
             }
+            vec4f mine;
+            mine.x = o[0]; mine.y = o[1]; mine.z = o[2]; mine.w = o[3];
+            [[maybe_unused]] float head = 0.0f;
+            if constexpr (LINES) {
+                *reinterpret_cast<vec4f*>(turn + lane * kQRun) = mine;
+                if (lane < kQLine) turn[kQWave + lane] = o[kQRun];
+                __builtin_amdgcn_wave_barrier();
+                mine = *reinterpret_cast<const vec4f_u*>(turn + t + lane * kQRun);
+                head = turn[lane % kQLine];
+                __builtin_amdgcn_wave_barrier();
+            }
+            // the visit's first residues, before its first whole line
+            const bool heads = LINES && wave_res == 0 && lane < static_cast<int>(t) && lane < len;
             if constexpr (RF > 0) {
-                float* dst = est + at;
                 if (my_len >= kQRun) {
                     float vx[RF], vy[RF], vz[RF], vw[RF];
 #pragma unroll
                     for (int q = 0; q < RF - 1; ++q) {
                         vx[q] = other[q].x; vy[q] = other[q].y; vz[q] = other[q].z; vw[q] = other[q].w;
                     }
-                    vx[RF - 1] = o[0]; vy[RF - 1] = o[1]; vz[RF - 1] = o[2]; vw[RF - 1] = o[3];
+                    vx[RF - 1] = mine.x; vy[RF - 1] = mine.y; vz[RF - 1] = mine.z; vw[RF - 1] = mine.w;
                     vec4f u;
                     u.x = median_odd<RF>(vx); u.y = median_odd<RF>(vy);
                     u.z = median_odd<RF>(vz); u.w = median_odd<RF>(vw);
-                    __builtin_nontemporal_store(u, reinterpret_cast<vec4f_u*>(dst));
+                    store_values<LINES>(est + at, u);
                     tally(u.x); tally(u.y); tally(u.z); tally(u.w);
                 } else {
                     for (int m = 0; m < kQRun; ++m) {
                         if (m >= my_len) break;
-                        float t[RF];
+                        float f[RF];
 #pragma unroll
-                        for (int q = 0; q < RF - 1; ++q) t[q] = rows[static_cast<size_t>(q) * d + at + m];
-                        t[RF - 1] = o[m];
-                        const float med = median_odd<RF>(t);
-                        dst[m] = med;
+                        for (int q = 0; q < RF - 1; ++q) f[q] = rows[static_cast<size_t>(q) * d + at + m];
+                        f[RF - 1] = mine[m];
+                        const float med = median_odd<RF>(f);
+                        est[at + m] = med;
                         tally(med);
                     }
+                }
+                if (heads) {
+                    float f[RF];
+#pragma unroll
+                    for (int q = 0; q < RF - 1; ++q) f[q] = rows[static_cast<size_t>(q) * d + s + lane];
+                    f[RF - 1] = head;
+                    const float med = median_odd<RF>(f);
+                    est[static_cast<size_t>(s) + lane] = med;
+                    tally(med);
                 }
             } else {
                 float* dst = out + at;
                 if (my_len >= kQRun) {
-                    vec4f u;
-                    u.x = o[0]; u.y = o[1]; u.z = o[2]; u.w = o[3];
-                    __builtin_nontemporal_store(u, reinterpret_cast<vec4f_u*>(dst));
+                    store_values<LINES>(dst, mine);
                 } else if (my_len > 0) {
-                    dst[0] = o[0];
-                    if (my_len > 1) dst[1] = o[1];
-                    if (my_len > 2) dst[2] = o[2];
+                    dst[0] = mine.x;
+                    if (my_len > 1) dst[1] = mine.y;
+                    if (my_len > 2) dst[2] = mine.z;
                 }
+                if (heads) out[static_cast<size_t>(s) + lane] = head;
             }
         }
     }
@@ -2072,6 +2127,7 @@ int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t 
         if (n > 16) n = 16;
         return static_cast<unsigned>(n < 1 ? 1 : n);
     };
+    const bool lines = static_cast<int64_t>(p->r) * d >= kLinesFrom && reinterpret_cast<uintptr_t>(est) % 4 == 0;
     const uint32_t last = p->r - 1;
     VisitGapsRows vr{};
     const int rc = for_each_anyc_launch(p, last, [&](const uint32_t* js, int n, uint32_t omega) {
@@ -2086,8 +2142,15 @@ int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t 
         }
         const unsigned nseg = pieces(waves, shortest);
         const dim3 grid(grid_x(most), static_cast<unsigned>(n), nseg);
-        if (omega == 1) k_row_values_visits<0, 2, false><<<grid, 64 * kQueryWaves, 0, stream>>>(vr, S, p->c, d, i0, rows, est, clear, static_cast<int>(nseg));
-        else k_row_values_visits<0, 4, false><<<grid, 64 * kQueryWaves, 0, stream>>>(vr, S, p->c, d, i0, rows, est, clear, static_cast<int>(nseg));
+        auto launch = [&](auto nc, auto lines) {
+            k_row_values_visits<0, decltype(nc)::value, false, decltype(lines)::value><<<grid, 64 * kQueryWaves, 0, stream>>>(
+                vr, S, p->c, d, i0, rows, est, clear, static_cast<int>(nseg));
+        };
+        using std::integral_constant;
+        if (omega == 1 && lines) launch(integral_constant<int, 2>(), std::true_type());
+        else if (omega == 1) launch(integral_constant<int, 2>(), std::false_type());
+        else if (lines) launch(integral_constant<int, 4>(), std::true_type());
+        else launch(integral_constant<int, 4>(), std::false_type());
         clear = nullptr;
         return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
     });
@@ -2097,13 +2160,14 @@ int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t 
     const unsigned nseg_last = pieces((p->anyc[last].gmax + 64 * kQRun - 1) / (64 * kQRun), p->anyc[last].K);
     const dim3 gx(grid_x(p->anyc[last].gmax), 1, nseg_last);
 #define CS_LASTQ(R_, NC_, H_) \
-    k_row_values_visits<R_, NC_, H_><<<gx, 64 * kQueryWaves, 0, stream>>>(vr, S, p->c, d, i0, rows, est, h, static_cast<int>(nseg_last))
+    if (lines) k_row_values_visits<R_, NC_, H_, true><<<gx, 64 * kQueryWaves, 0, stream>>>(vr, S, p->c, d, i0, rows, est, h, static_cast<int>(nseg_last)); \
+    else k_row_values_visits<R_, NC_, H_, false><<<gx, 64 * kQueryWaves, 0, stream>>>(vr, S, p->c, d, i0, rows, est, h, static_cast<int>(nseg_last))
 #define CS_LASTR(R_)                                                                                 \
     case R_:                                                                                         \
-        if (omega_last == 1 && h) CS_LASTQ(R_, 2, true);                                             \
-        else if (omega_last == 1) CS_LASTQ(R_, 2, false);                                            \
-        else if (h) CS_LASTQ(R_, 4, true);                                                           \
-        else CS_LASTQ(R_, 4, false);                                                                 \
+        if (omega_last == 1 && h) { CS_LASTQ(R_, 2, true); }                                         \
+        else if (omega_last == 1) { CS_LASTQ(R_, 2, false); }                                        \
+        else if (h) { CS_LASTQ(R_, 4, true); }                                                       \
+        else { CS_LASTQ(R_, 4, false); }                                                             \
         break;
     switch (p->r) {
         CS_LASTR(1) CS_LASTR(3) CS_LASTR(5) CS_LASTR(7) CS_LASTR(9) CS_LASTR(11) CS_LASTR(13) CS_LASTR(15)

@@ -51,6 +51,27 @@ def test_query_with_lists_is_the_query_by_hashes(r, c, d, seed, below, sign):
         np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
 
 
+# r d from 200 million on is written in whole lines, wherever the scratch and the result begin; lists with one cell and (the
+# second case, 15 rows) with two cells per wrap
+@pytest.mark.parametrize("r,c,d", [(5, 180_000, 40_000_001), (15, 250_007, 13_400_003)])
+@pytest.mark.parametrize("of_rows,of_est", [(0, 0), (3, 1), (30, 31)])
+def test_query_in_whole_lines(r, c, d, of_rows, of_est):
+    p = cs.cs_params_init(r, c, 190304488, d)
+    n = cs.cs_estimate_scratch_bytes(p, d)
+    assert n == 4 * r * d
+    S = torch.randn(r, c, generator=torch.Generator().manual_seed(d)).to(DEV)
+    want = torch.empty(d, device=DEV)
+    cs.cs_sketch_estimate_sparse(p, S, torch.arange(3, d + 3, device=DEV), want)
+    for hist in (None, torch.full((2048,), 9, dtype=torch.int64, device=DEV)):
+        got = torch.full((d + 64,), 77.0, device=DEV)
+        est = got[of_est:of_est + d]
+        cs.cs_sketch_estimate(p, S, est, 3, _scratch(n + 4 * of_rows)[4 * of_rows:], hist)
+        assert torch.equal(est, want)
+        assert (got[:of_est] == 77.0).all() and (got[of_est + d:] == 77.0).all()
+    bins = (want.abs().view(torch.int32).long() >> 20)
+    assert torch.equal(hist, torch.bincount(bins, minlength=2048))
+
+
 # strides that differ by a factor of 250 between the rows (one row of 8 wavefronts in 256 segments beside rows of
 # 1100 in one), the shortest vector that is walked, and the lengths on both sides of the fused last row
 @pytest.mark.parametrize("r,c,d", [(15, 1 << 16, 2_000_000), (5, 1 << 15, 1 << 20), (3, 64, 4096), (1, 1 << 10, 70_001),
