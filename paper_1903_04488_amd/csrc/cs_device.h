@@ -149,10 +149,9 @@ __device__ __forceinline__ bool segment_sum16(uint32_t key, float& v, int nsteps
 // any sorting network gives the same middle element; with a NaN among the values (every
 // comparison with it is false) the result depends on the sequence of comparisons, and this
 // sequence is the one a plain insertion sort with ">" makes: a NaN stays where it was put and
-// blocks what lies above it from moving down.  Infinities order as usual; -0 and +0 compare
-// equal and keep their order.
+// blocks what lies above it from moving down.  Infinities order as usual.
 template <int R>
-__device__ __forceinline__ float median_odd(float (&v)[R]) {
+__device__ __forceinline__ float median_by_sort(float (&v)[R]) {
 #pragma unroll
     for (int x = 1; x < R; ++x) {
 #pragma unroll
@@ -165,6 +164,93 @@ __device__ __forceinline__ float median_odd(float (&v)[R]) {
         }
     }
     return v[R / 2];
+}
+
+// minimum and maximum of two numbers that are no NaN, an instruction each (fminf would first make quiet what comes from memory)
+__device__ __forceinline__ float number_min(float a, float b) {
+    float x;
+    asm("v_min_f32 %0, %1, %2" : "=v"(x) : "v"(a), "v"(b));
+    return x;
+}
+__device__ __forceinline__ float number_max(float a, float b) {
+    float x;
+    asm("v_max_f32 %0, %1, %2" : "=v"(x) : "v"(a), "v"(b));
+    return x;
+}
+
+// The same of numbers that are no NaN.  Of any R / 2 + 2 of them neither the smallest nor the largest is the
+// median: both are dropped and one more is taken up, until three are left.  7 instructions for 5 numbers where the sort
+// takes 30, 20 for 63 of 7, and about 90 for 315 of 15.
+template <int R>
+__device__ __forceinline__ float median_of_numbers(const float (&v)[R]) {
+    if constexpr (R == 1) {
+        return v[0];
+    } else {
+        constexpr int kFirst = R / 2 + 2;
+        float w[kFirst];
+#pragma unroll
+        for (int i = 0; i < kFirst; ++i) w[i] = v[i];
+        // w[lo .. kFirst) are in the running; v[kFirst + lo] is the next
+#pragma unroll
+        for (int lo = 0; lo < kFirst - 3; ++lo) {
+            const int n = kFirst - lo;
+            auto order = [&](int x, int y) {
+                const float a = number_min(w[x], w[y]), b = number_max(w[x], w[y]);
+                w[x] = a;
+                w[y] = b;
+            };
+#pragma unroll
+            for (int i = 0; i < n / 2; ++i) order(lo + i, kFirst - 1 - i);
+#pragma unroll
+            for (int i = 1; i < (n + 1) / 2; ++i) order(lo, lo + i);                       // w[lo] the smallest
+#pragma unroll
+            for (int i = 1; i < (n + 1) / 2; ++i) order(kFirst - 1 - i, kFirst - 1);       // the last the largest
+            w[kFirst - 1] = v[kFirst + lo];
+        }
+        return __builtin_amdgcn_fmed3f(w[kFirst - 3], w[kFirst - 2], w[kFirst - 1]);
+    }
+}
+
+template <int R>
+__device__ __forceinline__ bool any_nan(const float (&v)[R]) {
+    bool nan = v[R - 1] != v[R - 1];
+#pragma unroll
+    for (int i = 0; i + 1 < R; i += 2) nan |= __builtin_isunordered(v[i], v[i + 1]);
+    return nan;
+}
+
+template <int R>
+__device__ __forceinline__ float median_odd(float (&v)[R]) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(any_nan(v)) != 0, 0)) return median_by_sort<R>(v);
+    return median_of_numbers<R>(v);
+}
+
+// four medians, one check
+template <int R>
+__device__ __forceinline__ void medians_odd(const float (&a)[R], const float (&b)[R], const float (&c)[R], const float (&e)[R],
+                                            float (&out)[4]) {
+    bool nan = any_nan(a);
+    nan |= any_nan(b);
+    nan |= any_nan(c);
+    nan |= any_nan(e);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(nan) != 0, 0)) {
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q) {
+            float t[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) t[j] = q == 0 ? a[j] : q == 1 ? b[j] : q == 2 ? c[j] : e[j];
+            const float x = median_by_sort<R>(t);
+            if (q == 0) out[0] = x;
+            else if (q == 1) out[1] = x;
+            else if (q == 2) out[2] = x;
+            else out[3] = x;
+        }
+        return;
+    }
+    out[0] = median_of_numbers<R>(a);
+    out[1] = median_of_numbers<R>(b);
+    out[2] = median_of_numbers<R>(c);
+    out[3] = median_of_numbers<R>(e);
 }
 
 }  // namespace cs

@@ -269,7 +269,9 @@ k_median_rows(const float* __restrict__ rows, int64_t d, float* __restrict__ est
                 }
                 vx[j] = q.x; vy[j] = q.y; vz[j] = q.z; vw[j] = q.w;
             }
-            const float4 m = make_float4(median_odd<R>(vx), median_odd<R>(vy), median_odd<R>(vz), median_odd<R>(vw));
+            float med[4];
+            medians_odd<R>(vx, vy, vz, vw, med);
+            const float4 m = make_float4(med[0], med[1], med[2], med[3]);
             if constexpr (VEC) {
                 reinterpret_cast<float4*>(est)[t] = m;
             } else {

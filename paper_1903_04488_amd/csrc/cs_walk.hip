@@ -1824,8 +1824,9 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
                     }
                     vx[RF - 1] = o[0]; vy[RF - 1] = o[1]; vz[RF - 1] = o[2]; vw[RF - 1] = o[3];
                     vec4f u;
-                    u.x = median_odd<RF>(vx); u.y = median_odd<RF>(vy);
-                    u.z = median_odd<RF>(vz); u.w = median_odd<RF>(vw);
+                    float med[4];
+                    medians_odd<RF>(vx, vy, vz, vw, med);
+                    u.x = med[0]; u.y = med[1]; u.z = med[2]; u.w = med[3];
                     __builtin_nontemporal_store(u, reinterpret_cast<vec4f_u*>(dst));
                     tally(u.x); tally(u.y); tally(u.z); tally(u.w);
                 } else {
@@ -2050,8 +2051,9 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
                     }
                     vx[RF - 1] = mine.x; vy[RF - 1] = mine.y; vz[RF - 1] = mine.z; vw[RF - 1] = mine.w;
                     vec4f u;
-                    u.x = median_odd<RF>(vx); u.y = median_odd<RF>(vy);
-                    u.z = median_odd<RF>(vz); u.w = median_odd<RF>(vw);
+                    float med[4];
+                    medians_odd<RF>(vx, vy, vz, vw, med);
+                    u.x = med[0]; u.y = med[1]; u.z = med[2]; u.w = med[3];
                     store_values<LINES>(est + at, u);
                     tally(u.x); tally(u.y); tally(u.z); tally(u.w);
                 } else {
