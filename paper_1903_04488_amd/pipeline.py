@@ -22,9 +22,9 @@ from . import binding as B
 
 class HotPath:
     # the update by way of running sums (cs_bundle_sketch), where the sketch has lists for it: its index, its
-    # workspace, and whether that leaves room for the mean of folded workers
+    # workspace, and whether they were made for folded workers
     _index = _sums_ws = _sums_fold = None
-    SUMS_OWN_BYTES = 256 << 20           # a workspace of its own for them up to here
+    SUMS_OWN_BYTES = 256 << 20           # the workspace: up to here, or up to what the query's scratch takes
 
     def __init__(self, d: int, W: int, r: int, c: int, k: int, seed: int,
                  rho: float | None = None, device="cuda:0", P: int = 1, fold_workers: bool = False):
@@ -91,14 +91,11 @@ class HotPath:
         if not n:
             return
         W = 1 if self.fold_workers else self.W
-        # the workspace is the query's scratch, free until the estimate, where that is large enough: all of it, or
-        # what the mean of folded workers leaves
         need = B.cs_update_workspace_bytes(self.params, W, self.d)
-        skip = (4 * self.d + 255) // 256 * 256 if self.fold_workers else 0
-        fits = self.est_ws is not None and self.est_ws.numel() >= skip + need
-        if not fits and need > self.SUMS_OWN_BYTES:
+        if need > max(self.SUMS_OWN_BYTES, self.est_ws.numel() if self.est_ws is not None else 0):
             return
-        self._sums_ws = self.est_ws[skip:] if fits else torch.empty(need, dtype=torch.uint8, device=self.device)
+        # (memory of its own, not the query's scratch: an update may run beside the query of the step before)
+        self._sums_ws = torch.empty(need, dtype=torch.uint8, device=self.device)
         self._index = torch.empty(n, dtype=torch.uint8, device=self.device)
         B.cs_update_index_build(self.params, self.d, self._index)
         self._sums_fold = self.fold_workers

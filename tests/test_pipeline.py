@@ -102,6 +102,23 @@ def test_folded_workers_are_all_summed_whenever_folding_was_chosen(calls, W, giv
         assert out.data_ptr() == path.est_ws.data_ptr()
 
 
+@pytest.mark.parametrize("scratch,need,built", [(5000, 4000, True), (0, 4000, True), (5000, 5001, False)])
+@pytest.mark.parametrize("fold", [False, True])
+def test_an_update_may_run_beside_the_query_of_the_step_before(monkeypatch, fold, scratch, need, built):
+    """on another stream: its running sums don't lie in the query's scratch, which that query still reads"""
+    monkeypatch.setattr(pipeline.B, "cs_update_index_bytes", lambda p, W, d: 64)
+    monkeypatch.setattr(pipeline.B, "cs_update_workspace_bytes", lambda p, W, d: need)
+    monkeypatch.setattr(pipeline.B, "cs_update_index_build", lambda p, d, index: None)
+    monkeypatch.setattr(pipeline.HotPath, "SUMS_OWN_BYTES", 4500)
+    path = bare(fold_workers=fold, d=100, est_ws=torch.empty(scratch, dtype=torch.uint8) if scratch else None)
+    path._build_index()
+    assert (path._index is not None) == built
+    if built and scratch:
+        ws, own = path._sums_ws, path.est_ws
+        assert ws.numel() == need
+        assert ws.data_ptr() + need <= own.data_ptr() or own.data_ptr() + scratch <= ws.data_ptr()
+
+
 @pytest.mark.parametrize("d", [784, 32_768, 32_769])
 def test_counts_by_magnitude_are_there_for_vectors_of_any_length(calls, d):
     """up to CS_TOPK_SMALL_D neither the estimate nor the selection is given the counts; whoever reads
