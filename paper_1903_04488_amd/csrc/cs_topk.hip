@@ -860,8 +860,10 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
 
 // Alg. 1 step 1: out[1 + j] = sum_b S[j][b]^2, one workgroup of 1024 threads per row, binary64
 // sums in a fixed order (each thread a strided share in four independent chains, then a tree
-// over the workgroup), 16-byte loads when the row allows.
+// over the workgroup), 16-byte loads when the row allows.  A workgroup alone on its CU waits for its loads: with one of a
+// thread in flight 5 x 180 000 took 16.7 us, with eight 10.4.
 constexpr int kSumBlock = 1024;
+constexpr int kSumAhead = 8;         // loads of a thread in flight
 __global__ void __launch_bounds__(kSumBlock)
 k_row_sumsq(const float* __restrict__ S, uint32_t c, double* __restrict__ out) {
     __shared__ double part[kSumBlock];
@@ -871,19 +873,32 @@ k_row_sumsq(const float* __restrict__ S, uint32_t c, double* __restrict__ out) {
     if (reinterpret_cast<uintptr_t>(row) % 16 == 0) {
         const uint32_t n4 = c / 4;
         const float4* row4 = reinterpret_cast<const float4*>(row);
-        for (uint32_t q = threadIdx.x; q < n4; q += kSumBlock) {
-            const float4 u = row4[q];
+        auto add = [&](const float4& u) {
             a0 += static_cast<double>(u.x) * static_cast<double>(u.x);
             a1 += static_cast<double>(u.y) * static_cast<double>(u.y);
             a2 += static_cast<double>(u.z) * static_cast<double>(u.z);
             a3 += static_cast<double>(u.w) * static_cast<double>(u.w);
+        };
+        uint32_t q = threadIdx.x;
+        for (; static_cast<uint64_t>(q) + (kSumAhead - 1) * kSumBlock < n4; q += kSumAhead * kSumBlock) {
+            float4 u[kSumAhead];
+#pragma unroll
+            for (int e = 0; e < kSumAhead; ++e) u[e] = row4[q + e * kSumBlock];
+#pragma unroll
+            for (int e = 0; e < kSumAhead; ++e) add(u[e]);
         }
+        for (; q < n4; q += kSumBlock) add(row4[q]);
         done = n4 * 4;
     }
-    for (uint32_t b = done + threadIdx.x; b < c; b += kSumBlock) {
-        const double v = static_cast<double>(row[b]);
-        a0 += v * v;
+    uint64_t b = done + threadIdx.x;
+    for (; b + (kSumAhead - 1) * kSumBlock < c; b += kSumAhead * kSumBlock) {
+        float u[kSumAhead];
+#pragma unroll
+        for (int e = 0; e < kSumAhead; ++e) u[e] = row[b + e * kSumBlock];
+#pragma unroll
+        for (int e = 0; e < kSumAhead; ++e) a0 += static_cast<double>(u[e]) * static_cast<double>(u[e]);
     }
+    for (; b < c; b += kSumBlock) a0 += static_cast<double>(row[b]) * static_cast<double>(row[b]);
     part[threadIdx.x] = (a0 + a1) + (a2 + a3);
     __syncthreads();
     for (int off = kSumBlock / 2; off > 0; off >>= 1) {
@@ -893,16 +908,30 @@ k_row_sumsq(const float* __restrict__ S, uint32_t c, double* __restrict__ out) {
     if (threadIdx.x == 0) out[1 + blockIdx.x] = part[0];
 }
 
-// out[0] = median of out[1 .. r] (r odd, <= CS_MAX_R): insertion sort by one thread
-__global__ void k_median_of_rows(double* out, int r) {
-    double v[CS_MAX_R];
-    for (int j = 0; j < r; ++j) {
-        double x = out[1 + j];
-        int q = j;
-        while (q > 0 && v[q - 1] > x) { v[q] = v[q - 1]; --q; }
-        v[q] = x;
+// out[0] = median of out[1 .. r] (r odd, <= CS_MAX_R): what an insertion sort leaves in the middle.  A lane per row counts the
+// values before its own; with a NaN, which no comparison moves, one lane sorts.
+__global__ void __launch_bounds__(64) k_median_of_rows(double* out, int r) {
+    const int lane = threadIdx.x;
+    const double mine = lane < r ? out[1 + lane] : 0.0;
+    if (__builtin_amdgcn_ballot_w64(mine != mine) != 0) {
+        if (lane != 0) return;
+        double v[CS_MAX_R];
+        for (int j = 0; j < r; ++j) {
+            double x = out[1 + j];
+            int q = j;
+            while (q > 0 && v[q - 1] > x) { v[q] = v[q - 1]; --q; }
+            v[q] = x;
+        }
+        out[0] = v[r / 2];
+        return;
     }
-    out[0] = v[r / 2];
+    int before = 0;
+#pragma unroll
+    for (int j = 0; j < CS_MAX_R; ++j) {
+        const double x = __shfl(mine, j);
+        if (j < r && (x < mine || (x == mine && j < lane))) ++before;
+    }
+    if (lane < r && before == r / 2) out[0] = mine;
 }
 
 __global__ void __launch_bounds__(kBlock) k_hist_zero(uint64_t* hist) {
@@ -1058,7 +1087,7 @@ extern "C" int cs_sketch_l2sq(const cs_params* p, const float* S, double* out, v
     if (reinterpret_cast<uintptr_t>(out) % 8 != 0) return CS_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     k_row_sumsq<<<p->r, kSumBlock, 0, s>>>(S, p->c, out);
-    k_median_of_rows<<<1, 1, 0, s>>>(out, static_cast<int>(p->r));
+    k_median_of_rows<<<1, 64, 0, s>>>(out, static_cast<int>(p->r));
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 

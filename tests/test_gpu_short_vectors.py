@@ -175,3 +175,30 @@ def sketch_in_slices_from(sk, g, i0):
     n = 1 << 19
     with ThreadPoolExecutor(max_workers=8) as pool:
         return sum(pool.map(lambda lo: sk.sketch(g[lo:lo + n], i0=i0 + lo), range(0, g.size, n)), sk.zeros())
+
+
+# sums of squares by rows, whole rounds of loads, remainders and rows at any address; their median, with NaN where the
+# insertion sort that defines it leaves them
+@pytest.mark.parametrize("r", [1, 3, 5, 15])
+@pytest.mark.parametrize("c", [5, 1023, 8192, 8197, 32_768 + 4, 40_001])
+@pytest.mark.parametrize("special", [None, "inf", "nan"])
+def test_row_norms_and_their_median(r, c, special):
+    p = cs.cs_params_init(r, c, 5, 100)
+    S = torch.randn(r, c, generator=torch.Generator().manual_seed(c))
+    if r > 1:
+        S[-1] = S[0]                                  # two equal rows
+    if special:
+        S[r // 2, c - 1] = float(special)
+    out = torch.empty(1 + r, dtype=torch.float64, device=DEV)
+    cs.cs_sketch_l2sq(p, S.to(DEV), out)
+    got = out.cpu().numpy()
+    want = (S.double() ** 2).sum(1).numpy()
+    # binary64 sums in another order: c 2^-53 at most
+    np.testing.assert_allclose(got[1:], want, rtol=c * 2.0 ** -53, equal_nan=True)
+    v = []
+    for x in got[1:]:
+        q = len(v)
+        while q > 0 and v[q - 1] > x:
+            q -= 1
+        v.insert(q, x)
+    np.testing.assert_equal(got[0], v[r // 2])
