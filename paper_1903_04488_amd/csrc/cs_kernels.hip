@@ -30,6 +30,16 @@ inline unsigned grid_for(int64_t n, int per_block = kBlock, int max_blocks = 256
     return static_cast<unsigned>(b);
 }
 
+// Workgroups of the kernels that hash every coordinate, with `slots` threads that take a coordinate each (of `groups` such
+// grids): 8 coordinates a thread, which share its first states, or one where that would be under 128 workgroups: short
+// vectors wait on chains of hashes and gathers (us, 8 a thread / one; query: 15 x 257, d = 12 001 22.4 / 10.4; 15 x 2001,
+// 150 003 24.9 / 17.4; 5 x 257, 12 001 7.1 / 5.2; 15 x 8193, 500 007 35.9 / 36.9; tables of 4 workers: 5 x 64, 3000 7.8 / 6.0;
+// 5 x 129, 5000 8.5 / 5.8).  Numbers between are no better: query of 5 x 8193, 700 001 16.6 with 8, 16.1 with 2, 18.2 with 5.
+inline unsigned grid_of_hashes(int64_t d, int slots, int64_t groups = 1) {
+    const bool few = d / (slots * 8) < 128 / groups;
+    return grid_for(d, few ? slots : slots * 8, 256 * 8);
+}
+
 // Dispatch on the (odd) row count and on "c is a power of two" so that the hash state of all
 // rows lives in registers and loops over rows are unrolled.
 #define CS_DISPATCH_R(p, CALL)                                                     \
@@ -437,7 +447,8 @@ k_estimate(KParams p, const float* __restrict__ S, int64_t d, int64_t i0,
             const float cellv = S[static_cast<size_t>(j) * c + bucket_of<POW2>(st.yb[j], col)];
             v[j] = apply_sign(cellv, sign_flip_of(st.ys[j]));
         }
-        est[t] = median_odd<R>(v);
+        // (up to 7 rows the sort, which needs no look for a NaN, lets more gathers overlap: 5 x 8193, d = 700 001 16.2 us for 16.9)
+        est[t] = R <= 7 ? median_by_sort<R>(v) : median_odd<R>(v);
         st.advance();
     }
 }
@@ -808,8 +819,8 @@ extern "C" int cs_sketch_accumulate_bundle(const cs_params* p, float* T, int32_t
         for (int w = 0; w < nw; ++w) vec.g[w] = g_w[w0 + w];
         float* T0 = T + (w0 / CS_BUNDLE_GROUP) * group_floats;
         // at least ~8 coordinates per lane so the per-lane hash set-up is amortised
-        const dim3 grid(grid_for(d, kSlots * 8, 256 * 8),
-                        static_cast<unsigned>((nw + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP));
+        const int groups = (nw + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP;
+        const dim3 grid(grid_of_hashes(d, kSlots, groups), static_cast<unsigned>(groups));
         if (lds_table_applies(p, d)) {
             const dim3 lgrid(grid_for(d, kSlots * 8, 512), grid.y);
             const size_t lds = static_cast<size_t>(p->r) * p->c * CS_BUNDLE_GROUP * sizeof(float);
@@ -1067,7 +1078,7 @@ static int estimate_all(const cs_params* p, const float* S, int64_t d, int64_t i
         if (anyc_query_needs_scratch(p, d))
             return !rows_ws || reinterpret_cast<uintptr_t>(rows_ws) % 4 != 0 ? CS_EINVAL : CS_EWORKSPACE;
     }
-    const unsigned grid = grid_for(d, kBlock * 8, 256 * 8);
+    const unsigned grid = grid_of_hashes(d, kBlock);
 #define CALL(R_, P2_) \
     k_estimate<R_, P2_><<<grid, kBlock, 0, as_stream(stream)>>>(kparams(p), S, d, i0, est)
     CS_DISPATCH_R(p, CALL);

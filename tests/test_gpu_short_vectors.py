@@ -177,6 +177,27 @@ def sketch_in_slices_from(sk, g, i0):
         return sum(pool.map(lambda lo: sk.sketch(g[lo:lo + n], i0=i0 + lo), range(0, g.size, n)), sk.zeros())
 
 
+# Kernels that hash every coordinate take one or 8 of them a thread: one thread and a remainder, both sides of where 8
+# begin for the query (2^18 coordinates) and for the tables (2^15, shared by the groups of workers).
+@pytest.mark.parametrize("r,c,d,W", [(7, 40, 1, 1), (5, 97, 31, 3), (5, 257, 33, 9), (3, 4099, 32_767, 1), (3, 4099, 32_768, 1),
+                                     (3, 4099, 16_383, 9), (3, 4099, 16_385, 9), (9, 4099, 262_143, 1), (3, 4099, 262_145, 2)])
+def test_coordinates_per_thread(r, c, d, W):
+    p = cs.cs_params_init(r, c, 5, d)
+    sk = orc.SketchOracle(r, c, 5)
+    rng = np.random.default_rng(d)
+    gs = [(rng.standard_normal(d) * 0.01).astype(np.float32) for _ in range(W)]
+    T = torch.zeros(cs.cs_bundle_floats(p, W), dtype=torch.float32, device=DEV)
+    cs.cs_sketch_accumulate_bundle(p, T, [torch.from_numpy(g).to(DEV) for g in gs])
+    got = T.cpu().numpy().reshape(-1, r, c, cs.CS_BUNDLE_GROUP)
+    for w in range(W):
+        assert_cells_close(got[w // 8, :, :, w % 8], sk.sketch(gs[w]), terms_per_cell=max(1.0, d / c), what=f"worker {w}")
+    S = torch.randn(r, c, generator=torch.Generator().manual_seed(d)).to(DEV)
+    est, want = torch.full((d + 1,), 77.0, device=DEV), torch.empty(d, device=DEV)
+    cs.cs_sketch_estimate(p, S, est[:d], 3)
+    cs.cs_sketch_estimate_sparse(p, S, torch.arange(3, d + 3, device=DEV), want)
+    assert torch.equal(est[:d], want) and est[d] == 77.0
+
+
 # sums of squares by rows, whole rounds of loads, remainders and rows at any address; their median, with NaN where the
 # insertion sort that defines it leaves them
 @pytest.mark.parametrize("r", [1, 3, 5, 15])
