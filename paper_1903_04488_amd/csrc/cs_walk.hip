@@ -28,10 +28,9 @@
 // up to fp32 rounding order.
 //
 // Data movement per visit: the 64 x RUN tile (64 runs = walkers x workers, RUN floats each) is
-// requested as contiguous pieces by neighbouring lanes, transposed through LDS so that every
-// lane gets its own run, and the (bucket, sign) of a walker's RUN coordinates are computed once
-// per walker by its lanes and shared through LDS.  Nothing is shared between the wavefronts of
-// a workgroup, so LDS needs no barrier.
+// requested as contiguous pieces by neighbouring lanes and transposed through LDS so that every
+// lane gets its own run; cell and sign of a walker's RUN coordinates are told once per walker, and its lanes take
+// them from wavefront masks (visit lists) or from LDS (stride walk).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
