@@ -908,30 +908,16 @@ k_row_sumsq(const float* __restrict__ S, uint32_t c, double* __restrict__ out) {
     if (threadIdx.x == 0) out[1 + blockIdx.x] = part[0];
 }
 
-// out[0] = median of out[1 .. r] (r odd, <= CS_MAX_R): what an insertion sort leaves in the middle.  A lane per row counts the
-// values before its own; with a NaN, which no comparison moves, one lane sorts.
-__global__ void __launch_bounds__(64) k_median_of_rows(double* out, int r) {
-    const int lane = threadIdx.x;
-    const double mine = lane < r ? out[1 + lane] : 0.0;
-    if (__builtin_amdgcn_ballot_w64(mine != mine) != 0) {
-        if (lane != 0) return;
-        double v[CS_MAX_R];
-        for (int j = 0; j < r; ++j) {
-            double x = out[1 + j];
-            int q = j;
-            while (q > 0 && v[q - 1] > x) { v[q] = v[q - 1]; --q; }
-            v[q] = x;
-        }
-        out[0] = v[r / 2];
-        return;
+// out[0] = median of out[1 .. r] (r odd, <= CS_MAX_R): insertion sort by one thread
+__global__ void k_median_of_rows(double* out, int r) {
+    double v[CS_MAX_R];
+    for (int j = 0; j < r; ++j) {
+        double x = out[1 + j];
+        int q = j;
+        while (q > 0 && v[q - 1] > x) { v[q] = v[q - 1]; --q; }
+        v[q] = x;
     }
-    int before = 0;
-#pragma unroll
-    for (int j = 0; j < CS_MAX_R; ++j) {
-        const double x = __shfl(mine, j);
-        if (j < r && (x < mine || (x == mine && j < lane))) ++before;
-    }
-    if (lane < r && before == r / 2) out[0] = mine;
+    out[0] = v[r / 2];
 }
 
 __global__ void __launch_bounds__(kBlock) k_hist_zero(uint64_t* hist) {
@@ -1087,7 +1073,7 @@ extern "C" int cs_sketch_l2sq(const cs_params* p, const float* S, double* out, v
     if (reinterpret_cast<uintptr_t>(out) % 8 != 0) return CS_EINVAL;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     k_row_sumsq<<<p->r, kSumBlock, 0, s>>>(S, p->c, out);
-    k_median_of_rows<<<1, 64, 0, s>>>(out, static_cast<int>(p->r));
+    k_median_of_rows<<<1, 1, 0, s>>>(out, static_cast<int>(p->r));
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
