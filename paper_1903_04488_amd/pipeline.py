@@ -22,8 +22,8 @@ from . import binding as B
 
 class HotPath:
     # the update by way of running sums (cs_bundle_sketch), where the sketch has lists for it: its index, its
-    # workspace, and whether they were made for folded workers
-    _index = _sums_ws = _sums_fold = None
+    # workspace, and what they were made for: the sketch's parameters, fold_workers, W and d
+    _index = _sums_ws = _sums_params = _sums_for = None
     SUMS_OWN_BYTES = 256 << 20           # the workspace: up to here, or up to what the query's scratch takes
 
     def __init__(self, d: int, W: int, r: int, c: int, k: int, seed: int,
@@ -98,12 +98,17 @@ class HotPath:
         self._sums_ws = torch.empty(need, dtype=torch.uint8, device=self.device)
         self._index = torch.empty(n, dtype=torch.uint8, device=self.device)
         B.cs_update_index_build(self.params, self.d, self._index)
-        self._sums_fold = self.fold_workers
+        self._sums_params = bytes(self.params)
+        self._sums_for = self.fold_workers, W, self.d
 
     def _indexed(self, g_w):
-        """the vectors are those that the index and its workspace were made for"""
-        return (self._index is not None and self.fold_workers == self._sums_fold and g_w[0].numel() == self.d
-                and (self.fold_workers or len(g_w) == self.W))
+        """The vectors and the sketch are those that the index and its workspace were made for.  (The parameters as they
+        are now, byte for byte, 1 us: whoever gives a path another sketch may do so by replacing them or in place.)"""
+        if self._index is None:
+            return False
+        fold, W, d = self._sums_for
+        return (self.fold_workers == fold and (fold or len(g_w) == W) and g_w[0].numel() == d
+                and bytes(self.params) == self._sums_params)
 
     def _mean(self, g_w):
         """the mean of folded workers, in scratch"""
@@ -126,7 +131,7 @@ class HotPath:
                                **{"S_t": self.S_t, **tables})
 
     def accumulate(self, g_w):
-        if self._index is not None and self._indexed(g_w):
+        if self._indexed(g_w):
             self._sketch_indexed(g_w)
             return
         if self.fold_workers:
@@ -203,8 +208,7 @@ class HotPath:
     def sketch_and_aggregate(self, g_w):
         """accumulate, merge and momentum: the last two come out of the pass that writes the tables, where there
         is one and no stage is overridden"""
-        if (self._index is not None and self._not_overridden("accumulate", "merge", "momentum", "aggregate")
-                and self._indexed(g_w)):
+        if self._indexed(g_w) and self._not_overridden("accumulate", "merge", "momentum", "aggregate"):
             self._sketch_indexed(g_w, S_t=self.S_t, S_u=self.S_u, S_v=self.S_v, rho=self.rho or 0.0)
             return
         self.accumulate(g_w)

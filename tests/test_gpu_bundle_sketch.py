@@ -7,6 +7,7 @@ import torch
 
 import paper_1903_04488_amd as cs
 from oracle import cs_oracle as orc
+from paper_1903_04488_amd.pipeline import HotPath
 from parity_util import assert_cells_close, sketch_in_slices
 
 pytestmark = pytest.mark.gpu
@@ -123,3 +124,20 @@ def test_what_is_refused():
         with pytest.raises(cs.CsError):
             cs.cs_bundle_sketch(p, torch.empty(cs.cs_bundle_floats(p, 1), dtype=torch.float32, device=DEV),
                                 [torch.zeros(other[2], device=DEV)], index, ws)
+
+
+@pytest.mark.parametrize("fold", [False, True])
+def test_a_path_given_another_sketch_sketches_with_that_one(fold):
+    """its index is of the sketch that it was made with; the sums are those of the sketch that it has now"""
+    r, c, d, W = 5, 1 << 12, 400_003, 2
+    if fold:                                         # (a single vector has an index from r d = 10 million on)
+        c, d = 1 << 14, 2_600_003
+    gs = [torch.randn(d, generator=torch.Generator().manual_seed(w)).to(DEV) for w in range(W)]
+    path = HotPath(d, W, r, c, 50, 190304488, rho=0.9, fold_workers=fold)
+    assert path._index is not None
+    path.step(gs)
+    path.params = cs.cs_params_init(r, c, 3, d)
+    path.S_u.zero_(), path.S_v.zero_()
+    path.step(gs)
+    want = sketch_in_slices(orc.SketchOracle(r, c, 3), ((gs[0].double() + gs[1].double()) / 2).float().cpu().numpy(), 1.0)
+    assert_cells_close(path.S_t.cpu().numpy(), want, terms_per_cell=d / c)

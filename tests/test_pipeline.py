@@ -110,13 +110,61 @@ def test_an_update_may_run_beside_the_query_of_the_step_before(monkeypatch, fold
     monkeypatch.setattr(pipeline.B, "cs_update_workspace_bytes", lambda p, W, d: need)
     monkeypatch.setattr(pipeline.B, "cs_update_index_build", lambda p, d, index: None)
     monkeypatch.setattr(pipeline.HotPath, "SUMS_OWN_BYTES", 4500)
-    path = bare(fold_workers=fold, d=100, est_ws=torch.empty(scratch, dtype=torch.uint8) if scratch else None)
+    path = bare(fold_workers=fold, d=100, params=binding.CsParams(),
+                est_ws=torch.empty(scratch, dtype=torch.uint8) if scratch else None)
     path._build_index()
     assert (path._index is not None) == built
     if built and scratch:
         ws, own = path._sums_ws, path.est_ws
         assert ws.numel() == need
         assert ws.data_ptr() + need <= own.data_ptr() or own.data_ptr() + scratch <= ws.data_ptr()
+
+
+def with_index(monkeypatch, cls=pipeline.HotPath, **attributes):
+    """a path that has an index for what it holds now; building it is not among the recorded calls"""
+    attributes = {"params": binding.cs_params_init(5, 64, 3, 5000), "d": 5000, "W": 2, **attributes}
+    path = bare(cls, **attributes)
+    with monkeypatch.context() as m:
+        m.setattr(pipeline.B, "cs_update_index_bytes", lambda p, W, d: 64)
+        m.setattr(pipeline.B, "cs_update_workspace_bytes", lambda p, W, d: 64)
+        m.setattr(pipeline.B, "cs_update_index_build", lambda p, d, index: None)
+        path._build_index()
+    return path
+
+
+def no_lists(path):
+    path.params.flags |= binding.CS_FLAG_NO_VISIT_LIST
+
+
+def hash_constant(path):
+    path.params.b[4] += 1
+
+
+@pytest.mark.parametrize("change", [
+    lambda path: setattr(path, "params", binding.cs_params_init(5, 64, 4, 5000)), no_lists, hash_constant,
+    lambda path: setattr(path, "W", 3), lambda path: setattr(path, "d", 4999),
+    lambda path: setattr(path, "fold_workers", not path.fold_workers)])
+@pytest.mark.parametrize("fold", [False, True])
+def test_an_index_serves_what_it_was_made_for_alone(calls, monkeypatch, fold, change):
+    """another sketch's cells have other sums, another length or number of vectors another workspace"""
+    path = with_index(monkeypatch, fold_workers=fold, g_mean=None)
+    path.step([torch.zeros(path.d)] * path.W)
+    path.accumulate([torch.zeros(path.d)] * path.W)
+    assert names(calls).count("cs_bundle_sketch") == 2
+    calls.clear()
+    path.params = binding.CsParams.from_buffer_copy(path.params)     # (equal ones are the same sketch)
+    path.accumulate([torch.zeros(path.d)] * path.W)
+    assert names(calls).count("cs_bundle_sketch") == 1
+    calls.clear()
+    change(path)
+    vectors = [torch.zeros(path.d)] * path.W
+    path.step(vectors)
+    path.accumulate(vectors)
+    if path.fold_workers and path.W != 2 and path.d == 5000:          # (folded: one vector, their sum, either way)
+        assert names(calls).count("cs_bundle_sketch") == 2
+        return
+    assert "cs_bundle_sketch" not in names(calls)
+    assert names(calls).count("cs_sketch_accumulate" if path.fold_workers else "cs_sketch_accumulate_bundle") == 2
 
 
 @pytest.mark.parametrize("d", [784, 32_768, 32_769])
