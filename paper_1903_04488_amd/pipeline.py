@@ -209,7 +209,8 @@ class HotPath:
         """accumulate, merge and momentum: the last two come out of the pass that writes the tables, where there
         is one and no stage is overridden"""
         if self._indexed(g_w) and self._not_overridden("accumulate", "merge", "momentum", "aggregate"):
-            self._sketch_indexed(g_w, S_t=self.S_t, S_u=self.S_u, S_v=self.S_v, rho=self.rho or 0.0)
+            state = {} if self.rho is None else {"S_u": self.S_u, "S_v": self.S_v, "rho": self.rho}
+            self._sketch_indexed(g_w, S_t=self.S_t, **state)
             return
         self.accumulate(g_w)
         self.aggregate()

@@ -167,6 +167,22 @@ def test_an_index_serves_what_it_was_made_for_alone(calls, monkeypatch, fold, ch
     assert names(calls).count("cs_sketch_accumulate" if path.fold_workers else "cs_sketch_accumulate_bundle") == 2
 
 
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("rho", [0.9, 0.0, None])
+def test_state_is_advanced_while_the_path_has_a_momentum_factor(calls, monkeypatch, fold, rho):
+    """rho set on a finished path, with an index as without one: None leaves S_u and S_v alone"""
+    path = with_index(monkeypatch, fold_workers=fold, g_mean=None, S_t="S_t", S_u="S_u", S_v="S_v")
+    path.rho = rho
+    path.sketch_and_aggregate([torch.zeros(path.d)] * path.W)
+    assert "cs_bundle_sketch" in names(calls) and "cs_sketch_momentum" not in names(calls)
+    tables = next(kw for name, _, kw in calls if name == "cs_bundle_sketch")
+    assert tables["S_t"] == "S_t"
+    if rho is None:
+        assert tables.get("S_u") is None and tables.get("S_v") is None
+    else:
+        assert (tables["S_u"], tables["S_v"], tables["rho"]) == ("S_u", "S_v", rho)
+
+
 @pytest.mark.parametrize("d", [784, 32_768, 32_769])
 def test_counts_by_magnitude_are_there_for_vectors_of_any_length(calls, d):
     """up to CS_TOPK_SMALL_D neither the estimate nor the selection is given the counts; whoever reads
