@@ -81,18 +81,58 @@ __global__ void __launch_bounds__(kBlock) k_index_fill(KParams p, IndexRows rows
         residue[atomicSub(&start[bucket_of<true>(hash_state(p.a[j], p.b[j], i), col)], 1u) - 1u] = static_cast<uint32_t>(i);
 }
 
-// a cell's residues in ascending order, so that sums have one order
+// A cell's residues in ascending order, so that sums have one order.  Cells of up to kShortCell residues by a thread
+// each, which inserts one after the other; those of more (narrow tables: 5 x 64 over 20 million coordinates has 51 000 in
+// a cell, where insertion would be 10^9 dependent steps) by a workgroup each, whose n log^2 n / 2 comparisons are independent
+// within a pass.
+constexpr uint32_t kShortCell = 32;
 __global__ void __launch_bounds__(kBlock) k_index_sort(uint32_t c, IndexRows rows, uint32_t* __restrict__ index) {
     uint32_t* start = index + rows.at[blockIdx.y];
     uint32_t* residue = start + c + 1;
     const uint32_t b = blockIdx.x * kBlock + threadIdx.x;
     if (b >= c) return;
     const uint32_t lo = start[b], hi = start[b + 1];
+    if (hi - lo > kShortCell) return;
     for (uint32_t e = lo + 1; e < hi; ++e) {
         const uint32_t x = residue[e];
         uint32_t at = e;
         for (; at > lo && residue[at - 1] > x; --at) residue[at] = residue[at - 1];
         residue[at] = x;
+    }
+}
+
+// Bitonic merges of runs of 2, 4, ... with every comparison towards ascending order (the first pass of a merge takes the
+// upper run backwards), so that places from n on, which would hold the largest values, are never touched.
+constexpr uint32_t kLongBlock = 1024;
+__global__ void __launch_bounds__(kLongBlock) k_index_sort_long(uint32_t c, uint32_t cells, IndexRows rows, uint32_t* index) {
+    const uint32_t* start = index + rows.at[blockIdx.y];
+    const uint32_t b0 = blockIdx.x * cells, b1 = b0 + cells < c ? b0 + cells : c;      // cells <= kLongBlock of a workgroup
+    const uint32_t mine = b0 + threadIdx.x;
+    if (!__syncthreads_or(mine < b1 && start[mine + 1] - start[mine] > kShortCell)) return;
+    for (uint32_t b = b0; b < b1; ++b) {
+        const uint32_t n = start[b + 1] - start[b];
+        if (n <= kShortCell) continue;
+        uint32_t* x = index + rows.at[blockIdx.y] + c + 1 + start[b];
+        uint32_t logn = 0;
+        while ((1ull << logn) < n) ++logn;
+        const uint32_t pairs = 1u << (logn - 1);
+        for (uint32_t run = 1; run <= logn; ++run) {
+            for (uint32_t step = run; step-- > 0;) {   // partners 2^step apart
+                const uint32_t low = (1u << step) - 1u;
+                for (uint32_t t = threadIdx.x; t < pairs; t += kLongBlock) {
+                    const uint32_t first = ((t & ~low) << 1) | (t & low);
+                    const uint32_t other = step + 1 == run ? first ^ ((2u << step) - 1u) : first + low + 1u;
+                    if (other < n) {
+                        const uint32_t u = x[first], v = x[other];
+                        if (u > v) {
+                            x[first] = v;
+                            x[other] = u;
+                        }
+                    }
+                }
+                __syncthreads();
+            }
+        }
     }
 }
 
@@ -244,6 +284,9 @@ int launch_index_build(const cs_params* p, uint32_t* index, hipStream_t stream) 
     k_index_scan<<<p->r, 1024, 0, stream>>>(kparams(p), rows, index);
     k_index_fill<<<grid, kBlock, 0, stream>>>(kparams(p), rows, index);
     k_index_sort<<<cells, kBlock, 0, stream>>>(p->c, rows, index);
+    uint32_t per = (p->c + 2047) / 2048;               // cells of a workgroup: one of a narrow table
+    per = per < kLongBlock ? per : kLongBlock;
+    k_index_sort_long<<<dim3((p->c + per - 1) / per, p->r), kLongBlock, 0, stream>>>(p->c, per, rows, index);
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 

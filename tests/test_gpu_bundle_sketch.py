@@ -67,6 +67,45 @@ def test_tables_merge_and_momentum(W, at_once, r, c, d):
         torch.testing.assert_close(only, S_t, rtol=0, atol=0)
 
 
+# cells of one and two residues up to 51 000 (a narrow table and a long vector); 15 to 33 on both sides of the sort by one
+# thread; 1024 cells and more a workgroup of the other one
+@pytest.mark.parametrize("r,c,d", [(5, 64, 4097), (5, 64, 100_000), (5, 64, 1_000_000), (5, 64, 20_000_000),
+                                   (5, 256, 300_000), (15, 1 << 12, 300_001), (3, 1 << 20, 20_000_000)])
+def test_index(r, c, d):
+    p = cs.cs_params_init(r, c, 190304488, d)
+    words = r * (c + 1) + sum(p.visit[j].gmax for j in range(r))
+    index = torch.full((words,), -1, dtype=torch.int32, device=DEV)
+    cs.cs_update_index_build(p, d, index.view(torch.uint8))
+    got, at, deepest = index.cpu().numpy(), 0, 0
+    for j in range(r):
+        n = p.visit[j].gmax
+        bucket, sign = torch.empty(r * n, dtype=torch.int32, device=DEV), torch.empty(r * n, dtype=torch.int8, device=DEV)
+        cs.cs_hash_debug_range(p, 0, n, bucket, sign)
+        cell = bucket.view(r, n)[j].cpu().numpy()
+        order = np.argsort(cell, kind="stable")          # by cell, ascending within one
+        start = np.searchsorted(cell[order], np.arange(c + 1))
+        np.testing.assert_array_equal(got[at:at + c + 1], start)
+        np.testing.assert_array_equal(got[at + c + 1:at + c + 1 + n], order)
+        at += c + 1 + n
+        deepest = max(deepest, np.diff(start).max())
+    assert at == words and (d != 20_000_000 or c != 64 or deepest > 50_000)
+
+
+def test_narrow_table():
+    """thousands of sums in a cell"""
+    r, c, d, W = 5, 64, 3_000_000, 2
+    p = cs.cs_params_init(r, c, 190304488, d)
+    gs = [torch.randn(d, generator=torch.Generator().manual_seed(w)).to(DEV) for w in range(W)]
+    words = r * (c + 1) + sum(p.visit[j].gmax for j in range(r))
+    index = torch.empty(4 * words, dtype=torch.uint8, device=DEV)
+    cs.cs_update_index_build(p, d, index)
+    T = torch.empty(cs.cs_bundle_floats(p, W), dtype=torch.float32, device=DEV)
+    cs.cs_bundle_sketch(p, T, gs, index, _workspace(p, W, d))
+    for w in range(W):
+        ref = sketch_in_slices(orc.SketchOracle(r, c, 190304488), gs[w].cpu().numpy(), 1.0)
+        assert_cells_close(T.view(r, c, G)[:, :, w].cpu().numpy(), ref, terms_per_cell=d / c)
+
+
 @pytest.mark.parametrize("W", [1, 2, 3, 8])
 @pytest.mark.parametrize("r,c,d", [(5, 1 << 12, 200_003), (3, 1 << 13, 400_003)])
 @pytest.mark.parametrize("below", [1, 0, -(1 << 28), 1 << 28])
