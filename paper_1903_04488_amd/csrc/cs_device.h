@@ -149,7 +149,8 @@ __device__ __forceinline__ bool segment_sum16(uint32_t key, float& v, int nsteps
 // any sorting network gives the same middle element; with a NaN among the values (every
 // comparison with it is false) the result depends on the sequence of comparisons, and this
 // sequence is the one a plain insertion sort with ">" makes: a NaN stays where it was put and
-// blocks what lies above it from moving down.  Infinities order as usual.
+// blocks what lies above it from moving down.  Infinities order as usual; -0 and +0 compare equal and keep their
+// order, which tells the sign of a median that is 0.
 template <int R>
 __device__ __forceinline__ float median_by_sort(float (&v)[R]) {
 #pragma unroll
@@ -219,38 +220,40 @@ __device__ __forceinline__ bool any_nan(const float (&v)[R]) {
     return nan;
 }
 
+// The selection, and the sort where one of the wavefront's medians depends on its sequence: there is a NaN among the
+// values, or the median is a zero (the instructions order -0 below +0, the sort has them equal).
 template <int R>
 __device__ __forceinline__ float median_odd(float (&v)[R]) {
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(any_nan(v)) != 0, 0)) return median_by_sort<R>(v);
-    return median_of_numbers<R>(v);
+    const float m = median_of_numbers<R>(v);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(any_nan(v) || m == 0.0f) != 0, 0)) return median_by_sort<R>(v);
+    return m;
 }
 
 // four medians, one check
 template <int R>
 __device__ __forceinline__ void medians_odd(const float (&a)[R], const float (&b)[R], const float (&c)[R], const float (&e)[R],
                                             float (&out)[4]) {
-    bool nan = any_nan(a);
-    nan |= any_nan(b);
-    nan |= any_nan(c);
-    nan |= any_nan(e);
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(nan) != 0, 0)) {
-#pragma unroll 1
-        for (int q = 0; q < 4; ++q) {
-            float t[R];
-#pragma unroll
-            for (int j = 0; j < R; ++j) t[j] = q == 0 ? a[j] : q == 1 ? b[j] : q == 2 ? c[j] : e[j];
-            const float x = median_by_sort<R>(t);
-            if (q == 0) out[0] = x;
-            else if (q == 1) out[1] = x;
-            else if (q == 2) out[2] = x;
-            else out[3] = x;
-        }
-        return;
-    }
     out[0] = median_of_numbers<R>(a);
     out[1] = median_of_numbers<R>(b);
     out[2] = median_of_numbers<R>(c);
     out[3] = median_of_numbers<R>(e);
+    bool sorted = out[0] == 0.0f || out[1] == 0.0f || out[2] == 0.0f || out[3] == 0.0f;
+    sorted |= any_nan(a);
+    sorted |= any_nan(b);
+    sorted |= any_nan(c);
+    sorted |= any_nan(e);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(sorted) == 0, 1)) return;
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+        float t[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) t[j] = q == 0 ? a[j] : q == 1 ? b[j] : q == 2 ? c[j] : e[j];
+        const float x = median_by_sort<R>(t);
+        if (q == 0) out[0] = x;
+        else if (q == 1) out[1] = x;
+        else if (q == 2) out[2] = x;
+        else out[3] = x;
+    }
 }
 
 }  // namespace cs

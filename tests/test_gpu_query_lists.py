@@ -7,6 +7,7 @@ import torch
 
 import paper_1903_04488_amd as cs
 from oracle import cs_oracle as orc
+from parity_util import estimate_in_slices
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -110,3 +111,34 @@ def test_medians_of_every_row_count(r, c, nan):
     cs.cs_sketch_estimate(p, S, est, 0, _scratch(cs.cs_estimate_workspace_bytes(p, d)))
     np.testing.assert_array_equal(sparse.cpu().numpy(), want)
     np.testing.assert_array_equal(est.cpu().numpy(), want)
+
+
+def _bits(x):
+    return x.view(torch.int32).cpu().numpy()
+
+
+# every kernel that takes a median: single coordinates hashed (d = 5003), lattice and its median of rows, the walk with the last row
+# fused, lists with and without whole lines
+@pytest.mark.parametrize("r,c,d", [(1, 64, 5003), (5, 64, 5003), (15, 97, 5003), (3, 1 << 10, 70_001), (15, 1 << 12, 300_001),
+                                   (5, 1 << 15, 1 << 24), (5, 30011, 3 << 19), (15, 250_007, 13_400_003)])
+@pytest.mark.parametrize("nan", [False, True])
+def test_the_sign_of_a_zero_median_is_that_of_the_sort(r, c, d, nan):
+    """-0 and +0 are equal and keep the order of the rows, whatever other coordinates of a wavefront hold; the oracle's
+    insertion sort in 64 bits has the same zeros"""
+    p = cs.cs_params_init(r, c, 7, d)
+    rng = np.random.default_rng(r * c)
+    T = rng.integers(-1, 2, (r, c)) * (rng.random((r, c)) < 0.5) * np.where(rng.random((r, c)) < 0.5, -1.0, 1.0)
+    if nan:
+        T[rng.integers(0, r), rng.integers(0, c)] = np.nan
+    S = torch.from_numpy(T.astype(np.float32)).to(DEV)
+    want = estimate_in_slices(orc.SketchOracle(r, c, 7), T, d)
+    number = ~np.isnan(want)
+    bits = want.astype(np.float32).view(np.int32)
+    assert {0, -(1 << 31)} <= set(bits[number].tolist())
+    est, sparse = torch.empty(d, device=DEV), torch.empty(d, device=DEV)
+    cs.cs_sketch_estimate_sparse(p, S, torch.arange(d, device=DEV), sparse)
+    for hist in (None, torch.empty(2048, dtype=torch.int64, device=DEV)):
+        cs.cs_sketch_estimate(p, S, est, 0, _scratch(cs.cs_estimate_scratch_bytes(p, d)), hist)
+        for got in (est, sparse):
+            np.testing.assert_array_equal(torch.isnan(got).cpu().numpy(), ~number)
+            np.testing.assert_array_equal(_bits(got)[number], bits[number])
