@@ -263,14 +263,15 @@ __global__ void __launch_bounds__(kBlock) k_gather_sums(GatherArgs a) {
     }
 }
 
-// lanes per cell: about 2^18 lanes in all
+// lanes per cell: about 2^18 lanes in all (16 from 4096 cells on: 7 x 1024, 108 000 coordinates, 7 workers, the whole update
+// with 4, 16, 64: 20.7, 19.3, 22.6 us; 5 x 512, 20 sums a cell: within 4 %)
 template <int WL>
 int launch_gather(const cs_params* p, const GatherArgs& a, hipStream_t stream) {
     const uint64_t cells = static_cast<uint64_t>(p->r) * p->c;
     auto grid = [&](unsigned per) { return dim3((p->c + per - 1) / per, p->r); };
     if (cells >= (1u << 17)) k_gather_sums<WL, 1><<<grid(kBlock), kBlock, 0, stream>>>(a);
     else if (cells >= (1u << 15)) k_gather_sums<WL, 4><<<grid(kBlock / 4), kBlock, 0, stream>>>(a);
-    else if (cells >= (1u << 13)) k_gather_sums<WL, 16><<<grid(kBlock / 16), kBlock, 0, stream>>>(a);
+    else if (cells >= (1u << 12)) k_gather_sums<WL, 16><<<grid(kBlock / 16), kBlock, 0, stream>>>(a);
     else k_gather_sums<WL, 64><<<grid(kBlock / 64), kBlock, 0, stream>>>(a);
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
@@ -353,33 +354,45 @@ bool params_ok(const cs_params* p) {
 
 using namespace cs;
 
-// Where the two passes take less time than clearing, requests and merge (us, update with merge: requests / two passes):
+// Where the two passes take less time than clearing, requests and merge (us, update with merge and momentum: requests / two
+// passes):
 //  * up to 4 workers, where a request carries 4 to 16 bytes and costs what one of 32 does: 1 worker, d = 2 M, 5 x 65 536:
-//    65 / 32; 2 workers, 25 M, 5 x 2^19: 332 / 254; 2 workers, 100 M, 5 x 2^20: 936 / 791; 4 workers, 2^20, 5 x 2^15: 45 / 32;
-//    30 M, 5 x 2^18: 436 / 426; unless the vectors take long to read and the requests little beside that: 4 workers,
-//    16 M, 5 x 32 768 (requests 0.29 of the reads at 24 G/s and 5 TB/s): 251 / 273; 30 M, 5 x 65 536: 429 / 449;
-//  * up to 16 workers and short vectors, whose time is requests, and three launches where one does: 8 workers, d = 30 000,
-//    5 x 512: 21 / 14; 16 workers, 300 000, 5 x 4096: 47 / 38; 16 workers, 2^20, 5 x 2^15: 111 / 98; (8 workers, 700 000,
-//    7 x 2^14: 50 / 54); from 3 million on even (8 workers, 3 M: 106 / 109; 6.5 M: 200 / 201; 16 workers, 11 M: 641 / 651),
-//    and with many groups of workers behind (39 workers, 106 000, 5 x 4096: 138 / 152);
-//    (of 55 shapes with r d below 10 million and 1 to 16 workers two passes are ahead in 41, by up to 1.8 times, and at most
-//    14 % behind: 5 workers, 9170, 7 x 64: 15 / 17);
+//    65 / 32; 2 workers, 25 M, 5 x 2^19: 332 / 254; 2 workers, 100 M, 5 x 2^20: 936 / 791; 4 workers, 2^20, 5 x 2^15: 46 / 34;
+//    unless the vectors take long to read and the requests little beside that (requests at 24 G/s, reads at 5 TB/s).
+//    4 workers, 16 M, 5 x 32 768 (0.29 of the reads): 260 / 285; 9 M, 5 x 16 384 (0.43): 132 / 150; 20 M, 3 x 2^19 (0.59):
+//    1.11 times; 3 workers, 18 M, 3 x 32 768 (0.40): 1.06 times;
+//  * up to 16 workers and short vectors, whose time is requests, and three launches where one does: 14 workers, 40 000, 5 x 64:
+//    53 / 33; 16 workers, 300 000, 5 x 4096: 49 / 39; 16 workers, 2^20, 5 x 2^15: 113 / 98; not with up to 8 rows (one launch of
+//    requests)
+//     - from r d = 5 million on with fewer than 2^15 columns, whose few requests hide behind the reads: 11 workers, 2.2 M,
+//       5 x 4096: 112 / 135; 12 workers, 1.4 M, 5 x 8192: 90 / 104;
+//     - from 130 000 to 600 000 with fewer than 400 coordinates per column, where launches are half of the time: 5 workers,
+//       76 000, 7 x 1024: 15.7 / 20.1; 15 workers, 47 000, 7 x 1024: 26 / 29;
+//    of 758 drawn shapes of 5 to 16 workers that leaves 562 to the two passes, ahead by 8 % on average (up to 1.7 times), 48 of
+//    them behind by more than 3 %; 18 of the others would have been ahead by more than 5 %;
+//  * 2 to 16 workers not with 64 columns, fewer than 200 coordinates per column and more than 0.4 sums per coordinate and row: a
+//    cell gathers hundreds of sums: 2 workers, 11 000, 5 x 64: 16 / 21; 11 workers, 10 800, 5 x 64: 29 / 41;
 //  * long vectors with tables that the memory-side cache does not hold beside them: 8 workers, 100 M, 5 x 2^20: 3284 / 3208;
 //    16 workers, 50 M, 5 x 2^19: 2963 / 2895; even at 25 M (1121 / 1118).
 // W = 0, a single vector into a table: against cs_sketch_zero and cs_sketch_accumulate, whose lattice form sends a request per
 // 8 to 15 coordinates.  Ahead from r d = 10 million on where the lists keep few sums: 5 x 65 536, d = 2.6 M, 0.14 sums per
 // coordinate and row: 51 / 33; 15 x 32 768, 1.3 M, 0.17: 112 / 75; 15 x 65 536, 1.8 M, 0.26: 101 / 144; 5 x 4096,
-// 460 000: 15 / 17.
+// 460 000: 15 / 17; more than 8 rows, a launch more, from 16 million on: 15 x 8192, 800 000: 39 / 50; 1.1 M: 72 / 60.
 static bool sums_pay(const cs_params* p, int32_t W, int64_t d) {
     double sums = 0.0;
     for (uint32_t j = 0; j < p->r; ++j) sums += static_cast<double>(p->visit[j].ncell) * static_cast<double>(p->visit[j].gmax);
-    const double rd = static_cast<double>(p->r) * static_cast<double>(d);
-    if (W == 0) return rd >= 1e7 && sums <= 0.2 * rd;
+    const double rd = static_cast<double>(p->r) * static_cast<double>(d), per_column = static_cast<double>(d) / p->c;
+    if (W == 0) return rd >= (p->r > 8 ? 1.6e7 : 1e7) && sums <= 0.2 * rd;
+    if (W > 1 && W <= 16 && p->c <= 64 && per_column < 200.0 && sums > 0.4 * rd) return false;
     if (W <= 4) {
         const double read_ns = 4.0 * rd * W / 5000.0;
-        return read_ns < 1e5 || sums / 24.0 >= 0.33 * read_ns;
+        return read_ns < 1e5 || sums / 24.0 >= (W == 4 ? 0.55 : 0.33) * read_ns;
     }
-    if (W <= 16 && rd <= 1e7) return true;
+    if (W <= 16 && rd <= 1e7) {
+        if (p->r > 8) return true;
+        if (rd >= 5e6) return p->c >= (1u << 15);
+        return rd < 1.3e5 || rd > 6e5 || per_column >= 400.0;
+    }
     return W <= 64 && d >= 32'000'000 && static_cast<uint64_t>(p->r) * p->c * CS_BUNDLE_GROUP * sizeof(float) >= (64u << 20);
 }
 

@@ -183,6 +183,22 @@ def test_state_is_advanced_while_the_path_has_a_momentum_factor(calls, monkeypat
         assert (tables["S_u"], tables["S_v"], tables["rho"]) == ("S_u", "S_v", rho)
 
 
+# shapes on both sides of every line of the rule, each where it was measured to be the faster one (W = 0: one vector)
+@pytest.mark.parametrize("W,d,r,c,two_passes", [
+    (1, 2_000_000, 5, 65_536, True), (4, 1 << 20, 5, 1 << 15, True), (4, 16_000_000, 5, 1 << 15, False),
+    (4, 9_054_897, 5, 1 << 14, False), (4, 20_279_047, 3, 1 << 19, True), (3, 18_219_159, 3, 1 << 15, True),
+    (16, 300_000, 5, 4096, True), (16, 1 << 20, 5, 1 << 15, True), (11, 2_244_359, 5, 4096, False),
+    (12, 1_353_347, 5, 8192, False), (7, 358_975, 15, 8192, True), (5, 75_740, 7, 1024, False), (15, 46_637, 7, 1024, False),
+    (14, 123_444, 5, 1024, True), (6, 18_193, 15, 1024, True), (8, 212_744, 5, 512, True), (14, 39_685, 5, 64, True),
+    (2, 11_187, 5, 64, False), (11, 10_840, 5, 64, False), (13, 24_449, 5, 64, True), (15, 5844, 7, 64, True),
+    (0, 2_600_000, 5, 65_536, True), (0, 460_000, 5, 4096, False), (0, 795_397, 15, 8192, False),
+    (0, 1_085_510, 15, 8192, True)])
+def test_the_way_of_an_update_is_the_faster_one(W, d, r, c, two_passes):
+    p = binding.cs_params_init(r, c, 190304488, d)
+    assert binding.cs_update_workspace_bytes(p, max(W, 1), d) > 0
+    assert (binding.cs_update_index_bytes(p, W, d) > 0) == two_passes
+
+
 @pytest.mark.parametrize("d", [784, 32_768, 32_769])
 def test_counts_by_magnitude_are_there_for_vectors_of_any_length(calls, d):
     """up to CS_TOPK_SMALL_D neither the estimate nor the selection is given the counts; whoever reads
