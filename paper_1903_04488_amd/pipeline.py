@@ -15,6 +15,8 @@ short vectors for whoever asks).
 """
 from __future__ import annotations
 
+import ctypes
+
 import torch
 
 from . import binding as B
@@ -98,17 +100,23 @@ class HotPath:
         self._sums_ws = torch.empty(need, dtype=torch.uint8, device=self.device)
         self._index = torch.empty(n, dtype=torch.uint8, device=self.device)
         B.cs_update_index_build(self.params, self.d, self._index)
-        self._sums_params = bytes(self.params)
+        self._sums_params = self._lists()
         self._sums_for = self.fold_workers, W, self.d
 
+    def _lists(self):
+        """the parameters as they are now, byte for byte, up to the visit lists of the last row (what lies behind is
+        for column counts that have no index)"""
+        n = B.CsParams.visit.offset + self.r * ctypes.sizeof(B.CsVisitPlan)
+        return memoryview(self.params).cast("B")[:n].tobytes()
+
     def _indexed(self, g_w):
-        """The vectors and the sketch are those that the index and its workspace were made for.  (The parameters as they
-        are now, byte for byte, 1 us: whoever gives a path another sketch may do so by replacing them or in place.)"""
+        """The vectors and the sketch are those that the index and its workspace were made for.  (Whoever gives a path
+        another sketch may do so by replacing its parameters or in place.)"""
         if self._index is None:
             return False
         fold, W, d = self._sums_for
         return (self.fold_workers == fold and (fold or len(g_w) == W) and g_w[0].numel() == d
-                and bytes(self.params) == self._sums_params)
+                and self._lists() == self._sums_params)
 
     def _mean(self, g_w):
         """the mean of folded workers, in scratch"""

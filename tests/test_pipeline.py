@@ -12,6 +12,7 @@ def calls(monkeypatch):
     """names of the library calls that the pipeline makes, in order, with their arguments"""
     made = []
     fake = types.SimpleNamespace(**{n: getattr(binding, n) for n in dir(binding) if n.startswith("CS_")})
+    fake.CsParams, fake.CsVisitPlan = binding.CsParams, binding.CsVisitPlan
     fake.DeviceVectors = lambda vectors, name=None: list(vectors)
     for name in dir(binding):
         if name.startswith("cs_"):
