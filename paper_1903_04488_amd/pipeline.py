@@ -26,7 +26,7 @@ class HotPath:
     # the update by way of running sums (cs_bundle_sketch), where the sketch has lists for it: its index, its
     # workspace, and what they were made for: the sketch's parameters, fold_workers, W and d
     _index = _sums_ws = _sums_params = _sums_for = None
-    SUMS_OWN_BYTES = 256 << 20           # the workspace: up to here, or up to what the query's scratch takes
+    SUMS_OWN_BYTES = 2 << 30             # the workspace: up to here, else the path does without (0: in any case)
 
     def __init__(self, d: int, W: int, r: int, c: int, k: int, seed: int,
                  rho: float | None = None, device="cuda:0", P: int = 1, fold_workers: bool = False):
@@ -36,7 +36,11 @@ class HotPath:
         (every vector is read once; the sum goes into d floats of scratch, then straight into
         S_t): no worker tables, no merge.  The scratch is the query's, so the stages of one
         path run one after the other; where the query has none (short vectors and column counts
-        without a traversal plan) the path holds d floats more."""
+        without a traversal plan) the path holds d floats more.
+        Memory beside the tables and est: the query's scratch (r d floats for long vectors), and where the update goes
+        by way of running sums (up to 4 workers, up to 16 with short vectors, up to 64 with vectors of 32 million on)
+        their index and workspace, 35 MB at d = 6.5 M, W = 4, 5 x 2^17 and 1.9 GB at d = 10^8, W = 32, 5 x 2^20, where they
+        save 1.8 % of the update: SUMS_OWN_BYTES, of the class or a subclass, bounds the workspace."""
         self.d, self.W, self.r, self.c, self.k = d, W, r, c, k
         self.P = P
         self.fold_workers = fold_workers
@@ -94,7 +98,7 @@ class HotPath:
             return
         W = 1 if self.fold_workers else self.W
         need = B.cs_update_workspace_bytes(self.params, W, self.d)
-        if need > max(self.SUMS_OWN_BYTES, self.est_ws.numel() if self.est_ws is not None else 0):
+        if need > self.SUMS_OWN_BYTES:
             return
         # (memory of its own, not the query's scratch: an update may run beside the query of the step before)
         self._sums_ws = torch.empty(need, dtype=torch.uint8, device=self.device)

@@ -103,7 +103,8 @@ def test_folded_workers_are_all_summed_whenever_folding_was_chosen(calls, W, giv
         assert out.data_ptr() == path.est_ws.data_ptr()
 
 
-@pytest.mark.parametrize("scratch,need,built", [(5000, 4000, True), (0, 4000, True), (5000, 5001, False)])
+@pytest.mark.parametrize("scratch,need,built", [(5000, 4000, True), (0, 4000, True), (5000, 5001, False),
+                                                (5000, 4600, False), (5000, 4500, True)])
 @pytest.mark.parametrize("fold", [False, True])
 def test_an_update_may_run_beside_the_query_of_the_step_before(monkeypatch, fold, scratch, need, built):
     """on another stream: its running sums don't lie in the query's scratch, which that query still reads"""
