@@ -359,8 +359,9 @@ using namespace cs;
 //  * up to 4 workers, where a request carries 4 to 16 bytes and costs what one of 32 does: 1 worker, d = 2 M, 5 x 65 536:
 //    65 / 32; 2 workers, 25 M, 5 x 2^19: 332 / 254; 2 workers, 100 M, 5 x 2^20: 936 / 791; 4 workers, 2^20, 5 x 2^15: 46 / 34;
 //    unless the vectors take long to read and the requests little beside that (requests at 24 G/s, reads at 5 TB/s).
-//    4 workers, 16 M, 5 x 32 768 (0.29 of the reads): 260 / 285; 9 M, 5 x 16 384 (0.43): 132 / 150; 20 M, 3 x 2^19 (0.59):
-//    1.11 times; 3 workers, 18 M, 3 x 32 768 (0.40): 1.06 times;
+//    3 workers, 23 M, 3 x 65 536 (0.23 of the reads): 178 / 209; 18 M, 3 x 32 768 (0.40): 164 / 154; with 4 workers also from 130
+//    coordinates per column on, whatever the requests: 9 M, 5 x 16 384 (0.43): 132 / 150; 9.4 M, 15 x 65 536 (0.69): 474 / 511;
+//    against 7.1 M, 5 x 65 536 (0.44): 144 / 131; 20 M, 3 x 2^19 (0.59): 257 / 231; 60 M, 5 x 2^20 (0.64): 1121 / 1013;
 //  * up to 16 workers and short vectors, whose time is requests, and three launches where one does: 14 workers, 40 000, 5 x 64:
 //    53 / 33; 16 workers, 300 000, 5 x 4096: 49 / 39; 16 workers, 2^20, 5 x 2^15: 113 / 98; not with up to 8 rows (one launch of
 //    requests)
@@ -386,7 +387,7 @@ static bool sums_pay(const cs_params* p, int32_t W, int64_t d) {
     if (W > 1 && W <= 16 && p->c <= 64 && per_column < 200.0 && sums > 0.4 * rd) return false;
     if (W <= 4) {
         const double read_ns = 4.0 * rd * W / 5000.0;
-        return read_ns < 1e5 || sums / 24.0 >= (W == 4 ? 0.55 : 0.33) * read_ns;
+        return read_ns < 1e5 || (sums / 24.0 >= 0.33 * read_ns && (W < 4 || per_column < 130.0));
     }
     if (W <= 16 && rd <= 1e7) {
         if (p->r > 8) return true;

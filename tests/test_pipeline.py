@@ -188,7 +188,8 @@ def test_state_is_advanced_while_the_path_has_a_momentum_factor(calls, monkeypat
 # shapes on both sides of every line of the rule, each where it was measured to be the faster one (W = 0: one vector)
 @pytest.mark.parametrize("W,d,r,c,two_passes", [
     (1, 2_000_000, 5, 65_536, True), (4, 1 << 20, 5, 1 << 15, True), (4, 16_000_000, 5, 1 << 15, False),
-    (4, 9_054_897, 5, 1 << 14, False), (4, 20_279_047, 3, 1 << 19, True), (3, 18_219_159, 3, 1 << 15, True),
+    (4, 9_054_897, 5, 1 << 14, False), (4, 20_279_047, 3, 1 << 19, True), (4, 9_378_155, 15, 65_536, False),
+    (4, 7_062_633, 5, 65_536, True), (3, 18_219_159, 3, 1 << 15, True), (3, 22_656_597, 3, 65_536, False),
     (16, 300_000, 5, 4096, True), (16, 1 << 20, 5, 1 << 15, True), (11, 2_244_359, 5, 4096, False),
     (12, 1_353_347, 5, 8192, False), (7, 358_975, 15, 8192, True), (5, 75_740, 7, 1024, False), (15, 46_637, 7, 1024, False),
     (14, 123_444, 5, 1024, True), (6, 18_193, 15, 1024, True), (8, 212_744, 5, 512, True), (14, 39_685, 5, 64, True),
