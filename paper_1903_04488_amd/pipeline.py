@@ -100,7 +100,8 @@ class HotPath:
         need = B.cs_update_workspace_bytes(self.params, W, self.d)
         if need > self.SUMS_OWN_BYTES:
             return
-        # (memory of its own, not the query's scratch: an update may run beside the query of the step before)
+        # (memory of its own, not the query's scratch: accumulate alone, workers not folded, may run beside the query
+        # of the step before; folded workers' mean lies in that scratch, and the later stages write what the query reads)
         self._sums_ws = torch.empty(need, dtype=torch.uint8, device=self.device)
         self._index = torch.empty(n, dtype=torch.uint8, device=self.device)
         B.cs_update_index_build(self.params, self.d, self._index)

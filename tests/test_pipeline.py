@@ -106,8 +106,8 @@ def test_folded_workers_are_all_summed_whenever_folding_was_chosen(calls, W, giv
 @pytest.mark.parametrize("scratch,need,built", [(5000, 4000, True), (0, 4000, True), (5000, 5001, False),
                                                 (5000, 4600, False), (5000, 4500, True)])
 @pytest.mark.parametrize("fold", [False, True])
-def test_an_update_may_run_beside_the_query_of_the_step_before(monkeypatch, fold, scratch, need, built):
-    """on another stream: its running sums don't lie in the query's scratch, which that query still reads"""
+def test_running_sums_have_memory_of_their_own_up_to_a_limit(monkeypatch, fold, scratch, need, built):
+    """whatever the query's scratch takes, and not in it"""
     monkeypatch.setattr(pipeline.B, "cs_update_index_bytes", lambda p, W, d: 64)
     monkeypatch.setattr(pipeline.B, "cs_update_workspace_bytes", lambda p, W, d: need)
     monkeypatch.setattr(pipeline.B, "cs_update_index_build", lambda p, d, index: None)
@@ -120,6 +120,27 @@ def test_an_update_may_run_beside_the_query_of_the_step_before(monkeypatch, fold
         ws, own = path._sums_ws, path.est_ws
         assert ws.numel() == need
         assert ws.data_ptr() + need <= own.data_ptr() or own.data_ptr() + scratch <= ws.data_ptr()
+
+
+@pytest.mark.parametrize("index", [False, True])
+def test_tables_of_workers_may_be_made_beside_the_query_of_the_step_before(calls, monkeypatch, index):
+    """accumulate alone, workers not folded: no memory that it is given is the query's"""
+    def memory(n):
+        return torch.empty(n, dtype=torch.uint8)
+    path = with_index(monkeypatch, S_t=memory(9), S_u=memory(9), S_v=memory(9), T=memory(9), est=memory(9), est_ws=memory(9),
+                      _counts=memory(9), d=100_000, params=binding.cs_params_init(5, 64, 3, 100_000))
+    if not index:
+        path._index = None
+    path.accumulate([torch.zeros(path.d)] * path.W)
+    assert ("cs_bundle_sketch" in names(calls)) == index
+    given = [t for _, a, kw in calls for t in (*a, *kw.values())]
+    given = [t for g in given for t in (g if isinstance(g, (list, tuple)) else [g]) if isinstance(t, torch.Tensor)]
+    calls.clear()
+    path.estimate()
+    query = [t for _, a, kw in calls for t in (*a, *kw.values()) if isinstance(t, torch.Tensor)]
+    assert len(query) == 4                               # the table asked, est, scratch, counts
+    assert path.T.data_ptr() in {t.data_ptr() for t in given}
+    assert not {t.data_ptr() for t in given} & {t.data_ptr() for t in query}
 
 
 def with_index(monkeypatch, cls=pipeline.HotPath, **attributes):
