@@ -99,7 +99,7 @@ typedef struct cs_visit_plan {
     uint64_t cost;              /* estimated time of one launch with this list, nanoseconds */
     uint64_t cost_walk;         /* the same for the stride walk with cs_row_plan.Dw */
     uint64_t gap[4];            /* gap value per code */
-    uint64_t A[4], As[4];       /* (a_j * gap) mod p, (a'_j * gap) mod p per code */
+    uint64_t A[4], As[4];       /* (a_j * gap) mod p, (a'_j * gap) mod p per code (the kernels do not read them) */
     uint32_t code[CS_MAX_VISITS / 16];   /* 2 bits per visit, visit k in word k / 16 */
 } cs_visit_plan;
 

@@ -978,10 +978,11 @@ int launch_visits_run(LIST& rows, const VisitWorkers& a, int nrows, uint32_t nce
     const dim3 grid(visits_grid<WL, RUN, NWAVE>(rows, nrows)), block(64 * NWAVE);
     const size_t lds = most_steps(rows, nrows) * sizeof(uint4);
     constexpr bool pow2 = std::is_same<LIST, VisitRows>::value;
-    if (!(a.sums ? pow2 : a.T != nullptr)) return CS_EINVAL;            // running sums: power-of-two columns only
+    constexpr bool partial = pow2 && WL > 1;           // running sums: power-of-two columns (and one vector: k_accumulate_one)
+    if (!(a.sums ? partial : a.T != nullptr)) return CS_EINVAL;
     auto launch = [&](auto nc) {
         constexpr int NC = decltype(nc)::value;
-        if constexpr (pow2) {
+        if constexpr (partial) {
             if (a.sums) {
                 k_accumulate_visits<WL, RUN, NWAVE, NC, true, LIST><<<grid, block, lds, stream>>>(rows, a);
                 return;
@@ -2104,14 +2105,10 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
 // up to kAnycRowsPerLaunch rows per launch (one row's wavefronts alone fill a third to two
 // thirds of the chip, and every launch has the tail of its longest chain of visits), then the
 // last row together with the median.  The rows of a launch use the same number of cells.
-// hist (or null): cleared, and receives the counts of est by magnitude bin
+// hist (or null): cleared, and receives the counts of est by magnitude bin.  3 rows or more (anyc_visits_serve_query).
 int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t i0, float* est,
                          float* rows, uint64_t* hist, hipStream_t stream) {
     unsigned long long* h = reinterpret_cast<unsigned long long*>(hist);
-    if (h && p->r == 1) {                              // (no kernel of rows 0 .. r-2 clears them)
-        const int rc = launch_magnitude_hist_zero(hist, stream);
-        if (rc != CS_OK) return rc;
-    }
     auto grid_x = [](uint64_t gmax) {
         const int64_t span = 64 * kQRun * kQueryWaves;
         const int64_t nsets = (static_cast<int64_t>(gmax) + span - 1) / span;
@@ -2171,7 +2168,7 @@ int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t 
         else { CS_LASTQ(R_, 4, false); }                                                             \
         break;
     switch (p->r) {
-        CS_LASTR(1) CS_LASTR(3) CS_LASTR(5) CS_LASTR(7) CS_LASTR(9) CS_LASTR(11) CS_LASTR(13) CS_LASTR(15)
+        CS_LASTR(3) CS_LASTR(5) CS_LASTR(7) CS_LASTR(9) CS_LASTR(11) CS_LASTR(13) CS_LASTR(15)
         default: return CS_EINVAL;
     }
 #undef CS_LASTR
