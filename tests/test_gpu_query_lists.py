@@ -74,6 +74,29 @@ def test_query_in_whole_lines(r, c, d, of_rows, of_est):
     assert torch.equal(hist, torch.bincount(bins, minlength=2048))
 
 
+# the same where the lower bits of a hash decide: of a residue of a wavefront's own, and of one of the line behind them that it
+# writes as well (lists with one cell and, the second case, with two cells per wrap)
+@pytest.mark.parametrize("r,c,d", [(5, 180_000, 40_000_001), (15, 250_007, 13_400_003)])
+@pytest.mark.parametrize("row", [0, -1])
+@pytest.mark.parametrize("residue", [5, 256 + 21])
+@pytest.mark.parametrize("below", [1, 0, 1 << 28])
+@pytest.mark.parametrize("sign", [False, True])
+def test_query_in_whole_lines_at_the_thresholds(r, c, d, row, residue, below, sign):
+    p = cs.cs_params_init(r, c, 190304488, d)
+    j = row % r
+    k = p.anyc[j].K // 2
+    a, b = (p.as_[j], p.bs[j]) if sign else (p.a[j], p.b[j])
+    s = int(sum(p.anyc[j].gaps()[:k]))
+    i0 = ((P - a * s % P - below - b) * pow(a, -1, P) - residue) % P
+    if i0 > P - d:                                   # (not reachable with a global index)
+        pytest.skip("index base beyond the range of the entry point")
+    S = torch.randn(r, c, generator=torch.Generator().manual_seed(d)).to(DEV)
+    want, got = torch.empty(d, device=DEV), torch.empty(d + 1, device=DEV)
+    cs.cs_sketch_estimate_sparse(p, S, torch.arange(i0, i0 + d, device=DEV), want)
+    cs.cs_sketch_estimate(p, S, got[1:], i0, _scratch(cs.cs_estimate_scratch_bytes(p, d)))
+    assert torch.equal(got[1:], want)
+
+
 # strides that differ by a factor of 250 between the rows (one row of 8 wavefronts in 256 segments beside rows of
 # 1100 in one), the shortest vector that is walked, and the lengths on both sides of the fused last row
 @pytest.mark.parametrize("r,c,d", [(15, 1 << 16, 2_000_000), (5, 1 << 15, 1 << 20), (3, 64, 4096), (1, 1 << 10, 70_001),
