@@ -139,8 +139,7 @@ def input_arenas_in_fast_memory(torch, B, hp, cfg, dev, n_sets):
     same update on the same data takes 13.0 ms on vectors within the first 100 GB and 11.8 ms on
     vectors beyond.  So the input sets are not simply allocated next.  This step allocates chunks
     of the size of one input set one after the other, fills them, and times a probe on each (the
-    stride-walk update of the chunk's W vectors into the step's own worker tables: the access
-    pattern of the step's update, under a kernel name of its own in a trace), until n_sets
+    step's own update of the chunk's W vectors), until n_sets
     chunks are within 0.6 % of the fastest and at least 4 % faster than the slowest.  Those
     become the input sets; the other chunks are freed.  The search goes on for n_sets + 10 chunks
     (one part alone is 8 chunks of 12.8 GB); when no chunk stands out by then, the first n_sets
@@ -151,14 +150,12 @@ def input_arenas_in_fast_memory(torch, B, hp, cfg, dev, n_sets):
     chunk_bytes = 4 * cfg.d * cfg.W
     if cfg.W < 8 or chunk_bytes < (2 << 30) or not B.cs_bundle_update_launches(hp.params, 8, cfg.d):
         return None, [], [], None
-    walk = B.CsParams.from_buffer_copy(hp.params)
-    walk.flags |= B.CS_FLAG_NO_VISIT_LIST
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
 
     def probe(vecs):
-        B.cs_sketch_accumulate_bundle(walk, hp.T, vecs)
+        hp.accumulate(vecs)
         e0.record()
-        B.cs_sketch_accumulate_bundle(walk, hp.T, vecs)
+        hp.accumulate(vecs)
         e1.record()
         torch.cuda.synchronize()
         return e0.elapsed_time(e1)
@@ -243,9 +240,8 @@ def main():
         l2sq = torch.empty(1 + cfg.r, dtype=torch.float64, device=dev)
         n_heavy = torch.empty(1, dtype=torch.int64, device=dev)
     else:
-        hp = HotPath(cfg.d, cfg.W, cfg.r, cfg.c, cfg.k, cfg.hash_seed, rho=cfg.rho, device=dev)
-        # (the worker tables stay allocated either way: the placement probe below uses them)
-        hp.fold_workers = variant == "fused-merge"
+        hp = HotPath(cfg.d, cfg.W, cfg.r, cfg.c, cfg.k, cfg.hash_seed, rho=cfg.rho, device=dev,
+                     fold_workers=variant == "fused-merge")
 
     # inputs resident in HBM before the timed region: a few distinct steps' worth, cycled
     bytes_per_set = 4 * cfg.d * cfg.W
@@ -267,12 +263,15 @@ def main():
         sets = sets_in(arenas)
     torch.cuda.synchronize()
 
-    # stage names per variant; stage i runs between events i and i + 1.  Stage 0 is always the
-    # update (zeroing the worker tables belongs to it); the batched update itself is bracketed
-    # by its own pair of events (ev[8], ev[9]) for the roofline figure.
-    stages = {"sketch-state": ["accumulate", "merge", "momentum", "estimate", "topk", "gather", "feedback"],
-              "fused-merge": ["accumulate", "-", "momentum", "estimate", "topk", "gather", "feedback"],
-              "top-pk": ["accumulate", "merge", "momentum", "estimate", "topk", "gather+select", "feedback"],
+    # stage names per variant; stage i runs between events i and i + 1.  The stages of HotPath.step are called as it
+    # calls them; where its update goes by way of running sums, merge and momentum come out of the pass that gathers
+    # them.  The update itself (all of it, or without the clearing of worker tables where requests add to them) is
+    # bracketed by its own pair of events (ev[8], ev[9]) for the roofline figure.
+    by_sums = hp._index is not None
+    sketch = ["accumulate+merge+momentum", "-", "-"] if by_sums else ["accumulate", "merge+momentum", "-"]
+    stages = {"sketch-state": [*sketch, "estimate", "topk", "gather", "feedback"],
+              "fused-merge": [*sketch, "estimate", "topk", "gather", "feedback"],
+              "top-pk": [*sketch, "estimate", "topk", "gather+select", "feedback"],
               "dense-state": ["dense_momentum", "accumulate", "merge", "estimate", "topk", "gather", "mask"],
               "heavymix": ["accumulate", "merge", "l2sq", "estimate", "heavymix_select", "gather", "-"]}[variant]
 
@@ -282,7 +281,7 @@ def main():
                 ev[i].record()
 
         def update(vecs):
-            if hp.fold_workers:
+            if hp.fold_workers or by_sums:
                 mark(8)
                 hp.accumulate(vecs)
                 mark(9)
@@ -311,9 +310,14 @@ def main():
             hp.gather(g_w); mark(6)
             mark(7)
         else:
-            update(g_w); mark(1)
-            hp.merge(); mark(2)
-            hp.momentum(); mark(3)
+            if by_sums:
+                mark(8)
+                hp.sketch_and_aggregate(g_w)
+                mark(9); mark(1); mark(2)
+            else:
+                update(g_w); mark(1)
+                hp.aggregate(); mark(2)
+            mark(3)
             hp.estimate(); mark(4)
             hp.topk(); mark(5)
             hp.gather(g_w); mark(6)
@@ -352,8 +356,10 @@ def main():
     # the update runs as a few launches per group of 8 workers (rows that share a traversal
     # share a launch); the algorithmic bytes of the whole update (every gradient read once,
     # every worker table written once) are spread evenly over those launches
-    # (folded workers: one call of several different kernels, taken as a whole)
-    n_launch = 1 if hp.fold_workers else B.cs_bundle_update_launches(hp.params, cfg.W, cfg.d)
+    # (folded workers: one call of several different kernels, taken as a whole; by running sums: a launch per group and
+    # 8 rows, with its share of the pass that gathers them)
+    n_launch = (1 if hp.fold_workers else (cfg.W + 7) // 8 * ((cfg.r + 7) // 8) if by_sums
+                else B.cs_bundle_update_launches(hp.params, cfg.W, cfg.d))
     acc_kernel_ms = sum(ev[8].elapsed_time(ev[9]) for ev in events) / args.steps / n_launch
     per_set = [[] for _ in range(n_sets)]         # the update's time on each resident input set
     for t, ev in enumerate(events):
@@ -388,7 +394,7 @@ def main():
     stream_one = read_rate(sets[0][:1], 8)
     stream_set = read_rate(sets[0], 3)
     # (measured for the update into worker tables; the fused-merge variant writes one table instead)
-    traffic = MEASURED_TRAFFIC_BYTES.get(cfg.cfg) if variant != "fused-merge" else None
+    traffic = MEASURED_TRAFFIC_BYTES.get(cfg.cfg) if variant != "fused-merge" and not by_sums else None
 
     out = {
         "metric": METRIC,
@@ -411,7 +417,7 @@ def main():
         "pct_stream_read_whole_step": 100.0 * step_alg_bytes / (ms_per_step * 1e-3) / 1e9 / stream_set,
         "stream_read": {"one_vector_GBs": stream_one, "one_input_set_GBs": stream_set,
                         "kernel": "cs_probe_stream_read (plain 16-byte loads)"},
-        "placement": {"probe": "stride-walk update of successive chunks of one input set's size",
+        "placement": {"probe": "the step's update of successive chunks of one input set's size",
                       "probe_ms": [round(t, 3) for t in probe_ms],
                       "chunks_used_for_inputs": chosen,
                       "update_ms_per_input_set": update_ms_per_set,
@@ -421,12 +427,13 @@ def main():
                       "note": "plain_*: the same timed steps with the inputs allocated in the plain "
                               "order of a fresh process (the first chunks), before the headline run"},
         "stage_ms": stage_ms,
-        "stage_Gcoords_s": {name: (cfg.W if name in ("accumulate", "dense_momentum") else 1) * cfg.d
+        "stage_Gcoords_s": {name: (cfg.W if name.startswith(("accumulate", "dense_momentum")) else 1) * cfg.d
                             / (stage_ms[name] * 1e-3) / 1e9
-                            for name in ("accumulate", "dense_momentum", "estimate", "topk", "heavymix_select")
+                            for name in ("accumulate", "accumulate+merge+momentum", "dense_momentum", "estimate", "topk", "heavymix_select")
                             if stage_ms.get(name)},
         "roofline": {
-            "kernel": ("HotPath.accumulate (k_vectors_sum, then k_accumulate_one)" if variant == "fused-merge"
+            "kernel": ("cs_vectors_sum and the sketch of the sum" if variant == "fused-merge"
+                       else "cs_bundle_sketch (k_accumulate_visits into running sums, k_gather_sums)" if by_sums
                        else "k_accumulate_visits (all launches of cs_sketch_accumulate_bundle)"),
             "bound": "hbm",
             "achieved": achieved,
