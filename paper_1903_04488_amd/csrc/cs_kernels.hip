@@ -40,6 +40,14 @@ inline unsigned grid_of_hashes(int64_t d, int slots, int64_t groups = 1) {
     return grid_for(d, few ? slots : slots * 8, 256 * 8);
 }
 
+// Tables of several groups of workers with few columns and many coordinates for each: their requests wait for one another at
+// the same few cells, the longer the more of them are sent at once (us, tables with 8 coordinates a thread / one: 17 workers,
+// 5 x 32, d = 7895 15.6 / 22.3; 127, 7 x 33, 7541 63 / 107; 153, 3 x 33, 2533 (77 a column) 38 / 40; 132, 5 x 33, 2223 (67) 41 / 37;
+// one group, 7 workers, 5 x 33, 6029 12.7 / 12.7; 152 workers, 3 x 91, 6663 62 / 55).
+inline bool crowded_cells(const cs_params* p, int64_t d, int64_t groups) {
+    return groups > 1 && p->c < 80 && d >= static_cast<int64_t>(75) * p->c;
+}
+
 // Dispatch on the (odd) row count and on "c is a power of two" so that the hash state of all
 // rows lives in registers and loops over rows are unrolled.
 #define CS_DISPATCH_R(p, CALL)                                                     \
@@ -820,7 +828,8 @@ extern "C" int cs_sketch_accumulate_bundle(const cs_params* p, float* T, int32_t
         float* T0 = T + (w0 / CS_BUNDLE_GROUP) * group_floats;
         // at least ~8 coordinates per lane so the per-lane hash set-up is amortised
         const int groups = (nw + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP;
-        const dim3 grid(grid_of_hashes(d, kSlots, groups), static_cast<unsigned>(groups));
+        const dim3 grid(crowded_cells(p, d, groups) ? grid_for(d, kSlots * 8, 256 * 8) : grid_of_hashes(d, kSlots, groups),
+                        static_cast<unsigned>(groups));
         if (lds_table_applies(p, d)) {
             const dim3 lgrid(grid_for(d, kSlots * 8, 512), grid.y);
             const size_t lds = static_cast<size_t>(p->r) * p->c * CS_BUNDLE_GROUP * sizeof(float);
