@@ -1088,7 +1088,10 @@ int launch_visits_anyc(const cs_params* p, const VisitWorkers& a, const uint32_t
 // the wait for a visit's values counts the loads behind them.
 // At the end the NC sums of a residue, which lie in neighbouring cells, are brought to
 // neighbouring lanes, so that they leave as one request (an aligned 64-byte block touched by an
-// instruction is one) instead of NC.  A workgroup of kOneWaves wavefronts shares one table of visits.
+// instruction is one) instead of NC.  A workgroup of kOneWaves wavefronts shares one table of visits; launches of fewer than
+// kOneFewWaves wavefronts have workgroups of one, which spread them over more CUs (us, 4 / 1: 21 wavefronts, 3 x 512,
+// d = 203 680 16.9 / 12.8; 138, 5 x 707, 326 476 41.8 / 29.2; 269, 5 x 2048, 304 889 17.3 / 14.7; 338, 5 x 2401, 224 320
+// 24.8 / 26.0; 642, 5 x 2641, 747 318 36.7 / 41.7; two launches of 16 000, 15 x 131 072, 31 M 536 / 572).
 // Measured (update alone, in us; with two 61-bit states per coordinate and a load for every visit of the list, taken
 // part in or not -> now): d = 73 M, 5 x 2^20 468 -> 326; d = 25 M, 5 x 2^19 176 -> 137; d = 11 M, 5 x 2^18 102 -> 74;
 // d = 73 M, 5 x 180 000 492 -> 445.  Bound: the requests at the end (without them 216, 92, 43 and 227 us, which
@@ -1097,11 +1100,12 @@ int launch_visits_anyc(const cs_params* p, const VisitWorkers& a, const uint32_t
 constexpr int kOneRun = 4;
 constexpr int kOneAhead = 3;
 constexpr int kOneWaves = 4;
+constexpr int64_t kOneFewWaves = 300;
 
 // PARTIAL: the sums go to a workspace, [piece][residue][running sum], instead of being added to the table
 // (cs_index.hip).
-template <int NC, bool PARTIAL, typename LIST>
-__global__ void __launch_bounds__(64 * kOneWaves)
+template <int NC, int NWAVE, bool PARTIAL, typename LIST>
+__global__ void __launch_bounds__(64 * NWAVE)
 k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, uint32_t c,
                  int cell_floats, int64_t d, int64_t i0, float scale) {
     constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
@@ -1113,8 +1117,8 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
     const int lane = threadIdx.x & 63;
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wavefront-uniform
     extern __shared__ uint4 steps[];                   // the visits of my piece
-    __shared__ __attribute__((aligned(16))) float sum_lds_all[kOneWaves][NC][SPAN];
-    __shared__ uint32_t first_lds_all[PARTIAL ? 1 : kOneWaves][SPAN];  // first cell of a residue
+    __shared__ __attribute__((aligned(16))) float sum_lds_all[NWAVE][NC][SPAN];
+    __shared__ uint32_t first_lds_all[PARTIAL ? 1 : NWAVE][SPAN];  // first cell of a residue
     float (*parked)[SPAN] = sum_lds_all[wq];
     uint32_t* first = first_lds_all[PARTIAL ? 0 : wq];
     const Columns col = columns_of<POW2>(c);
@@ -1139,17 +1143,17 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
     if constexpr (PARTIAL) at = v.at;
     float* __restrict__ Sj = S + at;
     const int64_t nwaves = (static_cast<int64_t>(v.gmax) + SPAN - 1) / SPAN;
-    const int64_t nsets = (nwaves + kOneWaves - 1) / kOneWaves;
+    const int64_t nsets = (nwaves + NWAVE - 1) / NWAVE;
     const uint32_t k0 = v.K * piece / v.pieces, k1 = v.K * (piece + 1) / v.pieces;
     VisitPlaces places;
     places.init(v);
-    const uint32_t listed = fill_visit_steps<POW2, kOneWaves>(steps, places, v, k0, k1, col, omega);
+    const uint32_t listed = fill_visit_steps<POW2, NWAVE>(steps, places, v, k0, k1, col, omega);
     const uint32_t last4 = static_cast<uint32_t>(d) - kOneRun;
 
     // sets of neighbouring wavefronts go to one XCD, as in k_accumulate_visits
     for (int64_t vi = block; ; vi += v.blocks) {
         if (visit_round(vi, v.blocks) >= nsets) break;
-        const int64_t wv = visit_set(vi, v.blocks) * kOneWaves + wq;
+        const int64_t wv = visit_set(vi, v.blocks) * NWAVE + wq;
         if (wv >= nwaves) continue;
         const uint32_t wave_res = static_cast<uint32_t>(wv * SPAN);
         const uint32_t my_res = wave_res + lane * kOneRun;
@@ -1448,25 +1452,43 @@ bool one_applies(const cs_params* p, int64_t d) {
     return 1.2 * residues <= static_cast<double>(p->r) * static_cast<double>(d) / 8.0;
 }
 
+namespace {
+
+// one launch of k_accumulate_one: n rows whose pieces are chosen
+template <int NC, bool PARTIAL, typename LIST>
+int launch_one(LIST& rows, int n, const float* g, float* S, uint32_t c, int cell_floats, int64_t d, int64_t i0, float scale,
+               hipStream_t stream) {
+    int64_t waves = 0;
+    for (int q = 0; q < n; ++q) waves += (static_cast<int64_t>(rows.row[q].gmax) + 64 * kOneRun - 1) / (64 * kOneRun);
+    const size_t lds = most_steps(rows, n) * sizeof(uint4);
+    if (waves < kOneFewWaves) {
+        const dim3 grid(visits_grid<1, kOneRun, 1>(rows, n));
+        k_accumulate_one<NC, 1, PARTIAL, LIST><<<grid, 64, lds, stream>>>(rows, g, S, c, cell_floats, d, i0, scale);
+    } else {
+        const dim3 grid(visits_grid<1, kOneRun, kOneWaves>(rows, n));
+        k_accumulate_one<NC, kOneWaves, PARTIAL, LIST><<<grid, 64 * kOneWaves, lds, stream>>>(rows, g, S, c, cell_floats, d, i0, scale);
+    }
+    return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+}
+
+}  // namespace
+
 // S = float[r][c][cell_floats]: the table itself (1) or one worker's slot of a bundle (kGroup)
 int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const float* g, int64_t d,
                           int64_t i0, float scale, hipStream_t stream) {
-    // grid of a launch of n rows, whose pieces are chosen here
-    auto shape = [&](auto& rows, int n) {
+    auto cut = [&](auto& rows, int n) {                // the chains of n rows into pieces
         double requests[kRowsPerLaunch];
         for (int q = 0; q < n; ++q) requests[q] = 1.2 * static_cast<double>(rows.row[q].gmax);
         const double stream_ns = 4.0 * static_cast<double>(d) * n / kStreamBytesPerNs;
         choose_pieces(rows, n, requests, kVisitNsOne, stream_ns);
-        return dim3(visits_grid<1, kOneRun, kOneWaves>(rows, n));
     };
     if (!p->c_pow2)
         return for_each_anyc_launch(p, p->r, [&](const uint32_t* js, int n, uint32_t omega) {
             VisitGapsRows rows{};
             for (int q = 0; q < n; ++q) fill_visit_gaps(p, js[q], rows.row[q]);
-            const dim3 grid = shape(rows, n);
-            if (omega == 1) k_accumulate_one<2, false, VisitGapsRows><<<grid, 64 * kOneWaves, most_steps(rows, n) * sizeof(uint4), stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale);
-            else k_accumulate_one<4, false, VisitGapsRows><<<grid, 64 * kOneWaves, most_steps(rows, n) * sizeof(uint4), stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale);
-            return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+            cut(rows, n);
+            return omega == 1 ? launch_one<2, false>(rows, n, g, S, p->c, cell_floats, d, i0, scale, stream)
+                              : launch_one<4, false>(rows, n, g, S, p->c, cell_floats, d, i0, scale, stream);
         });
     uint32_t order[CS_MAX_R], ncell = 2;
     for (uint32_t j = 0; j < p->r; ++j) {              // the longest lists first
@@ -1479,14 +1501,12 @@ int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const f
         const int n = p->r - q0 < kRowsPerLaunch ? static_cast<int>(p->r - q0) : kRowsPerLaunch;
         VisitRows rows{};
         for (int q = 0; q < n; ++q) fill_visit_args(p, order[q0 + q], rows.row[q]);
-        const dim3 grid = shape(rows, n);
-        switch (ncell) {
-            case 2: k_accumulate_one<2, false, VisitRows><<<grid, 64 * kOneWaves, most_steps(rows, n) * sizeof(uint4), stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
-            case 3: k_accumulate_one<3, false, VisitRows><<<grid, 64 * kOneWaves, most_steps(rows, n) * sizeof(uint4), stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
-            case 4: k_accumulate_one<4, false, VisitRows><<<grid, 64 * kOneWaves, most_steps(rows, n) * sizeof(uint4), stream>>>(rows, g, S, p->c, cell_floats, d, i0, scale); break;
-            default: return CS_EINVAL;
-        }
-        if (hipGetLastError() != hipSuccess) return CS_EHIP;
+        cut(rows, n);
+        int rc = CS_EINVAL;
+        if (ncell == 2) rc = launch_one<2, false>(rows, n, g, S, p->c, cell_floats, d, i0, scale, stream);
+        else if (ncell == 3) rc = launch_one<3, false>(rows, n, g, S, p->c, cell_floats, d, i0, scale, stream);
+        else if (ncell == 4) rc = launch_one<4, false>(rows, n, g, S, p->c, cell_floats, d, i0, scale, stream);
+        if (rc != CS_OK) return rc;
     }
     return CS_OK;
 }
@@ -1553,10 +1573,7 @@ int partial_rows(VisitRows& rows, const VisitWorkers& a, int n, bool run, SumsPl
     }
     if (!run) return CS_OK;
     if constexpr (WL == 1) {
-        const dim3 grid(visits_grid<1, kOneRun, kOneWaves>(rows, n));
-        k_accumulate_one<4, true, VisitRows><<<grid, 64 * kOneWaves, most_steps(rows, n) * sizeof(uint4), stream>>>(
-            rows, a.g[0], a.sums, a.c, 1, a.d, a.i0, a.scale);
-        return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+        return launch_one<4, true>(rows, n, a.g[0], a.sums, a.c, 1, a.d, a.i0, a.scale, stream);
     } else {
         if (log_run == 3) return launch_visits_run<WL, 8, 1>(rows, a, n, most, stream);
         return launch_visits_run<WL, 16, WL == 8 ? kWavesPerGroupOf8 : 1>(rows, a, n, most, stream);
