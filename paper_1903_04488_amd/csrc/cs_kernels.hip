@@ -41,11 +41,12 @@ inline unsigned grid_of_hashes(int64_t d, int slots, int64_t groups = 1) {
 }
 
 // Tables of several groups of workers with few columns and many coordinates for each: their requests wait for one another at
-// the same few cells, the longer the more of them are sent at once (us, tables with 8 coordinates a thread / one: 17 workers,
-// 5 x 32, d = 7895 15.6 / 22.3; 127, 7 x 33, 7541 63 / 107; 153, 3 x 33, 2533 (77 a column) 38 / 40; 132, 5 x 33, 2223 (67) 41 / 37;
-// one group, 7 workers, 5 x 33, 6029 12.7 / 12.7; 152 workers, 3 x 91, 6663 62 / 55).
+// the same few cells, the longer the more of them are sent at once (us, tables with 8 coordinates a thread / one, in brackets
+// coordinates a column: 17 workers, 5 x 32, d = 7895 (247) 15.6 / 22.3; 127, 7 x 33, 7541 (229) 63 / 107; 153, 3 x 33, 2533 (77)
+// 38 / 40; 132, 5 x 33, 2223 (67) 41 / 37; 152, 3 x 91, 6663 (73) 62 / 55; 10, 15 x 99, 11 843 (120) 26.3 / 29.0; 106, 15 x 69,
+// 4348 (63) 97 / 109; 184, 15 x 81, 2088 (26) 107 / 94; one group, 7 workers, 5 x 33, 6029 (183) 12.7 / 12.7).
 inline bool crowded_cells(const cs_params* p, int64_t d, int64_t groups) {
-    return groups > 1 && p->c < 80 && d >= static_cast<int64_t>(75) * p->c;
+    return groups > 1 && p->c < 128 && d >= static_cast<int64_t>(p->r > 8 ? 50 : p->c < 80 ? 75 : 100) * p->c;
 }
 
 // Dispatch on the (odd) row count and on "c is a power of two" so that the hash state of all
