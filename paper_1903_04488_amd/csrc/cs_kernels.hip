@@ -35,8 +35,10 @@ inline unsigned grid_for(int64_t n, int per_block = kBlock, int max_blocks = 256
 // vectors wait on chains of hashes and gathers (us, 8 a thread / one; query: 15 x 257, d = 12 001 22.4 / 10.4; 15 x 2001,
 // 150 003 24.9 / 17.4; 5 x 257, 12 001 7.1 / 5.2; 15 x 8193, 500 007 35.9 / 36.9; tables of 4 workers: 5 x 64, 3000 7.8 / 6.0;
 // 5 x 129, 5000 8.5 / 5.8).  Numbers between are no better: query of 5 x 8193, 700 001 16.6 with 8, 16.1 with 2, 18.2 with 5.
-inline unsigned grid_of_hashes(int64_t d, int slots, int64_t groups = 1) {
-    const bool few = d / (slots * 8) < 128 / groups;
+// `below`: the query of up to 5 rows that lie in L1 has gathers to wait for only up to 96 (5 x 709, d = 180 001 6.9 / 6.3, 200 001
+// 7.0 / 7.3; 3 x 257, 200 001 4.9 / 5.3; but 5 x 6605, 200 001 8.0 / 7.4; 7 x 709 9.3 / 9.3).
+inline unsigned grid_of_hashes(int64_t d, int slots, int64_t groups = 1, int64_t below = 128) {
+    const bool few = d / (slots * 8) < below / groups;
     return grid_for(d, few ? slots : slots * 8, 256 * 8);
 }
 
@@ -1088,7 +1090,8 @@ static int estimate_all(const cs_params* p, const float* S, int64_t d, int64_t i
         if (anyc_query_needs_scratch(p, d))
             return !rows_ws || reinterpret_cast<uintptr_t>(rows_ws) % 4 != 0 ? CS_EINVAL : CS_EWORKSPACE;
     }
-    const unsigned grid = grid_of_hashes(d, kBlock);
+    const bool in_l1 = p->r <= 5 && static_cast<uint64_t>(p->r) * p->c <= (1u << 14);
+    const unsigned grid = grid_of_hashes(d, kBlock, 1, in_l1 ? 96 : 128);
 #define CALL(R_, P2_) \
     k_estimate<R_, P2_><<<grid, kBlock, 0, as_stream(stream)>>>(kparams(p), S, d, i0, est)
     CS_DISPATCH_R(p, CALL);

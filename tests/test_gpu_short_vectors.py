@@ -178,11 +178,12 @@ def sketch_in_slices_from(sk, g, i0):
 
 
 # Kernels that hash every coordinate take one or 8 of them a thread: one thread and a remainder, both sides of where 8
-# begin for the query (2^18 coordinates) and for the tables (2^15, shared by the groups of workers; with several groups from 75
+# begin for the query (2^18 coordinates, 196 608 with few cells) and for the tables (2^15, shared by the groups of workers; with several groups from 75
 # coordinates per column on where there are fewer than 80, from 50 on with more than 8 rows).
 @pytest.mark.parametrize("r,c,d,W", [(7, 40, 1, 1), (5, 97, 31, 3), (5, 257, 33, 9), (3, 4099, 32_767, 1), (3, 4099, 32_768, 1),
                                      (3, 4099, 16_383, 9), (3, 4099, 16_385, 9), (9, 4099, 262_143, 1), (3, 4099, 262_145, 2),
-                                     (3, 33, 2474, 9), (3, 33, 2475, 9), (5, 79, 6001, 41), (15, 99, 4949, 10), (15, 99, 4950, 10)])
+                                     (3, 33, 2474, 9), (3, 33, 2475, 9), (5, 79, 6001, 41), (15, 99, 4949, 10), (15, 99, 4950, 10),
+                                     (5, 257, 196_607, 1), (5, 257, 196_609, 1)])
 def test_coordinates_per_thread(r, c, d, W):
     p = cs.cs_params_init(r, c, 5, d)
     sk = orc.SketchOracle(r, c, 5)
