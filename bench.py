@@ -139,7 +139,9 @@ def input_arenas_in_fast_memory(torch, B, hp, cfg, dev, n_sets):
     same update on the same data takes 13.0 ms on vectors within the first 100 GB and 11.8 ms on
     vectors beyond.  So the input sets are not simply allocated next.  This step allocates chunks
     of the size of one input set one after the other, fills them, and times a probe on each (the
-    step's own update of the chunk's W vectors), until n_sets
+    stride-walk update of the chunk's W vectors into the step's own worker tables: the access
+    pattern of the step's update, under a kernel name of its own in a trace; folded workers, which
+    have no such tables, the step's own update), until n_sets
     chunks are within 0.6 % of the fastest and at least 4 % faster than the slowest.  Those
     become the input sets; the other chunks are freed.  The search goes on for n_sets + 10 chunks
     (one part alone is 8 chunks of 12.8 GB); when no chunk stands out by then, the first n_sets
@@ -150,12 +152,20 @@ def input_arenas_in_fast_memory(torch, B, hp, cfg, dev, n_sets):
     chunk_bytes = 4 * cfg.d * cfg.W
     if cfg.W < 8 or chunk_bytes < (2 << 30) or not B.cs_bundle_update_launches(hp.params, 8, cfg.d):
         return None, [], [], None
+    walk = B.CsParams.from_buffer_copy(hp.params)
+    walk.flags |= B.CS_FLAG_NO_VISIT_LIST
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
 
+    def update(vecs):
+        if hp.fold_workers:
+            hp.accumulate(vecs)
+        else:
+            B.cs_sketch_accumulate_bundle(walk, hp.T, vecs)
+
     def probe(vecs):
-        hp.accumulate(vecs)
+        update(vecs)
         e0.record()
-        hp.accumulate(vecs)
+        update(vecs)
         e1.record()
         torch.cuda.synchronize()
         return e0.elapsed_time(e1)
@@ -417,7 +427,8 @@ def main():
         "pct_stream_read_whole_step": 100.0 * step_alg_bytes / (ms_per_step * 1e-3) / 1e9 / stream_set,
         "stream_read": {"one_vector_GBs": stream_one, "one_input_set_GBs": stream_set,
                         "kernel": "cs_probe_stream_read (plain 16-byte loads)"},
-        "placement": {"probe": "the step's update of successive chunks of one input set's size",
+        "placement": {"probe": ("the step's" if hp.fold_workers else "stride-walk")
+                      + " update of successive chunks of one input set's size",
                       "probe_ms": [round(t, 3) for t in probe_ms],
                       "chunks_used_for_inputs": chosen,
                       "update_ms_per_input_set": update_ms_per_set,
@@ -429,7 +440,8 @@ def main():
         "stage_ms": stage_ms,
         "stage_Gcoords_s": {name: (cfg.W if name.startswith(("accumulate", "dense_momentum")) else 1) * cfg.d
                             / (stage_ms[name] * 1e-3) / 1e9
-                            for name in ("accumulate", "accumulate+merge+momentum", "dense_momentum", "estimate", "topk", "heavymix_select")
+                            for name in ("accumulate", "accumulate+merge+momentum", "dense_momentum", "estimate",
+                                         "topk", "heavymix_select")
                             if stage_ms.get(name)},
         "roofline": {
             "kernel": ("cs_vectors_sum and the sketch of the sum" if variant == "fused-merge"
