@@ -31,7 +31,7 @@ METRIC = "sketch+estimate+top-k throughput, Gcoords/s and % HBM peak at d=100M, 
 # factors being what the same counters read for kernels of known traffic in the same run (the
 # plain read of one input set, 12.8 GB, and the clearing of the worker tables, 671 MB).
 # Source: profiles/accumulate_visits_cfg4_pmc.md.  None for other configs.
-MEASURED_TRAFFIC_BYTES = {4: 1.725e10}
+MEASURED_TRAFFIC_BYTES = {4: 1.688e10}
 
 
 def host_cpu():

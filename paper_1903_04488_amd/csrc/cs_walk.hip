@@ -534,8 +534,10 @@ struct VisitCursor {
 // visit of the list (us, update alone): d = 6.5 M, 8 workers, 5 x 2^17 206 -> 184; 6.5 M, 5 x 180 000 268 -> 246; 11 M,
 // 5 x 2^18 317 -> 304; 3 M, 2 workers, 3 x 2^15 48 -> 42; 90 M, 4 workers, 15 x 180 000 4177 -> 4074; 10^8, 8 workers,
 // 5 x 2^20 3260 -> 3156; 25 M, 7 x 2^19 1068 -> 1075; 40 M, 5 x 2^19 1116 -> 1143 (lists whose walkers nearly all take part
-// in nearly all visits have nothing to skip).  Bound: reads at 5.7 to 6.2 TB/s; without its requests the launch at
-// 10^8 takes 2690 us, which is 18.3 GB at 6.8 TB/s (16.0 GB and the cache lines that two wavefronts share).  Sums waiting in
+// in nearly all visits have nothing to skip; the whole update by either way 1163 -> 1178 at 40 M, a step 1617 -> 1638).
+// Bound: reads.  By the counters a launch at 10^8 reads 16.5 GB (16.0 GB and the cache lines that two wavefronts share) and
+// moves 16.9 with its requests, 17.1 with its sums to the workspace, at 5.6 to 5.8 TB/s; without requests or sums it takes
+// 2690 us, 6.1 TB/s.  Sums waiting in
 // LDS instead of registers: 10^8 3130, 25 M 1131; four wavefronts in step by a barrier per visit: 11 M 293, 10^8 3269.
 // PARTIAL (power-of-two columns): the sums go to a workspace instead of being added to the table (cs_index.hip).
 template <int WL, int RUN, int NWAVE, int NC, bool PARTIAL, typename LIST>
@@ -1095,7 +1097,8 @@ int launch_visits_anyc(const cs_params* p, const VisitWorkers& a, const uint32_t
 // Measured (update alone, in us; with two 61-bit states per coordinate and a load for every visit of the list, taken
 // part in or not -> now): d = 73 M, 5 x 2^20 468 -> 326; d = 25 M, 5 x 2^19 176 -> 137; d = 11 M, 5 x 2^18 102 -> 74;
 // d = 73 M, 5 x 180 000 492 -> 445.  Bound: the requests at the end (without them 216, 92, 43 and 227 us, which
-// is the five reads at 6.8 TB/s); 2 and 4 loads ahead and 2 and 8 wavefronts per workgroup: within 4 % either way.
+// is the five reads, 1.46 GB at 73 M by the counters too, at 6.8 TB/s; with them 1.63 GB at 4.8); 2 and 4 loads ahead and 2
+// and 8 wavefronts per workgroup: within 4 % either way.
 // ---------------------------------------------------------------------------------------
 constexpr int kOneRun = 4;
 constexpr int kOneAhead = 3;
