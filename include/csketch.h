@@ -330,7 +330,7 @@ int cs_sketch_momentum(const cs_params* p, float* S_u, float* S_v, const float* 
  * that call one read of est.  For long vectors the kernel that writes est counts as it goes;
  * otherwise est is read once more here.
  * rows_ws: device scratch of cs_estimate_workspace_bytes(p, d) bytes (may be NULL when that
- * size is 0).  */
+ * size is 0); of cs_estimate_scratch_bytes(p, d) it is used, and overwritten, also where that size is 0.  */
 #define CS_TOPK_HIST_BINS 2048
 int cs_estimate_workspace_bytes(const cs_params* p, int64_t d, size_t* bytes);
 /* Scratch with which the query is fastest: what cs_estimate_workspace_bytes says it needs, or, where it needs none
