@@ -300,7 +300,8 @@ int launch_bundle_sketch(const cs_params* p, float* T, int W, const float* const
     const int groups = (W + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP, lanes = sums_lanes(W);
     const uint64_t table = static_cast<uint64_t>(p->r) * p->c * CS_BUNDLE_GROUP;
     SumsPlan plan;
-    int rc = launch_accumulate_sums(p, nullptr, lanes, 0, nullptr, d, scale, plan, stream);
+    const int together = sums_groups(p, W, d);
+    int rc = launch_accumulate_sums(p, nullptr, 0, lanes, together, 0, nullptr, d, scale, plan, stream);
     if (rc != CS_OK) return rc;
     const uint64_t at_once = ws_floats / plan.floats;
     if (at_once == 0) return CS_EWORKSPACE;
@@ -318,9 +319,11 @@ int launch_bundle_sketch(const cs_params* p, float* T, int W, const float* const
     }
     for (int g0 = 0; g0 < groups; g0 += a.groups) {
         a.groups = static_cast<uint64_t>(groups - g0) < at_once ? groups - g0 : static_cast<int>(at_once);
-        for (int g = g0; g < g0 + a.groups; ++g) {
-            const int w0 = g * CS_BUNDLE_GROUP, nw = W - w0 < CS_BUNDLE_GROUP ? W - w0 : CS_BUNDLE_GROUP;
-            rc = launch_accumulate_sums(p, ws + (g - g0) * plan.floats, lanes, nw, g_w + w0, d, scale, plan, stream);
+        for (int g = g0; g < g0 + a.groups; g += together) {
+            const int end = g + together < g0 + a.groups ? g + together : g0 + a.groups;
+            const int w0 = g * CS_BUNDLE_GROUP, w1 = W < end * CS_BUNDLE_GROUP ? W : end * CS_BUNDLE_GROUP;
+            rc = launch_accumulate_sums(p, ws + (g - g0) * a.group_floats, a.group_floats, lanes, together, w1 - w0, g_w + w0, d,
+                                        scale, plan, stream);
             if (rc != CS_OK) return rc;
         }
         a.T = T ? T + g0 * table : nullptr;
@@ -415,7 +418,7 @@ extern "C" int cs_update_workspace_bytes(const cs_params* p, int32_t W, int64_t 
     *bytes = 0;
     if (!sums_apply(p, d)) return CS_OK;
     SumsPlan plan;
-    const int rc = launch_accumulate_sums(p, nullptr, sums_lanes(W), 0, nullptr, d, 1.0f, plan, nullptr);
+    const int rc = launch_accumulate_sums(p, nullptr, 0, sums_lanes(W), sums_groups(p, W, d), 0, nullptr, d, 1.0f, plan, nullptr);
     *bytes = plan.floats * sizeof(float) * ((W + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP);
     return rc;
 }

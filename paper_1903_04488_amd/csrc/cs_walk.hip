@@ -292,6 +292,8 @@ struct VisitArgs {
 // (most blocks, rows, most pieces) is nearly all empty workgroups for a short vector (32 000 for 2 500
 // at d = 30 403, c = 256, which took most of 19 us).
 constexpr int kRowsPerLaunch = 8;
+// Groups of workers of short vectors go into one launch too (groups_at_once).
+constexpr int kGroupsPerLaunch = 32;
 // Neighbouring sets of walkers that go to the same XCD (the kernel deals sets to XCDs in blocks
 // of this many, so that an XCD reads a few KB of contiguous addresses per visit).  Five, not a
 // power of two: with 4 sets of 2 wavefronts an XCD's block is exactly 4 KB of every vector, each
@@ -333,23 +335,39 @@ struct VisitGaps {
     uint32_t gap[CS_ANYC_MAX_VISITS];
 };
 constexpr int kAnycRowsPerLaunch = 6;
-struct VisitGapsRows {
-    uint32_t first[kAnycRowsPerLaunch];          // ~0: no such row
-    VisitGaps row[kAnycRowsPerLaunch];
+template <int ROWS>
+struct VisitGapsRowsOf {
+    uint32_t first[ROWS];                        // ~0: no such row
+    VisitGaps row[ROWS];
     __device__ __forceinline__ const VisitGaps& at(unsigned y) const { return row[y]; }
 };
+typedef VisitGapsRowsOf<kAnycRowsPerLaunch> VisitGapsRows;
+// a row less leaves room for the vectors of 8 groups
+constexpr int kAnycRowsOfGroups = 5, kAnycGroups = 8;
+typedef VisitGapsRowsOf<kAnycRowsOfGroups> VisitGapsRowsGroups;
 static_assert(sizeof(VisitGapsRows) + 128 <= 4096, "the lists of a launch and its other arguments are kernel arguments");
-struct VisitWorkers {
-    const float* g[kGroup];      // vectors of the workers of this group
-    float* T;                    // the group's table, float[r][c][kGroup]; with `fold` one table float[r][c]
+// (blockIdx.y is the group of a launch of several)
+template <int GROUPS>
+struct VisitWorkersOf {
+    float* T;                    // the first group's table, float[r][c][kGroup]; with `fold` one table float[r][c]
     int64_t d, i0;
     uint32_t c;
-    int32_t nw;                  // workers in this group (<= kGroup)
+    int32_t nw;                  // workers of all groups of the launch
     float scale;
-    float* sums;                 // PARTIAL: where the running sums go
     int32_t fold;                // != 0: the workers' sums of a cell are added up across the lanes
                                  // of a walker and leave as one 4-byte request into a single table
+    float* sums;                 // PARTIAL: where the first group's running sums go
+    uint64_t table_floats, sums_floats;          // from one group's to the next
+    const float* g[GROUPS * kGroup];             // vectors of the workers
 };
+typedef VisitWorkersOf<kGroupsPerLaunch> VisitWorkers;
+// what fits beside the lists of LIST
+template <typename LIST>
+using WorkersBeside = VisitWorkersOf<std::is_same<LIST, VisitRows>::value             ? kGroupsPerLaunch
+                                     : std::is_same<LIST, VisitGapsRowsGroups>::value ? kAnycGroups
+                                                                                      : 1>;
+static_assert(sizeof(VisitRows) + sizeof(VisitWorkers) <= 4096, "kernel arguments");
+static_assert(sizeof(VisitGapsRowsGroups) + sizeof(VisitWorkersOf<kAnycGroups>) <= 4096, "kernel arguments");
 
 
 typedef float vec2f __attribute__((ext_vector_type(2)));
@@ -542,7 +560,7 @@ struct VisitCursor {
 // PARTIAL (power-of-two columns): the sums go to a workspace instead of being added to the table (cs_index.hip).
 template <int WL, int RUN, int NWAVE, int NC, bool PARTIAL, typename LIST>
 __global__ void __launch_bounds__(64 * NWAVE)
-k_accumulate_visits(LIST rows, VisitWorkers a) {
+k_accumulate_visits(LIST rows, WorkersBeside<LIST> a) {
     constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
     const unsigned row = row_of_block(rows);
     const auto& v = rows.at(row);
@@ -569,8 +587,11 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
     float* tile_lds = tile_lds_all[wq];
     uint32_t* first_lds = first_lds_all[wq];
     const int h = lane / WL, wl = lane % WL;
-    const int nw = a.nw;
+    const uint32_t group = blockIdx.y;
+    const float* const* vectors = a.g + group * kGroup;
+    const int nw = a.nw - static_cast<int>(group) * kGroup < kGroup ? a.nw - static_cast<int>(group) * kGroup : kGroup;
     const bool live = wl < nw;                          // my worker exists
+    float* const T = a.T + group * a.table_floats;
 
     const int64_t chunks = (static_cast<int64_t>(v.gmax) + RUN - 1) / RUN;
     const int64_t nwaves = (chunks + WPW - 1) / WPW;
@@ -579,8 +600,8 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
     const uint32_t d = static_cast<uint32_t>(a.d);
     const bool fold = a.fold != 0;
     const size_t cell_floats = fold ? 1 : kGroup;      // floats from one cell to the next
-    float* __restrict__ Tcol = fold ? a.T + static_cast<size_t>(v.j) * a.c
-                                    : a.T + static_cast<size_t>(v.j) * a.c * kGroup + wl;
+    float* __restrict__ Tcol = fold ? T + static_cast<size_t>(v.j) * a.c
+                                    : T + static_cast<size_t>(v.j) * a.c * kGroup + wl;
     uint32_t ncell, omega;                             // running sums, and the values of A mod c that they cover
     if constexpr (POW2) {
         ncell = v.ncell;
@@ -619,7 +640,7 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
 #pragma unroll
     for (int w = 0; w < kLoads; ++w) {
         const int from = w * kShare + part;
-        src_of[w] = (gfloat_ptr)a.g[from < nw ? from : 0] + lspan;
+        src_of[w] = (gfloat_ptr)vectors[from < nw ? from : 0] + lspan;
     }
     // Walkers with small residues take part in every visit, those with large ones only in
     // the visits with the largest gap, so the sets of walkers are dealt to the XCDs in short
@@ -800,7 +821,7 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
         if constexpr (PARTIAL) {
             // [piece][wavefront][m][walker][running sum][worker]: the sums of a residue are neighbours, as the cells are
             // that they belong to
-            float* dst = a.sums + v.at + (static_cast<uint64_t>(piece) * nwaves + wv) * (SPAN * WL) * ncell + h * ncell * WL + wl;
+            float* dst = a.sums + group * a.sums_floats + v.at + (static_cast<uint64_t>(piece) * nwaves + wv) * (SPAN * WL) * ncell + h * ncell * WL + wl;
 #pragma unroll
             for (int m = 0; m < RUN; ++m) {
                 const uint32_t flip = first[m] & 0x80000000u;
@@ -832,7 +853,7 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
                     const float sum = tile_lds[item];
                     const uint32_t cell0 = first_lds[of * RUN + m] & 0x7ffffffeu;
                     if (sum != 0.0f)
-                        atomic_add_noret(a.T + (static_cast<size_t>(v.j) * a.c + ((cell0 + slot) & mask)) * kGroup + from,
+                        atomic_add_noret(T + (static_cast<size_t>(v.j) * a.c + ((cell0 + slot) & mask)) * kGroup + from,
                                          a.scale * sum);
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -858,7 +879,7 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
         // Visits whose cells are not kept (which cannot be with a list built by cs_params_init: a wrong list costs
         // time, never correctness): hashed by the definition, straight into memory.
         if (!PARTIAL && listed < k1 - k0) {
-            const gfloat_ptr of_mine = (gfloat_ptr)a.g[live ? wl : 0];
+            const gfloat_ptr of_mine = (gfloat_ptr)vectors[live ? wl : 0];
             for (uint32_t t = 0; t < k1 - k0; ++t) {
                 if (__builtin_amdgcn_readfirstlane(steps[t].w) >> 30 < 3u) continue;
                 const uint32_t s = __builtin_amdgcn_readfirstlane(steps[t].z), gap = __builtin_amdgcn_readfirstlane(steps[t].w) & kGapMask;
@@ -888,12 +909,14 @@ k_accumulate_visits(LIST rows, VisitWorkers a) {
 // takes to read its vectors in any case, so that long vectors, which fill the chip, stay whole.
 constexpr uint32_t kMaxPieces = 32;
 template <typename LIST>
-void choose_pieces(LIST& rows, int nrows, const double* requests, double visit_ns, double stream_ns) {
+void choose_pieces(LIST& rows, int nrows, const double* requests, double visit_ns, double stream_ns, int groups = 1) {
+
     uint32_t longest = 1;
     for (int q = 0; q < nrows; ++q) longest = rows.row[q].K > longest ? rows.row[q].K : longest;
     double best = 1e300, best_len = longest;
     for (double len = longest; len >= 3.0; len *= 0.8) {
         double cost = len * visit_ns > stream_ns ? len * visit_ns : stream_ns;
+        if (groups > 1) cost += 0.5 * len * visit_ns;
         for (int q = 0; q < nrows; ++q) cost += ceil(rows.row[q].K / len) * requests[q] / 24.0;
         if (cost < best) { best = cost; best_len = len; }
     }
@@ -913,13 +936,18 @@ constexpr double kStreamBytesPerNs = 5000.0;
 // The same for a group of workers; true = RUN = 8.  requests8, requests16: what a residue of each row
 // sends with either run length.
 // RUN = 16 with few wavefronts leaves most of the chip idle (1024 SIMDs): RUN = 8 then gives twice as
-// many, each with half the work per visit, which is what a short vector's time consists of.
+// many, each with half the work per visit, which is what a short vector's time consists of.  Up to 2048 wavefronts, and with
+// a power of two of columns up to 3 million coordinates twice that, four times with 8 lanes a walker (us, 16 / 8: 5 x 131 072,
+// 2.55 M, 5 workers 115 / 98; 5 x 32 768, 563 996, 6 workers 39 / 34; 15 x 4096, 608 341, 6 workers 80 / 73; 7 x 16 384, 1.8 M,
+// 3 workers 61 / 56; but 5 x 131 072, 9.9 M, 4 workers 166 / 196, 5 x 65 536, 7.2 M, 9 workers 287 / 335).
 template <int WL, typename LIST>
-bool choose_run8(LIST& rows, int nrows, const double* requests8, const double* requests16, double stream_ns) {
-    choose_pieces(rows, nrows, requests8, kVisitNs8, stream_ns);
+bool choose_run8(LIST& rows, int nrows, const double* requests8, const double* requests16, int64_t d, double stream_ns,
+                 int groups = 1) {
+    choose_pieces(rows, nrows, requests8, kVisitNs8, stream_ns, groups);
     int64_t waves = 0;                                   // with RUN = 16
     for (int q = 0; q < nrows; ++q) waves += static_cast<int64_t>(rows.row[q].gmax) * WL / 1024 * rows.row[q].pieces;
-    if (waves < 2048) return true;
+    constexpr bool pow2 = std::is_same<LIST, VisitRows>::value;
+    if (groups > 1 || waves < 2048 || (pow2 && d < 3'000'000 && waves < (WL == 8 ? 8192 : 4096))) return true;
     choose_pieces(rows, nrows, requests16, kVisitNs16, stream_ns);
     return false;
 }
@@ -976,8 +1004,8 @@ uint32_t most_steps(const LIST& rows, int nrows) {
 
 // one launch: rows that all have at most ncell running sums, of one group of workers
 template <int WL, int RUN, int NWAVE, typename LIST>
-int launch_visits_run(LIST& rows, const VisitWorkers& a, int nrows, uint32_t ncell, hipStream_t stream) {
-    const dim3 grid(visits_grid<WL, RUN, NWAVE>(rows, nrows)), block(64 * NWAVE);
+int launch_visits_run(LIST& rows, const WorkersBeside<LIST>& a, int nrows, uint32_t ncell, hipStream_t stream) {
+    const dim3 grid(visits_grid<WL, RUN, NWAVE>(rows, nrows), (a.nw + kGroup - 1) / kGroup), block(64 * NWAVE);
     const size_t lds = most_steps(rows, nrows) * sizeof(uint4);
     constexpr bool pow2 = std::is_same<LIST, VisitRows>::value;
     constexpr bool partial = pow2 && WL > 1;           // running sums: power-of-two columns (and one vector: k_accumulate_one)
@@ -1006,14 +1034,15 @@ int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js,
     VisitRows rows{};
     // every sum is a request, but RUN = 8 sends the two cells of an aligned block of a bundle in one
     double requests8[kRowsPerLaunch], requests16[kRowsPerLaunch];
+    const int groups = (a.nw + kGroup - 1) / kGroup;
     for (int q = 0; q < nrows; ++q) {
         const cs_visit_plan& vp = p->visit[js[q]];
         fill_visit_args(p, js[q], rows.row[q]);
-        requests16[q] = static_cast<double>(vp.ncell) * static_cast<double>(vp.gmax);
-        requests8[q] = a.fold ? requests16[q] : (0.5 * vp.ncell + 0.5) * static_cast<double>(vp.gmax);
+        requests16[q] = static_cast<double>(vp.ncell) * static_cast<double>(vp.gmax) * groups;
+        requests8[q] = a.fold ? requests16[q] : (0.5 * vp.ncell + 0.5) * static_cast<double>(vp.gmax) * groups;
     }
     const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * nrows / kStreamBytesPerNs;
-    if (choose_run8<WL>(rows, nrows, requests8, requests16, stream_ns))
+    if (choose_run8<WL>(rows, nrows, requests8, requests16, a.d, stream_ns, groups))
         return launch_visits_run<WL, 8, 1>(rows, a, nrows, ncell, stream);
     return launch_visits_run<WL, 16, NWAVE>(rows, a, nrows, ncell, stream);
 }
@@ -1028,6 +1057,30 @@ bool visits_apply(const cs_params* p, uint32_t j, int64_t d, bool any_cost = fal
     return any_cost || vp.cost < vp.cost_walk;
 }
 
+// Groups of 8 workers that share a launch, `most` at most.  A launch of one group of short vectors is a chain of visits
+// that leaves most of the chip idle, 15 to 30 us however little it reads; together they read at the rate of long vectors.
+// With runs of 8, chains cut as if half a chain came on top of the reads, us (requests and merge, one group at a time / together):
+// 5 x 1024, d = 79 230, 240 workers 356 / 104; 7 x 128, 20 344, 122 workers 174 / 55; 5 x 2048, 446 435, 66 workers 222 / 105
+// (318 where the chains were not cut, 174 in runs of 16); 15 x 2048, 767 209, 236 workers 2388 / 1806; 5 x 8192, 1.2 M, 92
+// workers 522 / 308; 3 x 65 536, 3.3 M, 205 workers 1844 / 1345; other column counts: 15 x 793, 95 678, 122 workers
+// 1163 / 239; 5 x 2109, 332 923, 144 workers 417 / 216.  Up to 1.6 GB of reads a group (other column counts 1.2): from there
+// the tables of several groups push each other out of the memory-side cache (5 x 131 072, 23 M, 26 workers, two together
+// 2167 / 2296; 3 x 262 144, 18 M, 1112 / 1148; 7 x 131 072, 9.4 M 742 / 784; 3 x 58 719, 17 M, six together 2182 / 2372; but 3 x
+// 65 536, 16.9 M 1250 / 989).
+int groups_at_once(const cs_params* p, int64_t d, int most = kGroupsPerLaunch) {
+    const double n = 1e10 / (32.0 * static_cast<double>(d) * p->r);
+    return n < (p->c_pow2 ? 6.0 : 8.0) ? 1 : n > most ? most : static_cast<int>(n);
+}
+// The workers of the next launch, of `left`.  Up to 4 workers that are left over share the launch of the others, with idle
+// lanes, while that reads less than 0.3 GB a group (7 x 2048, 725 668, 11 workers 74 / 66; but 5 x 131 072, 3.2 M, 9 workers
+// 198 / 208, 3 x 32 768, 11 M, 9 workers 253 / 288).
+int workers_of_launch(const cs_params* p, int64_t d, int left, int at_once) {
+    if (at_once == 1 || left <= kGroup) return left < kGroup ? left : kGroup;
+    if (left > at_once * kGroup) return at_once * kGroup;
+    const int tail = left % kGroup;
+    return tail <= kGroup / 2 && 32.0 * static_cast<double>(d) * p->r > 3e8 ? left - tail : left;
+}
+
 void fill_visit_gaps(const cs_params* p, uint32_t j, VisitGaps& v) {
     const cs_anyc_plan& vp = p->anyc[j];
     v.K = vp.K;
@@ -1040,10 +1093,10 @@ void fill_visit_gaps(const cs_params* p, uint32_t j, VisitGaps& v) {
 }
 
 // The rows of an any-c sketch in the launches that take them: rows with the same number of
-// running sums (omega = 1 or 2) together, up to kAnycRowsPerLaunch per launch, the longest lists
+// running sums (omega = 1 or 2) together, up to `at_once` per launch, the longest lists
 // first.  fn(rows, n, omega) is called per launch.
 template <typename FN>
-int for_each_anyc_launch(const cs_params* p, uint32_t nrows_of_sketch, FN fn) {
+int for_each_anyc_launch(const cs_params* p, uint32_t nrows_of_sketch, FN fn, int at_once = kAnycRowsPerLaunch) {
     for (uint32_t omega = 1; omega <= 2; ++omega) {
         uint32_t order[CS_MAX_R];
         int n = 0;
@@ -1053,8 +1106,8 @@ int for_each_anyc_launch(const cs_params* p, uint32_t nrows_of_sketch, FN fn) {
             for (; at > 0 && p->anyc[order[at - 1]].K < p->anyc[j].K; --at) order[at] = order[at - 1];
             order[at] = j;
         }
-        for (int q0 = 0; q0 < n; q0 += kAnycRowsPerLaunch) {
-            const int m = n - q0 < kAnycRowsPerLaunch ? n - q0 : kAnycRowsPerLaunch;
+        for (int q0 = 0; q0 < n; q0 += at_once) {
+            const int m = n - q0 < at_once ? n - q0 : at_once;
             const int rc = fn(order + q0, m, omega);
             if (rc != CS_OK) return rc;
         }
@@ -1065,7 +1118,7 @@ int for_each_anyc_launch(const cs_params* p, uint32_t nrows_of_sketch, FN fn) {
 // one launch: rows js[0 .. n) (all with the same omega) of one group of workers, each along
 // its list for any column count
 template <int WL, int NWAVE>
-int launch_visits_anyc(const cs_params* p, const VisitWorkers& a, const uint32_t* js, int n,
+int launch_visits_anyc(const cs_params* p, const VisitWorkersOf<1>& a, const uint32_t* js, int n,
                        uint32_t omega, hipStream_t stream) {
     VisitGapsRows rows{};
     double requests[kAnycRowsPerLaunch];
@@ -1074,7 +1127,7 @@ int launch_visits_anyc(const cs_params* p, const VisitWorkers& a, const uint32_t
         requests[q] = 2.0 * rows.row[q].omega * static_cast<double>(rows.row[q].gmax);
     }
     const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * n / kStreamBytesPerNs;
-    if (choose_run8<WL>(rows, n, requests, requests, stream_ns))
+    if (choose_run8<WL>(rows, n, requests, requests, a.d, stream_ns))
         return launch_visits_run<WL, 8, 1>(rows, a, n, 2 * omega, stream);
     return launch_visits_run<WL, 16, NWAVE>(rows, a, n, 2 * omega, stream);
 }
@@ -1347,16 +1400,40 @@ k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, 
 
 }  // namespace
 
-// Every row has a list for this column count and vector length, and by its own estimate the
-// list beats one request per coordinate.
-bool anyc_visits_apply(const cs_params* p, int64_t d) {
+// Every row has a list for this column count and vector length.
+static bool anyc_all_listed(const cs_params* p, int64_t d) {
     if (p->c_pow2 || d > kStepsMaxD || (p->flags & CS_FLAG_NO_VISIT_LIST) != 0) return false;
     for (uint32_t j = 0; j < p->r; ++j) {
         const cs_anyc_plan& vp = p->anyc[j];
         if (vp.K == 0 || vp.K > CS_ANYC_MAX_VISITS || (vp.omega != 1 && vp.omega != 2)) return false;
-        if (static_cast<uint64_t>(d) > vp.cover || vp.cost >= vp.cost_direct) return false;
+        if (static_cast<uint64_t>(d) > vp.cover) return false;
     }
     return true;
+}
+// ... and by its own estimate the list beats one request per coordinate.
+bool anyc_visits_apply(const cs_params* p, int64_t d) {
+    if (!anyc_all_listed(p, d)) return false;
+    for (uint32_t j = 0; j < p->r; ++j)
+        if (p->anyc[j].cost >= p->anyc[j].cost_direct) return false;
+    return true;
+}
+
+// The update of W workers follows the lists where the rows together are estimated to gain (one bad list of 5 x 46 897, d =
+// 1.8 M, 97 workers, is 9 % above its requests and the other four take a quarter of theirs).  Groups that share launches
+// wait for each other's chains of visits only once, so that their requests (24 G/s) and reads (5 TB/s) count and a chain.
+bool anyc_update_applies(const cs_params* p, int64_t d, int W) {
+    if (!anyc_all_listed(p, d)) return false;
+    double lists = 0.0, direct = 0.0, requests = 0.0;
+    for (uint32_t j = 0; j < p->r; ++j) {
+        lists += static_cast<double>(p->anyc[j].cost);
+        direct += static_cast<double>(p->anyc[j].cost_direct);
+        requests += 2.0 * p->anyc[j].omega * static_cast<double>(p->anyc[j].gmax);
+    }
+    if (lists < direct) return true;
+    const int groups = (W + kGroup - 1) / kGroup;
+    if (groups == 1 || groups_at_once(p, d, kAnycGroups) == 1) return false;
+    const double coordinates = static_cast<double>(p->r) * static_cast<double>(d);
+    return 15000.0 + groups * (requests / 24.0 + 32.0 * coordinates / kStreamBytesPerNs) < groups * coordinates / 21.0;
 }
 
 // The query follows the lists where its r launches are worth it. Below d = 1.5 million they are not (us of
@@ -1385,15 +1462,41 @@ int count_accumulate_anyc_launches(const cs_params* p, int W) {
 int launch_accumulate_anyc(const cs_params* p, float* T, int W, const float* const* g_w,
                            int64_t d, int64_t i0, float scale, bool fold, hipStream_t stream) {
     const size_t row_floats = static_cast<size_t>(p->c) * kGroup;
-    for (int w0 = 0; w0 < W; w0 += kGroup) {
-        const int nw = (W - w0 < kGroup) ? (W - w0) : kGroup;
+    const int at_once = groups_at_once(p, d, kAnycGroups);
+    for (int w0 = 0, nw; w0 < W; w0 += nw) {
+        nw = workers_of_launch(p, d, W - w0, at_once);
         float* Tg = fold ? T : T + static_cast<size_t>(w0 / kGroup) * p->r * row_floats;
+        if (nw > kGroup) {
+            VisitWorkersOf<kAnycGroups> vw{};
+            for (int w = 0; w < nw; ++w) vw.g[w] = g_w[w0 + w];
+            vw.T = Tg;
+            vw.d = d;
+            vw.i0 = i0;
+            vw.c = p->c;
+            vw.nw = nw;
+            vw.scale = scale;
+            vw.fold = fold ? 1 : 0;
+            vw.table_floats = fold ? 0 : p->r * row_floats;
+            const int groups = (nw + kGroup - 1) / kGroup;
+            const int rc = for_each_anyc_launch(p, p->r, [&](const uint32_t* js, int n, uint32_t omega) {
+                VisitGapsRowsGroups rows{};
+                double requests[kAnycRowsOfGroups];
+                for (int q = 0; q < n; ++q) {
+                    fill_visit_gaps(p, js[q], rows.row[q]);
+                    requests[q] = 2.0 * rows.row[q].omega * static_cast<double>(rows.row[q].gmax) * groups;
+                }
+                choose_pieces(rows, n, requests, kVisitNs8, 4.0 * static_cast<double>(d) * nw * n / kStreamBytesPerNs, groups);
+                return launch_visits_run<8, 8, 1>(rows, vw, n, 2 * omega, stream);
+            }, kAnycRowsOfGroups);
+            if (rc != CS_OK) return rc;
+            continue;
+        }
         if (nw == 1 && one_applies(p, d)) {
             const int rc = launch_accumulate_one(p, Tg, fold ? 1 : kGroup, g_w[w0], d, i0, scale, stream);
             if (rc != CS_OK) return rc;
             continue;
         }
-        VisitWorkers vw{};
+        VisitWorkersOf<1> vw{};
         for (int w = 0; w < nw; ++w) vw.g[w] = g_w[w0 + w];
         vw.T = Tg;
         vw.d = d;
@@ -1420,7 +1523,7 @@ bool walk_applies(const cs_params* p, int64_t d) {
     return true;
 }
 
-// kernel launches one call of launch_accumulate_walk makes (same grouping as below)
+// kernel launches one call of launch_accumulate_walk makes, a group at a time (same grouping as below)
 int count_accumulate_walk_launches(const cs_params* p, int W, int64_t d) {
     int listed = 0, per_group = 0;
     for (uint32_t j = 0; j < p->r; ++j) {
@@ -1548,7 +1651,7 @@ bool lists_hold(const cs_params* p) {
 // The rows of one launch: pieces and run length are chosen, their places in the workspace taken, and, with
 // `run`, the launch is made.
 template <int WL>
-int partial_rows(VisitRows& rows, const VisitWorkers& a, int n, bool run, SumsPlan& plan, hipStream_t stream) {
+int partial_rows(VisitRows& rows, VisitWorkers& a, int n, int groups, SumsPlan& plan, hipStream_t stream) {
     double writes[kRowsPerLaunch];
     uint32_t most = 2;
     for (int q = 0; q < n; ++q) {
@@ -1556,12 +1659,12 @@ int partial_rows(VisitRows& rows, const VisitWorkers& a, int n, bool run, SumsPl
         most = v.ncell > most ? v.ncell : most;
         // a running sum costs as many requests of 1/24 ns as four times its bytes written and read would take to stream
         // (one to eight times: within 3 % of each other, but for d = 60 789, W = 11, 5 x 1024: 32.8, 29.8, 28.4, 27.9 us)
-        writes[q] = 24.0 * 32.0 * WL * v.ncell * static_cast<double>(v.gmax) / kStreamBytesPerNs;
+        writes[q] = 24.0 * 32.0 * WL * v.ncell * static_cast<double>(v.gmax) / kStreamBytesPerNs * groups;
     }
-    const double stream_ns = 4.0 * static_cast<double>(a.d) * WL * n / kStreamBytesPerNs;
+    const double stream_ns = 4.0 * static_cast<double>(a.d) * WL * n / kStreamBytesPerNs * groups;
     int log_run = 0;                                   // (of one vector the sums lie in the order of the residues)
     if (WL == 1) choose_pieces(rows, n, writes, kVisitNsOne, stream_ns);
-    else log_run = choose_run8<WL>(rows, n, writes, writes, stream_ns) ? 3 : 4;
+    else log_run = choose_run8<WL>(rows, n, writes, writes, a.d, stream_ns, groups) ? 3 : 4;
     const uint64_t span = WL == 1 ? 64 * kOneRun : 64u / WL << log_run;
     for (int q = 0; q < n; ++q) {
         VisitArgs& v = rows.row[q];
@@ -1574,7 +1677,7 @@ int partial_rows(VisitRows& rows, const VisitWorkers& a, int n, bool run, SumsPl
         out.log_run = log_run;
         plan.floats += out.piece_floats * v.pieces;
     }
-    if (!run) return CS_OK;
+    if (a.nw == 0) return CS_OK;
     if constexpr (WL == 1) {
         return launch_one<4, true>(rows, n, a.g[0], a.sums, a.c, 1, a.d, a.i0, a.scale, stream);
     } else {
@@ -1584,7 +1687,7 @@ int partial_rows(VisitRows& rows, const VisitWorkers& a, int n, bool run, SumsPl
 }
 
 template <int WL>
-int partial_group(const cs_params* p, const VisitWorkers& a, bool run, SumsPlan& plan, hipStream_t stream) {
+int partial_group(const cs_params* p, VisitWorkers& a, int groups, SumsPlan& plan, hipStream_t stream) {
     uint32_t order[CS_MAX_R];
     for (uint32_t j = 0; j < p->r; ++j) {              // the longest lists first
         int at = static_cast<int>(j);
@@ -1595,7 +1698,7 @@ int partial_group(const cs_params* p, const VisitWorkers& a, bool run, SumsPlan&
         const int n = p->r - q0 < kRowsPerLaunch ? static_cast<int>(p->r - q0) : kRowsPerLaunch;
         VisitRows rows{};
         for (int q = 0; q < n; ++q) fill_visit_args(p, order[q0 + q], rows.row[q]);
-        const int rc = partial_rows<WL>(rows, a, n, run, plan, stream);
+        const int rc = partial_rows<WL>(rows, a, n, groups, plan, stream);
         if (rc != CS_OK) return rc;
     }
     return CS_OK;
@@ -1616,22 +1719,29 @@ bool sums_apply(const cs_params* p, int64_t d) {
 
 int sums_lanes(int W) { return W > 4 ? 8 : W > 2 ? 4 : W; }
 
+// Groups of a launch of W workers
+int sums_groups(const cs_params* p, int W, int64_t d) {
+    const int all = (W + kGroup - 1) / kGroup, most = groups_at_once(p, d);
+    return all < most ? all : most;
+}
+
 // g_w null: the plan only
-int launch_accumulate_sums(const cs_params* p, float* sums, int lanes, int nw, const float* const* g_w, int64_t d,
-                           float scale, SumsPlan& plan, hipStream_t stream) {
+int launch_accumulate_sums(const cs_params* p, float* sums, uint64_t sums_floats, int lanes, int groups, int nw,
+                           const float* const* g_w, int64_t d, float scale, SumsPlan& plan, hipStream_t stream) {
     plan = SumsPlan{};
     VisitWorkers a{};
     for (int w = 0; g_w && w < nw; ++w) a.g[w] = g_w[w];
     a.sums = sums;
+    a.sums_floats = sums_floats;
     a.d = d;
     a.c = p->c;
-    a.nw = nw;
+    a.nw = g_w ? nw : 0;
     a.scale = scale;
     switch (lanes) {
-        case 1: return partial_group<1>(p, a, g_w != nullptr, plan, stream);
-        case 2: return partial_group<2>(p, a, g_w != nullptr, plan, stream);
-        case 4: return partial_group<4>(p, a, g_w != nullptr, plan, stream);
-        default: return partial_group<8>(p, a, g_w != nullptr, plan, stream);
+        case 1: return partial_group<1>(p, a, groups, plan, stream);
+        case 2: return partial_group<2>(p, a, groups, plan, stream);
+        case 4: return partial_group<4>(p, a, groups, plan, stream);
+        default: return partial_group<8>(p, a, groups, plan, stream);
     }
 }
 
@@ -1643,8 +1753,11 @@ int launch_accumulate_walk(const cs_params* p, float* T, int W, const float* con
     const size_t row_floats = static_cast<size_t>(p->c) * kGroup;
     bool one = W % kGroup == 1 && one_applies(p, d);   // a group of one worker: a single vector
     for (uint32_t j = 0; j < p->r; ++j) one = one && visits_apply(p, j, d, fold);
-    for (int w0 = 0; w0 < W; w0 += kGroup) {
-        const int nw = (W - w0 < kGroup) ? (W - w0) : kGroup;
+    bool listed_all = true;
+    for (uint32_t j = 0; j < p->r; ++j) listed_all = listed_all && visits_apply(p, j, d, fold);
+    const int at_once = listed_all ? groups_at_once(p, d) : 1;
+    for (int w0 = 0, nw; w0 < W; w0 += nw) {
+        nw = workers_of_launch(p, d, W - w0, at_once);
         float* Tg = fold ? T : T + static_cast<size_t>(w0 / kGroup) * p->r * row_floats;
         if (nw == 1 && one) {
             const int rc = launch_accumulate_one(p, Tg, fold ? 1 : kGroup, g_w[w0], d, i0, scale, stream);
@@ -1660,6 +1773,7 @@ int launch_accumulate_walk(const cs_params* p, float* T, int W, const float* con
         vw.nw = nw;
         vw.scale = scale;
         vw.fold = fold ? 1 : 0;
+        vw.table_floats = fold ? 0 : p->r * row_floats;
         // All rows with a visit list go into one launch (per 8 rows), compiled for the largest
         // number of running sums among them: a row that needs fewer simply never touches the
         // extra ones.  One launch overlaps the rows' serial chains of visits and has one tail.
@@ -1690,8 +1804,8 @@ int launch_accumulate_walk(const cs_params* p, float* T, int W, const float* con
         // the other rows: stride walk, all in one launch, the longest chains of visits
         // (smallest strides) first
         WalkArgs a{};
-        a.nw = nw;
-        for (int w = 0; w < nw; ++w) a.g[w] = g_w[w0 + w];
+        a.nw = nw;                               // (one group: not all rows are listed)
+        for (int w = 0; w < nw && w < kGroup; ++w) a.g[w] = g_w[w0 + w];
         a.T = Tg;
         a.d = d;
         a.i0 = i0;
