@@ -108,6 +108,14 @@ _SIGNATURES = {
                          ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_size_t,
                          ctypes.c_void_p, ctypes.c_float, ctypes.c_void_p, ctypes.c_void_p,
                          ctypes.c_float, ctypes.c_void_p],
+    "cs_cell_lists_bytes": [ctypes.POINTER(CsParams), ctypes.c_int32, ctypes.c_int64,
+                            ctypes.POINTER(ctypes.c_size_t)],
+    "cs_cell_lists_build": [ctypes.POINTER(CsParams), ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t,
+                            ctypes.c_void_p],
+    "cs_bundle_sketch_lists": [ctypes.POINTER(CsParams), ctypes.c_void_p, ctypes.c_int32,
+                               ctypes.POINTER(ctypes.c_void_p), ctypes.c_int64, ctypes.c_float,
+                               ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_float,
+                               ctypes.c_void_p, ctypes.c_void_p, ctypes.c_float, ctypes.c_void_p],
     "cs_sketch_accumulate_sparse": [ctypes.POINTER(CsParams), ctypes.c_void_p, ctypes.c_void_p,
                                     ctypes.c_void_p, ctypes.c_int64, ctypes.c_float,
                                     ctypes.c_void_p],
@@ -540,6 +548,31 @@ def cs_bundle_sketch(p, T, g_w, index, workspace, scale: float = 1.0, S_t=None, 
         _ptr_array(g_w, torch.float32, "g_w", d), d, scale, _dev(index, torch.uint8, "index"), index.numel(),
         _dev(workspace, torch.uint8, "workspace"), workspace.numel(), table(S_t, "S_t"), alpha, table(S_u, "S_u"),
         table(S_v, "S_v"), rho, _stream(index)), "cs_bundle_sketch")
+
+
+def cs_cell_lists_bytes(p, W: int, d: int) -> int:
+    n = ctypes.c_size_t()
+    _check(load_library().cs_cell_lists_bytes(ctypes.byref(p), W, d, ctypes.byref(n)), "cs_cell_lists_bytes")
+    return n.value
+
+
+def cs_cell_lists_build(p, d: int, lists):
+    _check(load_library().cs_cell_lists_build(ctypes.byref(p), d, _dev(lists, torch.uint8, "lists"), lists.numel(),
+                                              _stream(lists)), "cs_cell_lists_build")
+
+
+def cs_bundle_sketch_lists(p, T, g_w, lists, scale: float = 1.0, S_t=None, alpha: float = 1.0, S_u=None, S_v=None,
+                           rho: float = 0.0):
+    W = len(g_w)
+    if W == 0:
+        raise CsError("g_w must be a non-empty list")
+    d = g_w[0].numel()
+    none = ctypes.c_void_p(0)
+    table = lambda t, name: none if t is None else _dev(t, torch.float32, name, _cells(p))      # noqa: E731
+    _check(load_library().cs_bundle_sketch_lists(
+        ctypes.byref(p), none if T is None else _dev(T, torch.float32, "T", cs_bundle_floats(p, W)), W,
+        _ptr_array(g_w, torch.float32, "g_w", d), d, scale, _dev(lists, torch.uint8, "lists"), lists.numel(),
+        table(S_t, "S_t"), alpha, table(S_u, "S_u"), table(S_v, "S_v"), rho, _stream(lists)), "cs_bundle_sketch_lists")
 
 
 def cs_sketch_feedback_pair(p, S_v, S_u, idx, val_v, val_u):

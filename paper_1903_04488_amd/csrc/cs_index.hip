@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "cs_device.h"
 #include "cs_internal.h"
 #include "csketch.h"
@@ -38,13 +40,14 @@ IndexRows index_rows(const cs_params* p) {
     return x;
 }
 
+template <bool POW2>
 __global__ void __launch_bounds__(kBlock) k_index_count(KParams p, IndexRows rows, uint32_t* __restrict__ index) {
     const uint32_t j = blockIdx.y;
     uint32_t* start = index + rows.at[j];
-    const Columns col = columns_of<true>(p.c);
+    const Columns col = columns_of<POW2>(p.c);
     const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kBlock;
     for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x; i < rows.residues[j]; i += stride)
-        atomicAdd(&start[bucket_of<true>(hash_state(p.a[j], p.b[j], i), col)], 1u);
+        atomicAdd(&start[bucket_of<POW2>(hash_state(p.a[j], p.b[j], i), col)], 1u);
 }
 
 // counts -> the end of every cell's residues; a workgroup per row
@@ -71,14 +74,19 @@ __global__ void __launch_bounds__(1024) k_index_scan(KParams p, IndexRows rows, 
     if (threadIdx.x == 0) start[p.c] = static_cast<uint32_t>(rows.residues[blockIdx.x]);
 }
 
+// SIGNS: an entry is twice the coordinate, and one more where its sign is -1
+template <bool POW2, bool SIGNS>
 __global__ void __launch_bounds__(kBlock) k_index_fill(KParams p, IndexRows rows, uint32_t* __restrict__ index) {
     const uint32_t j = blockIdx.y;
     uint32_t* start = index + rows.at[j];
     uint32_t* residue = start + p.c + 1;
-    const Columns col = columns_of<true>(p.c);
+    const Columns col = columns_of<POW2>(p.c);
     const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kBlock;
-    for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x; i < rows.residues[j]; i += stride)
-        residue[atomicSub(&start[bucket_of<true>(hash_state(p.a[j], p.b[j], i), col)], 1u) - 1u] = static_cast<uint32_t>(i);
+    for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x; i < rows.residues[j]; i += stride) {
+        uint32_t entry = static_cast<uint32_t>(i);
+        if constexpr (SIGNS) entry = 2u * entry | sign_flip_of(hash_state(p.as[j], p.bs[j], i)) >> 31;
+        residue[atomicSub(&start[bucket_of<POW2>(hash_state(p.a[j], p.b[j], i), col)], 1u) - 1u] = entry;
+    }
 }
 
 // A cell's residues in ascending order, so that sums have one order.  Cells of up to kShortCell residues by a thread
@@ -276,14 +284,15 @@ int launch_gather(const cs_params* p, const GatherArgs& a, hipStream_t stream) {
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
-int launch_index_build(const cs_params* p, uint32_t* index, hipStream_t stream) {
-    const IndexRows rows = index_rows(p);
+// of the residues (power-of-two columns) or, SIGNS, of whole coordinates
+template <bool POW2, bool SIGNS>
+int launch_index_build(const cs_params* p, const IndexRows& rows, uint32_t* index, hipStream_t stream) {
     const int rc = launch_bundle_zero(reinterpret_cast<float*>(index), static_cast<int64_t>(rows.words), stream);
     if (rc != CS_OK) return rc;
     const dim3 grid(2048, p->r), cells((p->c + kBlock - 1) / kBlock, p->r);
-    k_index_count<<<grid, kBlock, 0, stream>>>(kparams(p), rows, index);
+    k_index_count<POW2><<<grid, kBlock, 0, stream>>>(kparams(p), rows, index);
     k_index_scan<<<p->r, 1024, 0, stream>>>(kparams(p), rows, index);
-    k_index_fill<<<grid, kBlock, 0, stream>>>(kparams(p), rows, index);
+    k_index_fill<POW2, SIGNS><<<grid, kBlock, 0, stream>>>(kparams(p), rows, index);
     k_index_sort<<<cells, kBlock, 0, stream>>>(p->c, rows, index);
     uint32_t per = (p->c + 2047) / 2048;               // cells of a workgroup: one of a narrow table
     per = per < kLongBlock ? per : kLongBlock;
@@ -345,6 +354,135 @@ int launch_bundle_sketch(const cs_params* p, float* T, int W, const float* const
     const int64_t cells = static_cast<int64_t>(p->r) * p->c;
     if (S_u) return launch_bundle_merge_momentum(S_t, S_u, S_v, T, groups, alpha, rho, cells, stream);
     return launch_bundle_merge(S_t, 0.0f, T, groups, alpha, cells, stream);
+}
+
+// ---------------------------------------------------------------------------------------
+// The update of short vectors cell by cell: for every row the coordinates in the order of their cells are laid out
+// once, with their signs, and a cell is the sum of its coordinates' values, read where they lie.  The vectors of a
+// group stay in L2 meanwhile.  One launch writes the tables, their merge and the momentum: no clearing, no
+// atomics, and the same bits in every run.
+// ---------------------------------------------------------------------------------------
+constexpr int kListVectors = 256;    // of a launch: their addresses are kernel arguments
+
+struct ListArgs {
+    const uint32_t* lists;
+    float* T;                        // or null
+    float* S_t;                      // or null; S_u, S_v or null: as in GatherArgs
+    float* S_u;
+    float* S_v;
+    float scale, alpha, rho;
+    uint32_t r, c, d;
+    int32_t W, slices;
+    const float* g[kListVectors];
+};
+
+// L lanes of a cell (8 to 64) share out its coordinates; `slices` wavefronts share out the groups of 8 workers.
+template <int L>
+__global__ void __launch_bounds__(kBlock) k_sum_lists(ListArgs a) {
+    static_assert(L >= CS_BUNDLE_GROUP, "a lane per worker of a group");
+    constexpr int kCells = 64 / L, kWaves = kBlock / 64;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int slice = wave % a.slices;
+    const uint32_t j = blockIdx.y, part = lane % L, set = wave / a.slices;
+    const uint32_t b = (blockIdx.x * (kWaves / a.slices) + set) * kCells + lane / L;
+    const bool in = b < a.c;
+    const uint32_t* start = a.lists + static_cast<uint64_t>(j) * (a.c + 1ull + a.d);
+    const uint32_t* entry = start + a.c + 1;
+    uint32_t lo = 0, n = 0;
+    if (in) {
+        lo = start[b];
+        uint32_t hi = start[b + 1];
+        hi = hi < a.d ? hi : a.d;
+        n = hi > lo ? hi - lo : 0u;
+    }
+    const uint64_t at = static_cast<uint64_t>(j) * a.c + b;
+    const bool writes = in && part == 0 && slice == 0 && a.S_t;
+    float old_u = 0.0f, old_v = 0.0f;
+    if (writes && a.S_u) {
+        old_u = a.S_u[at];
+        old_v = a.S_v[at];
+    }
+    // after the exchange below a lane has the sum of this worker of a group
+    const uint32_t mine = (part & 1u) * 4 + (part >> 1 & 1u) * 2 + (part >> 2 & 1u);
+    double total = 0.0;
+    const int groups = (a.W + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP;
+    for (int g = slice; g < groups; g += a.slices) {
+        const int nw = a.W - g * CS_BUNDLE_GROUP < CS_BUNDLE_GROUP ? a.W - g * CS_BUNDLE_GROUP : CS_BUNDLE_GROUP;
+        float v[CS_BUNDLE_GROUP];
+        const float* const* vec = a.g + g * CS_BUNDLE_GROUP;
+#pragma unroll
+        for (int w = 0; w < CS_BUNDLE_GROUP; ++w) v[w] = 0.0f;
+        auto add = [&](auto whole) {
+            constexpr int kAhead = 2;
+            for (uint32_t t = part; t < n; t += kAhead * L) {
+                float x[kAhead][CS_BUNDLE_GROUP];
+                uint32_t flip[kAhead];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const uint32_t e = t + u * L < n ? entry[lo + t + u * L] : ~0u;
+                    const bool there = e >> 1 < a.d;   // (not: no more entries, or lists of another sketch)
+                    const uint32_t i = there ? e >> 1 : 0u;
+                    flip[u] = e << 31;
+#pragma unroll
+                    for (int w = 0; w < CS_BUNDLE_GROUP; ++w) {
+                        x[u][w] = 0.0f;
+                        if ((decltype(whole)::value || w < nw) && there) x[u][w] = vec[w][i];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                    for (int w = 0; w < CS_BUNDLE_GROUP; ++w) v[w] += apply_sign(x[u][w], flip[u]);
+            }
+        };
+        if (nw == CS_BUNDLE_GROUP) add(std::true_type());
+        else add(std::false_type());
+        // 8 sums of L lanes -> one sum of each lane
+#pragma unroll
+        for (int m = CS_BUNDLE_GROUP / 2, off = 1; m > 0; m /= 2, off *= 2) {
+            const bool upper = (part & off) != 0;
+#pragma unroll
+            for (int q = 0; q < m; ++q) {
+                const float keep = upper ? v[q + m] : v[q], give = upper ? v[q] : v[q + m];
+                v[q] = keep + __shfl_xor(give, off);
+            }
+        }
+#pragma unroll
+        for (int off = CS_BUNDLE_GROUP; off < L; off *= 2) v[0] += __shfl_xor(v[0], off);
+        const float sum = static_cast<int>(mine) < nw ? a.scale * v[0] : 0.0f;
+        if (a.T && in && part < CS_BUNDLE_GROUP)
+            a.T[((static_cast<uint64_t>(g) * a.r + j) * a.c + b) * CS_BUNDLE_GROUP + mine] = sum;
+        total += static_cast<double>(sum);
+    }
+    if (!a.S_t) return;
+#pragma unroll
+    for (int off = 1; off < CS_BUNDLE_GROUP; off *= 2) total += __shfl_xor(total, off);
+    if (a.slices > 1) {
+        __shared__ double totals[kWaves][kCells];
+        if (part == 0) totals[wave][lane / L] = total;
+        __syncthreads();
+        for (int q = 1; slice == 0 && q < a.slices; ++q) total += totals[wave + q][lane / L];
+    }
+    if (writes) {
+        const float st = static_cast<float>(static_cast<double>(a.alpha) * total);
+        a.S_t[at] = st;
+        if (a.S_u) {
+            const float u = a.rho * old_u + st;
+            a.S_u[at] = u;
+            a.S_v[at] = old_v + u;
+        }
+    }
+}
+
+IndexRows list_rows(const cs_params* p, int64_t d) {
+    IndexRows x{};
+    for (uint32_t j = 0; j < p->r; ++j) {
+        x.residues[j] = static_cast<uint64_t>(d);
+        x.at[j] = x.words;
+        x.words += p->c + 1 + x.residues[j];
+    }
+    return x;
 }
 
 bool params_ok(const cs_params* p) {
@@ -410,7 +548,7 @@ extern "C" int cs_update_index_build(const cs_params* p, int64_t d, void* index,
     if (!params_ok(p) || d < 0 || !index || reinterpret_cast<uintptr_t>(index) % 4 != 0) return CS_EINVAL;
     if (!sums_apply(p, d)) return CS_EINVAL;
     if (bytes < index_rows(p).words * sizeof(uint32_t)) return CS_EWORKSPACE;
-    return launch_index_build(p, static_cast<uint32_t*>(index), static_cast<hipStream_t>(stream));
+    return launch_index_build<true, false>(p, index_rows(p), static_cast<uint32_t*>(index), static_cast<hipStream_t>(stream));
 }
 
 extern "C" int cs_update_workspace_bytes(const cs_params* p, int32_t W, int64_t d, size_t* bytes) {
@@ -438,4 +576,80 @@ extern "C" int cs_bundle_sketch(const cs_params* p, float* T, int32_t W, const f
     if (index_bytes < index_rows(p).words * sizeof(uint32_t)) return CS_EWORKSPACE;
     return launch_bundle_sketch(p, T, W, g_w, d, scale, static_cast<const uint32_t*>(index), static_cast<float*>(ws),
                                 ws_bytes / sizeof(float), S_t, alpha, S_u, S_v, rho, static_cast<hipStream_t>(stream));
+}
+
+// Where the lists take less time than what else there is: about 4 us and r d W values at 250 G/s while the vectors lie in L2
+// (d W up to a million; 200 at 1.4, 180 at 4, 110 at 8 million), against (us, others / lists)
+//  * requests of every coordinate (short vectors, few columns): always: 7 x 32, d = 1947, 109 workers 35.8 / 10.3; 15 x 64,
+//    13 081, 99 workers 353 / 73; 3 x 73, 1573, 5 workers 7.8 / 4.0; 5 x 1913, 64 779, 1 worker 24.9 / 5.4;
+//  * visit lists of a power of two of columns, 13 to 16 us and 1.3 a million values, 2.7 with many groups of workers: 7 x 512,
+//    18 231, 8 workers (1.0 million) 13.9 / 7.0; 7 x 512, 65 729, 5 workers (2.3) 15.5 / 13.0; 7 x 2048, 73 440, 5 workers
+//    (2.6) 16.1 / 14.3; 5 x 512, 33 053, 42 workers (6.9) 30.7 / 32; with more than 8 rows, two launches: 15 x 1024,
+//    78 577, 4 workers (4.7) 29 / 23;
+//  * visit lists of other column counts: 7 x 2561, 217 913, 1 worker (1.5) 38.6 / 10; 5 x 853, 379 355, 2 workers (3.8)
+//    26.4 / 19; 3 x 847, 229 277, 7 workers (4.8, 1.6 million in the vectors) 20.4 / 24; 15 x 2277, 237 944, 3 workers (10.7)
+//    58.7 / 47.
+static bool lists_pay(const cs_params* p, int32_t W, int64_t d) {
+    const double vectors = static_cast<double>(d) * W, values = vectors * p->r;
+    if (vectors > 4e6) return false;
+    if (walk_applies(p, d)) return values <= (p->r > 8 ? (W > 16 ? 7e6 : 5e6) : W > 16 ? 5.5e6 : 3e6);
+    if (anyc_update_applies(p, d, W)) return vectors <= 1.2e6 && values <= (p->r > 8 ? 1e7 : 5e6);
+    return true;
+}
+
+extern "C" int cs_cell_lists_bytes(const cs_params* p, int32_t W, int64_t d, size_t* bytes) {
+    if (!params_ok(p) || W < 1 || d < 0 || !bytes) return CS_EINVAL;
+    *bytes = 0;
+    if (d >= 1 && d < (1ll << 30) && W <= kListVectors && lists_pay(p, W, d)) *bytes = list_rows(p, d).words * sizeof(uint32_t);
+    return CS_OK;
+}
+
+extern "C" int cs_cell_lists_build(const cs_params* p, int64_t d, void* lists, size_t bytes, void* stream) {
+    if (!params_ok(p) || d < 1 || d >= (1ll << 30) || !lists || reinterpret_cast<uintptr_t>(lists) % 4 != 0) return CS_EINVAL;
+    const IndexRows rows = list_rows(p, d);
+    if (bytes < rows.words * sizeof(uint32_t)) return CS_EWORKSPACE;
+    uint32_t* out = static_cast<uint32_t*>(lists);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    return p->c_pow2 ? launch_index_build<true, true>(p, rows, out, s) : launch_index_build<false, true>(p, rows, out, s);
+}
+
+extern "C" int cs_bundle_sketch_lists(const cs_params* p, float* T, int32_t W, const float* const* g_w, int64_t d,
+                                      float scale, const void* lists, size_t bytes, float* S_t, float alpha, float* S_u,
+                                      float* S_v, float rho, void* stream) {
+    if (!params_ok(p) || W < 1 || W > kListVectors || d < 1 || d >= (1ll << 30) || !g_w || !lists) return CS_EINVAL;
+    if ((!T && !S_t) || (!S_u != !S_v) || (S_u && !S_t)) return CS_EINVAL;
+    for (int w = 0; w < W; ++w)
+        if (!g_w[w]) return CS_EINVAL;
+    if (reinterpret_cast<uintptr_t>(lists) % 4 != 0) return CS_EINVAL;
+    if (bytes < list_rows(p, d).words * sizeof(uint32_t)) return CS_EWORKSPACE;
+    ListArgs a{};
+    a.lists = static_cast<const uint32_t*>(lists);
+    a.T = T;
+    a.S_t = S_t;
+    a.S_u = S_u;
+    a.S_v = S_v;
+    a.scale = scale;
+    a.alpha = alpha;
+    a.rho = rho;
+    a.r = p->r;
+    a.c = p->c;
+    a.d = static_cast<uint32_t>(d);
+    a.W = W;
+    for (int w = 0; w < W; ++w) a.g[w] = g_w[w];
+    const int groups = (W + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP;
+    a.slices = groups >= 4 ? 4 : groups >= 2 ? 2 : 1;
+    // about 65 536 lanes in all, and not more than 8 coordinates for each
+    const double want = 65536.0 / (static_cast<double>(p->r) * p->c * a.slices), each = static_cast<double>(d) / (8.0 * p->c);
+    int L = 8;
+    while (L < 64 && L < (want > each ? want : each)) L *= 2;
+    const uint32_t cells = kBlock / L / a.slices;      // of a workgroup
+    const dim3 grid((p->c + cells - 1) / cells, p->r);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    switch (L) {
+        case 8: k_sum_lists<8><<<grid, kBlock, 0, s>>>(a); break;
+        case 16: k_sum_lists<16><<<grid, kBlock, 0, s>>>(a); break;
+        case 32: k_sum_lists<32><<<grid, kBlock, 0, s>>>(a); break;
+        default: k_sum_lists<64><<<grid, kBlock, 0, s>>>(a);
+    }
+    return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }

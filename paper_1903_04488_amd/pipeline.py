@@ -26,6 +26,7 @@ class HotPath:
     # the update by way of running sums (cs_bundle_sketch), where the sketch has lists for it: its index, its
     # workspace, and what they were made for: the sketch's parameters, fold_workers, W and d
     _index = _sums_ws = _sums_params = _sums_for = None
+    _cell_lists = False                  # _index holds cell lists (cs_bundle_sketch_lists): short vectors
     SUMS_OWN_BYTES = 2 << 30             # the workspace: up to here, else the path does without (0: in any case)
 
     def __init__(self, d: int, W: int, r: int, c: int, k: int, seed: int,
@@ -37,7 +38,8 @@ class HotPath:
         S_t): no worker tables, no merge.  The scratch is the query's, so the stages of one
         path run one after the other; where the query has none (short vectors and column counts
         without a traversal plan) the path holds d floats more.
-        Memory beside the tables and est: the query's scratch (r d floats for long vectors), and where the update goes
+        Memory beside the tables and est: the query's scratch (r d floats for long vectors), for short vectors the lists of
+        the cells' coordinates (r (c + d) words, 1.3 MB at d = 65 536, 5 x 1024), and where the update goes
         by way of running sums (up to 4 workers, up to 16 with short vectors, up to 64 with vectors of 32 million on)
         their index and workspace, 35 MB at d = 6.5 M, W = 4, 5 x 2^17 and 1.9 GB at d = 10^8, W = 32, 5 x 2^20, where they
         save 1.8 % of the update: SUMS_OWN_BYTES, of the class or a subclass, bounds the workspace."""
@@ -74,7 +76,8 @@ class HotPath:
         self.g_mean = None
         if fold_workers and W > 1:
             self._mean_buffer(d)
-        self._build_index()
+        if not self._build_cell_lists():
+            self._build_index()
 
     # individual stages (bench.py times them separately) ---------------------------------
     def worker_table(self, w: int):
@@ -91,6 +94,22 @@ class HotPath:
             self.g_mean = (self.est_ws[:4 * size].view(torch.float32) if fits
                            else torch.empty(size, dtype=torch.float32, device=self.device))
         return self.g_mean[:n]
+
+    def _build_cell_lists(self):
+        """for short vectors; True where there are some"""
+        # folded workers: all of them cell by cell while that is less than a launch more, else their sum
+        few = self.r * self.d * self.W <= 1_250_000
+        for W in ((self.W, 1) if few else (1,)) if self.fold_workers else (self.W,):
+            n = B.cs_cell_lists_bytes(self.params, W, self.d)
+            if n:
+                self._index = torch.empty(n, dtype=torch.uint8, device=self.device)
+                B.cs_cell_lists_build(self.params, self.d, self._index)
+                self._cell_lists = True
+                self._sum_first = W < self.W
+                self._sums_params = self._lists()
+                self._sums_for = self.fold_workers, self.W, self.d
+                return True
+        return False
 
     def _build_index(self):
         n = B.cs_update_index_bytes(self.params, 0 if self.fold_workers else self.W, self.d)
@@ -120,7 +139,7 @@ class HotPath:
         if self._index is None:
             return False
         fold, W, d = self._sums_for
-        return (self.fold_workers == fold and (fold or len(g_w) == W) and g_w[0].numel() == d
+        return (self.fold_workers == fold and (len(g_w) == W or fold and not self._cell_lists) and g_w[0].numel() == d
                 and self._lists() == self._sums_params)
 
     def _mean(self, g_w):
@@ -134,6 +153,14 @@ class HotPath:
 
     def _sketch_indexed(self, g_w, **tables):
         """accumulate, and with the tables S_t (S_u, S_v) what follows it, in the pass that gathers the sums"""
+        if self._cell_lists:
+            T, alpha = self.T, 1.0 / self.W
+            if self.fold_workers:
+                T, tables = None, {"S_t": self.S_t, **tables}
+                if self._sum_first:
+                    g_w, alpha = [self._mean(g_w)], 1.0
+            B.cs_bundle_sketch_lists(self.params, T, g_w, self._index, alpha=alpha, **tables)
+            return
         if not self.fold_workers:
             B.cs_bundle_sketch(self.params, self.T, g_w, self._index, self._sums_ws, alpha=1.0 / self.W, **tables)
         elif len(g_w) == 1:
@@ -255,8 +282,11 @@ class ReproduciblePath(HotPath):
     `dropped` counts the coordinates that were left out (not finite, or too large for the
     chosen frac_bits) since the object was made."""
 
+    def _build_cell_lists(self):
+        return False                                  # (its update is another)
+
     def _build_index(self):
-        pass                                          # (its update is another)
+        pass
 
     def __init__(self, d, W, r, c, k, seed, rho=None, device="cuda:0", frac_bits: int = 40):
         super().__init__(d, 1, r, c, k, seed, rho=rho, device=device)     # no bundle of W tables
