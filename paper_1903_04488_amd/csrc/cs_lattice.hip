@@ -358,7 +358,7 @@ int launch_accumulate_lattice(const cs_params* p, const LatticePtrs& ptrs, int n
 int launch_estimate_lattice(const cs_params* p, const float* S, int64_t d, int64_t i0,
                             float* est, float* rows, uint64_t* hist, hipStream_t stream) {
     if (walk_applies(p, d)) {
-        const bool fuse_last = d >= (static_cast<int64_t>(1) << 24);
+        const bool fuse_last = walk_takes_median(p, d);
         const int rc = launch_estimate_walk(p, S, d, i0, est, rows, fuse_last, hist, stream);
         if (rc != CS_OK || fuse_last) return rc;
     } else {

@@ -1832,18 +1832,25 @@ int launch_accumulate_walk(const cs_params* p, float* T, int W, const float* con
 // ---------------------------------------------------------------------------------------
 // Alg. 4 estimate, walk order: rows[j][i] = s_j(i) S[j][h_j(i)] for every coordinate.
 //
-// The same stride serves the query: a lane that walks i, i + Dw, i + 2 Dw, ... stays in one
-// cell for ~1/sigma visits, so it keeps that cell's value in a register and gathers again
-// only when it leaves the cell (one gather per ~10 coordinates instead of one per
-// coordinate).  The 64 lanes of a wavefront own 64 neighbouring chunks of 4 residues, so
-// every visit writes 1 KB of contiguous output, 16 bytes per lane.  A second kernel takes the
-// median over rows.
+// The same stride serves the query.  A visit moves every hash on by the same A = (a n Dw) mod p, so a coordinate that
+// began in cell b is in cell b + A mod c, or one further where its hash wrapped past p, which a comparison with p - A tells
+// (as in the update along lists, with whole hash values here: there is nothing left to be unsure of); the sign is
+// that of the first visit, turned by the parity of A' and by a wrap.  A mod c is the same for the whole
+// wavefront and moves by one cell in ~1/sigma visits, so a lane keeps the four neighbouring cells ahead of
+// each coordinate, which are one 16-byte load, and loads again after three such steps (~30 visits).  The
+// 64 lanes of a wavefront own 64 neighbouring chunks of 4 residues, so every visit writes 1 KB of contiguous output, 16
+// bytes per lane.  A second kernel takes the median over rows, or the walk of the last row does.
+// Against two 61-bit states a coordinate, moved on at each visit, and a gather whenever a coordinate leaves its cell
+// (some of a wavefront's 256 does at nearly every visit), with the accesses of load_values below, the whole query with counts, us: 4 M
+// x 5 rows of 65 536 columns 56 -> 47; 6.5 M, 5 x 2^17 77 -> 59; 6.5 M, 15 x 65 536 204 -> 157; 11 M, 5 x 2^18 117 -> 91; 25 M,
+// 5 x 2^19 232 -> 205; 25 M, 7 x 2^19 342 -> 276; 50 M, 3 x 2^18 276 -> 226; 10^8, 5 x 2^20 939 -> 733.  Bound: the scratch, and the
+// first gathers of long rows, whose residues (2 to 4 million a row) each fetch a line of a table that L2 does not
+// hold (10^8: 350 us for rows 0 .. 3, 290 without those loads).
 // ---------------------------------------------------------------------------------------
 namespace {
 
 // Coordinates per lane and visit.  Four: a lane's values are one 16-byte piece of output, so no
-// transpose is needed, and the registers that 16 coordinates took (cell and value of each) are
-// better spent on twice as many resident wavefronts -- the kernel waits on its gathers.
+// transpose is needed.
 constexpr int kQRun = 4;
 
 // A short vector leaves a row with few chunks (Dw / 256 wavefronts) and a long serial chain
@@ -1857,6 +1864,32 @@ struct RowSegments {
     uint32_t first[CS_MAX_R];    // ~0: no such row
 };
 
+constexpr int kQWave = 64 * kQRun;                     // residues of a wavefront
+constexpr int kQLine = 32;                             // floats of a line of memory
+// How the scratch is written.  What the memory-side cache (256 MB) holds, the stride walk writes and reads with ordinary
+// accesses: pieces of 1 KB that begin anywhere are written at 5.8 TB/s then, and at 3.8 with nontemporal stores, which do not put
+// together in L2 a line that two wavefronts write in part each.  A larger scratch goes to memory, where such a line
+// costs about four times a whole one (400 MB: pieces anywhere 4.4 TB/s ordinary and 3.7 nontemporal, pieces on lines
+// 5.1; 1.6 GB: 4.0, 3.4, 5.4), and ordinary accesses push the sketch out of L2 (query of 5 rows of 100 M on lines, ordinary /
+// nontemporal: 995 / 845 us).  With LINES, then, a wavefront also works out the 32 residues behind its own and writes the
+// 256 that begin on a line (one short part at each visit's ends), past the caches.  Where that pays for the quarter more
+// arithmetic, by r d (us, ordinary pieces anywhere / lines): 11M x 5 rows 92 / 104, 16M x 5 143 / 130, 12M x 7
+// 139 / 142, 16M x 7 194 / 172, 6.5M x 15 157 / 171, 9M x 15 225 / 225, 25M x 15 717 / 583.  Lists (other column counts), whose accesses are
+// all nontemporal (ordinary: 2M x 5 rows of 41 111 columns 38 / 41, 30M x 5 280 / 300): 17M x 5 184 / 201, 22M x 5 214 / 209,
+// 30M x 5 280 / 258, 10M x 15 339 / 360, 20M x 15 627 / 570, 90M x 15 2439 / 2136.
+constexpr uint32_t kManyRows = 7;
+constexpr int64_t kWalkLinesFrom = 75000000, kWalkLinesFromMany = 120000000;
+constexpr int64_t kLinesFrom = 110000000, kLinesFromMany = 200000000;
+template <bool NT>
+__device__ __forceinline__ vec4f load_values(const float* p) {
+    if (NT) return __builtin_nontemporal_load(reinterpret_cast<const vec4f_u*>(p));
+    return *reinterpret_cast<const vec4f_u*>(p);
+}
+template <bool NT>
+__device__ __forceinline__ void store_values(float* p, vec4f u) {
+    if (NT) __builtin_nontemporal_store(u, reinterpret_cast<vec4f_u*>(p));
+    else *reinterpret_cast<vec4f_u*>(p) = u;
+}
 // RF = 0: rows[j][i] for the rows j = blockIdx.y.  RF = R (the row count): the walk of the last
 // row, which instead of storing its values reads those of rows 0 .. R-2 at the same coordinates
 // and writes their median, est[i] -- the last row never goes through memory.
@@ -1867,7 +1900,7 @@ struct RowSegments {
 // the end; a workgroup of kHistWaves wavefronts shares one set of counters (8 KB), so that LDS
 // does not limit how many wavefronts a CU holds.
 constexpr int kHistWaves = 4;
-template <int RF, bool HIST>
+template <int RF, bool HIST, bool LINES>
 __global__ void __launch_bounds__(HIST ? 64 * kHistWaves : 64)
 k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int64_t d, int64_t i0,
                   float* __restrict__ rows, float* __restrict__ est,
@@ -1875,6 +1908,7 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
     static_assert(kQRun == 4, "one 16-byte piece per lane");
     static_assert(!HIST || RF > 0, "only the kernel that writes est can count it");
     constexpr int NW = HIST ? kHistWaves : 1;          // wavefronts per workgroup
+    constexpr int kOwn = kQRun + (LINES ? 1 : 0);
     const int lane = threadIdx.x & 63;
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int j = RF ? RF - 1 : 0;
@@ -1888,6 +1922,8 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
     if (RF == 0 && hist && blockIdx.x == 0)
         for (int t = threadIdx.x; t < 2048; t += 64) hist[t] = 0;
     __shared__ uint32_t lh[HIST ? 2048 : 1];
+    __shared__ __align__(16) float turn_all[LINES ? NW : 1][LINES ? kQWave + kQLine : 4];
+    float* turn = turn_all[LINES ? wq : 0];
     if (HIST) {
         for (int t = threadIdx.x; t < 2048; t += 64 * NW) lh[t] = 0;
         __syncthreads();
@@ -1901,95 +1937,175 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
     const int64_t nD1 = visits * (seg + 1) / nseg * D;
     const uint64_t ADb = p.plan[j].ADw, ADs = p.plan[j].ADws;
     const uint64_t Ab = p.a[j], As = p.as[j];
-    const int64_t chunks = (D + kQRun - 1) / kQRun;
-    const int64_t nwaves = (chunks + 63) / 64;
+    const int64_t nwaves = (D + kQWave - 1) / kQWave;
     const uint32_t mask = p.c - 1u;
+    const bool down = (static_cast<uint32_t>(ADb) & mask) > mask / 2;      // the stride leads to lower cells
     const float* __restrict__ Sj = S + static_cast<size_t>(j) * p.c;
     float* __restrict__ out = rows + static_cast<size_t>(j) * d;
+    // floats from the last line boundary to the coordinate 0 that I write
+    const uint32_t line0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(RF ? est : out) / sizeof(float)) % kQLine;
 
     const int64_t per_xcd = (nwaves + 7) / 8;
     const int64_t xcd_first = static_cast<int64_t>(bx & 7) * per_xcd;
     for (int64_t k = static_cast<int64_t>(bx >> 3) * NW + wq; k < per_xcd; k += static_cast<int64_t>(across >> 3) * NW) {
         const int64_t wv = xcd_first + k;
         if (wv >= nwaves) break;
-        const int64_t chunk0 = wv * 64;
-        const int64_t my_off = (chunk0 + lane) * kQRun;          // my residue offset in [0, Dw)
-        uint64_t yb = hash_state(p.a[j], p.b[j], static_cast<uint64_t>(i0 + nD0 + my_off));
-        uint64_t ys = hash_state(p.as[j], p.bs[j], static_cast<uint64_t>(i0 + nD0 + my_off));
-        uint32_t cur[kQRun];
-        float val[kQRun];
+        const int64_t wave_off = wv * kQWave;                    // residue offsets in [0, Dw): of the wavefront
+        const int64_t my_off = wave_off + lane * kQRun;          // and mine
+        // my residues: four neighbours, and with LINES one of the kQLine that follow the wavefront's
+        uint64_t yb[kOwn], ys[kOwn];                             // hash states at the segment's first visit
+        yb[0] = hash_state(Ab, p.b[j], static_cast<uint64_t>(i0 + nD0 + my_off));
+        ys[0] = hash_state(As, p.bs[j], static_cast<uint64_t>(i0 + nD0 + my_off));
 #pragma unroll
-        for (int m = 0; m < kQRun; ++m) { cur[m] = 0xffffffffu; val[m] = 0.0f; }
-
-        for (int64_t nD = nD0; nD < nD1 && nD + chunk0 * kQRun < d; nD += D) {
-            int64_t my_len = D - my_off;                         // coordinates of mine that exist
-            if (d - (nD + my_off) < my_len) my_len = d - (nD + my_off);
+        for (int m = 1; m < kQRun; ++m) {
+            yb[m] = hash_advance(yb[m - 1], Ab);
+            ys[m] = hash_advance(ys[m - 1], As);
+        }
+        if constexpr (LINES) {
+            yb[kQRun] = hash_state(Ab, p.b[j], static_cast<uint64_t>(i0 + nD0 + wave_off + kQWave + lane % kQLine));
+            ys[kQRun] = hash_state(As, p.bs[j], static_cast<uint64_t>(i0 + nD0 + wave_off + kQWave + lane % kQLine));
+        }
+        // Values of four neighbouring cells of every coordinate, times the sign at the first visit, in the order in which
+        // the stride leads through them; the coordinate is in the first or the second.
+        float win[kOwn][4];
+        uint32_t q = 0, left = 0;                                // cells moved on by; cells behind the second one
+        auto load_cells = [&]() {
+            const uint32_t lowest = down ? q - 2u : q;
+            uint32_t f[kOwn];
+            bool edge = false;
+#pragma unroll
+            for (int m = 0; m < kOwn; ++m) {
+                f[m] = (static_cast<uint32_t>(yb[m]) - 1u + lowest) & mask;
+                edge |= f[m] > mask - 3u;
+            }
+            const bool some_edge = __builtin_amdgcn_ballot_w64(edge) != 0;
+#pragma unroll
+            for (int m = 0; m < kOwn; ++m) {
+                vec4f u;
+                if (!some_edge) {
+                    u = *reinterpret_cast<const vec4f_u*>(Sj + f[m]);
+                } else {                                         // a row's last cells are followed by its first
+                    u.x = Sj[f[m]];
+                    u.y = Sj[(f[m] + 1u) & mask];
+                    u.z = Sj[(f[m] + 2u) & mask];
+                    u.w = Sj[(f[m] + 3u) & mask];
+                }
+                const uint32_t flip = sign_flip_of(ys[m]);
+                win[m][0] = apply_sign(down ? u.w : u.x, flip);
+                win[m][1] = apply_sign(down ? u.z : u.y, flip);
+                win[m][2] = apply_sign(down ? u.y : u.z, flip);
+                win[m][3] = apply_sign(down ? u.x : u.w, flip);
+            }
+            left = 2;
+        };
+        load_cells();
+        uint64_t A = 0, As_n = 0;                                // how far the visit moves every hash on
+        for (int64_t nD = nD0; nD < nD1 && nD + wave_off < d; nD += D) {
+            // residues from wave_off on that exist
+            const int64_t in_gap = D - wave_off, in_vec = d - nD - wave_off;
+            const int64_t room = in_gap < in_vec ? in_gap : in_vec;
+            const int len = static_cast<int>(room < kQWave + kQLine ? room : kQWave + kQLine);
+            // with LINES the wavefront writes from its first whole line on, and on into the line of its last residue
+            const uint32_t t = LINES ? (0u - (line0 + static_cast<uint32_t>(nD + wave_off))) % kQLine : 0u;
+            const int my_len = len - static_cast<int>(t) - lane * kQRun;      // of the 4 that I write: >= 4 all, <= 0 none
+            const int64_t at = nD + my_off + t;
             [[maybe_unused]] vec4f other[RF > 1 ? RF - 1 : 1];       // the other rows' values, requested early
             if constexpr (RF > 1) {
                 if (my_len >= kQRun) {
 #pragma unroll
-                    for (int q = 0; q < RF - 1; ++q)
-                        other[q] = __builtin_nontemporal_load(reinterpret_cast<const vec4f_u*>(
-                            rows + static_cast<size_t>(q) * d + nD + my_off));
+                    for (int z = 0; z < RF - 1; ++z)
+                        other[z] = load_values<LINES>(rows + static_cast<size_t>(z) * d + at);
                 }
             }
-            uint64_t tb = yb, ts = ys;
-            float o[kQRun];
+            if ((static_cast<uint32_t>(A) & mask) != q) {
+                const uint32_t q_new = static_cast<uint32_t>(A) & mask;
+                const uint32_t by = (down ? q - q_new : q_new - q) & mask;
+                q = q_new;
+                if (by == 1 && left > 0) {
 #pragma unroll
-            for (int m = 0; m < kQRun; ++m) {
-                const uint32_t cell = (static_cast<uint32_t>(tb) - 1u) & mask;
-                if (cell != cur[m] && m < my_len) {              // entered a new cell: fetch it
-                    cur[m] = cell;
-                    val[m] = Sj[cell];
+                    for (int m = 0; m < kOwn; ++m) {
+                        win[m][0] = win[m][1];
+                        win[m][1] = win[m][2];
+                        win[m][2] = win[m][3];
+                    }
+                    --left;
+                } else {
+                    load_cells();
                 }
-                o[m] = apply_sign(val[m], sign_flip_of(ts));
-                tb = hash_advance(tb, Ab);
-                ts = hash_advance(ts, As);
             }
-            yb = hash_advance(yb, ADb);
-            ys = hash_advance(ys, ADs);
+            const uint64_t wraps = kP61 - A, flips = kP61 - As_n;    // a state above them passes p
+            const bool odd = (As_n & 1u) != 0;
+            float o[kOwn];
+#pragma unroll
+            for (int m = 0; m < kOwn; ++m) {
+                const float x = (yb[m] > wraps) != down ? win[m][1] : win[m][0];
+                o[m] = (ys[m] > flips) != odd ? -x : x;
+            }
+            A += ADb;
+            A = A >= kP61 ? A - kP61 : A;
+            As_n += ADs;
+            As_n = As_n >= kP61 ? As_n - kP61 : As_n;
+            vec4f mine;
+            mine.x = o[0]; mine.y = o[1]; mine.z = o[2]; mine.w = o[3];
+            [[maybe_unused]] float head = 0.0f;
+            if constexpr (LINES) {
+                *reinterpret_cast<vec4f*>(turn + lane * kQRun) = mine;
+                if (lane < kQLine) turn[kQWave + lane] = o[kQRun];
+                __builtin_amdgcn_wave_barrier();
+                mine = *reinterpret_cast<const vec4f_u*>(turn + t + lane * kQRun);
+                head = turn[lane % kQLine];
+                __builtin_amdgcn_wave_barrier();
+            }
+            // the visit's first residues, before its first whole line
+            const bool heads = LINES && wave_off == 0 && lane < static_cast<int>(t) && lane < len;
             if constexpr (RF > 0) {
-                float* dst = est + nD + my_off;
+                float* dst = est + at;
                 if (my_len >= kQRun) {
                     float vx[RF], vy[RF], vz[RF], vw[RF];
 #pragma unroll
-                    for (int q = 0; q < RF - 1; ++q) {
-                        vx[q] = other[q].x; vy[q] = other[q].y; vz[q] = other[q].z; vw[q] = other[q].w;
+                    for (int z = 0; z < RF - 1; ++z) {
+                        vx[z] = other[z].x; vy[z] = other[z].y; vz[z] = other[z].z; vw[z] = other[z].w;
                     }
-                    vx[RF - 1] = o[0]; vy[RF - 1] = o[1]; vz[RF - 1] = o[2]; vw[RF - 1] = o[3];
+                    vx[RF - 1] = mine.x; vy[RF - 1] = mine.y; vz[RF - 1] = mine.z; vw[RF - 1] = mine.w;
                     vec4f u;
                     float med[4];
                     medians_odd<RF>(vx, vy, vz, vw, med);
                     u.x = med[0]; u.y = med[1]; u.z = med[2]; u.w = med[3];
-                    __builtin_nontemporal_store(u, reinterpret_cast<vec4f_u*>(dst));
+                    store_values<LINES>(dst, u);
                     tally(u.x); tally(u.y); tally(u.z); tally(u.w);
                 } else {
                     for (int m = 0; m < kQRun; ++m) {
                         if (m >= my_len) break;
                         float v[RF];
 #pragma unroll
-                        for (int q = 0; q < RF - 1; ++q) v[q] = rows[static_cast<size_t>(q) * d + nD + my_off + m];
-                        v[RF - 1] = o[m];
+                        for (int z = 0; z < RF - 1; ++z) v[z] = rows[static_cast<size_t>(z) * d + at + m];
+                        v[RF - 1] = mine[m];
                         const float med = median_odd<RF>(v);
                         dst[m] = med;
                         tally(med);
                     }
                 }
+                if (heads) {
+                    float v[RF];
+#pragma unroll
+                    for (int z = 0; z < RF - 1; ++z) v[z] = rows[static_cast<size_t>(z) * d + nD + lane];
+                    v[RF - 1] = head;
+                    const float med = median_odd<RF>(v);
+                    est[nD + lane] = med;
+                    tally(med);
+                }
                 continue;
             }
             // the wavefront's 64 pieces are 1 KB of contiguous rows[j][i]
-            float* dst = out + nD + my_off;
+            float* dst = out + at;
             if (my_len >= kQRun) {
-                vec4f u;
-                u.x = o[0]; u.y = o[1]; u.z = o[2]; u.w = o[3];
-                // streamed out, read once by the median kernel: kept out of the way of the
-                // table row that the gathers want to find in L2
-                __builtin_nontemporal_store(u, reinterpret_cast<vec4f_u*>(dst));
+                store_values<LINES>(dst, mine);
             } else if (my_len > 0) {
-                dst[0] = o[0];
-                if (my_len > 1) dst[1] = o[1];
-                if (my_len > 2) dst[2] = o[2];
+                dst[0] = mine.x;
+                if (my_len > 1) dst[1] = mine.y;
+                if (my_len > 2) dst[2] = mine.z;
             }
+            if (heads) out[nD + lane] = head;
         }
     }
     if (HIST) {
@@ -2021,25 +2137,6 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
 // 15 rows of 90 M (10.4 GB of traffic: 1.7 ms at 6.2 TB/s) and 744 us for 5 rows of 73 M; now 2236 and 569.
 // ---------------------------------------------------------------------------------------
 constexpr int kQueryWaves = 4;                         // wavefronts per workgroup: one table of visits, one set of counters
-constexpr int kQWave = 64 * kQRun;                     // residues of a wavefront
-constexpr int kQLine = 32;                             // floats of a line of memory
-// Where the scratch is larger than the memory-side cache (256 MB), a line that two wavefronts write in part each
-// costs about four times a whole one: 1 KB pieces that begin anywhere are written at 3.1 to 5.0 TB/s, pieces on lines at 4.1
-// to 6.9, and the row kernels spent 1520 of the 2700 us of 15 rows of 90 M at 3.3 TB/s.  With LINES a wavefront also works out
-// the 32 residues behind its own and writes the 256 that begin on a line (one short part at each visit's ends).  That is a
-// quarter more arithmetic, so only from r d = 200 million on (us, pieces anywhere / on lines: 6.5M x 5 rows 85 / 94,
-// 20M x 5 215 / 241, 30M x 5 280 / 298, 20M x 15 648 / 651, 50M x 5 452 / 412, 73M x 5 651 / 569, 90M x 15 2697 / 2236).
-constexpr int64_t kLinesFrom = 200000000;
-template <bool LINES>
-__device__ __forceinline__ vec4f load_values(const float* p) {
-    if (LINES) return *reinterpret_cast<const vec4f_u*>(p);
-    return __builtin_nontemporal_load(reinterpret_cast<const vec4f_u*>(p));
-}
-template <bool LINES>
-__device__ __forceinline__ void store_values(float* p, vec4f u) {
-    if (LINES) *reinterpret_cast<vec4f*>(p) = u;
-    else __builtin_nontemporal_store(u, reinterpret_cast<vec4f_u*>(p));
-}
 template <int RF, int NC, bool HIST, bool LINES>
 __global__ void __launch_bounds__(64 * kQueryWaves)
 k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, int64_t d, int64_t i0,
@@ -2127,7 +2224,7 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
                 if (my_len >= kQRun) {
 #pragma unroll
                     for (int q = 0; q < RF - 1; ++q)
-                        other[q] = load_values<LINES>(rows + static_cast<size_t>(q) * d + at);
+                        other[q] = load_values<true>(rows + static_cast<size_t>(q) * d + at);
                 }
             }
             bool flip[kOwn], wrap[kOwn], unsure = false;
@@ -2188,7 +2285,7 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
                     float med[4];
                     medians_odd<RF>(vx, vy, vz, vw, med);
                     u.x = med[0]; u.y = med[1]; u.z = med[2]; u.w = med[3];
-                    store_values<LINES>(est + at, u);
+                    store_values<true>(est + at, u);
                     tally(u.x); tally(u.y); tally(u.z); tally(u.w);
                 } else {
                     for (int m = 0; m < kQRun; ++m) {
@@ -2214,7 +2311,7 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
             } else {
                 float* dst = out + at;
                 if (my_len >= kQRun) {
-                    store_values<LINES>(dst, mine);
+                    store_values<true>(dst, mine);
                 } else if (my_len > 0) {
                     dst[0] = mine.x;
                     if (my_len > 1) dst[1] = mine.y;
@@ -2259,7 +2356,7 @@ int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t 
         if (n > 16) n = 16;
         return static_cast<unsigned>(n < 1 ? 1 : n);
     };
-    const bool lines = static_cast<int64_t>(p->r) * d >= kLinesFrom && reinterpret_cast<uintptr_t>(est) % 4 == 0;
+    const bool lines = static_cast<int64_t>(p->r) * d >= (p->r > kManyRows ? kLinesFromMany : kLinesFrom);
     const uint32_t last = p->r - 1;
     VisitGapsRows vr{};
     const int rc = for_each_anyc_launch(p, last, [&](const uint32_t* js, int n, uint32_t omega) {
@@ -2310,13 +2407,26 @@ int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t 
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
-// fuse_last = false: all rows into the scratch (the caller takes the median).  fuse_last = true:
-// the last row's walk takes the median itself; worth it for long vectors, where the scratch
-// traffic it saves (write and read of one row) outweighs a second, narrower launch.
+// Whether the last row's walk takes the median itself (launch_estimate_walk), or all rows go into the scratch and the
+// caller takes it.  The scratch traffic it saves (write and read of one row) has to outweigh a second, narrower
+// launch, and the other rows' values at places of one row's order, one piece of each, are read more slowly than in a
+// row.  Query with counts, us, apart / fused: 5 rows 1.5 M 33 / 35, 4 M 47 / 48, 6.5 M 61 / 59, 11 M 104 / 91; 3 rows of
+// 10 M 61 / 58; but 7 rows of 12 M 139 / 166, 15 of 6.5 M 158 / 196.
+static bool walk_in_lines(const cs_params* p, int64_t d) {
+    return d * static_cast<int64_t>(p->r) >= (p->r > kManyRows ? kWalkLinesFromMany : kWalkLinesFrom);
+}
+bool walk_takes_median(const cs_params* p, int64_t d) {
+    return walk_in_lines(p, d) || (p->r <= 5 && d >= 5'000'000);
+}
+
 // hist: cleared; with fuse_last it also receives the counts of est by magnitude bin.
 int launch_estimate_walk(const cs_params* p, const float* S, int64_t d, int64_t i0,
                          float* est, float* rows, bool fuse_last, uint64_t* hist, hipStream_t stream) {
-    // about 2048 wavefronts per row, at least 4 visits per segment
+    // Segments of the chains of visits: about 2048 wavefronts per row, of at least 4 visits; where the scratch goes to
+    // memory up to 16 384 wavefronts of at least 16 (us, 2048 / 4096 / 8192: 16 M x 5 rows 141 / 130 / 149, 40 M 320 / 291 / 292,
+    // 100 M 844 / 770 / 748, 16 384 737).
+    const bool lines = walk_in_lines(p, d);
+    const int64_t most_waves = lines ? 16384 : 2048, least_visits = lines ? 16 : 4;
     RowSegments segs{};
     uint32_t total = 0, before_last = 0;
     for (uint32_t j = 0; j < CS_MAX_R; ++j) segs.first[j] = ~0u;
@@ -2324,8 +2434,8 @@ int launch_estimate_walk(const cs_params* p, const float* S, int64_t d, int64_t 
         const int64_t Dw = static_cast<int64_t>(p->plan[j].Dw);
         const int64_t nwaves = ((Dw + kQRun - 1) / kQRun + 63) / 64;
         const int64_t visits = (d + Dw - 1) / Dw;
-        int64_t n = 2048 / nwaves;
-        if (n > visits / 4) n = visits / 4;
+        int64_t n = most_waves / nwaves;
+        if (n > visits / least_visits) n = visits / least_visits;
         if (n < 1) n = 1;
         if (n > 1024) n = 1024;
         segs.n[j] = static_cast<int>(n);
@@ -2335,12 +2445,14 @@ int launch_estimate_walk(const cs_params* p, const float* S, int64_t d, int64_t 
     }
     unsigned long long* h = reinterpret_cast<unsigned long long*>(hist);
     if (!fuse_last) {
-        k_row_values_walk<0, false><<<total, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);
+        if (lines) k_row_values_walk<0, false, true><<<total, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);
+        else k_row_values_walk<0, false, false><<<total, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);
         return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
     }
     // rows 0 .. r-2 into the scratch, then the last row together with the median
     if (p->r > 1) {
-        k_row_values_walk<0, false><<<before_last, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);
+        if (lines) k_row_values_walk<0, false, true><<<before_last, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);
+        else k_row_values_walk<0, false, false><<<before_last, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);
     } else if (h) {
         const int rc = launch_magnitude_hist_zero(hist, stream);
         if (rc != CS_OK) return rc;
@@ -2349,8 +2461,10 @@ int launch_estimate_walk(const cs_params* p, const float* S, int64_t d, int64_t 
     const uint32_t hgrid = ((segs.across[last] + kHistWaves - 1) / kHistWaves + 7) / 8 * 8 * nlast;
 #define CS_LAST(R_)                                                                                    \
     case R_:                                                                                           \
-        if (h) k_row_values_walk<R_, true><<<hgrid, 64 * kHistWaves, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h); \
-        else k_row_values_walk<R_, false><<<grid, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);  \
+        if (h && lines) k_row_values_walk<R_, true, true><<<hgrid, 64 * kHistWaves, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h); \
+        else if (h) k_row_values_walk<R_, true, false><<<hgrid, 64 * kHistWaves, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h); \
+        else if (lines) k_row_values_walk<R_, false, true><<<grid, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);  \
+        else k_row_values_walk<R_, false, false><<<grid, 64, 0, stream>>>(kparams(p), segs, S, d, i0, rows, est, h);  \
         break;
     switch (p->r) {
         CS_LAST(1) CS_LAST(3) CS_LAST(5) CS_LAST(7) CS_LAST(9) CS_LAST(11) CS_LAST(13) CS_LAST(15)
