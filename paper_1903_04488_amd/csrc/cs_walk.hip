@@ -1048,13 +1048,17 @@ int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js,
 }
 
 // the visit list of row j serves vectors of length d, and (unless any_cost) is expected to take
-// less time than the stride walk
+// less time than the stride walk in a launch of its own.  The time model prices a row alone, and visits that its walkers
+// pass over too, so up to a quarter more than the walk is less in the launch of all rows (us, 8 workers unless said, such a row by
+// the walk / its list, priced 1.02 to 1.13 times the walk: 7 x 2^19, 25 M 1075 / 1025, 2 workers 506 / 469; 7 x 65 536, 22 M 849 / 801;
+// 5 x 2^20, 18 M 853 / 776; 15 x 2^20, 48 M, 5 workers 6181 / 4884; 15 x 2^18, 24 M, 2 workers 3056 / 2125; 15 x 32 768, 17 M 1408 / 1393;
+// the one that lost: 15 x 2^20, 61 M, 3 workers 4783 / 4873).
 bool visits_apply(const cs_params* p, uint32_t j, int64_t d, bool any_cost = false) {
     const cs_visit_plan& vp = p->visit[j];
     if ((p->flags & CS_FLAG_NO_VISIT_LIST) != 0 || vp.K == 0) return false;
     if (vp.ncell < 2 || vp.ncell > 4 || vp.K > CS_MAX_VISITS || d > kStepsMaxD) return false;   // (lists end at 2^28)
     if (static_cast<uint64_t>(d) > vp.cover) return false;
-    return any_cost || vp.cost < vp.cost_walk;
+    return any_cost || vp.cost <= vp.cost_walk + vp.cost_walk / 4;
 }
 
 // Groups of 8 workers that share a launch, `most` at most.  A launch of one group of short vectors is a chain of visits
@@ -1710,10 +1714,9 @@ int partial_group(const cs_params* p, VisitWorkers& a, int groups, SumsPlan& pla
 // them by cell fetches a block for each (5 x 180 000, d = 6.5 M, 8 workers: update 181 us and gathering 78, for
 // 255 with requests to the table).
 bool sums_apply(const cs_params* p, int64_t d) {
-    if (!p->c_pow2 || !all_rows_listed(p, d)) return false;
-    // (a list that is priced a little above the stride walk still belongs into the one launch of all rows)
+    if (!p->c_pow2 || !walk_applies(p, d)) return false;
     for (uint32_t j = 0; j < p->r; ++j)
-        if (p->visit[j].cost > p->visit[j].cost_walk + p->visit[j].cost_walk / 4) return false;
+        if (!visits_apply(p, j, d)) return false;
     return lists_hold(p);
 }
 
