@@ -1,0 +1,60 @@
+"""Merge of separate tables and the second round's gather: pieces of several tables and vectors in flight, remainders of
+both, and tables that do not begin on 16 bytes.  The sums are taken in ascending order (binary64 and binary32) and the
+factors are powers of two, so that every bit is determined."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import paper_1903_04488_amd as cs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _table(values, shift):
+    """the values on the device, `shift` floats past a 16-byte boundary"""
+    room = torch.empty(values.size + shift, dtype=torch.float32, device=DEV)
+    t = room[shift:].view(values.shape)
+    t.copy_(torch.from_numpy(values))
+    assert t.data_ptr() % 16 == 4 * shift % 16
+    return t
+
+
+@pytest.mark.parametrize("shift_dst, shift_src", [(0, 0), (1, 0), (0, 3)])
+@pytest.mark.parametrize("r, c", [(1, 1), (1, 3), (3, 33), (5, 1 << 12)])
+@pytest.mark.parametrize("W", [1, 2, 5, 8, 9, 128, 130])
+def test_merge_bit_for_bit(W, r, c, shift_dst, shift_src):
+    rng = np.random.default_rng(W * 1000 + c)
+    p = cs.cs_params_init(r, c, 3)
+    tabs = [rng.standard_normal((r, c)).astype(np.float32) for _ in range(W)]
+    dst0 = rng.standard_normal((r, c)).astype(np.float32)
+    # (the last source alone is off the boundary: one is enough to take the other loads)
+    src = [_table(t, shift_src if w == W - 1 else 0) for w, t in enumerate(tabs)]
+    for beta in (0.0, -2.0):
+        dst = _table(dst0 if beta else np.full_like(dst0, np.nan), shift_dst)
+        cs.cs_sketch_merge(p, dst, src, alpha=0.25, beta=beta)
+        want = None
+        for w0 in range(0, W, 128):                     # tables of a launch
+            s = np.zeros((r, c))
+            for t in tabs[w0:w0 + 128]:
+                s = s + t.astype(np.float64)
+            kept = want.astype(np.float64) if w0 else (beta * dst0.astype(np.float64) if beta else 0.0)
+            want = (kept + 0.25 * s).astype(np.float32)
+        np.testing.assert_array_equal(dst.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("k", [1, 63, 65, 3001])
+@pytest.mark.parametrize("W", [1, 3, 4, 7, 15, 16, 17, 21, 256, 259])
+def test_gather_bit_for_bit(W, k):
+    d = 4099
+    rng = np.random.default_rng(W + k)
+    vecs = [rng.standard_normal(d).astype(np.float32) for _ in range(W)]
+    idx = np.sort(rng.choice(d, k, replace=False))
+    out = torch.full((k,), float("nan"), dtype=torch.float32, device=DEV)
+    cs.cs_gather_exact([torch.from_numpy(v).to(DEV) for v in vecs], torch.from_numpy(idx).to(DEV), out, alpha=0.5)
+    want = np.zeros(k, dtype=np.float32)
+    for v in vecs:
+        want = want + v[idx]
+    np.testing.assert_array_equal(out.cpu().numpy(), want * np.float32(0.5))
