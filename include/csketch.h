@@ -442,6 +442,12 @@ int cs_dequantize16(const uint16_t* q, int64_t n, float* out, int32_t fmt, void*
 int cs_bundle_merge16(const cs_params* p, float* dst, float beta, const uint16_t* T16, int32_t W,
                       float alpha, int32_t fmt, void* stream);
 
+/* cs_sketch_estimate of coordinates 0 .. d - 1 and cs_heavy_hitters_topk of them in one launch, for short vectors:
+ * 1 <= k <= d, r d <= CS_QUERY_CHOOSE_CELLS (CS_ELIMIT beyond).  No workspace.  val_out: device float[k] or NULL. */
+#define CS_QUERY_CHOOSE_CELLS 6144
+int cs_sketch_estimate_topk(const cs_params* p, const float* S, int64_t d, float* est, int64_t k, int64_t* idx_out,
+                            float* val_out, void* stream);
+
 /* HEAVYMIX (Sec. 4, Alg. 1), the recovery the convergence proof is stated for.
  *
  * cs_sketch_l2sq -- Alg. 1 step 1, the squared l2 norm read off the sketch: by the AMS argument of
@@ -493,6 +499,10 @@ int cs_sketch_feedback(const cs_params* p, float* S, const int64_t* idx, int64_t
  * momentum sketch), in half the launches */
 int cs_sketch_feedback_pair(const cs_params* p, float* S_v, float* S_u, const int64_t* idx, int64_t k,
                             float* val_v, float* val_u, void* stream);
+/* cs_gather_exact of W vectors and cs_sketch_feedback_pair, with the same coordinates, in one launch less.  out, val_v,
+ * val_u: three different arrays of device float[k]. */
+int cs_gather_feedback(const cs_params* p, const float* const* vec, int32_t W, const int64_t* idx, int64_t k, float alpha,
+                       float* out, float* S_v, float* S_u, float* val_v, float* val_u, void* stream);
 
 const char* cs_status_string(int status);
 

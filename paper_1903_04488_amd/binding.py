@@ -163,6 +163,10 @@ _SIGNATURES = {
     "cs_bundle_merge_momentum": [ctypes.POINTER(CsParams), ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
                                  ctypes.c_void_p, ctypes.c_int32, ctypes.c_float, ctypes.c_float,
                                  ctypes.c_void_p],
+    "cs_gather_feedback": [ctypes.POINTER(CsParams), ctypes.POINTER(ctypes.c_void_p), ctypes.c_int32, ctypes.c_void_p,
+                           ctypes.c_int64, ctypes.c_float, *[ctypes.c_void_p] * 6],
+    "cs_sketch_estimate_topk": [ctypes.POINTER(CsParams), ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int64,
+                                *[ctypes.c_void_p] * 3],
     "cs_sketch_feedback_pair": [ctypes.POINTER(CsParams), ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
                                 ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p],
     "cs_quantize16": [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p],
@@ -443,6 +447,7 @@ def cs_estimate_workspace_bytes(p, d: int) -> int:
 
 CS_TOPK_HIST_BINS = 2048
 CS_TOPK_SMALL_D = 32768
+CS_QUERY_CHOOSE_CELLS = 6144
 
 
 def _hist(hist):
@@ -581,6 +586,22 @@ def cs_sketch_feedback_pair(p, S_v, S_u, idx, val_v, val_u):
         ctypes.byref(p), _dev(S_v, torch.float32, "S_v", n), _dev(S_u, torch.float32, "S_u", n),
         _dev(idx, torch.int64, "idx"), k, _dev(val_v, torch.float32, "val_v", k),
         _dev(val_u, torch.float32, "val_u", k), _stream(S_v)), "cs_sketch_feedback_pair")
+
+
+def cs_gather_feedback(p, vec, idx, out, S_v, S_u, val_v, val_u, alpha: float = 1.0):
+    k, n = idx.numel(), _cells(p)
+    _check(load_library().cs_gather_feedback(
+        ctypes.byref(p), _ptr_array(vec, torch.float32, "vec", vec[0].numel()), len(vec), _dev(idx, torch.int64, "idx"), k,
+        alpha, _dev(out, torch.float32, "out", k), _dev(S_v, torch.float32, "S_v", n), _dev(S_u, torch.float32, "S_u", n),
+        _dev(val_v, torch.float32, "val_v", k), _dev(val_u, torch.float32, "val_u", k), _stream(S_v)), "cs_gather_feedback")
+
+
+def cs_sketch_estimate_topk(p, S, est, k: int, idx_out, val_out):
+    _check(load_library().cs_sketch_estimate_topk(
+        ctypes.byref(p), _dev(S, torch.float32, "S", _cells(p)), est.numel(), _dev(est, torch.float32, "est"), k,
+        _dev(idx_out, torch.int64, "idx_out", k),
+        _dev(val_out, torch.float32, "val_out", k) if val_out is not None else ctypes.c_void_p(0), _stream(S)),
+        "cs_sketch_estimate_topk")
 
 
 def cs_heavy_hitters_topk_static(est, k: int, idx_out, val_out):

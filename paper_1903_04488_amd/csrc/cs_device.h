@@ -256,4 +256,15 @@ __device__ __forceinline__ void medians_odd(const float (&a)[R], const float (&b
     }
 }
 
+// the median of coordinate i's r signed cells of table S (p: KParams)
+template <int R, bool POW2, typename P>
+__device__ __forceinline__ float estimate_at(const P& p, const Columns& col, const float* S, uint64_t i) {
+    float v[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+        v[j] = apply_sign(S[static_cast<size_t>(j) * p.c + bucket_of<POW2>(hash_state(p.a[j], p.b[j], i), col)],
+                          sign_flip_of(hash_state(p.as[j], p.bs[j], i)));
+    return median_odd<R>(v);
+}
+
 }  // namespace cs

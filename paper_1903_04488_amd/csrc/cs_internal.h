@@ -21,6 +21,24 @@ struct KParams {
 static_assert(offsetof(cs_params, visit) == sizeof(KParams), "KParams is the head of cs_params");
 inline const KParams& kparams(const cs_params* p) { return *reinterpret_cast<const KParams*>(p); }
 
+// Dispatch on the (odd) row count and on "c is a power of two" so that the hash state of all
+// rows lives in registers and loops over rows are unrolled.
+#define CS_DISPATCH_R(p, CALL)                                                     \
+    do {                                                                           \
+        const bool pow2__ = (p)->c_pow2 != 0;                                      \
+        switch ((p)->r) {                                                          \
+            case 1: if (pow2__) { CALL(1, true); } else { CALL(1, false); } break;   \
+            case 3: if (pow2__) { CALL(3, true); } else { CALL(3, false); } break;   \
+            case 5: if (pow2__) { CALL(5, true); } else { CALL(5, false); } break;   \
+            case 7: if (pow2__) { CALL(7, true); } else { CALL(7, false); } break;   \
+            case 9: if (pow2__) { CALL(9, true); } else { CALL(9, false); } break;   \
+            case 11: if (pow2__) { CALL(11, true); } else { CALL(11, false); } break; \
+            case 13: if (pow2__) { CALL(13, true); } else { CALL(13, false); } break; \
+            case 15: if (pow2__) { CALL(15, true); } else { CALL(15, false); } break; \
+            default: return CS_EINVAL;                                             \
+        }                                                                          \
+    } while (0)
+
 constexpr int kMaxBatch = 32;   // workers per launch of the batched update kernels
 
 // kernel argument block: worker w's table and vector

@@ -53,24 +53,6 @@ inline bool crowded_cells(const cs_params* p, int64_t d, int64_t groups) {
     return groups > 1 && p->c < 128 && d >= static_cast<int64_t>(p->r > 8 ? 50 : p->c < 80 ? 75 : 100) * p->c;
 }
 
-// Dispatch on the (odd) row count and on "c is a power of two" so that the hash state of all
-// rows lives in registers and loops over rows are unrolled.
-#define CS_DISPATCH_R(p, CALL)                                                     \
-    do {                                                                           \
-        const bool pow2__ = (p)->c_pow2 != 0;                                      \
-        switch ((p)->r) {                                                          \
-            case 1: if (pow2__) { CALL(1, true); } else { CALL(1, false); } break;   \
-            case 3: if (pow2__) { CALL(3, true); } else { CALL(3, false); } break;   \
-            case 5: if (pow2__) { CALL(5, true); } else { CALL(5, false); } break;   \
-            case 7: if (pow2__) { CALL(7, true); } else { CALL(7, false); } break;   \
-            case 9: if (pow2__) { CALL(9, true); } else { CALL(9, false); } break;   \
-            case 11: if (pow2__) { CALL(11, true); } else { CALL(11, false); } break; \
-            case 13: if (pow2__) { CALL(13, true); } else { CALL(13, false); } break; \
-            case 15: if (pow2__) { CALL(15, true); } else { CALL(15, false); } break; \
-            default: return CS_EINVAL;                                             \
-        }                                                                          \
-    } while (0)
-
 // ---------------------------------------------------------------------------------------
 // hash parity hooks
 // ---------------------------------------------------------------------------------------
@@ -533,14 +515,26 @@ struct FeedbackTables {
 constexpr int kFeedbackBlock = 512;
 constexpr int64_t kFeedbackSmall = 4 * kFeedbackBlock;
 
+// threads t0, t0 + stride, ... of a table
 template <int R, bool POW2>
-__device__ __forceinline__ float estimate_at(const KParams& p, const Columns& col, const float* S, uint64_t i) {
-    float v[R];
+__device__ __forceinline__ void feedback_estimates(const KParams& p, const float* S, float* val, const int64_t* __restrict__ idx,
+                                                   int64_t n, int64_t t0, int64_t stride) {
+    const Columns col = columns_of<POW2>(p.c);
+    for (int64_t t = t0; t < n; t += stride) val[t] = estimate_at<R, POW2>(p, col, S, static_cast<uint64_t>(idx[t]));
+}
+
+template <int R, bool POW2>
+__device__ __forceinline__ void feedback_subtract(const KParams& p, float* S, const float* val, const int64_t* __restrict__ idx,
+                                                  int64_t n, int64_t t0, int64_t stride) {
+    const Columns col = columns_of<POW2>(p.c);
+    for (int64_t t = t0; t < n; t += stride) {
+        const uint64_t i = static_cast<uint64_t>(idx[t]);
+        const float v = -val[t];
 #pragma unroll
-    for (int j = 0; j < R; ++j)
-        v[j] = apply_sign(S[static_cast<size_t>(j) * p.c + bucket_of<POW2>(hash_state(p.a[j], p.b[j], i), col)],
-                          sign_flip_of(hash_state(p.as[j], p.bs[j], i)));
-    return median_odd<R>(v);
+        for (int j = 0; j < R; ++j)
+            atomic_add_noret(S + static_cast<size_t>(j) * p.c + bucket_of<POW2>(hash_state(p.a[j], p.b[j], i), col),
+                             apply_sign(v, sign_flip_of(hash_state(p.as[j], p.bs[j], i))));
+    }
 }
 
 // PHASES: 1 the estimates, 2 the subtraction, 3 both (one workgroup per table)
@@ -551,19 +545,9 @@ k_feedback(KParams p, FeedbackTables tab, const int64_t* __restrict__ idx, int64
     float* val = tab.val[blockIdx.y];
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kFeedbackBlock;
     const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kFeedbackBlock + threadIdx.x;
-    const Columns col = columns_of<POW2>(p.c);
-    if (PHASES & 1)
-        for (int64_t t = t0; t < n; t += stride) val[t] = estimate_at<R, POW2>(p, col, S, static_cast<uint64_t>(idx[t]));
+    if (PHASES & 1) feedback_estimates<R, POW2>(p, S, val, idx, n, t0, stride);
     if (PHASES == 3) __syncthreads();
-    if (PHASES & 2)
-        for (int64_t t = t0; t < n; t += stride) {
-            const uint64_t i = static_cast<uint64_t>(idx[t]);
-            const float v = -val[t];
-#pragma unroll
-            for (int j = 0; j < R; ++j)
-                atomic_add_noret(S + static_cast<size_t>(j) * p.c + bucket_of<POW2>(hash_state(p.a[j], p.b[j], i), col),
-                                 apply_sign(v, sign_flip_of(hash_state(p.as[j], p.bs[j], i))));
-        }
+    if (PHASES & 2) feedback_subtract<R, POW2>(p, S, val, idx, n, t0, stride);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -579,33 +563,68 @@ struct GatherPtrs {
     const float* vec[kMaxGather];
 };
 
+// s plus the values at i, in ascending order of the vectors
+__device__ __forceinline__ float gather_add(float s, const GatherPtrs& ptrs, int nw, int64_t i) {
+    int w = 0;
+    for (; w + kGatherAhead <= nw; w += kGatherAhead) {
+        float u[kGatherAhead];
+#pragma unroll
+        for (int q = 0; q < kGatherAhead; ++q) u[q] = __builtin_nontemporal_load(ptrs.vec[w + q] + i);
+#pragma unroll
+        for (int q = 0; q < kGatherAhead; ++q) s += u[q];
+    }
+    // (what is left, four at a time: the common numbers of workers are multiples of four)
+    for (; w + 4 <= nw; w += 4) {
+        float u[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) u[q] = __builtin_nontemporal_load(ptrs.vec[w + q] + i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s += u[q];
+    }
+    for (; w < nw; ++w) s += __builtin_nontemporal_load(ptrs.vec[w] + i);
+    return s;
+}
+
 __global__ void __launch_bounds__(kGatherBlock)
 k_gather(GatherPtrs ptrs, int nw, const int64_t* __restrict__ idx, int64_t k, float alpha,
          float* __restrict__ out, int first_chunk, int last_chunk) {
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kGatherBlock;
     for (int64_t n = static_cast<int64_t>(blockIdx.x) * kGatherBlock + threadIdx.x; n < k; n += stride) {
-        const int64_t i = idx[n];
-        float s = first_chunk ? 0.0f : out[n];
-        int w = 0;
-        for (; w + kGatherAhead <= nw; w += kGatherAhead) {
-            float u[kGatherAhead];
-#pragma unroll
-            for (int q = 0; q < kGatherAhead; ++q) u[q] = __builtin_nontemporal_load(ptrs.vec[w + q] + i);
-#pragma unroll
-            for (int q = 0; q < kGatherAhead; ++q) s += u[q];
-        }
-        // (what is left, four at a time: the common numbers of workers are multiples of four)
-        for (; w + 4 <= nw; w += 4) {
-            float u[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) u[q] = __builtin_nontemporal_load(ptrs.vec[w + q] + i);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) s += u[q];
-        }
-        for (; w < nw; ++w) s += __builtin_nontemporal_load(ptrs.vec[w] + i);
+        const float s = gather_add(first_chunk ? 0.0f : out[n], ptrs, nw, idx[n]);
         out[n] = last_chunk ? alpha * s : s;
     }
 }
+
+// The second round beside the feedback of a pair of tables: both start from idx and neither reads what the other writes,
+// and a launch of either is one chain of dependent loads.  SMALL (up to kFeedbackSmall coordinates): workgroups 0 and 1 are
+// the whole feedback of a table each, the others gather, 64 coordinates by their first wavefront.  Otherwise workgroups of
+// one wavefront in three equal parts, the gather and the tables' estimates; the subtraction is k_feedback's.
+// us, one launch more / this: 7 x 40, k = 2, 4 vectors 8.1 / 6.3; 5 x 2^15, k = 1000, 4 20.9 / 18.7; 5 x 2^17, k = 5000, 8 15.9 /
+// 11.4; 5 x 2^18, k = 10 000, 32 23.7 / 18.7.
+template <int R, bool POW2, bool SMALL>
+__global__ void __launch_bounds__(SMALL ? kFeedbackBlock : kGatherBlock)
+k_gather_feedback(KParams p, FeedbackTables tab, GatherPtrs ptrs, int nw, const int64_t* __restrict__ idx, int64_t k,
+                  float alpha, float* __restrict__ out) {
+    const unsigned part = SMALL ? 1 : gridDim.x / 3;                     // workgroups of a table
+    const unsigned first = 2 * part;                                     // that gathers
+    if (blockIdx.x >= first) {
+        if (SMALL && threadIdx.x >= kGatherBlock) return;
+        const int64_t stride = static_cast<int64_t>(gridDim.x - first) * kGatherBlock;
+        for (int64_t n = static_cast<int64_t>(blockIdx.x - first) * kGatherBlock + threadIdx.x; n < k; n += stride)
+            out[n] = alpha * gather_add(0.0f, ptrs, nw, idx[n]);
+        return;
+    }
+    const unsigned which = blockIdx.x / part;
+    constexpr int block = SMALL ? kFeedbackBlock : kGatherBlock;
+    const int64_t t0 = static_cast<int64_t>(blockIdx.x - which * part) * block + threadIdx.x;
+    const int64_t stride = static_cast<int64_t>(part) * block;
+    feedback_estimates<R, POW2>(p, tab.S[which], tab.val[which], idx, k, t0, stride);
+    if constexpr (SMALL) {
+        __syncthreads();
+        feedback_subtract<R, POW2>(p, tab.S[which], tab.val[which], idx, k, t0, stride);
+    }
+}
+static_assert(sizeof(KParams) + sizeof(FeedbackTables) + sizeof(GatherPtrs) + 128 <= 4096, "kernel arguments");
 
 // out = alpha * (sum of W vectors), added up in binary64 and rounded once.  Folded workers are
 // summed before they are sketched: the sketch is linear, W d floats are then read once
@@ -1330,4 +1349,40 @@ extern "C" int cs_sketch_feedback_pair(const cs_params* p, float* S_v, float* S_
     if (k == 0) return CS_OK;
     if (!S_v || !S_u || !idx || !val_v || !val_u || S_v == S_u || val_v == val_u) return CS_EINVAL;
     return feedback_tables(p, FeedbackTables{{S_v, S_u}, {val_v, val_u}}, 2, idx, k, stream);
+}
+
+extern "C" int cs_gather_feedback(const cs_params* p, const float* const* vec, int32_t W, const int64_t* idx, int64_t k,
+                                  float alpha, float* out, float* S_v, float* S_u, float* val_v, float* val_u, void* stream) {
+    if (!params_ok(p) || !vec || W < 1 || k < 0) return CS_EINVAL;
+    for (int w = 0; w < W; ++w)
+        if (!vec[w]) return CS_EINVAL;
+    if (k == 0) return CS_OK;
+    if (!idx || !out || !S_v || !S_u || !val_v || !val_u || S_v == S_u) return CS_EINVAL;
+    if (val_v == val_u || out == val_v || out == val_u) return CS_EINVAL;
+    if (W > kMaxGather) {
+        const int rc = cs_gather_exact(vec, W, idx, k, alpha, out, stream);
+        return rc != CS_OK ? rc : cs_sketch_feedback_pair(p, S_v, S_u, idx, k, val_v, val_u, stream);
+    }
+    const FeedbackTables tab{{S_v, S_u}, {val_v, val_u}};
+    GatherPtrs ptrs{};
+    for (int w = 0; w < W; ++w) ptrs.vec[w] = vec[w];
+    const unsigned part = grid_for(k, kGatherBlock, 256 * 8);
+    if (k <= kFeedbackSmall) {
+#define CALL(R_, P2_)                                                                                               \
+    k_gather_feedback<R_, P2_, true><<<2 + part, kFeedbackBlock, 0, as_stream(stream)>>>(kparams(p), tab, ptrs, W, idx, k, \
+                                                                                        alpha, out)
+        CS_DISPATCH_R(p, CALL);
+#undef CALL
+        return launch_status();
+    }
+    const dim3 grid(grid_for(k, kFeedbackBlock), 2);
+#define CALL(R_, P2_)                                                                                                   \
+    do {                                                                                                                \
+        k_gather_feedback<R_, P2_, false><<<3 * part, kGatherBlock, 0, as_stream(stream)>>>(kparams(p), tab, ptrs, W, idx, k, \
+                                                                                           alpha, out);                \
+        k_feedback<R_, P2_, 2><<<grid, kFeedbackBlock, 0, as_stream(stream)>>>(kparams(p), tab, idx, k);                 \
+    } while (0)
+    CS_DISPATCH_R(p, CALL);
+#undef CALL
+    return launch_status();
 }

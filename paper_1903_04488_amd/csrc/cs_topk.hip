@@ -48,6 +48,7 @@ constexpr int kSelBlock = 1024;       // threads of the workgroups that select
 constexpr int kSelWaves = kSelBlock / 64;
 constexpr int kKeep = 32;             // keys per thread that a single-workgroup selection keeps in LDS (128 KB)
 constexpr int64_t kSmall = static_cast<int64_t>(kSelBlock) * kKeep;
+constexpr int64_t kQueryChooseHashes = CS_QUERY_CHOOSE_CELLS;
 // Workgroups that read est in one pass.  512 of 512 threads keep 32 KB of reads in flight on every
 // CU; more of them only add to the atomic adds on one address at their end (12 ns each, one
 // after the other: with 3200 workgroups those were 38 of the compaction's 39 us at d = 6.5 M).
@@ -399,7 +400,8 @@ struct SmallLds {
 // order; segment b precedes segment b + 1 in index order and holds the indices of
 // [b seg_len, (b + 1) seg_len).  DIRECT: the items are est itself (index = position, one segment)
 // and the first histogram is taken here as well.
-template <bool DIRECT, typename KEY>
+// KEYED: their keys are in LDS already, each written by the thread that reads it here
+template <bool DIRECT, bool KEYED, typename KEY>
 __device__ __forceinline__ void select_in_workgroup(SmallLds& s, const float* __restrict__ val,
                                                     const int64_t* __restrict__ idx, uint32_t n,
                                                     uint32_t bin0, uint64_t k_rem,
@@ -407,8 +409,9 @@ __device__ __forceinline__ void select_in_workgroup(SmallLds& s, const float* __
                                                     const uint32_t* __restrict__ seg_count, int nseg,
                                                     uint32_t seg_tiles, const SelOut& out, const KEY& kf) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if constexpr (!KEYED)
 #pragma unroll 8
-    for (uint32_t p = tid; p < n; p += kSelBlock) s.key[p] = kf(val[p], DIRECT ? static_cast<int64_t>(p) : idx[p]);
+        for (uint32_t p = tid; p < n; p += kSelBlock) s.key[p] = kf(val[p], DIRECT ? static_cast<int64_t>(p) : idx[p]);
     // (a thread reads back only keys that it wrote itself)
     if constexpr (DIRECT) {
         for (int t = tid; t < kBins; t += kSelBlock) s.hist[t] = 0;
@@ -523,7 +526,26 @@ __global__ void __launch_bounds__(kSelBlock)
 k_topk_small(const float* __restrict__ est, uint32_t d, SelOut out, KEY kf) {
     kf.init();
     __shared__ SmallLds s;
-    select_in_workgroup<true>(s, est, nullptr, d, 0u, static_cast<uint64_t>(out.k), nullptr, nullptr, 1, 1u, out, kf);
+    select_in_workgroup<true, false>(s, est, nullptr, d, 0u, static_cast<uint64_t>(out.k), nullptr, nullptr, 1, 1u, out, kf);
+}
+
+// Query and selection of a short vector by the workgroup that selects: estimates go to est and their keys straight into LDS.
+// A step that short waits for the host, 6 us a call.  The hashes, 2 r per coordinate, are then one CU's work, so that r d is
+// bounded by kQueryChooseHashes where the kernels alone take as long either way: us, two launches / one, from a graph: 3 rows,
+// d = 900 11.5 / 10.6; 7, 784 13.0 / 13.0; 5, 2000 13.0 / 13.4; 5, 3276 14.1 / 16.7; 15, 800 18.4 / 22.4.
+template <int R, bool POW2>
+__global__ void __launch_bounds__(kSelBlock)
+k_estimate_choose(KParams p, const float* __restrict__ S, uint32_t d, float* est, SelOut out) {
+    __shared__ SmallLds s;
+    const KeyMagnitude kf{};
+    const Columns col = columns_of<POW2>(p.c);
+    for (uint32_t t = threadIdx.x; t < d; t += kSelBlock) {
+        const float v = estimate_at<R, POW2>(p, col, S, t);
+        est[t] = v;
+        s.key[t] = kf(v, static_cast<int64_t>(t));
+    }
+    // (est is read back by the threads that wrote it)
+    select_in_workgroup<true, true>(s, est, nullptr, d, 0u, static_cast<uint64_t>(out.k), nullptr, nullptr, 1, 1u, out, kf);
 }
 
 // values that other workgroups of the launch wrote or added to: read past this XCD's caches
@@ -552,7 +574,7 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
     const uint32_t n = from_list ? ws->ncand : 0u;
     if (from_list && n <= kSmall) {
         if (blockIdx.x != 0) return;
-        select_in_workgroup<false>(s, cand_val, cand_idx, n, ws->prefix, ws->k_rem, ws->seg_base, ws->seg_count,
+        select_in_workgroup<false, false>(s, cand_val, cand_idx, n, ws->prefix, ws->k_rem, ws->seg_base, ws->seg_count,
                                    nseg, seg_tiles, out, kf);
         if (tid == 0) ws->ncand = 0;
         return;
@@ -1065,6 +1087,20 @@ extern "C" int cs_heavy_hitters_topk_static(const float* est, int64_t d, int64_t
     if (rc != CS_OK) return rc;
     return select_largest(est, d, nullptr, SelOut{idx_out, val_out, nullptr, nullptr, k}, ws, sizeof(scratch),
                           reinterpret_cast<hipStream_t>(stream), KeyMagnitude{});
+}
+
+extern "C" int cs_sketch_estimate_topk(const cs_params* p, const float* S, int64_t d, float* est, int64_t k, int64_t* idx_out,
+                                       float* val_out, void* stream) {
+    if (!p || !S || !est || !idx_out || k < 1 || d < 1 || k > d) return CS_EINVAL;
+    if (p->r == 0 || p->r > CS_MAX_R || (p->r & 1u) == 0 || p->c == 0 || p->c > (1u << 31)) return CS_EINVAL;
+    if (d > kSmall || d * p->r > kQueryChooseHashes) return CS_ELIMIT;
+    const SelOut out{idx_out, val_out, nullptr, nullptr, k};
+#define CALL(R_, P2_)                                                                                       \
+    k_estimate_choose<R_, P2_><<<1, kSelBlock, 0, reinterpret_cast<hipStream_t>(stream)>>>(                  \
+        kparams(p), S, static_cast<uint32_t>(d), est, out)
+    CS_DISPATCH_R(p, CALL);
+#undef CALL
+    return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
 extern "C" int cs_sketch_l2sq(const cs_params* p, const float* S, double* out, void* stream) {

@@ -255,15 +255,30 @@ class HotPath:
         self.accumulate(g_w)
         self.aggregate()
 
+    def query_and_choose(self):
+        """estimate and topk, in one launch for short vectors"""
+        if self.params.r * self.est.numel() <= B.CS_QUERY_CHOOSE_CELLS and self._not_overridden("estimate", "topk"):
+            B.cs_sketch_estimate_topk(self.params, self.query_table(), self.est, self.kq, self.cand, self.est_at_cand)
+            return
+        self.estimate()
+        self.topk()
+
+    def second_round(self, g_w):
+        """gather and feedback, which share a launch where both begin with the candidates"""
+        if self.rho is not None and self.P == 1 and self.idx is self.cand and self._not_overridden("gather", "feedback"):
+            B.cs_gather_feedback(self.params, g_w, self.cand, self.x_cand, self.S_v, self.S_u, self.delta, self.uhat,
+                                 alpha=1.0 / self.W)
+            return
+        self.gather(g_w)
+        self.feedback()
+
     def step(self, g_w):
         """g_w: list of W fp32[d] device tensors.  Returns (idx, x): chosen coordinates
         (ascending) and their exact mean over workers."""
         g_w = B.DeviceVectors(g_w, name="g_w")
         self.sketch_and_aggregate(g_w)
-        self.estimate()
-        self.topk()
-        self.gather(g_w)
-        self.feedback()
+        self.query_and_choose()
+        self.second_round(g_w)
         return self.idx, self.x
 
 
@@ -351,8 +366,7 @@ class DenseStatePath(HotPath):
         else:
             self.accumulate(self.v_w)
             self.merge()
-        self.estimate()
-        self.topk()
+        self.query_and_choose()
         self.gather(self.v_w)
         self.mask()
         return self.idx, self.x

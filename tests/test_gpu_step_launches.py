@@ -1,0 +1,94 @@
+"""Stages that share a launch give what the stages give one by one, bit for bit (the queried and chosen coordinates, the
+gathered sums, the estimates taken out) or to the order of the atomic additions (the tables after the feedback)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import paper_1903_04488_amd as cs
+from paper_1903_04488_amd import binding as B
+from paper_1903_04488_amd.pipeline import HotPath
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+F32 = dict(dtype=torch.float32, device=DEV)
+
+
+def _bits(t):
+    return t.cpu().numpy().view(np.uint32)
+
+
+@pytest.mark.parametrize("special", [False, True])
+@pytest.mark.parametrize("r, c, d, k", [
+    (1, 1, 1, 1), (3, 5, 2, 2), (5, 33, 1023, 40), (5, 40, 1024, 1), (5, 64, 1025, 1025), (13, 63, 472, 7),
+    (15, 40, 409, 300), (1, 64, 6144, 5), (3, 8192, 2048, 100), (7, 40, 784, 2), (9, 33, 65, 64), (11, 32, 63, 2)])
+def test_query_and_choice_in_one_launch(r, c, d, k, special):
+    p = cs.cs_params_init(r, c, 17, d)
+    S = torch.randn(r, c, generator=torch.Generator().manual_seed(d)).to(DEV)
+    if special:                                       # equal magnitudes, zeros of both signs, NaN, infinities
+        S = torch.round(S * 2) / 2
+        flat = S.view(-1)
+        flat[::7], flat[1::11], flat[2::13] = float("nan"), float("inf"), -0.0
+    est, idx, val = torch.empty(d, **F32), torch.empty(k, dtype=torch.int64, device=DEV), torch.empty(k, **F32)
+    cs.cs_sketch_estimate_topk(p, S, est, k, idx, val)
+    est2, idx2, val2 = torch.empty_like(est), torch.empty_like(idx), torch.empty_like(val)
+    n = B.cs_estimate_scratch_bytes(p, d)
+    B.cs_sketch_estimate(p, S, est2, 0, torch.empty(n, dtype=torch.uint8, device=DEV) if n else None)
+    ws = torch.empty(B.cs_topk_workspace_bytes(d, k), dtype=torch.uint8, device=DEV)
+    B.cs_heavy_hitters_topk(est2, k, idx2, val2, ws)
+    np.testing.assert_array_equal(_bits(est), _bits(est2))
+    np.testing.assert_array_equal(idx.cpu().numpy(), idx2.cpu().numpy())
+    np.testing.assert_array_equal(_bits(val), _bits(val2))
+
+
+def test_query_and_choice_refuse_longer_vectors():
+    p = cs.cs_params_init(5, 64, 1, 4000)
+    est, idx = torch.empty(1229, **F32), torch.empty(3, dtype=torch.int64, device=DEV)
+    with pytest.raises(cs.CsError):
+        cs.cs_sketch_estimate_topk(p, torch.zeros(5, 64, **F32), est, 3, idx, None)
+
+
+# k: one and both sides of a wavefront, of what one workgroup takes back (2048); W: remainders of the loads in flight and
+# both sides of a launch's vectors (256)
+@pytest.mark.parametrize("r, c", [(1, 7), (5, 1 << 12), (7, 1001), (15, 1 << 10)])
+@pytest.mark.parametrize("k, W", [(1, 1), (65, 5), (2047, 21), (2048, 4), (2049, 16), (5000, 256), (70, 257)])
+def test_second_round_in_one_launch(r, c, k, W):
+    d = 9001
+    gen = torch.Generator().manual_seed(k + W)
+    p = cs.cs_params_init(r, c, 5, d)
+    vec = [torch.randn(d, generator=gen).to(DEV) for _ in range(W)]
+    idx = torch.sort(torch.randperm(d, generator=gen)[:k])[0].to(DEV)
+    tables = [torch.randn(r, c, generator=gen).to(DEV) for _ in range(2)]
+    one, two = ([t.clone() for t in tables] for _ in range(2))
+    x, a, b = (torch.full((k,), float("nan"), **F32) for _ in range(3))
+    cs.cs_gather_feedback(p, vec, idx, x, *one, a, b, alpha=1.0 / W)
+    x2, a2, b2 = (torch.full((k,), float("nan"), **F32) for _ in range(3))
+    cs.cs_gather_exact(vec, idx, x2, alpha=1.0 / W)
+    cs.cs_sketch_feedback_pair(p, *two, idx, a2, b2)
+    for got, want in ((x, x2), (a, a2), (b, b2)):
+        np.testing.assert_array_equal(_bits(got), _bits(want))
+    for got, want, before, v in zip(one, two, tables, (a, b)):
+        # a cell takes its share of |v| in some order: n additions are off by n half ulps of the sum of magnitudes, n <= k
+        bound = 2.0 ** -23 * k * (before.abs().max() + v.abs().sum()).item()
+        assert (got - want).abs().max().item() <= bound
+
+
+@pytest.mark.parametrize("d, W, r, c, k, rho", [(784, 4, 7, 40, 2, 0.9), (1100, 3, 5, 64, 5, None), (1300, 2, 5, 512, 9, 0.9)])
+def test_step_gives_what_its_stages_give(d, W, r, c, k, rho):
+    g_w = [torch.randint(-8, 9, (d,), generator=torch.Generator().manual_seed(w)).float().to(DEV) for w in range(W)]
+    whole, staged = (HotPath(d, W, r, c, k, 3, rho=rho) for _ in range(2))
+    for _ in range(2):
+        idx, x = whole.step(g_w)
+        staged.sketch_and_aggregate(g_w)
+        staged.estimate()
+        staged.topk()
+        staged.gather(g_w)
+        staged.feedback()
+        np.testing.assert_array_equal(idx.cpu().numpy(), staged.idx.cpu().numpy())
+        np.testing.assert_array_equal(_bits(x), _bits(staged.x))
+        if rho is not None:                            # (equal states for the next step)
+            torch.testing.assert_close(whole.S_u, staged.S_u)
+            torch.testing.assert_close(whole.S_v, staged.S_v)
+            staged.S_u.copy_(whole.S_u)
+            staged.S_v.copy_(whole.S_v)
