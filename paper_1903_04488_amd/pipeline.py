@@ -257,7 +257,9 @@ class HotPath:
 
     def query_and_choose(self):
         """estimate and topk, in one launch for short vectors"""
-        if self.params.r * self.est.numel() <= B.CS_QUERY_CHOOSE_CELLS and self._not_overridden("estimate", "topk"):
+        short = B.CS_QUERY_CHOOSE_CELLS
+        if (self.r * self.d <= short and self.params.r * self.est.numel() <= short    # (the sketch may have been replaced)
+                and self._not_overridden("estimate", "topk")):
             B.cs_sketch_estimate_topk(self.params, self.query_table(), self.est, self.kq, self.cand, self.est_at_cand)
             return
         self.estimate()

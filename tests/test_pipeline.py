@@ -241,3 +241,27 @@ def test_counts_by_magnitude_are_there_for_vectors_of_any_length(calls, d):
     bins = (est.numpy().view("uint32") & 0x7FFFFFFF) >> 20
     assert path.hist is counts
     assert counts.tolist() == torch.bincount(torch.from_numpy(bins.astype("int64")), minlength=2048).tolist()
+
+
+def test_a_step_shares_launches_only_between_stages_that_are_its_own(calls):
+    shared = {"cs_sketch_estimate_topk", "cs_gather_feedback"}
+    short = dict(d=100, est=torch.empty(100), params=types.SimpleNamespace(r=5))
+    bare(**short).step([None])
+    assert shared <= set(names(calls)) and "cs_gather_exact" not in names(calls)
+    for stage, call in (("estimate", "cs_sketch_estimate_topk"), ("topk", "cs_sketch_estimate_topk"),
+                        ("gather", "cs_gather_feedback"), ("feedback", "cs_gather_feedback")):
+        calls.clear()
+        path = bare(**short)
+        setattr(path, stage, lambda *a: calls.append(("own", (), {})))
+        path.step([None])
+        assert "own" in names(calls) and call not in names(calls) and shared - {call} <= set(names(calls))
+    for other in (dict(d=2000, est=torch.empty(2000)), dict(est=torch.empty(2000)), dict(params=types.SimpleNamespace(r=99))):
+        calls.clear()
+        bare(**{**short, **other}).step([None])
+        assert "cs_sketch_estimate_topk" not in names(calls) and "cs_heavy_hitters_topk_kept" in names(calls)
+    calls.clear()
+    bare(**short, idx=torch.empty(1)).step([None])             # (candidates and selection apart)
+    assert "cs_gather_feedback" not in names(calls) and "cs_sketch_feedback_pair" in names(calls)
+    calls.clear()
+    bare(**{**short, "rho": None}).step([None])
+    assert "cs_gather_feedback" not in names(calls) and "cs_gather_exact" in names(calls)
