@@ -139,29 +139,48 @@ __global__ void __launch_bounds__(kBlock) k_topk_clear(TopkWs* ws) {
     }
 }
 
+// v plus the value that the DPP control hands this lane (0 where it hands none, or in rows outside the mask)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t add_from_lane(uint64_t v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(v)), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(v >> 32)), CTRL, ROWS, 0xf, false);
+    return v + (static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32 | static_cast<uint32_t>(lo));
+}
+// inclusive sums over each row of 16 lanes: row_shr:1, 2, 4, 8
+__device__ __forceinline__ uint64_t row_inclusive_sum(uint64_t v) {
+    v = add_from_lane<0x111, 0xf>(v);
+    v = add_from_lane<0x112, 0xf>(v);
+    v = add_from_lane<0x114, 0xf>(v);
+    return add_from_lane<0x118, 0xf>(v);
+}
+__device__ __forceinline__ uint64_t read_lane(uint64_t v, int lane) {
+    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v)), lane));
+    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v >> 32)), lane));
+    return static_cast<uint64_t>(hi) << 32 | lo;
+}
+
 // Sum of v over the threads before this one in a workgroup of WAVES wavefronts; *total receives
-// the sum over all threads.  `lds` holds one word per wavefront; the workgroup is in step on return.
-template <int WAVES, typename T>
-__device__ __forceinline__ T block_exclusive_sum(T v, T* lds, T* total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    T inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const T up = __shfl_up(inc, off, 64);
-        if (lane >= off) inc += up;
-    }
+// the sum over all threads.  `lds` holds one word per wavefront; the workgroup is in step on return, and all of it calls.
+// A selection is a chain of four to six of these by one workgroup, whose 16 wavefronts share four SIMDs: what bounds it is
+// their instructions.  Shifts within the register file (row_shr, then row_bcast:15 into rows 1 and 3, row_bcast:31 into
+// rows 2 and 3) and one scan of the wavefronts' sums by lanes, instead of shuffles through LDS and a loop over the sums in
+// every thread, us of a selection: d = 784 8.6 / 6.5, d = 5000 11.9 / 10.0, d = 60 789 (shared out) 25.5 / 19.8, d = 6.5 M, k =
+// 5000 32.5 / 30.6, d = 90 M, k = 320 000 136 / 128.
+template <int WAVES>
+__device__ __forceinline__ uint64_t block_exclusive_sum(uint64_t v, uint64_t* lds, uint64_t* total) {
+    static_assert(WAVES <= 16, "the wavefronts' sums are one row of lanes");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    uint64_t inc = row_inclusive_sum(v);
+    inc = add_from_lane<0x142, 0xa>(inc);
+    inc = add_from_lane<0x143, 0xc>(inc);
     if (lane == 63) lds[wave] = inc;
     __syncthreads();
-    T before = 0, all = 0;
-#pragma unroll
-    for (int wv = 0; wv < WAVES; ++wv) {
-        const T s = lds[wv];
-        if (wv < wave) before += s;
-        all += s;
-    }
+    const uint64_t mine = lane < WAVES ? lds[lane] : 0;
     __syncthreads();
-    *total = all;
-    return before + inc - v;
+    const uint64_t sums = row_inclusive_sum(mine);
+    *total = read_lane(sums, WAVES - 1);
+    return read_lane(sums - mine, wave) + inc - v;
 }
 
 // The bin of a histogram (PER consecutive bins per thread, cnt[] of mine) that holds the k_rem-th
