@@ -616,7 +616,8 @@ k_accumulate_visits(LIST rows, WorkersBeside<LIST> a) {
             return (first + q) & mask;
         } else {
             const uint32_t c = a.c;
-            const uint32_t x = q < omega ? first + q : first + (q - omega) + (c - v.pc);
+            // (the half of the sums that wrapped past p begins at NC / 2, also in rows that use fewer)
+            const uint32_t x = q < NC / 2 ? first + q : first + (q - NC / 2) + (c - v.pc);
             return x >= c ? x - c : x;
         }
     };
@@ -1098,28 +1099,37 @@ void fill_visit_gaps(const cs_params* p, uint32_t j, VisitGaps& v) {
 
 // The rows of an any-c sketch in the launches that take them: rows with the same number of
 // running sums (omega = 1 or 2) together, up to `at_once` per launch, the longest lists
-// first.  fn(rows, n, omega) is called per launch.
+// first; where `mixed` (all but the update of one vector) and one launch takes all rows, all of them together,
+// with the sums of omega = 2: one tail instead of two, and the row or two of the other kind do not fill the chip by
+// themselves (us, two launches / one: 5 x 180 000, 6.5 M, 2 workers 198 / 177, 8 workers 249 / 227; 5 x 333 333, 30 M, 8
+// workers 1030 / 993; 3 x 180 001, 17 M, 2 workers 392 / 328, 8 workers 444 / 443; 3 x 200 001, 9 M, 8 workers 197 / 166; query with counts 5 x
+// 180 000, 6.5 M 84 / 75, 5 x 250 001, 12 M 143 / 139, 5 x 400 003, 9 M 145 / 134, 5 x 70 001, 2.3 M 67 / 68).
+// fn(rows, n, omega) is called per launch.
 template <typename FN>
-int for_each_anyc_launch(const cs_params* p, uint32_t nrows_of_sketch, FN fn, int at_once = kAnycRowsPerLaunch) {
+int for_each_anyc_launch(const cs_params* p, uint32_t nrows_of_sketch, FN fn, int at_once = kAnycRowsPerLaunch,
+                         bool mixed = false) {
+    mixed = mixed && nrows_of_sketch <= static_cast<uint32_t>(at_once);
     for (uint32_t omega = 1; omega <= 2; ++omega) {
-        uint32_t order[CS_MAX_R];
+        uint32_t order[CS_MAX_R], most = 0;
         int n = 0;
         for (uint32_t j = 0; j < nrows_of_sketch; ++j) {
-            if (p->anyc[j].omega != omega) continue;
+            if (!mixed && p->anyc[j].omega != omega) continue;
+            most = p->anyc[j].omega > most ? p->anyc[j].omega : most;
             int at = n++;
             for (; at > 0 && p->anyc[order[at - 1]].K < p->anyc[j].K; --at) order[at] = order[at - 1];
             order[at] = j;
         }
         for (int q0 = 0; q0 < n; q0 += at_once) {
             const int m = n - q0 < at_once ? n - q0 : at_once;
-            const int rc = fn(order + q0, m, omega);
+            const int rc = fn(order + q0, m, most);
             if (rc != CS_OK) return rc;
         }
+        if (mixed) break;
     }
     return CS_OK;
 }
 
-// one launch: rows js[0 .. n) (all with the same omega) of one group of workers, each along
+// one launch: rows js[0 .. n) (of at most that omega) of one group of workers, each along
 // its list for any column count
 template <int WL, int NWAVE>
 int launch_visits_anyc(const cs_params* p, const VisitWorkersOf<1>& a, const uint32_t* js, int n,
@@ -1453,6 +1463,7 @@ bool anyc_query_needs_scratch(const cs_params* p, int64_t d) {
     return anyc_visits_serve_query(p, d) && d * static_cast<int64_t>(p->r - 1) >= (static_cast<int64_t>(1) << 26);
 }
 
+// (rows of both kinds that share a launch count once for each kind)
 int count_accumulate_anyc_launches(const cs_params* p, int W) {
     int per_group = 0;
     for_each_anyc_launch(p, p->r, [&](const uint32_t*, int, uint32_t) { ++per_group; return CS_OK; });
@@ -1491,7 +1502,7 @@ int launch_accumulate_anyc(const cs_params* p, float* T, int W, const float* con
                 }
                 choose_pieces(rows, n, requests, kVisitNs8, 4.0 * static_cast<double>(d) * nw * n / kStreamBytesPerNs, groups);
                 return launch_visits_run<8, 8, 1>(rows, vw, n, 2 * omega, stream);
-            }, kAnycRowsOfGroups);
+            }, kAnycRowsOfGroups, true);
             if (rc != CS_OK) return rc;
             continue;
         }
@@ -1514,7 +1525,7 @@ int launch_accumulate_anyc(const cs_params* p, float* T, int W, const float* con
             if (nw > 2) return launch_visits_anyc<4, 1>(p, vw, js, n, omega, stream);
             if (nw > 1) return launch_visits_anyc<2, 1>(p, vw, js, n, omega, stream);
             return launch_visits_anyc<1, 1>(p, vw, js, n, omega, stream);
-        });
+        }, kAnycRowsPerLaunch, true);
         if (rc != CS_OK) return rc;
     }
     return CS_OK;
@@ -2171,7 +2182,8 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
     const uint32_t line0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(RF ? est : out) / sizeof(float)) % kQLine;
     const uint32_t omega = v.omega, pc = v.pc;
     auto cell_of_sum = [&](uint32_t first, uint32_t q) -> uint32_t {
-        const uint32_t x = q < omega ? first + q : first + (q - omega) + (c - pc);
+        // (the half that wrapped past p begins at NC / 2, also in rows that use fewer)
+        const uint32_t x = q < NC / 2 ? first + q : first + (q - NC / 2) + (c - pc);
         return x >= c ? x - c : x;
     };
     // A launch with few rows leaves the chip half empty and waits on its longest chain of
@@ -2338,7 +2350,7 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
 // The query along the rows' visit lists for any column count: rows 0 .. r-2 into the scratch,
 // up to kAnycRowsPerLaunch rows per launch (one row's wavefronts alone fill a third to two
 // thirds of the chip, and every launch has the tail of its longest chain of visits), then the
-// last row together with the median.  The rows of a launch use the same number of cells.
+// last row together with the median.
 // hist (or null): cleared, and receives the counts of est by magnitude bin.  3 rows or more (anyc_visits_serve_query).
 int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t i0, float* est,
                          float* rows, uint64_t* hist, hipStream_t stream) {
@@ -2385,7 +2397,7 @@ int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t 
         else launch(integral_constant<int, 4>(), std::false_type());
         clear = nullptr;
         return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
-    });
+    }, kAnycRowsPerLaunch, true);
     if (rc != CS_OK) return rc;
     fill_visit_gaps(p, last, vr.row[0]);
     const uint32_t omega_last = p->anyc[last].omega;
