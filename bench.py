@@ -274,8 +274,8 @@ def main():
     torch.cuda.synchronize()
 
     # stage names per variant; stage i runs between events i and i + 1.  The stages of HotPath.step are called as it
-    # calls them; where its update goes by way of running sums, merge and momentum come out of the pass that gathers
-    # them.  The update itself (all of it, or without the clearing of worker tables where requests add to them) is
+    # calls them, but second round and feedback, which begin in one launch there, one by one; where its update goes by way
+    # of running sums, merge and momentum come out of the pass that gathers them.  The update itself (all of it, or without the clearing of worker tables where requests add to them) is
     # bracketed by its own pair of events (ev[8], ev[9]) for the roofline figure.
     by_sums = hp._index is not None
     sketch = ["accumulate+merge+momentum", "-", "-"] if by_sums else ["accumulate", "merge+momentum", "-"]

@@ -376,8 +376,8 @@ struct MergePtrs {
 
 // dst = beta * dst + alpha * (src[0] + src[1] + ...), the sum taken in ascending order in
 // binary64 and the result rounded to binary32 once (see k_bundle_merge for why).  Bound by the read of the tables: with one
-// 4-byte load of a thread in flight at a time 16 tables of 5 x 2^18 took 24.4 us; 16-byte pieces (VEC: dst and every
-// source on 16 bytes) of kMergeAhead tables in flight 14.8.
+// 4-byte load of a thread in flight at a time 16 tables of 5 x 2^18 took 24.4 us in a step; 16-byte pieces (VEC: dst and
+// every source on 16 bytes) of kMergeAhead tables in flight 20.6, and 14.8 on tables that the memory-side cache holds.
 constexpr int kMergeAhead = 8;
 
 template <bool VEC>

@@ -10,6 +10,8 @@ Per step (Alg. 3 of the paper, with the W workers simulated on the one device):
     choose largest    idx = top-k |est|           cs_heavy_hitters_topk_kept
     second round      x = (1/W) sum_w g^w[idx]    cs_gather_exact
     feedback          S_v -= S(est[idx]) ; S_u -= S(estimate(S_u, idx))   cs_sketch_feedback_pair (stateful)
+step queries and chooses in one launch for short vectors (cs_sketch_estimate_topk), and second
+round and feedback together (cs_gather_feedback).  Update of short vectors: cs_bundle_sketch_lists.
 Every arithmetic step runs inside libcsketch.so; this class only owns tensors (and counts `hist` of
 short vectors for whoever asks).
 """
