@@ -382,11 +382,10 @@ class GraphedStep:
     Every stage of a step is a fixed sequence of kernel launches on the caller's stream with
     fixed device pointers -- no allocation, no host synchronisation, no memset node -- so the
     whole step can be recorded and replayed with one submission.  That pays where the host is what a
-    step waits for: at d = 784 (us per step, eager / replayed) 47 / 41, and where the program waits
-    for every step, d = 784: 57 / 50, d = 30 403: 83 / 71, d = 2^20: 107 / 106.  Steps enqueued one
-    behind the other run ahead of the device from d = 30 000 or so on, and then the kernels of a
-    graph follow each other a little more slowly than those of a stream: d = 30 403: 56 / 62,
-    d = 2^20: 90 / 96, d = 6.5 M: 334 / 340.  The gradients live in static buffers `g_w` that the
+    step waits for: where the program waits for every step (us per step, eager / replayed, 4 workers with momentum), d = 784:
+    43 / 39, d = 30 403: 64 / 58, d = 2^20: 116 / 111.  Steps enqueued one behind the other run ahead of the device, and then
+    the kernels of a graph follow each other a little more slowly than those of a stream: d = 784: 27 / 27, d = 30 403:
+    42 / 46, d = 2^20: 94 / 98, d = 6.5 M: 347 / 351.  The gradients live in static buffers `g_w` that the
     caller overwrites before each replay; results appear in the HotPath's own tensors."""
 
     def __init__(self, path: HotPath, g_w):
