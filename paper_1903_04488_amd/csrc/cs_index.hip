@@ -11,6 +11,7 @@
 // order, and writes the cell: the tables need no clearing, no atomics, the result does not depend on
 // the order of execution, and the merge over workers and the momentum, which read every cell, come along.
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include <type_traits>
@@ -578,27 +579,52 @@ extern "C" int cs_bundle_sketch(const cs_params* p, float* T, int32_t W, const f
                                 ws_bytes / sizeof(float), S_t, alpha, S_u, S_v, rho, static_cast<hipStream_t>(stream));
 }
 
-// Where the lists take less time than what else there is: about 4 us and r d W values at 250 G/s while the vectors lie in L2
-// (d W up to a million; 200 at 1.4, 180 at 4, 110 at 8 million), against (us, others / lists)
-//  * requests of every coordinate (short vectors, few columns): always: 7 x 32, d = 1947, 109 workers 35.8 / 10.3; 15 x 64,
-//    13 081, 99 workers 353 / 73; 3 x 73, 1573, 5 workers 7.8 / 4.0; 5 x 1913, 64 779, 1 worker 24.9 / 5.4;
+// Where the lists take less time than what else there is, by figures of 1300 shapes; us, others / lists.  Lists take 4 us,
+// then three things one after the other:
+//  * values: r d W at 250 G/s while the vectors lie in L2 (d W up to a million; 200 at 1.4, 180 at 4, 110 at 8 million);
+//  * a cell's chain: 64 lanes and two entries of each at once, so that a cell of n coordinates is n / 128 rounds of a load
+//    that waits for another, 0.6 us each, 0.95 with 8 workers, and 0.5 more where vectors and lists are more than L2 holds;
+//  * the cells of a wide table, 45 ps each and group of workers (14 in a launch that clears or merges).
+// Against
 //  * visit lists of a power of two of columns, 13 to 16 us and 1.3 a million values, 2.7 with many groups of workers: 7 x 512,
 //    18 231, 8 workers (1.0 million) 13.9 / 7.0; 7 x 512, 65 729, 5 workers (2.3) 15.5 / 13.0; 7 x 2048, 73 440, 5 workers
 //    (2.6) 16.1 / 14.3; 5 x 512, 33 053, 42 workers (6.9) 30.7 / 32; with more than 8 rows, two launches: 15 x 1024,
-//    78 577, 4 workers (4.7) 29 / 23;
+//    78 577, 4 workers (4.7) 29 / 23; few columns: 3 x 64, 400 000 37 / 34, 600 000 40 / 50, 10^6 42 / 131; 3 x 256, 400 000
+//    18 / 12, 10^6 22 / 38; 5 x 128, 600 000 25 / 38; wide: 3 x 2^18, 78 644 68 / 38; 3 x 2^20, 30 000 53 / 118;
 //  * visit lists of other column counts: 7 x 2561, 217 913, 1 worker (1.5) 38.6 / 10; 5 x 853, 379 355, 2 workers (3.8)
 //    26.4 / 19; 3 x 847, 229 277, 7 workers (4.8, 1.6 million in the vectors) 20.4 / 24; 15 x 2277, 237 944, 3 workers (10.7)
-//    58.7 / 47.
+//    58.7 / 47; few columns: 5 x 90, 600 000 50 / 52; 7 x 90 100 / 56; 3 x 100, 10^6 62 / 87;
+//  * requests of every coordinate into tables in LDS (lds_table_applies): 3 x 63, 100 000 21 / 12, 4 workers 22 / 16; 3 x 33,
+//    100 000, 4 workers 21 / 25; 3 x 33, 10^6 46 / 244, 4 workers 78 / 348; 15 x 33, 100 000, 32 workers 292 / 205;
+//    15 x 16, 400 000 63 / 192; or in memory: 7 x 32, 1947, 109 workers 35.8 / 10.3; 5 x 1913, 64 779 24.9 / 5.4;
+//    3 x 500 001, 500 002 103 / 74, 150 001 54 / 73; 3 x 1 000 001, 1000 42 / 99.
+// W = 0, one vector and one table: the lattice form of a power of two of columns, 5 x 16 384, 81 921 8.1 / 6.6, 400 000 x 3 x
+// 64 162 / 34, 5 x 65 536, 131 073 11 / 17; requests to few cells, 3 x 63, 4 million 6690 / 522; 3 x 200 001, 60 001 19 / 28.
 static bool lists_pay(const cs_params* p, int32_t W, int64_t d) {
-    const double vectors = static_cast<double>(d) * W, values = vectors * p->r;
+    const double r = p->r, c = p->c, n = static_cast<double>(d), workers = W > 0 ? W : 1;
+    const double vectors = n * workers, values = vectors * r, cells = r * c * ceil(workers / CS_BUNDLE_GROUP);
+    const double per_cell = n / c;
+    const bool beyond_l2 = n * (workers + r / 4) > 1e6;
     if (vectors > 4e6) return false;
-    if (walk_applies(p, d)) return values <= (p->r > 8 ? (W > 16 ? 7e6 : 5e6) : W > 16 ? 5.5e6 : 3e6);
-    if (anyc_update_applies(p, d, W)) return vectors <= 1.2e6 && values <= (p->r > 8 ? 1e7 : 5e6);
-    return true;
+    if (walk_applies(p, d)) {
+        if (W == 0 ? cells > 1.5e5 : c > 4.0 * n || per_cell > (beyond_l2 ? 1600.0 : 6400.0)) return false;
+        return values <= (p->r > 8 ? (W > 16 ? 7e6 : 5e6) : W > 16 ? 5.5e6 : 3e6);
+    }
+    if (anyc_update_applies(p, d, static_cast<int>(workers))) {
+        if (W > 0 && per_cell > (p->r > 5 ? 8000.0 : 6400.0)) return false;
+        return vectors <= 1.2e6 && values <= (p->r > 8 ? 1e7 : 5e6);
+    }
+    const double round = 0.55 + 0.05 * (workers < 8.0 ? workers : 8.0) + (beyond_l2 ? 0.5 : 0.0);
+    const double lists = 4.0 + 45e-6 * cells + per_cell / 128.0 * round + values / 250e3;
+    double others;
+    if (W == 0) others = 5.0 + 4.0 * r + 2e-6 * cells + r * n * (c < 250.0 ? 8.0 / c : 0.032) * 1e-3;
+    else if (lds_table_applies(p, d)) others = 10.0 + r + r * n * (5.0 + 5.0 * workers) * 1e-6;
+    else others = 10.0 + 14e-6 * cells + cells / c * n * (c < 208.0 ? 10.0 / c : 0.048) * 1e-3;
+    return lists <= others;
 }
 
 extern "C" int cs_cell_lists_bytes(const cs_params* p, int32_t W, int64_t d, size_t* bytes) {
-    if (!params_ok(p) || W < 1 || d < 0 || !bytes) return CS_EINVAL;
+    if (!params_ok(p) || W < 0 || d < 0 || !bytes) return CS_EINVAL;
     *bytes = 0;
     if (d >= 1 && d < (1ll << 30) && W <= kListVectors && lists_pay(p, W, d)) *bytes = list_rows(p, d).words * sizeof(uint32_t);
     return CS_OK;

@@ -63,6 +63,8 @@ int launch_magnitude_hist(const float* est, int64_t d, uint64_t* hist, hipStream
 int launch_hash_range_lattice(const cs_params* p, int64_t i0, int64_t n, uint32_t* bucket,
                               int8_t* sign, hipStream_t stream);
 
+bool lds_table_applies(const cs_params* p, int64_t d);   // the update of a bundle hash by hash, in LDS (cs_kernels.hip)
+
 // Walk-order update of a worker bundle T = float[ceil(W/8)][r][c][8] (cs_walk.hip).
 bool walk_applies(const cs_params* p, int64_t d);
 // fold = true: T is one table float[r][c] and receives the sum over the W workers

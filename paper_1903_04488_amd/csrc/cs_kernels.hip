@@ -202,7 +202,7 @@ k_accumulate_cells(KParams p, GroupedVectors vec, int nw, float* __restrict__ T,
 constexpr uint32_t kLdsCells = 2048;      // R * c at most: 64 KB of LDS for 8 workers
 constexpr uint32_t kLdsColumns = 128;     // c at most
 
-inline bool lds_table_applies(const cs_params* p, int64_t d) {
+bool lds_table_applies(const cs_params* p, int64_t d) {
     return !(p->flags & CS_FLAG_NO_LDS_TABLE) && p->c <= kLdsColumns &&
            static_cast<uint64_t>(p->r) * p->c <= kLdsCells &&
            d >= static_cast<int64_t>(2048) * p->c / p->r;

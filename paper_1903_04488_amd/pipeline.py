@@ -99,19 +99,17 @@ class HotPath:
 
     def _build_cell_lists(self):
         """for short vectors; True where there are some"""
+        n = B.cs_cell_lists_bytes(self.params, 0 if self.fold_workers else self.W, self.d)
+        if not n:
+            return False
+        self._index = torch.empty(n, dtype=torch.uint8, device=self.device)
+        B.cs_cell_lists_build(self.params, self.d, self._index)
+        self._cell_lists = True
         # folded workers: all of them cell by cell while that is less than a launch more, else their sum
-        few = self.r * self.d * self.W <= 1_250_000
-        for W in ((self.W, 1) if few else (1,)) if self.fold_workers else (self.W,):
-            n = B.cs_cell_lists_bytes(self.params, W, self.d)
-            if n:
-                self._index = torch.empty(n, dtype=torch.uint8, device=self.device)
-                B.cs_cell_lists_build(self.params, self.d, self._index)
-                self._cell_lists = True
-                self._sum_first = W < self.W
-                self._sums_params = self._lists()
-                self._sums_for = self.fold_workers, self.W, self.d
-                return True
-        return False
+        self._sum_first = self.W > 1 and (self.r * self.d * self.W > 1_250_000 or self.W > 256)
+        self._sums_params = self._lists()
+        self._sums_for = self.fold_workers, self.W, self.d
+        return True
 
     def _build_index(self):
         n = B.cs_update_index_bytes(self.params, 0 if self.fold_workers else self.W, self.d)
