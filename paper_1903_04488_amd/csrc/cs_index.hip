@@ -373,6 +373,7 @@ struct ListArgs {
     float* S_v;
     float scale, alpha, rho;
     uint32_t r, c, d;
+    uint32_t b0;                     // the launch's first column
     int32_t W, slices;
     const float* g[kListVectors];
 };
@@ -386,7 +387,7 @@ __global__ void __launch_bounds__(kBlock) k_sum_lists(ListArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int slice = wave % a.slices;
     const uint32_t j = blockIdx.y, part = lane % L, set = wave / a.slices;
-    const uint32_t b = (blockIdx.x * (kWaves / a.slices) + set) * kCells + lane / L;
+    const uint32_t b = a.b0 + (blockIdx.x * (kWaves / a.slices) + set) * kCells + lane / L;
     const bool in = b < a.c;
     const uint32_t* start = a.lists + static_cast<uint64_t>(j) * (a.c + 1ull + a.d);
     const uint32_t* entry = start + a.c + 1;
@@ -669,13 +670,18 @@ extern "C" int cs_bundle_sketch_lists(const cs_params* p, float* T, int32_t W, c
     int L = 8;
     while (L < 64 && L < (want > each ? want : each)) L *= 2;
     const uint32_t cells = kBlock / L / a.slices;      // of a workgroup
-    const dim3 grid((p->c + cells - 1) / cells, p->r);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    switch (L) {
-        case 8: k_sum_lists<8><<<grid, kBlock, 0, s>>>(a); break;
-        case 16: k_sum_lists<16><<<grid, kBlock, 0, s>>>(a); break;
-        case 32: k_sum_lists<32><<<grid, kBlock, 0, s>>>(a); break;
-        default: k_sum_lists<64><<<grid, kBlock, 0, s>>>(a);
+    constexpr uint32_t kListBlocks = 1u << 22;         // workgroups of a launch: one of 2^32 threads is refused
+    for (; a.b0 < p->c; a.b0 += cells * kListBlocks) { // (cells <= 32, c <= 2^31: no overflow)
+        const uint32_t blocks = (p->c - a.b0 - 1) / cells + 1;
+        const dim3 grid(blocks < kListBlocks ? blocks : kListBlocks, p->r);
+        switch (L) {
+            case 8: k_sum_lists<8><<<grid, kBlock, 0, s>>>(a); break;
+            case 16: k_sum_lists<16><<<grid, kBlock, 0, s>>>(a); break;
+            case 32: k_sum_lists<32><<<grid, kBlock, 0, s>>>(a); break;
+            default: k_sum_lists<64><<<grid, kBlock, 0, s>>>(a);
+        }
+        if (hipGetLastError() != hipSuccess) return CS_EHIP;
     }
-    return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+    return CS_OK;
 }

@@ -88,6 +88,18 @@ def test_arguments():
         cs.cs_bundle_sketch_lists(p, None, g, lists, S_t=S, S_u=S)       # one table of the two
 
 
+def test_more_columns_than_a_launch_takes():
+    """8 cells a workgroup of 256 threads: 2^27 columns and more would be a launch of 2^32 threads"""
+    r, c, d, W = 1, (1 << 27) + 3, 2001, 25
+    p = cs.cs_params_init(r, c, 190304488, d)
+    _, _, gs = _vectors(d, W)
+    got, want = (torch.zeros(cs.cs_bundle_floats(p, W), device=DEV) for _ in range(2))
+    got.fill_(float("nan"))
+    cs.cs_bundle_sketch_lists(p, got, gs, _lists(p, d))
+    cs.cs_sketch_accumulate_bundle(p, want, gs)
+    assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("kind", ["step", "fold", "fold-many", "dense", "graph"])
 def test_a_path_of_short_vectors_goes_by_its_lists(kind):
     """the same state and selection as a path that is given none"""
