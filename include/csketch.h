@@ -259,7 +259,8 @@ int cs_bundle_sketch(const cs_params* p, float* T, int32_t W, const float* const
 
 /* The same of short vectors, in one launch and for any column count: every cell is the sum of its coordinates, which
  * are laid out once per sketch, with their signs, in lists (device memory of the caller).  T and S_t, S_u, S_v as above;
- * T may be null for any W if S_t is wanted only.
+ * T may be null for any W if S_t is wanted only: the workers' values of a coordinate are then added in binary64, times
+ * alpha, and rounded once, as by cs_vectors_sum, before they are sketched.
  * cs_cell_lists_bytes: 0 where the other forms take less time (W = 0: for one vector and T null).  lists: what cs_cell_lists_build wrote for the same p
  * and d (of another sketch: wrong sums, never an access out of range).  W <= 256, 1 <= d < 2^30. */
 int cs_cell_lists_bytes(const cs_params* p, int32_t W, int64_t d, size_t* bytes);

@@ -379,7 +379,12 @@ struct ListArgs {
 };
 
 // L lanes of a cell (8 to 64) share out its coordinates; `slices` wavefronts share out the groups of 8 workers.
-template <int L>
+// FOLD (S_t alone): the workers are summed coordinate by coordinate, in binary64 and rounded once, before a cell is: values
+// that cancel between workers leave no rounding of their own size in it.  The slices share out a cell's coordinates too.
+// us, sums of every worker's cell / of the coordinates first (this) / a launch for the workers' sum more: 5 x 40, d = 784, 4
+// workers 3.9 / 3.3 / 5.6, 100 workers 7.7 / 6.6 / 10.7; 5 x 64, 5000, 32 workers 7.0 / 6.4 / 7.2; 3 x 33, 2000 (99 wavefronts that
+// each wait for 100 loads), 100 workers 8.7 / 13.0 / 10.7.
+template <int L, bool FOLD>
 __global__ void __launch_bounds__(kBlock) k_sum_lists(ListArgs a) {
     static_assert(L >= CS_BUNDLE_GROUP, "a lane per worker of a group");
     constexpr int kCells = 64 / L, kWaves = kBlock / 64;
@@ -409,6 +414,28 @@ __global__ void __launch_bounds__(kBlock) k_sum_lists(ListArgs a) {
     const uint32_t mine = (part & 1u) * 4 + (part >> 1 & 1u) * 2 + (part >> 2 & 1u);
     double total = 0.0;
     const int groups = (a.W + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP;
+    if constexpr (FOLD) {
+        float v = 0.0f;
+        for (uint32_t t = slice * L + part; t < n; t += a.slices * L) {
+            const uint32_t e = entry[lo + t];
+            if (e >> 1 >= a.d) continue;               // (lists of another sketch)
+            double sum = 0.0;
+            int w = 0;
+            for (; w + CS_BUNDLE_GROUP <= a.W; w += CS_BUNDLE_GROUP) {
+                float x[CS_BUNDLE_GROUP];
+#pragma unroll
+                for (int q = 0; q < CS_BUNDLE_GROUP; ++q) x[q] = a.g[w + q][e >> 1];
+#pragma unroll
+                for (int q = 0; q < CS_BUNDLE_GROUP; ++q) sum += static_cast<double>(x[q]);
+            }
+#pragma unroll 4
+            for (; w < a.W; ++w) sum += static_cast<double>(a.g[w][e >> 1]);
+            v += apply_sign(static_cast<float>(static_cast<double>(a.alpha) * sum), e << 31);
+        }
+#pragma unroll
+        for (int off = 1; off < L; off *= 2) v += __shfl_xor(v, off);
+        total = static_cast<double>(v);
+    } else
     for (int g = slice; g < groups; g += a.slices) {
         const int nw = a.W - g * CS_BUNDLE_GROUP < CS_BUNDLE_GROUP ? a.W - g * CS_BUNDLE_GROUP : CS_BUNDLE_GROUP;
         float v[CS_BUNDLE_GROUP];
@@ -458,8 +485,10 @@ __global__ void __launch_bounds__(kBlock) k_sum_lists(ListArgs a) {
         total += static_cast<double>(sum);
     }
     if (!a.S_t) return;
+    if constexpr (!FOLD) {
 #pragma unroll
-    for (int off = 1; off < CS_BUNDLE_GROUP; off *= 2) total += __shfl_xor(total, off);
+        for (int off = 1; off < CS_BUNDLE_GROUP; off *= 2) total += __shfl_xor(total, off);
+    }
     if (a.slices > 1) {
         __shared__ double totals[kWaves][kCells];
         if (part == 0) totals[wave][lane / L] = total;
@@ -467,7 +496,7 @@ __global__ void __launch_bounds__(kBlock) k_sum_lists(ListArgs a) {
         for (int q = 1; slice == 0 && q < a.slices; ++q) total += totals[wave + q][lane / L];
     }
     if (writes) {
-        const float st = static_cast<float>(static_cast<double>(a.alpha) * total);
+        const float st = static_cast<float>((FOLD ? static_cast<double>(a.scale) : static_cast<double>(a.alpha)) * total);
         a.S_t[at] = st;
         if (a.S_u) {
             const float u = a.rho * old_u + st;
@@ -664,22 +693,30 @@ extern "C" int cs_bundle_sketch_lists(const cs_params* p, float* T, int32_t W, c
     a.W = W;
     for (int w = 0; w < W; ++w) a.g[w] = g_w[w];
     const int groups = (W + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP;
-    a.slices = groups >= 4 ? 4 : groups >= 2 ? 2 : 1;
+    const bool fold = !T && W > 1;
+    a.slices = fold ? 1 : groups >= 4 ? 4 : groups >= 2 ? 2 : 1;
     // about 65 536 lanes in all, and not more than 8 coordinates for each
     const double want = 65536.0 / (static_cast<double>(p->r) * p->c * a.slices), each = static_cast<double>(d) / (8.0 * p->c);
     int L = 8;
     while (L < 64 && L < (want > each ? want : each)) L *= 2;
+    // (FOLD: up to four wavefronts of a cell while it has coordinates for them; 5 x 64, 5000, 32 workers 8.4 -> 6.4 us)
+    while (fold && L == 64 && a.slices < 4 && 64.0 * a.slices < want && 64.0 * a.slices * p->c < static_cast<double>(d)) a.slices *= 2;
     const uint32_t cells = kBlock / L / a.slices;      // of a workgroup
     hipStream_t s = static_cast<hipStream_t>(stream);
     constexpr uint32_t kListBlocks = 1u << 22;         // workgroups of a launch: one of 2^32 threads is refused
     for (; a.b0 < p->c; a.b0 += cells * kListBlocks) { // (cells <= 32, c <= 2^31: no overflow)
         const uint32_t blocks = (p->c - a.b0 - 1) / cells + 1;
         const dim3 grid(blocks < kListBlocks ? blocks : kListBlocks, p->r);
+        auto launch = [&](auto lanes) {
+            constexpr int N = decltype(lanes)::value;
+            if (fold) k_sum_lists<N, true><<<grid, kBlock, 0, s>>>(a);
+            else k_sum_lists<N, false><<<grid, kBlock, 0, s>>>(a);
+        };
         switch (L) {
-            case 8: k_sum_lists<8><<<grid, kBlock, 0, s>>>(a); break;
-            case 16: k_sum_lists<16><<<grid, kBlock, 0, s>>>(a); break;
-            case 32: k_sum_lists<32><<<grid, kBlock, 0, s>>>(a); break;
-            default: k_sum_lists<64><<<grid, kBlock, 0, s>>>(a);
+            case 8: launch(std::integral_constant<int, 8>()); break;
+            case 16: launch(std::integral_constant<int, 16>()); break;
+            case 32: launch(std::integral_constant<int, 32>()); break;
+            default: launch(std::integral_constant<int, 64>());
         }
         if (hipGetLastError() != hipSuccess) return CS_EHIP;
     }

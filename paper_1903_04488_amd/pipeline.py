@@ -37,7 +37,8 @@ class HotPath:
         values, and the k largest exact sums are kept (Alg. 3 as the paper trains with it).
         fold_workers: the workers, which share this GPU, are summed before they are sketched
         (every vector is read once; the sum goes into d floats of scratch, then straight into
-        S_t): no worker tables, no merge.  The scratch is the query's, so the stages of one
+        S_t; of short vectors each coordinate's sum is taken where a cell needs it, r times): no
+        worker tables, no merge.  The scratch is the query's, so the stages of one
         path run one after the other; where the query has none (short vectors and column counts
         without a traversal plan) the path holds d floats more.
         Memory beside the tables and est: the query's scratch (r d floats for long vectors), for short vectors the lists of

@@ -58,6 +58,28 @@ def test_tables_merge_and_momentum(r, c, d, W):
     np.testing.assert_array_equal(T.cpu().numpy().reshape(bundle.shape), bundle)
 
 
+@pytest.mark.parametrize("r,c,d", [(5, 40, 784), (3, 33, 2001), (3, 7, 5), (5, 1000, 5003), (3, 32, 20_011), (9, 4096, 50_001)])
+@pytest.mark.parametrize("W", [2, 4, 7, 8, 9, 17, 256])
+def test_folded_workers_are_summed_before_a_cell_is(r, c, d, W):
+    """without worker tables: a cell is off by roundings of the workers' mean, also where the workers all but cancel"""
+    gen = torch.Generator().manual_seed(W + d)
+    p = cs.cs_params_init(r, c, 190304488, d)
+    gs = [1e4 * torch.randn(d, generator=gen) for _ in range(W - 1)]
+    gs.append(-sum(g.double() for g in gs).float() + torch.randn(d, generator=gen))
+    gs = [g.to(DEV) for g in gs]
+    got = torch.full((3, r, c), 0.5, device=DEV)
+    cs.cs_bundle_sketch_lists(p, None, gs, _lists(p, d), 1.0, got[0], 1.0 / W, got[1], got[2], 0.5)
+    assert torch.equal(got[1], got[0] + 0.25) and torch.equal(got[2], got[1] + 0.5)
+    exact = sum(g.double() for g in gs) / W
+    bucket, sign = torch.empty(r, d, dtype=torch.int32, device=DEV), torch.empty(r, d, dtype=torch.int8, device=DEV)
+    cs.cs_hash_debug_range(p, 0, d, bucket, sign)
+    for j in range(r):
+        cell = lambda x: torch.zeros(c, dtype=torch.float64, device=DEV).index_add_(0, bucket[j].long(), x)   # noqa: B023, E731
+        # n values rounded once and n - 1 additions, each off by half an ulp of at most the sum of magnitudes; twice that
+        bound = 2.0 ** -23 * cell(torch.ones_like(exact)) * cell(exact.abs())
+        assert ((got[0][j].double() - cell(exact * sign[j])).abs() <= bound).all()
+
+
 def test_values_that_are_not_finite_stay_in_their_cells():
     r, c, d = 3, 64, 3001
     p = cs.cs_params_init(r, c, 5, d)
