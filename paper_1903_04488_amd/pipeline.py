@@ -29,7 +29,7 @@ class HotPath:
     # workspace, and what they were made for: the sketch's parameters, fold_workers, W and d
     _index = _sums_ws = _sums_params = _sums_for = None
     _cell_lists = False                  # _index holds cell lists (cs_bundle_sketch_lists): short vectors
-    SUMS_OWN_BYTES = 2 << 30             # the workspace: up to here, else the path does without (0: in any case)
+    SUMS_OWN_BYTES = 2 << 30             # the workspace, or the cell lists: up to here, else the path does without (0: in any case)
 
     def __init__(self, d: int, W: int, r: int, c: int, k: int, seed: int,
                  rho: float | None = None, device="cuda:0", P: int = 1, fold_workers: bool = False):
@@ -42,10 +42,10 @@ class HotPath:
         path run one after the other; where the query has none (short vectors and column counts
         without a traversal plan) the path holds d floats more.
         Memory beside the tables and est: the query's scratch (r d floats for long vectors), for short vectors the lists of
-        the cells' coordinates (r (c + d) words, 1.3 MB at d = 65 536, 5 x 1024), and where the update goes
-        by way of running sums (up to 4 workers, up to 16 with short vectors, up to 64 with vectors of 32 million on)
-        their index and workspace, 35 MB at d = 6.5 M, W = 4, 5 x 2^17 and 1.9 GB at d = 10^8, W = 32, 5 x 2^20, where they
-        save 1.8 % of the update: SUMS_OWN_BYTES, of the class or a subclass, bounds the workspace."""
+        the cells' coordinates (r (c + d) words, 1.3 MB at d = 65 536, 5 x 1024; up to 240 MB, for the sum
+        of folded vectors of 4 million and 15 rows of a few columns), and where the update goes by way of
+        running sums (up to 4 workers, up to 16 with short vectors, up to 64 with vectors of 32 million on) their index and workspace, 35 MB at d = 6.5 M, W = 4, 5 x 2^17 and 1.9 GB at d = 10^8, W = 32, 5 x 2^20, where they
+        save 1.8 % of the update: SUMS_OWN_BYTES, of the class or a subclass, bounds the workspace and the lists."""
         self.d, self.W, self.r, self.c, self.k = d, W, r, c, k
         self.P = P
         self.fold_workers = fold_workers
@@ -101,7 +101,7 @@ class HotPath:
     def _build_cell_lists(self):
         """for short vectors; True where there are some"""
         n = B.cs_cell_lists_bytes(self.params, 0 if self.fold_workers else self.W, self.d)
-        if not n:
+        if not n or n > self.SUMS_OWN_BYTES:
             return False
         self._index = torch.empty(n, dtype=torch.uint8, device=self.device)
         B.cs_cell_lists_build(self.params, self.d, self._index)

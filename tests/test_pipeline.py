@@ -122,6 +122,17 @@ def test_running_sums_have_memory_of_their_own_up_to_a_limit(monkeypatch, fold, 
         assert ws.data_ptr() + need <= own.data_ptr() or own.data_ptr() + scratch <= ws.data_ptr()
 
 
+@pytest.mark.parametrize("limit,built", [(0, False), (63, False), (64, True), (None, True)])
+@pytest.mark.parametrize("fold", [False, True])
+def test_cell_lists_are_bounded_by_the_limit_of_a_path_s_own_memory(monkeypatch, fold, limit, built):
+    monkeypatch.setattr(pipeline.B, "cs_cell_lists_bytes", lambda p, W, d: 64)
+    monkeypatch.setattr(pipeline.B, "cs_cell_lists_build", lambda p, d, lists: None)
+    if limit is not None:
+        monkeypatch.setattr(pipeline.HotPath, "SUMS_OWN_BYTES", limit)
+    path = bare(fold_workers=fold, d=100, params=binding.CsParams())
+    assert path._build_cell_lists() == built == path._cell_lists and (path._index is not None) == built
+
+
 @pytest.mark.parametrize("index", [False, True])
 def test_tables_of_workers_may_be_made_beside_the_query_of_the_step_before(calls, monkeypatch, index):
     """accumulate alone, workers not folded: no memory that it is given is the query's"""
