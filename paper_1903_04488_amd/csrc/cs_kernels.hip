@@ -389,7 +389,7 @@ k_merge(float* __restrict__ dst, float beta, MergePtrs ptrs, int nw, float alpha
     const double a = static_cast<double>(alpha);
     const int64_t n4 = VEC ? n / 4 : 0;
     for (int64_t t = t0; t < n4; t += stride) {
-        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        double s[4] = {-0.0, -0.0, -0.0, -0.0};        // (the one number that leaves the first table's zeros their sign)
         f4 base = {0.0f, 0.0f, 0.0f, 0.0f};
         if (beta != 0.0f) base = reinterpret_cast<const f4*>(dst)[t];
         auto add = [&](auto count, int w) {

@@ -45,6 +45,19 @@ def test_merge_bit_for_bit(W, r, c, shift_dst, shift_src):
         np.testing.assert_array_equal(dst.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("W", [1, 2, 9, 130])
+def test_merge_of_negative_zeros(W, shift):
+    """zeros of one sign keep it, whatever the tables' alignment"""
+    p = cs.cs_params_init(3, 33, 3)
+    zero = np.full((3, 33), -0.0, dtype=np.float32)
+    src = [_table(zero, shift) for _ in range(W)]
+    for beta, sign in ((2.0, True), (-2.0, False), (0.0, False)):   # -0 + -0, +0 + -0, and no term of dst: +0 + -0
+        dst = _table(zero, 0)
+        cs.cs_sketch_merge(p, dst, src, alpha=0.25, beta=beta)
+        assert not dst.any() and (np.signbit(dst.cpu().numpy()) == sign).all(), beta
+
+
 @pytest.mark.parametrize("k", [1, 63, 65, 3001])
 @pytest.mark.parametrize("W", [1, 3, 4, 7, 15, 16, 17, 21, 256, 259])
 def test_gather_bit_for_bit(W, k):
