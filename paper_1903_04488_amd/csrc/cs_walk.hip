@@ -1048,18 +1048,30 @@ int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js,
     return launch_visits_run<WL, 16, NWAVE>(rows, a, nrows, ncell, stream);
 }
 
-// the visit list of row j serves vectors of length d, and (unless any_cost) is expected to take
-// less time than the stride walk in a launch of its own.  The time model prices a row alone, and visits that its walkers
-// pass over too, so up to a quarter more than the walk is less in the launch of all rows (us, 8 workers unless said, such a row by
-// the walk / its list, priced 1.02 to 1.13 times the walk: 7 x 2^19, 25 M 1075 / 1025, 2 workers 506 / 469; 7 x 65 536, 22 M 849 / 801;
-// 5 x 2^20, 18 M 853 / 776; 15 x 2^20, 48 M, 5 workers 6181 / 4884; 15 x 2^18, 24 M, 2 workers 3056 / 2125; 15 x 32 768, 17 M 1408 / 1393;
-// the one that lost: 15 x 2^20, 61 M, 3 workers 4783 / 4873).
-bool visits_apply(const cs_params* p, uint32_t j, int64_t d, bool any_cost = false) {
+// the visit list of row j serves vectors of length d
+bool list_serves(const cs_params* p, uint32_t j, int64_t d) {
     const cs_visit_plan& vp = p->visit[j];
     if ((p->flags & CS_FLAG_NO_VISIT_LIST) != 0 || vp.K == 0) return false;
     if (vp.ncell < 2 || vp.ncell > 4 || vp.K > CS_MAX_VISITS || d > kStepsMaxD) return false;   // (lists end at 2^28)
-    if (static_cast<uint64_t>(d) > vp.cover) return false;
-    return any_cost || vp.cost <= vp.cost_walk + vp.cost_walk / 4;
+    return static_cast<uint64_t>(d) <= vp.cover;
+}
+
+// ... and (unless any_cost) is expected to take less time than the stride walk.  Up to a quarter above the walk that is
+// the launch of the walk more: us, 8 workers unless said, such a row by the walk / its list, priced 1.02 to 1.13 times the walk,
+// 7 x 2^19, 25 M 1075 / 1025, 2 workers 506 / 469; 7 x 65 536, 22 M 849 / 801; 5 x 2^20, 18 M 853 / 776, 25 M 1044 / 974; 15 x
+// 65 536, 25 M 2083 / 1995, 2 workers 734 / 601.  Where other rows walk in any case, such a row lengthens their launch
+// only by a longer chain of visits (a shorter stride) than theirs: 15 x 2^20, 48 M, 5 workers 6220 / 5011 (a stride of
+// 30 751 beside 118 023); but behind a longer chain 15 x 2^20, 18 M, 5 workers 3467 / 3606, 61 M 5692 / 5778; 15 x 2^18,
+// 100 M, 3 workers 4722 / 4891.
+bool visits_apply(const cs_params* p, uint32_t j, int64_t d, bool any_cost = false) {
+    const cs_visit_plan& vp = p->visit[j];
+    auto dear = [](const cs_visit_plan& v) { return v.cost > v.cost_walk + v.cost_walk / 4; };
+    if (!list_serves(p, j, d)) return false;
+    if (any_cost || vp.cost < vp.cost_walk) return true;
+    if (dear(vp)) return false;
+    for (uint32_t q = 0; q < p->r; ++q)
+        if ((!list_serves(p, q, d) || dear(p->visit[q])) && p->plan[q].Dw <= p->plan[j].Dw) return false;
+    return true;
 }
 
 // Groups of 8 workers that share a launch, `most` at most.  A launch of one group of short vectors is a chain of visits

@@ -41,11 +41,13 @@ class HotPath:
         worker tables, no merge.  The scratch is the query's, so the stages of one
         path run one after the other; where the query has none (short vectors and column counts
         without a traversal plan) the path holds d floats more.
-        Memory beside the tables and est: the query's scratch (r d floats for long vectors), for short vectors the lists of
-        the cells' coordinates (r (c + d) words, 1.3 MB at d = 65 536, 5 x 1024; up to 240 MB, for the sum
-        of folded vectors of 4 million and 15 rows of a few columns), and where the update goes by way of
-        running sums (up to 4 workers, up to 16 with short vectors, up to 64 with vectors of 32 million on) their index and workspace, 35 MB at d = 6.5 M, W = 4, 5 x 2^17 and 1.9 GB at d = 10^8, W = 32, 5 x 2^20, where they
-        save 1.8 % of the update: SUMS_OWN_BYTES, of the class or a subclass, bounds the workspace and the lists."""
+        Memory beside the tables and est: the query's scratch (r d floats for long vectors), for short
+        vectors the lists of the cells' coordinates (r (c + d) words, 1.3 MB at d = 65 536, 5 x 1024; up to
+        240 MB, for the sum of folded vectors of 4 million and 15 rows of a few columns), and where the
+        update goes by way of running sums (up to 4 workers, up to 16 with short vectors, up to 64 with
+        vectors of 32 million on) their index and workspace, 35 MB at d = 6.5 M, W = 4, 5 x 2^17 and 1.9 GB
+        at d = 10^8, W = 32, 5 x 2^20, where they save 1.8 % of the update: SUMS_OWN_BYTES, of the class or a
+        subclass, bounds the workspace and the lists."""
         self.d, self.W, self.r, self.c, self.k = d, W, r, c, k
         self.P = P
         self.fold_workers = fold_workers

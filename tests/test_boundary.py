@@ -252,6 +252,34 @@ def test_update_launch_count_follows_the_grouping(lib):
         assert cs.cs_bundle_update_launches(p, W, 6_500_000) == n
 
 
+def test_a_list_priced_a_little_above_the_walk_is_taken_where_that_saves_a_launch_or_the_longest_chain(lib):
+    """11 rows, 8 of them cheap along their lists: with the ninth listed too their lists are two launches, and the walk of what
+    is left is one"""
+    d = 3_000_000
+    p = cs.cs_params_init(11, 1 << 12, 4, d)
+    assert all(p.visit[j].K for j in range(11))
+    for j in range(11):
+        p.visit[j].cost, p.visit[j].cost_walk = 10, 1000
+    between = p.visit[8]
+
+    def launches(price, strides):
+        between.cost = price
+        for j, s in zip((8, 9, 10), strides):
+            p.plan[j].Dw = s
+        return cs.cs_bundle_update_launches(p, 8, d)
+
+    assert launches(1250, (500, 500, 500)) == 2                 # all rows are listed: no walk
+    for j in (9, 10):
+        p.visit[j].cost = 1251
+    assert launches(999, (500, 500, 500)) == 3                  # the cheaper way
+    assert launches(1250, (499, 500, 900)) == 3                 # a longer chain than any row that walks in any case
+    assert launches(1250, (500, 500, 900)) == 2 == launches(1000, (900, 500, 1200))
+    assert launches(1251, (499, 500, 900)) == 2
+    p.visit[9].K = 0                                            # (a row without a list walks, whatever its price)
+    p.visit[9].cost = 10
+    assert launches(1250, (500, 500, 900)) == 2 and launches(1250, (499, 500, 900)) == 3
+
+
 def test_status_strings(lib):
     assert cs.cs_status_string(0) == "ok"
     assert "invalid" in cs.cs_status_string(-1)
