@@ -366,9 +366,9 @@ def main():
     # the update runs as a few launches per group of 8 workers (rows that share a traversal
     # share a launch); the algorithmic bytes of the whole update (every gradient read once,
     # every worker table written once) are spread evenly over those launches
-    # (folded workers: one call of several different kernels, taken as a whole; by running sums: a launch per group and
-    # 8 rows, with its share of the pass that gathers them)
-    n_launch = (1 if hp.fold_workers else (cfg.W + 7) // 8 * ((cfg.r + 7) // 8) if by_sums
+    # (folded workers: one call of several different kernels, taken as a whole; cell lists: one launch; by running sums: a
+    # launch per group and 8 rows, with its share of the pass that gathers them)
+    n_launch = (1 if hp.fold_workers or hp._cell_lists else (cfg.W + 7) // 8 * ((cfg.r + 7) // 8) if by_sums
                 else B.cs_bundle_update_launches(hp.params, cfg.W, cfg.d))
     acc_kernel_ms = sum(ev[8].elapsed_time(ev[9]) for ev in events) / args.steps / n_launch
     per_set = [[] for _ in range(n_sets)]         # the update's time on each resident input set

@@ -204,9 +204,8 @@ int cs_sketch_accumulate_batch(const cs_params* p, float* const* S_w, const floa
 #define CS_BUNDLE_GROUP 8
 int cs_bundle_floats(const cs_params* p, int32_t W, int64_t* n);
 /* *n = number of kernel launches one cs_sketch_accumulate_bundle(p, T, W, g_w, d, ...) call
- * makes for one group of 8 workers after the other (rows that share a traversal share a launch; a launch
- * that takes several groups of short vectors, or rows with different numbers of running sums, counts once for each); for reading profiles and for dividing
- * a timed call into per-launch figures.  Host only. */
+ * makes (rows that share a traversal share a launch, and so do groups of 8 workers of short vectors);
+ * for reading profiles and for dividing a timed call into per-launch figures.  Host only. */
 int cs_bundle_update_launches(const cs_params* p, int32_t W, int64_t d, int32_t* n);
 int cs_bundle_zero(const cs_params* p, float* T, int32_t W, void* stream);
 int cs_sketch_accumulate_bundle(const cs_params* p, float* T, int32_t W,

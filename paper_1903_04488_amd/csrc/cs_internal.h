@@ -68,15 +68,15 @@ bool lds_table_applies(const cs_params* p, int64_t d);   // the update of a bund
 // Walk-order update of a worker bundle T = float[ceil(W/8)][r][c][8] (cs_walk.hip).
 bool walk_applies(const cs_params* p, int64_t d);
 // fold = true: T is one table float[r][c] and receives the sum over the W workers
-// (all_rows_listed(p, d) must hold for launch_accumulate_walk, anyc_visits_apply for the other)
+// (all_rows_listed(p, d) must hold for launch_accumulate_walk, anyc_update_applies for the other).
+// launches, here and below: kernel launches are added up there instead of made (T, g_w unused)
 bool all_rows_listed(const cs_params* p, int64_t d);
 int launch_accumulate_walk(const cs_params* p, float* T, int W, const float* const* g_w,
-                           int64_t d, int64_t i0, float scale, bool fold, hipStream_t stream);
-int count_accumulate_walk_launches(const cs_params* p, int W, int64_t d);
+                           int64_t d, int64_t i0, float scale, bool fold, hipStream_t stream, int* launches = nullptr);
 // one vector along visit lists, any column count (one_applies(p, d) must hold); S = float[r][c][cell_floats]
 bool one_applies(const cs_params* p, int64_t d);
 int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const float* g, int64_t d,
-                          int64_t i0, float scale, hipStream_t stream);
+                          int64_t i0, float scale, hipStream_t stream, int* launches = nullptr);
 // The update along visit lists into a workspace of running sums, one group of workers at a time, and what lies where
 // in it: row j's sums [pieces][piece_floats], piece_floats = residues (rounded up to whole wavefronts) x running sums x
 // lanes of a walker.
@@ -101,8 +101,7 @@ bool anyc_update_applies(const cs_params* p, int64_t d, int W);
 bool anyc_visits_serve_query(const cs_params* p, int64_t d);
 bool anyc_query_needs_scratch(const cs_params* p, int64_t d);    // ... and is the only form for this length
 int launch_accumulate_anyc(const cs_params* p, float* T, int W, const float* const* g_w,
-                           int64_t d, int64_t i0, float scale, bool fold, hipStream_t stream);
-int count_accumulate_anyc_launches(const cs_params* p, int W);
+                           int64_t d, int64_t i0, float scale, bool fold, hipStream_t stream, int* launches = nullptr);
 int launch_estimate_anyc(const cs_params* p, const float* S, int64_t d, int64_t i0, float* est,
                          float* rows, uint64_t* hist, hipStream_t stream);
 bool walk_takes_median(const cs_params* p, int64_t d);            // fuse_last is the faster way

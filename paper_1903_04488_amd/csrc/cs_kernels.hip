@@ -960,10 +960,11 @@ extern "C" int cs_sketch_accumulate_sum(const cs_params* p, float* S, int32_t W,
 
 extern "C" int cs_bundle_update_launches(const cs_params* p, int32_t W, int64_t d, int32_t* n) {
     if (!bundle_ok(p, W) || d < 0 || !n) return CS_EINVAL;
-    if (d == 0) { *n = 0; return CS_OK; }
-    if (walk_applies(p, d)) { *n = count_accumulate_walk_launches(p, W, d); return CS_OK; }
-    if (anyc_update_applies(p, d, W)) { *n = count_accumulate_anyc_launches(p, W); return CS_OK; }
-    *n = (W + kMaxBatch - 1) / kMaxBatch;
+    *n = 0;
+    if (d == 0) return CS_OK;
+    if (walk_applies(p, d)) return launch_accumulate_walk(p, nullptr, W, nullptr, d, 0, 1.0f, false, nullptr, n);
+    if (anyc_update_applies(p, d, W)) return launch_accumulate_anyc(p, nullptr, W, nullptr, d, 0, 1.0f, false, nullptr, n);
+    *n = static_cast<int32_t>((static_cast<int64_t>(W) + kMaxBatch - 1) / kMaxBatch);
     return CS_OK;
 }
 

@@ -1475,23 +1475,23 @@ bool anyc_query_needs_scratch(const cs_params* p, int64_t d) {
     return anyc_visits_serve_query(p, d) && d * static_cast<int64_t>(p->r - 1) >= (static_cast<int64_t>(1) << 26);
 }
 
-// (rows of both kinds that share a launch count once for each kind)
-int count_accumulate_anyc_launches(const cs_params* p, int W) {
-    int per_group = 0;
-    for_each_anyc_launch(p, p->r, [&](const uint32_t*, int, uint32_t) { ++per_group; return CS_OK; });
-    return per_group * ((W + kGroup - 1) / kGroup);
-}
-
 // Per group of 8 workers one launch for up to kAnycRowsPerLaunch rows: every row has its own
 // visiting order, so the group's vectors are read once per row (where the direct form reads them
 // once in all but sends d requests per row to the atomic unit, which is what bounds it); rows
 // that share a launch overlap their serial chains of visits and have one tail.
 int launch_accumulate_anyc(const cs_params* p, float* T, int W, const float* const* g_w,
-                           int64_t d, int64_t i0, float scale, bool fold, hipStream_t stream) {
+                           int64_t d, int64_t i0, float scale, bool fold, hipStream_t stream, int* launches) {
     const size_t row_floats = static_cast<size_t>(p->c) * kGroup;
     const int at_once = groups_at_once(p, d, kAnycGroups);
     for (int w0 = 0, nw; w0 < W; w0 += nw) {
         nw = workers_of_launch(p, d, W - w0, at_once);
+        const bool one = nw == 1 && one_applies(p, d);
+        if (launches) {
+            if (one) launch_accumulate_one(p, nullptr, kGroup, nullptr, d, i0, scale, stream, launches);
+            else for_each_anyc_launch(p, p->r, [&](const uint32_t*, int, uint32_t) { ++*launches; return CS_OK; },
+                                      nw > kGroup ? kAnycRowsOfGroups : kAnycRowsPerLaunch, true);
+            continue;
+        }
         float* Tg = fold ? T : T + static_cast<size_t>(w0 / kGroup) * p->r * row_floats;
         if (nw > kGroup) {
             VisitWorkersOf<kAnycGroups> vw{};
@@ -1518,7 +1518,7 @@ int launch_accumulate_anyc(const cs_params* p, float* T, int W, const float* con
             if (rc != CS_OK) return rc;
             continue;
         }
-        if (nw == 1 && one_applies(p, d)) {
+        if (one) {
             const int rc = launch_accumulate_one(p, Tg, fold ? 1 : kGroup, g_w[w0], d, i0, scale, stream);
             if (rc != CS_OK) return rc;
             continue;
@@ -1548,17 +1548,6 @@ bool walk_applies(const cs_params* p, int64_t d) {
     for (uint32_t j = 0; j < p->r; ++j)
         if (p->plan[j].Dw <= 1) return false;
     return true;
-}
-
-// kernel launches one call of launch_accumulate_walk makes, a group at a time (same grouping as below)
-int count_accumulate_walk_launches(const cs_params* p, int W, int64_t d) {
-    int listed = 0, per_group = 0;
-    for (uint32_t j = 0; j < p->r; ++j) {
-        if (visits_apply(p, j, d)) ++listed;
-        else ++per_group;
-    }
-    const int launches = (listed + kRowsPerLaunch - 1) / kRowsPerLaunch + (per_group > 0 ? 1 : 0);
-    return launches * ((W + kGroup - 1) / kGroup);
 }
 
 // every row of the sketch has a visit list for vectors of length d (what the folded form of
@@ -1608,7 +1597,7 @@ int launch_one(LIST& rows, int n, const float* g, float* S, uint32_t c, int cell
 
 // S = float[r][c][cell_floats]: the table itself (1) or one worker's slot of a bundle (kGroup)
 int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const float* g, int64_t d,
-                          int64_t i0, float scale, hipStream_t stream) {
+                          int64_t i0, float scale, hipStream_t stream, int* launches) {
     auto cut = [&](auto& rows, int n) {                // the chains of n rows into pieces
         double requests[kRowsPerLaunch];
         for (int q = 0; q < n; ++q) requests[q] = 1.2 * static_cast<double>(rows.row[q].gmax);
@@ -1617,6 +1606,10 @@ int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const f
     };
     if (!p->c_pow2)
         return for_each_anyc_launch(p, p->r, [&](const uint32_t* js, int n, uint32_t omega) {
+            if (launches) {
+                ++*launches;
+                return static_cast<int>(CS_OK);
+            }
             VisitGapsRows rows{};
             for (int q = 0; q < n; ++q) fill_visit_gaps(p, js[q], rows.row[q]);
             cut(rows, n);
@@ -1774,16 +1767,20 @@ int launch_accumulate_sums(const cs_params* p, float* sums, uint64_t sums_floats
 // fold: T is one table float[r][c] that receives the sum over all W workers (all_rows_listed
 // must hold); otherwise T is the bundle and every worker has its own slot.
 int launch_accumulate_walk(const cs_params* p, float* T, int W, const float* const* g_w,
-                           int64_t d, int64_t i0, float scale, bool fold, hipStream_t stream) {
+                           int64_t d, int64_t i0, float scale, bool fold, hipStream_t stream, int* launches) {
     if (fold && !all_rows_listed(p, d)) return CS_EINVAL;
     const size_t row_floats = static_cast<size_t>(p->c) * kGroup;
-    bool one = W % kGroup == 1 && one_applies(p, d);   // a group of one worker: a single vector
-    for (uint32_t j = 0; j < p->r; ++j) one = one && visits_apply(p, j, d, fold);
-    bool listed_all = true;
-    for (uint32_t j = 0; j < p->r; ++j) listed_all = listed_all && visits_apply(p, j, d, fold);
+    uint32_t along_lists = 0;
+    for (uint32_t j = 0; j < p->r; ++j) along_lists += visits_apply(p, j, d, fold) ? 1 : 0;
+    const bool listed_all = along_lists == p->r;
+    const bool one = W % kGroup == 1 && listed_all && one_applies(p, d);   // a group of one worker: a single vector
     const int at_once = listed_all ? groups_at_once(p, d) : 1;
     for (int w0 = 0, nw; w0 < W; w0 += nw) {
         nw = workers_of_launch(p, d, W - w0, at_once);
+        if (launches) {                                // (one vector: as many launches of as many rows)
+            *launches += static_cast<int>(along_lists + kRowsPerLaunch - 1) / kRowsPerLaunch + (listed_all ? 0 : 1);
+            continue;
+        }
         float* Tg = fold ? T : T + static_cast<size_t>(w0 / kGroup) * p->r * row_floats;
         if (nw == 1 && one) {
             const int rc = launch_accumulate_one(p, Tg, fold ? 1 : kGroup, g_w[w0], d, i0, scale, stream);

@@ -221,31 +221,44 @@ def test_vectors_sum_refuses_an_output_that_overlaps_an_input(lib):
 
 
 def test_update_launch_count_follows_the_grouping(lib):
-    """cs_bundle_update_launches: per group of 8 workers one launch for the rows with a visit list
-    (8 rows at most per launch) and one for the rows walked by stride; for other column counts
-    one launch per group and up to 6 rows of equal omega with visit lists, one per 32 workers
-    without; none for an empty vector."""
-    for r, c, seed, d in [(5, 1 << 20, 190304492, 10**8), (5, 1 << 15, 190304489, 1 << 20),
-                          (7, 1 << 19, 190304493, 25_000_000), (15, 1 << 12, 4, 3_000_000)]:
+    """cs_bundle_update_launches: per group of 8 workers, or several groups of short vectors, one launch for the
+    rows with a visit list (8 rows at most per launch) and one for the rows walked by stride; for other column
+    counts one for up to 6 rows (5 with several groups) with visit lists, one per 32 workers without; none for
+    an empty vector."""
+    def listed(p, j):                       # (the prices of these sketches are all below the walk's or above 1.25 times)
+        v = p.visit[j]
+        assert not v.cost_walk <= v.cost <= 1.25 * v.cost_walk
+        return v.K > 0 and v.cost < v.cost_walk
+
+    # W -> launches of the rows' groups of workers: one group at a time, all of them together, or six with a rest of
+    # more than 4 workers shared
+    alone = {1: 1, 8: 1, 9: 2, 32: 4, 250: 32}
+    together = {1: 1, 8: 1, 9: 1, 32: 1, 250: 1, 256: 1, 257: 2, 261: 2}
+    six = {1: 1, 8: 1, 9: 2, 13: 1, 32: 1, 48: 1, 49: 2, 250: 7}
+    for r, c, seed, d, calls in [(5, 1 << 20, 190304492, 10**8, alone), (5, 1 << 15, 190304489, 1 << 20, together),
+                                 (7, 1 << 19, 190304493, 25_000_000, alone), (15, 1 << 12, 4, 3_000_000, six)]:
         p = cs.cs_params_init(r, c, seed, d)
-        listed = sum(1 for j in range(r) if p.visit[j].K > 0 and p.visit[j].cost < p.visit[j].cost_walk)
-        per_group = -(-listed // 8) + (1 if listed < r else 0)
-        for W in (1, 8, 9, 32, 250):
-            assert cs.cs_bundle_update_launches(p, W, d) == per_group * -(-W // 8), (r, c, W)
+        n = sum(listed(p, j) for j in range(r))
+        if n < r:
+            calls = {W: -(-W // 8) for W in calls}         # (rows that walk go group by group, and the others with them)
+        per_call = -(-n // 8) + (1 if n < r else 0)
+        for W, times in calls.items():
+            assert cs.cs_bundle_update_launches(p, W, d) == per_call * times, (r, c, W)
         assert cs.cs_bundle_update_launches(p, 8, 0) == 0
         walk = binding.CsParams.from_buffer_copy(p)
         walk.flags = binding.CS_FLAG_NO_VISIT_LIST
         assert cs.cs_bundle_update_launches(walk, 16, d) == 2
-    # a column count that is not a power of two: per group of 8 workers one launch for up to 6 rows
-    # that keep the same number of running sums (omega), along the rows' visit lists; one launch
-    # per 32 workers without them
-    for r in (5, 15):
-        p = cs.cs_params_init(r, 180_000, 1, 6_500_000)
+    # a column count that is not a power of two: up to 6 rows in a launch, more than that by the number of running
+    # sums they keep (omega); a single vector, that of the last group too, always so; one launch per 32 workers
+    # without lists
+    for r, d in ((5, 6_500_000), (5, 30_000_000), (15, 6_500_000)):
+        p = cs.cs_params_init(r, 180_000, 1, d)
         assert all(p.anyc[j].K > 0 for j in range(r))
-        per_group = sum(-(-sum(1 for j in range(r) if p.anyc[j].omega == omega) // 6) for omega in (1, 2))
-        assert 1 <= per_group <= (2 if r == 5 else 4)
-        for W, groups in ((1, 1), (8, 1), (9, 2), (100, 13)):
-            assert cs.cs_bundle_update_launches(p, W, 6_500_000) == per_group * groups
+        by_kind = sum(-(-sum(1 for j in range(r) if p.anyc[j].omega == omega) // 6) for omega in (1, 2))
+        assert 1 <= by_kind <= (2 if r == 5 else 4)
+        groups = 1 if r == 5 else by_kind
+        for W, n in ((1, by_kind), (8, groups), (9, groups + by_kind), (100, 3 * groups if d * r < 4e7 else 13 * groups)):
+            assert cs.cs_bundle_update_launches(p, W, d) == n, (r, d, W)
     p = cs.cs_params_init(5, 180_000, 1, 6_500_000)
     p.flags = binding.CS_FLAG_NO_VISIT_LIST
     for W, n in ((1, 1), (32, 1), (33, 2), (100, 4)):
