@@ -379,14 +379,16 @@ struct ListArgs {
 };
 
 // L lanes of a cell (8 to 64) share out its coordinates; `slices` wavefronts share out the groups of 8 workers.
-// FOLD (S_t alone): the workers are summed coordinate by coordinate, in binary64 and rounded once, before a cell is: values
-// that cancel between workers leave no rounding of their own size in it.  The slices share out a cell's coordinates too.
+// SHARES > 0 (S_t alone): the workers are summed coordinate by coordinate, in binary64 and rounded once, before a cell is: values
+// that cancel between workers leave no rounding of their own size in it.  The slices share out a cell's coordinates too, and
+// where there are more lanes than coordinates, SHARES lanes (1 or 4) a coordinate's workers.
 // us, sums of every worker's cell / of the coordinates first (this) / a launch for the workers' sum more: 5 x 40, d = 784, 4
-// workers 3.9 / 3.3 / 5.6, 100 workers 7.7 / 6.6 / 10.7; 5 x 64, 5000, 32 workers 7.0 / 6.4 / 7.2; 3 x 33, 2000 (99 wavefronts that
-// each wait for 100 loads), 100 workers 8.7 / 13.0 / 10.7.
-template <int L, bool FOLD>
+// workers 3.9 / 3.3 / 5.6, 100 workers 7.7 / 5.5 / 10.7; 5 x 64, 5000, 32 workers 7.0 / 6.4 / 7.2 (8.4 with one slice); 3 x 33,
+// 2000, 100 workers 8.8 / 7.1 / 10.7 (13.0 with one lane a coordinate).
+template <int L, int SHARES>
 __global__ void __launch_bounds__(kBlock) k_sum_lists(ListArgs a) {
     static_assert(L >= CS_BUNDLE_GROUP, "a lane per worker of a group");
+    constexpr bool FOLD = SHARES > 0;
     constexpr int kCells = 64 / L, kWaves = kBlock / 64;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -416,12 +418,14 @@ __global__ void __launch_bounds__(kBlock) k_sum_lists(ListArgs a) {
     const int groups = (a.W + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP;
     if constexpr (FOLD) {
         float v = 0.0f;
-        for (uint32_t t = slice * L + part; t < n; t += a.slices * L) {
+        constexpr int kStep = L / SHARES;
+        const int share = part % SHARES, w0 = share * a.W / SHARES, w1 = (share + 1) * a.W / SHARES;
+        for (uint32_t t = slice * kStep + part / SHARES; t < n; t += a.slices * kStep) {
             const uint32_t e = entry[lo + t];
             if (e >> 1 >= a.d) continue;               // (lists of another sketch)
             double sum = 0.0;
-            int w = 0;
-            for (; w + CS_BUNDLE_GROUP <= a.W; w += CS_BUNDLE_GROUP) {
+            int w = w0;
+            for (; w + CS_BUNDLE_GROUP <= w1; w += CS_BUNDLE_GROUP) {
                 float x[CS_BUNDLE_GROUP];
 #pragma unroll
                 for (int q = 0; q < CS_BUNDLE_GROUP; ++q) x[q] = a.g[w + q][e >> 1];
@@ -429,11 +433,13 @@ __global__ void __launch_bounds__(kBlock) k_sum_lists(ListArgs a) {
                 for (int q = 0; q < CS_BUNDLE_GROUP; ++q) sum += static_cast<double>(x[q]);
             }
 #pragma unroll 4
-            for (; w < a.W; ++w) sum += static_cast<double>(a.g[w][e >> 1]);
+            for (; w < w1; ++w) sum += static_cast<double>(a.g[w][e >> 1]);
+#pragma unroll
+            for (int off = 1; off < SHARES; off *= 2) sum += __shfl_xor(sum, off);       // (lanes of one coordinate: in step)
             v += apply_sign(static_cast<float>(static_cast<double>(a.alpha) * sum), e << 31);
         }
 #pragma unroll
-        for (int off = 1; off < L; off *= 2) v += __shfl_xor(v, off);
+        for (int off = SHARES; off < L; off *= 2) v += __shfl_xor(v, off);
         total = static_cast<double>(v);
     } else
     for (int g = slice; g < groups; g += a.slices) {
@@ -699,8 +705,13 @@ extern "C" int cs_bundle_sketch_lists(const cs_params* p, float* T, int32_t W, c
     const double want = 65536.0 / (static_cast<double>(p->r) * p->c * a.slices), each = static_cast<double>(d) / (8.0 * p->c);
     int L = 8;
     while (L < 64 && L < (want > each ? want : each)) L *= 2;
-    // (FOLD: up to four wavefronts of a cell while it has coordinates for them; 5 x 64, 5000, 32 workers 8.4 -> 6.4 us)
-    while (fold && L == 64 && a.slices < 4 && 64.0 * a.slices < want && 64.0 * a.slices * p->c < static_cast<double>(d)) a.slices *= 2;
+    int shares = fold ? 1 : 0;
+    if (fold && L == 64) {                             // up to four wavefronts of a cell, where they have work
+        const bool idle = static_cast<double>(d) <= 64.0 * p->c;    // more lanes than coordinates: with many workers four for each
+        while (a.slices < 4 && 64.0 * a.slices < want && (idle ? W >= 16 : 64.0 * a.slices * p->c < static_cast<double>(d)))
+            a.slices *= 2;
+        if (idle && a.slices == 4) shares = 4;
+    }
     const uint32_t cells = kBlock / L / a.slices;      // of a workgroup
     hipStream_t s = static_cast<hipStream_t>(stream);
     constexpr uint32_t kListBlocks = 1u << 22;         // workgroups of a launch: one of 2^32 threads is refused
@@ -709,8 +720,10 @@ extern "C" int cs_bundle_sketch_lists(const cs_params* p, float* T, int32_t W, c
         const dim3 grid(blocks < kListBlocks ? blocks : kListBlocks, p->r);
         auto launch = [&](auto lanes) {
             constexpr int N = decltype(lanes)::value;
-            if (fold) k_sum_lists<N, true><<<grid, kBlock, 0, s>>>(a);
-            else k_sum_lists<N, false><<<grid, kBlock, 0, s>>>(a);
+            if constexpr (N == 64)
+                if (shares == 4) return k_sum_lists<N, 4><<<grid, kBlock, 0, s>>>(a);
+            if (shares) k_sum_lists<N, 1><<<grid, kBlock, 0, s>>>(a);
+            else k_sum_lists<N, 0><<<grid, kBlock, 0, s>>>(a);
         };
         switch (L) {
             case 8: launch(std::integral_constant<int, 8>()); break;
