@@ -550,8 +550,10 @@ k_topk_small(const float* __restrict__ est, uint32_t d, SelOut out, KEY kf) {
 
 // Query and selection of a short vector by the workgroup that selects: estimates go to est and their keys straight into LDS.
 // A step that short waits for the host, 6 us a call.  The hashes, 2 r per coordinate, are then one CU's work, so that r d is
-// bounded by kQueryChooseHashes where the kernels alone take as long either way: us, two launches / one, from a graph: 3 rows,
-// d = 900 11.5 / 10.6; 7, 784 13.0 / 13.0; 5, 2000 13.0 / 13.4; 5, 3276 14.1 / 16.7; 15, 800 18.4 / 22.4.
+// bounded by kQueryChooseHashes, where the kernels alone take as long either way: us from a graph, two launches / one, at 6144 (in
+// brackets at 3000 to 4500), 40 columns: 1 row 14.0 / 14.0 (11.0 / 10.1); 3 10.8 / 11.1 (10.4 / 9.9); 5 11.0 / 10.5; 7 11.5 / 11.2;
+// 9 12.3 / 12.4 (12.2 / 10.5); 11 13.2 / 13.4; 13 15.8 / 12.3; 15 16.0 / 13.8; 64 columns, no division: 0.4 to 2 less for the one.
+// Beyond: 5 rows, d = 2000 13.0 / 13.4, 3276 14.1 / 16.7; 15, 800 18.4 / 22.4.
 template <int R, bool POW2>
 __global__ void __launch_bounds__(kSelBlock)
 k_estimate_choose(KParams p, const float* __restrict__ S, uint32_t d, float* est, SelOut out) {
