@@ -130,8 +130,8 @@ void plan_walk(cs_row_plan* rp, uint64_t a, uint64_t as, uint32_t c, bool pow2, 
 // chains by its own prices (cs_walk.hip: 700 ns with RUN = 8, 1300 with 16, 500 for one vector).
 // It prices every visit of a list for every walker.  The kernels pass over the visits that a walker takes no part in without
 // a turn, so lists with short gaps beside long ones are priced too high: one row of 7 x 2^19 over 25 million (51 visits,
-// gaps 7628, 529 875 and 1 613 543) comes out at 308 us for 307 of the stride walk and takes that, 210 us a launch,
-// where a row along its list takes 138.
+// gaps 7628, 529 875 and 1 613 543) comes out at 308 us for 307 of the stride walk, which takes 210 us in a launch
+// of its own where a row along its list takes 138; visits_apply (cs_walk.hip) takes lists up to a quarter above the walk.
 double update_time_ns(double visits, double residues, double requests, double d, bool shared) {
     const double kVisitNs = 900.0, kResidentWaves = 4096.0;
     const double kBytesPerNs = 4600.0, kRequestsPerNs = 24.0;

@@ -77,8 +77,8 @@ int launch_accumulate_walk(const cs_params* p, float* T, int W, const float* con
 bool one_applies(const cs_params* p, int64_t d);
 int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const float* g, int64_t d,
                           int64_t i0, float scale, hipStream_t stream, int* launches = nullptr);
-// The update along visit lists into a workspace of running sums, one group of workers at a time, and what lies where
-// in it: row j's sums [pieces][piece_floats], piece_floats = residues (rounded up to whole wavefronts) x running sums x
+// The update along visit lists into a workspace of running sums, one group of workers after the other or, of short
+// vectors, several in a launch, and what lies where in a group's: row j's sums [pieces][piece_floats], piece_floats = residues (rounded up to whole wavefronts) x running sums x
 // lanes of a walker.
 struct SumsRow {
     uint64_t at, residues, piece_floats;

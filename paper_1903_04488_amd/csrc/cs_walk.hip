@@ -1003,7 +1003,7 @@ uint32_t most_steps(const LIST& rows, int nrows) {
     return most;
 }
 
-// one launch: rows that all have at most ncell running sums, of one group of workers
+// one launch: rows that all have at most ncell running sums, of the groups of workers that `a` holds
 template <int WL, int RUN, int NWAVE, typename LIST>
 int launch_visits_run(LIST& rows, const WorkersBeside<LIST>& a, int nrows, uint32_t ncell, hipStream_t stream) {
     const dim3 grid(visits_grid<WL, RUN, NWAVE>(rows, nrows), (a.nw + kGroup - 1) / kGroup), block(64 * NWAVE);

@@ -131,8 +131,8 @@ class HotPath:
         self._sums_for = self.fold_workers, W, self.d
 
     def _lists(self):
-        """the parameters as they are now, byte for byte, up to the visit lists of the last row (what lies behind is
-        for column counts that have no index)"""
+        """the parameters as they are now, byte for byte, up to the visit lists of the last row (what lies behind are
+        lists that neither the index, which is for powers of two, nor the cell lists depend on)"""
         n = B.CsParams.visit.offset + self.r * ctypes.sizeof(B.CsVisitPlan)
         return memoryview(self.params).cast("B")[:n].tobytes()
 
