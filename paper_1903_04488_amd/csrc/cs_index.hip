@@ -615,11 +615,12 @@ extern "C" int cs_bundle_sketch(const cs_params* p, float* T, int32_t W, const f
                                 ws_bytes / sizeof(float), S_t, alpha, S_u, S_v, rho, static_cast<hipStream_t>(stream));
 }
 
-// Where the lists take less time than what else there is, by figures of 1300 shapes; us, others / lists.  Lists take 4 us,
-// then three things one after the other:
+// Where the lists take less time than what else there is, by figures of 1300 shapes; us, others / lists.  Lists take 4 us
+// and three things that partly overlap (the root of their squares comes closest: it picks the faster way for all but 9 of 509
+// shapes that have no visit lists, within 4 %):
 //  * values: r d W at 250 G/s while the vectors lie in L2 (d W up to a million; 200 at 1.4, 180 at 4, 110 at 8 million);
 //  * a cell's chain: 64 lanes and two entries of each at once, so that a cell of n coordinates is n / 128 rounds of a load
-//    that waits for another, 0.6 us each, 0.95 with 8 workers, and 0.5 more where vectors and lists are more than L2 holds;
+//    that waits for another, 0.6 us each, 1.1 with 8 workers, and 1.0 and 2.2 where vectors and lists are more than L2 holds;
 //  * the cells of a wide table, 45 ps each and group of workers (14 in a launch that clears or merges).
 // Against
 //  * visit lists of a power of two of columns, 13 to 16 us and 1.3 a million values, 2.7 with many groups of workers: 7 x 512,
@@ -642,7 +643,12 @@ static bool lists_pay(const cs_params* p, int32_t W, int64_t d) {
     const double per_cell = n / c;
     const bool beyond_l2 = n * (workers + r / 4) > 1e6;
     if (vectors > 4e6) return false;
+    const double eight = workers < 8.0 ? workers : 8.0;
+    const double chain = per_cell / 128.0 * (0.55 + 0.07 * eight + (beyond_l2 ? 0.3 + 0.1 * eight : 0.0));
+    const double lists = 4.0 + sqrt(chain * chain + pow(45e-6 * cells, 2) + pow(values / 250e3, 2));
+    const double direct = 5.0 + 4.0 * r + 2e-6 * cells + r * n * (c < 250.0 ? 8.0 / c : 0.032) * 1e-3;   // one vector, hash by hash
     if (walk_applies(p, d)) {
+        if (W == 0 && c > n) return lists <= direct;   // (the lattice form is no better there)
         if (W == 0 ? cells > 1.5e5 : c > 4.0 * n || per_cell > (beyond_l2 ? 1600.0 : 6400.0)) return false;
         return values <= (p->r > 8 ? (W > 16 ? 7e6 : 5e6) : W > 16 ? 5.5e6 : 3e6);
     }
@@ -650,12 +656,10 @@ static bool lists_pay(const cs_params* p, int32_t W, int64_t d) {
         if (W > 0 && per_cell > (p->r > 5 ? 8000.0 : 6400.0)) return false;
         return vectors <= 1.2e6 && values <= (p->r > 8 ? 1e7 : 5e6);
     }
-    const double round = 0.55 + 0.05 * (workers < 8.0 ? workers : 8.0) + (beyond_l2 ? 0.5 : 0.0);
-    const double lists = 4.0 + 45e-6 * cells + per_cell / 128.0 * round + values / 250e3;
-    double others;
-    if (W == 0) others = 5.0 + 4.0 * r + 2e-6 * cells + r * n * (c < 250.0 ? 8.0 / c : 0.032) * 1e-3;
-    else if (lds_table_applies(p, d)) others = 10.0 + r + r * n * (5.0 + 5.0 * workers) * 1e-6;
-    else others = 10.0 + 14e-6 * cells + cells / c * n * (c < 208.0 ? 10.0 / c : 0.048) * 1e-3;
+    double others = direct;
+    if (W > 0 && lds_table_applies(p, d)) others = 10.0 + r + r * n * (5.0 + 5.0 * workers) * 1e-6;
+    else if (W > 0)                                    // (a launch for every 32 workers)
+        others = 6.0 + 4.0 * ceil(workers / 32.0) + 14e-6 * cells + cells / c * n * (c < 208.0 ? 10.0 / c : 0.048) * 1e-3;
     return lists <= others;
 }
 
@@ -706,11 +710,11 @@ extern "C" int cs_bundle_sketch_lists(const cs_params* p, float* T, int32_t W, c
     int L = 8;
     while (L < 64 && L < (want > each ? want : each)) L *= 2;
     int shares = fold ? 1 : 0;
-    if (fold && L == 64) {                             // up to four wavefronts of a cell, where they have work
-        const bool idle = static_cast<double>(d) <= 64.0 * p->c;    // more lanes than coordinates: with many workers four for each
-        while (a.slices < 4 && 64.0 * a.slices < want && (idle ? W >= 16 : 64.0 * a.slices * p->c < static_cast<double>(d)))
-            a.slices *= 2;
-        if (idle && a.slices == 4) shares = 4;
+    if (fold) {
+        const double per_cell = static_cast<double>(d) / p->c;
+        const bool idle = per_cell <= 64.0;            // up to four wavefronts of a cell, where they have work:
+        while (L == 64 && a.slices < 4 && 64.0 * a.slices < want && (idle ? W >= 16 : 64.0 * a.slices < per_cell)) a.slices *= 2;
+        if (W >= 16 && (a.slices == 4 ? idle : 4.0 * per_cell <= L)) shares = 4;     // four lanes for each coordinate
     }
     const uint32_t cells = kBlock / L / a.slices;      // of a workgroup
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -720,9 +724,8 @@ extern "C" int cs_bundle_sketch_lists(const cs_params* p, float* T, int32_t W, c
         const dim3 grid(blocks < kListBlocks ? blocks : kListBlocks, p->r);
         auto launch = [&](auto lanes) {
             constexpr int N = decltype(lanes)::value;
-            if constexpr (N == 64)
-                if (shares == 4) return k_sum_lists<N, 4><<<grid, kBlock, 0, s>>>(a);
-            if (shares) k_sum_lists<N, 1><<<grid, kBlock, 0, s>>>(a);
+            if (shares == 4) k_sum_lists<N, 4><<<grid, kBlock, 0, s>>>(a);
+            else if (shares) k_sum_lists<N, 1><<<grid, kBlock, 0, s>>>(a);
             else k_sum_lists<N, 0><<<grid, kBlock, 0, s>>>(a);
         };
         switch (L) {
