@@ -58,7 +58,9 @@ def test_tables_merge_and_momentum(r, c, d, W):
     np.testing.assert_array_equal(T.cpu().numpy().reshape(bundle.shape), bundle)
 
 
-@pytest.mark.parametrize("r,c,d", [(5, 40, 784), (3, 33, 2001), (3, 7, 5), (5, 1000, 5003), (3, 32, 20_011), (9, 4096, 50_001)])
+# cells with fewer coordinates than lanes and with more, of one and of several wavefronts; with 16 workers four lanes a coordinate
+@pytest.mark.parametrize("r,c,d", [(5, 40, 784), (3, 33, 2001), (3, 7, 5), (5, 1000, 5003), (5, 1000, 3001), (3, 1311, 656), (3, 32, 20_011),
+                                   (9, 4096, 50_001)])
 @pytest.mark.parametrize("W", [2, 4, 7, 8, 9, 17, 256])
 def test_folded_workers_are_summed_before_a_cell_is(r, c, d, W):
     """without worker tables: a cell is off by roundings of the workers' mean, also where the workers all but cancel"""
