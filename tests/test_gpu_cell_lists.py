@@ -126,17 +126,19 @@ def test_more_columns_than_a_launch_takes():
 
 @pytest.mark.parametrize("kind", ["step", "fold", "fold-many", "dense", "graph"])
 def test_a_path_of_short_vectors_goes_by_its_lists(kind):
-    """the same state and selection as a path that is given none"""
-    r, c, d, W, k = 5, 40, 784, 40 if kind == "fold-many" else 4, 2
+    """the same state and selection as a path that is given none, whose atomic additions come in any order: whole numbers, powers
+    of two of workers and halves of momentum keep every sum of the three steps a multiple of 2^-8 below 2^15, so that none is
+    rounded (with normal values a cell of 500 coordinates and a large one was off by 2e-4 in one run of many)"""
+    r, c, d, W, k = 5, 40, 784, 32 if kind == "fold-many" else 4, 2
     d = 20_003 if kind == "fold-many" else d
-    gs = [torch.randn(d, generator=torch.Generator().manual_seed(w)).to(DEV) for w in range(W)]
+    gs = [torch.randint(-4, 5, (d,), generator=torch.Generator().manual_seed(w)).float().to(DEV) for w in range(W)]
     for g in gs:
-        g[5], g[300] = 40.0, -50.0
+        g[5], g[300] = 400.0, -500.0
     paths = []
     for lists in (True, False):
         cls = DenseStatePath if kind == "dense" else HotPath
         fold = {"fold_workers": True} if kind.startswith("fold") else {}
-        path = cls(d, W, r, c, k, 3, rho=0.9, **fold)
+        path = cls(d, W, r, c, k, 3, rho=0.5, **fold)
         assert path._cell_lists and path._index is not None
         if not lists:
             path._index = None
@@ -145,10 +147,10 @@ def test_a_path_of_short_vectors_goes_by_its_lists(kind):
             step()
         paths.append(path)
     a, b = paths
-    torch.testing.assert_close(a.S_t, b.S_t, rtol=1e-5, atol=1e-5 * float(b.S_t.std()))
-    assert a.idx.tolist() == b.idx.tolist()
+    assert torch.equal(a.S_t, b.S_t) and float(a.S_t.abs().max()) < 2.0 ** 15
+    assert a.idx.tolist() == b.idx.tolist() and torch.equal(a.x, b.x)
     if a.S_v is not None:
-        torch.testing.assert_close(a.S_v, b.S_v, rtol=1e-5, atol=1e-4)
+        assert torch.equal(a.S_v, b.S_v) and torch.equal(a.S_u, b.S_u) and float(a.S_v.abs().max()) < 2.0 ** 15
     # another sketch: not by these lists
     p2 = cs.cs_params_init(r, c, 4, d)
     for path in paths:
@@ -156,4 +158,4 @@ def test_a_path_of_short_vectors_goes_by_its_lists(kind):
         path.accumulate(gs if kind != "dense" else path.v_w)
         if not kind.startswith("fold"):
             path.merge()
-    torch.testing.assert_close(a.S_t, b.S_t, rtol=1e-5, atol=1e-4)
+    assert torch.equal(a.S_t, b.S_t)
