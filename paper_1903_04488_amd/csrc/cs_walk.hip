@@ -1009,7 +1009,7 @@ int launch_visits_run(LIST& rows, const WorkersBeside<LIST>& a, int nrows, uint3
     const dim3 grid(visits_grid<WL, RUN, NWAVE>(rows, nrows), (a.nw + kGroup - 1) / kGroup), block(64 * NWAVE);
     const size_t lds = most_steps(rows, nrows) * sizeof(uint4);
     constexpr bool pow2 = std::is_same<LIST, VisitRows>::value;
-    constexpr bool partial = pow2 && WL > 1;           // running sums: power-of-two columns (and one vector: k_accumulate_one)
+    constexpr bool partial = pow2 && WL > 1;           // running sums: power-of-two columns
     if (!(a.sums ? partial : a.T != nullptr)) return CS_EINVAL;
     auto launch = [&](auto nc) {
         constexpr int NC = decltype(nc)::value;
@@ -1028,6 +1028,360 @@ int launch_visits_run(LIST& rows, const WorkersBeside<LIST>& a, int nrows, uint3
     return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
 }
 
+// ---------------------------------------------------------------------------------------
+// The update of one vector (one worker, or the workers' vectors summed beforehand), or of a few that the
+// memory-side cache holds together, along visit lists: a wavefront per vector.
+//
+// Nothing is shared between the lanes of a wavefront, so a lane owns 4 neighbouring residues: a visit
+// is one 16-byte load, 8 comparisons and 8 masked additions in registers, and a
+// wavefront reads 1 KB of contiguous addresses.  Loads of the next kOneAhead visits are in flight; every
+// request is one whole load, at the vector's last four values where its own would lie beyond, so that
+// the wait for a visit's values counts the loads behind them.  The sums of a residue that the present visits do not add to wait
+// in LDS.  A workgroup has SETS sets of WL wavefronts, of which each takes another vector over the same residues; at the end the
+// sums of all WL vectors, which lie in neighbouring cells of the bundle, are brought to
+// neighbouring lanes, so that they leave as one request (an aligned 64-byte block touched by an
+// instruction is one).  The workgroup shares one table of visits; launches of one vector with fewer than
+// kOneFewWaves wavefronts have workgroups of one, which spread them over more CUs (us, 4 / 1: 21 wavefronts, 3 x 512,
+// d = 203 680 16.9 / 12.8; 138, 5 x 707, 326 476 41.8 / 29.2; 269, 5 x 2048, 304 889 17.3 / 14.7; 338, 5 x 2401, 224 320
+// 24.8 / 26.0; 642, 5 x 2641, 747 318 36.7 / 41.7; two launches of 16 000, 15 x 131 072, 31 M 536 / 572).
+// Measured, one vector (update alone, in us; with two 61-bit states per coordinate and a load for every visit of the list, taken
+// part in or not -> now): d = 73 M, 5 x 2^20 468 -> 326; d = 25 M, 5 x 2^19 176 -> 137; d = 11 M, 5 x 2^18 102 -> 74;
+// d = 73 M, 5 x 180 000 492 -> 445; with waits for one visit's values at a time 338 -> 325, 126 -> 122, 73 -> 72, 434 -> 435 (of
+// another machine).  Bound: the requests at the end (without them 216, 92, 43 and 227 us, which
+// is the five reads, 1.46 GB at 73 M by the counters too, at 6.8 TB/s; with them 1.63 GB at 4.8); 2 and 4 loads ahead and 2
+// and 8 wavefronts per workgroup: within 4 % either way.
+// Several vectors: against k_accumulate_visits, whose lanes are walkers times workers, the comparisons are made once per vector
+// instead of once per walker, but no value goes through LDS, four times as many wavefronts have a quarter of the work
+// each, and 24 of them on a CU have 72 KB of reads in flight instead of 48.  The memory-side cache answers that with 6.4 TB/s for
+// 5.6 (d = 6.5 M, 8 workers, 5 x 2^17: 1.04 GB in 162 us for 185), memory does not: see vectors_pay.
+// ---------------------------------------------------------------------------------------
+constexpr int kOneRun = 4;
+constexpr int kOneAhead = 3;
+constexpr int64_t kOneFewWaves = 300;
+
+// PARTIAL: the sums go to a workspace, [piece][residue][running sum][worker], instead of being added to the table
+// (cs_index.hip).
+template <int WL, int SETS, int NC, bool PARTIAL, typename LIST>
+__global__ void __launch_bounds__(64 * WL * SETS)
+k_accumulate_vectors(LIST rows, WorkersBeside<LIST> a) {
+    constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
+    constexpr int SPAN = 64 * kOneRun, kRow = SPAN + 4;
+    const unsigned row = row_of_block(rows);
+    const auto& v = rows.at(row);
+    const uint32_t piece = (blockIdx.x - rows.first[row]) / v.blocks;
+    const uint32_t block = (blockIdx.x - rows.first[row]) % v.blocks;
+    const int lane = threadIdx.x & 63;
+    const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wavefront-uniform
+    const int worker = wq % WL, set = wq / WL;
+    extern __shared__ uint4 steps[];                   // the visits of my piece
+    __shared__ __attribute__((aligned(16))) float sums_lds[SETS][WL][NC][kRow];
+    __shared__ uint32_t first_lds[PARTIAL ? 1 : SETS][SPAN];           // first cell of a residue
+    float (*parked)[kRow] = sums_lds[set][worker];
+    uint32_t* first = first_lds[PARTIAL ? 0 : set];
+    const uint32_t group = blockIdx.y;
+    const int nw = a.nw - static_cast<int>(group) * kGroup < kGroup ? a.nw - static_cast<int>(group) * kGroup : kGroup;
+    const bool live = worker < nw;
+    const gfloat_ptr g = (gfloat_ptr)a.g[group * kGroup + (live ? worker : 0)];
+    const int64_t i0 = a.i0;
+    const uint32_t c = a.c, mask = c - 1u, d = static_cast<uint32_t>(a.d);
+    const Columns col = columns_of<POW2>(c);
+    const float scale = a.scale;
+    const bool fold = a.fold != 0;
+    const uint32_t cell_floats = fold ? 1u : static_cast<uint32_t>(kGroup);
+    uint32_t ncell, omega;                             // running sums, and the values of A mod c that they cover
+    if constexpr (POW2) {
+        ncell = v.ncell;
+        omega = ncell - 1;
+    } else {
+        omega = v.omega;
+        ncell = 2 * omega;
+    }
+    auto cell_of_sum = [&](uint32_t first, uint32_t q) -> uint32_t {
+        if constexpr (POW2) {
+            return (first + q) & mask;
+        } else {
+            const uint32_t x = q < omega ? first + q : first + (q - omega) + (c - v.pc);
+            return x >= c ? x - c : x;
+        }
+    };
+    float* const Tj = PARTIAL ? nullptr : a.T + group * a.table_floats + static_cast<uint64_t>(v.j) * c * cell_floats;
+    const int64_t nwaves = (static_cast<int64_t>(v.gmax) + SPAN - 1) / SPAN;
+    const int64_t nsets = (nwaves + SETS - 1) / SETS;
+    const uint32_t k0 = v.K * piece / v.pieces, k1 = v.K * (piece + 1) / v.pieces;
+    VisitPlaces places;
+    places.init(v);
+    const uint32_t listed = fill_visit_steps<POW2, WL * SETS>(steps, places, v, k0, k1, col, omega);
+    const uint32_t last4 = d - kOneRun;
+
+    // sets of neighbouring wavefronts go to one XCD, as in k_accumulate_visits
+    for (int64_t vi = block; ; vi += v.blocks) {
+        if (visit_round(vi, v.blocks) >= nsets) break;
+        const int64_t wv = visit_set(vi, v.blocks) * SETS + set;
+        const uint32_t wave_res = static_cast<uint32_t>(wv * SPAN);
+        const uint32_t my_res = wave_res + lane * kOneRun;
+        if (live && wv < nwaves) {
+            uint32_t xb[kOneRun], xs[kOneRun];              // top bits of the hashes at my residues
+            uint32_t signs = 0;                             // bit m: the sign of residue m is -1
+            {
+                uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
+                uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res));
+#pragma unroll
+                for (int m = 0; m < kOneRun; ++m) {
+                    xb[m] = top_of(yb);
+                    xs[m] = top_of(ys);
+                    signs |= (sign_flip_of(ys) >> 31) << m;
+                    yb = hash_advance(yb, v.a);
+                    ys = hash_advance(ys, v.as);
+                }
+            }
+            struct Step {                                   // a visit that was requested
+                vec4f x;
+                uint32_t tb, ts, s, w;                      // the step, as in steps[k]
+                uint32_t k;                                 // ~0u for none
+            };
+            VisitCursor cursor(steps, k1 - k0, wave_res, d);
+            auto request = [&](Step& st) {
+                st.k = cursor.next();
+                const uint4 e = steps[st.k == ~0u ? 0u : st.k];
+                st.tb = e.x;
+                st.ts = e.y;
+                st.s = __builtin_amdgcn_readfirstlane(e.z);
+                st.w = __builtin_amdgcn_readfirstlane(e.w);
+                uint32_t at = st.s + my_res;
+                at = at < last4 ? at : last4;
+                st.x = *(gvec4_ptr)(g + at);
+            };
+            // of the residues from wave_res on, how many take part in the visit and exist in the vector (> 0)
+            auto room_of = [&](uint32_t s, uint32_t w) -> uint32_t {
+                const uint32_t in_gap = (w & kGapMask) - wave_res, in_vec = d - s - wave_res;
+                return in_gap < in_vec ? in_gap : in_vec;
+            };
+            // x: four values read at min(s + my_res, last4)  ->  those of my residues, 0 for the missing ones
+            auto cut = [&](vec4f x, uint32_t s, uint32_t room) -> vec4f {
+                const int len = static_cast<int>(room) - lane * kOneRun;
+                const int over = static_cast<int>(s + my_res) - static_cast<int>(last4);
+                const float in[kOneRun] = {x.x, x.y, x.z, x.w};
+                float out[kOneRun];
+#pragma unroll
+                for (int m = 0; m < kOneRun; ++m) {
+                    float val = over <= 0 ? in[m] : 0.0f;
+#pragma unroll
+                    for (int t = m + 1; t < kOneRun; ++t) val = over == t - m ? in[t] : val;
+                    out[m] = m < len ? val : 0.0f;
+                }
+                return vec4f{out[0], out[1], out[2], out[3]};
+            };
+            // sums of the coordinates whose bucket hash did not wrap and of those whose did, for visits with
+            // A mod c = cur; their signs less that of the residue itself
+            float plain[kOneRun], wrapped[kOneRun];
+            uint32_t cur = 0;
+#pragma unroll
+            for (int m = 0; m < kOneRun; ++m) plain[m] = wrapped[m] = 0.0f;
+            auto park = [&](uint32_t q, const float (&x)[kOneRun]) {
+                vec4f u;
+#pragma unroll
+                for (int m = 0; m < kOneRun; ++m) u[m] = x[m];
+                *reinterpret_cast<vec4f*>(&parked[q][lane * kOneRun]) = u;
+            };
+            auto fetch = [&](uint32_t q, float (&x)[kOneRun]) {
+                const vec4f u = *reinterpret_cast<const vec4f*>(&parked[q][lane * kOneRun]);
+#pragma unroll
+                for (int m = 0; m < kOneRun; ++m) x[m] = u[m];
+            };
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+                *reinterpret_cast<vec4f*>(&parked[q][lane * kOneRun]) = vec4f{0.0f, 0.0f, 0.0f, 0.0f};
+            auto move_to = [&](uint32_t q) {                // (neighbouring cells share a sum: power-of-two c)
+                const uint32_t step = POW2 ? 1 : omega;
+                park(cur, plain);
+                park(cur + step, wrapped);
+                fetch(q, plain);
+                fetch(q + step, wrapped);
+                cur = q;
+            };
+            auto add_up = [&](Step& st) {
+                const uint32_t room = room_of(st.s, st.w);
+                vec4f x = st.x;
+                if (room < SPAN) x = cut(x, st.s, room);
+                if (cur != st.w >> 30) move_to(st.w >> 30);
+                uint64_t flips[kOneRun], wraps[kOneRun], unsure = 0;
+#pragma unroll
+                for (int m = 0; m < kOneRun; ++m) {
+                    flips[m] = __builtin_amdgcn_ballot_w64(xs[m] > st.ts);
+                    wraps[m] = __builtin_amdgcn_ballot_w64(xb[m] > st.tb);
+                    unsure |= __builtin_amdgcn_ballot_w64(xb[m] == st.tb) | __builtin_amdgcn_ballot_w64(xs[m] == st.ts);
+                }
+                if (__builtin_expect(unsure != 0, 0)) {
+                    // the lower bits decide: whole hash values against whole thresholds
+                    const uint64_t A = mulmod_p(v.a, st.s), As = mulmod_p(v.as, st.s);
+                    uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
+                    uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res));
+#pragma unroll
+                    for (int m = 0; m < kOneRun; ++m) {
+                        flips[m] = __builtin_amdgcn_ballot_w64(ys > kP61 - As);
+                        wraps[m] = __builtin_amdgcn_ballot_w64(yb > kP61 - A);
+                        yb = hash_advance(yb, v.a);
+                        ys = hash_advance(ys, v.as);
+                    }
+                }
+                const uint64_t odd = (st.w >> 29 & 1u) != 0 ? ~0ull : 0ull;
+#pragma unroll
+                for (int m = 0; m < kOneRun; ++m) {
+                    const float val = __builtin_amdgcn_inverse_ballot_w64(flips[m] ^ odd) ? -x[m] : x[m];
+                    const bool wrap = __builtin_amdgcn_inverse_ballot_w64(wraps[m]);
+                    plain[m] += wrap ? 0.0f : val;
+                    wrapped[m] += wrap ? val : 0.0f;
+                }
+            };
+            Step st[kOneAhead];
+#pragma unroll
+            for (int u = 0; u < kOneAhead; ++u) request(st[u]);
+            // (a buffer is refilled where it was read: moving a value that is still on its way would
+            // wait for it)
+            // (a break from every turn: where the turns meet again before the end is known, the wait for the oldest
+            // values becomes one for all that are on their way)
+            static_assert(kOneAhead == 3, "a turn for each");
+            for (;;) {
+                if (st[0].k == ~0u) break;
+                add_up(st[0]);
+                request(st[0]);
+                if (st[1].k == ~0u) break;
+                add_up(st[1]);
+                request(st[1]);
+                if (st[2].k == ~0u) break;
+                add_up(st[2]);
+                request(st[2]);
+            }
+            park(cur, plain);
+            park(cur + (POW2 ? 1 : omega), wrapped);
+#pragma unroll
+            for (int q = 0; q < NC; ++q) {                  // the signs of the residues
+                float x[kOneRun];
+                fetch(q, x);
+#pragma unroll
+                for (int m = 0; m < kOneRun; ++m) x[m] = apply_sign(x[m], (signs >> m) << 31);
+                park(q, x);
+            }
+        }
+        if constexpr (!PARTIAL) {
+            if (worker == 0) {
+                uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
+#pragma unroll
+                for (int m = 0; m < kOneRun; ++m) {
+                    first[lane * kOneRun + m] = bucket_of<POW2>(yb, col);
+                    yb = hash_advance(yb, v.a);
+                }
+            }
+        }
+        if constexpr (WL > 1) __syncthreads();
+        else __builtin_amdgcn_wave_barrier();
+        if (wv < nwaves) {
+            const uint32_t tid = worker * 64 + lane;
+            if constexpr (PARTIAL) {
+                float* dst = a.sums + group * a.sums_floats + v.at + (static_cast<uint64_t>(piece) * nwaves + wv) * SPAN * ncell * WL;
+                auto write = [&](auto n) {             // (a division by a constant where all sums are used)
+                    for (uint32_t item = tid; item < SPAN * WL * n; item += 64 * WL) {
+                        const uint32_t w = item % WL, t = item / WL;
+                        dst[item] = static_cast<int>(w) < nw ? scale * sums_lds[set][w][t % n][t / n] : 0.0f;
+                    }
+                };
+                if (ncell == NC) write(std::integral_constant<uint32_t, NC>());
+                else write(ncell);
+            } else if (fold) {
+                for (uint32_t item = tid; item < SPAN * NC; item += 64 * WL) {
+                    const uint32_t res = item / NC, q = item % NC;     // (a sum that is not used is 0)
+                    float x[WL];
+#pragma unroll
+                    for (int w = 0; w < WL; ++w) x[w] = w < nw ? sums_lds[set][w][q][res] : 0.0f;
+#pragma unroll
+                    for (int off = 1; off < WL; off <<= 1)
+#pragma unroll
+                        for (int w = 0; w + off < WL; w += 2 * off) x[w] += x[w + off];
+                    if (x[0] != 0.0f) atomic_add_noret(Tj + cell_of_sum(first[res], q), scale * x[0]);
+                }
+            } else {
+#pragma unroll 1
+                for (uint32_t item = tid; item < SPAN * WL * NC; item += 64 * WL) {
+                    const uint32_t w = item % WL, t = item / WL, res = t / NC, q = t % NC;
+                    const float sum = static_cast<int>(w) < nw ? sums_lds[set][w][q][res] : 0.0f;
+                    if (sum != 0.0f)
+                        atomic_add_noret(Tj + static_cast<size_t>(cell_of_sum(first[res], q)) * kGroup + w, scale * sum);
+                }
+            }
+        }
+        // visits whose cells are not kept (never with a list of cs_params_init): hashed by the definition,
+        // straight into memory
+        if (!PARTIAL && listed < k1 - k0 && live && wv < nwaves) {
+            for (uint32_t k = 0; k < k1 - k0; ++k) {
+                const uint32_t s = __builtin_amdgcn_readfirstlane(steps[k].z), w = __builtin_amdgcn_readfirstlane(steps[k].w);
+                if (w >> 30 < 3u || (w & kGapMask) <= my_res || s + my_res >= d) continue;
+                const uint32_t in_gap = (w & kGapMask) - my_res, in_vec = d - s - my_res;
+                const uint32_t len = in_gap < in_vec ? in_gap : in_vec;
+                const uint32_t at = s + my_res;
+                uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + at));
+                uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + at));
+                for (uint32_t m = 0; m < kOneRun && m < len; ++m) {
+                    const float val = apply_sign(scale * g[at + m], sign_flip_of(ys));
+                    if (val != 0.0f)
+                        atomic_add_noret(Tj + static_cast<size_t>(bucket_of<POW2>(yb, col)) * cell_floats + (fold ? 0 : worker), val);
+                    yb = hash_advance(yb, v.a);
+                    ys = hash_advance(ys, v.as);
+                }
+            }
+        }
+        if constexpr (WL > 1) __syncthreads();
+        else __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// One launch of k_accumulate_vectors: n rows whose pieces are chosen, with at most ncell running sums.
+template <int WL, bool PARTIAL, typename LIST>
+int launch_vectors(LIST& rows, const WorkersBeside<LIST>& a, int n, uint32_t ncell, hipStream_t stream) {
+    auto launch = [&](auto sets, auto nc) -> int {
+        constexpr int SETS = decltype(sets)::value, NC = decltype(nc)::value;
+        const dim3 grid(visits_grid<1, kOneRun, SETS>(rows, n), (a.nw + kGroup - 1) / kGroup);
+        const size_t lds = most_steps(rows, n) * sizeof(uint4);
+        k_accumulate_vectors<WL, SETS, NC, PARTIAL, LIST><<<grid, 64 * WL * SETS, lds, stream>>>(rows, a);
+        return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
+    };
+    auto with = [&](auto sets) -> int {
+        if (ncell == 2) return launch(sets, std::integral_constant<int, 2>());
+        if (ncell == 4) return launch(sets, std::integral_constant<int, 4>());
+        if constexpr (std::is_same<LIST, VisitRows>::value) {
+            if (ncell == 3) return launch(sets, std::integral_constant<int, 3>());
+        }
+        return CS_EINVAL;
+    };
+    if (!PARTIAL && !a.T) return CS_EINVAL;
+    if constexpr (WL == 1) {
+        int64_t waves = 0;
+        for (int q = 0; q < n; ++q) waves += (static_cast<int64_t>(rows.row[q].gmax) + 64 * kOneRun - 1) / (64 * kOneRun);
+        if (waves < kOneFewWaves) return with(std::integral_constant<int, 1>());
+    }
+    return with(std::integral_constant<int, WL >= 4 ? 1 : 4 / WL>());
+}
+
+// A wavefront per vector is the faster way for 2 to 8 vectors that the memory-side cache (256 MB) holds, or nearly (us, update with
+// merge, lanes for workers / wavefronts for vectors): 5 x 2^17, 6.5 M, 8 workers 201 / 178, 9 M 267 / 238; 5 x 2^18, 14 M
+// 390 / 435; 7 x 65 536, 15.4 M 544 / 575; 4 workers and less, up to 480 MB: 5 x 2^17, 10 M, 4 workers 167 / 148, 5 x 2^18,
+// 30 M 437 / 422; 5 x 2^19, 40 M, 2 workers 371 / 287; 7 x 161 771, 30 M, 4 workers 671 / 675.  Less so where a residue takes part in
+// few visits, so that what a workgroup does once (its table of visits, the sums at its end) is much of it, in short vectors, and for the
+// row of another column count's seventh that has a launch of its own: 5 x 8192, 300 000, 8 workers 25 / 34; 5 x 16 384,
+// 600 000 33 / 38; 7 x 65 536, 5 M (23 visits) 207 / 212; 7 x 2^17, 5 M, 4 workers (14) 192 / 203; 7 x 8387, 2.5 M 110 / 124.
+// Of the drawn shapes that it leaves a few are behind, by up to 5 % (3 x 2^17, 8.6 M, 4 workers 83 / 86).  Several groups of 8 in a
+// launch: 5 x 8192, 300 000, 64 workers 126 / 140.
+template <typename LIST>
+bool vectors_pay(const LIST& rows, int n, int64_t d, int vectors, int groups) {
+    double residues = 0.0;
+    for (int q = 0; q < n; ++q) residues += static_cast<double>(rows.row[q].gmax);
+    const double bytes = 4.0 * static_cast<double>(d) * vectors;
+    if (groups != 1 || d < 1'200'000 || bytes > (vectors > 4 ? 3.4e8 : 4.8e8)) return false;
+    return n * static_cast<double>(d) >= 25.0 * residues;
+}
+// A visit of theirs with the chip full, and the rate at which the cache is read
+constexpr double kVisitNsVectors = 650.0;
+constexpr double kCachedBytesPerNs = 6400.0;
+
 template <int WL, int NWAVE>
 int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js, int nrows,
                   uint32_t ncell, hipStream_t stream) {
@@ -1043,6 +1397,12 @@ int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js,
         requests8[q] = a.fold ? requests16[q] : (0.5 * vp.ncell + 0.5) * static_cast<double>(vp.gmax) * groups;
     }
     const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * nrows / kStreamBytesPerNs;
+    if constexpr (WL > 1) {
+        if (vectors_pay(rows, nrows, a.d, a.nw, groups)) {
+            choose_pieces(rows, nrows, requests8, kVisitNsVectors, stream_ns * kStreamBytesPerNs / kCachedBytesPerNs);
+            return launch_vectors<WL, false>(rows, a, nrows, ncell, stream);
+        }
+    }
     if (choose_run8<WL>(rows, nrows, requests8, requests16, a.d, stream_ns, groups))
         return launch_visits_run<WL, 8, 1>(rows, a, nrows, ncell, stream);
     return launch_visits_run<WL, 16, NWAVE>(rows, a, nrows, ncell, stream);
@@ -1153,275 +1513,19 @@ int launch_visits_anyc(const cs_params* p, const VisitWorkersOf<1>& a, const uin
         requests[q] = 2.0 * rows.row[q].omega * static_cast<double>(rows.row[q].gmax);
     }
     const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * n / kStreamBytesPerNs;
+    if constexpr (WL > 1) {
+        // (with 6 to 8 workers and few coordinates per column the requests are too much of it: 5 x 180 000, 6.5 M, 8 workers 245 /
+        // 245, 3 x 88 897, 4.3 M 86 / 89, 3 x 126 461, 3 M 129 / 131; but 5 x 65 723, 2.5 M, 5 workers 127 / 115, 3 x 32 571,
+        // 8.5 M, 8 workers 153 / 144)
+        const bool wide = a.nw > 5 && a.d < 64 * static_cast<int64_t>(a.c);
+        if (p->r <= kAnycRowsPerLaunch && !wide && vectors_pay(rows, n, a.d, a.nw, 1)) {
+            choose_pieces(rows, n, requests, kVisitNsVectors, stream_ns * kStreamBytesPerNs / kCachedBytesPerNs);
+            return launch_vectors<WL, false>(rows, a, n, 2 * omega, stream);
+        }
+    }
     if (choose_run8<WL>(rows, n, requests, requests, a.d, stream_ns))
         return launch_visits_run<WL, 8, 1>(rows, a, n, 2 * omega, stream);
     return launch_visits_run<WL, 16, NWAVE>(rows, a, n, 2 * omega, stream);
-}
-
-// ---------------------------------------------------------------------------------------
-// The update of one vector (one worker, or the workers' vectors summed beforehand) along visit
-// lists.
-//
-// With one vector nothing is shared between lanes, so a lane owns 4 neighbouring residues: a visit
-// is one 16-byte load, 8 comparisons and 8 masked additions in registers, and a
-// wavefront reads 1 KB of contiguous addresses.  Loads of the next kOneAhead visits are in flight; every
-// request is one whole load, at the vector's last four values where its own would lie beyond, so that
-// the wait for a visit's values counts the loads behind them.
-// At the end the NC sums of a residue, which lie in neighbouring cells, are brought to
-// neighbouring lanes, so that they leave as one request (an aligned 64-byte block touched by an
-// instruction is one) instead of NC.  A workgroup of kOneWaves wavefronts shares one table of visits; launches of fewer than
-// kOneFewWaves wavefronts have workgroups of one, which spread them over more CUs (us, 4 / 1: 21 wavefronts, 3 x 512,
-// d = 203 680 16.9 / 12.8; 138, 5 x 707, 326 476 41.8 / 29.2; 269, 5 x 2048, 304 889 17.3 / 14.7; 338, 5 x 2401, 224 320
-// 24.8 / 26.0; 642, 5 x 2641, 747 318 36.7 / 41.7; two launches of 16 000, 15 x 131 072, 31 M 536 / 572).
-// Measured (update alone, in us; with two 61-bit states per coordinate and a load for every visit of the list, taken
-// part in or not -> now): d = 73 M, 5 x 2^20 468 -> 326; d = 25 M, 5 x 2^19 176 -> 137; d = 11 M, 5 x 2^18 102 -> 74;
-// d = 73 M, 5 x 180 000 492 -> 445.  Bound: the requests at the end (without them 216, 92, 43 and 227 us, which
-// is the five reads, 1.46 GB at 73 M by the counters too, at 6.8 TB/s; with them 1.63 GB at 4.8); 2 and 4 loads ahead and 2
-// and 8 wavefronts per workgroup: within 4 % either way.
-// ---------------------------------------------------------------------------------------
-constexpr int kOneRun = 4;
-constexpr int kOneAhead = 3;
-constexpr int kOneWaves = 4;
-constexpr int64_t kOneFewWaves = 300;
-
-// PARTIAL: the sums go to a workspace, [piece][residue][running sum], instead of being added to the table
-// (cs_index.hip).
-template <int NC, int NWAVE, bool PARTIAL, typename LIST>
-__global__ void __launch_bounds__(64 * NWAVE)
-k_accumulate_one(LIST rows, const float* __restrict__ g, float* __restrict__ S, uint32_t c,
-                 int cell_floats, int64_t d, int64_t i0, float scale) {
-    constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
-    constexpr int SPAN = 64 * kOneRun;
-    const unsigned row = row_of_block(rows);
-    const auto& v = rows.at(row);
-    const uint32_t piece = (blockIdx.x - rows.first[row]) / v.blocks;
-    const uint32_t block = (blockIdx.x - rows.first[row]) % v.blocks;
-    const int lane = threadIdx.x & 63;
-    const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wavefront-uniform
-    extern __shared__ uint4 steps[];                   // the visits of my piece
-    __shared__ __attribute__((aligned(16))) float sum_lds_all[NWAVE][NC][SPAN];
-    __shared__ uint32_t first_lds_all[PARTIAL ? 1 : NWAVE][SPAN];  // first cell of a residue
-    float (*parked)[SPAN] = sum_lds_all[wq];
-    uint32_t* first = first_lds_all[PARTIAL ? 0 : wq];
-    const Columns col = columns_of<POW2>(c);
-    const uint32_t mask = c - 1u;
-    uint32_t ncell, omega;                             // running sums, and the values of A mod c that they cover
-    if constexpr (POW2) {
-        ncell = v.ncell;
-        omega = ncell - 1;
-    } else {
-        omega = v.omega;
-        ncell = 2 * omega;
-    }
-    auto cell_of_sum = [&](uint32_t first, uint32_t q) -> uint32_t {
-        if constexpr (POW2) {
-            return (first + q) & mask;
-        } else {
-            const uint32_t x = q < omega ? first + q : first + (q - omega) + (c - v.pc);
-            return x >= c ? x - c : x;
-        }
-    };
-    uint64_t at = static_cast<uint64_t>(v.j) * c * cell_floats;
-    if constexpr (PARTIAL) at = v.at;
-    float* __restrict__ Sj = S + at;
-    const int64_t nwaves = (static_cast<int64_t>(v.gmax) + SPAN - 1) / SPAN;
-    const int64_t nsets = (nwaves + NWAVE - 1) / NWAVE;
-    const uint32_t k0 = v.K * piece / v.pieces, k1 = v.K * (piece + 1) / v.pieces;
-    VisitPlaces places;
-    places.init(v);
-    const uint32_t listed = fill_visit_steps<POW2, NWAVE>(steps, places, v, k0, k1, col, omega);
-    const uint32_t last4 = static_cast<uint32_t>(d) - kOneRun;
-
-    // sets of neighbouring wavefronts go to one XCD, as in k_accumulate_visits
-    for (int64_t vi = block; ; vi += v.blocks) {
-        if (visit_round(vi, v.blocks) >= nsets) break;
-        const int64_t wv = visit_set(vi, v.blocks) * NWAVE + wq;
-        if (wv >= nwaves) continue;
-        const uint32_t wave_res = static_cast<uint32_t>(wv * SPAN);
-        const uint32_t my_res = wave_res + lane * kOneRun;
-        uint32_t xb[kOneRun], xs[kOneRun];              // top bits of the hashes at my residues
-        uint32_t signs = 0;                             // bit m: the sign of residue m is -1
-        {
-            uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
-            uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res));
-#pragma unroll
-            for (int m = 0; m < kOneRun; ++m) {
-                xb[m] = top_of(yb);
-                xs[m] = top_of(ys);
-                signs |= (sign_flip_of(ys) >> 31) << m;
-                yb = hash_advance(yb, v.a);
-                ys = hash_advance(ys, v.as);
-            }
-        }
-        struct Step {                                   // a visit that was requested
-            vec4f x;
-            uint32_t tb, ts, s, w;                      // the step, as in steps[k]
-            uint32_t k;                                 // ~0u for none
-        };
-        VisitCursor cursor(steps, k1 - k0, wave_res, static_cast<uint32_t>(d));
-        auto request = [&](Step& st) {
-            st.k = cursor.next();
-            const uint4 e = steps[st.k == ~0u ? 0u : st.k];
-            st.tb = e.x;
-            st.ts = e.y;
-            st.s = __builtin_amdgcn_readfirstlane(e.z);
-            st.w = __builtin_amdgcn_readfirstlane(e.w);
-            uint32_t at = st.s + my_res;
-            at = at < last4 ? at : last4;
-            st.x = *(gvec4_ptr)((gfloat_ptr)g + at);
-        };
-        // of the residues from wave_res on, how many take part in the visit and exist in the vector (> 0)
-        auto room_of = [&](uint32_t s, uint32_t w) -> uint32_t {
-            const uint32_t in_gap = (w & kGapMask) - wave_res, in_vec = static_cast<uint32_t>(d) - s - wave_res;
-            return in_gap < in_vec ? in_gap : in_vec;
-        };
-        // x: four values read at min(s + my_res, last4)  ->  those of my residues, 0 for the missing ones
-        auto cut = [&](vec4f x, uint32_t s, uint32_t room) -> vec4f {
-            const int len = static_cast<int>(room) - lane * kOneRun;
-            const int over = static_cast<int>(s + my_res) - static_cast<int>(last4);
-            const float in[kOneRun] = {x.x, x.y, x.z, x.w};
-            float out[kOneRun];
-#pragma unroll
-            for (int m = 0; m < kOneRun; ++m) {
-                float val = over <= 0 ? in[m] : 0.0f;
-#pragma unroll
-                for (int t = m + 1; t < kOneRun; ++t) val = over == t - m ? in[t] : val;
-                out[m] = m < len ? val : 0.0f;
-            }
-            return vec4f{out[0], out[1], out[2], out[3]};
-        };
-        // sums of the coordinates whose bucket hash did not wrap and of those whose did, for visits with
-        // A mod c = cur; their signs less that of the residue itself
-        float plain[kOneRun], wrapped[kOneRun];
-        uint32_t cur = 0;
-#pragma unroll
-        for (int m = 0; m < kOneRun; ++m) plain[m] = wrapped[m] = 0.0f;
-        auto park = [&](uint32_t q, const float (&x)[kOneRun]) {
-            vec4f u;
-#pragma unroll
-            for (int m = 0; m < kOneRun; ++m) u[m] = x[m];
-            *reinterpret_cast<vec4f*>(&parked[q][lane * kOneRun]) = u;
-        };
-        auto fetch = [&](uint32_t q, float (&x)[kOneRun]) {
-            const vec4f u = *reinterpret_cast<const vec4f*>(&parked[q][lane * kOneRun]);
-#pragma unroll
-            for (int m = 0; m < kOneRun; ++m) x[m] = u[m];
-        };
-#pragma unroll
-        for (int q = 0; q < NC; ++q)
-            *reinterpret_cast<vec4f*>(&parked[q][lane * kOneRun]) = vec4f{0.0f, 0.0f, 0.0f, 0.0f};
-        auto move_to = [&](uint32_t q) {                // (neighbouring cells share a sum: power-of-two c)
-            const uint32_t step = POW2 ? 1 : omega;
-            park(cur, plain);
-            park(cur + step, wrapped);
-            fetch(q, plain);
-            fetch(q + step, wrapped);
-            cur = q;
-        };
-        auto add_up = [&](Step& st) {
-            const uint32_t room = room_of(st.s, st.w);
-            vec4f x = st.x;
-            if (room < SPAN) x = cut(x, st.s, room);
-            if (cur != st.w >> 30) move_to(st.w >> 30);
-            bool flip[kOneRun], wrap[kOneRun], unsure = false;
-#pragma unroll
-            for (int m = 0; m < kOneRun; ++m) {
-                flip[m] = xs[m] > st.ts;
-                wrap[m] = xb[m] > st.tb;
-                unsure |= xb[m] == st.tb || xs[m] == st.ts;
-            }
-            if (__builtin_amdgcn_ballot_w64(unsure) != 0) {
-                // the lower bits decide: whole hash values against whole thresholds
-                const uint64_t A = mulmod_p(v.a, st.s), As = mulmod_p(v.as, st.s);
-                uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
-                uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + my_res));
-#pragma unroll
-                for (int m = 0; m < kOneRun; ++m) {
-                    flip[m] = ys > kP61 - As;
-                    wrap[m] = yb > kP61 - A;
-                    yb = hash_advance(yb, v.a);
-                    ys = hash_advance(ys, v.as);
-                }
-            }
-            const bool odd = (st.w >> 29 & 1u) != 0;
-#pragma unroll
-            for (int m = 0; m < kOneRun; ++m) {
-                const float val = flip[m] != odd ? -x[m] : x[m];
-                plain[m] += wrap[m] ? 0.0f : val;
-                wrapped[m] += wrap[m] ? val : 0.0f;
-            }
-        };
-        Step st[kOneAhead];
-#pragma unroll
-        for (int u = 0; u < kOneAhead; ++u) request(st[u]);
-        // (a buffer is refilled where it was read: moving a value that is still on its way would
-        // wait for it)
-        for (bool more = true; more;) {
-#pragma unroll
-            for (int u = 0; u < kOneAhead; ++u) {
-                if (st[u].k == ~0u) {
-                    more = false;
-                    break;
-                }
-                add_up(st[u]);
-                request(st[u]);
-            }
-        }
-        park(cur, plain);
-        park(cur + (POW2 ? 1 : omega), wrapped);
-#pragma unroll
-        for (int q = 0; q < NC; ++q) {                  // the signs of the residues
-            float x[kOneRun];
-            fetch(q, x);
-#pragma unroll
-            for (int m = 0; m < kOneRun; ++m) x[m] = apply_sign(x[m], (signs >> m) << 31);
-            park(q, x);
-        }
-        __builtin_amdgcn_wave_barrier();
-        if constexpr (PARTIAL) {
-            float* dst = Sj + (static_cast<uint64_t>(piece) * nwaves + wv) * SPAN * ncell;
-            for (uint32_t item = lane; item < SPAN * ncell; item += 64)
-                dst[item] = scale * parked[item % ncell][item / ncell];
-            __builtin_amdgcn_wave_barrier();
-        } else {
-            // visits whose cells are not kept (never with a list of cs_params_init): hashed by the definition,
-            // straight into memory
-            for (uint32_t k = 0; listed < k1 - k0 && k < k1 - k0; ++k) {
-                const uint32_t s = __builtin_amdgcn_readfirstlane(steps[k].z), w = __builtin_amdgcn_readfirstlane(steps[k].w);
-                if (w >> 30 < 3u) continue;
-                if ((w & kGapMask) <= wave_res || s + wave_res >= static_cast<uint32_t>(d)) continue;
-                const uint32_t at = s + my_res;
-                const vec4f x = cut(*(gvec4_ptr)((gfloat_ptr)g + (at < last4 ? at : last4)), s, room_of(s, w));
-                uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + at));
-                uint64_t ys = hash_state(v.as, v.bs, static_cast<uint64_t>(i0 + at));
-#pragma unroll
-                for (int m = 0; m < kOneRun; ++m) {
-                    const float val = apply_sign(scale * x[m], sign_flip_of(ys));
-                    if (val != 0.0f)
-                        atomic_add_noret(Sj + static_cast<size_t>(bucket_of<POW2>(yb, col)) * cell_floats, val);
-                    yb = hash_advance(yb, v.a);
-                    ys = hash_advance(ys, v.as);
-                }
-            }
-            // every sum goes to memory once, the NC sums of a residue by neighbouring lanes
-            uint64_t yb = hash_state(v.a, v.b, static_cast<uint64_t>(i0 + my_res));
-#pragma unroll
-            for (int m = 0; m < kOneRun; ++m) {
-                first[lane * kOneRun + m] = bucket_of<POW2>(yb, col);
-                yb = hash_advance(yb, v.a);
-            }
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll 1
-            for (uint32_t item = lane; item < SPAN * NC; item += 64) {
-                const uint32_t res = item / NC, q = item % NC;
-                const float sum = parked[q][res];
-                const uint32_t f = first[res];
-                if (sum != 0.0f)
-                    atomic_add_noret(Sj + static_cast<size_t>(cell_of_sum(f, q)) * cell_floats, scale * sum);
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-    }
 }
 
 }  // namespace
@@ -1574,27 +1678,6 @@ bool one_applies(const cs_params* p, int64_t d) {
     return 1.2 * residues <= static_cast<double>(p->r) * static_cast<double>(d) / 8.0;
 }
 
-namespace {
-
-// one launch of k_accumulate_one: n rows whose pieces are chosen
-template <int NC, bool PARTIAL, typename LIST>
-int launch_one(LIST& rows, int n, const float* g, float* S, uint32_t c, int cell_floats, int64_t d, int64_t i0, float scale,
-               hipStream_t stream) {
-    int64_t waves = 0;
-    for (int q = 0; q < n; ++q) waves += (static_cast<int64_t>(rows.row[q].gmax) + 64 * kOneRun - 1) / (64 * kOneRun);
-    const size_t lds = most_steps(rows, n) * sizeof(uint4);
-    if (waves < kOneFewWaves) {
-        const dim3 grid(visits_grid<1, kOneRun, 1>(rows, n));
-        k_accumulate_one<NC, 1, PARTIAL, LIST><<<grid, 64, lds, stream>>>(rows, g, S, c, cell_floats, d, i0, scale);
-    } else {
-        const dim3 grid(visits_grid<1, kOneRun, kOneWaves>(rows, n));
-        k_accumulate_one<NC, kOneWaves, PARTIAL, LIST><<<grid, 64 * kOneWaves, lds, stream>>>(rows, g, S, c, cell_floats, d, i0, scale);
-    }
-    return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
-}
-
-}  // namespace
-
 // S = float[r][c][cell_floats]: the table itself (1) or one worker's slot of a bundle (kGroup)
 int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const float* g, int64_t d,
                           int64_t i0, float scale, hipStream_t stream, int* launches) {
@@ -1603,6 +1686,16 @@ int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const f
         for (int q = 0; q < n; ++q) requests[q] = 1.2 * static_cast<double>(rows.row[q].gmax);
         const double stream_ns = 4.0 * static_cast<double>(d) * n / kStreamBytesPerNs;
         choose_pieces(rows, n, requests, kVisitNsOne, stream_ns);
+    };
+    auto fill = [&](auto& a) {
+        a.g[0] = g;
+        a.T = S;
+        a.d = d;
+        a.i0 = i0;
+        a.c = p->c;
+        a.nw = 1;
+        a.scale = scale;
+        a.fold = cell_floats == 1 ? 1 : 0;
     };
     if (!p->c_pow2)
         return for_each_anyc_launch(p, p->r, [&](const uint32_t* js, int n, uint32_t omega) {
@@ -1613,8 +1706,9 @@ int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const f
             VisitGapsRows rows{};
             for (int q = 0; q < n; ++q) fill_visit_gaps(p, js[q], rows.row[q]);
             cut(rows, n);
-            return omega == 1 ? launch_one<2, false>(rows, n, g, S, p->c, cell_floats, d, i0, scale, stream)
-                              : launch_one<4, false>(rows, n, g, S, p->c, cell_floats, d, i0, scale, stream);
+            VisitWorkersOf<1> a{};
+            fill(a);
+            return launch_vectors<1, false>(rows, a, n, 2 * omega, stream);
         });
     uint32_t order[CS_MAX_R], ncell = 2;
     for (uint32_t j = 0; j < p->r; ++j) {              // the longest lists first
@@ -1628,10 +1722,9 @@ int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const f
         VisitRows rows{};
         for (int q = 0; q < n; ++q) fill_visit_args(p, order[q0 + q], rows.row[q]);
         cut(rows, n);
-        int rc = CS_EINVAL;
-        if (ncell == 2) rc = launch_one<2, false>(rows, n, g, S, p->c, cell_floats, d, i0, scale, stream);
-        else if (ncell == 3) rc = launch_one<3, false>(rows, n, g, S, p->c, cell_floats, d, i0, scale, stream);
-        else if (ncell == 4) rc = launch_one<4, false>(rows, n, g, S, p->c, cell_floats, d, i0, scale, stream);
+        VisitWorkers a{};
+        fill(a);
+        const int rc = launch_vectors<1, false>(rows, a, n, ncell, stream);
         if (rc != CS_OK) return rc;
     }
     return CS_OK;
@@ -1682,10 +1775,12 @@ int partial_rows(VisitRows& rows, VisitWorkers& a, int n, int groups, SumsPlan& 
         writes[q] = 24.0 * 32.0 * WL * v.ncell * static_cast<double>(v.gmax) / kStreamBytesPerNs * groups;
     }
     const double stream_ns = 4.0 * static_cast<double>(a.d) * WL * n / kStreamBytesPerNs * groups;
-    int log_run = 0;                                   // (of one vector the sums lie in the order of the residues)
+    int log_run = 0;                                   // (a wavefront per vector: the sums lie in the order of the residues)
+    const bool vectors = WL == 1 || vectors_pay(rows, n, a.d, WL, groups);
     if (WL == 1) choose_pieces(rows, n, writes, kVisitNsOne, stream_ns);
+    else if (vectors) choose_pieces(rows, n, writes, kVisitNsVectors, stream_ns * kStreamBytesPerNs / kCachedBytesPerNs);
     else log_run = choose_run8<WL>(rows, n, writes, writes, a.d, stream_ns, groups) ? 3 : 4;
-    const uint64_t span = WL == 1 ? 64 * kOneRun : 64u / WL << log_run;
+    const uint64_t span = vectors ? 64 * kOneRun : 64u / WL << log_run;
     for (int q = 0; q < n; ++q) {
         VisitArgs& v = rows.row[q];
         SumsRow& out = plan.row[v.j];
@@ -1698,12 +1793,12 @@ int partial_rows(VisitRows& rows, VisitWorkers& a, int n, int groups, SumsPlan& 
         plan.floats += out.piece_floats * v.pieces;
     }
     if (a.nw == 0) return CS_OK;
-    if constexpr (WL == 1) {
-        return launch_one<4, true>(rows, n, a.g[0], a.sums, a.c, 1, a.d, a.i0, a.scale, stream);
-    } else {
+    if (vectors) return launch_vectors<WL, true>(rows, a, n, most, stream);
+    if constexpr (WL > 1) {
         if (log_run == 3) return launch_visits_run<WL, 8, 1>(rows, a, n, most, stream);
         return launch_visits_run<WL, 16, WL == 8 ? kWavesPerGroupOf8 : 1>(rows, a, n, most, stream);
     }
+    return CS_EINVAL;
 }
 
 template <int WL>
