@@ -35,6 +35,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <type_traits>
 
 #include "cs_device.h"
@@ -356,6 +357,7 @@ struct VisitWorkersOf {
     float scale;
     int32_t fold;                // != 0: the workers' sums of a cell are added up across the lanes
                                  // of a walker and leave as one 4-byte request into a single table
+    uint32_t at_once;            // workgroups that the chip holds at a time (set by the launch): see walks_down
     float* sums;                 // PARTIAL: where the first group's running sums go
     uint64_t table_floats, sums_floats;          // from one group's to the next
     const float* g[GROUPS * kGroup];             // vectors of the workers
@@ -484,11 +486,20 @@ struct VisitPlaces {
     }
 };
 
-// The visits k0 .. k1 - 1, by all wavefronts of the workgroup; returns how many of them are not `3`.  within: A mod c
-// must be below it.
+// The way of a workgroup through its visits: the workgroups that the chip holds at a time begin together, take about the same
+// time and so pass over the vectors side by side.  The first such round walks down from the last visit, the
+// next up, and so on: every round begins where the round before ended, on what the memory-side cache (256 MB) still holds of
+// that, and the first on the end of vectors that a pass before wrote in order (dense state).  Us a step, all
+// rounds up / in turn: 5 x 2^18, 11 M, 8 workers, dense 778 / 764 (in turn, rounds of half the size 784), 7 x 2^19, 25 M, 256 workers
+// 34 580 / 33 400 (rounds of two thirds 35 260, of four thirds 34 130), 15 x 180 000, 90 M, 4 workers 6500 / 6350, 5 x 2^20, 10^8,
+// 32 workers 13 640 / 13 520.  The more of the vectors the cache holds, the more of a round's reads it answers.
+__device__ __forceinline__ bool walks_down(uint32_t at_once) { return (blockIdx.x / at_once & 1u) == 0; }
+
+// The visits k0 .. k1 - 1, by all wavefronts of the workgroup, the last one first with `down`; returns how many of them are
+// not `3`.  within: A mod c must be below it.
 template <bool POW2, int NWAVE, typename ARGS>
 __device__ __forceinline__ uint32_t fill_visit_steps(uint4* steps, const VisitPlaces& places, const ARGS& v, uint32_t k0,
-                                                     uint32_t k1, const Columns& col, uint32_t within) {
+                                                     uint32_t k1, const Columns& col, uint32_t within, bool down) {
     __shared__ uint32_t count[CS_MAX_VISITS / 64];
     const uint32_t lane = threadIdx.x & 63, wq = threadIdx.x >> 6;
     const uint32_t chunks = (k1 - k0 + 63) / 64;
@@ -502,7 +513,8 @@ __device__ __forceinline__ uint32_t fill_visit_steps(uint4* steps, const VisitPl
         const uint32_t listed = __builtin_popcountll(__builtin_amdgcn_ballot_w64(k < k1 && q < 3u));
         if (lane == 0) count[chunk] = listed;
         if (k < k1)
-            steps[k - k0] = make_uint4(threshold_of(A), threshold_of(As), s, gap | static_cast<uint32_t>(As & 1u) << 29 | q << 30);
+            steps[down ? k1 - 1 - k : k - k0] =
+                make_uint4(threshold_of(A), threshold_of(As), s, gap | static_cast<uint32_t>(As & 1u) << 29 | q << 30);
     }
     __syncthreads();
     uint32_t listed = 0;
@@ -575,7 +587,7 @@ k_accumulate_visits(LIST rows, WorkersBeside<LIST> a) {
     // even, and leave as one request then: on average ncell / 2 + 1/2 requests per residue instead of ncell.  For
     // that the sums go through LDS.  Only short vectors (RUN = 8) gain, whose time is mostly these
     // requests; long ones stream meanwhile.
-    constexpr bool kPairs = !PARTIAL && POW2 && RUN == 8;
+constexpr bool kPairs = !PARTIAL && POW2 && RUN == 8;
     // Per wavefront: the value tile (one padded row per lane), the walkers' first cells and signs
     __shared__ float tile_lds_all[NWAVE][64 * kStride];
     __shared__ uint32_t first_lds_all[NWAVE][SPAN];
@@ -651,7 +663,7 @@ k_accumulate_visits(LIST rows, WorkersBeside<LIST> a) {
     const uint32_t k0 = v.K * piece / v.pieces, k1 = v.K * (piece + 1) / v.pieces;
     VisitPlaces places;
     places.init(v);
-    const uint32_t listed = fill_visit_steps<POW2, NWAVE>(steps, places, v, k0, k1, col, omega);
+    const uint32_t listed = fill_visit_steps<POW2, NWAVE>(steps, places, v, k0, k1, col, omega, walks_down(a.at_once));
     for (int64_t vi = block; ; vi += v.blocks) {
         if (visit_round(vi, v.blocks) >= ngroups) break;
         const int64_t set = visit_set(vi, v.blocks);
@@ -1003,9 +1015,26 @@ uint32_t most_steps(const LIST& rows, int nrows) {
     return most;
 }
 
+// Workgroups of a kernel that the chip holds at a time.  (The runtime works it out from the kernel's registers and LDS; asked once
+// for each amount of LDS in a row of equal ones, as a program that steps has them.)
+template <auto KERNEL>
+uint32_t workgroups_at_once(int threads, size_t lds) {
+    static std::atomic<uint64_t> known{0};             // LDS, workgroups
+    const uint64_t k = known.load(std::memory_order_relaxed);
+    if (k != 0 && k >> 32 == lds) return static_cast<uint32_t>(k);
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, threads, lds) != hipSuccess || per_cu < 1) {
+        (void)hipGetLastError();
+        per_cu = 1;
+    }
+    const uint32_t n = 256u * static_cast<uint32_t>(per_cu);
+    known.store(static_cast<uint64_t>(lds) << 32 | n, std::memory_order_relaxed);
+    return n;
+}
+
 // one launch: rows that all have at most ncell running sums, of the groups of workers that `a` holds
 template <int WL, int RUN, int NWAVE, typename LIST>
-int launch_visits_run(LIST& rows, const WorkersBeside<LIST>& a, int nrows, uint32_t ncell, hipStream_t stream) {
+int launch_visits_run(LIST& rows, WorkersBeside<LIST> a, int nrows, uint32_t ncell, hipStream_t stream) {
     const dim3 grid(visits_grid<WL, RUN, NWAVE>(rows, nrows), (a.nw + kGroup - 1) / kGroup), block(64 * NWAVE);
     const size_t lds = most_steps(rows, nrows) * sizeof(uint4);
     constexpr bool pow2 = std::is_same<LIST, VisitRows>::value;
@@ -1013,13 +1042,15 @@ int launch_visits_run(LIST& rows, const WorkersBeside<LIST>& a, int nrows, uint3
     if (!(a.sums ? partial : a.T != nullptr)) return CS_EINVAL;
     auto launch = [&](auto nc) {
         constexpr int NC = decltype(nc)::value;
+        auto with = [&](auto sums) {
+            constexpr auto kernel = k_accumulate_visits<WL, RUN, NWAVE, NC, decltype(sums)::value, LIST>;
+            a.at_once = workgroups_at_once<kernel>(64 * NWAVE, lds);
+            kernel<<<grid, block, lds, stream>>>(rows, a);
+        };
         if constexpr (partial) {
-            if (a.sums) {
-                k_accumulate_visits<WL, RUN, NWAVE, NC, true, LIST><<<grid, block, lds, stream>>>(rows, a);
-                return;
-            }
+            if (a.sums) return with(std::true_type());
         }
-        k_accumulate_visits<WL, RUN, NWAVE, NC, false, LIST><<<grid, block, lds, stream>>>(rows, a);
+        with(std::false_type());
     };
     if (ncell == 2) launch(std::integral_constant<int, 2>());
     else if (ncell == 4) launch(std::integral_constant<int, 4>());
@@ -1110,7 +1141,7 @@ k_accumulate_vectors(LIST rows, WorkersBeside<LIST> a) {
     const uint32_t k0 = v.K * piece / v.pieces, k1 = v.K * (piece + 1) / v.pieces;
     VisitPlaces places;
     places.init(v);
-    const uint32_t listed = fill_visit_steps<POW2, WL * SETS>(steps, places, v, k0, k1, col, omega);
+    const uint32_t listed = fill_visit_steps<POW2, WL * SETS>(steps, places, v, k0, k1, col, omega, walks_down(a.at_once));
     const uint32_t last4 = d - kOneRun;
 
     // sets of neighbouring wavefronts go to one XCD, as in k_accumulate_visits
@@ -1336,12 +1367,14 @@ k_accumulate_vectors(LIST rows, WorkersBeside<LIST> a) {
 
 // One launch of k_accumulate_vectors: n rows whose pieces are chosen, with at most ncell running sums.
 template <int WL, bool PARTIAL, typename LIST>
-int launch_vectors(LIST& rows, const WorkersBeside<LIST>& a, int n, uint32_t ncell, hipStream_t stream) {
+int launch_vectors(LIST& rows, WorkersBeside<LIST> a, int n, uint32_t ncell, hipStream_t stream) {
     auto launch = [&](auto sets, auto nc) -> int {
         constexpr int SETS = decltype(sets)::value, NC = decltype(nc)::value;
         const dim3 grid(visits_grid<1, kOneRun, SETS>(rows, n), (a.nw + kGroup - 1) / kGroup);
         const size_t lds = most_steps(rows, n) * sizeof(uint4);
-        k_accumulate_vectors<WL, SETS, NC, PARTIAL, LIST><<<grid, 64 * WL * SETS, lds, stream>>>(rows, a);
+        constexpr auto kernel = k_accumulate_vectors<WL, SETS, NC, PARTIAL, LIST>;
+        a.at_once = workgroups_at_once<kernel>(64 * WL * SETS, lds);
+        kernel<<<grid, 64 * WL * SETS, lds, stream>>>(rows, a);
         return hipGetLastError() == hipSuccess ? CS_OK : CS_EHIP;
     };
     auto with = [&](auto sets) -> int {
@@ -2295,7 +2328,7 @@ k_row_values_visits(VisitGapsRows vr, const float* __restrict__ S, uint32_t c, i
     const uint32_t k0 = v.K * blockIdx.z / nseg, k1 = v.K * (blockIdx.z + 1) / nseg;
     VisitPlaces places;
     places.init(v);
-    fill_visit_steps<false, kQueryWaves>(steps, places, v, k0, k1, col, omega);          // (a barrier in it: lh is clear)
+    fill_visit_steps<false, kQueryWaves>(steps, places, v, k0, k1, col, omega, false);          // (a barrier in it: lh is clear)
     const uint32_t d32 = static_cast<uint32_t>(d);
     const int64_t nwaves = (static_cast<int64_t>(v.gmax) + 64 * kQRun - 1) / (64 * kQRun);
     const int64_t nsets = (nwaves + kQueryWaves - 1) / kQueryWaves;
