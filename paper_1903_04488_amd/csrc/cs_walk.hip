@@ -585,9 +585,9 @@ k_accumulate_visits(LIST rows, WorkersBeside<LIST> a) {
     static_assert(WL <= 8 && WL * PPL == RUN, "every coordinate of a walker gets a hash lane");
     // Two neighbouring cells of a bundle are one aligned 64-byte block when the lower one is
     // even, and leave as one request then: on average ncell / 2 + 1/2 requests per residue instead of ncell.  For
-    // that the sums go through LDS.  Only short vectors (RUN = 8) gain, whose time is mostly these
-    // requests; long ones stream meanwhile.
-constexpr bool kPairs = !PARTIAL && POW2 && RUN == 8;
+    // that the sums go through LDS.  (7 x 2^19, 25 M, 256 workers, whose 10 M requests a launch of 8 workers end each round:
+    // a step 33 450 / 32 870 us; 5 x 2^20, 10^8, and 5 x 2^18, 11 M, which have fewer of them to a byte read: the same.)
+constexpr bool kPairs = !PARTIAL && POW2;
     // Per wavefront: the value tile (one padded row per lane), the walkers' first cells and signs
     __shared__ float tile_lds_all[NWAVE][64 * kStride];
     __shared__ uint32_t first_lds_all[NWAVE][SPAN];
