@@ -123,6 +123,16 @@ typedef struct cs_anyc_plan {
     uint32_t gap[CS_ANYC_MAX_VISITS];   /* gap_k = s_{k+1} - s_k, s_0 = 0, s_K = d_hint */
 } cs_anyc_plan;
 
+/* The list that one vector by itself is sketched along where it is the cheaper one (power-of-two column counts): as
+ * cs_visit_plan, with up to CS_VECTOR_CELLS running sums.  It lies where sketches of other column counts have their
+ * cs_anyc_plan; `none` is that one's K and omega, 0 (no list of that kind).  list.K = 0: visit[] serves. */
+#define CS_VECTOR_CELLS 8
+typedef struct cs_vector_plan {
+    uint64_t none;
+    cs_visit_plan list;
+    uint8_t pad[sizeof(cs_anyc_plan) - sizeof(uint64_t) - sizeof(cs_visit_plan)];
+} cs_vector_plan;
+
 #define CS_FLAG_NO_VISIT_LIST 1u   /* cs_params.flags: always use the stride walk (testing) */
 #define CS_FLAG_NO_LDS_TABLE 2u    /* cs_params.flags: tiny tables are updated in memory, not in a
                                       workgroup-private LDS copy (testing) */
@@ -137,7 +147,10 @@ typedef struct cs_params {
     uint64_t as[CS_MAX_R], bs[CS_MAX_R];   /* sign hashes */
     cs_row_plan plan[CS_MAX_R];
     cs_visit_plan visit[CS_MAX_R];
-    cs_anyc_plan anyc[CS_MAX_R];
+    union {
+        cs_anyc_plan anyc[CS_MAX_R];        /* column counts that are not a power of two */
+        cs_vector_plan vector[CS_MAX_R];    /* powers of two */
+    };
 } cs_params;
 
 /* Alg. 4 init: fills *p for an r x c sketch from `seed` (host, no GPU needed).

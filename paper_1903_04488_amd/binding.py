@@ -58,7 +58,20 @@ class CsAnycPlan(ctypes.Structure):
         return [int(self.gap[k]) for k in range(self.K)]
 
 
+CS_VECTOR_CELLS = 8
+
+
+class CsVectorPlan(ctypes.Structure):
+    _fields_ = [("none", ctypes.c_uint64), ("list", CsVisitPlan),
+                ("pad", ctypes.c_uint8 * (ctypes.sizeof(CsAnycPlan) - 8 - ctypes.sizeof(CsVisitPlan)))]
+
+
+class _CsLists(ctypes.Union):
+    _fields_ = [("anyc", CsAnycPlan * CS_MAX_R), ("vector", CsVectorPlan * CS_MAX_R)]
+
+
 class CsParams(ctypes.Structure):
+    _anonymous_ = ("lists",)
     _fields_ = [("r", ctypes.c_uint32), ("c", ctypes.c_uint32),
                 ("c_pow2", ctypes.c_uint32), ("flags", ctypes.c_uint32),
                 ("seed", ctypes.c_uint64),
@@ -66,7 +79,7 @@ class CsParams(ctypes.Structure):
                 ("as_", ctypes.c_uint64 * CS_MAX_R), ("bs", ctypes.c_uint64 * CS_MAX_R),
                 ("plan", CsRowPlan * CS_MAX_R),
                 ("visit", CsVisitPlan * CS_MAX_R),
-                ("anyc", CsAnycPlan * CS_MAX_R)]
+                ("lists", _CsLists)]
 
 
 def library_path() -> str:

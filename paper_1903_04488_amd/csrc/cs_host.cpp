@@ -147,6 +147,21 @@ double update_time_ns(double visits, double residues, double requests, double d,
     return best;
 }
 
+// The same for one vector by itself, r rows alike in one launch.  Requests of 64 bytes at 21 G/s, of which a residue sends one or,
+// where its ncell cells lie across a boundary, two, are most of it; half of the reads, or a chain of visits of 450 ns
+// if that is longer, come on top.
+uint64_t vector_time_ns(double visits, double residues, uint32_t ncell, double d, double r) {
+    const double kVisitNs = 450.0, kBytesPerNs = 6800.0, kRequestsPerNs = 21.0;
+    const double stream = r * 4.0 * d / kBytesPerNs, requests = r * residues * (1.0 + (ncell - 1) / 16.0);
+    double best = 1e300;
+    for (double n = 1.0; n <= 32.0 && (n == 1.0 || visits / n >= 3.0); n += 1.0) {
+        const double chain = visits / n * kVisitNs;
+        const double t = (chain > 0.5 * stream ? chain : 0.5 * stream) + n * requests / kRequestsPerNs;
+        if (t < best) best = t;
+    }
+    return (uint64_t)best;
+}
+
 // Visit list of the bundle update for one row (cs_visit_plan).
 //
 // Rotating a hash value left by sh = 61 - log2(c) bits is a multiplication by 2^sh mod p, so
@@ -159,8 +174,11 @@ double update_time_ns(double visits, double residues, double requests, double d,
 // wide bound means many visits and few requests, a narrow one the opposite; the bound is
 // chosen by the time model above (one scan of s = 1 .. d - 1 collects the candidates for the
 // widest bound, narrower ones are subsets).
-void plan_visits(cs_visit_plan* vp, const cs_row_plan* rp, uint64_t a, uint64_t as, uint32_t c,
-                 bool pow2, uint64_t d_hint) {
+// One vector by itself is sketched along a list of its own (`vec`) where that pays: its cells are neighbours in 64 bytes, so a
+// residue sends one request or two however many running sums it has, and a wider bound, with fewer residues, sends
+// fewer in all.  Every list is a subset of one scan.
+void plan_visits(cs_visit_plan* vp, cs_visit_plan* vec, const cs_row_plan* rp, uint64_t a, uint64_t as, uint32_t c,
+                 bool pow2, uint64_t d_hint, uint32_t r) {
     memset(vp, 0, sizeof(*vp));
     if (!pow2 || c < 64 || d_hint < 4096 || d_hint > kPlanScanMax) return;
     int lc = 0;
@@ -183,25 +201,29 @@ void plan_visits(cs_visit_plan* vp, const cs_row_plan* rp, uint64_t a, uint64_t 
     if (omega_max > 3.0) omega_max = 3.0;
     if (omega_max * per_cell < 8.0) return;                // too few visits to pay off
     const uint64_t U_max = (uint64_t)(omega_max * (double)cell);
+    double omega_vec = (CS_MAX_VISITS - 16) / per_cell;
+    if (omega_vec > CS_VECTOR_CELLS - 1.0) omega_vec = CS_VECTOR_CELLS - 1.0;
+    const uint64_t U_vec = (uint64_t)(omega_vec * (double)cell);     // >= U_max
+    size_t in_bound = 0;                                   // candidates below U_max
     std::vector<uint64_t> cs_, cu_;                        // candidate offsets and their U
     {
         uint64_t u = 0;
         for (uint64_t s = 1; s < d_hint; ++s) {
             u += u1;
             if (u >= kP61) u -= kP61;
-            if (u < U_max) {
+            if (u < U_max || (u < U_vec && cs_.size() < 64 * CS_MAX_VISITS)) {
                 cs_.push_back(s);
                 cu_.push_back(u);
-                if (cs_.size() > 16 * CS_MAX_VISITS) return;   // not a rotation-like row: give up
+                if (u < U_max && ++in_bound > 16 * CS_MAX_VISITS) return;   // not a rotation-like row: give up
             }
         }
     }
-    uint64_t best_cost = ~0ull, best_bound = 0;
     constexpr int kGrid = 96;
-    for (int t = 1; t <= kGrid; ++t) {
-        const uint64_t bound = (uint64_t)((double)U_max * t / kGrid);
-        if (bound == 0) continue;
-        uint64_t prev = 0, gmax = 0, K = 1;
+    // visits and largest gap of the list below a bound
+    auto measure = [&](uint64_t bound, uint64_t& K, uint64_t& gmax) {
+        uint64_t prev = 0;
+        gmax = 0;
+        K = 1;
         for (size_t q = 0; q < cs_.size(); ++q)
             if (cu_[q] < bound) {
                 if (cs_[q] - prev > gmax) gmax = cs_[q] - prev;
@@ -209,48 +231,71 @@ void plan_visits(cs_visit_plan* vp, const cs_row_plan* rp, uint64_t a, uint64_t 
                 ++K;
             }
         if (d_hint - prev > gmax) gmax = d_hint - prev;
-        if (K < 4 || K > CS_MAX_VISITS) continue;
+        return K >= 4 && K <= CS_MAX_VISITS;
+    };
+    uint64_t best_cost = ~0ull, best_bound = 0;
+    for (int t = 1; t <= kGrid; ++t) {
+        const uint64_t bound = (uint64_t)((double)U_max * t / kGrid);
+        uint64_t K, gmax;
+        if (bound == 0 || !measure(bound, K, gmax)) continue;
         const uint64_t ncell = ((bound + cell - 1) >> sh) + 1;
         const uint64_t cost = (uint64_t)update_time_ns((double)K, (double)gmax,
                                                        (double)(ncell * gmax), (double)d_hint, true);
         if (cost < best_cost) { best_cost = cost; best_bound = bound; }
     }
     if (best_bound == 0) return;
-    // build the list for the chosen bound
-    uint64_t gaps[3], prev = 0;
-    int ngap = 0;
-    uint32_t K = 0;
-    auto add_visit = [&](uint64_t gap, bool last) -> bool {
-        int code = 3;
-        if (!last) {
-            for (code = 0; code < ngap; ++code)
-                if (gaps[code] == gap) break;
-            if (code == ngap) {
-                if (ngap == 3) return false;               // more than three return times
-                gaps[ngap++] = gap;
+    // the list for a bound
+    auto build = [&](cs_visit_plan* out, uint64_t bound, uint64_t cost) {
+        uint64_t gaps[3], prev = 0;
+        int ngap = 0;
+        uint32_t K = 0;
+        auto add_visit = [&](uint64_t gap, bool last) -> bool {
+            int code = 3;
+            if (!last) {
+                for (code = 0; code < ngap; ++code)
+                    if (gaps[code] == gap) break;
+                if (code == ngap) {
+                    if (ngap == 3) return false;           // more than three return times
+                    gaps[ngap++] = gap;
+                }
             }
+            out->code[K / 16] |= (uint32_t)code << (2 * (K % 16));
+            ++K;
+            return true;
+        };
+        for (size_t q = 0; q < cs_.size(); ++q)
+            if (cu_[q] < bound) {
+                if (!add_visit(cs_[q] - prev, false)) { memset(out->code, 0, sizeof(out->code)); return false; }
+                prev = cs_[q];
+            }
+        add_visit(d_hint - prev, true);
+        for (int q = 0; q < 4; ++q) {
+            const uint64_t gap = q < ngap ? gaps[q] : (q == 3 ? d_hint - prev : 0);
+            out->gap[q] = gap;
+            out->A[q] = mulmod(a, gap % kP61);
+            out->As[q] = mulmod(as, gap % kP61);
+            if (gap > out->gmax) out->gmax = gap;
         }
-        vp->code[K / 16] |= (uint32_t)code << (2 * (K % 16));
-        ++K;
+        out->ncell = (uint32_t)(((bound + cell - 1) >> sh) + 1);
+        out->cover = d_hint;
+        out->cost = cost;
+        out->cost_walk = vp->cost_walk;
+        out->K = K;
         return true;
     };
-    for (size_t q = 0; q < cs_.size(); ++q)
-        if (cu_[q] < best_bound) {
-            if (!add_visit(cs_[q] - prev, false)) { memset(vp->code, 0, sizeof(vp->code)); return; }
-            prev = cs_[q];
-        }
-    add_visit(d_hint - prev, true);
-    for (int q = 0; q < 4; ++q) {
-        const uint64_t gap = q < ngap ? gaps[q] : (q == 3 ? d_hint - prev : 0);
-        vp->gap[q] = gap;
-        vp->A[q] = mulmod(a, gap % kP61);
-        vp->As[q] = mulmod(as, gap % kP61);
-        if (gap > vp->gmax) vp->gmax = gap;
+    if (!build(vp, best_bound, best_cost)) return;
+    const uint64_t as_it_is = vector_time_ns((double)vp->K, (double)vp->gmax, vp->ncell, (double)d_hint, r);
+    if (cs_.size() >= 64 * CS_MAX_VISITS) return;
+    uint64_t best_vec = as_it_is - as_it_is / 8;
+    best_bound = 0;
+    for (int t = 1; t <= kGrid; ++t) {
+        const uint64_t bound = (uint64_t)((double)U_vec * t / kGrid);
+        uint64_t K, gmax;
+        if (bound == 0 || !measure(bound, K, gmax)) continue;
+        const uint64_t cost = vector_time_ns((double)K, (double)gmax, (uint32_t)(((bound + cell - 1) >> sh) + 1), (double)d_hint, r);
+        if (cost < best_vec) { best_vec = cost; best_bound = bound; }
     }
-    vp->ncell = (uint32_t)(((best_bound + cell - 1) >> sh) + 1);
-    vp->cover = d_hint;
-    vp->cost = best_cost;
-    vp->K = K;
+    if (best_bound) build(vec, best_bound, best_vec);
 }
 
 // Visit list for a column count that is not a power of two (cs_anyc_plan).
@@ -332,6 +377,24 @@ void plan_anyc(cs_anyc_plan* vp, uint64_t a, uint32_t c, bool pow2, uint64_t d_h
     }
 }
 
+// The lists of their own that single vectors have in some rows stay where they save 300 000 requests and a fifth of all: update of
+// one vector, us, without / with them: 5 x 2^20, 73 M (5.3 M requests, 2.5 M) 325 / 250, 25 M 251 / 149; 7 x 2^20, 50 M 403 / 329;
+// 7 x 65 536, 3 M (1.56 M, 1.16 M) 95 / 74; 5 x 2^17, 3 M (767 000, 413 000) 54 / 48.  Fewer saved cost more in pieces of longer
+// chains than they save: 5 x 2^18, 25 M (1.17 M, 0.99 M) 107 / 118; 15 x 8192, 1.3 M (612 000, 401 000) 74 / 83.
+void keep_vector_lists(cs_params* p) {
+    double base = 0.0, own = 0.0;
+    auto requests = [](const cs_visit_plan& v) { return (double)v.gmax * (1.0 + (v.ncell - 1) / 16.0); };
+    bool listed = true;
+    for (uint32_t j = 0; j < p->r; ++j) {
+        listed = listed && p->visit[j].K != 0;
+        if (!listed) break;
+        base += requests(p->visit[j]);
+        own += requests(p->vector[j].list.K ? p->vector[j].list : p->visit[j]);
+    }
+    if (listed && base - own >= 300e3 && own <= 0.8 * base) return;
+    for (uint32_t j = 0; j < p->r; ++j) memset(&p->vector[j], 0, sizeof(p->vector[j]));
+}
+
 }  // namespace
 
 extern "C" int cs_params_init(cs_params* p, uint32_t r, uint32_t c, uint64_t seed,
@@ -357,10 +420,11 @@ extern "C" int cs_params_init(cs_params* p, uint32_t r, uint32_t c, uint64_t see
     {
         plan_row(&p->plan[j], p->a[j], p->as[j], c, p->c_pow2 != 0, (uint64_t)d_hint);
         plan_walk(&p->plan[j], p->a[j], p->as[j], c, p->c_pow2 != 0, (uint64_t)d_hint);
-        plan_visits(&p->visit[j], &p->plan[j], p->a[j], p->as[j], c, p->c_pow2 != 0,
-                    (uint64_t)d_hint);
-        plan_anyc(&p->anyc[j], p->a[j], c, p->c_pow2 != 0, (uint64_t)d_hint);
+        plan_visits(&p->visit[j], &p->vector[j].list, &p->plan[j], p->a[j], p->as[j], c, p->c_pow2 != 0,
+                    (uint64_t)d_hint, r);
+        if (!p->c_pow2) plan_anyc(&p->anyc[j], p->a[j], c, false, (uint64_t)d_hint);
     }
+    if (p->c_pow2) keep_vector_lists(p);
     return CS_OK;
 }
 

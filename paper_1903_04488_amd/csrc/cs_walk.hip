@@ -429,7 +429,14 @@ __device__ __forceinline__ uint32_t threshold_of(uint64_t A) { return static_cas
 // A visit.  x: threshold of the bucket hash, y: of the sign hash, z: offset, w: bits 0..28 its gap (residues
 // that take part), bit 29 the parity of A', bits 30-31 A mod c (the running sum of a coordinate that does not
 // wrap), or 3 where that is none of the sums that are kept.
+// WIDE (more than four running sums): z has the third bit of A mod c in bit 31, and `none` is 7.
 constexpr uint32_t kGapMask = (1u << 29) - 1u;
+template <bool WIDE>
+__device__ __forceinline__ uint32_t place_of(uint4 e) { return WIDE ? e.z & 0x7fffffffu : e.z; }
+template <bool WIDE>
+__device__ __forceinline__ uint32_t sum_of_visit(uint4 e) { return e.w >> 30 | (WIDE ? e.z >> 31 << 2 : 0u); }
+template <bool WIDE>
+constexpr uint32_t kNoSum = WIDE ? 7u : 3u;
 constexpr int64_t kStepsMaxD = 1ll << 29;              // offsets and gaps of longer vectors do not fit
 
 // Offsets and gaps of the visits of a list, by the lanes of a wavefront together.  A power-of-two list has four gaps
@@ -496,8 +503,8 @@ struct VisitPlaces {
 __device__ __forceinline__ bool walks_down(uint32_t at_once) { return (blockIdx.x / at_once & 1u) == 0; }
 
 // The visits k0 .. k1 - 1, by all wavefronts of the workgroup, the last one first with `down`; returns how many of them are
-// not `3`.  within: A mod c must be below it.
-template <bool POW2, int NWAVE, typename ARGS>
+// not `none`.  within: A mod c must be below it.
+template <bool POW2, int NWAVE, bool WIDE = false, typename ARGS>
 __device__ __forceinline__ uint32_t fill_visit_steps(uint4* steps, const VisitPlaces& places, const ARGS& v, uint32_t k0,
                                                      uint32_t k1, const Columns& col, uint32_t within, bool down) {
     __shared__ uint32_t count[CS_MAX_VISITS / 64];
@@ -509,12 +516,13 @@ __device__ __forceinline__ uint32_t fill_visit_steps(uint4* steps, const VisitPl
         places.at(v, k, s, gap);
         const uint64_t A = mulmod_p(v.a, s), As = mulmod_p(v.as, s);
         const uint32_t cell = bucket_of<POW2>(A + 1, col);
-        const uint32_t q = cell < within ? cell : 3u;
-        const uint32_t listed = __builtin_popcountll(__builtin_amdgcn_ballot_w64(k < k1 && q < 3u));
+        const uint32_t q = cell < within ? cell : kNoSum<WIDE>;
+        const uint32_t listed = __builtin_popcountll(__builtin_amdgcn_ballot_w64(k < k1 && q < kNoSum<WIDE>));
         if (lane == 0) count[chunk] = listed;
         if (k < k1)
             steps[down ? k1 - 1 - k : k - k0] =
-                make_uint4(threshold_of(A), threshold_of(As), s, gap | static_cast<uint32_t>(As & 1u) << 29 | q << 30);
+                make_uint4(threshold_of(A), threshold_of(As), WIDE ? s | q >> 2 << 31 : s,
+                           gap | static_cast<uint32_t>(As & 1u) << 29 | q << 30);
     }
     __syncthreads();
     uint32_t listed = 0;
@@ -525,6 +533,7 @@ __device__ __forceinline__ uint32_t fill_visit_steps(uint4* steps, const VisitPl
 // The visits of steps[0 .. n) that are not `3` and that residues from first_res on take part in, one after the other: a list with one
 // short and one long gap leaves most walkers with few of its visits (K = 277, gaps 243 885 and 1 495 226:
 // 66 for five residues in six), and looking at 64 visits at once finds the next without stepping through the others.
+template <bool WIDE = false>
 struct VisitCursor {
     const uint4* steps;
     uint64_t todo;                                      // visits base .. base + 63 that are left
@@ -533,7 +542,8 @@ struct VisitCursor {
     __device__ __forceinline__ void look() {
         const uint32_t k = base + (threadIdx.x & 63);
         const uint4 e = steps[k < n ? k : 0];
-        todo = __builtin_amdgcn_ballot_w64(k < n && e.w >> 30 < 3u && (e.w & kGapMask) > first_res && e.z + first_res < d);
+        todo = __builtin_amdgcn_ballot_w64(k < n && sum_of_visit<WIDE>(e) < kNoSum<WIDE> && (e.w & kGapMask) > first_res &&
+                                          place_of<WIDE>(e) + first_res < d);
     }
     __device__ __forceinline__ VisitCursor(const uint4* steps_, uint32_t n_, uint32_t first_res_, uint32_t d_)
         : steps(steps_), base(0), n(n_), first_res(first_res_), d(d_) { look(); }
@@ -758,7 +768,7 @@ constexpr bool kPairs = !PARTIAL && POW2;
                 }
             }
         };
-        VisitCursor cursor(steps, k1 - k0, first_res, d);
+        VisitCursor<> cursor(steps, k1 - k0, first_res, d);
         uint32_t k = cursor.next();                    // the visit whose values are on their way
         uint4 e = steps[k == ~0u ? 0u : k];
         if (k != ~0u) load_visit(__builtin_amdgcn_readfirstlane(e.z), __builtin_amdgcn_readfirstlane(e.w));
@@ -965,8 +975,7 @@ bool choose_run8(LIST& rows, int nrows, const double* requests8, const double* r
     return false;
 }
 
-void fill_visit_args(const cs_params* p, uint32_t j, VisitArgs& v) {
-    const cs_visit_plan& vp = p->visit[j];
+void fill_visit_args(const cs_params* p, uint32_t j, const cs_visit_plan& vp, VisitArgs& v) {
     v.K = vp.K;
     v.j = static_cast<int32_t>(j);
     v.gmax = vp.gmax;
@@ -975,6 +984,8 @@ void fill_visit_args(const cs_params* p, uint32_t j, VisitArgs& v) {
     for (int t = 0; t < 4; ++t) v.gap[t] = vp.gap[t];
     for (int t = 0; t < CS_MAX_VISITS / 16; ++t) v.code[t] = vp.code[t];
 }
+
+void fill_visit_args(const cs_params* p, uint32_t j, VisitArgs& v) { fill_visit_args(p, j, p->visit[j], v); }
 
 // Workgroups of a launch of nrows rows whose gmax and pieces are set; fills in `blocks` and `first`.
 template <int WL, int RUN, int NWAVE, typename LIST>
@@ -1095,8 +1106,9 @@ constexpr int64_t kOneFewWaves = 300;
 template <int WL, int SETS, int NC, bool PARTIAL, typename LIST>
 __global__ void __launch_bounds__(64 * WL * SETS)
 k_accumulate_vectors(LIST rows, WorkersBeside<LIST> a) {
+    constexpr bool WIDE = NC > 4;
     constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
-    constexpr int SPAN = 64 * kOneRun, kRow = SPAN + 4;
+    constexpr int SPAN = 64 * kOneRun, kRow = SPAN + 4, kAhead = WIDE ? kOneAhead + 1 : kOneAhead;
     const unsigned row = row_of_block(rows);
     const auto& v = rows.at(row);
     const uint32_t piece = (blockIdx.x - rows.first[row]) / v.blocks;
@@ -1141,7 +1153,7 @@ k_accumulate_vectors(LIST rows, WorkersBeside<LIST> a) {
     const uint32_t k0 = v.K * piece / v.pieces, k1 = v.K * (piece + 1) / v.pieces;
     VisitPlaces places;
     places.init(v);
-    const uint32_t listed = fill_visit_steps<POW2, WL * SETS>(steps, places, v, k0, k1, col, omega, walks_down(a.at_once));
+    const uint32_t listed = fill_visit_steps<POW2, WL * SETS, WIDE>(steps, places, v, k0, k1, col, omega, walks_down(a.at_once));
     const uint32_t last4 = d - kOneRun;
 
     // sets of neighbouring wavefronts go to one XCD, as in k_accumulate_visits
@@ -1167,16 +1179,17 @@ k_accumulate_vectors(LIST rows, WorkersBeside<LIST> a) {
             }
             struct Step {                                   // a visit that was requested
                 vec4f x;
-                uint32_t tb, ts, s, w;                      // the step, as in steps[k]
+                uint32_t tb, ts, s, w, q;                   // the step, as in steps[k]
                 uint32_t k;                                 // ~0u for none
             };
-            VisitCursor cursor(steps, k1 - k0, wave_res, d);
+            VisitCursor<WIDE> cursor(steps, k1 - k0, wave_res, d);
             auto request = [&](Step& st) {
                 st.k = cursor.next();
                 const uint4 e = steps[st.k == ~0u ? 0u : st.k];
                 st.tb = e.x;
                 st.ts = e.y;
-                st.s = __builtin_amdgcn_readfirstlane(e.z);
+                st.s = __builtin_amdgcn_readfirstlane(place_of<WIDE>(e));
+                st.q = __builtin_amdgcn_readfirstlane(sum_of_visit<WIDE>(e));
                 st.w = __builtin_amdgcn_readfirstlane(e.w);
                 uint32_t at = st.s + my_res;
                 at = at < last4 ? at : last4;
@@ -1234,7 +1247,7 @@ k_accumulate_vectors(LIST rows, WorkersBeside<LIST> a) {
                 const uint32_t room = room_of(st.s, st.w);
                 vec4f x = st.x;
                 if (room < SPAN) x = cut(x, st.s, room);
-                if (cur != st.w >> 30) move_to(st.w >> 30);
+                if (cur != st.q) move_to(st.q);
                 uint64_t flips[kOneRun], wraps[kOneRun], unsure = 0;
 #pragma unroll
                 for (int m = 0; m < kOneRun; ++m) {
@@ -1264,14 +1277,14 @@ k_accumulate_vectors(LIST rows, WorkersBeside<LIST> a) {
                     wrapped[m] += wrap ? val : 0.0f;
                 }
             };
-            Step st[kOneAhead];
+            Step st[kAhead];
 #pragma unroll
-            for (int u = 0; u < kOneAhead; ++u) request(st[u]);
+            for (int u = 0; u < kAhead; ++u) request(st[u]);
             // (a buffer is refilled where it was read: moving a value that is still on its way would
             // wait for it)
             // (a break from every turn: where the turns meet again before the end is known, the wait for the oldest
             // values becomes one for all that are on their way)
-            static_assert(kOneAhead == 3, "a turn for each");
+            static_assert(kAhead == 3 || kAhead == 4, "a turn for each");
             for (;;) {
                 if (st[0].k == ~0u) break;
                 add_up(st[0]);
@@ -1282,6 +1295,11 @@ k_accumulate_vectors(LIST rows, WorkersBeside<LIST> a) {
                 if (st[2].k == ~0u) break;
                 add_up(st[2]);
                 request(st[2]);
+                if constexpr (kAhead > 3) {
+                    if (st[kAhead - 1].k == ~0u) break;
+                    add_up(st[kAhead - 1]);
+                    request(st[kAhead - 1]);
+                }
             }
             park(cur, plain);
             park(cur + (POW2 ? 1 : omega), wrapped);
@@ -1344,8 +1362,8 @@ k_accumulate_vectors(LIST rows, WorkersBeside<LIST> a) {
         // straight into memory
         if (!PARTIAL && listed < k1 - k0 && live && wv < nwaves) {
             for (uint32_t k = 0; k < k1 - k0; ++k) {
-                const uint32_t s = __builtin_amdgcn_readfirstlane(steps[k].z), w = __builtin_amdgcn_readfirstlane(steps[k].w);
-                if (w >> 30 < 3u || (w & kGapMask) <= my_res || s + my_res >= d) continue;
+                const uint32_t s = __builtin_amdgcn_readfirstlane(place_of<WIDE>(steps[k])), w = __builtin_amdgcn_readfirstlane(steps[k].w);
+                if (sum_of_visit<WIDE>(steps[k]) < kNoSum<WIDE> || (w & kGapMask) <= my_res || s + my_res >= d) continue;
                 const uint32_t in_gap = (w & kGapMask) - my_res, in_vec = d - s - my_res;
                 const uint32_t len = in_gap < in_vec ? in_gap : in_vec;
                 const uint32_t at = s + my_res;
@@ -1382,6 +1400,10 @@ int launch_vectors(LIST& rows, WorkersBeside<LIST> a, int n, uint32_t ncell, hip
         if (ncell == 4) return launch(sets, std::integral_constant<int, 4>());
         if constexpr (std::is_same<LIST, VisitRows>::value) {
             if (ncell == 3) return launch(sets, std::integral_constant<int, 3>());
+            if constexpr (WL == 1 && !PARTIAL) {
+                if (ncell > 4 && ncell <= 6) return launch(sets, std::integral_constant<int, 6>());
+                if (ncell > 6 && ncell <= CS_VECTOR_CELLS) return launch(sets, std::integral_constant<int, CS_VECTOR_CELLS>());
+            }
         }
         return CS_EINVAL;
     };
@@ -1697,13 +1719,24 @@ bool all_rows_listed(const cs_params* p, int64_t d) {
     return true;
 }
 
+// the list that one vector takes in row j
+static const cs_visit_plan& vector_list(const cs_params* p, uint32_t j, int64_t d) {
+    const cs_visit_plan& own = p->vector[j].list;
+    const bool serves = own.K != 0 && own.K <= CS_MAX_VISITS && own.ncell >= 2 && own.ncell <= CS_VECTOR_CELLS &&
+                        static_cast<uint64_t>(d) <= own.cover;
+    return serves ? own : p->visit[j];
+}
+
 // The lists serve the update of one vector: every row has one that covers d, and all of them
 // together send fewer requests than the lattice form (about one per 8 to 15 coordinates).
 bool one_applies(const cs_params* p, int64_t d) {
     double residues = 0.0;
     if (p->c_pow2) {
         if (!all_rows_listed(p, d)) return false;
-        for (uint32_t j = 0; j < p->r; ++j) residues += static_cast<double>(p->visit[j].gmax);
+        for (uint32_t j = 0; j < p->r; ++j) {
+            const cs_visit_plan& vp = vector_list(p, j, d);
+            residues += static_cast<double>(vp.gmax) * (vp.ncell > 4 ? (vp.ncell + 15) / 19.2 : 1.0);
+        }
     } else {
         if (!anyc_visits_apply(p, d)) return false;
         for (uint32_t j = 0; j < p->r; ++j) residues += static_cast<double>(p->anyc[j].gmax);
@@ -1714,9 +1747,9 @@ bool one_applies(const cs_params* p, int64_t d) {
 // S = float[r][c][cell_floats]: the table itself (1) or one worker's slot of a bundle (kGroup)
 int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const float* g, int64_t d,
                           int64_t i0, float scale, hipStream_t stream, int* launches) {
-    auto cut = [&](auto& rows, int n) {                // the chains of n rows into pieces
+    auto cut = [&](auto& rows, int n, double more) {   // the chains of n rows into pieces
         double requests[kRowsPerLaunch];
-        for (int q = 0; q < n; ++q) requests[q] = 1.2 * static_cast<double>(rows.row[q].gmax);
+        for (int q = 0; q < n; ++q) requests[q] = (1.2 + more) * static_cast<double>(rows.row[q].gmax);
         const double stream_ns = 4.0 * static_cast<double>(d) * n / kStreamBytesPerNs;
         choose_pieces(rows, n, requests, kVisitNsOne, stream_ns);
     };
@@ -1738,23 +1771,24 @@ int launch_accumulate_one(const cs_params* p, float* S, int cell_floats, const f
             }
             VisitGapsRows rows{};
             for (int q = 0; q < n; ++q) fill_visit_gaps(p, js[q], rows.row[q]);
-            cut(rows, n);
+            cut(rows, n, 0.0);
             VisitWorkersOf<1> a{};
             fill(a);
             return launch_vectors<1, false>(rows, a, n, 2 * omega, stream);
         });
     uint32_t order[CS_MAX_R], ncell = 2;
     for (uint32_t j = 0; j < p->r; ++j) {              // the longest lists first
-        if (p->visit[j].ncell > ncell) ncell = p->visit[j].ncell;
+        const cs_visit_plan& vp = vector_list(p, j, d);
+        if (vp.ncell > ncell) ncell = vp.ncell;
         int at = static_cast<int>(j);
-        for (; at > 0 && p->visit[order[at - 1]].K < p->visit[j].K; --at) order[at] = order[at - 1];
+        for (; at > 0 && vector_list(p, order[at - 1], d).K < vp.K; --at) order[at] = order[at - 1];
         order[at] = j;
     }
     for (uint32_t q0 = 0; q0 < p->r; q0 += kRowsPerLaunch) {
         const int n = p->r - q0 < kRowsPerLaunch ? static_cast<int>(p->r - q0) : kRowsPerLaunch;
         VisitRows rows{};
-        for (int q = 0; q < n; ++q) fill_visit_args(p, order[q0 + q], rows.row[q]);
-        cut(rows, n);
+        for (int q = 0; q < n; ++q) fill_visit_args(p, order[q0 + q], vector_list(p, order[q0 + q], d), rows.row[q]);
+        cut(rows, n, ncell > 4 ? (ncell - 4) / 16.0 : 0.0);
         VisitWorkers a{};
         fill(a);
         const int rc = launch_vectors<1, false>(rows, a, n, ncell, stream);
