@@ -285,7 +285,8 @@ void plan_visits(cs_visit_plan* vp, cs_visit_plan* vec, const cs_row_plan* rp, u
     };
     if (!build(vp, best_bound, best_cost)) return;
     const uint64_t as_it_is = vector_time_ns((double)vp->K, (double)vp->gmax, vp->ncell, (double)d_hint, r);
-    if (cs_.size() >= 64 * CS_MAX_VISITS) return;
+    // (rows that send less than their part of what keep_vector_lists asks for are not looked at)
+    if (cs_.size() >= 64 * CS_MAX_VISITS || (double)vp->gmax * r < 300e3) return;
     uint64_t best_vec = as_it_is - as_it_is / 8;
     best_bound = 0;
     for (int t = 1; t <= kGrid; ++t) {

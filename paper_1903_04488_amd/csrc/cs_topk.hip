@@ -21,8 +21,8 @@
 // A selection from at most kSmall entries is one launch of one workgroup that holds every key in
 // LDS (k_topk_small).
 //
-// k_topk_finish does the same with the candidates when there are at most kSmall of them: its
-// first workgroup does everything, the others return.  Longer lists, and inputs that do not fit
+// k_topk_finish does the same with the candidates when there are at most kSmall of them: its first
+// workgroups, up to 8, all find the key and each writes a share, the others return.  Longer lists, and inputs that do not fit
 // the list (many equal magnitudes, k close to d: decided on the device), are shared out among
 // the workgroups: the work is cut into 4 phases of T tasks, T workgroups draw tasks in order
 // from a counter, and before it starts a task it waits until every task of the phase before is
@@ -57,6 +57,8 @@ constexpr int kScanWaves = kScanBlock / 64;
 constexpr int kMaxSegs = 512;
 constexpr int kStage = 8192;          // candidates one block can hold in LDS for its chunk
 constexpr int kFinishBlocks = 256;
+// Workgroups that share a short list out among them (k_topk_finish), and the items of each at least.
+constexpr uint32_t kShares = 8, kShareItems = 2048;
 // Polls of a phase's counter, without a task of that phase ending in between, after which a wait is
 // given up: 1.4 s (a poll sleeps 512 cycles and reads memory, 0.33 us measured), plus one poll per
 // 16 entries of a task, forty times what a task with the chip to itself takes.
@@ -288,6 +290,19 @@ k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* 
     __shared__ uint32_t wave_n[kScanWaves];
     __shared__ uint32_t seg[2];                     // base, ok
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t lo = static_cast<int64_t>(blockIdx.x) * chunk;
+    const int64_t hi = (lo + chunk < d) ? lo + chunk : d;
+    const int64_t part = (chunk / kScanWaves + kWaveTile - 1) / kWaveTile * kWaveTile;
+    const int64_t wlo = lo + wave * part;
+    const int64_t whi = (wlo + part < hi) ? wlo + part : hi;
+    float v[kTiles][kItems];                        // the first tiles of my part are on their way while the bin is found
+    int n[kTiles];
+    auto load_tiles = [&](int64_t tile) {
+#pragma unroll
+        for (int u = 0; u < kTiles; ++u)
+            load_items<VEC>(est, tile + static_cast<int64_t>(lane) * kItems + u * kWaveTile, whi, v[u], n[u]);
+    };
+    load_tiles(wlo);
     uint32_t bin0;
     {
         constexpr int per = kBins / kScanBlock;
@@ -300,11 +315,6 @@ k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* 
             ws->k_rem = rem;
         }
     }
-    const int64_t lo = static_cast<int64_t>(blockIdx.x) * chunk;
-    const int64_t hi = (lo + chunk < d) ? lo + chunk : d;
-    const int64_t part = (chunk / kScanWaves + kWaveTile - 1) / kWaveTile * kWaveTile;
-    const int64_t wlo = lo + wave * part;
-    const int64_t whi = (wlo + part < hi) ? wlo + part : hi;
     uint32_t* my_off = st_off + wave * kWaveStage;
     float* my_val = st_val + wave * kWaveStage;
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));   // lanes before mine
@@ -345,11 +355,8 @@ k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* 
     };
     auto read_part = [&](bool direct, uint32_t at) {
         for (int64_t tile = wlo; tile < whi; tile += kTiles * kWaveTile) {
-            float v[kTiles][kItems];
-            int n[kTiles];
+            if (direct || tile != wlo) load_tiles(tile);
             const int64_t b0 = tile + static_cast<int64_t>(lane) * kItems;
-#pragma unroll
-            for (int u = 0; u < kTiles; ++u) load_items<VEC>(est, b0 + u * kWaveTile, whi, v[u], n[u]);
 #pragma unroll
             for (int u = 0; u < kTiles; ++u) take(v[u], n[u], b0 + u * kWaveTile, direct, at);
         }
@@ -409,8 +416,45 @@ struct SmallLds {
     uint64_t before[kKeep * kSelWaves];       // flags set before those 64 (low word: gt, high word: eq)
     uint64_t seg[kMaxSegs];                   // (selected before segment b) - (flags before its first item)
     uint64_t scan[kSelWaves], found[2];
+    uint64_t bin_sums[3][kSelWaves];          // find_bin_once, a set for each histogram
+    uint64_t bin[3][2];
     uint32_t heavy;
 };
+static_assert(sizeof(SmallLds) <= 160 * 1024, "the LDS of a CU");
+
+// find_bin in buffers that nothing else uses, so that it waits twice instead of four times; *all: the bin has no more
+// entries than are wanted.
+template <int PER>
+__device__ __forceinline__ void find_bin_once(const uint32_t (&cnt)[PER], uint64_t k_rem, uint64_t (&sums)[kSelWaves],
+                                              uint64_t (&found)[2], uint32_t* bin, uint64_t* rem, bool* all) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    uint64_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) mine += cnt[q];
+    uint64_t inc = row_inclusive_sum(mine);
+    inc = add_from_lane<0x142, 0xa>(inc);
+    inc = add_from_lane<0x143, 0xc>(inc);
+    if (lane == 63) sums[wave] = inc;
+    __syncthreads();
+    const uint64_t of_wave = lane < kSelWaves ? sums[lane] : 0;
+    const uint64_t upto = row_inclusive_sum(of_wave);
+    uint64_t acc = read_lane(upto, kSelWaves - 1) - (read_lane(upto - of_wave, wave) + inc);   // entries in bins above mine
+    if (acc < k_rem && k_rem <= acc + mine) {      // true for exactly one thread
+#pragma unroll
+        for (int q = PER - 1; q >= 0; --q) {
+            if (acc < k_rem && k_rem <= acc + cnt[q]) {
+                found[0] = static_cast<uint64_t>(threadIdx.x) * PER + q;
+                found[1] = (k_rem - acc) << 1 | (k_rem - acc == cnt[q] ? 1u : 0u);
+            }
+            acc += cnt[q];
+        }
+    }
+    __syncthreads();
+    *bin = static_cast<uint32_t>(found[0]);
+    *rem = found[1] >> 1;
+    *all = (found[1] & 1u) != 0;
+}
 
 // Selection among n <= kSmall items by one workgroup of kSelBlock threads that keeps their keys in
 // LDS: the remaining histograms in LDS, then one ballot per 64 items and kind (greater than
@@ -420,43 +464,77 @@ struct SmallLds {
 // [b seg_len, (b + 1) seg_len).  DIRECT: the items are est itself (index = position, one segment)
 // and the first histogram is taken here as well.
 // KEYED: their keys are in LDS already, each written by the thread that reads it here
+// Of `shares` workgroups that all call this on the same items, this one (`share`) writes the items of its part and returns how
+// many of its threads' items were heavy; with one, *out.n_heavy is written here.
 template <bool DIRECT, bool KEYED, typename KEY>
-__device__ __forceinline__ void select_in_workgroup(SmallLds& s, const float* __restrict__ val,
+__device__ __forceinline__ uint32_t select_in_workgroup(SmallLds& s, const float* __restrict__ val,
                                                     const int64_t* __restrict__ idx, uint32_t n,
                                                     uint32_t bin0, uint64_t k_rem,
                                                     const uint32_t* __restrict__ seg_base,
                                                     const uint32_t* __restrict__ seg_count, int nseg,
-                                                    uint32_t seg_tiles, const SelOut& out, const KEY& kf) {
+                                                    uint32_t seg_tiles, const SelOut& out, const KEY& kf, uint32_t share = 0,
+                                                    uint32_t shares = 1) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int kAhead = 4;                       // items of a thread whose index and value are on their way
+    const uint32_t rounds = (n + kSelBlock - 1) / kSelBlock;
+    const uint32_t from = rounds * share / shares * kSelBlock, upto = rounds * (share + 1) / shares * kSelBlock;
+    const uint32_t end = upto < n ? upto : n;
+    int64_t at[kAhead];
+    float x[kAhead];
+    auto load_ahead = [&](uint32_t p0) {
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const uint32_t p = p0 + q * kSelBlock < end ? p0 + q * kSelBlock : p0;
+            at[q] = DIRECT ? static_cast<int64_t>(p) : idx[p];
+            x[q] = val[p];
+        }
+    };
+    // What comes last is on its way from here on.
+    uint32_t base = 0, cnt_seg = 0;
+    if constexpr (!DIRECT)
+        if (tid < nseg) { base = seg_base[tid]; cnt_seg = seg_count[tid]; }
+    if (!KEYED && from + tid < end) load_ahead(from + tid);
+    for (int t = tid; t < kBins; t += kSelBlock) s.hist[t] = 0;
     if constexpr (!KEYED)
 #pragma unroll 8
         for (uint32_t p = tid; p < n; p += kSelBlock) s.key[p] = kf(val[p], DIRECT ? static_cast<int64_t>(p) : idx[p]);
     // (a thread reads back only keys that it wrote itself)
+    __syncthreads();
+    // The histogram of a pass is cleared by the threads that read it, for the next one; with a bin whose entries are all
+    // wanted the rest of the bits has nothing to decide: theta is then the key below that bin's first, none equal to it
+    // is wanted.  us of k_topk_finish, with all passes, seven waits in each and one workgroup for the write / so: d = 2^20, k = 1000
+    // 7.6 / 6.1; 11 M, k = 10 000 28.1 / 22.9; k_estimate_choose, 7 x 40, d = 784 11.1 / 9.6.
+    bool all_of_bin = false;
     if constexpr (DIRECT) {
-        for (int t = tid; t < kBins; t += kSelBlock) s.hist[t] = 0;
-        __syncthreads();
 #pragma unroll 4
         for (uint32_t p = tid; p < n; p += kSelBlock) atomicAdd(&s.hist[s.key[p] >> 20], 1u);
         __syncthreads();
-        const uint64_t cnt[2] = {s.hist[2 * tid], s.hist[2 * tid + 1]};
-        find_bin<kSelWaves, 2>(cnt, k_rem, s.scan, s.found, &bin0, &k_rem);
+        const uint32_t cnt[2] = {s.hist[2 * tid], s.hist[2 * tid + 1]};
+        s.hist[2 * tid] = s.hist[2 * tid + 1] = 0;
+        find_bin_once(cnt, k_rem, s.bin_sums[0], s.bin[0], &bin0, &k_rem, &all_of_bin);
     }
     uint32_t theta = bin0;
+    int shift = 20;                                 // of theta
 #pragma unroll
     for (int pass = 1; pass <= 2; ++pass) {         // bits 19..10, then 9..0
-        const int shift = pass == 1 ? 10 : 0;
-        s.hist[tid] = 0;
-        __syncthreads();
+        if (all_of_bin && theta != 0) break;
+        shift -= 10;
+        uint32_t* hist = s.hist + (DIRECT ? 0 : (pass - 1) * 1024);
 #pragma unroll 4
         for (uint32_t p = tid; p < n; p += kSelBlock) {
             const uint32_t key = s.key[p];
-            if ((key >> (shift + 10)) == theta) atomicAdd(&s.hist[(key >> shift) & 1023u], 1u);
+            if ((key >> (shift + 10)) == theta) atomicAdd(&hist[(key >> shift) & 1023u], 1u);
         }
         __syncthreads();
-        const uint64_t cnt[1] = {s.hist[tid]};
+        const uint32_t cnt[1] = {hist[tid]};
+        if (DIRECT) hist[tid] = 0;
         uint32_t bin;
-        find_bin<kSelWaves, 1>(cnt, k_rem, s.scan, s.found, &bin, &k_rem);
+        find_bin_once(cnt, k_rem, s.bin_sums[pass], s.bin[pass], &bin, &k_rem, &all_of_bin);
         theta = (theta << 10) | bin;
+    }
+    if (shift > 0) {
+        theta = (theta << shift) - 1u;
+        k_rem = 0;
     }
     const uint64_t need_eq = k_rem;
     const int groups = static_cast<int>((n + 63) / 64);       // of 64 items
@@ -493,9 +571,7 @@ __device__ __forceinline__ void select_in_workgroup(SmallLds& s, const float* __
                               (static_cast<uint64_t>(__builtin_popcountll(s.mask_eq[t] & low)) << 32));
     };
     if constexpr (!DIRECT) {                        // two 32-bit counters side by side, modulo 2^32 each
-        uint32_t base = 0, cnt = 0;
-        if (tid < nseg) { base = seg_base[tid]; cnt = seg_count[tid]; }
-        const uint64_t f0 = cnt ? flags_before(base) : 0, f1 = cnt ? flags_before(base + cnt) : 0;
+        const uint64_t f0 = cnt_seg ? flags_before(base) : 0, f1 = cnt_seg ? flags_before(base + cnt_seg) : 0;
         const uint64_t b = block_exclusive_sum<kSelWaves>(f1 - f0, s.scan, &all);
         if (tid < nseg)
             s.seg[tid] = static_cast<uint32_t>(static_cast<uint32_t>(b) - static_cast<uint32_t>(f0)) |
@@ -503,20 +579,12 @@ __device__ __forceinline__ void select_in_workgroup(SmallLds& s, const float* __
         __syncthreads();
     }
     uint32_t heavy = 0;
-    constexpr int kAhead = 4;                       // items of a thread whose index and value are on their way
-    for (uint32_t p0 = tid; p0 < n; p0 += kAhead * kSelBlock) {
-        int64_t at[kAhead];
-        float x[kAhead];
-#pragma unroll
-        for (int q = 0; q < kAhead; ++q) {
-            const uint32_t p = p0 + q * kSelBlock < n ? p0 + q * kSelBlock : p0;
-            at[q] = DIRECT ? static_cast<int64_t>(p) : idx[p];
-            x[q] = val[p];
-        }
+    for (uint32_t p0 = from + tid; p0 < end; p0 += kAhead * kSelBlock) {
+        if (KEYED || p0 != from + tid) load_ahead(p0);
 #pragma unroll
         for (int q = 0; q < kAhead; ++q) {
             const uint32_t p = p0 + q * kSelBlock;
-            if (p >= n) break;
+            if (p >= end) break;
             const uint32_t key = s.key[p];
             const bool is_gt = key > theta, is_eq = key == theta;
             if (!(is_gt || is_eq)) continue;
@@ -536,8 +604,9 @@ __device__ __forceinline__ void select_in_workgroup(SmallLds& s, const float* __
     if (out.n_heavy) {
         if (heavy) atomicAdd(&s.heavy, heavy);
         __syncthreads();
-        if (tid == 0) *out.n_heavy = s.heavy;
+        if (tid == 0 && shares == 1) *out.n_heavy = s.heavy;
     }
+    return out.n_heavy ? s.heavy : 0u;
 }
 
 template <typename KEY>
@@ -594,10 +663,22 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
     const bool from_list = listed && ws->failed == 0;
     const uint32_t n = from_list ? ws->ncand : 0u;
     if (from_list && n <= kSmall) {
-        if (blockIdx.x != 0) return;
-        select_in_workgroup<false, false>(s, cand_val, cand_idx, n, ws->prefix, ws->k_rem, ws->seg_base, ws->seg_count,
-                                   nseg, seg_tiles, out, kf);
-        if (tid == 0) ws->ncand = 0;
+        // Finding theta and counting take a workgroup 4 us and the slots and the write, 100 instructions an item, several times
+        // that: every workgroup of up to kShares finds and counts, and writes its share.
+        const uint32_t most = (n + kShareItems - 1) / kShareItems, shares = most < kShares ? most < 1 ? 1 : most : kShares;
+        if (blockIdx.x >= shares) return;
+        const uint32_t heavy = select_in_workgroup<false, false>(s, cand_val, cand_idx, n, ws->prefix, ws->k_rem, ws->seg_base,
+                                                                 ws->seg_count, nseg, seg_tiles, out, kf, blockIdx.x, shares);
+        if (tid != 0) return;
+        if (shares > 1) {                              // the last one through puts the workspace back as it was
+            if (heavy) __hip_atomic_fetch_add(&ws->heavy, heavy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (atomicAdd(&ws->exits, 1u) + 1 != shares) return;
+            if (out.n_heavy) *out.n_heavy = load_shared(&ws->heavy);
+            ws->exits = 0;
+            ws->heavy = 0;
+        }
+        ws->ncand = 0;
         return;
     }
     // 4096 entries per task: a phase is then one load per thread.  What the phases hand on (the
