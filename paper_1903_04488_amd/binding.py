@@ -250,13 +250,19 @@ def _address(t: torch.Tensor, dtype, name: str, numel: int | None = None) -> int
     return t.data_ptr()
 
 
-def _dev(t: torch.Tensor, dtype, name: str, numel: int | None = None):
-    return ctypes.c_void_p(_address(t, dtype, name, numel))
+def _dev(t: torch.Tensor, dtype, name: str, numel: int | None = None) -> int:
+    # A step of a short vector waits for the host, and its calls check twenty tensors: one expression for those that are fine,
+    # the address as it is (a ctypes object for it is as dear as two of the checks).  d = 784, W = 4: 27 us of host work a step,
+    # 22.5 with this, _bundle_floats and the loop in _ptr_array.
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype and t.is_contiguous()
+            and (numel is None or t.numel() == numel)):
+        return t.data_ptr()
+    return _address(t, dtype, name, numel)
 
 
-def _stream(t: torch.Tensor):
+def _stream(t: torch.Tensor) -> int:
     # the raw handle: building a torch.cuda.Stream object for it costs ten times as much
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(t.device.index))
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 
 class DeviceVectors(tuple):
@@ -279,18 +285,25 @@ def _ptr_array(tensors, dtype, name, numel=None):
             raise CsError(f"{name} must hold vectors of {numel} elements of {dtype}")
         return tensors.ptrs
     try:
-        fine = all(t.is_cuda and t.dtype == dtype and t.is_contiguous() and (numel is None or t.numel() == numel)
-                   for t in tensors)
+        for t in tensors:
+            if not (t.is_cuda and t.dtype is dtype and t.is_contiguous() and (numel is None or t.numel() == numel)):
+                break
+        else:
+            return (ctypes.c_void_p * len(tensors))(*[t.data_ptr() for t in tensors])
     except AttributeError:
-        fine = False
-    if not fine:                                     # names the one that is not
-        for w, t in enumerate(tensors):
-            _address(t, dtype, f"{name}[{w}]", numel)
+        pass
+    for w, t in enumerate(tensors):                  # names the one that is not
+        _address(t, dtype, f"{name}[{w}]", numel)
     return (ctypes.c_void_p * len(tensors))(*[t.data_ptr() for t in tensors])
 
 
 def _cells(p: CsParams) -> int:
-    return int(p.r) * int(p.c)
+    return p.r * p.c
+
+
+def _bundle_floats(p: CsParams, W: int) -> int:
+    """what cs_bundle_floats says (W >= 1)"""
+    return -(-W // CS_BUNDLE_GROUP) * CS_BUNDLE_GROUP * p.r * p.c
 
 
 # ------------------------------------------------------------------------------------------
@@ -584,11 +597,10 @@ def cs_bundle_sketch_lists(p, T, g_w, lists, scale: float = 1.0, S_t=None, alpha
     W = len(g_w)
     if W == 0:
         raise CsError("g_w must be a non-empty list")
-    d = g_w[0].numel()
-    none = ctypes.c_void_p(0)
-    table = lambda t, name: none if t is None else _dev(t, torch.float32, name, _cells(p))      # noqa: E731
+    d, n = g_w[0].numel(), _cells(p)
+    table = lambda t, name: None if t is None else _dev(t, torch.float32, name, n)              # noqa: E731
     _check(load_library().cs_bundle_sketch_lists(
-        ctypes.byref(p), none if T is None else _dev(T, torch.float32, "T", cs_bundle_floats(p, W)), W,
+        ctypes.byref(p), None if T is None else _dev(T, torch.float32, "T", _bundle_floats(p, W)), W,
         _ptr_array(g_w, torch.float32, "g_w", d), d, scale, _dev(lists, torch.uint8, "lists"), lists.numel(),
         table(S_t, "S_t"), alpha, table(S_u, "S_u"), table(S_v, "S_v"), rho, _stream(lists)), "cs_bundle_sketch_lists")
 

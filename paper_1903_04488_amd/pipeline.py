@@ -246,7 +246,10 @@ class HotPath:
 
     def _not_overridden(self, *stages):
         cls, own = type(self), self.__dict__
-        return all(getattr(cls, x) is getattr(HotPath, x) and x not in own for x in stages)
+        for x in stages:
+            if x in own or (cls is not HotPath and getattr(cls, x) is not getattr(HotPath, x)):
+                return False
+        return True
 
     def sketch_and_aggregate(self, g_w):
         """accumulate, merge and momentum: the last two come out of the pass that writes the tables, where there
