@@ -2085,6 +2085,7 @@ __device__ __forceinline__ void store_values(float* p, vec4f u) {
 // the end; a workgroup of kHistWaves wavefronts shares one set of counters (8 KB), so that LDS
 // does not limit how many wavefronts a CU holds.
 constexpr int kHistWaves = 4;
+constexpr int kQAheadRows = 7;                         // up to so many rows the next visit's values are in registers too
 template <int RF, bool HIST, bool LINES>
 __global__ void __launch_bounds__(HIST ? 64 * kHistWaves : 64)
 k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int64_t d, int64_t i0,
@@ -2185,23 +2186,28 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
         };
         load_cells();
         uint64_t A = 0, As_n = 0;                                // how far the visit moves every hash on
-        for (int64_t nD = nD0; nD < nD1 && nD + wave_off < d; nD += D) {
+        // with LINES the wavefront writes from its first whole line on, and on into the line of its last residue
+        auto turn_of = [&](int64_t nD) -> uint32_t {
+            return LINES ? (0u - (line0 + static_cast<uint32_t>(nD + wave_off))) % kQLine : 0u;
+        };
+        // The other rows' values of a visit; where its four do not exist, four that do.
+        constexpr int kOther = RF > 1 ? RF - 1 : 1;
+        auto request = [&](vec4f (&other)[kOther], int64_t nD) {
+            if constexpr (RF > 1) {
+                const int64_t at = nD + my_off + turn_of(nD), last = d - kQRun;
+                const float* from = rows + (at < last ? at : last);
+#pragma unroll
+                for (int z = 0; z < RF - 1; ++z) other[z] = load_values<LINES>(from + static_cast<size_t>(z) * d);
+            }
+        };
+        auto visit = [&](int64_t nD, const vec4f (&other)[kOther]) {
             // residues from wave_off on that exist
             const int64_t in_gap = D - wave_off, in_vec = d - nD - wave_off;
             const int64_t room = in_gap < in_vec ? in_gap : in_vec;
             const int len = static_cast<int>(room < kQWave + kQLine ? room : kQWave + kQLine);
-            // with LINES the wavefront writes from its first whole line on, and on into the line of its last residue
-            const uint32_t t = LINES ? (0u - (line0 + static_cast<uint32_t>(nD + wave_off))) % kQLine : 0u;
+            const uint32_t t = turn_of(nD);
             const int my_len = len - static_cast<int>(t) - lane * kQRun;      // of the 4 that I write: >= 4 all, <= 0 none
             const int64_t at = nD + my_off + t;
-            [[maybe_unused]] vec4f other[RF > 1 ? RF - 1 : 1];       // the other rows' values, requested early
-            if constexpr (RF > 1) {
-                if (my_len >= kQRun) {
-#pragma unroll
-                    for (int z = 0; z < RF - 1; ++z)
-                        other[z] = load_values<LINES>(rows + static_cast<size_t>(z) * d + at);
-                }
-            }
             if ((static_cast<uint32_t>(A) & mask) != q) {
                 const uint32_t q_new = static_cast<uint32_t>(A) & mask;
                 const uint32_t by = (down ? q - q_new : q_new - q) & mask;
@@ -2279,7 +2285,7 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
                     est[nD + lane] = med;
                     tally(med);
                 }
-                continue;
+                return;
             }
             // the wavefront's 64 pieces are 1 KB of contiguous rows[j][i]
             float* dst = out + at;
@@ -2291,6 +2297,31 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
                 if (my_len > 2) dst[2] = mine.z;
             }
             if (heads) out[nD + lane] = head;
+        };
+        auto there = [&](int64_t nD) { return nD < nD1 && nD + wave_off < d; };
+        // The last row's wavefronts alone do not fill the chip, and a visit is one round of loads: the next visit's
+        // are under way meanwhile (a buffer for each of two turns: moving a value that is on its way would wait for it).
+        // us of the last row, without / with: 6.5 M, 5 x 2^17 36.3 / 30.8; 11 M, 5 x 2^18 45.1 / 44.6; 25 M, 5 x 2^19 106 / 106.
+        vec4f one[kOther];
+        if constexpr (RF > 1 && RF <= kQAheadRows) {
+            vec4f two[kOther];
+            int64_t nD = nD0;
+            if (there(nD)) request(one, nD);
+            for (;;) {
+                if (!there(nD)) break;
+                request(two, nD + D);
+                visit(nD, one);
+                nD += D;
+                if (!there(nD)) break;
+                request(one, nD + D);
+                visit(nD, two);
+                nD += D;
+            }
+        } else {
+            for (int64_t nD = nD0; there(nD); nD += D) {
+                request(one, nD);
+                visit(nD, one);
+            }
         }
     }
     if (HIST) {
