@@ -204,8 +204,8 @@ void plan_visits(cs_visit_plan* vp, cs_visit_plan* vec, const cs_row_plan* rp, u
     double omega_vec = (CS_MAX_VISITS - 16) / per_cell;
     if (omega_vec > CS_VECTOR_CELLS - 1.0) omega_vec = CS_VECTOR_CELLS - 1.0;
     const uint64_t U_vec = (uint64_t)(omega_vec * (double)cell);     // >= U_max
-    size_t in_bound = 0;                                   // candidates below U_max
-    std::vector<uint64_t> cs_, cu_;                        // candidate offsets and their U
+    std::vector<uint64_t> cs_, cu_;                        // candidate offsets and their U, below U_vec
+    std::vector<uint64_t> bs_, bu_;                        // those below U_max
     {
         uint64_t u = 0;
         for (uint64_t s = 1; s < d_hint; ++s) {
@@ -214,20 +214,25 @@ void plan_visits(cs_visit_plan* vp, cs_visit_plan* vec, const cs_row_plan* rp, u
             if (u < U_max || (u < U_vec && cs_.size() < 64 * CS_MAX_VISITS)) {
                 cs_.push_back(s);
                 cu_.push_back(u);
-                if (u < U_max && ++in_bound > 16 * CS_MAX_VISITS) return;   // not a rotation-like row: give up
+                if (u < U_max) {
+                    bs_.push_back(s);
+                    bu_.push_back(u);
+                    if (bs_.size() > 16 * CS_MAX_VISITS) return;   // not a rotation-like row: give up
+                }
             }
         }
     }
-    constexpr int kGrid = 96;
+    constexpr int kGrid = 96, kGridVec = 42;
+    typedef std::vector<uint64_t> list;
     // visits and largest gap of the list below a bound
-    auto measure = [&](uint64_t bound, uint64_t& K, uint64_t& gmax) {
+    auto measure = [&](const list& at, const list& U, uint64_t bound, uint64_t& K, uint64_t& gmax) {
         uint64_t prev = 0;
         gmax = 0;
         K = 1;
-        for (size_t q = 0; q < cs_.size(); ++q)
-            if (cu_[q] < bound) {
-                if (cs_[q] - prev > gmax) gmax = cs_[q] - prev;
-                prev = cs_[q];
+        for (size_t q = 0; q < at.size(); ++q)
+            if (U[q] < bound) {
+                if (at[q] - prev > gmax) gmax = at[q] - prev;
+                prev = at[q];
                 ++K;
             }
         if (d_hint - prev > gmax) gmax = d_hint - prev;
@@ -237,7 +242,7 @@ void plan_visits(cs_visit_plan* vp, cs_visit_plan* vec, const cs_row_plan* rp, u
     for (int t = 1; t <= kGrid; ++t) {
         const uint64_t bound = (uint64_t)((double)U_max * t / kGrid);
         uint64_t K, gmax;
-        if (bound == 0 || !measure(bound, K, gmax)) continue;
+        if (bound == 0 || !measure(bs_, bu_, bound, K, gmax)) continue;
         const uint64_t ncell = ((bound + cell - 1) >> sh) + 1;
         const uint64_t cost = (uint64_t)update_time_ns((double)K, (double)gmax,
                                                        (double)(ncell * gmax), (double)d_hint, true);
@@ -289,10 +294,10 @@ void plan_visits(cs_visit_plan* vp, cs_visit_plan* vec, const cs_row_plan* rp, u
     if (cs_.size() >= 64 * CS_MAX_VISITS || (double)vp->gmax * r < 300e3) return;
     uint64_t best_vec = as_it_is - as_it_is / 8;
     best_bound = 0;
-    for (int t = 1; t <= kGrid; ++t) {
-        const uint64_t bound = (uint64_t)((double)U_vec * t / kGrid);
+    for (int t = 1; t <= kGridVec; ++t) {
+        const uint64_t bound = (uint64_t)((double)U_vec * t / kGridVec);
         uint64_t K, gmax;
-        if (bound == 0 || !measure(bound, K, gmax)) continue;
+        if (bound == 0 || !measure(cs_, cu_, bound, K, gmax)) continue;
         const uint64_t cost = vector_time_ns((double)K, (double)gmax, (uint32_t)(((bound + cell - 1) >> sh) + 1), (double)d_hint, r);
         if (cost < best_vec) { best_vec = cost; best_bound = bound; }
     }

@@ -1090,8 +1090,11 @@ int launch_visits_run(LIST& rows, WorkersBeside<LIST> a, int nrows, uint32_t nce
 // part in or not -> now): d = 73 M, 5 x 2^20 468 -> 326; d = 25 M, 5 x 2^19 176 -> 137; d = 11 M, 5 x 2^18 102 -> 74;
 // d = 73 M, 5 x 180 000 492 -> 445; with waits for one visit's values at a time 338 -> 325, 126 -> 122, 73 -> 72, 434 -> 435 (of
 // another machine).  Bound: the requests at the end (without them 216, 92, 43 and 227 us, which
-// is the five reads, 1.46 GB at 73 M by the counters too, at 6.8 TB/s; with them 1.63 GB at 4.8); 2 and 4 loads ahead and 2
-// and 8 wavefronts per workgroup: within 4 % either way.
+// is the five reads, 1.46 GB at 73 M by the counters too, at 6.8 TB/s; with them 1.63 GB at 4.8), 64 bytes each and 21 G/s, so that
+// for one vector a residue's sums cost one or two however many they are: along lists of its own with up to CS_VECTOR_CELLS of them
+// 73 M takes 250, 25 M, 5 x 2^20 149 (250 before).  With more than 4 sums a CU holds 12 to 16 wavefronts instead of 24, so
+// that each has a load more on its way.  2 and 4 loads ahead and 2
+// and 8 wavefronts per workgroup, with up to 4 sums: within 4 % either way.
 // Several vectors: against k_accumulate_visits, whose lanes are walkers times workers, the comparisons are made once per vector
 // instead of once per walker, but no value goes through LDS, four times as many wavefronts have a quarter of the work
 // each, and 24 of them on a CU have 72 KB of reads in flight instead of 48.  The memory-side cache answers that with 6.4 TB/s for
@@ -1728,20 +1731,26 @@ static const cs_visit_plan& vector_list(const cs_params* p, uint32_t j, int64_t 
 }
 
 // The lists serve the update of one vector: every row has one that covers d, and all of them
-// together send fewer requests than the lattice form (about one per 8 to 15 coordinates).
+// together send fewer requests than the lattice form (about one per 8 to 15 coordinates).  Lists of its own count where one launch
+// takes all rows, and with more than 5 rows for less (us, lattice / lists: 3 x 2^20, 5.2 M 99 / 68, 10.5 M 139 / 72; 5 x 2^20,
+// 4.2 M 142 / 129, 8.4 M 218 / 134; 7 x 2^20, 8.4 M 294 / 240, but 6.3 M 228 / 237; 15 x 65 536, 1 M 71 / 106; 15 x 2^18, 5.2 M
+// 315 / 410).
 bool one_applies(const cs_params* p, int64_t d) {
-    double residues = 0.0;
+    double residues = 0.0, own = 0.0;
     if (p->c_pow2) {
         if (!all_rows_listed(p, d)) return false;
         for (uint32_t j = 0; j < p->r; ++j) {
             const cs_visit_plan& vp = vector_list(p, j, d);
-            residues += static_cast<double>(vp.gmax) * (vp.ncell > 4 ? (vp.ncell + 15) / 19.2 : 1.0);
+            residues += static_cast<double>(p->visit[j].gmax);
+            own += static_cast<double>(vp.gmax) * (vp.ncell > 4 ? (vp.ncell + 15) / 19.2 : 1.0);
         }
     } else {
         if (!anyc_visits_apply(p, d)) return false;
         for (uint32_t j = 0; j < p->r; ++j) residues += static_cast<double>(p->anyc[j].gmax);
+        own = residues;
     }
-    return 1.2 * residues <= static_cast<double>(p->r) * static_cast<double>(d) / 8.0;
+    const double most = static_cast<double>(p->r) * static_cast<double>(d) / 8.0;
+    return 1.2 * residues <= most || (p->r <= kRowsPerLaunch && 1.2 * own <= (p->r > 5 ? 0.85 : 1.0) * most);
 }
 
 // S = float[r][c][cell_floats]: the table itself (1) or one worker's slot of a bundle (kGroup)

@@ -39,7 +39,7 @@ def test_kept_only_where_they_save_requests(r, c, d):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("forged", [False, True])
-@pytest.mark.parametrize("r,c,planned", SHAPES)
+@pytest.mark.parametrize("r,c,planned", SHAPES + [(3, 1 << 20, 5_242_881), (7, 1 << 20, 8_388_609)])
 def test_one_vector(r, c, planned, forged):
     p = cs.cs_params_init(r, c, 190304488, planned)
     plain = cs.CsParams.from_buffer_copy(p)
