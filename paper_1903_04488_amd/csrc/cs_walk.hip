@@ -2094,7 +2094,12 @@ __device__ __forceinline__ void store_values(float* p, vec4f u) {
 // the end; a workgroup of kHistWaves wavefronts shares one set of counters (8 KB), so that LDS
 // does not limit how many wavefronts a CU holds.
 constexpr int kHistWaves = 4;
-constexpr int kQAheadRows = 7;                         // up to so many rows the next visit's values are in registers too
+// The last row's wavefronts alone do not fill the chip, and a visit is one round of loads: where the next visit's are under way
+// meanwhile (us of the query, without / with): 3 rows, 9.8 M, vectors of 8 workers read before it 67 / 57; 16 M 85.5 / 84; 32 M 165 / 161;
+// 5 rows, 6.5 M, 8 workers 72.6 / 64.8, 11.2 M 106 / 97, 14.7 M 137 / 125, one worker 13.9 M 143 / 135, but 5 x 65 536, 6.7 M 66.5 / 67.9.
+// The registers of more rows cost a wavefront a SIMD: 7 rows of 12 M 138 / 142, 17 M 191 / 201; and 5 rows past the caches find memory
+// busy as it is: 17 M 137 / 143, 27 M 199 / 206.
+constexpr bool query_reads_ahead(int RF, bool LINES) { return RF == 3 || (RF == 5 && !LINES); }
 template <int RF, bool HIST, bool LINES>
 __global__ void __launch_bounds__(HIST ? 64 * kHistWaves : 64)
 k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int64_t d, int64_t i0,
@@ -2104,6 +2109,7 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
     static_assert(!HIST || RF > 0, "only the kernel that writes est can count it");
     constexpr int NW = HIST ? kHistWaves : 1;          // wavefronts per workgroup
     constexpr int kOwn = kQRun + (LINES ? 1 : 0);
+    constexpr bool kAhead = query_reads_ahead(RF, LINES);
     const int lane = threadIdx.x & 63;
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int j = RF ? RF - 1 : 0;
@@ -2195,141 +2201,135 @@ k_row_values_walk(KParams p, RowSegments segs, const float* __restrict__ S, int6
         };
         load_cells();
         uint64_t A = 0, As_n = 0;                                // how far the visit moves every hash on
+        auto there = [&](int64_t nD) { return nD < nD1 && nD + wave_off < d; };
         // with LINES the wavefront writes from its first whole line on, and on into the line of its last residue
-        auto turn_of = [&](int64_t nD) -> uint32_t {
+        auto skipped = [&](int64_t nD) -> uint32_t {
             return LINES ? (0u - (line0 + static_cast<uint32_t>(nD + wave_off))) % kQLine : 0u;
         };
-        // The other rows' values of a visit; where its four do not exist, four that do.
-        constexpr int kOther = RF > 1 ? RF - 1 : 1;
-        auto request = [&](vec4f (&other)[kOther], int64_t nD) {
-            if constexpr (RF > 1) {
-                const int64_t at = nD + my_off + turn_of(nD), last = d - kQRun;
-                const float* from = rows + (at < last ? at : last);
+        // The other rows' values of two visits (a buffer for each of two turns: moving a value that is on its way would
+        // wait for it).  kAhead: where a lane's four do not exist, four that do, which it does not use.
+        constexpr int kTurns = kAhead ? 2 : 1;
+        [[maybe_unused]] vec4f others[kTurns][RF > 1 ? RF - 1 : 1];
+        [[maybe_unused]] auto request = [&](vec4f (&other)[RF > 1 ? RF - 1 : 1], int64_t nD) {
+            const int64_t at = nD + my_off + skipped(nD), last = d - kQRun;
+            const float* from = rows + (at < last ? at : last);
 #pragma unroll
-                for (int z = 0; z < RF - 1; ++z) other[z] = load_values<LINES>(from + static_cast<size_t>(z) * d);
-            }
+            for (int z = 0; z < RF - 1; ++z) other[z] = load_values<LINES>(from + static_cast<size_t>(z) * d);
         };
-        auto visit = [&](int64_t nD, const vec4f (&other)[kOther]) {
-            // residues from wave_off on that exist
-            const int64_t in_gap = D - wave_off, in_vec = d - nD - wave_off;
-            const int64_t room = in_gap < in_vec ? in_gap : in_vec;
-            const int len = static_cast<int>(room < kQWave + kQLine ? room : kQWave + kQLine);
-            const uint32_t t = turn_of(nD);
-            const int my_len = len - static_cast<int>(t) - lane * kQRun;      // of the 4 that I write: >= 4 all, <= 0 none
-            const int64_t at = nD + my_off + t;
-            if ((static_cast<uint32_t>(A) & mask) != q) {
-                const uint32_t q_new = static_cast<uint32_t>(A) & mask;
-                const uint32_t by = (down ? q - q_new : q_new - q) & mask;
-                q = q_new;
-                if (by == 1 && left > 0) {
+        if constexpr (kAhead) {
+            if (there(nD0)) request(others[0], nD0);
+        }
+        for (int64_t nD = nD0; there(nD);) {
 #pragma unroll
-                    for (int m = 0; m < kOwn; ++m) {
-                        win[m][0] = win[m][1];
-                        win[m][1] = win[m][2];
-                        win[m][2] = win[m][3];
+            for (int buf = 0; buf < kTurns; ++buf, nD += D) {
+                if (buf > 0 && !there(nD)) break;
+                // residues from wave_off on that exist
+                const int64_t in_gap = D - wave_off, in_vec = d - nD - wave_off;
+                const int64_t room = in_gap < in_vec ? in_gap : in_vec;
+                const int len = static_cast<int>(room < kQWave + kQLine ? room : kQWave + kQLine);
+                const uint32_t t = skipped(nD);
+                const int my_len = len - static_cast<int>(t) - lane * kQRun;      // of the 4 that I write: >= 4 all, <= 0 none
+                const int64_t at = nD + my_off + t;
+                [[maybe_unused]] vec4f (&other)[RF > 1 ? RF - 1 : 1] = others[buf];     // the other rows' values, requested early
+                if constexpr (kAhead) {
+                    // (behind the last visit of mine the present one's again, which are in L2: nothing is read for no one)
+                    request(others[buf ^ 1], there(nD + D) ? nD + D : nD);
+                } else if constexpr (RF > 1) {
+                    if (my_len >= kQRun) {
+#pragma unroll
+                        for (int z = 0; z < RF - 1; ++z)
+                            other[z] = load_values<LINES>(rows + static_cast<size_t>(z) * d + at);
                     }
-                    --left;
-                } else {
-                    load_cells();
                 }
-            }
-            const uint64_t wraps = kP61 - A, flips = kP61 - As_n;    // a state above them passes p
-            const bool odd = (As_n & 1u) != 0;
-            float o[kOwn];
+                if ((static_cast<uint32_t>(A) & mask) != q) {
+                    const uint32_t q_new = static_cast<uint32_t>(A) & mask;
+                    const uint32_t by = (down ? q - q_new : q_new - q) & mask;
+                    q = q_new;
+                    if (by == 1 && left > 0) {
 #pragma unroll
-            for (int m = 0; m < kOwn; ++m) {
-                const float x = (yb[m] > wraps) != down ? win[m][1] : win[m][0];
-                o[m] = (ys[m] > flips) != odd ? -x : x;
-            }
-            A += ADb;
-            A = A >= kP61 ? A - kP61 : A;
-            As_n += ADs;
-            As_n = As_n >= kP61 ? As_n - kP61 : As_n;
-            vec4f mine;
-            mine.x = o[0]; mine.y = o[1]; mine.z = o[2]; mine.w = o[3];
-            [[maybe_unused]] float head = 0.0f;
-            if constexpr (LINES) {
-                *reinterpret_cast<vec4f*>(turn + lane * kQRun) = mine;
-                if (lane < kQLine) turn[kQWave + lane] = o[kQRun];
-                __builtin_amdgcn_wave_barrier();
-                mine = *reinterpret_cast<const vec4f_u*>(turn + t + lane * kQRun);
-                head = turn[lane % kQLine];
-                __builtin_amdgcn_wave_barrier();
-            }
-            // the visit's first residues, before its first whole line
-            const bool heads = LINES && wave_off == 0 && lane < static_cast<int>(t) && lane < len;
-            if constexpr (RF > 0) {
-                float* dst = est + at;
-                if (my_len >= kQRun) {
-                    float vx[RF], vy[RF], vz[RF], vw[RF];
-#pragma unroll
-                    for (int z = 0; z < RF - 1; ++z) {
-                        vx[z] = other[z].x; vy[z] = other[z].y; vz[z] = other[z].z; vw[z] = other[z].w;
+                        for (int m = 0; m < kOwn; ++m) {
+                            win[m][0] = win[m][1];
+                            win[m][1] = win[m][2];
+                            win[m][2] = win[m][3];
+                        }
+                        --left;
+                    } else {
+                        load_cells();
                     }
-                    vx[RF - 1] = mine.x; vy[RF - 1] = mine.y; vz[RF - 1] = mine.z; vw[RF - 1] = mine.w;
-                    vec4f u;
-                    float med[4];
-                    medians_odd<RF>(vx, vy, vz, vw, med);
-                    u.x = med[0]; u.y = med[1]; u.z = med[2]; u.w = med[3];
-                    store_values<LINES>(dst, u);
-                    tally(u.x); tally(u.y); tally(u.z); tally(u.w);
-                } else {
-                    for (int m = 0; m < kQRun; ++m) {
-                        if (m >= my_len) break;
+                }
+                const uint64_t wraps = kP61 - A, flips = kP61 - As_n;    // a state above them passes p
+                const bool odd = (As_n & 1u) != 0;
+                float o[kOwn];
+#pragma unroll
+                for (int m = 0; m < kOwn; ++m) {
+                    const float x = (yb[m] > wraps) != down ? win[m][1] : win[m][0];
+                    o[m] = (ys[m] > flips) != odd ? -x : x;
+                }
+                A += ADb;
+                A = A >= kP61 ? A - kP61 : A;
+                As_n += ADs;
+                As_n = As_n >= kP61 ? As_n - kP61 : As_n;
+                vec4f mine;
+                mine.x = o[0]; mine.y = o[1]; mine.z = o[2]; mine.w = o[3];
+                [[maybe_unused]] float head = 0.0f;
+                if constexpr (LINES) {
+                    *reinterpret_cast<vec4f*>(turn + lane * kQRun) = mine;
+                    if (lane < kQLine) turn[kQWave + lane] = o[kQRun];
+                    __builtin_amdgcn_wave_barrier();
+                    mine = *reinterpret_cast<const vec4f_u*>(turn + t + lane * kQRun);
+                    head = turn[lane % kQLine];
+                    __builtin_amdgcn_wave_barrier();
+                }
+                // the visit's first residues, before its first whole line
+                const bool heads = LINES && wave_off == 0 && lane < static_cast<int>(t) && lane < len;
+                if constexpr (RF > 0) {
+                    float* dst = est + at;
+                    if (my_len >= kQRun) {
+                        float vx[RF], vy[RF], vz[RF], vw[RF];
+#pragma unroll
+                        for (int z = 0; z < RF - 1; ++z) {
+                            vx[z] = other[z].x; vy[z] = other[z].y; vz[z] = other[z].z; vw[z] = other[z].w;
+                        }
+                        vx[RF - 1] = mine.x; vy[RF - 1] = mine.y; vz[RF - 1] = mine.z; vw[RF - 1] = mine.w;
+                        vec4f u;
+                        float med[4];
+                        medians_odd<RF>(vx, vy, vz, vw, med);
+                        u.x = med[0]; u.y = med[1]; u.z = med[2]; u.w = med[3];
+                        store_values<LINES>(dst, u);
+                        tally(u.x); tally(u.y); tally(u.z); tally(u.w);
+                    } else {
+                        for (int m = 0; m < kQRun; ++m) {
+                            if (m >= my_len) break;
+                            float v[RF];
+#pragma unroll
+                            for (int z = 0; z < RF - 1; ++z) v[z] = rows[static_cast<size_t>(z) * d + at + m];
+                            v[RF - 1] = mine[m];
+                            const float med = median_odd<RF>(v);
+                            dst[m] = med;
+                            tally(med);
+                        }
+                    }
+                    if (heads) {
                         float v[RF];
 #pragma unroll
-                        for (int z = 0; z < RF - 1; ++z) v[z] = rows[static_cast<size_t>(z) * d + at + m];
-                        v[RF - 1] = mine[m];
+                        for (int z = 0; z < RF - 1; ++z) v[z] = rows[static_cast<size_t>(z) * d + nD + lane];
+                        v[RF - 1] = head;
                         const float med = median_odd<RF>(v);
-                        dst[m] = med;
+                        est[nD + lane] = med;
                         tally(med);
                     }
+                    continue;
                 }
-                if (heads) {
-                    float v[RF];
-#pragma unroll
-                    for (int z = 0; z < RF - 1; ++z) v[z] = rows[static_cast<size_t>(z) * d + nD + lane];
-                    v[RF - 1] = head;
-                    const float med = median_odd<RF>(v);
-                    est[nD + lane] = med;
-                    tally(med);
+                // the wavefront's 64 pieces are 1 KB of contiguous rows[j][i]
+                float* dst = out + at;
+                if (my_len >= kQRun) {
+                    store_values<LINES>(dst, mine);
+                } else if (my_len > 0) {
+                    dst[0] = mine.x;
+                    if (my_len > 1) dst[1] = mine.y;
+                    if (my_len > 2) dst[2] = mine.z;
                 }
-                return;
-            }
-            // the wavefront's 64 pieces are 1 KB of contiguous rows[j][i]
-            float* dst = out + at;
-            if (my_len >= kQRun) {
-                store_values<LINES>(dst, mine);
-            } else if (my_len > 0) {
-                dst[0] = mine.x;
-                if (my_len > 1) dst[1] = mine.y;
-                if (my_len > 2) dst[2] = mine.z;
-            }
-            if (heads) out[nD + lane] = head;
-        };
-        auto there = [&](int64_t nD) { return nD < nD1 && nD + wave_off < d; };
-        // The last row's wavefronts alone do not fill the chip, and a visit is one round of loads: the next visit's
-        // are under way meanwhile (a buffer for each of two turns: moving a value that is on its way would wait for it).
-        // us of the last row, without / with: 6.5 M, 5 x 2^17 36.3 / 30.8; 11 M, 5 x 2^18 45.1 / 44.6; 25 M, 5 x 2^19 106 / 106.
-        vec4f one[kOther];
-        if constexpr (RF > 1 && RF <= kQAheadRows) {
-            vec4f two[kOther];
-            int64_t nD = nD0;
-            if (there(nD)) request(one, nD);
-            for (;;) {
-                if (!there(nD)) break;
-                request(two, nD + D);
-                visit(nD, one);
-                nD += D;
-                if (!there(nD)) break;
-                request(one, nD + D);
-                visit(nD, two);
-                nD += D;
-            }
-        } else {
-            for (int64_t nD = nD0; there(nD); nD += D) {
-                request(one, nD);
-                visit(nD, one);
+                if (heads) out[nD + lane] = head;
             }
         }
     }
