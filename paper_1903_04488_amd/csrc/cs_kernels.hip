@@ -699,19 +699,28 @@ k_dequantize16(const uint16_t* __restrict__ q, int64_t n, float* __restrict__ ou
 // The momentum and error-accumulation steps of Alg. 3 with dense per-worker state:
 // u = rho u + g (one fused multiply-add), v = v + u.  blockIdx.y = worker; 20 bytes of
 // traffic per coordinate, 16-byte accesses when the three vectors are 16-byte aligned.
-// Bound: memory, read and write in turn (a copy reaches 5.0 TB/s).  u and g, which nothing reads before the next step, go past
-// the caches, so that what the memory-side cache holds at the end is v, which the update reads next, from its end
-// (11 M, 8 workers: a step 824 / 778 us; v past them too: the same).
+// Bound: memory, read and write in turn (a copy reaches 5.0 TB/s).
+// u and g, which nothing reads before the next step, go past the caches where u, v and g of all workers are more than the
+// memory-side cache (256 MB) keeps beside a step's tables, estimates and scratch: what it holds at the end is then v, which the
+// update reads next, from its end.  Where it keeps them, the next step finds u there.  us of this pass / of the pass with update
+// and query, through the caches and past them: 22 MB 9.6 / 60.7 and 10.3 / 61.6; 42 MB 14.2 / 60.5 and 16.3 / 62.5; 112 MB 31.1 /
+// 108.0 and 32.6 / 109.5; 141 MB 38.4 / 106.2 and 40.4 / 108.2; 161 MB 42.5 / 154.4 and 42.5 / 153.3; 199 MB 51.6 / 166.0 and 51.3 /
+// 162.2; 245 MB 75.0 / 265.6 and 64.7 / 253.3; 877 MB 262 / 486 and 220 / 433; 11 M, 8 workers (1.06 GB) 342 / 759 and 289 /
+// 701; v past them too: the same.
+constexpr double kDensePastBytes = 1.5e8;
+inline bool dense_goes_past(int W, int64_t d) { return 12.0 * W * static_cast<double>(d) > kDensePastBytes; }
 struct DensePtrs {
     float* u[kMaxBatch];
     float* v[kMaxBatch];
     const float* g[kMaxBatch];
 };
 
-template <bool VEC>
+// PAST: u and g go past the caches (dense_goes_past).
+template <bool VEC, bool PAST>
 __global__ void __launch_bounds__(kBlock)
 k_dense_momentum(DensePtrs ptrs, int64_t d, float rho) {
     typedef float f4 __attribute__((ext_vector_type(4)));
+    auto load = [](const f4* p) { return PAST ? __builtin_nontemporal_load(p) : *p; };
     float* __restrict__ u = ptrs.u[blockIdx.y];
     float* __restrict__ v = ptrs.v[blockIdx.y];
     const float* __restrict__ g = ptrs.g[blockIdx.y];
@@ -721,12 +730,13 @@ k_dense_momentum(DensePtrs ptrs, int64_t d, float rho) {
     if (VEC) {
         const int64_t n4 = d / 4;
         for (int64_t t = t0; t < n4; t += stride) {
-            f4 uu = __builtin_nontemporal_load(reinterpret_cast<f4*>(u) + t), vv = reinterpret_cast<f4*>(v)[t];
-            const f4 gg = __builtin_nontemporal_load(reinterpret_cast<const f4*>(g) + t);
+            f4 uu = load(reinterpret_cast<f4*>(u) + t), vv = reinterpret_cast<f4*>(v)[t];
+            const f4 gg = load(reinterpret_cast<const f4*>(g) + t);
             uu.x = __fmaf_rn(rho, uu.x, gg.x); uu.y = __fmaf_rn(rho, uu.y, gg.y);
             uu.z = __fmaf_rn(rho, uu.z, gg.z); uu.w = __fmaf_rn(rho, uu.w, gg.w);
             vv.x += uu.x; vv.y += uu.y; vv.z += uu.z; vv.w += uu.w;
-            __builtin_nontemporal_store(uu, reinterpret_cast<f4*>(u) + t);
+            if (PAST) __builtin_nontemporal_store(uu, reinterpret_cast<f4*>(u) + t);
+            else reinterpret_cast<f4*>(u)[t] = uu;
             reinterpret_cast<f4*>(v)[t] = vv;
         }
         done = n4 * 4;
@@ -1260,6 +1270,7 @@ extern "C" int cs_dense_momentum(float* const* u_w, float* const* v_w, const flo
                       reinterpret_cast<uintptr_t>(g_w[w])) % 16 == 0;
     }
     if (d == 0) return CS_OK;
+    const bool past = dense_goes_past(W, d);
     for (int w0 = 0; w0 < W; w0 += kMaxBatch) {
         const int nw = (W - w0 < kMaxBatch) ? (W - w0) : kMaxBatch;
         DensePtrs ptrs{};
@@ -1269,8 +1280,9 @@ extern "C" int cs_dense_momentum(float* const* u_w, float* const* v_w, const flo
             ptrs.g[w] = g_w[w0 + w];
         }
         const dim3 grid(grid_for(vec ? (d + 3) / 4 : d, kBlock, 2048), static_cast<unsigned>(nw));
-        if (vec) k_dense_momentum<true><<<grid, kBlock, 0, as_stream(stream)>>>(ptrs, d, rho);
-        else k_dense_momentum<false><<<grid, kBlock, 0, as_stream(stream)>>>(ptrs, d, rho);
+        if (vec && past) k_dense_momentum<true, true><<<grid, kBlock, 0, as_stream(stream)>>>(ptrs, d, rho);
+        else if (vec) k_dense_momentum<true, false><<<grid, kBlock, 0, as_stream(stream)>>>(ptrs, d, rho);
+        else k_dense_momentum<false, false><<<grid, kBlock, 0, as_stream(stream)>>>(ptrs, d, rho);
         if (launch_status() != CS_OK) return CS_EHIP;
     }
     return CS_OK;
