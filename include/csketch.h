@@ -93,7 +93,7 @@ typedef struct cs_row_plan {
 #define CS_MAX_VISITS 512
 typedef struct cs_visit_plan {
     uint32_t K;                 /* number of visits; 0 = no list (the stride walk is used) */
-    uint32_t ncell;             /* running sums per lane and coordinate: 2, 3 or 4 */
+    uint32_t ncell;             /* running sums per lane and coordinate: 2, 3 or 4 (in a cs_vector_plan up to CS_VECTOR_CELLS) */
     uint64_t cover;             /* the list covers vectors of length <= cover (= d_hint) */
     uint64_t gmax;              /* largest gap = number of residues that lanes own */
     uint64_t cost;              /* estimated time of one launch with this list, nanoseconds */
@@ -147,10 +147,14 @@ typedef struct cs_params {
     uint64_t as[CS_MAX_R], bs[CS_MAX_R];   /* sign hashes */
     cs_row_plan plan[CS_MAX_R];
     cs_visit_plan visit[CS_MAX_R];
+#if defined(__cplusplus) || (defined(__STDC_VERSION__) && __STDC_VERSION__ >= 201112L)
     union {
         cs_anyc_plan anyc[CS_MAX_R];        /* column counts that are not a power of two */
         cs_vector_plan vector[CS_MAX_R];    /* powers of two */
     };
+#else                                       /* C before C11 has no unnamed unions: the same bytes */
+    cs_anyc_plan anyc[CS_MAX_R];
+#endif
 } cs_params;
 
 /* Alg. 4 init: fills *p for an r x c sketch from `seed` (host, no GPU needed).
