@@ -499,7 +499,9 @@ struct VisitPlaces {
 // that, and the first on the end of vectors that a pass before wrote in order (dense state).  Us a step, all
 // rounds up / in turn: 5 x 2^18, 11 M, 8 workers, dense 778 / 764 (in turn, rounds of half the size 784), 7 x 2^19, 25 M, 256 workers
 // 34 580 / 33 400 (rounds of two thirds 35 260, of four thirds 34 130), 15 x 180 000, 90 M, 4 workers 6500 / 6350, 5 x 2^20, 10^8,
-// 32 workers 13 640 / 13 520.  The more of the vectors the cache holds, the more of a round's reads it answers.
+// 32 workers 13 640 / 13 520.  The more of the vectors the cache holds, the more of a round's reads it answers.  (Of 55 drawn updates
+// 0.7 % in the mean, 3 to 5 % in a fifth of them, and two slower: 5 x 2^18, 27 M, 24 workers 2060 / 2190, 3 x 2^19, 20 M, 8 workers
+// 386 / 403.)  Launches of several groups of workers count by blockIdx.x alone: their groups read other vectors.
 __device__ __forceinline__ bool walks_down(uint32_t at_once) { return (blockIdx.x / at_once & 1u) == 0; }
 
 // The visits k0 .. k1 - 1, by all wavefronts of the workgroup, the last one first with `down`; returns how many of them are
@@ -1026,20 +1028,29 @@ uint32_t most_steps(const LIST& rows, int nrows) {
     return most;
 }
 
-// Workgroups of a kernel that the chip holds at a time.  (The runtime works it out from the kernel's registers and LDS; asked once
-// for each amount of LDS in a row of equal ones, as a program that steps has them.)
+// Workgroups of a kernel that the chip holds at a time.  The runtime works it out from the kernel's registers and LDS, and is asked
+// once for each of the last kLdsSizes amounts of LDS: sketches of more rows than a launch takes, and programs with several
+// sketches, go through a few in turn.  (Us of host work a call, asked at every launch / with one amount known / so: 15 x 4096, two
+// launches 9.5 / 9.2 / 9.0; 5 x 4096, one 6.2 / 5.9 / 5.9.)
+constexpr unsigned kLdsSizes = 8;
 template <auto KERNEL>
 uint32_t workgroups_at_once(int threads, size_t lds) {
-    static std::atomic<uint64_t> known{0};             // LDS, workgroups
-    const uint64_t k = known.load(std::memory_order_relaxed);
-    if (k != 0 && k >> 32 == lds) return static_cast<uint32_t>(k);
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, threads, lds) != hipSuccess || per_cu < 1) {
-        (void)hipGetLastError();
-        per_cu = 1;
+    static std::atomic<uint64_t> known[kLdsSizes];     // LDS, workgroups; 0 = none yet
+    static std::atomic<unsigned> oldest{0};
+    for (const auto& one : known) {
+        const uint64_t k = one.load(std::memory_order_relaxed);
+        if (k != 0 && k >> 32 == lds) return static_cast<uint32_t>(k);
     }
-    const uint32_t n = 256u * static_cast<uint32_t>(per_cu);
-    known.store(static_cast<uint64_t>(lds) << 32 | n, std::memory_order_relaxed);
+    int per_cu = 0, device = 0, cus = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, threads, lds) != hipSuccess || per_cu < 1 ||
+        hipGetDevice(&device) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1) {
+        (void)hipGetLastError();
+        return 256u;                                   // (an order of visits like any other; asked again next time)
+    }
+    const uint32_t n = static_cast<uint32_t>(cus) * static_cast<uint32_t>(per_cu);
+    known[oldest.fetch_add(1, std::memory_order_relaxed) % kLdsSizes].store(static_cast<uint64_t>(lds) << 32 | n,
+                                                                            std::memory_order_relaxed);
     return n;
 }
 
