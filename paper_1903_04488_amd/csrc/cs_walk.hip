@@ -582,7 +582,8 @@ struct VisitCursor {
 // 2690 us, 6.1 TB/s.  Sums waiting in
 // LDS instead of registers: 10^8 3130, 25 M 1131; four wavefronts in step by a barrier per visit: 11 M 293, 10^8 3269.
 // PARTIAL (power-of-two columns): the sums go to a workspace instead of being added to the table (cs_index.hip).
-template <int WL, int RUN, int NWAVE, int NC, bool PARTIAL, typename LIST>
+// PAIRS: two neighbouring cells of a bundle leave as one request (with RUN = 16 a kernel of its own, which is not for `fold`).
+template <int WL, int RUN, int NWAVE, int NC, bool PARTIAL, bool PAIRS, typename LIST>
 __global__ void __launch_bounds__(64 * NWAVE)
 k_accumulate_visits(LIST rows, WorkersBeside<LIST> a) {
     constexpr bool POW2 = std::is_same<LIST, VisitRows>::value;
@@ -595,11 +596,9 @@ k_accumulate_visits(LIST rows, WorkersBeside<LIST> a) {
     constexpr int SPAN = WPW * RUN;                    // residues a wavefront owns
     constexpr int kStride = RUN + 1;
     static_assert(WL <= 8 && WL * PPL == RUN, "every coordinate of a walker gets a hash lane");
-    // Two neighbouring cells of a bundle are one aligned 64-byte block when the lower one is
-    // even, and leave as one request then: on average ncell / 2 + 1/2 requests per residue instead of ncell.  For
-    // that the sums go through LDS.  (7 x 2^19, 25 M, 256 workers, whose 10 M requests a launch of 8 workers end each round:
-    // a step 33 450 / 32 870 us; 5 x 2^20, 10^8, and 5 x 2^18, 11 M, which have fewer of them to a byte read: the same.)
-constexpr bool kPairs = !PARTIAL && POW2;
+    // PAIRS: two neighbouring cells of a bundle are one aligned 64-byte block when the lower one is even, and leave as one request
+    // then: on average ncell / 2 + 1/2 requests per residue instead of ncell.  For that the sums go through LDS.
+    static_assert(!PAIRS || (!PARTIAL && POW2), "neighbouring cells");
     // Per wavefront: the value tile (one padded row per lane), the walkers' first cells and signs
     __shared__ float tile_lds_all[NWAVE][64 * kStride];
     __shared__ uint32_t first_lds_all[NWAVE][SPAN];
@@ -622,7 +621,7 @@ constexpr bool kPairs = !PARTIAL && POW2;
     const uint32_t mask = a.c - 1u;
     const Columns col = columns_of<POW2>(a.c);
     const uint32_t d = static_cast<uint32_t>(a.d);
-    const bool fold = a.fold != 0;
+    const bool fold = !(PAIRS && RUN == 16) && a.fold != 0;
     const size_t cell_floats = fold ? 1 : kGroup;      // floats from one cell to the next
     float* __restrict__ Tcol = fold ? T + static_cast<size_t>(v.j) * a.c
                                     : T + static_cast<size_t>(v.j) * a.c * kGroup + wl;
@@ -855,7 +854,7 @@ constexpr bool kPairs = !PARTIAL && POW2;
                     if (q < static_cast<int>(ncell))
                         dst[(m * WPW * ncell + q) * WL] = live ? apply_sign(a.scale * sum_of(q, m), flip) : 0.0f;
             }
-        } else if (kPairs && !fold) {
+        } else if (PAIRS && !fold) {
             // The sums of a residue take the slots of those blocks in LDS (an even first cell: slots 0 .. ncell-1, an
             // odd one: 1 .. ncell), and a block then leaves as one request.
             constexpr int kSlots = (NC + 2) / 2 * 2;
@@ -1055,21 +1054,23 @@ uint32_t workgroups_at_once(int threads, size_t lds) {
 }
 
 // one launch: rows that all have at most ncell running sums, of the groups of workers that `a` holds
-template <int WL, int RUN, int NWAVE, typename LIST>
+template <int WL, int RUN, int NWAVE, bool PAIRS16 = false, typename LIST>
 int launch_visits_run(LIST& rows, WorkersBeside<LIST> a, int nrows, uint32_t ncell, hipStream_t stream) {
     const dim3 grid(visits_grid<WL, RUN, NWAVE>(rows, nrows), (a.nw + kGroup - 1) / kGroup), block(64 * NWAVE);
     const size_t lds = most_steps(rows, nrows) * sizeof(uint4);
     constexpr bool pow2 = std::is_same<LIST, VisitRows>::value;
     constexpr bool partial = pow2 && WL > 1;           // running sums: power-of-two columns
-    if (!(a.sums ? partial : a.T != nullptr)) return CS_EINVAL;
+    constexpr bool pairs = pow2 && (RUN == 8 || PAIRS16);
+    if (!(a.sums ? partial : a.T != nullptr) || (PAIRS16 && (a.sums || a.fold))) return CS_EINVAL;
     auto launch = [&](auto nc) {
         constexpr int NC = decltype(nc)::value;
         auto with = [&](auto sums) {
-            constexpr auto kernel = k_accumulate_visits<WL, RUN, NWAVE, NC, decltype(sums)::value, LIST>;
+            constexpr bool to_sums = decltype(sums)::value;
+            constexpr auto kernel = k_accumulate_visits<WL, RUN, NWAVE, NC, to_sums, pairs && !to_sums, LIST>;
             a.at_once = workgroups_at_once<kernel>(64 * NWAVE, lds);
             kernel<<<grid, block, lds, stream>>>(rows, a);
         };
-        if constexpr (partial) {
+        if constexpr (partial && !PAIRS16) {
             if (a.sums) return with(std::true_type());
         }
         with(std::false_type());
@@ -1451,19 +1452,35 @@ bool vectors_pay(const LIST& rows, int n, int64_t d, int vectors, int groups) {
 constexpr double kVisitNsVectors = 650.0;
 constexpr double kCachedBytesPerNs = 6400.0;
 
+// In runs of 16 pairs cost a turn through LDS for every coordinate of a walker, with two sums half of it for nothing, and
+// 9 to 16 registers, with 3 sums of 8 workers the fourth wavefront of a SIMD.  They pay for it where requests are much of
+// the launch: of up to 4 workers, whose requests are 8 or 16 bytes, in rows of 4 MB and more, which one XCD's L2 does not hold, and
+// in long vectors.  Us, one by one / in pairs: 7 x 131 072, 4.2 M, 2 workers 143 / 116; 5 x 2^19, 17 M, 4 workers 413 / 358; 5 x
+// 131 072, 5.1 M, 8 workers 177 / 155; 5 x 2^19, 11 M, 16 workers 755 / 699; 7 x 65 536, 15.8 M, 8 workers 606 / 574; 7 x 2^19, 25 M,
+// 256 workers, whose 10 M requests a launch of 8 workers end each round, a step 33 450 / 32 870.  But 5 x 32 768, 1.65 M, 6 workers
+// 118 / 132; 7 x 32 768, 4.7 M, 6 workers 172 / 211; 7 x 65 536, 4.2 M, 5 workers 152 / 171; two sums: 5 x 32 768, 3.5 M, 6
+// workers 104 / 120, 3 x 65 536, 21.9 M, 24 workers 1080 / 1154, 5 x 131 072, 32 M, 4 workers 430 / 446, and 5 x 2^18, 8 M, 2
+// workers 220 / 197.  What it leaves behind is up to 7 % (3 x 131 072, 16.8 M, 8 workers 261 / 280).
+bool pairs_pay(uint32_t ncell, uint32_t c, int workers, int64_t d) {
+    if (ncell == 2) return workers <= 4 && d < 64 * static_cast<int64_t>(c);
+    return workers <= 4 || c >= 1u << 17 || d >= 12'000'000;
+}
+
 template <int WL, int NWAVE>
 int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js, int nrows,
                   uint32_t ncell, hipStream_t stream) {
     if (ncell < 2 || ncell > 4) return CS_EINVAL;
     VisitRows rows{};
-    // every sum is a request, but RUN = 8 sends the two cells of an aligned block of a bundle in one
+    // every sum is a request, but those of the two cells of an aligned block of a bundle are one where they leave in pairs
     double requests8[kRowsPerLaunch], requests16[kRowsPerLaunch];
     const int groups = (a.nw + kGroup - 1) / kGroup;
+    const bool pairs16 = a.fold == 0 && pairs_pay(ncell, p->c, a.nw, a.d);
     for (int q = 0; q < nrows; ++q) {
         const cs_visit_plan& vp = p->visit[js[q]];
         fill_visit_args(p, js[q], rows.row[q]);
-        requests16[q] = static_cast<double>(vp.ncell) * static_cast<double>(vp.gmax) * groups;
-        requests8[q] = a.fold ? requests16[q] : (0.5 * vp.ncell + 0.5) * static_cast<double>(vp.gmax) * groups;
+        const double residues = static_cast<double>(vp.gmax) * groups, paired = 0.5 * vp.ncell + 0.5;
+        requests8[q] = (a.fold ? vp.ncell : paired) * residues;
+        requests16[q] = (pairs16 ? paired : vp.ncell) * residues;
     }
     const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * nrows / kStreamBytesPerNs;
     if constexpr (WL > 1) {
@@ -1472,8 +1489,9 @@ int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js,
             return launch_vectors<WL, false>(rows, a, nrows, ncell, stream);
         }
     }
-    if (choose_run8<WL>(rows, nrows, requests8, requests16, a.d, stream_ns, groups))
-        return launch_visits_run<WL, 8, 1>(rows, a, nrows, ncell, stream);
+    const bool run8 = choose_run8<WL>(rows, nrows, requests8, requests16, a.d, stream_ns, groups);
+    if (run8) return launch_visits_run<WL, 8, 1>(rows, a, nrows, ncell, stream);
+    if (pairs16) return launch_visits_run<WL, 16, NWAVE, true>(rows, a, nrows, ncell, stream);
     return launch_visits_run<WL, 16, NWAVE>(rows, a, nrows, ncell, stream);
 }
 
