@@ -311,7 +311,7 @@ int launch_bundle_sketch(const cs_params* p, float* T, int W, const float* const
     const uint64_t table = static_cast<uint64_t>(p->r) * p->c * CS_BUNDLE_GROUP;
     SumsPlan plan;
     const int together = sums_groups(p, W, d);
-    int rc = launch_accumulate_sums(p, nullptr, 0, lanes, together, 0, nullptr, d, scale, plan, stream);
+    int rc = launch_accumulate_sums(p, nullptr, 0, W, together, 0, nullptr, d, scale, plan, stream);
     if (rc != CS_OK) return rc;
     const uint64_t at_once = ws_floats / plan.floats;
     if (at_once == 0) return CS_EWORKSPACE;
@@ -332,7 +332,7 @@ int launch_bundle_sketch(const cs_params* p, float* T, int W, const float* const
         for (int g = g0; g < g0 + a.groups; g += together) {
             const int end = g + together < g0 + a.groups ? g + together : g0 + a.groups;
             const int w0 = g * CS_BUNDLE_GROUP, w1 = W < end * CS_BUNDLE_GROUP ? W : end * CS_BUNDLE_GROUP;
-            rc = launch_accumulate_sums(p, ws + (g - g0) * a.group_floats, a.group_floats, lanes, together, w1 - w0, g_w + w0, d,
+            rc = launch_accumulate_sums(p, ws + (g - g0) * a.group_floats, a.group_floats, W, together, w1 - w0, g_w + w0, d,
                                         scale, plan, stream);
             if (rc != CS_OK) return rc;
         }
@@ -593,7 +593,7 @@ extern "C" int cs_update_workspace_bytes(const cs_params* p, int32_t W, int64_t 
     *bytes = 0;
     if (!sums_apply(p, d)) return CS_OK;
     SumsPlan plan;
-    const int rc = launch_accumulate_sums(p, nullptr, 0, sums_lanes(W), sums_groups(p, W, d), 0, nullptr, d, 1.0f, plan, nullptr);
+    const int rc = launch_accumulate_sums(p, nullptr, 0, W, sums_groups(p, W, d), 0, nullptr, d, 1.0f, plan, nullptr);
     *bytes = plan.floats * sizeof(float) * ((W + CS_BUNDLE_GROUP - 1) / CS_BUNDLE_GROUP);
     return rc;
 }

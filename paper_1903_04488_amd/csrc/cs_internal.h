@@ -91,9 +91,9 @@ struct SumsPlan {
 bool sums_apply(const cs_params* p, int64_t d);
 int sums_lanes(int W);           // lanes of a walker (1, 2, 4, 8) with W workers, the same in all groups of 8
 int sums_groups(const cs_params* p, int W, int64_t d);   // groups of 8 workers that a launch takes, of W workers
-// nw: workers of this launch, up to 8 `groups` (the plan is that of launches of `groups`); g_w null: the plan only.
+// workers: of the whole update (every launch of it has the same plan); nw: of this launch, up to 8 `groups`; g_w null: the plan only.
 // sums_floats: from one group's sums to the next
-int launch_accumulate_sums(const cs_params* p, float* sums, uint64_t sums_floats, int lanes, int groups, int nw,
+int launch_accumulate_sums(const cs_params* p, float* sums, uint64_t sums_floats, int workers, int groups, int nw,
                            const float* const* g_w, int64_t d, float scale, SumsPlan& plan, hipStream_t stream);
 // the same along visit lists for column counts that are not a power of two
 bool anyc_visits_apply(const cs_params* p, int64_t d);

@@ -950,10 +950,12 @@ void choose_pieces(LIST& rows, int nrows, const double* requests, double visit_n
     }
 }
 
-// A turn of the walkers of 8 (4, 2) workers with RUN = 8 and with RUN = 16, and of a single vector.  (The
+// A turn of the walkers of 8 (4, 2) workers with RUN = 8 and with RUN = 16, and of a wavefront per vector.  (The
 // planner, which knows neither the workers nor the run length that a launch will have, prices a
 // turn at 900 ns.)
 // (priced as RUN = 8, chains of 316 visits of 4 workers stayed whole: d = 22.4 M, c = 65 536, 738 us a step for 596)
+// (of 2 to 8 vectors: priced at 650, as with the chip full, 805 timings of drawn shapes take 3 % more in the mean, and a single table's requests
+// at one or two for all of a residue's sums 2 %)
 constexpr double kVisitNs8 = 700.0, kVisitNs16 = 1300.0, kVisitNsOne = 500.0;
 constexpr double kStreamBytesPerNs = 5000.0;
 
@@ -1434,22 +1436,32 @@ int launch_vectors(LIST& rows, WorkersBeside<LIST> a, int n, uint32_t ncell, hip
 // A wavefront per vector is the faster way for 2 to 8 vectors that the memory-side cache (256 MB) holds, or nearly (us, update with
 // merge, lanes for workers / wavefronts for vectors): 5 x 2^17, 6.5 M, 8 workers 201 / 178, 9 M 267 / 238; 5 x 2^18, 14 M
 // 390 / 435; 7 x 65 536, 15.4 M 544 / 575; 4 workers and less, up to 480 MB: 5 x 2^17, 10 M, 4 workers 167 / 148, 5 x 2^18,
-// 30 M 437 / 422; 5 x 2^19, 40 M, 2 workers 371 / 287; 7 x 161 771, 30 M, 4 workers 671 / 675.  Less so where a residue takes part in
-// few visits, so that what a workgroup does once (its table of visits, the sums at its end) is much of it, in short vectors, and for the
-// row of another column count's seventh that has a launch of its own: 5 x 8192, 300 000, 8 workers 25 / 34; 5 x 16 384,
-// 600 000 33 / 38; 7 x 65 536, 5 M (23 visits) 207 / 212; 7 x 2^17, 5 M, 4 workers (14) 192 / 203; 7 x 8387, 2.5 M 110 / 124.
-// Of the drawn shapes that it leaves a few are behind, by up to 5 % (3 x 2^17, 8.6 M, 4 workers 83 / 86).  Several groups of 8 in a
-// launch: 5 x 8192, 300 000, 64 workers 126 / 140.
+// 30 M 437 / 422; 5 x 2^19, 40 M, 2 workers 371 / 287.  Less so where a residue takes part in few visits, so that what a workgroup
+// does once (its table of visits, the sums at its end) is much of it, and in short vectors: 5 x 8192, 300 000, 8 workers 25 / 34;
+// 5 x 16 384, 600 000 33 / 38; 7 x 65 536, 5 M (23 visits) 207 / 212; 7 x 2^17, 5 M, 4 workers (14) 192 / 203.  Several groups of 8 in
+// a launch: 5 x 8192, 300 000, 64 workers 126 / 140.
+// And where few residues make a round or two of workgroups of 5 to 8 vectors, the last of them nearly empty (the update alone):
+// 3 x 8192, 1.5 M, 8 workers (41 000 residues) 37 / 47; 3 x 4096, 2 M, 5 workers (26 000) 39 / 45; but 3 x 4096, 1.3 M, 8 workers
+// (62 000) 32 / 28; in launches of 5 rows and more 5 x 8192, 2.7 M, 8 workers (107 000) 74 / 83, 3.7 M, 6 workers (122 000) 83 / 100; but
+// 2.1 M, 6 workers (197 000) 56 / 52, 5 x 16 384, 5.1 M, 8 workers (220 000) 145 / 130.  With sums to a workspace: 3 x 4096, 1.3 M, 8
+// workers 30 / 35, 7 x 8192, 2 M, 4 workers (187 000) 48 / 52; but 3 x 65 536, 5.4 M, 4 workers (241 000) 63 / 59, 3 x 16 384, 2.6 M,
+// 3 workers (139 000) 35 / 29.  Of 300 timings of drawn shapes that it leaves, 12 % faster in the mean, 15 are behind by 3 to 10 % (7 x
+// 8192, 2.4 M, 8 workers 93 / 101; 5 x 16 384, 3 M, 3 workers 50 / 54; 7 x 16 384, 5.7 M, 2 workers, to a workspace 80 / 85).
+// workers_of_sums: those of an update whose sums go to a workspace; `vectors` are a walker's lanes then.
 template <typename LIST>
-bool vectors_pay(const LIST& rows, int n, int64_t d, int vectors, int groups) {
+bool vectors_pay(const LIST& rows, int n, int64_t d, int vectors, int groups, int workers_of_sums = 0) {
     double residues = 0.0;
     for (int q = 0; q < n; ++q) residues += static_cast<double>(rows.row[q].gmax);
     const double bytes = 4.0 * static_cast<double>(d) * vectors;
     if (groups != 1 || d < 1'200'000 || bytes > (vectors > 4 ? 3.4e8 : 4.8e8)) return false;
+    if (workers_of_sums > 0) {
+        if (workers_of_sums > 3 && residues < 200e3) return false;
+    } else if (vectors > 4 && residues < (vectors > 5 && n >= 5 ? 150e3 : 50e3)) {
+        return false;
+    }
     return n * static_cast<double>(d) >= 25.0 * residues;
 }
-// A visit of theirs with the chip full, and the rate at which the cache is read
-constexpr double kVisitNsVectors = 650.0;
+// The rate at which the cache is read
 constexpr double kCachedBytesPerNs = 6400.0;
 
 // In runs of 16 pairs cost a turn through LDS for every coordinate of a walker, with two sums half of it for nothing, and
@@ -1485,7 +1497,7 @@ int launch_visits(const cs_params* p, const VisitWorkers& a, const uint32_t* js,
     const double stream_ns = 4.0 * static_cast<double>(a.d) * a.nw * nrows / kStreamBytesPerNs;
     if constexpr (WL > 1) {
         if (vectors_pay(rows, nrows, a.d, a.nw, groups)) {
-            choose_pieces(rows, nrows, requests8, kVisitNsVectors, stream_ns * kStreamBytesPerNs / kCachedBytesPerNs);
+            choose_pieces(rows, nrows, requests8, kVisitNsOne, stream_ns * kStreamBytesPerNs / kCachedBytesPerNs);
             return launch_vectors<WL, false>(rows, a, nrows, ncell, stream);
         }
     }
@@ -1606,7 +1618,7 @@ int launch_visits_anyc(const cs_params* p, const VisitWorkersOf<1>& a, const uin
         // 8.5 M, 8 workers 153 / 144)
         const bool wide = a.nw > 5 && a.d < 64 * static_cast<int64_t>(a.c);
         if (p->r <= kAnycRowsPerLaunch && !wide && vectors_pay(rows, n, a.d, a.nw, 1)) {
-            choose_pieces(rows, n, requests, kVisitNsVectors, stream_ns * kStreamBytesPerNs / kCachedBytesPerNs);
+            choose_pieces(rows, n, requests, kVisitNsOne, stream_ns * kStreamBytesPerNs / kCachedBytesPerNs);
             return launch_vectors<WL, false>(rows, a, n, 2 * omega, stream);
         }
     }
@@ -1869,7 +1881,7 @@ bool lists_hold(const cs_params* p) {
 // The rows of one launch: pieces and run length are chosen, their places in the workspace taken, and, with
 // `run`, the launch is made.
 template <int WL>
-int partial_rows(VisitRows& rows, VisitWorkers& a, int n, int groups, SumsPlan& plan, hipStream_t stream) {
+int partial_rows(VisitRows& rows, VisitWorkers& a, int n, int workers, int groups, SumsPlan& plan, hipStream_t stream) {
     double writes[kRowsPerLaunch];
     uint32_t most = 2;
     for (int q = 0; q < n; ++q) {
@@ -1881,9 +1893,9 @@ int partial_rows(VisitRows& rows, VisitWorkers& a, int n, int groups, SumsPlan& 
     }
     const double stream_ns = 4.0 * static_cast<double>(a.d) * WL * n / kStreamBytesPerNs * groups;
     int log_run = 0;                                   // (a wavefront per vector: the sums lie in the order of the residues)
-    const bool vectors = WL == 1 || vectors_pay(rows, n, a.d, WL, groups);
+    const bool vectors = WL == 1 || vectors_pay(rows, n, a.d, WL, groups, workers);
     if (WL == 1) choose_pieces(rows, n, writes, kVisitNsOne, stream_ns);
-    else if (vectors) choose_pieces(rows, n, writes, kVisitNsVectors, stream_ns * kStreamBytesPerNs / kCachedBytesPerNs);
+    else if (vectors) choose_pieces(rows, n, writes, kVisitNsOne, stream_ns * kStreamBytesPerNs / kCachedBytesPerNs);
     else log_run = choose_run8<WL>(rows, n, writes, writes, a.d, stream_ns, groups) ? 3 : 4;
     const uint64_t span = vectors ? 64 * kOneRun : 64u / WL << log_run;
     for (int q = 0; q < n; ++q) {
@@ -1907,7 +1919,7 @@ int partial_rows(VisitRows& rows, VisitWorkers& a, int n, int groups, SumsPlan& 
 }
 
 template <int WL>
-int partial_group(const cs_params* p, VisitWorkers& a, int groups, SumsPlan& plan, hipStream_t stream) {
+int partial_group(const cs_params* p, VisitWorkers& a, int workers, int groups, SumsPlan& plan, hipStream_t stream) {
     uint32_t order[CS_MAX_R];
     for (uint32_t j = 0; j < p->r; ++j) {              // the longest lists first
         int at = static_cast<int>(j);
@@ -1918,7 +1930,7 @@ int partial_group(const cs_params* p, VisitWorkers& a, int groups, SumsPlan& pla
         const int n = p->r - q0 < kRowsPerLaunch ? static_cast<int>(p->r - q0) : kRowsPerLaunch;
         VisitRows rows{};
         for (int q = 0; q < n; ++q) fill_visit_args(p, order[q0 + q], rows.row[q]);
-        const int rc = partial_rows<WL>(rows, a, n, groups, plan, stream);
+        const int rc = partial_rows<WL>(rows, a, n, workers, groups, plan, stream);
         if (rc != CS_OK) return rc;
     }
     return CS_OK;
@@ -1945,7 +1957,7 @@ int sums_groups(const cs_params* p, int W, int64_t d) {
 }
 
 // g_w null: the plan only
-int launch_accumulate_sums(const cs_params* p, float* sums, uint64_t sums_floats, int lanes, int groups, int nw,
+int launch_accumulate_sums(const cs_params* p, float* sums, uint64_t sums_floats, int workers, int groups, int nw,
                            const float* const* g_w, int64_t d, float scale, SumsPlan& plan, hipStream_t stream) {
     plan = SumsPlan{};
     VisitWorkers a{};
@@ -1956,11 +1968,11 @@ int launch_accumulate_sums(const cs_params* p, float* sums, uint64_t sums_floats
     a.c = p->c;
     a.nw = g_w ? nw : 0;
     a.scale = scale;
-    switch (lanes) {
-        case 1: return partial_group<1>(p, a, groups, plan, stream);
-        case 2: return partial_group<2>(p, a, groups, plan, stream);
-        case 4: return partial_group<4>(p, a, groups, plan, stream);
-        default: return partial_group<8>(p, a, groups, plan, stream);
+    switch (sums_lanes(workers)) {
+        case 1: return partial_group<1>(p, a, workers, groups, plan, stream);
+        case 2: return partial_group<2>(p, a, workers, groups, plan, stream);
+        case 4: return partial_group<4>(p, a, workers, groups, plan, stream);
+        default: return partial_group<8>(p, a, workers, groups, plan, stream);
     }
 }
 
