@@ -185,31 +185,48 @@ __device__ __forceinline__ uint64_t block_exclusive_sum(uint64_t v, uint64_t* ld
     return read_lane(sums - mine, wave) + inc - v;
 }
 
-// The bin of a histogram (PER consecutive bins per thread, cnt[] of mine) that holds the k_rem-th
-// entry counted from the top; *rem = how many of that bin's entries are wanted.  All threads of the
-// workgroup get the answer through `found`.
-template <int WAVES, int PER>
-__device__ __forceinline__ void find_bin(const uint64_t (&cnt)[PER], uint64_t k_rem, uint64_t* lds,
-                                         uint64_t* found, uint32_t* bin, uint64_t* rem) {
+// The bin of a histogram (PER consecutive bins per thread, cnt[] of mine) that holds the k_rem-th entry counted from the top; *rem =
+// how many of that bin's entries are wanted, *all: it has no more than those.  All threads of the workgroup get the answer
+// through `found`, and wait twice: `sums` (a word per wavefront) and `found` are for nothing else before and after.
+template <int WAVES, int PER, typename COUNT>
+__device__ __forceinline__ void find_bin_once(const COUNT (&cnt)[PER], uint64_t k_rem, uint64_t* sums, uint64_t* found,
+                                              uint32_t* bin, uint64_t* rem, bool* all) {
+    static_assert(WAVES <= 16, "the wavefronts' sums are one row of lanes");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     uint64_t mine = 0;
 #pragma unroll
     for (int q = 0; q < PER; ++q) mine += cnt[q];
-    uint64_t all;
-    const uint64_t below = block_exclusive_sum<WAVES>(mine, lds, &all);
-    uint64_t acc = all - below - mine;             // entries in bins above my segment
+    uint64_t inc = row_inclusive_sum(mine);
+    inc = add_from_lane<0x142, 0xa>(inc);
+    inc = add_from_lane<0x143, 0xc>(inc);
+    if (lane == 63) sums[wave] = inc;
+    __syncthreads();
+    const uint64_t of_wave = lane < WAVES ? sums[lane] : 0;
+    const uint64_t upto = row_inclusive_sum(of_wave);
+    uint64_t acc = read_lane(upto, WAVES - 1) - (read_lane(upto - of_wave, wave) + inc);   // entries in bins above mine
     if (acc < k_rem && k_rem <= acc + mine) {      // true for exactly one thread
 #pragma unroll
         for (int q = PER - 1; q >= 0; --q) {
             if (acc < k_rem && k_rem <= acc + cnt[q]) {
                 found[0] = static_cast<uint64_t>(threadIdx.x) * PER + q;
-                found[1] = k_rem - acc;
+                found[1] = (k_rem - acc) << 1 | (k_rem - acc == cnt[q] ? 1u : 0u);
             }
             acc += cnt[q];
         }
     }
     __syncthreads();
     *bin = static_cast<uint32_t>(found[0]);
-    *rem = found[1];
+    *rem = found[1] >> 1;
+    *all = (found[1] & 1u) != 0;
+}
+
+// ... in buffers that the next step may use.
+template <int WAVES, int PER, typename COUNT>
+__device__ __forceinline__ void find_bin(const COUNT (&cnt)[PER], uint64_t k_rem, uint64_t* sums, uint64_t* found, uint32_t* bin,
+                                         uint64_t* rem) {
+    bool all;
+    find_bin_once<WAVES>(cnt, k_rem, sums, found, bin, rem, &all);
     __syncthreads();
 }
 
@@ -309,7 +326,7 @@ k_topk_compact(const float* __restrict__ est, int64_t d, int64_t chunk, TopkWs* 
         uint64_t cnt[per], rem;
 #pragma unroll
         for (int q = 0; q < per; ++q) cnt[q] = hist0[threadIdx.x * per + q];
-        find_bin<kScanWaves, per>(cnt, k, scan, found, &bin0, &rem);
+        find_bin<kScanWaves>(cnt, k, scan, found, &bin0, &rem);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             ws->prefix = bin0;
             ws->k_rem = rem;
@@ -422,40 +439,6 @@ struct SmallLds {
 };
 static_assert(sizeof(SmallLds) <= 160 * 1024, "the LDS of a CU");
 
-// find_bin in buffers that nothing else uses, so that it waits twice instead of four times; *all: the bin has no more
-// entries than are wanted.
-template <int PER>
-__device__ __forceinline__ void find_bin_once(const uint32_t (&cnt)[PER], uint64_t k_rem, uint64_t (&sums)[kSelWaves],
-                                              uint64_t (&found)[2], uint32_t* bin, uint64_t* rem, bool* all) {
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-    uint64_t mine = 0;
-#pragma unroll
-    for (int q = 0; q < PER; ++q) mine += cnt[q];
-    uint64_t inc = row_inclusive_sum(mine);
-    inc = add_from_lane<0x142, 0xa>(inc);
-    inc = add_from_lane<0x143, 0xc>(inc);
-    if (lane == 63) sums[wave] = inc;
-    __syncthreads();
-    const uint64_t of_wave = lane < kSelWaves ? sums[lane] : 0;
-    const uint64_t upto = row_inclusive_sum(of_wave);
-    uint64_t acc = read_lane(upto, kSelWaves - 1) - (read_lane(upto - of_wave, wave) + inc);   // entries in bins above mine
-    if (acc < k_rem && k_rem <= acc + mine) {      // true for exactly one thread
-#pragma unroll
-        for (int q = PER - 1; q >= 0; --q) {
-            if (acc < k_rem && k_rem <= acc + cnt[q]) {
-                found[0] = static_cast<uint64_t>(threadIdx.x) * PER + q;
-                found[1] = (k_rem - acc) << 1 | (k_rem - acc == cnt[q] ? 1u : 0u);
-            }
-            acc += cnt[q];
-        }
-    }
-    __syncthreads();
-    *bin = static_cast<uint32_t>(found[0]);
-    *rem = found[1] >> 1;
-    *all = (found[1] & 1u) != 0;
-}
-
 // Selection among n <= kSmall items by one workgroup of kSelBlock threads that keeps their keys in
 // LDS: the remaining histograms in LDS, then one ballot per 64 items and kind (greater than
 // theta, equal to it) from which the number of flags before any item can be read, so that an
@@ -511,7 +494,7 @@ __device__ __forceinline__ uint32_t select_in_workgroup(SmallLds& s, const float
         __syncthreads();
         const uint32_t cnt[2] = {s.hist[2 * tid], s.hist[2 * tid + 1]};
         s.hist[2 * tid] = s.hist[2 * tid + 1] = 0;
-        find_bin_once(cnt, k_rem, s.bin_sums[0], s.bin[0], &bin0, &k_rem, &all_of_bin);
+        find_bin_once<kSelWaves>(cnt, k_rem, s.bin_sums[0], s.bin[0], &bin0, &k_rem, &all_of_bin);
     }
     uint32_t theta = bin0;
     int shift = 20;                                 // of theta
@@ -529,7 +512,7 @@ __device__ __forceinline__ uint32_t select_in_workgroup(SmallLds& s, const float
         const uint32_t cnt[1] = {hist[tid]};
         if (DIRECT) hist[tid] = 0;
         uint32_t bin;
-        find_bin_once(cnt, k_rem, s.bin_sums[pass], s.bin[pass], &bin, &k_rem, &all_of_bin);
+        find_bin_once<kSelWaves>(cnt, k_rem, s.bin_sums[pass], s.bin[pass], &bin, &k_rem, &all_of_bin);
         theta = (theta << 10) | bin;
     }
     if (shift > 0) {
@@ -736,11 +719,11 @@ k_topk_finish(const float* __restrict__ est, int64_t d, TopkWs* ws, const uint64
             uint32_t bin;
             if (known == 0) {
                 const uint64_t cnt[2] = {hist0[2 * tid], hist0[2 * tid + 1]};
-                find_bin<kSelWaves, 2>(cnt, k_rem, s.scan, s.found, &bin, &k_rem);
+                find_bin<kSelWaves>(cnt, k_rem, s.scan, s.found, &bin, &k_rem);
                 prefix = bin;
             } else {
                 const uint64_t cnt[1] = {load_shared(&ws->hist[known][tid])};
-                find_bin<kSelWaves, 1>(cnt, k_rem, s.scan, s.found, &bin, &k_rem);
+                find_bin<kSelWaves>(cnt, k_rem, s.scan, s.found, &bin, &k_rem);
                 prefix = (prefix << 10) | bin;
             }
         }
